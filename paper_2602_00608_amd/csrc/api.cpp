@@ -29,8 +29,9 @@ int hip_fail(hipError_t e, const char* what) {
 
 int launch_conv(const ConvArgs& a, hipStream_t s) {
   if (conv_taps_supported(a)) return launch_conv_taps(a, s);
+  if (conv_ksplit_supported(a)) return launch_conv_ksplit(a, s);
   if (conv_mfma_supported(a)) return launch_conv_mfma(a, s);
-  WMDEC_REQUIRE(!a.x2, WMDEC_ERR_UNSUPPORTED, "conv: only the matrix-core kernel folds a shortcut into the contraction");
+  WMDEC_REQUIRE(!a.x2, WMDEC_ERR_UNSUPPORTED, "conv: only the matrix-core kernels fold a shortcut into the contraction");
   if (conv_small_cin_supported(a)) return launch_conv_small_cin(a, s);
   return launch_conv_direct(a, s);
 }
@@ -38,12 +39,14 @@ int launch_conv(const ConvArgs& a, hipStream_t s) {
 // Triples per (sample, group) that the kernel launch_conv picks for this shape emits with stats_ws set; 0: it emits none.
 static int conv_stats_slots(const ConvArgs& a) {
   if (conv_taps_supported(a)) return 0;
+  if (conv_ksplit_supported(a)) return conv_ksplit_stats_slots(a);
   if (conv_mfma_supported(a)) return conv_mfma_stats_slots(a);
   return conv_small_cin_supported(a) ? conv_small_cin_stats_slots(a) : 0;
 }
 
 const char* conv_kernel_label(const ConvArgs& a) {
   if (conv_taps_supported(a)) return conv_taps_label(a);
+  if (conv_ksplit_supported(a)) return conv_ksplit_label(a);
   if (!conv_mfma_supported(a)) return conv_small_cin_supported(a) ? "conv_small_cin_kernel" : "conv_direct_kernel";
   return conv_mfma_label(a);
 }
@@ -138,6 +141,7 @@ static ConvArgs step_shape_args(const wmdec_decoder& d, const Step& st, int batc
   a.y_dtype = st.dst == BUF_OUT ? (int)WMDEC_F32 : a.op_dtype; a.y_nchw = st.y_nchw;
   a.n = batch; a.h = st.h; a.w = st.w; a.cin = st.cin; a.cout = st.cout; a.ksize = st.ksize; a.upsample = st.upsample;
   a.stats_groups = d.cfg.groups;
+  a.cin2 = st.sc_cin;
   return a;
 }
 
@@ -281,7 +285,8 @@ static void fuse_stats_into_producers(wmdec_decoder& d) {
       d.launches -= 1;
       continue;
     }
-    if (!conv_mfma_supported(step_shape_args(d, d.steps[j], 1))) continue;   // only that kernel merges by row
+    const ConvArgs prod = step_shape_args(d, d.steps[j], 1);
+    if (conv_ksplit_supported(prod) || !conv_mfma_supported(prod)) continue;   // only that kernel merges by row
     int rows = 0, ctiles = 0, per_row = 0;
     conv_mfma_row_extents(step_shape_args(d, d.steps[j], 1), &rows, &ctiles, &per_row);
     if (rows > 64) continue;   // keeps the consumer's merge short
@@ -555,18 +560,19 @@ int wmdec_gn_silu_conv3x3_shortcut(const void* x, int act_dtype, const float* me
   a.groups = mean ? groups : 1; a.silu = (mean && apply_silu) ? 1 : 0;
   a.wt = w_packed; a.op_dtype = act_dtype; a.bias = bias; a.res_dtype = act_dtype;
   a.y = y; a.y_dtype = y_dtype; a.n = n; a.h = h; a.w = w; a.cin = cin; a.cout = cout; a.ksize = 3;
-  if (conv_mfma_supported(a) && cin2 % 32 == 0) {   // one launch: the shortcut is part of the contraction
-    a.x2 = x2; a.cin2 = cin2; a.w2 = w2_packed; a.bias2 = bias2;
+  a.cin2 = cin2;
+  if (conv_ksplit_supported(a) || (conv_mfma_supported(a) && cin2 % 32 == 0)) {   // one launch: the shortcut is part of the contraction
+    a.x2 = x2; a.w2 = w2_packed; a.bias2 = bias2;
     return launch_conv(a, (hipStream_t)stream);
   }
-  // other shapes and fp32: the shortcut is written to y first, and the convolution adds it from there (every
+  // other shapes: the shortcut is written to y first, and the convolution adds it from there (every
   // element is read and then written by the same thread)
   ConvArgs sc;
   sc.x = x2; sc.x_dtype = act_dtype; sc.wt = w2_packed; sc.op_dtype = act_dtype; sc.bias = bias2; sc.res_dtype = act_dtype;
   sc.y = y; sc.y_dtype = y_dtype; sc.n = n; sc.h = h; sc.w = w; sc.cin = cin2; sc.cout = cout; sc.ksize = 1;
   const int r1 = launch_conv_direct(sc, (hipStream_t)stream);
   if (r1 != WMDEC_OK) return r1;
-  a.res = y; a.res_dtype = y_dtype;
+  a.res = y; a.res_dtype = y_dtype; a.cin2 = 0;
   return launch_conv_direct(a, (hipStream_t)stream);
 }
 
@@ -599,7 +605,13 @@ int wmdec_gn_silu_conv3x3_stats(const void* x, int act_dtype, const float* mean,
   a.x = x; a.mean = mean; a.rstd = mean ? rstd : nullptr; a.gamma = gamma; a.beta = beta;
   a.groups = mean ? groups : 1; a.silu = (mean && apply_silu) ? 1 : 0;
   a.wt = w_packed; a.bias = bias; a.res = residual; a.y = y;
-  const int slots = conv_stats_slots(a);
+  int slots = conv_stats_slots(a);
+  if (workspace_bytes < (size_t)n * out_groups * slots * 3 * sizeof(float)) {   // enough for the wide tiles' fewer triples?
+    ConvArgs wide = a;
+    wide.wide_tiles = 1;
+    const int fewer = conv_stats_slots(wide);
+    if (fewer > 0 && workspace_bytes >= (size_t)n * out_groups * fewer * 3 * sizeof(float)) { a.wide_tiles = 1; slots = fewer; }
+  }
   WMDEC_REQUIRE(slots > 0, WMDEC_ERR_UNSUPPORTED,
                 "%s: this shape / type takes no kernel that emits moments (16-bit types and either cin %% 32 == 0, cout %% 64 == 0, "
                 "channels per output group a power of two <= 32, or cin <= 8 without normalisation and residual, channels per "

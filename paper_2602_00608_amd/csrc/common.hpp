@@ -92,6 +92,7 @@ struct ConvArgs {
   const void* w2 = nullptr;      //   ResBlock folded into the contraction; x2 [n,h,w,cin2] of op_dtype, w2 packed with k = 1
   const float* bias2 = nullptr;
   int cin2 = 0;
+  int wide_tiles = 0;            // 1: not the kernel that splits the contraction over wavefronts (its statistics take more slots)
   void* stats_ws = nullptr;      // non-null: also emit GroupNorm moments of y, [n][stats_groups][slots] triples
   int stats_groups = 0;
   // matrix-core kernel only: statistics handed from producer to consumer without a merge launch
@@ -118,6 +119,11 @@ bool conv_mfma_uses_phase(const ConvArgs& a);
 int conv_mfma_stats_slots(const ConvArgs& a);
 void conv_mfma_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row);
 const char* conv_mfma_label(const ConvArgs& a);   // instantiation name, valid until the thread's next call
+// kernels_conv_ksplit.hip: 3x3 convolution of small images, and of fp32, with the contraction split over wavefronts
+bool conv_ksplit_supported(const ConvArgs& a);
+int launch_conv_ksplit(const ConvArgs& a, hipStream_t s);
+int conv_ksplit_stats_slots(const ConvArgs& a);   // moment triples per (sample, group) it would write; 0: it cannot
+const char* conv_ksplit_label(const ConvArgs& a);
 // kernels_conv_taps.hip: 3x3 convolution with at most three output channels into a planar fp32 tensor (the frame),
 // evaluated as a 1x1 contraction onto (tap, channel) pairs followed by nine shifted adds
 bool conv_taps_supported(const ConvArgs& a);

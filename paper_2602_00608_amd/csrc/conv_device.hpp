@@ -1,0 +1,133 @@
+// Pieces shared by the matrix-core convolution kernels: launch parameters, operand loads, the activation on the load
+// path and the row hand-over of the output statistics.
+#pragma once
+#include <type_traits>
+#include <utility>
+
+#include "mfma.hpp"
+#include "moments.hpp"
+#include "pack_layout.hpp"
+
+namespace wmdec {
+
+struct MfmaParams {
+  const void* x; const float* mean; const float* rstd; const float* gamma; const float* beta;
+  const void* w; const float* bias; const void* res; void* y;
+  int silu, groups, norm;
+  int n, h, w_out, cin, cout, upsample;
+  int tiles_x, tiles_y, ntiles, total;
+  int cin_blocks, cout_blocks;   // packed-layout extents: ceil(cin/16), ceil(cout/32)
+  int w_bytes;                   // size of the packed weights the kernel may read
+  int y_nchw;                    // 1: y is planar [n][cout][h][w] (the frame), else NHWC
+  Moments* stats;                // non-null: moments of y per (sample, group, slot); slot = spatial tile * WM + wave row
+  int stats_cpg, stats_groups, stats_slots;
+  // Statistics hand-over without a merge launch.  rows_out: the last workgroup of every (sample, tile row, channel
+  // tile) merges that row's triples into one triple per group, [n][stats_groups][tiles_y]; tickets: one counter per
+  // (sample, tile row, channel tile), zero before the launch and zero again after it.  rows_in: the statistics of x
+  // arrive as such row triples, [n][groups][rows_in_count], and are merged while the scale/shift table is built.
+  Moments* rows_out; unsigned* tickets;
+  const Moments* rows_in; int rows_in_count; float eps;
+  // 1x1 shortcut folded into the contraction (3x3 only): y += W2 * x2 + bias2, x2 [n,h,w,cin2] taken as stored
+  const void* x2; const void* w2; const float* bias2;
+  int cin2, w2_bytes;
+};
+
+template <typename T> __device__ __forceinline__ void unpack8(const u32x4& v, float* f) {
+  f[0] = unpack_lo<T>(v.x); f[1] = unpack_hi<T>(v.x); f[2] = unpack_lo<T>(v.y); f[3] = unpack_hi<T>(v.y);
+  f[4] = unpack_lo<T>(v.z); f[5] = unpack_hi<T>(v.z); f[6] = unpack_lo<T>(v.w); f[7] = unpack_hi<T>(v.w);
+}
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>)
+template <int N, typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) { static_for_impl<N>(f, std::make_integer_sequence<int, N>{}); }
+
+// silu(t) from u = -log2(e) * t (see the scale/shift table)
+__device__ __forceinline__ float silu_from_scaled(float u) {
+  constexpr float k = -1.4426950408889634f;
+  return u * __builtin_amdgcn_rcpf(fmaf(__builtin_amdgcn_exp2f(u), k, k));
+}
+
+// One weight fragment (1 KiB, a lane's 16 bytes at lane16 = 16 * lane) at byte offset `off` of the packed weights.
+// A buffer load takes the wave-uniform offset in a scalar register, so the address costs no vector-ALU work
+// (a global load would add the 64-bit base per fragment), and offsets past the blob read zeros instead of faulting.
+__device__ __forceinline__ u32x4 load_fragment(__amdgpu_buffer_rsrc_t rsrc, int lane16, int off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane16, off, 0);
+}
+
+// Word (two channels) of a staged vector with the table entries ab = (a0, b0, a1, b1); ACT: 0 as it is, 1 scale/shift,
+// 2 scale/shift + SiLU.  PIN: the last fp32 operation and the conversion stay apart.  The compiler otherwise folds them into
+// one (v_fma_mixlo_f16, one rounding instead of two) at some places and not at others, and the bits of a value would
+// depend on the instantiation that staged it.
+template <typename T, int ACT, bool PIN = false> __device__ __forceinline__ uint32_t activate_word(uint32_t wv, const f32x4& ab) {
+  if constexpr (ACT > 0) {
+    float f0 = fmaf(unpack_lo<T>(wv), ab[0], ab[1]), f1 = fmaf(unpack_hi<T>(wv), ab[2], ab[3]);
+    if constexpr (ACT == 2) { f0 = silu_from_scaled(f0); f1 = silu_from_scaled(f1); }
+    if constexpr (PIN) asm("" : "+v"(f0), "+v"(f1));
+    wv = pack2<T>(f0, f1);
+  }
+  return wv;
+}
+
+// Row hand-over: the workgroup that finishes a (sample, tile row, channel tile) last merges that row's triples.  Same
+// protocol as the single-launch statistics kernel: the triples were written with device-scope stores, every wavefront
+// waits for its stores, the workgroup takes a ticket (a wrapping counter that returns to zero by itself), and only the
+// last one reads, with device-scope loads, in a fixed order.  per_tile: triples of one group a workgroup leaves.
+template <int NT>
+__device__ __forceinline__ void hand_over_row(const MfmaParams& p, int n, int tile_y, int nt, int co0, int tn, int per_tile,
+                                              int tid, int lane) {
+  __shared__ unsigned s_last;
+  wait_stores();
+  __syncthreads();
+  if (tid == 0) s_last = atomicInc(p.tickets + ((size_t)n * p.tiles_y + tile_y) * p.ntiles + nt, p.tiles_x - 1) == (unsigned)(p.tiles_x - 1);
+  __syncthreads();
+  if (!s_last) return;
+  const int per_row = p.tiles_x * per_tile;                  // triples of one group in this tile row
+  const int g0 = co0 / p.stats_cpg, gcount = min(tn, p.cout - co0) / p.stats_cpg;
+  const int sub = tid & 7;
+  for (int gi = tid >> 3; gi < gcount; gi += NT / 8) {
+    const Moments* src = p.stats + ((size_t)n * p.stats_groups + g0 + gi) * p.stats_slots + (size_t)tile_y * per_row;
+    Moments m{0.f, 0.f, 0.f};
+    for (int e0 = sub; e0 < per_row; e0 += 64) {     // eight loads in flight per lane
+      Moments t[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int e = e0 + 8 * k;
+        t[k] = load_device(src + min(e, per_row - 1));
+        if (e >= per_row) t[k].n = 0.f;
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) m = merge(m, t[k]);
+    }
+    m = merge_to_first(m, lane, 8);
+    if (sub == 0) p.rows_out[((size_t)n * p.stats_groups + g0 + gi) * p.tiles_y + tile_y] = m;
+  }
+}
+
+// Launch parameters of a th x tw tile (on an h_t x w_t grid) with tn output channels and slots_per_tile moment triples;
+// the weights and the shortcut are the caller's.
+inline MfmaParams conv_params(const ConvArgs& a, int th, int tw, int tn, int slots_per_tile, int h_t, int w_t) {
+  MfmaParams p;
+  p.x = a.x; p.mean = a.mean; p.rstd = a.rstd; p.gamma = a.gamma; p.beta = a.beta;
+  p.w = nullptr; p.w_bytes = 0; p.bias = a.bias; p.res = a.res; p.y = a.y;
+  p.silu = a.silu; p.groups = a.groups; p.norm = a.mean != nullptr || a.rows_in != nullptr;
+  p.n = a.n; p.h = a.h; p.w_out = a.w; p.cin = a.cin; p.cout = a.cout; p.upsample = a.upsample;
+  p.tiles_x = (w_t + tw - 1) / tw; p.tiles_y = (h_t + th - 1) / th; p.ntiles = (a.cout + tn - 1) / tn;
+  p.total = p.tiles_x * p.tiles_y * p.ntiles * a.n;
+  p.cin_blocks = packed_cin_blocks(a.cin); p.cout_blocks = packed_cout_blocks(a.cout); p.y_nchw = a.y_nchw;
+  p.stats = (Moments*)a.stats_ws; p.stats_groups = a.stats_groups; p.stats_cpg = a.stats_groups > 0 ? a.cout / a.stats_groups : 1;
+  p.stats_slots = p.tiles_x * p.tiles_y * slots_per_tile;
+  p.rows_out = (Moments*)a.rows_out; p.tickets = (unsigned*)a.tickets;
+  p.rows_in = (const Moments*)a.rows_in; p.rows_in_count = a.rows_in_count; p.eps = a.eps;
+  p.x2 = nullptr; p.w2 = nullptr; p.bias2 = nullptr; p.cin2 = 0; p.w2_bytes = 0;
+  return p;
+}
+// the statistics hand-over a launch is asked for is one its kernel can serve
+inline int check_hand_over(const MfmaParams& p) {
+  WMDEC_REQUIRE(!p.rows_out || (p.stats && p.tickets), WMDEC_ERR_INVALID_ARG, "convolution: row moments need the triple scratch and the ticket counters");
+  WMDEC_REQUIRE(!p.rows_in || (p.rows_in_count >= 1 && p.rows_in_count <= 128), WMDEC_ERR_UNSUPPORTED, "convolution: at most 128 triples per group can be merged in the prologue");
+  return WMDEC_OK;
+}
+
+}  // namespace wmdec

@@ -23,44 +23,11 @@
 #include <stdio.h>
 
 #include <mutex>
-#include <type_traits>
-#include <utility>
 
-#include "mfma.hpp"
-#include "moments.hpp"
-#include "pack_layout.hpp"
+#include "conv_device.hpp"
 
 namespace wmdec {
 namespace {
-
-struct MfmaParams {
-  const void* x; const float* mean; const float* rstd; const float* gamma; const float* beta;
-  const void* w; const float* bias; const void* res; void* y;
-  int silu, groups, norm;
-  int n, h, w_out, cin, cout, upsample;
-  int tiles_x, tiles_y, ntiles, total;
-  int cin_blocks, cout_blocks;   // packed-layout extents: ceil(cin/16), ceil(cout/32)
-  int w_bytes;                   // size of the packed weights the kernel may read
-  int y_nchw;                    // 1: y is planar [n][cout][h][w] (the frame), else NHWC
-  Moments* stats;                // non-null: moments of y per (sample, group, slot); slot = spatial tile * WM + wave row
-  int stats_cpg, stats_groups, stats_slots;
-  // Statistics hand-over without a merge launch.  rows_out: the last workgroup of every (sample, tile row, channel
-  // tile) merges that row's triples into one triple per group, [n][stats_groups][tiles_y]; tickets: one counter per
-  // (sample, tile row, channel tile), zero before the launch and zero again after it.  rows_in: the statistics of x
-  // arrive as such row triples, [n][groups][rows_in_count], and are merged while the scale/shift table is built.
-  Moments* rows_out; unsigned* tickets;
-  const Moments* rows_in; int rows_in_count; float eps;
-  // 1x1 shortcut folded into the contraction (3x3 only): y += W2 * x2 + bias2, x2 [n,h,w,cin2] taken as stored
-  const void* x2; const void* w2; const float* bias2;
-  int cin2, w2_bytes;
-};
-
-template <typename T> __device__ __forceinline__ void unpack8(const u32x4& v, float* f) {
-  f[0] = unpack_lo<T>(v.x); f[1] = unpack_hi<T>(v.x); f[2] = unpack_lo<T>(v.y); f[3] = unpack_hi<T>(v.y);
-  f[4] = unpack_lo<T>(v.z); f[5] = unpack_hi<T>(v.z); f[6] = unpack_lo<T>(v.w); f[7] = unpack_hi<T>(v.w);
-}
-
-
 
 // Epilogue of one wavefront: its MI x NI accumulator tiles (32 pixels x 32 channels each, a lane
 // holding one channel column) go through a wavefront-private LDS patch, one 32-pixel M tile at a
@@ -217,12 +184,6 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
   }
 }
 
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>)
-template <int N, typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) { static_for_impl<N>(f, std::make_integer_sequence<int, N>{}); }
-
 // Ring length of the weight-fragment prefetch: it must divide the k-steps of a chunk so that the ring
 // position is the same at every chunk start.
 // It is as long as the register budget of the tile allows (`room`: accumulator tiles per wavefront): the fragments
@@ -232,19 +193,6 @@ constexpr int prefetch_ring(int steps, int room) {
   if (room > 4 && steps % 3 == 0) return 3;
   if (steps % 6 == 0) return 6;
   return steps % 3 == 0 ? 3 : (steps % 4 == 0 ? 4 : 2);
-}
-
-// silu(t) from u = -log2(e) * t (see the scale/shift table)
-__device__ __forceinline__ float silu_from_scaled(float u) {
-  constexpr float k = -1.4426950408889634f;
-  return u * __builtin_amdgcn_rcpf(fmaf(__builtin_amdgcn_exp2f(u), k, k));
-}
-
-// One weight fragment (1 KiB, a lane's 16 bytes at lane16 = 16 * lane) at byte offset `off` of the packed weights.
-// A buffer load takes the wave-uniform offset in a scalar register, so the address costs no vector-ALU work
-// (a global load would add the 64-bit base per fragment), and offsets past the blob read zeros instead of faulting.
-__device__ __forceinline__ u32x4 load_fragment(__amdgpu_buffer_rsrc_t rsrc, int lane16, int off) {
-  return __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane16, off, 0);
 }
 
 // MFMA work of one staged chunk: STEPS = taps * KC/16 k-steps, each MI x NI 32x32x16 MFMAs.
@@ -464,14 +412,7 @@ void conv_mfma_kernel(MfmaParams p) {
     for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(xin + (unsigned)(src_off[i] + cb));
   };
   // word (two channels) of a staged vector: scale/shift (+ SiLU) with the table entries ab = (a0, b0, a1, b1)
-  auto activate_with = [&](uint32_t wv, const f32x4& ab) -> uint32_t {
-    if constexpr (ACT > 0) {
-      float f0 = fmaf(unpack_lo<T>(wv), ab[0], ab[1]), f1 = fmaf(unpack_hi<T>(wv), ab[2], ab[3]);
-      if constexpr (ACT == 2) { f0 = silu_from_scaled(f0); f1 = silu_from_scaled(f1); }
-      wv = pack2<T>(f0, f1);
-    }
-    return wv;
-  };
+  auto activate_with = [&](uint32_t wv, const f32x4& ab) -> uint32_t { return wmdec::activate_word<T, ACT>(wv, ab); };
   // table entries of word `part` of this thread's channel octet in the chunk that starts at channel c0
   auto table_entry = [&](int part, int c0) -> f32x4 {
     if constexpr (ACT > 0) return *reinterpret_cast<const f32x4*>(s_ab + c0 + cvec * 8 + 2 * part);
@@ -663,40 +604,7 @@ void conv_mfma_kernel(MfmaParams p) {
                                                                p.bias2, rin, yout, p.h, p.w_out, p.cout, p.y_nchw != 0, st, p.stats_cpg, p.stats_slots,
                                                                PH ? 2 : 1, PH ? wave >> 1 : 0, PH ? wave & 1 : 0);
 
-  // ---- row hand-over: the workgroup that finishes a (sample, tile row, channel tile) last merges the row's triples.
-  // Same protocol as the single-launch statistics kernel: the triples were written with device-scope stores, every
-  // wavefront waits for its stores, the workgroup takes a ticket (a wrapping counter that returns to zero by itself),
-  // and only the last one reads, with device-scope loads, in a fixed order.
-  if (p.rows_out) {
-    __shared__ unsigned s_last;
-    wait_stores();
-    __syncthreads();
-    const int tile_y = tile / p.tiles_x;
-    if (tid == 0) s_last = atomicInc(p.tickets + ((size_t)n * p.tiles_y + tile_y) * p.ntiles + nt, p.tiles_x - 1) == (unsigned)(p.tiles_x - 1);
-    __syncthreads();
-    if (s_last) {
-      const int per_row = p.tiles_x * WM;                  // triples of one group in this tile row
-      const int g0 = co0 / p.stats_cpg, gcount = min(TN, p.cout - co0) / p.stats_cpg;
-      const int sub = tid & 7;
-      for (int gi = tid >> 3; gi < gcount; gi += NT / 8) {
-        const Moments* src = p.stats + ((size_t)n * p.stats_groups + g0 + gi) * p.stats_slots + (size_t)tile_y * per_row;
-        Moments m{0.f, 0.f, 0.f};
-        for (int e0 = sub; e0 < per_row; e0 += 64) {     // eight loads in flight per lane
-          Moments t[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int e = e0 + 8 * k;
-            t[k] = load_device(src + min(e, per_row - 1));
-            if (e >= per_row) t[k].n = 0.f;
-          }
-#pragma unroll
-          for (int k = 0; k < 8; ++k) m = merge(m, t[k]);
-        }
-        m = merge_to_first(m, lane, 8);
-        if (sub == 0) p.rows_out[((size_t)n * p.stats_groups + g0 + gi) * p.tiles_y + tile_y] = m;
-      }
-    }
-  }
+  if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, co0, TN, WM, tid, lane);
 }
 
 template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, bool PH = false, int RING = 0>
@@ -704,24 +612,12 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
   constexpr int PAD = PH ? 1 : KS / 2;
   constexpr int TN = WN * NI * 32;
   WMDEC_REQUIRE(!PH || (a.wt_phase && a.h % 2 == 0 && a.w % 2 == 0), WMDEC_ERR_INVALID_ARG, "conv_mfma: upsampling convolution without phase weights");
-  MfmaParams p;
-  p.x = a.x; p.mean = a.mean; p.rstd = a.rstd; p.gamma = a.gamma; p.beta = a.beta;
-  p.w = PH ? a.wt_phase : a.wt; p.bias = a.bias; p.res = a.res; p.y = a.y;
-  p.silu = a.silu; p.groups = a.groups; p.norm = a.mean != nullptr;
-  p.n = a.n; p.h = a.h; p.w_out = a.w; p.cin = a.cin; p.cout = a.cout; p.upsample = a.upsample;
-  const int w_t = PH ? a.w / 2 : a.w, h_t = PH ? a.h / 2 : a.h;   // the grid the tiles live on
-  p.tiles_x = (w_t + TW - 1) / TW; p.tiles_y = (h_t + TH - 1) / TH; p.ntiles = (a.cout + TN - 1) / TN;
-  p.total = p.tiles_x * p.tiles_y * p.ntiles * a.n;
-  p.cin_blocks = packed_cin_blocks(a.cin); p.cout_blocks = packed_cout_blocks(a.cout); p.y_nchw = a.y_nchw;
+  // the tiles of a phase-decomposed launch live on the input grid
+  MfmaParams p = conv_params(a, TH, TW, TN, WM, PH ? a.h / 2 : a.h, PH ? a.w / 2 : a.w);
+  const int rc = check_hand_over(p);
+  if (rc != WMDEC_OK) return rc;
+  p.w = PH ? a.wt_phase : a.wt;
   p.w_bytes = (int)(packed_elems(PH ? 16 : KS * KS, a.cout, a.cin) * sizeof(T));
-  p.stats = (Moments*)a.stats_ws; p.stats_groups = a.stats_groups; p.stats_cpg = a.stats_groups > 0 ? a.cout / a.stats_groups : 1;
-  p.stats_slots = p.tiles_x * p.tiles_y * WM;
-  p.rows_out = (Moments*)a.rows_out; p.tickets = (unsigned*)a.tickets;
-  p.rows_in = (const Moments*)a.rows_in; p.rows_in_count = a.rows_in_count; p.eps = a.eps;
-  WMDEC_REQUIRE(!p.rows_out || (p.stats && p.tickets), WMDEC_ERR_INVALID_ARG, "conv_mfma: row moments need the triple scratch and the ticket counters");
-  WMDEC_REQUIRE(!p.rows_in || (p.rows_in_count >= 1 && p.rows_in_count <= 128), WMDEC_ERR_UNSUPPORTED, "conv_mfma: at most 128 triples per group can be merged in the prologue");
-  p.norm = a.mean != nullptr || a.rows_in != nullptr;
-  p.x2 = nullptr; p.w2 = nullptr; p.bias2 = nullptr; p.cin2 = 0; p.w2_bytes = 0;
   if (a.x2) {
     WMDEC_REQUIRE(KS == 3 && !PH && a.w2 && a.cin2 > 0 && a.cin2 % KC == 0 && (long)a.h * a.w * a.cin2 < (1L << 29), WMDEC_ERR_UNSUPPORTED,
                   "conv_mfma: a folded shortcut needs a 3x3 convolution without upsampling and cin2 %% %d == 0", KC);
