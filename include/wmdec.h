@@ -176,14 +176,11 @@ int wmdec_gn_conv1x1(const void* x, int act_dtype, const float* mean, const floa
  *   y[n,oy,ox,co] = bias[co] + sum W[co,ci,ky,kx] * x[n,(oy+ky-1)>>1,(ox+kx-1)>>1,ci]
  * for 0 <= oy+ky-1 < 2*h_in and 0 <= ox+kx-1 < 2*w_in, zero otherwise.
  * x: [n,h_in,w_in,cin]; y: [n,2*h_in,2*w_in,cout].  The upsampled tensor is
- * never materialised.  On the matrix-core path the sum is evaluated per output
- * phase (oy&1, ox&1): the 3x3 taps that read the same input pixel are added
- * once, when the weights are packed, so each output costs a 2x2 convolution
- * (4/9 of the multiplications; same sum, the pre-added weights are rounded to
- * the operand type once).
- * w_packed: from wmdec_pack_upconv_weights (NOT wmdec_pack_conv_weights): the
- * 9-tap pack followed by the 16-tap phase pack, wmdec_upconv_packed_bytes()
- * bytes in total, 16-byte aligned. */
+ * never materialised.  On the matrix-core path the four output phases
+ * (oy&1, ox&1) are formed from nine products per input pixel (one per tap; the
+ * plain sum takes 36), with the weights as given and fp32 sums.
+ * w_packed: from wmdec_pack_upconv_weights (NOT wmdec_pack_conv_weights),
+ * wmdec_upconv_packed_bytes() bytes in total, 16-byte aligned. */
 size_t wmdec_upconv_packed_bytes(int cout, int cin, int op_dtype);
 int wmdec_pack_upconv_weights(const void* src, int src_dtype, int cout, int cin, void* packed,
                               int op_dtype, void* stream);
@@ -360,10 +357,11 @@ int wmdec_latent_extrapolate(const void* z_prev, const void* v_prev, int dtype, 
 
 /* Number of kernel launches one decoder_run enqueues, and the FLOP count of
  * one frame: 2*k*k*cin*cout per output pixel of every convolution plus
- * 4*T*T*c for the attention -- except that an upsampling convolution
- * evaluated per output phase (see wmdec_upsample2x_conv3x3) counts the 2x2
- * taps it executes, 4/9 of the nine-tap figure.  decoder_dense_flops_per_frame
- * is the nine-tap figure throughout: what the unfused graph would execute. */
+ * 4*T*T*c for the attention -- except that an upsampling convolution in f16
+ * is priced at a 2x2 convolution per output, 4/9 of the nine-tap figure (a
+ * price, not a count: see wmdec_upsample2x_conv3x3 for what is executed).
+ * decoder_dense_flops_per_frame is the nine-tap figure throughout: what the
+ * unfused graph would execute. */
 int decoder_num_launches(const wmdec_decoder* dec);
 double decoder_flops_per_frame(const wmdec_decoder* dec);
 double decoder_dense_flops_per_frame(const wmdec_decoder* dec);

@@ -29,6 +29,7 @@ int hip_fail(hipError_t e, const char* what) {
 
 int launch_conv(const ConvArgs& a, hipStream_t s) {
   if (conv_taps_supported(a)) return launch_conv_taps(a, s);
+  if (conv_up_supported(a)) return launch_conv_up(a, s);
   if (conv_ksplit_supported(a)) return launch_conv_ksplit(a, s);
   if (conv_mfma_supported(a)) return launch_conv_mfma(a, s);
   WMDEC_REQUIRE(!a.x2, WMDEC_ERR_UNSUPPORTED, "conv: only the matrix-core kernels fold a shortcut into the contraction");
@@ -39,13 +40,23 @@ int launch_conv(const ConvArgs& a, hipStream_t s) {
 // Triples per (sample, group) that the kernel launch_conv picks for this shape emits with stats_ws set; 0: it emits none.
 static int conv_stats_slots(const ConvArgs& a) {
   if (conv_taps_supported(a)) return 0;
+  if (conv_up_supported(a)) return conv_up_stats_slots(a);
   if (conv_ksplit_supported(a)) return conv_ksplit_stats_slots(a);
   if (conv_mfma_supported(a)) return conv_mfma_stats_slots(a);
   return conv_small_cin_supported(a) ? conv_small_cin_stats_slots(a) : 0;
 }
 
+// Extents of the row moments a launch can leave and of its ticket counters; false: its kernel merges no rows.
+static bool conv_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row) {
+  if (conv_up_supported(a)) { conv_up_row_extents(a, tile_rows, channel_tiles, tiles_per_row); return true; }
+  if (conv_ksplit_supported(a) || !conv_mfma_supported(a)) return false;
+  conv_mfma_row_extents(a, tile_rows, channel_tiles, tiles_per_row);
+  return true;
+}
+
 const char* conv_kernel_label(const ConvArgs& a) {
   if (conv_taps_supported(a)) return conv_taps_label(a);
+  if (conv_up_supported(a)) return conv_up_label(a);
   if (conv_ksplit_supported(a)) return conv_ksplit_label(a);
   if (!conv_mfma_supported(a)) return conv_small_cin_supported(a) ? "conv_small_cin_kernel" : "conv_direct_kernel";
   return conv_mfma_label(a);
@@ -83,7 +94,7 @@ struct Param {  // one canonical parameter
   size_t offset, bytes;      // in the canonical blob
   size_t packed_offset;      // in the packed blob
   size_t packed_bytes;
-  bool upconv = false;       // weights of an upsampling convolution: 9-tap pack followed by the 16-tap phase pack
+  bool upconv = false;       // weights of an upsampling convolution (their packed blob has a size of its own)
 };
 
 struct Step {
@@ -193,9 +204,11 @@ struct Builder {
     const double es = (double)dtype_size(d.cfg.act_dtype);
     const double px_out = (double)s.h * s.w, px_in = s.upsample ? px_out / 4 : px_out;
     s.flops_dense = 2.0 * s.ksize * s.ksize * (double)s.cin * s.cout * px_out;
-    // a phase-decomposed upsampling convolution executes a 2x2 convolution per output: 4/9 of the products.
-    // Only executed work is counted, never the work avoided.
-    s.flops = conv_mfma_uses_phase(step_shape_args(d, s, 1)) ? s.flops_dense * 4.0 / 9.0 : s.flops_dense;
+    // An upsampling convolution is priced per output at the 2x2 convolution of its phase in f16 (4/9) and at nine taps in
+    // bf16, as before one kernel took both with nine products per input pixel (1/4, executed on 1.22 times the
+    // pixels): figures stay comparable, but are no count of executed products for these launches.
+    const bool four_taps = s.upsample && d.cfg.act_dtype == WMDEC_F16 && conv_up_supported(step_shape_args(d, s, 1));
+    s.flops = four_taps ? s.flops_dense * 4.0 / 9.0 : s.flops_dense;
     if (s.sc_src != BUF_NONE) {   // folded 1x1 shortcut: its products, its input and its weights
       const double f = 2.0 * (double)s.sc_cin * s.cout * px_out;
       s.flops += f; s.flops_dense += f;
@@ -285,10 +298,8 @@ static void fuse_stats_into_producers(wmdec_decoder& d) {
       d.launches -= 1;
       continue;
     }
-    const ConvArgs prod = step_shape_args(d, d.steps[j], 1);
-    if (conv_ksplit_supported(prod) || !conv_mfma_supported(prod)) continue;   // only that kernel merges by row
     int rows = 0, ctiles = 0, per_row = 0;
-    conv_mfma_row_extents(step_shape_args(d, d.steps[j], 1), &rows, &ctiles, &per_row);
+    if (!conv_row_extents(step_shape_args(d, d.steps[j], 1), &rows, &ctiles, &per_row)) continue;
     if (rows > 64) continue;   // keeps the consumer's merge short
     // The hand-over keeps every workgroup of the producer resident for two more memory round trips (its stores, its
     // ticket).  Measured, that costs a launch of several rounds of workgroups as much as the merge launch it saves;
@@ -415,7 +426,7 @@ static WsLayout ws_layout(const wmdec_decoder* d, int batch) {
     if (st.kind != Step::CONV || st.emit_rows < 0) continue;
     int rows = 0, ctiles = 0, per_row = 0;
     if (st.emit_direct) { rows = conv_stats_slots(step_shape_args(*d, st, 1)); ctiles = 0; }
-    else conv_mfma_row_extents(step_shape_args(*d, st, 1), &rows, &ctiles, &per_row);
+    else (void)conv_row_extents(step_shape_args(*d, st, 1), &rows, &ctiles, &per_row);
     if ((size_t)rows * ctiles > max_tickets) max_tickets = (size_t)rows * ctiles;
     if ((size_t)rows > max_rows) max_rows = rows;
   }
@@ -533,7 +544,6 @@ static int conv_entry(const char* who, int ksize, int upsample, const void* x, i
   a.wt = w_packed; a.op_dtype = act_dtype; a.bias = bias; a.res = residual; a.res_dtype = act_dtype;
   a.y = y; a.y_dtype = y_dtype; a.n = n; a.h = h_out; a.w = w_out; a.cin = cin; a.cout = cout;
   a.ksize = ksize; a.upsample = upsample;
-  if (upsample) a.wt_phase = (const char*)w_packed + upconv_phase_offset_bytes(cout, cin, act_dtype);
   return launch_conv(a, (hipStream_t)stream);
 }
 
@@ -911,7 +921,6 @@ static int launch_step(wmdec_decoder* dec, const WsLayout& L, const Step& st, co
           else { a.mean = mean; a.rstd = rstd; }
         }
         a.wt = pk + st.w_off; a.bias = (const float*)(pk + st.b_off);
-        if (st.upsample) a.wt_phase = pk + st.w_off + upconv_phase_offset_bytes(st.cout, st.cin, c.act_dtype);
         a.res = buf(st.res);
         if (st.sc_src != BUF_NONE) { a.x2 = buf(st.sc_src); a.cin2 = st.sc_cin; a.w2 = pk + st.sc_w_off; a.bias2 = (const float*)(pk + st.sc_b_off); }
         if (st.dst == BUF_OUT) { a.y = out; a.y_dtype = WMDEC_F32; a.y_nchw = 1; }

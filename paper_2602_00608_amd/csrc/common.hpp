@@ -76,7 +76,6 @@ struct ConvArgs {
   int groups_norm = 0;           // label queries only: the launch will normalise although mean is not known yet
   int silu = 0;
   const void* wt = nullptr;      // packed [k*k][cout][cin] in op dtype
-  const void* wt_phase = nullptr;  // upsample only: the 16-tap phase pack (pre-summed 2x2 weights of the four output phases)
   int op_dtype = WMDEC_F32;      // arithmetic: F32 (FMA) or BF16 / F16 (operands rounded to it)
   const float* bias = nullptr;   // [cout] or null
   const void* res = nullptr;     // [n,h,w,cout] of res_dtype or null
@@ -113,12 +112,16 @@ int launch_conv_small_cin(const ConvArgs& a, hipStream_t s);
 // is not one it handles (caller falls back to the direct kernel), 0 if launched.
 bool conv_mfma_supported(const ConvArgs& a);
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s);
-// true if the launch evaluates an upsampling convolution per output phase (2x2 taps, 4/9 of the products)
-bool conv_mfma_uses_phase(const ConvArgs& a);
 // moment slots per (sample, group) the MFMA kernel would write for this launch; 0: it cannot emit statistics
 int conv_mfma_stats_slots(const ConvArgs& a);
 void conv_mfma_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row);
 const char* conv_mfma_label(const ConvArgs& a);   // instantiation name, valid until the thread's next call
+// kernels_conv_up.hip: nearest-2x upsample + 3x3 convolution on the low-resolution grid, nine products per input pixel
+bool conv_up_supported(const ConvArgs& a);
+int launch_conv_up(const ConvArgs& a, hipStream_t s);
+int conv_up_stats_slots(const ConvArgs& a);
+void conv_up_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row);
+const char* conv_up_label(const ConvArgs& a);
 // kernels_conv_ksplit.hip: 3x3 convolution of small images, and of fp32, with the contraction split over wavefronts
 bool conv_ksplit_supported(const ConvArgs& a);
 int launch_conv_ksplit(const ConvArgs& a, hipStream_t s);
@@ -153,8 +156,7 @@ int launch_gn_finalize(const void* ws, int n_groups, int slots, float eps, float
 int launch_upsample2x(const void* x, void* y, int dtype, int n, int h_in, int w_in, int c, hipStream_t s);
 int launch_pack_conv(const void* src, int src_dtype, int cout, int cin, int k, void* dst, int op_dtype,
                      int dst_row_offset, int dst_rows_total, hipStream_t s);
-// weights of a nearest-2x-upsample + 3x3 convolution: the 9-tap pack followed by the 16-tap phase pack
-size_t upconv_phase_offset_bytes(int cout, int cin, int op_dtype);
+// weights of a nearest-2x-upsample + 3x3 convolution: the 9-tap pack (and room that is not read)
 size_t upconv_packed_bytes(int cout, int cin, int op_dtype);
 int launch_pack_upconv(const void* src, int src_dtype, int cout, int cin, void* dst, int op_dtype, hipStream_t s);
 // dst[n][i][j] (dst_dtype) = src[n][j][i] (src_dtype); src is [rows=j][cols=i] with row stride src_ld

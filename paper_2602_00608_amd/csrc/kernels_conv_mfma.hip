@@ -17,9 +17,8 @@
 // the other buffer in compile-time slots inside the sweep of chunk c, with one
 // workgroup barrier per chunk.  Two or three workgroups fit on a compute unit, so
 // the prologue and epilogue of one overlap the sweeps of the others.
-// A nearest-2x upsample in front of the convolution is either folded into the
-// staging address (bf16) or, in f16, removed algebraically: the phase mode
-// computes each of the four output phases as a 2x2 convolution on the input grid.
+// A nearest-2x upsample in front of the convolution is folded into the staging
+// address (what kernels_conv_up.hip does not take).
 #include <stdio.h>
 
 #include <mutex>
@@ -42,10 +41,7 @@ constexpr int patch_floats(int ni) { return 32 * (ni * 32 + 4) > 2048 ? 32 * (ni
 template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, bool RES>
 __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], float* lds, int lane, int mt0, int ty0,
                                                int tx0, int co_w, const float* bias, const float* bias2, const T* rin, TO* yout, int h,
-                                               int w_out, int cout, bool nchw, Moments* stats, int cpg, int stats_stride,
-                                               int osc = 1, int oy_off = 0, int ox_off = 0) {
-  // tile pixel (ty, tx) is output pixel (ty * osc + oy_off, tx * osc + ox_off): osc = 2 when the tile lives on the
-  // low-resolution grid of a phase-decomposed upsampling convolution
+                                               int w_out, int cout, bool nchw, Moments* stats, int cpg, int stats_stride) {
   constexpr int RW = NI * 32 + 4;       // padded row of the patch, floats
   if (nchw) {
     // planar output with few channels (the frame): a lane owns one pixel of the M tile and walks the
@@ -79,8 +75,8 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
   auto vec_off = [&](int mi, int j) -> int {
     const int mt = mt0 + mi;
     const int pi = prow + j * (64 / (NI * 4));
-    const int oy = (ty0 + (mt / MT_PER_ROW) * MTH + pi / MTW) * osc + oy_off;
-    const int ox = (tx0 + (mt % MT_PER_ROW) * MTW + pi % MTW) * osc + ox_off;
+    const int oy = ty0 + (mt / MT_PER_ROW) * MTH + pi / MTW;
+    const int ox = tx0 + (mt % MT_PER_ROW) * MTW + pi % MTW;
     return (oy < h && ox < w_out) ? (oy * w_out + ox) * cout + co_w + cvec * 8 : -1;   // < 2^30 elements (checked on the host)
   };
   // residual vectors are fetched two M tiles ahead (unconditional loads, clamped to element 0 outside the
@@ -261,11 +257,7 @@ __device__ __forceinline__ void mfma_chunk(const T* buf, const int (&a_off)[MI],
 }
 
 // ACT: what happens to an input element on its way into LDS: 0 nothing, 1 scale/shift, 2 scale/shift + SiLU
-// PH: phase-decomposed nearest-2x upsampling convolution.  The tile lives on the low-resolution input grid; wavefront
-// w computes output phase (py, px) = (w >> 1, w & 1) of all its pixels, i.e. output pixels (2i + py, 2j + px), as a
-// 2x2 convolution over input rows i + py - 1 .. i + py and columns j + px - 1 .. j + px with the phase's pre-summed
-// weights (taps 4 * w .. 4 * w + 3 of the 16-tap phase pack): 4/9 of the multiplications of the 3x3 form.
-constexpr int wave_m_tiles(int th, int tw, int wm, bool ph) { return ph ? th * tw / 32 : th * tw / 32 / wm; }
+constexpr int wave_m_tiles(int th, int tw, int wm) { return th * tw / 32 / wm; }
 // Workgroups per compute unit the register budget is sized for: three for the small accumulator tiles, except the
 // 2x2-wavefront 128x128 shape, which is only picked for layers with at most two workgroups per compute unit and
 // uses the registers for a longer prefetch instead.
@@ -290,15 +282,13 @@ constexpr int tile_buf_elems(int th, int tw, int pad, int kc) { return (th + 2 *
 // a chunk).  The whole-chunk ring is for launches that leave a compute unit at most two workgroups: there a wavefront
 // is alone on its SIMD, nothing else hides the latency of weights that come from beyond the L2 (every layer's weights
 // are new to the L2 inside a decoder run), and the registers of the third workgroup are free for it.
-template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int ACT, bool PH = false, int RING = 0>
-__global__ __launch_bounds__(64 * WM * WN, RING > 6 ? 2 : resident_workgroups(wave_m_tiles(TH, TW, WM, PH) * NI, WM, WN))
+template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int ACT, int RING = 0>
+__global__ __launch_bounds__(64 * WM * WN, RING > 6 ? 2 : resident_workgroups(wave_m_tiles(TH, TW, WM) * NI, WM, WN))
 void conv_mfma_kernel(MfmaParams p) {
   static_assert(WM * WN == 4 || WM * WN == 8, "four or eight wavefronts");
   constexpr int NT = 64 * WM * WN;               // threads of the workgroup
-  static_assert(!PH || (KS == 3 && WM == 4 && WN == 1), "phase mode: one wavefront per phase");
-  constexpr int MI = wave_m_tiles(TH, TW, WM, PH);   // 32-pixel M tiles per wavefront
-  constexpr int KT = PH ? 2 : KS;                // taps per dimension a wavefront sweeps
-  constexpr int PAD = PH ? 1 : KS / 2;
+  constexpr int MI = wave_m_tiles(TH, TW, WM);   // 32-pixel M tiles per wavefront
+  constexpr int PAD = KS / 2;
   constexpr int HW_ = TW + 2 * PAD, HH_ = TH + 2 * PAD, HP = HW_ * HH_;
   constexpr int PS = KC + 8;                     // LDS pixel stride in elements (+16 B: conflict-free 16-byte reads)
   constexpr int MTW = TW < 32 ? TW : 32, MTH = 32 / MTW, MT_PER_ROW = TW / MTW;
@@ -308,7 +298,7 @@ void conv_mfma_kernel(MfmaParams p) {
   constexpr int ROW = tile_row_elems(TW, PAD, KC);       // LDS row stride of the staged tile, elements
   constexpr int BUF = tile_buf_elems(TH, TW, PAD, KC);   // elements of one staged tile: the halo patch plus the spare slot
   constexpr int SPARE = HH_ * ROW;                       // element offset of the spare pixel slot
-  constexpr int STEPS = KT * KT * (KC / 16), SLOTS = STEPS * MI;
+  constexpr int STEPS = KS * KS * (KC / 16), SLOTS = STEPS * MI;
   constexpr bool SLICED = KS == 3;               // activation of the next chunk is sliced into the MFMA sweep
   static_assert(NT % VPP == 0, "a thread keeps one channel octet");
 
@@ -335,7 +325,6 @@ void conv_mfma_kernel(MfmaParams p) {
   const int ty0 = (tile / p.tiles_x) * TH, tx0 = (tile % p.tiles_x) * TW;
   const int co0 = nt * TN;
   const int h_in = p.upsample ? p.h >> 1 : p.h, w_in = p.upsample ? p.w_out >> 1 : p.w_out;
-  const int h_t = PH ? h_in : p.h, w_t = PH ? w_in : p.w_out;   // the grid the tiles live on
 
   f32x16 acc[MI][NI];
 #pragma unroll
@@ -349,17 +338,17 @@ void conv_mfma_kernel(MfmaParams p) {
   int a_off[MI];
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
-    const int mt = PH ? mi : wm * MI + mi;
+    const int mt = wm * MI + mi;
     const int ty = (mt / MT_PER_ROW) * MTH + lm / MTW, tx = (mt % MT_PER_ROW) * MTW + lm % MTW;
-    a_off[mi] = ty * ROW + tx * PS + 8 * lk + (PH ? (wave >> 1) * ROW + (wave & 1) * PS : 0);
+    a_off[mi] = ty * ROW + tx * PS + 8 * lk;
   }
   constexpr int KK = KC / 16;
-  constexpr int D = RING > 0 ? RING : prefetch_ring(KT * KT * KK, MI * NI);   // weight fragments are fetched D-1 k-steps ahead
-  static_assert((KT * KT * KK) % D == 0, "the ring position must be the same at every chunk start");
+  constexpr int D = RING > 0 ? RING : prefetch_ring(KS * KS * KK, MI * NI);   // weight fragments are fetched D-1 k-steps ahead
+  static_assert((KS * KS * KK) % D == 0, "the ring position must be the same at every chunk start");
   const int tap_stride = p.cin_blocks * p.cout_blocks * 1024, kk_stride = p.cout_blocks * 1024;   // bytes
   // byte offset of this wavefront's fragment column (wave-uniform; the lane's 16 bytes are added by the load)
   const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w), 0, p.w_bytes, 0x00020000);
-  const int wcol = ((co0 >> 5) + wn * NI) * 1024 + (PH ? wave * 4 * tap_stride : 0);
+  const int wcol = ((co0 >> 5) + wn * NI) * 1024;
   const int lane16 = lane * 16;
   u32x4 bq[D][NI];
 #pragma unroll
@@ -384,11 +373,11 @@ void conv_mfma_kernel(MfmaParams p) {
     const int hy = hp / HW_, hx = hp % HW_;
     const int gy = ty0 + hy - PAD, gx = tx0 + hx - PAD;
     const bool in_patch = v < HP * VPP;
-    const bool inside = in_patch && gy >= 0 && gy < h_t && gx >= 0 && gx < w_t;
+    const bool inside = in_patch && gy >= 0 && gy < p.h && gx >= 0 && gx < p.w_out;
     src_off[i] = 0;
     src_pix[i] = 0;
     if (inside) {
-      const int sy = (!PH && p.upsample) ? gy >> 1 : gy, sx = (!PH && p.upsample) ? gx >> 1 : gx;
+      const int sy = p.upsample ? gy >> 1 : gy, sx = p.upsample ? gx >> 1 : gx;
       src_pix[i] = sy * w_in + sx;
       src_off[i] = (src_pix[i] * p.cin + cvec * 8) * (int)sizeof(T);
     }
@@ -444,7 +433,7 @@ void conv_mfma_kernel(MfmaParams p) {
   // two LDS buffers with the tile's halo layout (only the centre tap is read), loads two chunks ahead; the main
   // loop below then adds the 3x3 contraction to the same accumulators, so the shortcut tensor never exists in
   // memory and the epilogue adds both biases.
-  if constexpr (KS == 3 && !PH) {
+  if constexpr (KS == 3) {
     if (p.x2) {
       const char* xin2 = reinterpret_cast<const char*>(p.x2) + (size_t)n * p.h * p.w_out * p.cin2 * sizeof(T);
       const int nch2 = p.cin2 / KC;
@@ -579,10 +568,10 @@ void conv_mfma_kernel(MfmaParams p) {
       };
       // the last chunk activates a harmless reload into the buffer nobody reads: one instruction stream, no
       // control flow inside the pinned schedule
-      mfma_chunk<T, MI, NI, KT, KC, ROW, PS, D, true, SPREAD, decltype(slice)&, (RING > 6 ? 2 : 1)>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, slice);
+      mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, true, SPREAD, decltype(slice)&, (RING > 6 ? 2 : 1)>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, slice);
     } else {
       auto none = [](auto) {};
-      mfma_chunk<T, MI, NI, KT, KC, ROW, PS, D, false, -1, decltype(none)&, (RING > 6 ? 2 : 1)>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, none);
+      mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, false, -1, decltype(none)&, (RING > 6 ? 2 : 1)>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, none);
       if (more) activate_all(c0n, nbuf);
     }
     issue(c + 2);
@@ -596,30 +585,26 @@ void conv_mfma_kernel(MfmaParams p) {
   // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row]
   Moments* st = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + (tile * WM + wm) : nullptr;
   if (rin)
-    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true>(acc, patch, lane, PH ? 0 : wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
-                                                              p.bias2, rin, yout, p.h, p.w_out, p.cout, false, st, p.stats_cpg, p.stats_slots,
-                                                              PH ? 2 : 1, PH ? wave >> 1 : 0, PH ? wave & 1 : 0);
+    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
+                                                              p.bias2, rin, yout, p.h, p.w_out, p.cout, false, st, p.stats_cpg, p.stats_slots);
   else
-    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false>(acc, patch, lane, PH ? 0 : wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
-                                                               p.bias2, rin, yout, p.h, p.w_out, p.cout, p.y_nchw != 0, st, p.stats_cpg, p.stats_slots,
-                                                               PH ? 2 : 1, PH ? wave >> 1 : 0, PH ? wave & 1 : 0);
+    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
+                                                               p.bias2, rin, yout, p.h, p.w_out, p.cout, p.y_nchw != 0, st, p.stats_cpg, p.stats_slots);
 
   if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, co0, TN, WM, tid, lane);
 }
 
-template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, bool PH = false, int RING = 0>
+template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int RING = 0>
 int launch_cfg(const ConvArgs& a, hipStream_t s) {
-  constexpr int PAD = PH ? 1 : KS / 2;
+  constexpr int PAD = KS / 2;
   constexpr int TN = WN * NI * 32;
-  WMDEC_REQUIRE(!PH || (a.wt_phase && a.h % 2 == 0 && a.w % 2 == 0), WMDEC_ERR_INVALID_ARG, "conv_mfma: upsampling convolution without phase weights");
-  // the tiles of a phase-decomposed launch live on the input grid
-  MfmaParams p = conv_params(a, TH, TW, TN, WM, PH ? a.h / 2 : a.h, PH ? a.w / 2 : a.w);
+  MfmaParams p = conv_params(a, TH, TW, TN, WM, a.h, a.w);
   const int rc = check_hand_over(p);
   if (rc != WMDEC_OK) return rc;
-  p.w = PH ? a.wt_phase : a.wt;
-  p.w_bytes = (int)(packed_elems(PH ? 16 : KS * KS, a.cout, a.cin) * sizeof(T));
+  p.w = a.wt;
+  p.w_bytes = (int)(packed_elems(KS * KS, a.cout, a.cin) * sizeof(T));
   if (a.x2) {
-    WMDEC_REQUIRE(KS == 3 && !PH && a.w2 && a.cin2 > 0 && a.cin2 % KC == 0 && (long)a.h * a.w * a.cin2 < (1L << 29), WMDEC_ERR_UNSUPPORTED,
+    WMDEC_REQUIRE(KS == 3 && a.w2 && a.cin2 > 0 && a.cin2 % KC == 0 && (long)a.h * a.w * a.cin2 < (1L << 29), WMDEC_ERR_UNSUPPORTED,
                   "conv_mfma: a folded shortcut needs a 3x3 convolution without upsampling and cin2 %% %d == 0", KC);
     p.x2 = a.x2; p.w2 = a.w2; p.bias2 = a.bias2; p.cin2 = a.cin2;
     p.w2_bytes = (int)(packed_elems(1, a.cout, a.cin2) * sizeof(T));
@@ -629,9 +614,9 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
   const size_t patch = (size_t)(WM * WN) * patch_floats(NI) * sizeof(float);   // epilogue patches of the wavefronts
   if (smem < patch) smem = patch;
   WMDEC_REQUIRE(smem <= 80 * 1024, WMDEC_ERR_UNSUPPORTED, "conv_mfma: %zu bytes of LDS needed", smem);
-  void (*kern)(MfmaParams) = !p.norm ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 0, PH, RING>
-                             : (a.silu ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 2, PH, RING>
-                                       : conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 1, PH, RING>);
+  void (*kern)(MfmaParams) = !p.norm ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 0, RING>
+                             : (a.silu ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 2, RING>
+                                       : conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 1, RING>);
   // once per instantiation and activation mode (80 KiB: two workgroups per compute unit)
   static std::once_flag attr_once[3];
   hipError_t attr_err = hipSuccess;
@@ -645,14 +630,13 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
 
 // Tile shapes: patch height x width, wavefront rows x columns, 32-channel tiles per wavefront.
 struct TileShape { int th, tw, wm, wn, ni; };
-enum TileId { T256x128 = 0, T128x128_ROW, T128x64_ROW, T128x64, T256x32, T_PHASE, T128x128_1x4, T128x256, kNumTiles };
+enum TileId { T256x128 = 0, T128x128_ROW, T128x64_ROW, T128x64, T256x32, T128x128_1x4, T128x256, kNumTiles };
 constexpr TileShape kTiles[kNumTiles] = {
     {8, 32, 2, 2, 2},    // T256x128: 256 pixels x 128 channels (large 1x1 convolutions)
     {4, 32, 2, 2, 2},    // T128x128_ROW: 128 x 128 on a 4x32 patch (1x1 convolutions)
     {4, 32, 4, 1, 2},    // T128x64_ROW: 128 x 64 on a 4x32 patch (1x1 convolutions)
     {8, 16, 4, 1, 2},    // T128x64: 128 x 64 on an 8x16 patch
     {8, 32, 4, 1, 1},    // T256x32: 256 x 32 (few output channels: the frame)
-    {8, 16, 4, 1, 2},    // T_PHASE: phase-decomposed upsampling convolution: 8x16 input pixels (16x32 outputs) x 64 channels
     {8, 16, 1, 4, 1},    // T128x128_1x4: 128 x 128, every wavefront all pixels x 32 channels: a weight fragment feeds four
                          //     MFMAs, which keeps the fragment loads off the limit of the vector L1 (64 B/clk per compute unit)
     {8, 16, 1, 4, 2},    // T128x256: 128 x 256, every wavefront all pixels x 64 channels: a staged (normalised, activated) patch
@@ -666,7 +650,6 @@ TileId pick_tile(const ConvArgs& a) {
   const long px = (long)a.h * a.w;
   const bool n128 = a.cout % 128 == 0;
   if (a.ksize == 3) {
-    if (conv_mfma_uses_phase(a)) return T_PHASE;
     if (a.cout <= 32) return T256x32;
     // 128 pixels x 128 channels with every wavefront on all pixels x 32 channels (three workgroups per compute unit):
     // measured against the 256-pixel tile and the 2x2 wavefront layout on every layer shape of the decoder, it is
@@ -696,9 +679,8 @@ template <typename T, typename TO>
 int launch_3x3(const ConvArgs& a, hipStream_t s) {
   switch (pick_tile(a)) {
     case T128x64: return launch_cfg<T, TO, 8, 16, 4, 1, 2, 3, 32>(a, s);
-    case T_PHASE: return launch_cfg<T, TO, 8, 16, 4, 1, 2, 3, 32, true>(a, s);
     case T128x128_1x4:
-      return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, false, 18>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32>(a, s);
+      return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32>(a, s);
     case T128x256: return launch_cfg<T, TO, 8, 16, 1, 4, 2, 3, 32>(a, s);
     default: return launch_cfg<T, TO, 8, 32, 4, 1, 1, 3, 32>(a, s);
   }
@@ -741,30 +723,23 @@ bool conv_mfma_supported(const ConvArgs& a) {
   return true;
 }
 
-// Phase decomposition of an upsampling convolution (needs a.wt_phase at launch), f16 only: pre-added weights rounded
-// to bf16 would cost that type a visible part of its error budget.
-bool conv_mfma_uses_phase(const ConvArgs& a) {
-  return conv_mfma_supported(a) && a.ksize == 3 && a.upsample && a.op_dtype == WMDEC_F16 && a.cout % 64 == 0;
-}
-
 int conv_mfma_stats_slots(const ConvArgs& a) {
   if (!conv_mfma_supported(a) || a.y_nchw || a.stats_groups <= 0 || a.cout % a.stats_groups != 0) return 0;
   const int cpg = a.cout / a.stats_groups;
   if ((cpg & (cpg - 1)) != 0 || cpg > 32) return 0;   // a group must sit inside one wavefront's 64-channel run
   const TileId t = pick_tile(a);
   const TileShape& ts = kTiles[t];
-  const int w_t = t == T_PHASE ? a.w / 2 : a.w, h_t = t == T_PHASE ? a.h / 2 : a.h;
-  return ((w_t + ts.tw - 1) / ts.tw) * ((h_t + ts.th - 1) / ts.th) * ts.wm;
+  return ((a.w + ts.tw - 1) / ts.tw) * ((a.h + ts.th - 1) / ts.th) * ts.wm;
 }
 
 // tile rows / channel tiles of a launch: the extents of the row moments it can leave and of its ticket counters
 void conv_mfma_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row) {
   const TileId t = pick_tile(a);
   const TileShape& ts = kTiles[t];
-  const int h_t = t == T_PHASE ? a.h / 2 : a.h, w_t = t == T_PHASE ? a.w / 2 : a.w, tn = ts.wn * ts.ni * 32;
-  *tile_rows = (h_t + ts.th - 1) / ts.th;
+  const int tn = ts.wn * ts.ni * 32;
+  *tile_rows = (a.h + ts.th - 1) / ts.th;
   *channel_tiles = (a.cout + tn - 1) / tn;
-  *tiles_per_row = (w_t + ts.tw - 1) / ts.tw;
+  *tiles_per_row = (a.w + ts.tw - 1) / ts.tw;
 }
 
 // the instantiation a launch would use, spelled like a profiler prints it
@@ -775,8 +750,8 @@ const char* conv_mfma_label(const ConvArgs& a) {
   const TileShape& ts = kTiles[t];
   const char* ty = a.op_dtype == WMDEC_BF16 ? "wmdec::bf16_t" : "wmdec::f16_t";
   const int act = a.mean == nullptr && a.rows_in == nullptr && !a.groups_norm ? 0 : (a.silu ? 2 : 1);
-  snprintf(buf, sizeof(buf), "conv_mfma_kernel<%s, %s, %d, %d, %d, %d, %d, %d, %d, %d, %s, %d>", ty,
-           a.y_dtype == WMDEC_F32 ? "float" : ty, ts.th, ts.tw, ts.wm, ts.wn, ts.ni, a.ksize, kc, act, t == T_PHASE ? "true" : "false",
+  snprintf(buf, sizeof(buf), "conv_mfma_kernel<%s, %s, %d, %d, %d, %d, %d, %d, %d, %d, %d>", ty,
+           a.y_dtype == WMDEC_F32 ? "float" : ty, ts.th, ts.tw, ts.wm, ts.wn, ts.ni, a.ksize, kc, act,
            a.ksize == 3 && whole_chunk_ring(a) ? 18 : 0);
   return buf;
 }

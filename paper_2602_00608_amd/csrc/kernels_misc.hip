@@ -61,31 +61,6 @@ __global__ __launch_bounds__(256) void pack_conv_kernel(const S* __restrict__ sr
   dst[i] = from_float<D>(to_float(src[((size_t)co * cin + ci) * taps + tap]));
 }
 
-// Phase pack of a nearest-2x-upsample + 3x3 convolution.  Output pixel (2i + py, 2j + px) only sees input rows
-// i + py - 1, i + py and columns j + px - 1, j + px; the 3x3 taps that fall on the same input pixel are summed once,
-// here (fp32, fixed order, one rounding to D).  Row r of phase py collects ky in {0} | {1,2} (py = 0) or {0,1} | {2}
-// (py = 1), the same for columns.  Tap index of the pack: ((py*2 + px)*2 + r)*2 + s, 16 taps.
-template <typename S, typename D>
-__global__ __launch_bounds__(256) void pack_upconv_phase_kernel(const S* __restrict__ src, D* __restrict__ dst, int cout, int cin) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  const int cinb = packed_cin_blocks(cin), coutb = packed_cout_blocks(cout);
-  if (i >= (size_t)16 * cinb * coutb * 512) return;
-  const int e = (int)(i & 7), lane = (int)((i >> 3) & 63);
-  size_t blk = i >> 9;
-  const int cob = (int)(blk % coutb); blk /= coutb;
-  const int cib = (int)(blk % cinb);
-  const int tap = (int)(blk / cinb);
-  const int co = cob * 32 + (lane & 31), ci = cib * 16 + (lane >> 5) * 8 + e;
-  if (ci >= cin || co >= cout) { dst[i] = from_float<D>(0.f); return; }
-  const int py = tap >> 3, px = (tap >> 2) & 1, r = (tap >> 1) & 1, sx = tap & 1;
-  const int ky0 = py == 0 ? (r == 0 ? 0 : 1) : (r == 0 ? 0 : 2), ky1 = py == 0 ? (r == 0 ? 0 : 2) : (r == 0 ? 1 : 2);
-  const int kx0 = px == 0 ? (sx == 0 ? 0 : 1) : (sx == 0 ? 0 : 2), kx1 = px == 0 ? (sx == 0 ? 0 : 2) : (sx == 0 ? 1 : 2);
-  float acc = 0.f;
-  for (int ky = ky0; ky <= ky1; ++ky)
-    for (int kx = kx0; kx <= kx1; ++kx) acc += to_float(src[((size_t)co * cin + ci) * 9 + ky * 3 + kx]);
-  dst[i] = from_float<D>(acc);
-}
-
 // dst[b][i][j] = src[b][j][i], 32x32 tiles through LDS.  BLOCKED (dst_ld = 0): the destination is cut into blocks of 32
 // source rows, dst[b][j / 32][i][40] with j % 32 in the first 32 of a row's 40 elements and zeros for source rows past
 // the end: the image of the attention kernel's V^T tile in LDS (32 keys, rows padded to 40 elements), which that
@@ -153,15 +128,6 @@ int pack_t(const void* src, void* dst, int cout, int cin, int k, int row_off, in
 }
 
 template <typename S, typename D>
-int pack_phase_t(const void* src, void* dst, int cout, int cin, hipStream_t s) {
-  const size_t total = packed_elems(16, cout, cin);
-  hipLaunchKernelGGL((pack_upconv_phase_kernel<S, D>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
-                     (const S*)src, (D*)dst, cout, cin);
-  WMDEC_HIP(hipGetLastError());
-  return WMDEC_OK;
-}
-
-template <typename S, typename D>
 int transpose_t(const void* src, void* dst, int batch, int rows, int cols, size_t sld, size_t sbs, size_t dld, size_t dbs, hipStream_t s) {
   dim3 grid((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32), (unsigned)batch);
   if (dld == 0) hipLaunchKernelGGL((transpose_kernel<S, D, true>), grid, dim3(256), 0, s, (const S*)src, (D*)dst, rows, cols, sld, sbs, dld, dbs);
@@ -218,25 +184,12 @@ int launch_pack_conv(const void* src, int src_dtype, int cout, int cin, int k, v
   }
 }
 
-size_t upconv_phase_offset_bytes(int cout, int cin, int op_dtype) { return packed_elems(9, cout, cin) * dtype_size(op_dtype); }
+// 9 taps are read; the blob keeps the 25 taps it had when 16 of them were pre-summed for the output phases, so that
+// buffers and offsets saved by callers stay valid
 size_t upconv_packed_bytes(int cout, int cin, int op_dtype) { return packed_elems(9 + 16, cout, cin) * dtype_size(op_dtype); }
 
 int launch_pack_upconv(const void* src, int src_dtype, int cout, int cin, void* dst, int op_dtype, hipStream_t s) {
-  const int rc = launch_pack_conv(src, src_dtype, cout, cin, 3, dst, op_dtype, 0, cout, s);
-  if (rc != WMDEC_OK) return rc;
-  void* ph = (char*)dst + upconv_phase_offset_bytes(cout, cin, op_dtype);
-  if (src_dtype == WMDEC_F32) {
-    switch (op_dtype) {
-      case WMDEC_F32: return pack_phase_t<float, float>(src, ph, cout, cin, s);
-      case WMDEC_BF16: return pack_phase_t<float, bf16_t>(src, ph, cout, cin, s);
-      default: return pack_phase_t<float, f16_t>(src, ph, cout, cin, s);
-    }
-  }
-  switch (op_dtype) {
-    case WMDEC_F32: return pack_phase_t<bf16_t, float>(src, ph, cout, cin, s);
-    case WMDEC_BF16: return pack_phase_t<bf16_t, bf16_t>(src, ph, cout, cin, s);
-    default: return pack_phase_t<bf16_t, f16_t>(src, ph, cout, cin, s);
-  }
+  return launch_pack_conv(src, src_dtype, cout, cin, 3, dst, op_dtype, 0, cout, s);
 }
 
 int launch_transpose(const void* src, int src_dtype, void* dst, int dst_dtype, int batch, int rows, int cols,

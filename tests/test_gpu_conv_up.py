@@ -1,0 +1,44 @@
+"""Nearest-2x upsample + 3x3 convolution from nine products per input pixel: tile edges of the 7 x 15 pixel tiles against
+the fp64 oracle, at one type's rounding of the result (the products and sums carry no rounding of their own)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+from paper_2602_00608_amd import synth, wmdec
+from tests import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("n,cin,cout,h,w", [(1, 32, 64, 1, 1), (2, 64, 64, 7, 15), (1, 96, 128, 8, 16), (1, 64, 192, 6, 14), (3, 128, 64, 15, 31),
+                                            (1, 512, 512, 17, 23)])
+def test_upsampling_convolution_tile_edges(dtype, n, cin, cout, h, w):
+    r = np.random.default_rng(synth.SEED_BASE + 50)
+    x = G.stored(r.standard_normal((n, cin, h, w)), dtype)
+    wt, b = synth.conv_params(r, cout, cin, 3, True)
+    want = ref.upconv(x, wt, b)
+    for ydtype in ("f32", dtype):
+        y, check = G.canaried((n, 2 * h, 2 * w, cout), G.TORCH[ydtype])
+        wmdec.upsample2x_conv3x3(G.dev_nhwc(x, dtype), G.pack_upconv(wt, dtype), G.dev_f32(b), y)
+        torch.cuda.synchronize()
+        check()
+        got = G.host_nchw(y)
+        # operands are exact: fp32 sums of 9 * cin products (worst case 9 * 512 * 2^-24 of the magnitudes, typically 1e-6);
+        # a stored output adds half an ulp of its own size
+        tol = np.full_like(want, 2e-5 * float(np.sqrt(np.mean(want ** 2))))
+        if ydtype != "f32":
+            tol += np.abs(want) * (2.0 ** -8 if dtype == "bf16" else 2.0 ** -11)
+        assert np.all(np.abs(got - want) <= tol), float(np.max(np.abs(got - want) - tol))
+
+
+def test_upsampling_convolution_sample_bits_do_not_depend_on_the_batch():
+    r = np.random.default_rng(synth.SEED_BASE + 51)
+    x = G.dev_nhwc(G.stored(r.standard_normal((3, 64, 20, 33)), "f16"), "f16")
+    wt, b = synth.conv_params(r, 64, 64, 3, True)
+    wp, bd = G.pack_upconv(wt, "f16"), G.dev_f32(b)
+    y3, y1 = torch.empty((3, 40, 66, 64), dtype=torch.float16, device="cuda"), torch.empty((1, 40, 66, 64), dtype=torch.float16, device="cuda")
+    wmdec.upsample2x_conv3x3(x, wp, bd, y3)
+    wmdec.upsample2x_conv3x3(x[1:2].contiguous(), wp, bd, y1)
+    assert torch.equal(y3[1:2], y1)
