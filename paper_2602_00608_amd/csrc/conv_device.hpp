@@ -70,6 +70,41 @@ template <typename T, int ACT, bool PIN = false> __device__ __forceinline__ uint
   return wv;
 }
 
+// Sum over LANES (8 or 16) consecutive lanes, left in all of them (data-parallel moves: xor 1, xor 2, mirrors of 8 and 16).
+template <int LANES> __device__ __forceinline__ float lanes_sum(float v) {
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true));
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xf, 0xf, true));
+  if constexpr (LANES == 16) v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xf, 0xf, true));
+  return v;
+}
+
+// (mean, rstd) of a group from the `count` triples of its row, merged by LANES consecutive lanes (all of them active), eight
+// loads in flight per lane: weighted sums of the differences to the first triple's mean instead of a chain of pairwise
+// merges with a reciprocal each, which stood in front of every layer's first chunk.
+template <int LANES>
+__device__ __forceinline__ float2 merge_row(const Moments* row, int count, int sub, float eps) {
+  const float shift = row[0].mean;
+  float n = 0.f, s = 0.f, q = 0.f;
+  for (int r0 = sub; r0 < count; r0 += 8 * LANES) {
+    Moments t[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int r = r0 + LANES * k;
+      t[k] = row[min(r, count - 1)];
+      if (r >= count) { t[k].n = 0.f; t[k].m2 = 0.f; }
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const float d = t[k].mean - shift, nd = t[k].n * d;
+      n += t[k].n; s += nd; q += fmaf(nd, d, t[k].m2);
+    }
+  }
+  n = lanes_sum<LANES>(n); s = lanes_sum<LANES>(s); q = lanes_sum<LANES>(q);
+  const float d = s / n;
+  return make_float2(shift + d, 1.0f / sqrtf(fmaxf(q - s * d, 0.f) / n + eps));
+}
+
 // Row hand-over: the workgroup that finishes a (sample, tile row, channel tile) last merges that row's triples.  Same
 // protocol as the single-launch statistics kernel: the triples were written with device-scope stores, every wavefront
 // waits for its stores, the workgroup takes a ticket (a wrapping counter that returns to zero by itself), and only the

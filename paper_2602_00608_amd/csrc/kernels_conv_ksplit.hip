@@ -211,18 +211,8 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
       const int sub = tid % TPG;
       for (int g = tid / TPG; g < p.groups; g += NT / TPG) {
         const Moments* row = p.rows_in + (size_t)(n * p.groups + g) * p.rows_in_count;
-        Moments t[8];                                // at most 128 triples per group
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int r = sub + TPG * k;
-          t[k] = row[min(r, p.rows_in_count - 1)];
-          if (r >= p.rows_in_count) t[k].n = 0.f;
-        }
-        Moments m = t[0];
-#pragma unroll
-        for (int k = 1; k < 8; ++k) m = merge(m, t[k]);
-        m = merge_to_first(m, lane, TPG);
-        if (sub == 0) s_stat[g] = make_float2(m.mean, 1.0f / sqrtf(m.m2 / m.n + p.eps));
+        const float2 st = merge_row<TPG>(row, p.rows_in_count, sub, p.eps);
+        if (sub == 0) s_stat[g] = st;   // (at most 128 triples per group)
       }
     } else {
       for (int g = tid; g < p.groups; g += NT) s_stat[g] = make_float2(p.mean[n * p.groups + g], p.rstd[n * p.groups + g]);

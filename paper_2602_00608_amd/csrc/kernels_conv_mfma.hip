@@ -38,10 +38,10 @@ namespace {
 // that the statistics reduction parks there
 constexpr int patch_floats(int ni) { return 32 * (ni * 32 + 4) > 2048 ? 32 * (ni * 32 + 4) : 2048; }
 
-template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, bool RES>
+template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, bool RES, bool HALVES>
 __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], float* lds, int lane, int mt0, int ty0,
                                                int tx0, int co_w, const float* bias, const float* bias2, const T* rin, TO* yout, int h,
-                                               int w_out, int cout, bool nchw, Moments* stats, int cpg, int stats_stride) {
+                                               int w_out, int cout, bool nchw, Moments* stats, int cpg, int stats_stride, int half_stride) {
   constexpr int RW = NI * 32 + 4;       // padded row of the patch, floats
   if (nchw) {
     // planar output with few channels (the frame): a lane owns one pixel of the M tile and walks the
@@ -93,6 +93,36 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
   float st_shift[8], st_s[8], st_q[8], st_n = 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) { st_shift[e] = 0.f; st_s[e] = 0.f; st_q[e] = 0.f; }
+  auto emit_moments = [&](Moments* dst) {
+    // lane -> wavefront: every lane parks its 8 channels' (count, shift, sum, sum of squares) in the LDS patch;
+    // lane L then owns channel L of the wavefront's run, re-centres the entries of the lanes that held that
+    // channel (they differ in the pixel rows they read back) on one shift and adds them in a fixed order.
+    constexpr int CV = NI * 4;                 // octets per row of the patch
+    constexpr int ROWS = 64 / CV;              // lanes per octet
+    f32x4* park = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) park[lane * 8 + e] = f32x4{st_n, st_shift[e], st_s[e], st_q[e]};
+    Moments m{0.f, 0.f, 0.f};
+    if (lane < CV * 8) {
+      float n0 = 0.f, a0 = 0.f, s0 = 0.f, q0 = 0.f;
+#pragma unroll
+      for (int r = 0; r < ROWS; ++r) {
+        const f32x4 en = park[r * (CV * 8) + lane];     // (row r, octet lane / 8, channel lane % 8)
+        if (en[0] > 0.f) {
+          if (n0 == 0.f) a0 = en[1];
+          const float d = en[1] - a0;
+          s0 += en[2] + en[0] * d;
+          q0 += en[3] + 2.f * d * en[2] + en[0] * d * d;
+          n0 += en[0];
+        }
+      }
+      if (n0 > 0.f) { const float ds = s0 / n0; m.n = n0; m.mean = a0 + ds; m.m2 = fmaxf(q0 - s0 * ds, 0.f); }
+    }
+    // channels of one group are cpg consecutive lanes
+    m = merge_to_first(m, lane, cpg);
+    // (device-scope stores: another workgroup of this launch may merge them, see the row hand-over in the kernel)
+    if (lane < CV * 8 && (lane & (cpg - 1)) == 0) store_device(dst + (size_t)((co_w + lane) / cpg) * stats_stride, m);
+  };
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
 #pragma unroll
@@ -147,37 +177,18 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
         }
       }
     }
-  }
-  if (stats) {
-    // lane -> wavefront: every lane parks its 8 channels' (count, shift, sum, sum of squares) in the LDS patch;
-    // lane L then owns channel L of the wavefront's run, re-centres the entries of the lanes that held that
-    // channel (they differ in the pixel rows they read back) on one shift and adds them in a fixed order.
-    constexpr int CV = NI * 4;                 // octets per row of the patch
-    constexpr int ROWS = 64 / CV;              // lanes per octet
-    f32x4* park = reinterpret_cast<f32x4*>(lds);
+    if constexpr (HALVES) {   // the upper half of the tile's rows: a slot of its own, then the sums start again
+      if (mi == MI / 2 - 1 && stats) {
+        emit_moments(stats);
+        st_n = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) park[lane * 8 + e] = f32x4{st_n, st_shift[e], st_s[e], st_q[e]};
-    Moments m{0.f, 0.f, 0.f};
-    if (lane < CV * 8) {
-      float n0 = 0.f, a0 = 0.f, s0 = 0.f, q0 = 0.f;
-#pragma unroll
-      for (int r = 0; r < ROWS; ++r) {
-        const f32x4 en = park[r * (CV * 8) + lane];     // (row r, octet lane / 8, channel lane % 8)
-        if (en[0] > 0.f) {
-          if (n0 == 0.f) a0 = en[1];
-          const float d = en[1] - a0;
-          s0 += en[2] + en[0] * d;
-          q0 += en[3] + 2.f * d * en[2] + en[0] * d * d;
-          n0 += en[0];
-        }
+        for (int e = 0; e < 8; ++e) { st_s[e] = 0.f; st_q[e] = 0.f; }
       }
-      if (n0 > 0.f) { const float ds = s0 / n0; m.n = n0; m.mean = a0 + ds; m.m2 = fmaxf(q0 - s0 * ds, 0.f); }
     }
-    // channels of one group are cpg consecutive lanes
-    m = merge_to_first(m, lane, cpg);
-    // (device-scope stores: another workgroup of this launch may merge them, see the row hand-over in the kernel)
-    if (lane < CV * 8 && (lane & (cpg - 1)) == 0) store_device(stats + (size_t)((co_w + lane) / cpg) * stats_stride, m);
   }
+  if (!stats) return;
+  if constexpr (!HALVES) emit_moments(stats);
+  else if (half_stride) emit_moments(stats + half_stride);
 }
 
 // Ring length of the weight-fragment prefetch: it must divide the k-steps of a chunk so that the ring
@@ -282,7 +293,9 @@ constexpr int tile_buf_elems(int th, int tw, int pad, int kc) { return (th + 2 *
 // a chunk).  The whole-chunk ring is for launches that leave a compute unit at most two workgroups: there a wavefront
 // is alone on its SIMD, nothing else hides the latency of weights that come from beyond the L2 (every layer's weights
 // are new to the L2 inside a decoder run), and the registers of the third workgroup are free for it.
-template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int ACT, int RING = 0>
+// ROWS4: one of a pair of tiles, 4x16 and 8x16, of which the batch decides (see four_row_slots): a sample's bits must not
+// depend on that choice, so both keep the activation's roundings apart (PIN) and emit moments per four rows.
+template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int ACT, bool ROWS4 = false, int RING = 0>
 __global__ __launch_bounds__(64 * WM * WN, RING > 6 ? 2 : resident_workgroups(wave_m_tiles(TH, TW, WM) * NI, WM, WN))
 void conv_mfma_kernel(MfmaParams p) {
   static_assert(WM * WN == 4 || WM * WN == 8, "four or eight wavefronts");
@@ -401,7 +414,7 @@ void conv_mfma_kernel(MfmaParams p) {
     for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(xin + (unsigned)(src_off[i] + cb));
   };
   // word (two channels) of a staged vector: scale/shift (+ SiLU) with the table entries ab = (a0, b0, a1, b1)
-  auto activate_with = [&](uint32_t wv, const f32x4& ab) -> uint32_t { return wmdec::activate_word<T, ACT>(wv, ab); };
+  auto activate_with = [&](uint32_t wv, const f32x4& ab) -> uint32_t { return wmdec::activate_word<T, ACT, ROWS4>(wv, ab); };
   // table entries of word `part` of this thread's channel octet in the chunk that starts at channel c0
   auto table_entry = [&](int part, int c0) -> f32x4 {
     if constexpr (ACT > 0) return *reinterpret_cast<const f32x4*>(s_ab + c0 + cvec * 8 + 2 * part);
@@ -482,7 +495,7 @@ void conv_mfma_kernel(MfmaParams p) {
     const float k = ACT == 2 ? -1.4426950408889634f : 1.0f;
     if (p.rows_in) {
       // mean / rstd of every group from the row triples its producer left: eight lanes per group take the rows
-      // round-robin in order, then a fixed butterfly; (mean, rstd) parked behind the table
+      // round-robin; (mean, rstd) parked behind the table
       float2* s_stat = s_ab + p.cin;
       // Launches that leave a wavefront alone on its SIMD (RING): gamma / beta of this thread's first two table
       // entries are requested together with the triples, one memory round trip less in front of the first chunk
@@ -497,20 +510,8 @@ void conv_mfma_kernel(MfmaParams p) {
       const int sub = tid & 7;
       for (int g = tid >> 3; g < p.groups; g += NT / 8) {
         const Moments* row = p.rows_in + (size_t)(n * p.groups + g) * p.rows_in_count;
-        Moments m{0.f, 0.f, 0.f};
-        for (int r0 = sub; r0 < p.rows_in_count; r0 += 64) {   // eight loads in flight per lane before the first merge
-          Moments t[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int r = r0 + 8 * k;
-            t[k] = row[min(r, p.rows_in_count - 1)];
-            if (r >= p.rows_in_count) t[k].n = 0.f;
-          }
-#pragma unroll
-          for (int k = 0; k < 8; ++k) m = merge(m, t[k]);
-        }
-        m = merge_to_first(m, lane, 8);
-        if (sub == 0) s_stat[g] = make_float2(m.mean, 1.0f / sqrtf(m.m2 / m.n + p.eps));
+        const float2 m = merge_row<8>(row, p.rows_in_count, sub, p.eps);
+        if (sub == 0) s_stat[g] = m;
       }
       __syncthreads();
 #pragma unroll
@@ -583,22 +584,30 @@ void conv_mfma_kernel(MfmaParams p) {
   const T* rin = p.res ? reinterpret_cast<const T*>(p.res) + (size_t)n * p.h * p.w_out * p.cout : nullptr;
   float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(NI);
   // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row]
-  Moments* st = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + (tile * WM + wm) : nullptr;
+  constexpr bool HALVES = ROWS4 && TH == 8;
+  int slot = tile * WM + wm, half_stride = 0;
+  if constexpr (HALVES) {   // slots are numbered by rows of four; the lower half may lie below the image
+    slot = 2 * (tile / p.tiles_x) * p.tiles_x + tile % p.tiles_x;
+    half_stride = ty0 + 4 < p.h ? p.tiles_x : 0;
+  }
+  Moments* st = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + slot : nullptr;
   if (rin)
-    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
-                                                              p.bias2, rin, yout, p.h, p.w_out, p.cout, false, st, p.stats_cpg, p.stats_slots);
+    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true, HALVES>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
+                                                              p.bias2, rin, yout, p.h, p.w_out, p.cout, false, st, p.stats_cpg, p.stats_slots, half_stride);
   else
-    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
-                                                               p.bias2, rin, yout, p.h, p.w_out, p.cout, p.y_nchw != 0, st, p.stats_cpg, p.stats_slots);
+    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false, HALVES>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
+                                                               p.bias2, rin, yout, p.h, p.w_out, p.cout, p.y_nchw != 0, st, p.stats_cpg, p.stats_slots, half_stride);
 
   if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, co0, TN, WM, tid, lane);
 }
 
-template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int RING = 0>
+template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int RING = 0, bool ROWS4 = false>
 int launch_cfg(const ConvArgs& a, hipStream_t s) {
   constexpr int PAD = KS / 2;
   constexpr int TN = WN * NI * 32;
   MfmaParams p = conv_params(a, TH, TW, TN, WM, a.h, a.w);
+  if (ROWS4) p.stats_slots = ((a.h + 3) / 4) * p.tiles_x;
+  WMDEC_REQUIRE(!ROWS4 || !a.rows_out, WMDEC_ERR_UNSUPPORTED, "conv_mfma: this tile hands over no rows");
   const int rc = check_hand_over(p);
   if (rc != WMDEC_OK) return rc;
   p.w = a.wt;
@@ -614,9 +623,9 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
   const size_t patch = (size_t)(WM * WN) * patch_floats(NI) * sizeof(float);   // epilogue patches of the wavefronts
   if (smem < patch) smem = patch;
   WMDEC_REQUIRE(smem <= 80 * 1024, WMDEC_ERR_UNSUPPORTED, "conv_mfma: %zu bytes of LDS needed", smem);
-  void (*kern)(MfmaParams) = !p.norm ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 0, RING>
-                             : (a.silu ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 2, RING>
-                                       : conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 1, RING>);
+  void (*kern)(MfmaParams) = !p.norm ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 0, ROWS4, RING>
+                             : (a.silu ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 2, ROWS4, RING>
+                                       : conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 1, ROWS4, RING>);
   // once per instantiation and activation mode (80 KiB: two workgroups per compute unit)
   static std::once_flag attr_once[3];
   hipError_t attr_err = hipSuccess;
@@ -630,7 +639,7 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
 
 // Tile shapes: patch height x width, wavefront rows x columns, 32-channel tiles per wavefront.
 struct TileShape { int th, tw, wm, wn, ni; };
-enum TileId { T256x128 = 0, T128x128_ROW, T128x64_ROW, T128x64, T256x32, T128x128_1x4, T128x256, kNumTiles };
+enum TileId { T256x128 = 0, T128x128_ROW, T128x64_ROW, T128x64, T256x32, T128x128_1x4, T128x256, T64x128, T128x128_ROWS4, kNumTiles };
 constexpr TileShape kTiles[kNumTiles] = {
     {8, 32, 2, 2, 2},    // T256x128: 256 pixels x 128 channels (large 1x1 convolutions)
     {4, 32, 2, 2, 2},    // T128x128_ROW: 128 x 128 on a 4x32 patch (1x1 convolutions)
@@ -642,15 +651,28 @@ constexpr TileShape kTiles[kNumTiles] = {
     {8, 16, 1, 4, 2},    // T128x256: 128 x 256, every wavefront all pixels x 64 channels: a staged (normalised, activated) patch
                          //     feeds twice the channels, i.e. half the staging work and input traffic per MFMA; two
                          //     workgroups per compute unit
+    {4, 16, 1, 4, 1},    // T64x128: 64 x 128, T128x128_1x4 at half the height, for launches of at most one workgroup per compute unit
+    {8, 16, 1, 4, 1},    // T128x128_ROWS4: the same layers in larger batches
 };
 
-// which tile shape a launch uses; a function of the per-sample shape only, so that the tiling, hence every summation
-// order, does not depend on the batch
+// Layers whose 128 x 128 tiles leave half of the compute units empty at batch 1 and whose moments, per 4x16 block, are few
+// enough for the consumer to merge: 64 x 128 tiles where the launch still fits one round, 128 x 128 otherwise, with the same
+// order of summation and the same moments.  Measured, us, 64 x 128 against 128 x 128: 512 channels at 64x64 27.8 / 35.3, at
+// 45x80 26.2 / 34.1, 256 channels at 68x92 16.9 / 21.8; past one round 47.4 / 43.5 (64x64, two samples), 89 / 78 (four).
+bool four_row_slots(const ConvArgs& a) {
+  const long blocks = (long)((a.h + 3) / 4) * ((a.w + 15) / 16);
+  return a.ksize == 3 && !a.upsample && !a.y_nchw && a.cout % 128 == 0 && !a.rows_out && !a.wide_tiles && blocks <= 128 && blocks * (a.cout / 128) <= 256;
+}
+
+// which tile shape a launch uses; a function of the per-sample shape only (but for the pair above), so that every
+// summation order does not depend on the batch
 TileId pick_tile(const ConvArgs& a) {
   const long px = (long)a.h * a.w;
   const bool n128 = a.cout % 128 == 0;
   if (a.ksize == 3) {
     if (a.cout <= 32) return T256x32;
+    if (four_row_slots(a))
+      return (long)((a.h + 3) / 4) * ((a.w + 15) / 16) * (a.cout / 128) * a.n <= 256 ? T64x128 : T128x128_ROWS4;
     // 128 pixels x 128 channels with every wavefront on all pixels x 32 channels (three workgroups per compute unit):
     // measured against the 256-pixel tile and the 2x2 wavefront layout on every layer shape of the decoder, it is
     // equal or faster everywhere (128 -> 128 at 480x720: 110 against 120 us; 512 -> 512 at 60x90: 33.5 against 35.1)
@@ -681,6 +703,8 @@ int launch_3x3(const ConvArgs& a, hipStream_t s) {
     case T128x64: return launch_cfg<T, TO, 8, 16, 4, 1, 2, 3, 32>(a, s);
     case T128x128_1x4:
       return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32>(a, s);
+    case T64x128: return launch_cfg<T, TO, 4, 16, 1, 4, 1, 3, 32, 9, true>(a, s);
+    case T128x128_ROWS4: return launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 0, true>(a, s);
     case T128x256: return launch_cfg<T, TO, 8, 16, 1, 4, 2, 3, 32>(a, s);
     default: return launch_cfg<T, TO, 8, 32, 4, 1, 1, 3, 32>(a, s);
   }
@@ -729,6 +753,7 @@ int conv_mfma_stats_slots(const ConvArgs& a) {
   if ((cpg & (cpg - 1)) != 0 || cpg > 32) return 0;   // a group must sit inside one wavefront's 64-channel run
   const TileId t = pick_tile(a);
   const TileShape& ts = kTiles[t];
+  if (t == T64x128 || t == T128x128_ROWS4) return ((a.h + 3) / 4) * ((a.w + 15) / 16);
   return ((a.w + ts.tw - 1) / ts.tw) * ((a.h + ts.th - 1) / ts.th) * ts.wm;
 }
 
@@ -750,9 +775,9 @@ const char* conv_mfma_label(const ConvArgs& a) {
   const TileShape& ts = kTiles[t];
   const char* ty = a.op_dtype == WMDEC_BF16 ? "wmdec::bf16_t" : "wmdec::f16_t";
   const int act = a.mean == nullptr && a.rows_in == nullptr && !a.groups_norm ? 0 : (a.silu ? 2 : 1);
-  snprintf(buf, sizeof(buf), "conv_mfma_kernel<%s, %s, %d, %d, %d, %d, %d, %d, %d, %d, %d>", ty,
+  snprintf(buf, sizeof(buf), "conv_mfma_kernel<%s, %s, %d, %d, %d, %d, %d, %d, %d, %d, %s, %d>", ty,
            a.y_dtype == WMDEC_F32 ? "float" : ty, ts.th, ts.tw, ts.wm, ts.wn, ts.ni, a.ksize, kc, act,
-           a.ksize == 3 && whole_chunk_ring(a) ? 18 : 0);
+           t == T64x128 || t == T128x128_ROWS4 ? "true" : "false", a.ksize == 3 && whole_chunk_ring(a) ? 18 : t == T64x128 ? 9 : 0);
   return buf;
 }
 

@@ -64,10 +64,12 @@ def test_split_convolution_with_folded_shortcut(dtype, n, cin, cin2, cout, h, w)
     assert err <= (1e-5 if dtype == "f32" else G.TOL[dtype] / 2), err
 
 
+# the last three: images past the split path whose 64 x 128 and 128 x 128 tiles the batch decides between (one sample of
+# them fills at most one round); heights that end in either half of the larger tile
 @pytest.mark.parametrize("cin,cout,groups,h,w", [(512, 512, 32, 17, 23), (128, 256, 32, 33, 40), (64, 128, 32, 61, 47), (64, 64, 32, 9, 31), (64, 64, 64, 5, 3),
-                                                 (64, 256, 8, 13, 17)])
+                                                 (64, 256, 8, 13, 17), (128, 512, 32, 57, 45), (96, 256, 32, 68, 92), (64, 384, 48, 36, 90)])
 def test_moments_and_bits_do_not_depend_on_the_batch(cin, cout, groups, h, w):
-    """Batches of 1, 2 and 7 take different tiles: the sample they share, and its statistics, must agree bit for bit, and
+    """Batches of 1, 2 and 7 take different tiles (of either 16-bit kernel): the sample they share, and its statistics, must agree bit for bit, and
     the statistics with the oracle's of the stored tensor.  A workspace that only holds the wide tiles' fewer triples is
     served by the wide tiles."""
     c = case(42, "f16", 7, cin, cout, h, w)
