@@ -70,15 +70,6 @@ template <typename T, int ACT, bool PIN = false> __device__ __forceinline__ uint
   return wv;
 }
 
-// Sum over LANES (8 or 16) consecutive lanes, left in all of them (data-parallel moves: xor 1, xor 2, mirrors of 8 and 16).
-template <int LANES> __device__ __forceinline__ float lanes_sum(float v) {
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true));
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xf, 0xf, true));
-  if constexpr (LANES == 16) v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xf, 0xf, true));
-  return v;
-}
-
 // (mean, rstd) of a group from the `count` triples of its row, merged by LANES consecutive lanes (all of them active), eight
 // loads in flight per lane: weighted sums of the differences to the first triple's mean instead of a chain of pairwise
 // merges with a reciprocal each, which stood in front of every layer's first chunk.

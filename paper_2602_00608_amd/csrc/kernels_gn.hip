@@ -76,6 +76,8 @@ __global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict_
   constexpr int V = Vec16<T>::N;
   constexpr int U = 8;
   __shared__ float2 s_e[kVecThreads * V];   // (sum, sum of squares) per (pixel lane, channel)
+  __shared__ float2 s_p[kVecThreads];       // the same per (part of the pixel lanes, channel)
+  __shared__ float s_shift[kVecThreads];    // the shift of every channel
   __shared__ Moments s_g[kVecMaxGroups];    // the slab's moments per group
   __shared__ unsigned s_last;
   const int tid = threadIdx.x;
@@ -99,20 +101,40 @@ __global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict_
 
 #pragma unroll
   for (int j = 0; j < V; ++j) s_e[(tid / vp) * c + cv * V + j] = float2{s[j], q[j]};
+  if (tid < vp) {
+#pragma unroll
+    for (int j = 0; j < V; ++j) s_shift[tid * V + j] = shift[j];
+  }
+  __syncthreads();
+  // all threads take V of a channel's ppi entries each (c is a power of two <= 1024 here), then one per channel the parts:
+  // with a thread per channel alone the walk over 64 entries at 64 channels was a quarter of a small tensor's time
+  const int parts = kVecThreads / c;
+  {
+    const int ch = tid % c;
+    float s0 = 0.f, q0 = 0.f;
+#pragma unroll
+    for (int k = 0; k < V; ++k) { const float2 e = s_e[(tid / c + k * parts) * c + ch]; s0 += e.x; q0 += e.y; }
+    s_p[tid] = float2{s0, q0};
+  }
   __syncthreads();
   const int cpg = c / groups;
   const float cnt = (float)(p1 - p0);
   for (int ch = tid; ch < c; ch += kVecThreads) {
     float s0 = 0.f, q0 = 0.f;
 #pragma unroll 8
-    for (int r = 0; r < ppi; ++r) { const float2 e = s_e[r * c + ch]; s0 += e.x; q0 += e.y; }
-    // every thread of a channel used the same shift: the slab's first pixel
-    const float a0 = to_float(x[((size_t)n * pixels + p0) * c + ch]);
+    for (int r = 0; r < parts; ++r) { const float2 e = s_p[r * c + ch]; s0 += e.x; q0 += e.y; }
+    const float a0 = s_shift[ch];   // every thread of a channel used the same shift: the slab's first pixel
     const float ds = s0 / cnt;
     Moments m{cnt, a0 + ds, fmaxf(q0 - s0 * ds, 0.f)};
     for (int mask = 1; mask < cpg; mask <<= 1) m = butterfly(m, tid, mask);   // cpg consecutive lanes = one group
-    if ((ch & (cpg - 1)) == 0) s_g[ch / cpg] = m;
+    if ((ch & (cpg - 1)) == 0) {
+      if (chunks == 1) {   // a slab is the sample: nothing to hand over
+        mean[n * groups + ch / cpg] = m.mean;
+        rstd[n * groups + ch / cpg] = 1.0f / sqrtf(m.m2 / m.n + eps);
+      } else s_g[ch / cpg] = m;
+    }
   }
+  if (chunks == 1) return;
   __syncthreads();
 
   // One wavefront publishes the slab's triples and takes the sample's ticket.  No fences (a fence walks the whole
@@ -126,24 +148,30 @@ __global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict_
   }
   __syncthreads();
   if (!s_last) return;
-  // half a wavefront per group, 8 slots per lane, merged in a fixed order
+  // half a wavefront per group, 8 slots per lane: weighted sums of the differences to the first slab's mean, in a fixed order
   const int sub = tid & 31, half = tid >> 5;
   for (int g = half; g < groups; g += kVecThreads / 32) {
     const Moments* row = ws + ((size_t)n * groups + g) * chunks;
     Moments t[kVecMaxChunks / 32];
+    const float first = load_device(row).mean;
 #pragma unroll
     for (int k = 0; k < kVecMaxChunks / 32; ++k) {
       const int i = sub + 32 * k;
       t[k] = load_device(row + min(i, chunks - 1));
-      if (i >= chunks) t[k].n = 0.f;
+      if (i >= chunks) { t[k].n = 0.f; t[k].m2 = 0.f; }
     }
-    Moments m = t[0];
+    float cn = 0.f, sd = 0.f, sq = 0.f;
 #pragma unroll
-    for (int k = 1; k < kVecMaxChunks / 32; ++k) m = merge(m, t[k]);
-    for (int mask = 1; mask < 32; mask <<= 1) m = butterfly(m, sub, mask);
+    for (int k = 0; k < kVecMaxChunks / 32; ++k) {
+      const float d = t[k].mean - first, nd = t[k].n * d;
+      cn += t[k].n; sd += nd; sq += fmaf(nd, d, t[k].m2);
+    }
+    cn = lanes_sum<16>(cn); sd = lanes_sum<16>(sd); sq = lanes_sum<16>(sq);
+    cn += __shfl_xor(cn, 16); sd += __shfl_xor(sd, 16); sq += __shfl_xor(sq, 16);
     if (sub == 0) {
-      mean[n * groups + g] = m.mean;
-      rstd[n * groups + g] = 1.0f / sqrtf(m.m2 / m.n + eps);
+      const float d = sd / cn;
+      mean[n * groups + g] = first + d;
+      rstd[n * groups + g] = 1.0f / sqrtf(fmaxf(sq - sd * d, 0.f) / cn + eps);
     }
   }
 }
@@ -219,6 +247,9 @@ int pick_chunks(int pixels, int c, int V, bool vec) {
   // Never a function of the batch size: a sample's result must not depend on its neighbours.
   const int ppi = vec ? kVecThreads / (c / V) : 1;
   const int min_chunk = vec ? 4 * ppi : 1024;
+  // A tensor of at most 16 sweeps (256 KiB a sample) stays with one workgroup: streaming it alone takes less than the
+  // hand-over's three memory round trips.
+  if (vec && pixels <= 16 * ppi) return 1;
   int chunks = (pixels + min_chunk - 1) / min_chunk;
   const int cap = vec ? kVecMaxChunks : 2048;
   if (chunks > cap) chunks = cap;

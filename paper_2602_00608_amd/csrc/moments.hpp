@@ -54,6 +54,15 @@ __device__ __forceinline__ Moments merge_to_first(Moments m, int lane, int width
   return m;
 }
 
+// Sum over LANES (8 or 16) consecutive lanes, left in all of them (data-parallel moves: xor 1, xor 2, mirrors of 8 and 16).
+template <int LANES> __device__ __forceinline__ float lanes_sum(float v) {
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true));
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xf, 0xf, true));
+  if constexpr (LANES == 16) v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xf, 0xf, true));
+  return v;
+}
+
 // Device-scope (write-through / L2-bypassing) accesses of a triple and the wait that orders a wavefront's stores before
 // a ticket it takes afterwards: the hand-over between workgroups of one launch that both the single-launch statistics
 // kernel and the convolution epilogue use (gfx950; see the note at the top of kernels_gn.hip).
