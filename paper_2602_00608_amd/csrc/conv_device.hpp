@@ -87,7 +87,7 @@ __device__ __forceinline__ float2 merge_row(const Moments* row, int count, int s
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const float d = t[k].mean - shift, nd = t[k].n * d;
+      const float d = t[k].n > 0.f ? t[k].mean - shift : 0.f, nd = t[k].n * d;   // an empty triple's mean has no meaning
       n += t[k].n; s += nd; q += fmaf(nd, d, t[k].m2);
     }
   }

@@ -266,8 +266,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_mfma_kernel(MfmaParams p
       for (int k = 0; k < NS; ++k) {
         float s = half_sum(ss[k]), t = half_sum(sq[k]), cnt = 4.f * CH * (float)live_px;
         if (!FINE && cpg >= 8) { s += __shfl_xor(s, 32); t += __shfl_xor(t, 32); cnt *= 2.f; }
+        // without a finished pixel sh is a value outside the image, possibly not finite: an empty triple, all zeros
         const float ds = live_px > 0 ? s / cnt : 0.f;
-        const Moments m{cnt, sh[k] + ds, fmaxf(t - s * ds, 0.f)};
+        const Moments m{cnt, live_px > 0 ? sh[k] + ds : 0.f, fmaxf(t - s * ds, 0.f)};
         if constexpr (FINE) mq[k % 4] = m;
         else mq[2 * qp + k] = m;
         if (FINE && k % 4 == 3 && lm == 0) {   // one quad's channels

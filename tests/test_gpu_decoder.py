@@ -232,6 +232,36 @@ def test_decoder_reduced_size(dtype):
     assert np.array_equal(one[0], got[1])
 
 
+def test_statistics_of_an_upsampling_convolution_ignore_positions_outside_the_image():
+    """A tile of the upsampling convolution forms values below the image too, from the taps of the last image row alone.
+    Here these overflow f16 (weights +16 and -16 in the two upper tap rows of a channel, a ramp of activations: the taps
+    of one row reach 1e5, every output stays below 1.5e4), in a wavefront that finishes no pixel at all (11 = 7 + 4 rows):
+    the moments of the tensor, and with them the frame, must not see them."""
+    cfg = small_cfg(wmdec.F16)
+    cfg.latent_h, cfg.latent_w, cfg.resblocks_per_level = 11, 9, 1
+    chans = (512, 128, 64, 32)
+    weights = synth.draw_params(synth.decoder_weight_spec(level_channels=chans, resblocks_per_level=1), synth.weight_seed(14))
+    r = np.random.default_rng(synth.input_seed(14))
+    for name in ("mid.res1.conv2", "mid.attn.proj", "mid.res2.conv2", "up.0.res0.conv2"):   # up to here the blocks pass x on
+        weights[name + ".w"][:] = 0
+        weights[name + ".b"][:] = 0
+    weights["conv_in.w"][:] = 0
+    weights["conv_in.w"][:, 0, 1, 1] = r.choice([0.75, 1.0], 512)   # times z (8 bits): exact in f16, so that the
+    # difference of two rows, a tenth of a row, carries no rounding of x (2^-11 of it would be 0.5 % of the difference)
+    up = weights["up.0.upsample.w"]
+    up[:] = 0
+    up[np.arange(512), np.arange(512), 0, 1], up[np.arange(512), np.arange(512), 1, 1] = 16, -16
+    weights["up.1.res0.shortcut.w"] = synth.bf16_round(0.1 * weights["up.1.res0.shortcut.w"])
+    z = np.zeros((1, 4, 11, 9), np.float32)
+    z[0, 0] = (6250 / 10 * np.arange(11))[:, None] * np.linspace(1.0, 0.8, 9)[None, :]
+    z = synth.bf16_round(z)
+    got = run_decoder(cfg, weights, z)
+    assert np.isfinite(got).all()
+    want = ref.decoder(z, weights, level_channels=chans, resblocks_per_level=1, groups=32, eps=1e-6)
+    err = ref.rel_err(got, want)
+    assert err <= G.TOL["f16"], err
+
+
 @pytest.mark.parametrize("dtype,last", [("f16", 128), ("bf16", 128), ("f16", 64)])
 def test_last_convolution_as_taps_contraction(dtype, last):
     """The decoder's last layer (few output channels, planar fp32 frame) runs as a 1x1 contraction onto (tap, channel)
