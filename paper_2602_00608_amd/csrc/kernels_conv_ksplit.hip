@@ -73,8 +73,8 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
 
   extern __shared__ __align__(16) unsigned char smem[];
   float2* s_ab = reinterpret_cast<float2*>(smem + 2 * BUFB);       // [cin] (scale, shift)
-  float2* s_stat = s_ab + p.cin;                                   // [groups] (mean, rstd)
-  float* s_mu = reinterpret_cast<float*>(s_stat + p.groups);       // [cin] mean per channel (fp32 only)
+  float* s_mu = reinterpret_cast<float*>(s_ab + p.cin);            // [cin] mean per channel (fp32 only), read as 16-byte vectors
+  float2* s_stat = reinterpret_cast<float2*>(s_mu + (ES == 4 ? p.cin : 0));   // [groups] (mean, rstd): any number, so it comes last
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

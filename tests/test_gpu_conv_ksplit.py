@@ -48,6 +48,21 @@ def test_split_convolution(dtype, n, cin, cout, h, w, norm):
     assert err <= (1e-5 if dtype == "f32" else G.TOL[dtype] / 2), err
 
 
+# any group count: the table of per-channel means behind the scale/shift table is read as 16-byte vectors
+@pytest.mark.parametrize("dtype,cin,cout,groups,h,w", [("f32", 64, 32, 1, 5, 9), ("f32", 96, 64, 3, 9, 7), ("f32", 32, 32, 1, 1, 1), ("f16", 64, 64, 1, 5, 9),
+                                                       ("bf16", 192, 64, 3, 9, 7)])
+def test_split_convolution_with_an_odd_number_of_groups(dtype, cin, cout, groups, h, w):
+    c = case(43, dtype, 2, cin, cout, h, w)
+    xd = G.dev_nhwc(c["x"], dtype)
+    mean, rstd = G.gn_stats(xd, groups, EPS)
+    y, check = G.canaried((2, h, w, cout), torch.float32)
+    wmdec.gn_silu_conv3x3(xd, mean, rstd, G.dev_f32(c["gamma"]), G.dev_f32(c["beta"]), groups, True, G.pack(c["w"], dtype), G.dev_f32(c["b"]), None, y)
+    torch.cuda.synchronize()
+    check()
+    err = ref.rel_err(G.host_nchw(y), ref.conv2d(ref.group_norm(c["x"], groups, EPS, c["gamma"], c["beta"], apply_silu=True), c["w"], c["b"]))
+    assert err <= (1e-5 if dtype == "f32" else G.TOL[dtype] / 2), err
+
+
 @pytest.mark.parametrize("dtype,n,cin,cin2,cout,h,w", [("f16", 1, 128, 256, 128, 17, 23), ("bf16", 2, 256, 512, 256, 30, 44), ("f32", 1, 64, 128, 64, 9, 11),
                                                        ("f32", 1, 96, 32, 32, 7, 9)])
 def test_split_convolution_with_folded_shortcut(dtype, n, cin, cin2, cout, h, w):
