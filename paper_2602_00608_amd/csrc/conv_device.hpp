@@ -131,6 +131,12 @@ __device__ __forceinline__ void hand_over_row(const MfmaParams& p, int n, int ti
   }
 }
 
+// The kernels address packed weights by 32-bit byte offsets, and a fragment past the last round by one of 0x7fff0000:
+// larger layers are left to the general kernel.
+inline bool packed_offsets_fit(int taps, int cout, int cin, int op_dtype) {
+  return packed_elems(taps, cout, cin) * dtype_size(op_dtype) < 0x7fff0000u;
+}
+
 // Launch parameters of a th x tw tile (on an h_t x w_t grid) with tn output channels and slots_per_tile moment triples;
 // the weights and the shortcut are the caller's.
 inline MfmaParams conv_params(const ConvArgs& a, int th, int tw, int tn, int slots_per_tile, int h_t, int w_t) {

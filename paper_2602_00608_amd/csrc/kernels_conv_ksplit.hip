@@ -476,6 +476,7 @@ bool conv_ksplit_supported(const ConvArgs& a) {
   if (a.res && a.res_dtype != a.op_dtype) return false;
   if (a.y_dtype != a.op_dtype && a.y_dtype != WMDEC_F32) return false;
   if (a.cin > 2048 || a.cin2 > 2048 || a.groups > 2048) return false;   // scale/shift table in LDS
+  if (!packed_offsets_fit(9, a.cout, a.cin, a.op_dtype) || !packed_offsets_fit(1, a.cout, a.cin2, a.op_dtype)) return false;
   if ((long)a.h * a.w * a.cin >= (1L << 29) || (long)a.h * a.w * a.cout >= (1L << 29) || (long)a.h * a.w * a.cin2 >= (1L << 29)) return false;
   if (a.op_dtype == WMDEC_F32) return a.cin % 32 == 0 && a.cin2 % (a.cin % 64 == 0 ? 64 : 32) == 0 && a.cout % 32 == 0 && !a.stats_ws;
   return is_16bit(a.op_dtype) && a.cin % 64 == 0 && a.cin2 % 64 == 0 && a.cout % 64 == 0 && (long)a.h * a.w * a.cout <= (1L << 20);

@@ -743,6 +743,7 @@ bool conv_mfma_supported(const ConvArgs& a) {
   if (a.cout % 64 != 0 && !(a.y_nchw && a.cout <= 32)) return false;
   if (a.cin > 2048) return false;   // scale/shift table lives in LDS
   if (a.ksize != 1 && a.ksize != 3) return false;
+  if (!packed_offsets_fit(a.ksize * a.ksize, a.cout, a.cin, a.op_dtype) || !packed_offsets_fit(1, a.cout, a.cin2, a.op_dtype)) return false;
   if ((long)a.h * a.w * a.cin >= (1L << 29) || (long)a.h * a.w * a.cout >= (1L << 29)) return false;   // 32-bit byte offsets per sample
   return true;
 }

@@ -317,7 +317,7 @@ int launch_up(const ConvArgs& a, hipStream_t s) {
 bool conv_up_supported(const ConvArgs& a) {
   if (a.ksize != 3 || !a.upsample || !is_16bit(a.op_dtype) || a.x_dtype != a.op_dtype || a.x_nchw || a.y_nchw) return false;
   if (a.mean || a.groups_norm || a.rows_in || a.res || a.x2 || a.cin2 || (a.y_dtype != a.op_dtype && a.y_dtype != WMDEC_F32)) return false;
-  if (a.cin % KC != 0 || a.cout % kTN != 0 || a.h % 2 != 0 || a.w % 2 != 0) return false;
+  if (a.cin % KC != 0 || a.cout % kTN != 0 || a.h % 2 != 0 || a.w % 2 != 0 || !packed_offsets_fit(9, a.cout, a.cin, a.op_dtype)) return false;
   if (a.stats_ws && conv_up_stats_slots(a) == 0) return false;
   // 32-bit byte offsets per sample, with room for the offset of a dropped store
   return (long)(a.h / 2) * (a.w / 2) * a.cin < (1L << 29) && (long)a.h * a.w * a.cout * (long)dtype_size(a.y_dtype) < 0x7f000000L;

@@ -125,6 +125,23 @@ def test_step_accounting_adds_up():
     dec.close()
 
 
+def test_layers_whose_packed_weights_pass_32_bit_offsets_take_the_general_kernel():
+    """9 * cin * cout * 2 bytes of weights from 2^31 on: no matrix-core kernel may take the layer (their fragment offsets and
+    buffer sizes have 32 bits).  Only the dispatch is asked; nothing of that size is allocated."""
+    cfg = wmdec.decoder_default_config()
+    cfg.latent_h = cfg.latent_w = 2
+    cfg.num_levels, cfg.resblocks_per_level = 3, 1
+    for ch, label in ((10240, "conv_mfma_kernel<"), (16384, "conv_direct_kernel")):   # 1.9e9 and 4.8e9 bytes
+        cfg.level_channels[0], cfg.level_channels[1], cfg.level_channels[2] = 512, ch, 32
+        dec = wmdec.Decoder(cfg)
+        up = [k for k, f, _ in dec.step_info() if f in (2.0 * 9 * ch * ch * 64 * s for s in (1, 4 / 9, 1 / 4))]
+        assert up and up[-1].startswith(label), (ch, up)   # (the last of them: a ResBlock convolution a level below has a quarter of the dense count)
+        dec.close()
+    size = wmdec.lib().wmdec_conv_stats_workspace_bytes
+    assert size(wmdec.F16, wmdec.F16, 1, 4, 4, 2048, 32768, 2048) > 0
+    assert size(wmdec.F16, wmdec.F16, 1, 4, 4, 2048, 65536, 2048) == 0
+
+
 def test_argument_errors_are_reported_without_a_gpu():
     l = wmdec.lib()
     assert l.wmdec_gn_stats(None, 0, 1, 1, 1, 32, 32, 1e-6, None, None, None, 0, None) == wmdec.ERR_INVALID_ARG
