@@ -71,29 +71,47 @@ template <typename T, int ACT, bool PIN = false> __device__ __forceinline__ uint
 }
 
 // (mean, rstd) of a group from the `count` triples of its row, merged by LANES consecutive lanes (all of them active), eight
-// loads in flight per lane: weighted sums of the differences to the first triple's mean instead of a chain of pairwise
-// merges with a reciprocal each, which stood in front of every layer's first chunk.
+// loads in flight per lane: the mean first, then the differences to it and their squares, from the same registers.  (A chain
+// of pairwise merges has a reciprocal each and stood in front of every layer's first chunk; one pass of sums about the
+// first triple's mean cancels where that triple is an outlier: 1e-5 of the variance at 100 standard deviations.)  Triples
+// past 8 * LANES are summed about the mean of those, at least half of the row, which costs a factor of two at most.
 template <int LANES>
 __device__ __forceinline__ float2 merge_row(const Moments* row, int count, int sub, float eps) {
-  const float shift = row[0].mean;
-  float n = 0.f, s = 0.f, q = 0.f;
-  for (int r0 = sub; r0 < count; r0 += 8 * LANES) {
-    Moments t[8];
+  const float first = row[0].mean;
+  Moments t[8];
+  auto load = [&](int r0) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       const int r = r0 + LANES * k;
       t[k] = row[min(r, count - 1)];
       if (r >= count) { t[k].n = 0.f; t[k].m2 = 0.f; }
     }
+  };
+  float n = 0.f, s = 0.f, q = 0.f;
+  auto add = [&](float shift) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       const float d = t[k].n > 0.f ? t[k].mean - shift : 0.f, nd = t[k].n * d;   // an empty triple's mean has no meaning
       n += t[k].n; s += nd; q += fmaf(nd, d, t[k].m2);
     }
+  };
+  load(sub);
+  add(first);
+  const float head = lanes_sum<LANES>(n);
+  const float mean = first + lanes_sum<LANES>(s) * __builtin_amdgcn_rcpf(head);
+  n = 0.f; s = 0.f; q = 0.f;
+  add(mean);
+  if (count > 8 * LANES) {
+    n = 0.f;
+    for (int r0 = sub + 8 * LANES; r0 < count + sub; r0 += 8 * LANES) { load(r0); add(mean); }
+    n = head + lanes_sum<LANES>(n);
+  } else {
+    n = head;
   }
-  n = lanes_sum<LANES>(n); s = lanes_sum<LANES>(s); q = lanes_sum<LANES>(q);
-  const float d = s / n;
-  return make_float2(shift + d, 1.0f / sqrtf(fmaxf(q - s * d, 0.f) / n + eps));
+  s = lanes_sum<LANES>(s); q = lanes_sum<LANES>(q);
+  const float d = s * __builtin_amdgcn_rcpf(n);     // (also what the roundings of `mean` left)
+  q -= s * d;
+  return make_float2(mean + d, 1.0f / sqrtf((q < 0.f ? 0.f : q) / n + eps));   // (NaN stays NaN)
 }
 
 // Row hand-over: the workgroup that finishes a (sample, tile row, channel tile) last merges that row's triples.  Same

@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict_
   }
   __syncthreads();
   if (!s_last) return;
-  // half a wavefront per group, 8 slots per lane: weighted sums of the differences to the first slab's mean, in a fixed order
+  // half a wavefront per group, 8 slots per lane: the mean, then the differences to it and their squares, in a fixed order
   const int sub = tid & 31, half = tid >> 5;
   for (int g = half; g < groups; g += kVecThreads / 32) {
     const Moments* row = ws + ((size_t)n * groups + g) * chunks;
@@ -162,16 +162,18 @@ __global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict_
     }
     float cn = 0.f, sd = 0.f, sq = 0.f;
 #pragma unroll
-    for (int k = 0; k < kVecMaxChunks / 32; ++k) {
-      const float d = t[k].mean - first, nd = t[k].n * d;
-      cn += t[k].n; sd += nd; sq += fmaf(nd, d, t[k].m2);
-    }
-    cn = lanes_sum<16>(cn); sd = lanes_sum<16>(sd); sq = lanes_sum<16>(sq);
-    cn += __shfl_xor(cn, 16); sd += __shfl_xor(sd, 16); sq += __shfl_xor(sq, 16);
+    for (int k = 0; k < kVecMaxChunks / 32; ++k) { cn += t[k].n; sd = fmaf(t[k].n, t[k].mean - first, sd); }
+    cn = lanes_sum<16>(cn); sd = lanes_sum<16>(sd);
+    cn += __shfl_xor(cn, 16); sd += __shfl_xor(sd, 16);
+    const float m = first + sd / cn;
+    sd = 0.f;
+#pragma unroll
+    for (int k = 0; k < kVecMaxChunks / 32; ++k) { const float d = t[k].mean - m, nd = t[k].n * d; sd += nd; sq += fmaf(nd, d, t[k].m2); }
+    sd = lanes_sum<16>(sd); sq = lanes_sum<16>(sq);
+    sd += __shfl_xor(sd, 16); sq += __shfl_xor(sq, 16);
     if (sub == 0) {
-      const float d = sd / cn;
-      mean[n * groups + g] = first + d;
-      rstd[n * groups + g] = 1.0f / sqrtf(fmaxf(sq - sd * d, 0.f) / cn + eps);
+      mean[n * groups + g] = m + sd / cn;    // what the rounding of m left
+      rstd[n * groups + g] = 1.0f / sqrtf(sq / cn + eps);
     }
   }
 }

@@ -52,6 +52,33 @@ def test_gn_stats_large_offset_no_cancellation():
     assert np.max(np.abs(mean.cpu().numpy() - wm.ravel())) < 1e-4
 
 
+@pytest.mark.parametrize("rows,offset", [(1, 10.0), (1, 100.0), (4, 100.0)])
+def test_gn_stats_with_a_first_band_off_the_rest(rows, offset):
+    """A letterboxed image: the first slab's mean lies `offset` standard deviations from the others'.  Two passes over the
+    triples round each of some 13 sequential additions (8 per lane, 5 levels across lanes) once: 13 * 2^-24 = 8e-7 at worst
+    for the variance, as the sums inside a slab do; one pass about the first triple's mean was off by 1e-5."""
+    x = rng(5).standard_normal((1, 256, 120, 180)).astype(np.float32)
+    x[:, :, :rows] += offset
+    mean, rstd = G.gn_stats(G.dev_nhwc(x, "f32"), 32, 1e-6)
+    wm, wr = ref.gn_stats(x, 32, 1e-6)
+    assert np.max(np.abs(rstd.cpu().numpy() / wr.ravel() - 1.0)) < 1e-6
+    assert np.max(np.abs(mean.cpu().numpy() - wm.ravel()) * wr.ravel()) < 5e-7
+
+
+@pytest.mark.parametrize("h,w", [(120, 180)])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("last", [False, True])
+def test_gn_stats_of_a_group_that_is_not_finite(h, w, bad, last):
+    """One infinity or NaN: the group's rstd must not look like one of finite data; the other groups keep their bits."""
+    x = rng(6).standard_normal((1, 64, h, w)).astype(np.float32)
+    good = G.gn_stats(G.dev_nhwc(x, "f32"), 32, 1e-6)
+    x[0, 6, -1 if last else 0, 0] = bad      # group 3
+    mean, rstd = G.gn_stats(G.dev_nhwc(x, "f32"), 32, 1e-6)
+    assert not torch.isfinite(mean[3]) and not bool(rstd[3] > 0)
+    keep = [g for g in range(32) if g != 3]
+    assert torch.equal(mean[keep], good[0][keep]) and torch.equal(rstd[keep], good[1][keep])
+
+
 def test_gn_stats_deterministic():
     x = G.dev_nhwc(G.stored(rng(3).standard_normal((2, 128, 61, 47)), "bf16"), "bf16")
     a = G.gn_stats(x, 32, 1e-6)
