@@ -5,8 +5,8 @@
 // 16-byte vector loads (every thread keeps a fixed set of channels), accumulates
 // shifted sums in fp32 (so that E[d^2]-E[d]^2 never cancels) and produces one
 // (count, mean, M2) triple per group.  Triples are merged with the pairwise
-// update of Chan et al. in a fixed order, so the result does not depend on
-// scheduling.  Channel counts that fit the vector layout take the single-launch
+// update of Chan et al., or many at a time about their common mean, in a fixed
+// order, so the result does not depend on scheduling.  Channel counts that fit the vector layout take the single-launch
 // kernel gn_stats_vec, whose last workgroup per sample does the merge; everything
 // else takes gn_partial_any followed by gn_finalize, which also merges the
 // moments a convolution emitted from its epilogue.
@@ -39,9 +39,9 @@ template <> struct alignas(16) Vec16<f16_t> { static constexpr int N = 8; f16_t 
 // Fast path: c % V == 0, vp = c / V divides 1024, channels per group a power of two <= 64.
 // grid = (chunks, n), 1024 threads.  ws: [n][groups][chunks] Moments.  One launch does everything: a workgroup
 // streams its slab (8 loads of 16 bytes in flight per thread, the ragged end as one masked batch), sums
-// x - shift and its square per thread (shift = the slab's first pixel, shared by all threads of a channel),
-// adds the threads of a channel in a fixed order through LDS, the channels of a group with a butterfly, and
-// writes one triple per group.  The workgroup of a sample that finishes last (one wrapping ticket counter per
+// x - shift and its square per thread (shift = the thread's first pixel, so that an outlier costs only the sums of
+// the thread that starts with it), merges the (mean, M2) of a channel's threads in a fixed order through LDS, the
+// channels of a group with a butterfly, and writes one triple per group.  The workgroup of a sample that finishes last (one wrapping ticket counter per
 // sample, which returns to zero by itself) merges the sample's triples in a fixed order into mean / rstd.
 constexpr int kVecThreads = 1024;
 constexpr int kVecMaxChunks = 256;
@@ -69,15 +69,35 @@ __device__ __forceinline__ void gn_accumulate(const Vec16<T>* base, int p, int p
   }
 }
 
+// Merge of the triples at(0), ..., at(COUNT-1), or of `count` of them if COUNT is 0: the mean first, then the differences to it and their squares.
+template <int COUNT, typename At> __device__ __forceinline__ Moments merge_all(At&& at, int count = COUNT) {
+  const float first = at(0).mean;
+  Moments m{0.f, 0.f, 0.f};
+  float s = 0.f;
+#pragma unroll 8
+  for (int k = 0; k < (COUNT ? COUNT : count); ++k) { const Moments t = at(k); m.n += t.n; s = fmaf(t.n, t.mean - first, s); }
+  if (m.n == 0.f) return m;
+  const float inv = 1.0f / m.n;
+  m.mean = fmaf(s, inv, first);
+  s = 0.f;
+#pragma unroll 8
+  for (int k = 0; k < (COUNT ? COUNT : count); ++k) {
+    const Moments t = at(k);
+    const float d = t.mean - m.mean, nd = t.n * d;
+    s += nd; m.m2 += fmaf(nd, d, t.m2);
+  }
+  m.mean = fmaf(s, inv, m.mean);    // what the rounding of the mean left
+  return m;
+}
+
 template <typename T>
 __global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict__ x, int pixels, int c, int groups,
                                                             int chunk_pixels, Moments* ws, unsigned* ticket, float eps,
                                                             float* __restrict__ mean, float* __restrict__ rstd) {
   constexpr int V = Vec16<T>::N;
   constexpr int U = 8;
-  __shared__ float2 s_e[kVecThreads * V];   // (sum, sum of squares) per (pixel lane, channel)
-  __shared__ float2 s_p[kVecThreads];       // the same per (part of the pixel lanes, channel)
-  __shared__ float s_shift[kVecThreads];    // the shift of every channel
+  __shared__ float2 s_e[kVecThreads * V];   // (mean, M2) per (pixel lane, channel)
+  __shared__ Moments s_p[kVecThreads];      // triples per (part of the pixel lanes, channel)
   __shared__ Moments s_g[kVecMaxGroups];    // the slab's moments per group
   __shared__ unsigned s_last;
   const int tid = threadIdx.x;
@@ -89,43 +109,39 @@ __global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict_
   const int p1 = min(p0 + chunk_pixels, pixels);
   const Vec16<T>* base = reinterpret_cast<const Vec16<T>*>(x + (size_t)n * pixels * c) + cv;
 
+  int p = p0 + tid / vp;
   float shift[V], s[V], q[V];
   {
-    const Vec16<T> v = base[(size_t)p0 * vp];
+    const Vec16<T> v = base[(size_t)min(p, p1 - 1) * vp];
 #pragma unroll
     for (int j = 0; j < V; ++j) { shift[j] = to_float(v.v[j]); s[j] = 0.f; q[j] = 0.f; }
   }
-  int p = p0 + tid / vp;
   for (; p + (U - 1) * ppi < p1; p += U * ppi) gn_accumulate<T, V, false>(base, p, p1, ppi, vp, shift, s, q);
   if (p < p1) gn_accumulate<T, V, true>(base, p, p1, ppi, vp, shift, s, q);
 
+  const int sweeps = (p1 - p0) / ppi, rest = (p1 - p0) % ppi;
+  auto lane_pixels = [&](int lane) { return (float)(sweeps + (lane < rest ? 1 : 0)); };   // pixels of a pixel lane
+  {
+    const float cnt = lane_pixels(tid / vp), inv = cnt > 0.f ? 1.0f / cnt : 0.f;
 #pragma unroll
-  for (int j = 0; j < V; ++j) s_e[(tid / vp) * c + cv * V + j] = float2{s[j], q[j]};
-  if (tid < vp) {
-#pragma unroll
-    for (int j = 0; j < V; ++j) s_shift[tid * V + j] = shift[j];
+    for (int j = 0; j < V; ++j) {
+      const float ds = s[j] * inv, m2 = q[j] - s[j] * ds;
+      s_e[(tid / vp) * c + cv * V + j] = float2{shift[j] + ds, m2 < 0.f ? 0.f : m2};   // (NaN stays NaN)
+    }
   }
   __syncthreads();
   // all threads take V of a channel's ppi entries each (c is a power of two <= 1024 here), then one per channel the parts:
   // with a thread per channel alone the walk over 64 entries at 64 channels was a quarter of a small tensor's time
   const int parts = kVecThreads / c;
-  {
-    const int ch = tid % c;
-    float s0 = 0.f, q0 = 0.f;
-#pragma unroll
-    for (int k = 0; k < V; ++k) { const float2 e = s_e[(tid / c + k * parts) * c + ch]; s0 += e.x; q0 += e.y; }
-    s_p[tid] = float2{s0, q0};
-  }
+  s_p[tid] = merge_all<V>([&](int k) {
+    const int r = tid / c + k * parts;
+    const float2 e = s_e[r * c + tid % c];
+    return Moments{lane_pixels(r), e.x, e.y};
+  });
   __syncthreads();
   const int cpg = c / groups;
-  const float cnt = (float)(p1 - p0);
   for (int ch = tid; ch < c; ch += kVecThreads) {
-    float s0 = 0.f, q0 = 0.f;
-#pragma unroll 8
-    for (int r = 0; r < parts; ++r) { const float2 e = s_p[r * c + ch]; s0 += e.x; q0 += e.y; }
-    const float a0 = s_shift[ch];   // every thread of a channel used the same shift: the slab's first pixel
-    const float ds = s0 / cnt;
-    Moments m{cnt, a0 + ds, fmaxf(q0 - s0 * ds, 0.f)};
+    Moments m = merge_all<0>([&](int r) { return s_p[r * c + ch]; }, parts);
     for (int mask = 1; mask < cpg; mask <<= 1) m = butterfly(m, tid, mask);   // cpg consecutive lanes = one group
     if ((ch & (cpg - 1)) == 0) {
       if (chunks == 1) {   // a slab is the sample: nothing to hand over

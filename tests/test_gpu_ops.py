@@ -52,12 +52,13 @@ def test_gn_stats_large_offset_no_cancellation():
     assert np.max(np.abs(mean.cpu().numpy() - wm.ravel())) < 1e-4
 
 
+@pytest.mark.parametrize("c,h,w", [(256, 120, 180), (64, 32, 32), (512, 7, 9)])
 @pytest.mark.parametrize("rows,offset", [(1, 10.0), (1, 100.0), (4, 100.0)])
-def test_gn_stats_with_a_first_band_off_the_rest(rows, offset):
+def test_gn_stats_with_a_first_band_off_the_rest(rows, offset, c, h, w):
     """A letterboxed image: the first slab's mean lies `offset` standard deviations from the others'.  Two passes over the
     triples round each of some 13 sequential additions (8 per lane, 5 levels across lanes) once: 13 * 2^-24 = 8e-7 at worst
     for the variance, as the sums inside a slab do; one pass about the first triple's mean was off by 1e-5."""
-    x = rng(5).standard_normal((1, 256, 120, 180)).astype(np.float32)
+    x = rng(5).standard_normal((1, c, h, w)).astype(np.float32)
     x[:, :, :rows] += offset
     mean, rstd = G.gn_stats(G.dev_nhwc(x, "f32"), 32, 1e-6)
     wm, wr = ref.gn_stats(x, 32, 1e-6)
@@ -65,7 +66,21 @@ def test_gn_stats_with_a_first_band_off_the_rest(rows, offset):
     assert np.max(np.abs(mean.cpu().numpy() - wm.ravel()) * wr.ravel()) < 5e-7
 
 
-@pytest.mark.parametrize("h,w", [(120, 180)])
+@pytest.mark.parametrize("c,h,w", [(64, 32, 32), (512, 10, 12), (8, 3, 5)])
+def test_gn_stats_with_an_outlier_first_pixel(c, h, w):
+    """The first pixel of the tensor 1000 standard deviations off.  Only one thread's sums are shifted by it, a share 1/ppi
+    of the slab (ppi = 1024 * 4 / c pixels a sweep): its own cancellation is 1000^2 * 2^-24 = 6e-2 of a variance of 1, that
+    of the group gains 1000^2 / pixels, so 6e-8 * pixels / ppi relative, and the sums' own 8e-7."""
+    x = rng(7).standard_normal((1, c, h, w)).astype(np.float32)
+    x[:, :, 0, 0] += 1000.0
+    groups = min(32, c)
+    mean, rstd = G.gn_stats(G.dev_nhwc(x, "f32"), groups, 1e-6)
+    wm, wr = ref.gn_stats(x, groups, 1e-6)
+    assert np.max(np.abs(rstd.cpu().numpy() / wr.ravel() - 1.0)) < 8e-7 + 6e-8 * max(h * w * c / 4096, 1)
+    assert np.max(np.abs(mean.cpu().numpy() - wm.ravel()) * wr.ravel()) < 5e-7
+
+
+@pytest.mark.parametrize("h,w", [(120, 180), (16, 16)])
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
 @pytest.mark.parametrize("last", [False, True])
 def test_gn_stats_of_a_group_that_is_not_finite(h, w, bad, last):
