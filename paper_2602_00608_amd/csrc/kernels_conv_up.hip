@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_mfma_kernel(MfmaParams p
   const int es = y_f32 ? 4 : 2;
   const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(p.y) + sample * es, 0, p.h * p.w_out * p.cout * es, 0x00020000);
   unsigned y_off[MI];
-  int live_px = 0;
+  int live_px = 0, first_px = 0;   // pixels this wavefront finishes, and those of its first M tile (of which it has some if any)
   bool live[MI];
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
@@ -189,12 +189,15 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_mfma_kernel(MfmaParams p
     const int iy = ty0 + gy, ix = tx0 + gx;
     live[mi] = gy < TH && gx < TW && iy < h_in && ix < w_in;
     y_off[mi] = live[mi] ? ((2 * iy * p.w_out + 2 * ix) * p.cout + co_w + (y_f32 ? 4 : 8) * lk) * es : 0x7fff0000u;
-    live_px += __builtin_popcountll(__ballot(live[mi])) / 2;   // pixels (both halves of the wavefront hold every pixel)
+    live_px += __builtin_popcountll(__ballot(live[mi])) / 2;   // (both halves of the wavefront hold every pixel)
+    if (mi == 0) first_px = live_px;
   }
   Moments mq[4];
 #pragma unroll
   for (int qp = 0; qp < 2; ++qp) {              // eight channels of the lane at a time: quads 2 qp and 2 qp + 1
-    // moments of the stored values: plain sums of a quad, shifted by one value of its group (the first pixel's)
+    // moments of the stored values: plain sums of a quad, shifted by the mean of the first M tile's first phase over the
+    // quad (over both halves where a group spans them): an eighth of the values or more, so that no single one of them,
+    // however far off, can cancel the sums
     constexpr int NS = FINE ? 8 : 2, CH = 8 / NS;
     float sh[NS], ss[NS], sq[NS];
 #pragma unroll
@@ -246,11 +249,15 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_mfma_kernel(MfmaParams p
       }
       if (p.stats) {
         if (mi == 0) {
+          const float inv = first_px > 0 ? 1.0f / (float)(CH * first_px) : 0.f;
 #pragma unroll
           for (int k = 0; k < NS; ++k) {
-            const int v = __builtin_bit_cast(int, out[0][CH * k]);
-            const int v0 = __builtin_amdgcn_readlane(v, 0), v1 = __builtin_amdgcn_readlane(v, 32);
-            sh[k] = __builtin_bit_cast(float, lk && cpg < 8 ? v1 : v0);
+            float v = 0.f;
+#pragma unroll
+            for (int e = 0; e < CH; ++e) v += out[0][CH * k + e];
+            const int sum = __builtin_bit_cast(int, half_sum(live[0] ? v : 0.f));
+            const float v0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(sum, 0)), v1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(sum, 32));
+            sh[k] = (cpg >= 8 ? 0.5f * v0 + 0.5f * v1 : lk ? v1 : v0) * inv;
           }
         }
         if (live[mi]) {
@@ -266,9 +273,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_mfma_kernel(MfmaParams p
       for (int k = 0; k < NS; ++k) {
         float s = half_sum(ss[k]), t = half_sum(sq[k]), cnt = 4.f * CH * (float)live_px;
         if (!FINE && cpg >= 8) { s += __shfl_xor(s, 32); t += __shfl_xor(t, 32); cnt *= 2.f; }
-        // without a finished pixel sh is a value outside the image, possibly not finite: an empty triple, all zeros
-        const float ds = live_px > 0 ? s / cnt : 0.f;
-        const Moments m{cnt, live_px > 0 ? sh[k] + ds : 0.f, fmaxf(t - s * ds, 0.f)};
+        const float ds = live_px > 0 ? s / cnt : 0.f;   // (without a finished pixel all zeros: nothing outside the image enters)
+        const float m2 = t - s * ds;
+        const Moments m{cnt, sh[k] + ds, m2 < 0.f ? 0.f : m2};
         if constexpr (FINE) mq[k % 4] = m;
         else mq[2 * qp + k] = m;
         if (FINE && k % 4 == 3 && lm == 0) {   // one quad's channels
