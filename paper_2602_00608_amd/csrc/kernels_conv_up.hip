@@ -17,7 +17,6 @@
 #include "conv_device.hpp"
 
 namespace wmdec {
-struct Upsampled;   // names the instantiations of this file
 namespace {
 
 constexpr int GH = 8, GW = 16, TH = GH - 1, TW = GW - 1;   // grid of a workgroup, input pixels it finishes
@@ -53,10 +52,10 @@ __device__ __forceinline__ float half_sum(float v) {
   return v + __shfl_xor(v, 16);
 }
 
-// WM wavefront rows share the grid's four M tiles, four wavefront columns of 32 channels
+// WM wavefront rows share the grid's four M tiles, WN wavefront columns of 32 channels.
 // FINE: moments of groups of one or two channels (sums per channel instead of per quad).
-template <typename T, typename Tag, int WM, int WN, bool FINE>
-__global__ __launch_bounds__(64 * WM * WN, 2) void conv_mfma_kernel(MfmaParams p, int y_f32) {
+template <typename T, int WM, int WN, bool FINE>
+__global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, int y_f32) {
   constexpr int NT = 64 * WM * WN, MI = 4 / WM, TN = 32 * WN;
   constexpr int VPP = KC / 8, NV = (PH_ * PW * VPP + NT - 1) / NT;
   extern __shared__ __align__(16) unsigned char smem[];   // [2][BUFB]
@@ -278,10 +277,12 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_mfma_kernel(MfmaParams p
         const Moments m{cnt, sh[k] + ds, m2 < 0.f ? 0.f : m2};
         if constexpr (FINE) mq[k % 4] = m;
         else mq[2 * qp + k] = m;
-        if (FINE && k % 4 == 3 && lm == 0) {   // one quad's channels
+        if (FINE && k % 4 == 3 && lm == 0) {   // one quad's channels: four groups of one or two of two
           Moments* dst = p.stats + ((size_t)n * p.stats_groups + (co_w + 8 * (2 * qp + k / 4) + 4 * lk) / cpg) * p.stats_slots + tile * WM + wm;
           if (cpg == 2) { mq[0] = merge(mq[0], mq[1]); mq[1] = merge(mq[2], mq[3]); }
-          for (int g = 0; g < 4 / cpg; ++g) store_device(dst + (size_t)g * p.stats_slots, mq[g]);
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            if (g < 2 || cpg == 1) store_device(dst + (size_t)g * p.stats_slots, mq[g]);
         }
       }
     }
@@ -304,6 +305,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_mfma_kernel(MfmaParams p
 // 170, one wavefront row 170, four 246); a wavefront row per M tile re-reads every weight fragment four times.
 constexpr int kWM = 2, kWN = 2, kTN = 32 * kWN;
 
+bool fine_moments(const ConvArgs& a) { return a.stats_groups > 0 && a.cout / a.stats_groups < 4; }
+
 template <typename T>
 int launch_up(const ConvArgs& a, hipStream_t s) {
   MfmaParams p = conv_params(a, TH, TW, kTN, kWM, a.h / 2, a.w / 2);
@@ -313,7 +316,7 @@ int launch_up(const ConvArgs& a, hipStream_t s) {
   p.w_bytes = (int)(packed_elems(9, a.cout, a.cin) * sizeof(T));
   constexpr size_t kExchange = (size_t)kWM * kWN * 2 * 16 * 64 * sizeof(float);   // rows handed between wavefront rows
   constexpr size_t kSmem = 2 * BUFB > kExchange ? 2 * BUFB : kExchange;
-  hipLaunchKernelGGL(p.stats && p.stats_cpg < 4 ? (conv_mfma_kernel<T, Upsampled, kWM, kWN, true>) : (conv_mfma_kernel<T, Upsampled, kWM, kWN, false>),
+  hipLaunchKernelGGL(fine_moments(a) ? (conv_up_kernel<T, kWM, kWN, true>) : (conv_up_kernel<T, kWM, kWN, false>),
                      dim3((unsigned)p.total), dim3(64 * kWM * kWN), kSmem, s, p, a.y_dtype == WMDEC_F32 ? 1 : 0);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
@@ -344,7 +347,9 @@ void conv_up_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, 
 }
 
 const char* conv_up_label(const ConvArgs& a) {
-  return a.op_dtype == WMDEC_BF16 ? "conv_mfma_kernel<wmdec::bf16_t, wmdec::Upsampled, 2, 2, false>" : "conv_mfma_kernel<wmdec::f16_t, wmdec::Upsampled, 2, 2, false>";
+  static_assert(kWM == 2 && kWN == 2, "spelled out below");
+  if (fine_moments(a)) return a.op_dtype == WMDEC_BF16 ? "conv_up_kernel<wmdec::bf16_t, 2, 2, true>" : "conv_up_kernel<wmdec::f16_t, 2, 2, true>";
+  return a.op_dtype == WMDEC_BF16 ? "conv_up_kernel<wmdec::bf16_t, 2, 2, false>" : "conv_up_kernel<wmdec::f16_t, 2, 2, false>";
 }
 
 int launch_conv_up(const ConvArgs& a, hipStream_t s) { return a.op_dtype == WMDEC_BF16 ? launch_up<bf16_t>(a, s) : launch_up<f16_t>(a, s); }

@@ -96,10 +96,11 @@ def test_step_accounting_adds_up():
     assert abs(sum(f for _, f, _ in info) - dec.flops_per_frame()) / dec.flops_per_frame() < 1e-12
     assert all(k for k, _, _ in info)
     convs = [(k, f, b) for k, f, b in info if k.startswith("conv_mfma_kernel<")]
-    # 30 ResBlock convolutions (the two 1x1 shortcuts are folded into their second convolutions), three upsampling
-    # convolutions, qkv and output projection: 33 launches of the implicit-GEMM kernel; conv_out (three output
-    # channels) runs as a contraction onto (tap, channel) pairs
-    assert len(convs) == 33 and all(k.endswith(">") for k, _, _ in convs)
+    # 28 ResBlock convolutions (the two 1x1 shortcuts are folded into their second convolutions), qkv and output
+    # projection: 30 launches of the implicit-GEMM kernel; the three upsampling convolutions have a kernel of their own, and
+    # conv_out (three output channels) runs as a contraction onto (tap, channel) pairs
+    assert len(convs) == 30 and all(k.endswith(">") for k, _, _ in convs)
+    assert [k for k, _, _ in info if k.startswith("conv_up_kernel<")] == ["conv_up_kernel<wmdec::f16_t, 2, 2, false>"] * 3
     assert info[-1][0] == "conv_taps_kernel<wmdec::f16_t, 8, 2>"
     # the ten 512 -> 512 layers at 60x90 leave compute units at most one workgroup: whole-chunk weight ring
     assert sum(1 for k, _, _ in convs if k.endswith(", 18>")) == 10
@@ -131,7 +132,7 @@ def test_layers_whose_packed_weights_pass_32_bit_offsets_take_the_general_kernel
     cfg = wmdec.decoder_default_config()
     cfg.latent_h = cfg.latent_w = 2
     cfg.num_levels, cfg.resblocks_per_level = 3, 1
-    for ch, label in ((10240, "conv_mfma_kernel<"), (16384, "conv_direct_kernel")):   # 1.9e9 and 4.8e9 bytes
+    for ch, label in ((10240, "conv_up_kernel<"), (16384, "conv_direct_kernel")):   # 1.9e9 and 4.8e9 bytes
         cfg.level_channels[0], cfg.level_channels[1], cfg.level_channels[2] = 512, ch, 32
         dec = wmdec.Decoder(cfg)
         up = [k for k, f, _ in dec.step_info() if f in (2.0 * 9 * ch * ch * 64 * s for s in (1, 4 / 9, 1 / 4))]

@@ -262,6 +262,21 @@ def test_statistics_of_an_upsampling_convolution_ignore_positions_outside_the_im
     assert err <= G.TOL["f16"], err
 
 
+def test_upsampling_convolutions_with_groups_of_one_and_two_channels():
+    """64 groups: the upsampling convolutions at 512, 128 and 64 channels emit moments of 8, 2 and 1 channels; the last two are
+    an instantiation of their own."""
+    cfg = small_cfg(wmdec.F16)
+    cfg.latent_h, cfg.latent_w, cfg.groups, cfg.level_channels[3] = 5, 8, 64, 64
+    chans = (512, 128, 64, 64)
+    dec = wmdec.Decoder(cfg)
+    assert [k[-6:-1].strip() for k, _, _ in dec.step_info() if k.startswith("conv_up_kernel<")] == ["false", "true", "true"]
+    dec.close()
+    weights = synth.draw_params(synth.decoder_weight_spec(level_channels=chans, resblocks_per_level=2), synth.weight_seed(15), random_affine=True)
+    z = synth.latent_sequence(workload=15, frames=2, h=5, w=8)
+    err = ref.rel_err(run_decoder(cfg, weights, z), ref.decoder(z, weights, level_channels=chans, resblocks_per_level=2, groups=64, eps=1e-6))
+    assert err <= G.TOL["f16"], err
+
+
 @pytest.mark.parametrize("dtype,last", [("f16", 128), ("bf16", 128), ("f16", 64)])
 def test_last_convolution_as_taps_contraction(dtype, last):
     """The decoder's last layer (few output channels, planar fp32 frame) runs as a 1x1 contraction onto (tap, channel)
