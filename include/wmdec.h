@@ -357,11 +357,11 @@ int wmdec_latent_extrapolate(const void* z_prev, const void* v_prev, int dtype, 
 
 /* Number of kernel launches one decoder_run enqueues, and the FLOP count of
  * one frame: 2*k*k*cin*cout per output pixel of every convolution plus
- * 4*T*T*c for the attention -- except that an upsampling convolution in f16
- * is priced at a 2x2 convolution per output, 4/9 of the nine-tap figure (a
- * price, not a count: see wmdec_upsample2x_conv3x3 for what is executed).
- * decoder_dense_flops_per_frame is the nine-tap figure throughout: what the
- * unfused graph would execute. */
+ * 4*T*T*c for the attention -- except that an upsampling convolution on the
+ * matrix-core path counts the nine products per input pixel it executes, 1/4
+ * of the nine-tap figure (see wmdec_upsample2x_conv3x3; what tiles repeat at
+ * their edges is not counted).  decoder_dense_flops_per_frame is the nine-tap
+ * figure throughout: what the unfused graph would execute. */
 int decoder_num_launches(const wmdec_decoder* dec);
 double decoder_flops_per_frame(const wmdec_decoder* dec);
 double decoder_dense_flops_per_frame(const wmdec_decoder* dec);

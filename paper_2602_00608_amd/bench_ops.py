@@ -9,8 +9,7 @@ events on the current stream and inputs resident in HBM:
         cache between calls);
   cold  between two calls a 2 GiB buffer is streamed (read and written), which evicts every cache level; the time
         of the streaming kernel alone, measured the same way, is subtracted.
-An f16 upsampling convolution is priced at a 2x2 convolution per output (4/9 of the nine-tap figure; a price: the kernel
-executes nine products per input pixel).  Inputs are seeded N(0,1) tensors and 1/sqrt(fan_in) weights; real activations toggle fewer bits,
+A 16-bit upsampling convolution is priced at the nine products per input pixel it executes (1/4 of the nine-tap figure).  Inputs are seeded N(0,1) tensors and 1/sqrt(fan_in) weights; real activations toggle fewer bits,
 so inside decoder_run the same convolutions run somewhat faster.
 """
 import argparse
@@ -112,8 +111,8 @@ def main():
             wmdec.pack_upconv_weights(wsrc, wp, en)
             us = timeit(lambda: wmdec.upsample2x_conv3x3(x, wp, bias, y), args.reps)
             name = "upsample2x_conv3x3"
-            if args.dtype == "f16" and cout % 64 == 0:
-                flops *= 4.0 / 9.0        # the price of the output phases' 2x2 taps
+            if args.dtype != "f32" and cin % 32 == 0 and cout % 64 == 0:
+                flops /= 4.0              # nine products per input pixel
         else:
             wp = torch.empty(wmdec.conv_packed_bytes(cout, cin, k, en), dtype=torch.uint8, device="cuda")
             wmdec.pack_conv_weights(wsrc, wp, en)

@@ -204,11 +204,9 @@ struct Builder {
     const double es = (double)dtype_size(d.cfg.act_dtype);
     const double px_out = (double)s.h * s.w, px_in = s.upsample ? px_out / 4 : px_out;
     s.flops_dense = 2.0 * s.ksize * s.ksize * (double)s.cin * s.cout * px_out;
-    // An upsampling convolution is priced per output at the 2x2 convolution of its phase in f16 (4/9) and at nine taps in
-    // bf16, as before one kernel took both with nine products per input pixel (1/4, executed on 1.22 times the
-    // pixels): figures stay comparable, but are no count of executed products for these launches.
-    const bool four_taps = s.upsample && d.cfg.act_dtype == WMDEC_F16 && conv_up_supported(step_shape_args(d, s, 1));
-    s.flops = four_taps ? s.flops_dense * 4.0 / 9.0 : s.flops_dense;
+    // The upsampling kernel takes nine products per input pixel where the plain form takes 36; what its tiles repeat at
+    // their edges (products on up to 128 / 105 of the pixels) is not counted, as for any tile.
+    s.flops = s.upsample && conv_up_supported(step_shape_args(d, s, 1)) ? s.flops_dense / 4.0 : s.flops_dense;
     if (s.sc_src != BUF_NONE) {   // folded 1x1 shortcut: its products, its input and its weights
       const double f = 2.0 * (double)s.sc_cin * s.cout * px_out;
       s.flops += f; s.flops_dense += f;

@@ -54,9 +54,9 @@ def test_default_config_and_weight_table_match_input_recipe():
     nparam = sum(int(np.prod(s[1])) for s in spec)
     assert 49_000_000 < nparam < 50_000_000          # ~49.5 M parameters
     # work of one frame: 3329 GFLOP with every convolution priced at nine taps (incl. 59.7 GFLOP attention core);
-    # the default (f16) decoder evaluates its three upsampling convolutions per output phase and executes 2820
+    # the three upsampling convolutions take a quarter of their products, which leaves 2642
     assert abs(dec.dense_flops_per_frame() / 1e9 - 3329) < 5
-    assert abs(dec.flops_per_frame() / 1e9 - 2820) < 5
+    assert abs(dec.flops_per_frame() / 1e9 - 2642) < 5
     assert dec.workspace_bytes(1) > 3 * 480 * 720 * 256 * 2
     assert dec.workspace_bytes(5) == 0                # beyond max_batch
     dec.close()
@@ -64,11 +64,10 @@ def test_default_config_and_weight_table_match_input_recipe():
 
 def test_flops_independent_count():
     """Recount the decoder's FLOPs from the weight spec: every conv weight contributes 2*k*k*cin*cout per output
-    pixel at the resolution its name implies.  Only executed work counts: where an upsampling convolution is
-    evaluated per output phase (the f16 decoder) it executes 2x2 taps per output, 4/9 of the nine-tap figure; the
-    bf16 decoder keeps the nine-tap form."""
+    pixel at the resolution its name implies.  Only executed work counts: an upsampling convolution takes nine
+    products per input pixel in both types, a quarter of the nine-tap figure."""
     res = {"conv_in": 1, "mid": 1, "up.0": 1, "up.1": 2, "up.2": 4, "up.3": 8, "conv_out": 8}
-    dense = phase = 0.0
+    dense = shared = 0.0
     for name, shape in synth.decoder_weight_spec():
         if not name.endswith(".w"):
             continue
@@ -76,9 +75,10 @@ def test_flops_independent_count():
         s = res[key] * (2 if ".upsample" in name else 1)
         f = 2.0 * np.prod(shape) * (60 * s) * (90 * s)
         dense += f
-        phase += f * 4.0 / 9.0 if ".upsample" in name else f
+        shared += f / 4.0 if ".upsample" in name else f
     attn = 4.0 * 5400 * 5400 * 512
-    for act, executed in ((wmdec.F16, phase + attn), (wmdec.BF16, dense + attn)):
+    executed = shared + attn
+    for act in (wmdec.F16, wmdec.BF16):
         cfg = wmdec.decoder_default_config()
         cfg.act_dtype = act
         dec = wmdec.Decoder(cfg)
@@ -135,7 +135,7 @@ def test_layers_whose_packed_weights_pass_32_bit_offsets_take_the_general_kernel
     for ch, label in ((10240, "conv_up_kernel<"), (16384, "conv_direct_kernel")):   # 1.9e9 and 4.8e9 bytes
         cfg.level_channels[0], cfg.level_channels[1], cfg.level_channels[2] = 512, ch, 32
         dec = wmdec.Decoder(cfg)
-        up = [k for k, f, _ in dec.step_info() if f in (2.0 * 9 * ch * ch * 64 * s for s in (1, 4 / 9, 1 / 4))]
+        up = [k for k, f, _ in dec.step_info() if f in (2.0 * 9 * ch * ch * 64 * s for s in (1, 1 / 4))]
         assert up and up[-1].startswith(label), (ch, up)   # (the last of them: a ResBlock convolution a level below has a quarter of the dense count)
         dec.close()
     size = wmdec.lib().wmdec_conv_stats_workspace_bytes
