@@ -127,9 +127,12 @@ int wmdec_gn_silu_conv3x3(const void* x, int act_dtype, const float* mean, const
  * wmdec_gn_stats would return for y up to fp32 summation order.  Every
  * workgroup writes per-group partial moments of its tile to `workspace`
  * (wmdec_conv_stats_workspace_bytes(...) bytes, no initialisation needed); a
- * second small launch merges them in a fixed order.
- * Two kernels can emit moments, both for 16-bit act_dtype: the matrix-core
- * kernel (cin % 32 == 0, cout % 64 == 0, cout/out_groups a power of two <= 32)
+ * second small launch merges them in a fixed order.  A smaller workspace that
+ * still holds a triple per (sample, group) and tile of 8x16 pixels (four per
+ * tile if cout % 128 != 0) is accepted: y has the same bits, its statistics are
+ * then taken by a pass over y.
+ * Moments are emitted for 16-bit act_dtype by the matrix-core kernels
+ * (cin % 32 == 0, cout % 64 == 0, cout/out_groups a power of two <= 32)
  * and the kernel for cin <= 8 (the decoder's conv_in: no normalisation of x,
  * no residual, cout/out_groups a power of two <= 64); any other shape gives
  * WMDEC_ERR_UNSUPPORTED (the workspace query then returns 0). */

@@ -613,23 +613,23 @@ int wmdec_gn_silu_conv3x3_stats(const void* x, int act_dtype, const float* mean,
   a.x = x; a.mean = mean; a.rstd = mean ? rstd : nullptr; a.gamma = gamma; a.beta = beta;
   a.groups = mean ? groups : 1; a.silu = (mean && apply_silu) ? 1 : 0;
   a.wt = w_packed; a.bias = bias; a.res = residual; a.y = y;
-  int slots = conv_stats_slots(a);
-  if (workspace_bytes < (size_t)n * out_groups * slots * 3 * sizeof(float)) {   // enough for the wide tiles' fewer triples?
-    ConvArgs wide = a;
-    wide.wide_tiles = 1;
-    const int fewer = conv_stats_slots(wide);
-    if (fewer > 0 && workspace_bytes >= (size_t)n * out_groups * fewer * 3 * sizeof(float)) { a.wide_tiles = 1; slots = fewer; }
-  }
+  const int slots = conv_stats_slots(a);
   WMDEC_REQUIRE(slots > 0, WMDEC_ERR_UNSUPPORTED,
                 "%s: this shape / type takes no kernel that emits moments (16-bit types and either cin %% 32 == 0, cout %% 64 == 0, "
                 "channels per output group a power of two <= 32, or cin <= 8 without normalisation and residual, channels per "
                 "output group a power of two <= 64); use wmdec_gn_stats on y", who);
-  const size_t need = (size_t)n * out_groups * slots * 3 * sizeof(float);
-  WMDEC_REQUIRE(workspace && aligned16(workspace) && workspace_bytes >= need, WMDEC_ERR_WORKSPACE,
+  // A workspace that holds the triples of the widest tiles only is still served, but the workspace may not choose the
+  // kernel (the bits of y would depend on it): the same convolution, then a statistics pass over y with what triples fit.
+  ConvArgs wide = a;
+  wide.wide_tiles = 1;
+  const size_t triple = (size_t)n * out_groups * 3 * sizeof(float), need = triple * slots, least = triple * conv_stats_slots(wide);
+  WMDEC_REQUIRE(workspace && aligned16(workspace) && workspace_bytes >= (least > 0 && least < need ? least : need), WMDEC_ERR_WORKSPACE,
                 "%s: workspace needs %zu bytes, got %zu", who, need, workspace_bytes);
-  a.stats_ws = workspace;
+  if (workspace_bytes >= need) a.stats_ws = workspace;
   const int rl = launch_conv(a, (hipStream_t)stream);
   if (rl != WMDEC_OK) return rl;
+  if (!a.stats_ws)
+    return launch_gn_stats_small_ws(y, y_dtype, n, h, w, cout, out_groups, out_eps, mean_out, rstd_out, workspace, (int)(workspace_bytes / triple), (hipStream_t)stream);
   return launch_gn_finalize(workspace, n * out_groups, slots, out_eps, mean_out, rstd_out, (hipStream_t)stream);
 }
 

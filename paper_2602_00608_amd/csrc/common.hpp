@@ -91,7 +91,7 @@ struct ConvArgs {
   const void* w2 = nullptr;      //   ResBlock folded into the contraction; x2 [n,h,w,cin2] of op_dtype, w2 packed with k = 1
   const float* bias2 = nullptr;
   int cin2 = 0;
-  int wide_tiles = 0;            // 1: not the kernel that splits the contraction over wavefronts (its statistics take more slots)
+  int wide_tiles = 0;            // size queries only: 1: the widest tiles, i.e. the fewest moment triples a launch of this shape can leave
   void* stats_ws = nullptr;      // non-null: also emit GroupNorm moments of y, [n][stats_groups][slots] triples
   int stats_groups = 0;
   // matrix-core kernel only: statistics handed from producer to consumer without a merge launch
@@ -148,6 +148,8 @@ int launch_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int 
 // same statistics with the library's built-in scratch (a file-scope device array) instead of a caller workspace
 int launch_gn_stats_static(const void* x, int x_dtype, int n, int h, int w, int c, int groups, float eps,
                            float* mean, float* rstd, hipStream_t s);
+int launch_gn_stats_small_ws(const void* x, int x_dtype, int n, int h, int w, int c, int groups, float eps, float* mean,
+                             float* rstd, void* moments, int max_slabs, hipStream_t s);
 
 // merges `slots` moment triples per (sample, group) from ws[n_groups][slots] into mean / rstd
 int launch_gn_finalize(const void* ws, int n_groups, int slots, float eps, float* mean, float* rstd, hipStream_t s);

@@ -315,6 +315,18 @@ int gn_stats_num_launches(int x_dtype, int h, int w, int c, int groups) {
   return make_plan(x_dtype, 1, h, w, c, groups).vec ? 1 : 2;
 }
 
+static int launch_general(const void* x, int x_dtype, int n, int pixels, int c, int groups, int slabs, int slab_pixels, float eps,
+                          float* mean, float* rstd, Moments* wsm, hipStream_t s) {
+  dim3 grid((unsigned)slabs, (unsigned)groups, (unsigned)n);
+  switch (x_dtype) {
+    case WMDEC_F32: hipLaunchKernelGGL(gn_partial_any<float>, grid, dim3(256), 0, s, (const float*)x, pixels, c, groups, slab_pixels, wsm); break;
+    case WMDEC_BF16: hipLaunchKernelGGL(gn_partial_any<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)x, pixels, c, groups, slab_pixels, wsm); break;
+    default: hipLaunchKernelGGL(gn_partial_any<f16_t>, grid, dim3(256), 0, s, (const f16_t*)x, pixels, c, groups, slab_pixels, wsm); break;
+  }
+  WMDEC_HIP(hipGetLastError());
+  return launch_gn_finalize(wsm, n * groups, slabs, eps, mean, rstd, s);
+}
+
 int launch_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int groups, float eps,
                     float* mean, float* rstd, unsigned* ticket, void* moments, size_t moments_bytes, hipStream_t s) {
   const Plan p = make_plan(x_dtype, n, h, w, c, groups);
@@ -331,18 +343,18 @@ int launch_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int 
     }
     WMDEC_HIP(hipGetLastError());
     return WMDEC_OK;
-  } else {
-    dim3 grid((unsigned)p.chunks, (unsigned)groups, (unsigned)n);
-    switch (x_dtype) {
-      case WMDEC_F32: hipLaunchKernelGGL(gn_partial_any<float>, grid, dim3(256), 0, s, (const float*)x, pixels, c, groups, p.chunk_pixels, wsm); break;
-      case WMDEC_BF16: hipLaunchKernelGGL(gn_partial_any<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)x, pixels, c, groups, p.chunk_pixels, wsm); break;
-      default: hipLaunchKernelGGL(gn_partial_any<f16_t>, grid, dim3(256), 0, s, (const f16_t*)x, pixels, c, groups, p.chunk_pixels, wsm); break;
-    }
   }
-  WMDEC_HIP(hipGetLastError());
-  hipLaunchKernelGGL(gn_finalize, dim3((unsigned)(n * groups)), dim3(kFinThreads), 0, s, wsm, p.chunks, eps, mean, rstd);
-  WMDEC_HIP(hipGetLastError());
-  return WMDEC_OK;
+  return launch_general(x, x_dtype, n, pixels, c, groups, p.chunks, p.chunk_pixels, eps, mean, rstd, wsm, s);
+}
+
+// The general path in at most max_slabs slabs, for callers whose workspace holds that many triples per (sample, group) and
+// no ticket counters.
+int launch_gn_stats_small_ws(const void* x, int x_dtype, int n, int h, int w, int c, int groups, float eps, float* mean,
+                             float* rstd, void* moments, int max_slabs, hipStream_t s) {
+  const int pixels = h * w;
+  const int slabs = max(1, min(max_slabs, (pixels + 63) / 64));
+  const int slab_pixels = (pixels + slabs - 1) / slabs;
+  return launch_general(x, x_dtype, n, pixels, c, groups, (pixels + slab_pixels - 1) / slab_pixels, slab_pixels, eps, mean, rstd, (Moments*)moments, s);
 }
 
 // ---- the variant for callers that cannot allocate: the workspace is a file-scope device array
