@@ -19,6 +19,7 @@
 // before it takes the ticket, and only the workgroup that draws the last ticket reads.  Under the language memory
 // model the relaxed accesses alone would not order the stores before the ticket; the wait does, on this hardware.
 #include <mutex>
+#include <type_traits>
 
 #include "moments.hpp"
 
@@ -41,25 +42,25 @@ template <> struct alignas(16) Vec16<f16_t> { static constexpr int N = 8; f16_t 
 // streams its slab (8 loads of 16 bytes in flight per thread, the ragged end as one masked batch), sums
 // x - shift and its square per thread (shift = the thread's first pixel, so that an outlier costs only the sums of
 // the thread that starts with it), merges the (mean, M2) of a channel's threads in a fixed order through LDS, the
-// channels of a group with a butterfly, and writes one triple per group.  The workgroup of a sample that finishes last (one wrapping ticket counter per
+// channels of a group in its lanes, and writes one triple per group.  The workgroup of a sample that finishes last (one wrapping ticket counter per
 // sample, which returns to zero by itself) merges the sample's triples in a fixed order into mean / rstd.
 constexpr int kVecThreads = 1024;
 constexpr int kVecMaxChunks = 256;
 constexpr int kVecMaxGroups = 256;
 
 template <typename T, int V, bool MASKED>
-__device__ __forceinline__ void gn_accumulate(const Vec16<T>* base, int p, int p1, int ppi, int vp, const float* shift,
+__device__ __forceinline__ void gn_accumulate(const char* slab, unsigned off, unsigned end, unsigned sweep, const float* shift,
                                               float* s, float* q) {
   constexpr int U = 8;
   Vec16<T> v[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int pp = p + u * ppi;
-    v[u] = base[(size_t)((MASKED && pp >= p1) ? p : pp) * vp];   // always a pixel of this slab: no branch around the load
+    const unsigned at = off + u * sweep;
+    v[u] = *reinterpret_cast<const Vec16<T>*>(slab + (MASKED && at >= end ? off : at));   // always a pixel of this slab: no branch around the load
   }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const bool live = !MASKED || p + u * ppi < p1;
+    const bool live = !MASKED || off + u * sweep < end;
 #pragma unroll
     for (int j = 0; j < V; ++j) {
       const float d = live ? to_float(v[u].v[j]) - shift[j] : 0.f;
@@ -77,7 +78,7 @@ template <int COUNT, typename At> __device__ __forceinline__ Moments merge_all(A
 #pragma unroll 8
   for (int k = 0; k < (COUNT ? COUNT : count); ++k) { const Moments t = at(k); m.n += t.n; s = fmaf(t.n, t.mean - first, s); }
   if (m.n == 0.f) return m;
-  const float inv = 1.0f / m.n;
+  const float inv = __builtin_amdgcn_rcpf(m.n);   // 1 ulp: the second pass corrects the mean
   m.mean = fmaf(s, inv, first);
   s = 0.f;
 #pragma unroll 8
@@ -86,12 +87,16 @@ template <int COUNT, typename At> __device__ __forceinline__ Moments merge_all(A
     const float d = t.mean - m.mean, nd = t.n * d;
     s += nd; m.m2 += fmaf(nd, d, t.m2);
   }
-  m.mean = fmaf(s, inv, m.mean);    // what the rounding of the mean left
+  m.mean = fmaf(s, inv, m.mean);
   return m;
 }
 
+// Eight wavefronts per SIMD, two workgroups per compute unit, where 64 registers hold the eight loads and the sums: at one,
+// eight f16 samples of 256 channels at 68x92 took 2.7 us more.  bf16, which converts by shifts and masks, would spill.
+template <typename T> constexpr int vec_waves() { return std::is_same<T, bf16_t>::value ? 4 : 8; }
+
 template <typename T>
-__global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict__ x, int pixels, int c, int groups,
+__global__ __launch_bounds__(kVecThreads, vec_waves<T>()) void gn_stats_vec(const T* __restrict__ x, int pixels, int c, int groups,
                                                             int chunk_pixels, Moments* ws, unsigned* ticket, float eps,
                                                             float* __restrict__ mean, float* __restrict__ rstd) {
   constexpr int V = Vec16<T>::N;
@@ -107,22 +112,25 @@ __global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict_
   const int chunk = blockIdx.x, n = blockIdx.y, chunks = gridDim.x;
   const int p0 = chunk * chunk_pixels;
   const int p1 = min(p0 + chunk_pixels, pixels);
-  const Vec16<T>* base = reinterpret_cast<const Vec16<T>*>(x + (size_t)n * pixels * c) + cv;
+  // A sweep is 16 KiB of consecutive memory, a thread's vectors are 16 KiB apart.  Byte offsets into the slab have 32 bits
+  // (a slab is the 256th part of a sample, or a few sweeps).
+  const char* slab = reinterpret_cast<const char*>(x + ((size_t)n * pixels + p0) * c);
+  const unsigned end = (unsigned)(p1 - p0) * vp * 16, sweep = kVecThreads * 16;
 
-  int p = p0 + tid / vp;
+  unsigned off = tid * 16;   // pixel tid / vp, channel vector tid % vp
   float shift[V], s[V], q[V];
   {
-    const Vec16<T> v = base[(size_t)min(p, p1 - 1) * vp];
+    const Vec16<T> v = *reinterpret_cast<const Vec16<T>*>(slab + (off < end ? off : cv * 16));
 #pragma unroll
     for (int j = 0; j < V; ++j) { shift[j] = to_float(v.v[j]); s[j] = 0.f; q[j] = 0.f; }
   }
-  for (; p + (U - 1) * ppi < p1; p += U * ppi) gn_accumulate<T, V, false>(base, p, p1, ppi, vp, shift, s, q);
-  if (p < p1) gn_accumulate<T, V, true>(base, p, p1, ppi, vp, shift, s, q);
+  for (; off + (U - 1) * sweep < end; off += U * sweep) gn_accumulate<T, V, false>(slab, off, end, sweep, shift, s, q);
+  if (off < end) gn_accumulate<T, V, true>(slab, off, end, sweep, shift, s, q);
 
   const int sweeps = (p1 - p0) / ppi, rest = (p1 - p0) % ppi;
   auto lane_pixels = [&](int lane) { return (float)(sweeps + (lane < rest ? 1 : 0)); };   // pixels of a pixel lane
   {
-    const float cnt = lane_pixels(tid / vp), inv = cnt > 0.f ? 1.0f / cnt : 0.f;
+    const float cnt = lane_pixels(tid / vp), inv = cnt > 0.f ? __builtin_amdgcn_rcpf(cnt) : 0.f;   // 1 ulp of a difference to the shift
 #pragma unroll
     for (int j = 0; j < V; ++j) {
       const float ds = s[j] * inv, m2 = q[j] - s[j] * ds;
@@ -142,7 +150,7 @@ __global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict_
   const int cpg = c / groups;
   for (int ch = tid; ch < c; ch += kVecThreads) {
     Moments m = merge_all<0>([&](int r) { return s_p[r * c + ch]; }, parts);
-    for (int mask = 1; mask < cpg; mask <<= 1) m = butterfly(m, tid, mask);   // cpg consecutive lanes = one group
+    m = merge_to_first(m, tid & 63, cpg);   // cpg consecutive lanes = one group
     if ((ch & (cpg - 1)) == 0) {
       if (chunks == 1) {   // a slab is the sample: nothing to hand over
         mean[n * groups + ch / cpg] = m.mean;
@@ -181,14 +189,14 @@ __global__ __launch_bounds__(kVecThreads) void gn_stats_vec(const T* __restrict_
     for (int k = 0; k < kVecMaxChunks / 32; ++k) { cn += t[k].n; sd = fmaf(t[k].n, t[k].mean - first, sd); }
     cn = lanes_sum<16>(cn); sd = lanes_sum<16>(sd);
     cn += __shfl_xor(cn, 16); sd += __shfl_xor(sd, 16);
-    const float m = first + sd / cn;
+    const float inv = __builtin_amdgcn_rcpf(cn), m = fmaf(sd, inv, first);
     sd = 0.f;
 #pragma unroll
     for (int k = 0; k < kVecMaxChunks / 32; ++k) { const float d = t[k].mean - m, nd = t[k].n * d; sd += nd; sq += fmaf(nd, d, t[k].m2); }
     sd = lanes_sum<16>(sd); sq = lanes_sum<16>(sq);
     sd += __shfl_xor(sd, 16); sq += __shfl_xor(sq, 16);
     if (sub == 0) {
-      mean[n * groups + g] = m + sd / cn;    // what the rounding of m left
+      mean[n * groups + g] = fmaf(sd, inv, m);    // (what the roundings of m left)
       rstd[n * groups + g] = 1.0f / sqrtf(sq / cn + eps);
     }
   }
