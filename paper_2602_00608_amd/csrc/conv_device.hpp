@@ -114,6 +114,27 @@ __device__ __forceinline__ float2 merge_row(const Moments* row, int count, int s
   return make_float2(mean + d, 1.0f / sqrtf((q < 0.f ? 0.f : q) / n + eps));   // (NaN stays NaN)
 }
 
+// Moments of one channel over rows x cols pixels in row-major order, plain sums about the first value; `src` points at the
+// first pixel's value in LDS, pixels PX and image rows ROW floats apart, of a block of H x W.
+template <int H, int W, int ROW, int PX> __device__ __forceinline__ Moments block_moments(const float* src, int rows, int cols) {
+  if (rows <= 0 || cols <= 0) return Moments{0.f, 0.f, 0.f};
+  const float shift = src[0];
+  float s = 0.f, q = 0.f;
+  auto add = [&](int ty, int tx) {
+    const float d = src[ty * ROW + tx * PX] - shift;
+    s += d; q = fmaf(d, d, q);
+  };
+  if (rows == H && cols == W) {
+#pragma unroll
+    for (int i = 0; i < H * W; ++i) add(i / W, i % W);
+  } else {
+    for (int ty = 0; ty < rows; ++ty)
+      for (int tx = 0; tx < cols; ++tx) add(ty, tx);
+  }
+  const float cnt = (float)(rows * cols), ds = s / cnt, m2 = q - s * ds;
+  return Moments{cnt, shift + ds, m2 < 0.f ? 0.f : m2};
+}
+
 // Row hand-over: the workgroup that finishes a (sample, tile row, channel tile) last merges that row's triples.  Same
 // protocol as the single-launch statistics kernel: the triples were written with device-scope stores, every wavefront
 // waits for its stores, the workgroup takes a ticket (a wrapping counter that returns to zero by itself), and only the

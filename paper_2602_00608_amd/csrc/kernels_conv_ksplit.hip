@@ -385,16 +385,7 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
       const int b = i / TN, c = i % TN, x0 = tx0 + 8 * b;
       const int rows = min(4, p.h - ty0), cols = min(8, p.w_out - x0);
       if (cols <= 0) continue;
-      const float* src = red + (size_t)(8 * b) * RR + c;
-      const float shift = src[0];
-      float s = 0.f, q = 0.f;
-      for (int ty = 0; ty < rows; ++ty)
-        for (int tx = 0; tx < cols; ++tx) {
-          const float d = src[(size_t)(ty * TW + tx) * RR] - shift;
-          s += d; q = fmaf(d, d, q);
-        }
-      const float cnt = (float)(rows * cols), ds = s / cnt;
-      Moments m = merge_to_first(Moments{cnt, shift + ds, fmaxf(q - s * ds, 0.f)}, lane, p.stats_cpg);
+      const Moments m = merge_to_first(block_moments<4, 8, TW * RR, RR>(red + (size_t)(8 * b) * RR + c, rows, cols), lane, p.stats_cpg);
       if (c % p.stats_cpg == 0)
         p.stats[((size_t)n * p.stats_groups + (co0 + c) / p.stats_cpg) * p.stats_slots + (ty0 / 4) * ((p.w_out + 7) / 8) + x0 / 8] = m;
     }

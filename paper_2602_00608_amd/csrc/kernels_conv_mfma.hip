@@ -36,12 +36,16 @@ namespace {
 // in order, so the patch needs no barrier between its write and read phases.
 // floats of the wavefront-private epilogue patch: 32 padded rows, and at least the 64 x 8 four-float entries
 // that the statistics reduction parks there
-constexpr int patch_floats(int ni) { return 32 * (ni * 32 + 4) > 2048 ? 32 * (ni * 32 + 4) : 2048; }
+constexpr int patch_floats(int ni, bool pairs = false) { return pairs ? 2 * 32 * (ni * 32 + 4) : 32 * (ni * 32 + 4) > 2048 ? 32 * (ni * 32 + 4) : 2048; }
 
-template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, bool RES, bool HALVES>
-__device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], float* lds, int lane, int mt0, int ty0,
+// PAIRS (NI = 1): two patches, and moments per pair of M tiles (four image rows) from the values written back to them:
+// a lane walks one channel of either tile's 32 pixels.  A second emission of the other form (per-lane sums parked in LDS)
+// cost 1.3 us of a launch of one round.
+template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, bool RES, bool PAIRS>
+__device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], float* wave_lds, int lane, int mt0, int ty0,
                                                int tx0, int co_w, const float* bias, const float* bias2, const T* rin, TO* yout, int h,
-                                               int w_out, int cout, bool nchw, Moments* stats, int cpg, int stats_stride, int half_stride) {
+                                               int w_out, int cout, bool nchw, Moments* stats, int cpg, int stats_stride, int pair_stride) {
+  float* lds = wave_lds;
   constexpr int RW = NI * 32 + 4;       // padded row of the patch, floats
   if (nchw) {
     // planar output with few channels (the frame): a lane owns one pixel of the M tile and walks the
@@ -125,6 +129,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
   };
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
+    if constexpr (PAIRS) lds = wave_lds + (mi & 1) * 32 * RW;
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
@@ -159,13 +164,18 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
 #pragma unroll
           for (int e = 0; e < 8; ++e) sv[e] = v[e];
         }
-        if (st_n == 0.f) {
+        if constexpr (PAIRS) {
+          *reinterpret_cast<f32x4*>(lds + pi * RW + cvec * 8) = f32x4{sv[0], sv[1], sv[2], sv[3]};
+          *reinterpret_cast<f32x4*>(lds + pi * RW + cvec * 8 + 4) = f32x4{sv[4], sv[5], sv[6], sv[7]};
+        } else {
+          if (st_n == 0.f) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) st_shift[e] = sv[e];
+            for (int e = 0; e < 8; ++e) st_shift[e] = sv[e];
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) { const float dv = sv[e] - st_shift[e]; st_s[e] += dv; st_q[e] = fmaf(dv, dv, st_q[e]); }
+          st_n += 1.f;
         }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { const float dv = sv[e] - st_shift[e]; st_s[e] += dv; st_q[e] = fmaf(dv, dv, st_q[e]); }
-        st_n += 1.f;
       }
       if (off >= 0) {
         TO* dst = reinterpret_cast<TO*>(reinterpret_cast<char*>(yout) + (unsigned)(off * (int)sizeof(TO)));
@@ -177,18 +187,20 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
         }
       }
     }
-    if constexpr (HALVES) {   // the upper half of the tile's rows: a slot of its own, then the sums start again
-      if (mi == MI / 2 - 1 && stats) {
-        emit_moments(stats);
-        st_n = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { st_s[e] = 0.f; st_q[e] = 0.f; }
+    if constexpr (PAIRS) {
+      static_assert(NI == 1 && MTW == 16 && MTH == 2 && MT_PER_ROW == 1 && MI % 2 == 0, "a pair is four rows of 16 pixels");
+      if (mi % 2 == 1 && stats) {   // lanes 0-31: a channel of the pair's first tile, lanes 32-63: of the second
+        const int y0 = ty0 + (mi - 1 + lk) * MTH;
+        Moments m = block_moments<MTH, MTW, MTW * RW, RW>(wave_lds + lk * 32 * RW + lm, min(MTH, h - y0), min(MTW, w_out - tx0));
+        m = merge_to_first(butterfly(m, lane, 32), lane, cpg);
+        if (lk == 0 && (lm & (cpg - 1)) == 0 && m.n > 0.f) store_device(stats + (size_t)((co_w + lm) / cpg) * stats_stride, m);
+        stats += pair_stride;
       }
     }
   }
-  if (!stats) return;
-  if constexpr (!HALVES) emit_moments(stats);
-  else if (half_stride) emit_moments(stats + half_stride);
+  if constexpr (!PAIRS) {
+    if (stats) emit_moments(stats);
+  }
 }
 
 // Ring length of the weight-fragment prefetch: it must divide the k-steps of a chunk so that the ring
@@ -582,21 +594,16 @@ void conv_mfma_kernel(MfmaParams p) {
   // ---- epilogue: bias, residual, one rounding, store (through a wavefront-private LDS patch over the tile buffers)
   TO* yout = reinterpret_cast<TO*>(p.y) + (size_t)n * p.h * p.w_out * p.cout;
   const T* rin = p.res ? reinterpret_cast<const T*>(p.res) + (size_t)n * p.h * p.w_out * p.cout : nullptr;
-  float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(NI);
-  // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row]
-  constexpr bool HALVES = ROWS4 && TH == 8;
-  int slot = tile * WM + wm, half_stride = 0;
-  if constexpr (HALVES) {   // slots are numbered by rows of four; the lower half may lie below the image
-    slot = 2 * (tile / p.tiles_x) * p.tiles_x + tile % p.tiles_x;
-    half_stride = ty0 + 4 < p.h ? p.tiles_x : 0;
-  }
+  float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(NI, ROWS4);
+  // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row], or by rows of four (an 8-row tile has two)
+  const int slot = ROWS4 ? TH / 4 * (tile / p.tiles_x) * p.tiles_x + tile % p.tiles_x : tile * WM + wm;
   Moments* st = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + slot : nullptr;
   if (rin)
-    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true, HALVES>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
-                                                              p.bias2, rin, yout, p.h, p.w_out, p.cout, false, st, p.stats_cpg, p.stats_slots, half_stride);
+    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true, ROWS4>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
+                                                              p.bias2, rin, yout, p.h, p.w_out, p.cout, false, st, p.stats_cpg, p.stats_slots, p.tiles_x);
   else
-    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false, HALVES>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
-                                                               p.bias2, rin, yout, p.h, p.w_out, p.cout, p.y_nchw != 0, st, p.stats_cpg, p.stats_slots, half_stride);
+    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false, ROWS4>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
+                                                               p.bias2, rin, yout, p.h, p.w_out, p.cout, p.y_nchw != 0, st, p.stats_cpg, p.stats_slots, p.tiles_x);
 
   if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, co0, TN, WM, tid, lane);
 }
@@ -620,7 +627,7 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
   }
   constexpr int NT = 64 * WM * WN;
   size_t smem = (((size_t)2 * tile_buf_elems(TH, TW, PAD, KC) * 2 + 15) & ~(size_t)15) + (size_t)(a.cin + a.groups) * sizeof(float2);
-  const size_t patch = (size_t)(WM * WN) * patch_floats(NI) * sizeof(float);   // epilogue patches of the wavefronts
+  const size_t patch = (size_t)(WM * WN) * patch_floats(NI, ROWS4) * sizeof(float);   // epilogue patches of the wavefronts
   if (smem < patch) smem = patch;
   WMDEC_REQUIRE(smem <= 80 * 1024, WMDEC_ERR_UNSUPPORTED, "conv_mfma: %zu bytes of LDS needed", smem);
   void (*kern)(MfmaParams) = !p.norm ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 0, ROWS4, RING>
@@ -659,6 +666,8 @@ constexpr TileShape kTiles[kNumTiles] = {
 // enough for the consumer to merge: 64 x 128 tiles where the launch still fits one round, 128 x 128 otherwise, with the same
 // order of summation and the same moments.  Measured, us, 64 x 128 against 128 x 128: 512 channels at 64x64 27.8 / 35.3, at
 // 45x80 26.2 / 34.1, 256 channels at 68x92 16.9 / 21.8; past one round 47.4 / 43.5 (64x64, two samples), 89 / 78 (four).
+// The larger tile of the pair runs as T128x128_1x4 does: ResBlocks of 2 / 4 / 8 samples take 93.0 / 156.6 / 284.6 us at 512
+// channels 45x80 against 93.2 / 157.5 / 286.0, at 256 channels 68x92 61.5 / 92.1 / 157.9 against 61.3 / 92.5 / 158.8.
 bool four_row_slots(const ConvArgs& a) {
   const long blocks = (long)((a.h + 3) / 4) * ((a.w + 15) / 16);
   return a.ksize == 3 && !a.upsample && !a.y_nchw && a.cout % 128 == 0 && !a.rows_out && !a.wide_tiles && blocks <= 128 && blocks * (a.cout / 128) <= 256;
@@ -689,10 +698,11 @@ TileId pick_tile(const ConvArgs& a) {
   return n128 ? T128x128_ROW : T128x64_ROW;
 }
 
-// The 128x128 tile with a whole chunk of weight fragments in flight (see RING): launches of at most two workgroups per
-// compute unit.  Unlike the tile shape this may depend on the batch: the ring changes no summation order.
+// The 128x128 tiles with a whole chunk of weight fragments in flight (see RING): launches of at most two workgroups per
+// compute unit (two frames of 360x640: 4.13 -> 4.08 ms with the ring and the pair's moments from the written-back values).  Unlike the tile shape this may depend on the batch: the ring changes no summation order.
 bool whole_chunk_ring(const ConvArgs& a) {
-  if (pick_tile(a) != T128x128_1x4) return false;
+  const TileId t = pick_tile(a);
+  if (t != T128x128_1x4 && t != T128x128_ROWS4) return false;
   const long wgs = (long)((a.h + 7) / 8) * ((a.w + 15) / 16) * (a.cout / 128) * a.n;
   return wgs <= 2 * 256;
 }
@@ -704,7 +714,8 @@ int launch_3x3(const ConvArgs& a, hipStream_t s) {
     case T128x128_1x4:
       return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32>(a, s);
     case T64x128: return launch_cfg<T, TO, 4, 16, 1, 4, 1, 3, 32, 9, true>(a, s);
-    case T128x128_ROWS4: return launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 0, true>(a, s);
+    case T128x128_ROWS4:
+      return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18, true>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 0, true>(a, s);
     case T128x256: return launch_cfg<T, TO, 8, 16, 1, 4, 2, 3, 32>(a, s);
     default: return launch_cfg<T, TO, 8, 32, 4, 1, 1, 3, 32>(a, s);
   }
