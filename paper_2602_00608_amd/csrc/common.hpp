@@ -112,6 +112,8 @@ int launch_conv_small_cin(const ConvArgs& a, hipStream_t s);
 // is not one it handles (caller falls back to the direct kernel), 0 if launched.
 bool conv_mfma_supported(const ConvArgs& a);
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s);
+// the layers of conv_ksplit_supported (16 bit, cout % 128 == 0, no shortcut) in large batches: that kernel's bits and moments
+int launch_conv_quarters(const ConvArgs& a, hipStream_t s);
 // moment slots per (sample, group) the MFMA kernel would write for this launch; 0: it cannot emit statistics
 int conv_mfma_stats_slots(const ConvArgs& a);
 void conv_mfma_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row);

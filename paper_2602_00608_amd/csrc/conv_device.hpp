@@ -64,7 +64,10 @@ template <typename T, int ACT, bool PIN = false> __device__ __forceinline__ uint
   if constexpr (ACT > 0) {
     float f0 = fmaf(unpack_lo<T>(wv), ab[0], ab[1]), f1 = fmaf(unpack_hi<T>(wv), ab[2], ab[3]);
     if constexpr (ACT == 2) { f0 = silu_from_scaled(f0); f1 = silu_from_scaled(f1); }
-    if constexpr (PIN) asm("" : "+v"(f0), "+v"(f1));
+    if constexpr (PIN) {
+      asm("" : "+v"(f0), "+v"(f1));
+      if constexpr (std::is_same<T, f16_t>::value) return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{f0, f1}, f16x2_t));   // one instruction
+    }
     wv = pack2<T>(f0, f1);
   }
   return wv;

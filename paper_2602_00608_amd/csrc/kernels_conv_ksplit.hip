@@ -4,8 +4,8 @@
 // per staged element, zeros outside the image, bias / residual / folded 1x1 shortcut, moments of the stored output), for
 // layers that leave most compute units empty when every workgroup takes 128 pixels x 128 channels: there a wavefront is
 // alone on its SIMD and walks the whole contraction (4608 products deep at 512 channels) by itself, so the launch takes
-// the latency of one such walk however small the image is.  Here a workgroup takes a small tile (32 to 96 pixels x 32 to
-// 128 channels) with eight wavefronts, WN of them side by side in the channels and WK in the contraction: a round stages
+// the latency of one such walk however small the image is.  Here a workgroup takes a small tile (32 or 64 pixels x 32 to
+// 128 channels) with eight wavefronts (two or four for the 32-channel tiles), WN of them side by side in the channels and WK in the contraction: a round stages
 // 16 * WK input channels, wavefront wk multiplies its own 16 of them with all nine taps, and the WK partial sums
 // of an output are added in a fixed order through LDS at the end.  What bounds it is the activation on the load path
 // (a staged element serves only the tile's channels) and the fixed parts of a launch, not the matrix pipe.
@@ -453,14 +453,26 @@ template <typename T> int launch_16bit(const ConvArgs& a, hipStream_t s) {
   }
 }
 
+// Batches past one round of the largest tile above take the 128 x 128 form that reproduces this kernel's sums and moments
+// (launch_conv_quarters): a weight fragment then feeds four MFMAs instead of two.  Its tiles are eight rows high, so
+// images that leave much of them empty stay here (ratio of the two tile counts below 5 / 3).  ResBlocks in us, this kernel /
+// that form: 512 channels 17x23 6 samples 56.5 / 77.8, 8 samples 83.6 / 79.6; 32x32 4: 62.1 / 77.5, 6: 93.2 / 85.1, 16: 195.6 /
+// 169.0; 34x46 2: 58.3 / 78.9, 3: 90.8 / 82.8, 8: 182.3 / 157.2; 256 channels 46x60 2: 41.8 / 54.7, 3: 64.1 / 55.9, 16: 185.2 /
+// 142.8.  (The ordinary 128 x 128 tile, whose order of summation is another, takes 4 to 8 % less than that form: it fits
+// three workgroups on a compute unit, the second set of accumulators two.)
+bool batched_form(const ConvArgs& a) {
+  if (!is_16bit(a.op_dtype) || a.cout % 128 != 0 || a.x2) return false;
+  const long cols = (a.w + 15) / 16, b4 = (a.h + 3) / 4 * cols, b8 = (a.h + 7) / 8 * cols;
+  return b4 * (a.cout / 128) * a.n > 256 && 5 * b8 <= 3 * b4;
+}
+
 }  // namespace
 
 // 16-bit types: images of at most 2^20 output elements a sample (2048 pixels of 512 channels), where the 128 x 128 tiles
-// leave at least three quarters of the compute units empty.  Measured against them, us at 1 / 2 / 4 samples: 17x23 of 512
-// channels 11.4 / - / 19.8 against 29.8 / - / 31.6; 32x32 15.3 / 19.4 / 26.1 against 30.2 / 29.9 / 32.9; 34x46
-// 17.3 / 23.7 / 45.3 against 30.2 / 33.8 / 40.7 (where four samples make two rounds of workgroups: the line is where
-// two samples still fill one); 68x92 of 256 channels, past the line, 16.2 / 31.0 / 62.4 against 21.7 / 24.9 / 41.6.
-// The choice may not depend on the batch: it changes the order of summation.
+// leave at least three quarters of the compute units empty.  Measured against them, us at one sample: 17x23 of 512
+// channels 11.4 against 29.8; 32x32 15.3 / 30.2; 34x46 17.3 / 30.2; 68x92 of 256 channels, past the line, 16.2 / 21.7.  The
+// line may not depend on the batch: the order of summation does.  What the batch decides is the tile, see batched_form
+// and pick_ksplit_tile.
 // fp32: every size; 64 -> 64 channels at 32x32 take 10 us where the vector-ALU kernel takes 97.
 bool conv_ksplit_supported(const ConvArgs& a) {
   if (a.ksize != 3 || a.upsample || a.x_nchw || a.y_nchw || a.x_dtype != a.op_dtype || a.rows_out || a.wide_tiles) return false;
@@ -483,12 +495,15 @@ const char* conv_ksplit_label(const ConvArgs& a) {
   static thread_local char buf[128];
   static const char* const tile[] = {"4, 8, 1, 1, 4, 2, 2", "4, 8, 1, 2, 4, 1, 4", "4, 16, 1, 2, 4, 2, 2", "4, 16, 2, 2, 4, 1, 2"};
   const int act = a.mean == nullptr && a.rows_in == nullptr && !a.groups_norm ? 0 : (a.silu ? 2 : 1);
-  if (a.op_dtype == WMDEC_F32) snprintf(buf, sizeof(buf), "conv_ksplit_kernel<float, 4, 8, 1, 1, %d, 1, 1, %d>", a.cin % 64 == 0 ? 4 : 2, act);
-  else snprintf(buf, sizeof(buf), "conv_ksplit_kernel<%s, %s, %d>", a.op_dtype == WMDEC_BF16 ? "wmdec::bf16_t" : "wmdec::f16_t", tile[pick_ksplit_tile(a)], act);
+  const char* const ty = a.op_dtype == WMDEC_BF16 ? "wmdec::bf16_t" : "wmdec::f16_t";
+  if (batched_form(a)) snprintf(buf, sizeof(buf), "conv_mfma_kernel<%s, %s, 8, 16, 1, 4, 1, 3, 32, %d, 2, 9>", ty, a.y_dtype == WMDEC_F32 ? "float" : ty, act);
+  else if (a.op_dtype == WMDEC_F32) snprintf(buf, sizeof(buf), "conv_ksplit_kernel<float, 4, 8, 1, 1, %d, 1, 1, %d>", a.cin % 64 == 0 ? 4 : 2, act);
+  else snprintf(buf, sizeof(buf), "conv_ksplit_kernel<%s, %s, %d>", ty, tile[pick_ksplit_tile(a)], act);
   return buf;
 }
 
 int launch_conv_ksplit(const ConvArgs& a, hipStream_t s) {
+  if (batched_form(a)) return launch_conv_quarters(a, s);
   if (a.op_dtype == WMDEC_F32) return a.cin % 64 == 0 ? launch_tile<float, 4, 8, 1, 1, 4, 1, 1>(a, s) : launch_tile<float, 4, 8, 1, 1, 2, 1, 1>(a, s);
   return a.op_dtype == WMDEC_BF16 ? launch_16bit<bf16_t>(a, s) : launch_16bit<f16_t>(a, s);
 }

@@ -38,9 +38,9 @@ namespace {
 // that the statistics reduction parks there
 constexpr int patch_floats(int ni, bool pairs = false) { return pairs ? 2 * 32 * (ni * 32 + 4) : 32 * (ni * 32 + 4) > 2048 ? 32 * (ni * 32 + 4) : 2048; }
 
-// PAIRS (NI = 1): two patches, and moments per pair of M tiles (four image rows) from the values written back to them:
-// a lane walks one channel of either tile's 32 pixels.  A second emission of the other form (per-lane sums parked in LDS)
-// cost 1.3 us of a launch of one round.
+// PAIRS (NI = 1): two patches, and moments of the two M tiles of a pair from the values written back to them: a lane walks
+// one channel of either tile's 32 pixels.  One triple for both tiles (four rows of 16 pixels), or one for each (4 x 8 pixels).
+// A second emission of the other form (per-lane sums parked in LDS) cost 1.3 us of a launch of one round.
 template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, bool RES, bool PAIRS>
 __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], float* wave_lds, int lane, int mt0, int ty0,
                                                int tx0, int co_w, const float* bias, const float* bias2, const T* rin, TO* yout, int h,
@@ -188,12 +188,14 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
       }
     }
     if constexpr (PAIRS) {
-      static_assert(NI == 1 && MTW == 16 && MTH == 2 && MT_PER_ROW == 1 && MI % 2 == 0, "a pair is four rows of 16 pixels");
+      static_assert(NI == 1 && MI % 2 == 0 && ((MTW == 16 && MTH == 2) || (MTW == 8 && MTH == 4 && MT_PER_ROW == 2)), "a pair is four rows of 16 pixels");
       if (mi % 2 == 1 && stats) {   // lanes 0-31: a channel of the pair's first tile, lanes 32-63: of the second
-        const int y0 = ty0 + (mi - 1 + lk) * MTH;
-        Moments m = block_moments<MTH, MTW, MTW * RW, RW>(wave_lds + lk * 32 * RW + lm, min(MTH, h - y0), min(MTW, w_out - tx0));
-        m = merge_to_first(butterfly(m, lane, 32), lane, cpg);
-        if (lk == 0 && (lm & (cpg - 1)) == 0 && m.n > 0.f) store_device(stats + (size_t)((co_w + lm) / cpg) * stats_stride, m);
+        const int y0 = ty0 + (mt0 + mi - 1 + lk) / MT_PER_ROW * MTH, x0 = tx0 + (mt0 + mi - 1 + lk) % MT_PER_ROW * MTW;
+        Moments m = block_moments<MTH, MTW, MTW * RW, RW>(wave_lds + lk * 32 * RW + lm, min(MTH, h - y0), min(MTW, w_out - x0));
+        if constexpr (MT_PER_ROW == 1) m = butterfly(m, lane, 32);
+        m = merge_to_first(m, lane, cpg);
+        if ((MT_PER_ROW == 2 || lk == 0) && (lm & (cpg - 1)) == 0 && m.n > 0.f)
+          store_device(stats + (size_t)((co_w + lm) / cpg) * stats_stride + (MT_PER_ROW == 2 ? lk : 0), m);
         stats += pair_stride;
       }
     }
@@ -223,20 +225,28 @@ constexpr int prefetch_ring(int steps, int room) {
 // and each k-step pays a full memory latency.
 // VALU_PER_MFMA: -1 pins the order as written (slot hook after the MFMAs of an M tile); >= 0 asks the scheduler to
 // interleave that many vector-ALU instructions behind every MFMA of a k-step.
+// KMAJOR: all taps of the chunk's first 16 channels come before those of its second 16 (otherwise both 16 tap by tap), the
+// weights of the two lie at bcur / bcur1, and flush(0 / 1) runs behind each.
 // AD: how many k-steps ahead the A fragments are read (1 or 2).  One step is MI - 1 MFMAs of slack, about the LDS
 // latency: enough where other wavefronts of the SIMD fill the gaps, too little for a wavefront that is alone on it.
-template <typename T, int MI, int NI, int KS, int KC, int ROW, int PS, int D, bool SLICED, int VALU_PER_MFMA, typename Slice, int AD = 1>
+struct NoFlush { __device__ void operator()(int) const {} };
+template <typename T, int MI, int NI, int KS, int KC, int ROW, int PS, int D, bool SLICED, int VALU_PER_MFMA, typename Slice, int AD = 1, bool KMAJOR = false, typename Flush = NoFlush>
 __device__ __forceinline__ void mfma_chunk(const T* buf, const int (&a_off)[MI], __amdgpu_buffer_rsrc_t wrsrc, int bcur, int bnext,
                                            int tap_stride, int kk_stride, int lane16, u32x4 (&bq)[D][NI],
-                                           f32x16 (&acc)[MI][NI], Slice&& slice) {
-  constexpr int KK = KC / 16, STEPS = KS * KS * KK;
+                                           f32x16 (&acc)[MI][NI], Slice&& slice, int bcur1 = 0, int bnext1 = 0, Flush&& flush = NoFlush()) {
+  constexpr int KK = KC / 16, TAPS = KS * KS, STEPS = TAPS * KK;
+  static_assert(!KMAJOR || KK == 2, "two groups of 16 channels");
+  // element offset of a k-step's pixels in the staged tile
+  auto a_at = [](int s) constexpr {
+    const int tap = KMAJOR ? s % TAPS : s / KK, kk = KMAJOR ? s / TAPS : s % KK;
+    return (tap / KS) * ROW + (tap % KS) * PS + kk * 16;
+  };
   static_assert(AD == 1 || AD == 2, "A fragments one or two k-steps ahead");
   u32x4 af[AD][MI];   // af[s % AD]: fragments of k-step s
 #pragma unroll
   for (int a = 0; a < AD && a < STEPS; ++a) {
-    const int tap = a / KK, kk = a % KK;
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) af[a][mi] = *reinterpret_cast<const u32x4*>(buf + a_off[mi] + (tap / KS) * ROW + (tap % KS) * PS + kk * 16);
+    for (int mi = 0; mi < MI; ++mi) af[a][mi] = *reinterpret_cast<const u32x4*>(buf + a_off[mi] + a_at(a));
   }
   // one k-step; the slot hook runs after the MFMAs of every M tile so that its vector-ALU work issues
   // while those MFMAs occupy the matrix pipe
@@ -244,11 +254,12 @@ __device__ __forceinline__ void mfma_chunk(const T* buf, const int (&a_off)[MI],
     constexpr int s = decltype(s_c)::value;
     {
       constexpr int sp = s + D - 1;
-      const int src = sp < STEPS ? bcur : bnext;
       constexpr int spp = sp < STEPS ? sp : sp - STEPS;
+      int at;
+      if constexpr (KMAJOR) at = (sp < STEPS ? (spp / TAPS ? bcur1 : bcur) : (spp / TAPS ? bnext1 : bnext)) + (spp % TAPS) * tap_stride;
+      else at = (sp < STEPS ? bcur : bnext) + (spp / KK) * tap_stride + (spp % KK) * kk_stride;
 #pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-        bq[sp % D][ni] = load_fragment(wrsrc, lane16, src + (spp / KK) * tap_stride + (spp % KK) * kk_stride + ni * 1024);
+      for (int ni = 0; ni < NI; ++ni) bq[sp % D][ni] = load_fragment(wrsrc, lane16, at + ni * 1024);
     }
     __builtin_amdgcn_sched_barrier(0);
     auto tile = [&](auto mi_c) {
@@ -256,8 +267,8 @@ __device__ __forceinline__ void mfma_chunk(const T* buf, const int (&a_off)[MI],
 #pragma unroll
       for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = Mma<T>::m32(af[s % AD][mi], bq[s % D][ni], acc[mi][ni]);
       if constexpr (s + AD < STEPS) {
-        constexpr int tap = (s + AD) / KK, kk = (s + AD) % KK;
-        af[s % AD][mi] = *reinterpret_cast<const u32x4*>(buf + a_off[mi] + (tap / KS) * ROW + (tap % KS) * PS + kk * 16);
+        constexpr int at = a_at(s + AD);
+        af[s % AD][mi] = *reinterpret_cast<const u32x4*>(buf + a_off[mi] + at);
       }
       if constexpr (SLICED) slice(std::integral_constant<int, s * MI + mi>{});
       if constexpr (VALU_PER_MFMA < 0) __builtin_amdgcn_sched_barrier(0);
@@ -273,6 +284,10 @@ __device__ __forceinline__ void mfma_chunk(const T* buf, const int (&a_off)[MI],
         if constexpr (j % NI == NI - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
         if constexpr (VALU_PER_MFMA > 0) __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER_MFMA, 0);
       });
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (KMAJOR && s % TAPS == TAPS - 1) {
+      flush(s / TAPS);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -295,19 +310,28 @@ constexpr int resident_workgroups(int acc_tiles, int wm, int wn) {
 // any other row stride costs a second pass per read), so for those patches the row stride is rounded up to 256 bytes.
 // One pixel slot behind the patch is spare: vectors that lie outside the image (or past the patch) are stored there,
 // where no MFMA reads them.
-constexpr int tile_row_elems(int tw, int pad, int kc) {
+// Where an M tile is 8 pixels wide and spans four rows, i and i + 16 are two rows apart and i and i + 8 one: the stride of a
+// row is then 128 modulo 256, that of eight pixels.
+constexpr int tile_row_elems(int tw, int pad, int kc, int mtw) {
   const int raw = (tw + 2 * pad) * (kc + 8);
-  return tw < 32 ? (raw * 2 + 255) / 256 * 128 : raw;
+  return mtw == 8 ? (raw * 2 + 127) / 256 * 128 + 64 : tw < 32 ? (raw * 2 + 255) / 256 * 128 : raw;
 }
-constexpr int tile_buf_elems(int th, int tw, int pad, int kc) { return (th + 2 * pad) * tile_row_elems(tw, pad, kc) + (kc + 8); }
+constexpr int tile_buf_elems(int th, int tw, int pad, int kc, int mtw) { return (th + 2 * pad) * tile_row_elems(tw, pad, kc, mtw) + (kc + 8); }
 
 // RING: 0 = weight-fragment ring sized by prefetch_ring; otherwise its length in k-steps (a divisor of the k-steps of
 // a chunk).  The whole-chunk ring is for launches that leave a compute unit at most two workgroups: there a wavefront
 // is alone on its SIMD, nothing else hides the latency of weights that come from beyond the L2 (every layer's weights
 // are new to the L2 inside a decoder run), and the registers of the third workgroup are free for it.
-// ROWS4: one of a pair of tiles, 4x16 and 8x16, of which the batch decides (see four_row_slots): a sample's bits must not
-// depend on that choice, so both keep the activation's roundings apart (PIN) and emit moments per four rows.
-template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int ACT, bool ROWS4 = false, int RING = 0>
+// MODE: kRows4 and kQuarters are forms between which and another kernel the batch decides, while a sample's bits must not
+// depend on that choice; so both keep the activation's roundings apart (PIN).
+//   kRows4     one of a pair of tiles, 4x16 and 8x16 (see four_row_slots): moments per four rows.
+//   kQuarters  the batched form of kernels_conv_ksplit.hip, with its order of summation: of every 64 input channels the
+//              k-th 16 belong to partial sum k, each of them is summed on its own, 16 channels and their nine taps at a
+//              time, and the four are added in order.  Here one after the other into a second set of accumulators, on M tiles of 4 x 8
+//              pixels, the blocks of that kernel's moments.
+enum ConvMode { kPlain = 0, kRows4 = 1, kQuarters = 2 };
+constexpr int m_tile_width(int tw, int mode) { return mode == kQuarters ? 8 : tw < 32 ? tw : 32; }
+template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int ACT, int MODE = kPlain, int RING = 0>
 __global__ __launch_bounds__(64 * WM * WN, RING > 6 ? 2 : resident_workgroups(wave_m_tiles(TH, TW, WM) * NI, WM, WN))
 void conv_mfma_kernel(MfmaParams p) {
   static_assert(WM * WN == 4 || WM * WN == 8, "four or eight wavefronts");
@@ -316,12 +340,13 @@ void conv_mfma_kernel(MfmaParams p) {
   constexpr int PAD = KS / 2;
   constexpr int HW_ = TW + 2 * PAD, HH_ = TH + 2 * PAD, HP = HW_ * HH_;
   constexpr int PS = KC + 8;                     // LDS pixel stride in elements (+16 B: conflict-free 16-byte reads)
-  constexpr int MTW = TW < 32 ? TW : 32, MTH = 32 / MTW, MT_PER_ROW = TW / MTW;
+  constexpr bool QUARTERS = MODE == kQuarters;
+  constexpr int MTW = m_tile_width(TW, MODE), MTH = 32 / MTW, MT_PER_ROW = TW / MTW;
   constexpr int TN = WN * NI * 32;
   constexpr int VPP = KC / 8;                    // 16-byte vectors per pixel per chunk
   constexpr int NV = (HP * VPP + NT - 1) / NT;   // vectors a thread stages per chunk
-  constexpr int ROW = tile_row_elems(TW, PAD, KC);       // LDS row stride of the staged tile, elements
-  constexpr int BUF = tile_buf_elems(TH, TW, PAD, KC);   // elements of one staged tile: the halo patch plus the spare slot
+  constexpr int ROW = tile_row_elems(TW, PAD, KC, MTW);       // LDS row stride of the staged tile, elements
+  constexpr int BUF = tile_buf_elems(TH, TW, PAD, KC, MTW);   // elements of one staged tile: the halo patch plus the spare slot
   constexpr int SPARE = HH_ * ROW;                       // element offset of the spare pixel slot
   constexpr int STEPS = KS * KS * (KC / 16), SLOTS = STEPS * MI;
   constexpr bool SLICED = KS == 3;               // activation of the next chunk is sliced into the MFMA sweep
@@ -375,11 +400,37 @@ void conv_mfma_kernel(MfmaParams p) {
   const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w), 0, p.w_bytes, 0x00020000);
   const int wcol = ((co0 >> 5) + wn * NI) * 1024;
   const int lane16 = lane * 16;
+  // QUARTERS: partial sum k takes the groups of 16 channels k, k + 4, k + 8, ...; the two groups of a chunk are kept for the current chunk and
+  // the two after it, and advance by running counters (a division per use cost 10 % of a launch of one round)
+  const int quarter = p.cin / 64;
+  int run_j = 0, run_k = 0;
+  auto next_group = [&]() {
+    const int g = run_j * 4 + run_k;
+    const bool wrap = ++run_j == quarter;
+    run_j = wrap ? 0 : run_j;
+    run_k += wrap ? 1 : 0;
+    return g;
+  };
+  struct Groups { int a, b; };
+  Groups grp[3] = {};     // of chunks c, c + 1, c + 2; past the last chunk: those of the last, a harmless reload
+  if constexpr (QUARTERS) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      if (i < 2 || p.cin > 2 * KC) { grp[i].a = next_group(); grp[i].b = next_group(); }
+      else grp[i] = grp[i - 1];
+    }
+  }
+  auto weights_at = [&](int chunk, int ahead, int kk) {   // chunk = c + ahead
+    if constexpr (QUARTERS) return __builtin_amdgcn_readfirstlane(wcol + (kk ? grp[ahead].b : grp[ahead].a) * kk_stride);   // (said to be uniform: else a loop around every load)
+    else return wcol + (chunk * KK + kk) * kk_stride;
+  };
   u32x4 bq[D][NI];
 #pragma unroll
-  for (int sp = 0; sp < D - 1; ++sp)
+  for (int sp = 0; sp < D - 1; ++sp) {
+    const int tap = QUARTERS ? sp % (KS * KS) : sp / KK, kk = QUARTERS ? sp / (KS * KS) : sp % KK;
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) bq[sp][ni] = load_fragment(wrsrc, lane16, wcol + (sp / KK) * tap_stride + (sp % KK) * kk_stride + ni * 1024);
+    for (int ni = 0; ni < NI; ++ni) bq[sp][ni] = load_fragment(wrsrc, lane16, weights_at(0, 0, kk) + tap * tap_stride + ni * 1024);
+  }
 
   // ---- staging: a thread owns NV (pixel, channel-octet) vectors of the halo tile; the octet is the same for all
   const int cvec = tid % VPP;
@@ -388,7 +439,7 @@ void conv_mfma_kernel(MfmaParams p) {
   // mask would make the compiler wait for it at the end of the branch), activated like any other, and stored to
   // the spare pixel slot behind the patch; its real slot is zeroed once, here, in both buffers.  A 1x1 convolution
   // has no halo: what its out-of-image pixels hold only reaches outputs that are never stored.
-  int src_off[NV];          // byte offset of the vector in x (chunk 0)
+  int src_off[NV];          // byte offset of the vector's pixel in x
   int dst_off[NV];          // element offset of its slot in a staged tile
   int src_pix[NV];          // index of its source pixel in the sample (0 outside the image); only the shortcut phase reads it
 #pragma unroll
@@ -404,7 +455,7 @@ void conv_mfma_kernel(MfmaParams p) {
     if (inside) {
       const int sy = p.upsample ? gy >> 1 : gy, sx = p.upsample ? gx >> 1 : gx;
       src_pix[i] = sy * w_in + sx;
-      src_off[i] = (src_pix[i] * p.cin + cvec * 8) * (int)sizeof(T);
+      src_off[i] = src_pix[i] * p.cin * (int)sizeof(T);
     }
     const bool keep = KS == 1 ? in_patch : inside;
     dst_off[i] = (keep ? hy * ROW + hx * PS : SPARE) + cvec * 8;
@@ -420,16 +471,21 @@ void conv_mfma_kernel(MfmaParams p) {
   // a few elements after every M tile's MFMAs, so that this vector-ALU work overlaps the matrix pipe instead of
   // forming a phase of its own.
   u32x4 raw[NV];
-  auto issue = [&](int chunk) {
-    const int cb = min(chunk, p.cin / KC - 1) * KC * (int)sizeof(T);   // past the last chunk: a harmless reload
+  // first channel of this thread's octet in chunk c + ahead; past the last chunk: that of the last, a harmless reload
+  auto channel = [&](int chunk, int ahead) -> int {
+    if constexpr (QUARTERS) return (cvec / 2 ? grp[ahead].b : grp[ahead].a) * 16 + cvec % 2 * 8;
+    else return min(chunk, p.cin / KC - 1) * KC + cvec * 8;
+  };
+  auto issue = [&](int chunk, int ahead) {
+    const int cb = channel(chunk, ahead) * (int)sizeof(T);
 #pragma unroll
     for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(xin + (unsigned)(src_off[i] + cb));
   };
   // word (two channels) of a staged vector: scale/shift (+ SiLU) with the table entries ab = (a0, b0, a1, b1)
-  auto activate_with = [&](uint32_t wv, const f32x4& ab) -> uint32_t { return wmdec::activate_word<T, ACT, ROWS4>(wv, ab); };
-  // table entries of word `part` of this thread's channel octet in the chunk that starts at channel c0
+  auto activate_with = [&](uint32_t wv, const f32x4& ab) -> uint32_t { return wmdec::activate_word<T, ACT, MODE != kPlain>(wv, ab); };
+  // table entries of word `part` of the octet that starts at channel c0
   auto table_entry = [&](int part, int c0) -> f32x4 {
-    if constexpr (ACT > 0) return *reinterpret_cast<const f32x4*>(s_ab + c0 + cvec * 8 + 2 * part);
+    if constexpr (ACT > 0) return *reinterpret_cast<const f32x4*>(s_ab + c0 + 2 * part);
     else return f32x4{0.f, 0.f, 0.f, 0.f};
   };
   auto activate_word = [&](uint32_t wv, int i, int part, int c0) -> uint32_t {
@@ -458,7 +514,7 @@ void conv_mfma_kernel(MfmaParams p) {
   // two LDS buffers with the tile's halo layout (only the centre tap is read), loads two chunks ahead; the main
   // loop below then adds the 3x3 contraction to the same accumulators, so the shortcut tensor never exists in
   // memory and the epilogue adds both biases.
-  if constexpr (KS == 3) {
+  if constexpr (KS == 3 && !QUARTERS) {
     if (p.x2) {
       const char* xin2 = reinterpret_cast<const char*>(p.x2) + (size_t)n * p.h * p.w_out * p.cin2 * sizeof(T);
       const int nch2 = p.cin2 / KC;
@@ -497,7 +553,7 @@ void conv_mfma_kernel(MfmaParams p) {
     }
   }
 
-  issue(0);
+  issue(0, 0);
   // (built behind the first chunk's loads, so that its own global loads overlap them)
   // per-channel scale/shift table: a = gamma*rstd, b = beta - mean*a.  With SiLU the table holds -log2(e) * (a, b):
   // the staged value is u = -log2(e) * t, from which silu(t) = t / (1 + 2^u) = u / (-log2(e) - log2(e) * 2^u) takes
@@ -507,7 +563,7 @@ void conv_mfma_kernel(MfmaParams p) {
     const float k = ACT == 2 ? -1.4426950408889634f : 1.0f;
     if (p.rows_in) {
       // mean / rstd of every group from the row triples its producer left: eight lanes per group take the rows
-      // round-robin; (mean, rstd) parked behind the table
+      // round-robin (16 in the form that has to reproduce a kernel with 16); (mean, rstd) parked behind the table
       float2* s_stat = s_ab + p.cin;
       // Launches that leave a wavefront alone on its SIMD (RING): gamma / beta of this thread's first two table
       // entries are requested together with the triples, one memory round trip less in front of the first chunk
@@ -519,10 +575,11 @@ void conv_mfma_kernel(MfmaParams p) {
         const int c = min(tid + j * NT, p.cin - 1);
         gpre[j] = p.gamma[c]; bpre[j] = p.beta[c];
       }
-      const int sub = tid & 7;
-      for (int g = tid >> 3; g < p.groups; g += NT / 8) {
+      constexpr int LANES = QUARTERS ? 16 : 8;
+      const int sub = tid % LANES;
+      for (int g = tid / LANES; g < p.groups; g += NT / LANES) {
         const Moments* row = p.rows_in + (size_t)(n * p.groups + g) * p.rows_in_count;
-        const float2 m = merge_row<8>(row, p.rows_in_count, sub, p.eps);
+        const float2 m = merge_row<LANES>(row, p.rows_in_count, sub, p.eps);
         if (sub == 0) s_stat[g] = m;
       }
       __syncthreads();
@@ -549,16 +606,38 @@ void conv_mfma_kernel(MfmaParams p) {
     }
   }
   __syncthreads();            // scale/shift table complete
-  activate_all(0, s_a);
-  issue(1);
+  activate_all(channel(0, 0), s_a);
+  issue(1, 1);
+  f32x16 total[QUARTERS ? MI : 1][NI];   // the partial sums so far
+#pragma unroll
+  for (int i = 0; i < (QUARTERS ? MI : 1); ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) total[i][j][r] = 0.f;
+  int left = quarter;   // groups of 16 channels until the running partial sum is complete
+  auto flush = [&](int) {
+    if constexpr (QUARTERS) {
+      if (--left == 0) {
+        left = quarter;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { total[i][j][r] += acc[i][j][r]; acc[i][j][r] = 0.f; }
+      }
+    }
+  };
   __syncthreads();
   for (int c = 0; c < nchunks; ++c) {
     const bool more = c + 1 < nchunks;
-    const int bcur = wcol + c * KK * kk_stride;
-    const int bnext = more ? bcur + KK * kk_stride : bcur;
+    const int next = more ? c + 1 : c;
+    const int bcur = weights_at(c, 0, 0), bnext = weights_at(next, 1, 0);
+    const int bcur1 = QUARTERS ? weights_at(c, 0, 1) : 0, bnext1 = QUARTERS ? weights_at(next, 1, 1) : 0;
     const T* buf = s_a + (c & 1) * BUF;
     T* nbuf = s_a + ((c + 1) & 1) * BUF;
-    const int c0n = (c + 1) * KC;
+    const int c0n = channel(c + 1, 1);
     if constexpr (SLICED) {
       // Slots FIRST .. SLOTS-1 share the NV*4 words of the next chunk evenly.  All vectors of a thread hold the same
       // channel octet, so the words are taken part by part (word `part` of every vector, then the next part) and
@@ -581,40 +660,51 @@ void conv_mfma_kernel(MfmaParams p) {
       };
       // the last chunk activates a harmless reload into the buffer nobody reads: one instruction stream, no
       // control flow inside the pinned schedule
-      mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, true, SPREAD, decltype(slice)&, (RING > 6 ? 2 : 1)>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, slice);
+      mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, true, SPREAD, decltype(slice)&, (RING > 6 ? 2 : 1), QUARTERS>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, slice, bcur1, bnext1, flush);
     } else {
       auto none = [](auto) {};
       mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, false, -1, decltype(none)&, (RING > 6 ? 2 : 1)>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, none);
       if (more) activate_all(c0n, nbuf);
     }
-    issue(c + 2);
+    issue(c + 2, 2);
+    if constexpr (QUARTERS) {
+      grp[0] = grp[1]; grp[1] = grp[2];
+      if (c + 3 < nchunks) { grp[2].a = next_group(); grp[2].b = next_group(); }
+    }
     __syncthreads();          // other buffer staged; this one free for chunk c+2
   }
 
   // ---- epilogue: bias, residual, one rounding, store (through a wavefront-private LDS patch over the tile buffers)
   TO* yout = reinterpret_cast<TO*>(p.y) + (size_t)n * p.h * p.w_out * p.cout;
   const T* rin = p.res ? reinterpret_cast<const T*>(p.res) + (size_t)n * p.h * p.w_out * p.cout : nullptr;
-  float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(NI, ROWS4);
-  // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row], or by rows of four (an 8-row tile has two)
-  const int slot = ROWS4 ? TH / 4 * (tile / p.tiles_x) * p.tiles_x + tile % p.tiles_x : tile * WM + wm;
+  constexpr bool PAIRS = MODE != kPlain;
+  float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(NI, PAIRS);
+  // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row], or by blocks of 4 rows x 16 or 8 pixels
+  const int per_row = QUARTERS ? (p.w_out + 7) / 8 : p.tiles_x;   // slots of a row of blocks
+  const int slot = PAIRS ? ty0 / 4 * per_row + tx0 / (QUARTERS ? 8 : TW) : tile * WM + wm;
   Moments* st = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + slot : nullptr;
-  if (rin)
-    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true, ROWS4>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
-                                                              p.bias2, rin, yout, p.h, p.w_out, p.cout, false, st, p.stats_cpg, p.stats_slots, p.tiles_x);
-  else
-    epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false, ROWS4>(acc, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
-                                                               p.bias2, rin, yout, p.h, p.w_out, p.cout, p.y_nchw != 0, st, p.stats_cpg, p.stats_slots, p.tiles_x);
+  auto store = [&](const f32x16 (&sums)[MI][NI]) {
+    if (rin)
+      epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true, PAIRS>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
+                                                                p.bias2, rin, yout, p.h, p.w_out, p.cout, false, st, p.stats_cpg, p.stats_slots, per_row);
+    else
+      epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false, PAIRS>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
+                                                                 p.bias2, rin, yout, p.h, p.w_out, p.cout, p.y_nchw != 0, st, p.stats_cpg, p.stats_slots, per_row);
+  };
+  if constexpr (QUARTERS) store(total);
+  else store(acc);
 
   if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, co0, TN, WM, tid, lane);
 }
 
-template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int RING = 0, bool ROWS4 = false>
+template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int RING = 0, int MODE = kPlain>
 int launch_cfg(const ConvArgs& a, hipStream_t s) {
   constexpr int PAD = KS / 2;
   constexpr int TN = WN * NI * 32;
   MfmaParams p = conv_params(a, TH, TW, TN, WM, a.h, a.w);
-  if (ROWS4) p.stats_slots = ((a.h + 3) / 4) * p.tiles_x;
-  WMDEC_REQUIRE(!ROWS4 || !a.rows_out, WMDEC_ERR_UNSUPPORTED, "conv_mfma: this tile hands over no rows");
+  if (MODE != kPlain) p.stats_slots = ((a.h + 3) / 4) * (MODE == kQuarters ? (a.w + 7) / 8 : p.tiles_x);
+  WMDEC_REQUIRE(MODE != kQuarters || (!a.x2 && a.cin % 64 == 0), WMDEC_ERR_UNSUPPORTED, "conv_mfma: this form takes no shortcut");
+  WMDEC_REQUIRE(MODE == kPlain || !a.rows_out, WMDEC_ERR_UNSUPPORTED, "conv_mfma: this tile hands over no rows");
   const int rc = check_hand_over(p);
   if (rc != WMDEC_OK) return rc;
   p.w = a.wt;
@@ -626,13 +716,13 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
     p.w2_bytes = (int)(packed_elems(1, a.cout, a.cin2) * sizeof(T));
   }
   constexpr int NT = 64 * WM * WN;
-  size_t smem = (((size_t)2 * tile_buf_elems(TH, TW, PAD, KC) * 2 + 15) & ~(size_t)15) + (size_t)(a.cin + a.groups) * sizeof(float2);
-  const size_t patch = (size_t)(WM * WN) * patch_floats(NI, ROWS4) * sizeof(float);   // epilogue patches of the wavefronts
+  size_t smem = (((size_t)2 * tile_buf_elems(TH, TW, PAD, KC, m_tile_width(TW, MODE)) * 2 + 15) & ~(size_t)15) + (size_t)(a.cin + a.groups) * sizeof(float2);
+  const size_t patch = (size_t)(WM * WN) * patch_floats(NI, MODE != kPlain) * sizeof(float);   // epilogue patches of the wavefronts
   if (smem < patch) smem = patch;
   WMDEC_REQUIRE(smem <= 80 * 1024, WMDEC_ERR_UNSUPPORTED, "conv_mfma: %zu bytes of LDS needed", smem);
-  void (*kern)(MfmaParams) = !p.norm ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 0, ROWS4, RING>
-                             : (a.silu ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 2, ROWS4, RING>
-                                       : conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 1, ROWS4, RING>);
+  void (*kern)(MfmaParams) = !p.norm ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 0, MODE, RING>
+                             : (a.silu ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 2, MODE, RING>
+                                       : conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 1, MODE, RING>);
   // once per instantiation and activation mode (80 KiB: two workgroups per compute unit)
   static std::once_flag attr_once[3];
   hipError_t attr_err = hipSuccess;
@@ -713,9 +803,9 @@ int launch_3x3(const ConvArgs& a, hipStream_t s) {
     case T128x64: return launch_cfg<T, TO, 8, 16, 4, 1, 2, 3, 32>(a, s);
     case T128x128_1x4:
       return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32>(a, s);
-    case T64x128: return launch_cfg<T, TO, 4, 16, 1, 4, 1, 3, 32, 9, true>(a, s);
+    case T64x128: return launch_cfg<T, TO, 4, 16, 1, 4, 1, 3, 32, 9, kRows4>(a, s);
     case T128x128_ROWS4:
-      return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18, true>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 0, true>(a, s);
+      return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18, kRows4>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 0, kRows4>(a, s);
     case T128x256: return launch_cfg<T, TO, 8, 16, 1, 4, 2, 3, 32>(a, s);
     default: return launch_cfg<T, TO, 8, 32, 4, 1, 1, 3, 32>(a, s);
   }
@@ -787,10 +877,17 @@ const char* conv_mfma_label(const ConvArgs& a) {
   const TileShape& ts = kTiles[t];
   const char* ty = a.op_dtype == WMDEC_BF16 ? "wmdec::bf16_t" : "wmdec::f16_t";
   const int act = a.mean == nullptr && a.rows_in == nullptr && !a.groups_norm ? 0 : (a.silu ? 2 : 1);
-  snprintf(buf, sizeof(buf), "conv_mfma_kernel<%s, %s, %d, %d, %d, %d, %d, %d, %d, %d, %s, %d>", ty,
+  snprintf(buf, sizeof(buf), "conv_mfma_kernel<%s, %s, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d>", ty,
            a.y_dtype == WMDEC_F32 ? "float" : ty, ts.th, ts.tw, ts.wm, ts.wn, ts.ni, a.ksize, kc, act,
-           t == T64x128 || t == T128x128_ROWS4 ? "true" : "false", a.ksize == 3 && whole_chunk_ring(a) ? 18 : t == T64x128 ? 9 : 0);
+           t == T64x128 || t == T128x128_ROWS4 ? kRows4 : kPlain, a.ksize == 3 && whole_chunk_ring(a) ? 18 : t == T64x128 ? 9 : 0);
   return buf;
+}
+
+int launch_conv_quarters(const ConvArgs& a, hipStream_t s) {
+  WMDEC_REQUIRE(conv_mfma_supported(a) && a.ksize == 3 && !a.upsample && !a.y_nchw && a.cout % 128 == 0, WMDEC_ERR_UNSUPPORTED, "conv_mfma: no layer for this form");
+  if (a.op_dtype == WMDEC_BF16)
+    return a.y_dtype == WMDEC_F32 ? launch_cfg<bf16_t, float, 8, 16, 1, 4, 1, 3, 32, 9, kQuarters>(a, s) : launch_cfg<bf16_t, bf16_t, 8, 16, 1, 4, 1, 3, 32, 9, kQuarters>(a, s);
+  return a.y_dtype == WMDEC_F32 ? launch_cfg<f16_t, float, 8, 16, 1, 4, 1, 3, 32, 9, kQuarters>(a, s) : launch_cfg<f16_t, f16_t, 8, 16, 1, 4, 1, 3, 32, 9, kQuarters>(a, s);
 }
 
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s) {

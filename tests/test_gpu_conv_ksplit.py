@@ -114,3 +114,35 @@ def test_moments_and_bits_do_not_depend_on_the_batch(cin, cout, groups, h, w):
                 wmdec.gn_silu_conv3x3_stats(x, m, r, gamma, beta, 32, True, wt, b, None, y2, groups, EPS, mo, ro, small[:wide - 12])
     for g in got[1:]:
         assert all(torch.equal(a, b) for a, b in zip(got[0], g))
+
+
+# batches past one round take 128 x 128 tiles: one 16-channel group per partial sum (cin 64), an odd number of them (a partial sum
+# ends inside a chunk), even ones; a single column, ragged blocks in both directions; outputs as stored and in fp32.  The
+# last: images of one row, which stay with the small tiles
+@pytest.mark.parametrize("dtype,n,cin,cout,h,w,norm,res,y32", [
+    ("f16", 48, 64, 512, 7, 1, True, False, False), ("bf16", 24, 64, 128, 35, 21, True, True, False), ("f16", 16, 192, 512, 13, 30, True, False, True),
+    ("f16", 8, 512, 512, 17, 23, True, True, False), ("bf16", 4, 512, 512, 34, 46, True, False, False), ("f16", 15, 320, 256, 36, 7, True, True, True),
+    ("bf16", 70, 128, 256, 5, 9, False, False, False), ("f16", 100, 128, 256, 1, 9, False, False, False)])
+def test_large_batches_keep_the_bits_of_a_sample(dtype, n, cin, cout, h, w, norm, res, y32):
+    c = case(44, dtype, n, cin, cout, h, w)
+    xd, wt, b, rd = G.dev_nhwc(c["x"], dtype), G.pack(c["w"], dtype), G.dev_f32(c["b"]), G.dev_nhwc(c["res"], dtype) if res else None
+    gamma, beta, yt = G.dev_f32(c["gamma"]), G.dev_f32(c["beta"]), torch.float32 if y32 else G.TORCH[dtype]
+    mean, rstd = G.gn_stats(xd, 32, EPS) if norm else (None, None)
+
+    def run(lo, k):
+        y, check = G.canaried((k, h, w, cout), yt)
+        mo, ro = torch.empty(k * 32, device="cuda"), torch.empty(k * 32, device="cuda")
+        ws = torch.empty(wmdec.conv_stats_workspace_bytes(G.ENUM[dtype], wmdec.F32 if y32 else G.ENUM[dtype], k, h, w, cin, cout, 32), dtype=torch.uint8, device="cuda")
+        part = lambda t, m=1: None if t is None else t[lo * m:(lo + k) * m].contiguous()
+        wmdec.gn_silu_conv3x3_stats(part(xd), part(mean, 32), part(rstd, 32), gamma, beta, 32, True, wt, b, part(rd), y, 32, EPS, mo, ro, ws)
+        torch.cuda.synchronize()
+        check()
+        return y, mo, ro
+
+    y, mo, ro = run(0, n)
+    for i in (0, n // 2, n - 1):
+        y1, m1, r1 = run(i, 1)
+        assert torch.equal(y[i:i + 1], y1) and torch.equal(mo[32 * i:32 * i + 32], m1) and torch.equal(ro[32 * i:32 * i + 32], r1), i
+    a = ref.group_norm(c["x"][-1:], 32, EPS, c["gamma"], c["beta"], apply_silu=True) if norm else c["x"][-1:]
+    want = ref.conv2d(a, c["w"], c["b"]) + (c["res"][-1:] if res else 0)
+    assert ref.rel_err(G.host_nchw(y[-1:]), want) <= G.TOL[dtype]
