@@ -14,7 +14,7 @@ struct MfmaParams {
   const void* x; const float* mean; const float* rstd; const float* gamma; const float* beta;
   const void* w; const float* bias; const void* res; void* y;
   int silu, groups, norm;
-  int n, h, w_out, cin, cout, upsample;
+  int n, h, w_out, cin, cout;
   int tiles_x, tiles_y, ntiles, total;
   int cin_blocks, cout_blocks;   // packed-layout extents: ceil(cin/16), ceil(cout/32)
   int w_bytes;                   // size of the packed weights the kernel may read
@@ -186,7 +186,7 @@ inline MfmaParams conv_params(const ConvArgs& a, int th, int tw, int tn, int slo
   p.x = a.x; p.mean = a.mean; p.rstd = a.rstd; p.gamma = a.gamma; p.beta = a.beta;
   p.w = nullptr; p.w_bytes = 0; p.bias = a.bias; p.res = a.res; p.y = a.y;
   p.silu = a.silu; p.groups = a.groups; p.norm = a.mean != nullptr || a.rows_in != nullptr;
-  p.n = a.n; p.h = a.h; p.w_out = a.w; p.cin = a.cin; p.cout = a.cout; p.upsample = a.upsample;
+  p.n = a.n; p.h = a.h; p.w_out = a.w; p.cin = a.cin; p.cout = a.cout;
   p.tiles_x = (w_t + tw - 1) / tw; p.tiles_y = (h_t + th - 1) / th; p.ntiles = (a.cout + tn - 1) / tn;
   p.total = p.tiles_x * p.tiles_y * p.ntiles * a.n;
   p.cin_blocks = packed_cin_blocks(a.cin); p.cout_blocks = packed_cout_blocks(a.cout); p.y_nchw = a.y_nchw;

@@ -17,8 +17,6 @@
 // the other buffer in compile-time slots inside the sweep of chunk c, with one
 // workgroup barrier per chunk.  Two or three workgroups fit on a compute unit, so
 // the prologue and epilogue of one overlap the sweeps of the others.
-// A nearest-2x upsample in front of the convolution is folded into the staging
-// address (what kernels_conv_up.hip does not take).
 #include <stdio.h>
 
 #include <mutex>
@@ -374,7 +372,6 @@ void conv_mfma_kernel(MfmaParams p) {
   const int tile = L % tiles;
   const int ty0 = (tile / p.tiles_x) * TH, tx0 = (tile % p.tiles_x) * TW;
   const int co0 = nt * TN;
-  const int h_in = p.upsample ? p.h >> 1 : p.h, w_in = p.upsample ? p.w_out >> 1 : p.w_out;
 
   f32x16 acc[MI][NI];
 #pragma unroll
@@ -434,7 +431,7 @@ void conv_mfma_kernel(MfmaParams p) {
 
   // ---- staging: a thread owns NV (pixel, channel-octet) vectors of the halo tile; the octet is the same for all
   const int cvec = tid % VPP;
-  const char* xin = reinterpret_cast<const char*>(p.x) + (size_t)n * h_in * w_in * p.cin * sizeof(T);   // uniform base
+  const char* xin = reinterpret_cast<const char*>(p.x) + (size_t)n * p.h * p.w_out * p.cin * sizeof(T);   // uniform base
   // Zero padding without per-element work: a vector outside the image is loaded from pixel 0 (a load under a lane
   // mask would make the compiler wait for it at the end of the branch), activated like any other, and stored to
   // the spare pixel slot behind the patch; its real slot is zeroed once, here, in both buffers.  A 1x1 convolution
@@ -453,8 +450,7 @@ void conv_mfma_kernel(MfmaParams p) {
     src_off[i] = 0;
     src_pix[i] = 0;
     if (inside) {
-      const int sy = p.upsample ? gy >> 1 : gy, sx = p.upsample ? gx >> 1 : gx;
-      src_pix[i] = sy * w_in + sx;
+      src_pix[i] = gy * p.w_out + gx;
       src_off[i] = src_pix[i] * p.cin * (int)sizeof(T);
     }
     const bool keep = KS == 1 ? in_patch : inside;
@@ -760,7 +756,7 @@ constexpr TileShape kTiles[kNumTiles] = {
 // channels 45x80 against 93.2 / 157.5 / 286.0, at 256 channels 68x92 61.5 / 92.1 / 157.9 against 61.3 / 92.5 / 158.8.
 bool four_row_slots(const ConvArgs& a) {
   const long blocks = (long)((a.h + 3) / 4) * ((a.w + 15) / 16);
-  return a.ksize == 3 && !a.upsample && !a.y_nchw && a.cout % 128 == 0 && !a.rows_out && !a.wide_tiles && blocks <= 128 && blocks * (a.cout / 128) <= 256;
+  return a.ksize == 3 && !a.y_nchw && a.cout % 128 == 0 && !a.rows_out && !a.wide_tiles && blocks <= 128 && blocks * (a.cout / 128) <= 256;
 }
 
 // which tile shape a launch uses; a function of the per-sample shape only (but for the pair above), so that every
@@ -835,7 +831,7 @@ int launch_type(const ConvArgs& a, hipStream_t s) {
 }  // namespace
 
 bool conv_mfma_supported(const ConvArgs& a) {
-  if (!is_16bit(a.op_dtype) || a.x_dtype != a.op_dtype) return false;
+  if (!is_16bit(a.op_dtype) || a.x_dtype != a.op_dtype || a.upsample) return false;
   if (a.res && a.res_dtype != a.op_dtype) return false;
   if (a.y_dtype != a.op_dtype && a.y_dtype != WMDEC_F32) return false;
   if (a.x_nchw) return false;
@@ -884,7 +880,7 @@ const char* conv_mfma_label(const ConvArgs& a) {
 }
 
 int launch_conv_quarters(const ConvArgs& a, hipStream_t s) {
-  WMDEC_REQUIRE(conv_mfma_supported(a) && a.ksize == 3 && !a.upsample && !a.y_nchw && a.cout % 128 == 0, WMDEC_ERR_UNSUPPORTED, "conv_mfma: no layer for this form");
+  WMDEC_REQUIRE(conv_mfma_supported(a) && a.ksize == 3 && !a.y_nchw && a.cout % 128 == 0, WMDEC_ERR_UNSUPPORTED, "conv_mfma: no layer for this form");
   if (a.op_dtype == WMDEC_BF16)
     return a.y_dtype == WMDEC_F32 ? launch_cfg<bf16_t, float, 8, 16, 1, 4, 1, 3, 32, 9, kQuarters>(a, s) : launch_cfg<bf16_t, bf16_t, 8, 16, 1, 4, 1, 3, 32, 9, kQuarters>(a, s);
   return a.y_dtype == WMDEC_F32 ? launch_cfg<f16_t, float, 8, 16, 1, 4, 1, 3, 32, 9, kQuarters>(a, s) : launch_cfg<f16_t, f16_t, 8, 16, 1, 4, 1, 3, 32, 9, kQuarters>(a, s);

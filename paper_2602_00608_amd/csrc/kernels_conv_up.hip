@@ -176,7 +176,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
   const size_t sample = (size_t)n * p.h * p.w_out * p.cout;
   const int cpg = p.stats_cpg;
   // output bytes of the sample are addressed by 32-bit offsets (< 2^31, checked on the host); a lane without a pixel
-  // gets an offset behind the sample, where a store is dropped
+  // gets an offset of 2^31, behind any sample, where a store is dropped (a row further is still below 2^32)
   const int es = y_f32 ? 4 : 2;
   const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(p.y) + sample * es, 0, p.h * p.w_out * p.cout * es, 0x00020000);
   unsigned y_off[MI];
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
     const int gy = 2 * (wm * MI + mi) + lm / GW, gx = lm % GW;
     const int iy = ty0 + gy, ix = tx0 + gx;
     live[mi] = gy < TH && gx < TW && iy < h_in && ix < w_in;
-    y_off[mi] = live[mi] ? ((2 * iy * p.w_out + 2 * ix) * p.cout + co_w + (y_f32 ? 4 : 8) * lk) * es : 0x7fff0000u;
+    y_off[mi] = live[mi] ? ((2 * iy * p.w_out + 2 * ix) * p.cout + co_w + (y_f32 ? 4 : 8) * lk) * es : 0x80000000u;
     live_px += __builtin_popcountll(__ballot(live[mi])) / 2;   // (both halves of the wavefront hold every pixel)
     if (mi == 0) first_px = live_px;
   }
@@ -329,8 +329,8 @@ bool conv_up_supported(const ConvArgs& a) {
   if (a.mean || a.groups_norm || a.rows_in || a.res || a.x2 || a.cin2 || (a.y_dtype != a.op_dtype && a.y_dtype != WMDEC_F32)) return false;
   if (a.cin % KC != 0 || a.cout % kTN != 0 || a.h % 2 != 0 || a.w % 2 != 0 || !packed_offsets_fit(9, a.cout, a.cin, a.op_dtype)) return false;
   if (a.stats_ws && conv_up_stats_slots(a) == 0) return false;
-  // 32-bit byte offsets per sample, with room for the offset of a dropped store
-  return (long)(a.h / 2) * (a.w / 2) * a.cin < (1L << 29) && (long)a.h * a.w * a.cout * (long)dtype_size(a.y_dtype) < 0x7f000000L;
+  // 32-bit byte offsets per sample
+  return (long)(a.h / 2) * (a.w / 2) * a.cin < (1L << 29) && (long)a.h * a.w * a.cout * (long)dtype_size(a.y_dtype) < (1L << 31);
 }
 
 int conv_up_stats_slots(const ConvArgs& a) {
