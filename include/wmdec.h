@@ -152,9 +152,10 @@ int wmdec_gn_silu_conv3x3_stats(const void* x, int act_dtype, const float* mean,
  * i.e. a contraction over K = 9*cin + cin2.  x2: [n,h,w,cin2] of act_dtype, taken
  * as stored (no normalisation); w2_packed: [cout][cin2] packed with k = 1; bias2
  * fp32 [cout] or NULL.  x2 and y must not overlap.  Shapes the matrix-core
- * kernel takes (16-bit types, cin % 32 == 0, cin2 % 32 == 0, cout % 64 == 0) run
- * as one launch; anything else (and F32) as two launches of the general kernel,
- * the second adding the shortcut it finds in y. */
+ * kernels take (16-bit types: cin % 32 == 0, cin2 % 32 == 0, cout % 64 == 0;
+ * F32: cin and cout % 32 == 0, cin2 % 32 == 0, or % 64 where cin % 64 == 0) run as
+ * one launch; anything else as two launches of the general kernel, the second
+ * adding the shortcut it finds in y. */
 int wmdec_gn_silu_conv3x3_shortcut(const void* x, int act_dtype, const float* mean, const float* rstd,
                                    const float* gamma, const float* beta, int groups, int apply_silu,
                                    const void* w_packed, const float* bias,

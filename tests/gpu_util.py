@@ -42,7 +42,7 @@ def pack(w_oihw, dtype):
 
 
 def pack_upconv(w_oihw, dtype):
-    """Pack [cout,cin,3,3] float32 weights of an upsampling convolution (9-tap pack + phase pack) through the ABI."""
+    """Pack [cout,cin,3,3] float32 weights of an upsampling convolution through the ABI."""
     cout, cin, _, _ = w_oihw.shape
     src = torch.from_numpy(np.ascontiguousarray(w_oihw, dtype=np.float32)).cuda()
     nbytes = wmdec.upconv_packed_bytes(cout, cin, ENUM[dtype])

@@ -162,7 +162,7 @@ def test_argument_errors_are_reported_without_a_gpu():
     assert l.wmdec_conv_packed_bytes(64, 64, 3, wmdec.F32) == 9 * 64 * 64 * 4
     assert l.wmdec_conv_packed_bytes(3, 4, 3, wmdec.BF16) == 9 * 32 * 16 * 2   # padded to 32 x 16 fragments
     assert l.wmdec_conv_packed_bytes(64, 64, 2, wmdec.F32) == 0
-    # upsampling convolution: the 9-tap pack plus the 16-tap phase pack
+    # upsampling convolution: the 9-tap pack, and room for 16 more taps that is kept for buffers sized by earlier versions
     assert l.wmdec_upconv_packed_bytes(64, 64, wmdec.F16) == (9 + 16) * 64 * 64 * 2
     assert l.wmdec_upconv_packed_bytes(64, 64, 9) == 0
     assert l.wmdec_pack_upconv_weights(p, wmdec.F16, 64, 64, 2 * p, wmdec.F16, None) == wmdec.ERR_INVALID_ARG   # source type

@@ -127,7 +127,7 @@ def check_staged(errs, dtype):
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_workload3_resblock_full_size(dtype):
     """Workload 3 as stated: x[1,128,480,720], GN(32) -> SiLU -> conv 128->128, twice, + x.  At this size the
-    convolutions take the 256-pixel x 128-channel tile (1380 workgroups), compared here at their own outputs."""
+    convolutions take the 128-pixel x 128-channel tile (2700 workgroups), compared here at their own outputs."""
     x = synth.activation(2, (1, 128, 480, 720), True)
     p = resblock_params(synth.weight_seed(2), 128, 128, True)
     check_staged(staged_resblock(G.dev_nhwc(x, dtype), x, p, dtype), dtype)
@@ -136,9 +136,8 @@ def test_workload3_resblock_full_size(dtype):
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_workload2_upsample_stage_full_size(dtype):
     """Workload 2 as stated: x[1,256,120,180] -> nearest-2x -> conv3x3 256->256 -> ResBlock(256) at 240x360.  The
-    upsampling convolution (phase-decomposed in f16: 2760 workgroups; nine taps with the gather in bf16) and the
-    ResBlock convolutions (128-pixel tile with one weight fragment per four MFMAs) are each compared at their own
-    output."""
+    upsampling convolution (nine products per input pixel in both types: 864 workgroups) and the ResBlock convolutions
+    (128-pixel tile with one weight fragment per four MFMAs) are each compared at their own output."""
     x = synth.activation(1, (1, 256, 120, 180), True)
     r = np.random.default_rng(synth.weight_seed(1))
     wu, bu = synth.conv_params(r, 256, 256, 3, True)

@@ -388,7 +388,7 @@ def test_upsample2x_conv3x3(dtype, ydtype, n, cin, cout, h, w):
     assert ref.rel_err(G.host_nchw(y), want) <= G.TOL[dtype] / (2 if ydtype == "f32" else 1)
 
 
-# 32 channels: general kernel; 64: matrix-core kernel, 3x3 form (bf16) and phase-decomposed form (f16)
+# 32 channels: general kernel; 64: the upsampling kernel on the matrix cores
 @pytest.mark.parametrize("ch,dtype", [(32, "bf16"), (64, "bf16"), (64, "f16")])
 def test_upconv_gather_index_map_bit_exact(ch, dtype):
     """One-hot kernels turn the fused upsample-conv into a pure gather: the output must equal the
