@@ -92,6 +92,7 @@ def main():
     # cin, cout, h_out, w_out, kernel, upsample, normalise + SiLU on load, residual
     convs = [(128, 128, 480, 720, 3, 0, 1, 1), (256, 128, 480, 720, 3, 0, 1, 0), (256, 256, 240, 360, 3, 0, 1, 1),
              (512, 256, 240, 360, 3, 0, 1, 0), (512, 512, 120, 180, 3, 0, 1, 1), (512, 512, 60, 90, 3, 0, 1, 1),
+             (512, 512, 34, 46, 3, 0, 1, 1), (512, 512, 17, 23, 3, 0, 1, 1),      # of a 136x184 frame
              (256, 256, 480, 720, 3, 1, 0, 0), (512, 512, 240, 360, 3, 1, 0, 0), (512, 512, 120, 180, 3, 1, 0, 0),
              (256, 128, 480, 720, 1, 0, 0, 0), (512, 256, 240, 360, 1, 0, 0, 0), (512, 1536, 60, 90, 1, 0, 1, 0),
              ]
