@@ -545,3 +545,14 @@ def test_measure_copy_bit_exact(nbytes):
             with pytest.raises(wmdec.WmdecError) as e:
                 wmdec.measure_copy(bad_src, bad_dst)
             assert e.value.status == wmdec.ERR_INVALID_ARG
+
+
+# ------------------------------------------------------------------ binding: the stream a call is enqueued on
+def test_calls_are_enqueued_on_the_current_stream():
+    """The raw handle the binding asks for is that of torch's current stream, inside and outside a stream context."""
+    side = torch.cuda.Stream()
+    outer = torch.cuda.current_stream().cuda_stream
+    assert wmdec._stream() == outer
+    with torch.cuda.stream(side):
+        assert wmdec._stream() == side.cuda_stream != outer
+    assert wmdec._stream() == outer
