@@ -98,7 +98,7 @@ struct Param {  // one canonical parameter
 };
 
 struct Step {
-  enum Kind { STATS, CONV, QKV_TRANSPOSE_V, FLASH, NONE } kind;
+  enum Kind { STATS, CONV, FLASH, NONE } kind;
   int src = BUF_NONE, dst = BUF_NONE, res = BUF_NONE;
   int h = 0, w = 0, cin = 0, cout = 0;   // conv: OUTPUT h, w; stats: tensor h, w, c = cin
   int ksize = 3, upsample = 0, norm = 0, silu = 0;
@@ -332,7 +332,7 @@ static int build_plan(wmdec_decoder& d) {
   }
   B.resblock("mid.res1", cur, other(1), other(2), h, w, c0, c0);
   cur = other(2);
-  {  // attention: stats, fused qkv projection, V transpose, flash core, output projection + residual
+  {  // attention: stats, fused qkv projection, flash core, output projection + residual
     Step q; q.kind = Step::CONV; q.src = cur; q.to_attn = 1; q.h = h; q.w = w; q.cin = c0; q.cout = 3 * c0; q.ksize = 1;
     q.norm = 1; q.silu = 0;
     B.norm_params("mid.attn.norm", c0, &q.gamma_off, &q.beta_off);
@@ -347,9 +347,6 @@ static int build_plan(wmdec_decoder& d) {
     q.b_off = d.qkv_b_off;
     B.stats(cur, h, w, c0);
     d.steps.push_back(q); B.count_conv(q);
-    Step tv; tv.kind = Step::QKV_TRANSPOSE_V; tv.h = h; tv.w = w; tv.cin = c0;
-    tv.bytes = 2.0 * h * w * c0 * dtype_size(c.act_dtype);
-    d.steps.push_back(tv); d.launches += 1;
     Step f; f.kind = Step::FLASH; f.h = h; f.w = w; f.cin = c0;
     f.flops = 4.0 * (double)(h * w) * (double)(h * w) * c0;
     f.flops_dense = f.flops;
@@ -408,7 +405,7 @@ static const Param* find_param(const wmdec_decoder* d, const char* name) {
 
 // layout of the workspace for `batch` frames
 struct WsLayout {
-  size_t tickets, conv_tickets, conv_ticket_bytes, rows[2], act[3], qkv, vt, attn_o, attn_scratch, mean, rstd, stats_ws, stats_ws_bytes, total;
+  size_t tickets, conv_tickets, conv_ticket_bytes, rows[2], act[3], qkv, attn_o, attn_scratch, mean, rstd, stats_ws, stats_ws_bytes, total;
 };
 
 static WsLayout ws_layout(const wmdec_decoder* d, int batch) {
@@ -432,10 +429,9 @@ static WsLayout ws_layout(const wmdec_decoder* d, int batch) {
   L.conv_tickets = o; o += L.conv_ticket_bytes;
   for (int i = 0; i < 2; ++i) { L.rows[i] = o; o += align_up(max_rows * d->cfg.max_batch * d->cfg.groups * 3 * sizeof(float), 256); }
   for (int i = 0; i < 3; ++i) { L.act[i] = o; o += act; }
-  L.qkv = o; o += align_up((size_t)batch * d->attn_t * 3 * d->attn_c * es, 256);
-  L.vt = o; o += align_up((size_t)batch * flash_attention_vt_elems(d->attn_t, d->attn_c) * es, 256);
+  L.qkv = o; o += align_up(attention_fragment_bytes(batch, d->attn_t), 256);
   L.attn_o = o; o += align_up((size_t)batch * d->attn_t * d->attn_c * es, 256);
-  L.attn_scratch = o; o += align_up(flash_attention_scratch_bytes(batch, d->attn_t, d->attn_c), 256);
+  L.attn_scratch = o; o += align_up(flash_attention_scratch_bytes(batch, d->attn_t), 256);
   L.mean = o; o += align_up((size_t)batch * d->cfg.groups * sizeof(float), 256);
   L.rstd = o; o += align_up((size_t)batch * d->cfg.groups * sizeof(float), 256);
   L.stats_ws_bytes = gn_stats_moments_bytes(batch, d->cfg.groups);
@@ -685,40 +681,31 @@ int wmdec_nhwc_to_nchw(const void* src, int sd, void* dst, int dd, int n, int c,
 }
 
 // ---- attention
-static void attn_ws_layout(int n, int t, int c, size_t es, size_t* qkv, size_t* vt, size_t* o, size_t* scratch, size_t* total) {
+static void attn_ws_layout(int n, int t, int c, size_t es, size_t* qkv, size_t* o, size_t* scratch, size_t* total) {
   size_t off = 0;
-  *qkv = off; off += align_up((size_t)n * t * 3 * c * es, 256);
-  *vt = off; off += align_up((size_t)n * flash_attention_vt_elems(t, c) * es, 256);
+  *qkv = off; off += align_up(attention_fragment_bytes(n, t), 256);
   *o = off; off += align_up((size_t)n * t * c * es, 256);
-  *scratch = off; off += align_up(flash_attention_scratch_bytes(n, t, c), 256);
+  *scratch = off; off += align_up(flash_attention_scratch_bytes(n, t), 256);
   *total = off;
 }
 
 size_t wmdec_attention_workspace_bytes(int n, int h, int w, int c) {
   if (n <= 0 || h <= 0 || w <= 0 || c <= 0) return 0;
-  size_t a, b, d, e, total;
-  attn_ws_layout(n, h * w, c, 2, &a, &b, &d, &e, &total);
+  size_t a, b, d, total;
+  attn_ws_layout(n, h * w, c, 2, &a, &b, &d, &total);
   return total;
 }
 
 static int attention_impl(const void* x, int act_dtype, const float* mean, const float* rstd, const float* gamma,
                           const float* beta, int groups, const void* wqkv, const float* bqkv, const void* wo,
-                          const float* bo, void* y, int n, int h, int w, int c, void* qkv, void* vt, void* ob,
-                          void* scratch, hipStream_t s) {
-  const int t = h * w, tpad = (t + 31) / 32 * 32;
-  const size_t es = 2;
+                          const float* bo, void* y, int n, int h, int w, int c, void* qkv, void* ob, void* scratch, hipStream_t s) {
   ConvArgs a;
   a.x = x; a.x_dtype = act_dtype; a.mean = mean; a.rstd = rstd; a.gamma = gamma; a.beta = beta; a.groups = groups; a.silu = 0;
-  a.wt = wqkv; a.op_dtype = act_dtype; a.bias = bqkv; a.y = qkv; a.y_dtype = act_dtype;
+  a.wt = wqkv; a.op_dtype = act_dtype; a.bias = bqkv; a.y_dtype = act_dtype;
   a.n = n; a.h = h; a.w = w; a.cin = c; a.cout = 3 * c; a.ksize = 1;
-  int rc = launch_conv(a, s);
+  int rc = launch_attention_qkv(a, qkv, s);
   if (rc != WMDEC_OK) return rc;
-  // V^T[n][d][key]: transpose the v columns of the qkv buffer
-  rc = launch_transpose((const char*)qkv + (size_t)2 * c * es, act_dtype, vt, act_dtype, n, t, c, (size_t)3 * c,
-                        (size_t)t * 3 * c, 0 /* blocks of 32 keys */, flash_attention_vt_elems(t, c), s);
-  if (rc != WMDEC_OK) return rc;
-  rc = launch_flash_attention(qkv, (const char*)qkv + (size_t)c * es, (size_t)3 * c, (size_t)t * 3 * c, vt, tpad, ob,
-                              scratch, act_dtype, n, t, c, 1.0f / sqrtf((float)c), s);
+  rc = launch_flash_attention(qkv, ob, scratch, act_dtype, n, h * w, 1.0f / sqrtf((float)c), s);
   if (rc != WMDEC_OK) return rc;
   ConvArgs p;
   p.x = ob; p.x_dtype = act_dtype; p.wt = wo; p.op_dtype = act_dtype; p.bias = bo; p.res = x; p.res_dtype = act_dtype;
@@ -739,13 +726,13 @@ int wmdec_attention(const void* x, int act_dtype, const float* mean, const float
   WMDEC_REQUIRE(x != y, WMDEC_ERR_INVALID_ARG, "attention: x and y must not overlap");
   WMDEC_REQUIRE(aligned16(x) && aligned16(y) && aligned16(workspace) && aligned16(wqkv_packed) && aligned16(wo_packed),
                 WMDEC_ERR_INVALID_ARG, "attention: pointers must be 16-byte aligned");
-  size_t qo, vo, oo, so, total;
-  attn_ws_layout(n, h * w, c, 2, &qo, &vo, &oo, &so, &total);
+  size_t qo, oo, so, total;
+  attn_ws_layout(n, h * w, c, 2, &qo, &oo, &so, &total);
   WMDEC_REQUIRE(workspace && workspace_bytes >= total, WMDEC_ERR_WORKSPACE, "attention: workspace needs %zu bytes, got %zu",
                 total, workspace_bytes);
   char* ws = (char*)workspace;
   return attention_impl(x, act_dtype, mean, rstd, gamma, beta, groups, wqkv_packed, bqkv, wo_packed, bo, y, n, h, w, c,
-                        ws + qo, ws + vo, ws + oo, ws + so, (hipStream_t)stream);
+                        ws + qo, ws + oo, ws + so, (hipStream_t)stream);
 }
 
 // ---- horizontally fused AdaLN projections
@@ -922,7 +909,7 @@ static int launch_step(wmdec_decoder* dec, const WsLayout& L, const Step& st, co
         a.res = buf(st.res);
         if (st.sc_src != BUF_NONE) { a.x2 = buf(st.sc_src); a.cin2 = st.sc_cin; a.w2 = pk + st.sc_w_off; a.bias2 = (const float*)(pk + st.sc_b_off); }
         if (st.dst == BUF_OUT) { a.y = out; a.y_dtype = WMDEC_F32; a.y_nchw = 1; }
-        else if (st.to_attn == 1) { a.y = ws + L.qkv; a.y_dtype = c.act_dtype; }
+        else if (st.to_attn == 1) { a.y_dtype = c.act_dtype; }   // (in fragment order, see kernels_attn.hip)
         else { a.y = buf(st.dst); a.y_dtype = c.act_dtype; }
         a.n = batch; a.h = st.h; a.w = st.w; a.cin = st.cin; a.cout = st.cout; a.ksize = st.ksize; a.upsample = st.upsample;
         if (st.emit_stats) {
@@ -931,25 +918,13 @@ static int launch_step(wmdec_decoder* dec, const WsLayout& L, const Step& st, co
           if ((*emitted_slots) > 0) a.stats_ws = st.emit_direct ? ws + L.rows[st.emit_rows] : ws + L.stats_ws;
           if (st.emit_rows >= 0 && !st.emit_direct) { a.rows_out = ws + L.rows[st.emit_rows]; a.tickets = ws + L.conv_tickets; }
         }
-        rc = launch_conv(a, s);
-        break;
-      }
-      case Step::QKV_TRANSPOSE_V: {
-        const size_t es = dtype_size(c.act_dtype);
-        const int t = st.h * st.w;
-        rc = launch_transpose(ws + L.qkv + (size_t)2 * st.cin * es, c.act_dtype, ws + L.vt, c.act_dtype, batch, t, st.cin,
-                              (size_t)3 * st.cin, (size_t)t * 3 * st.cin, 0 /* blocks of 32 keys */, flash_attention_vt_elems(t, st.cin), s);
+        rc = st.to_attn == 1 ? launch_attention_qkv(a, ws + L.qkv, s) : launch_conv(a, s);
         break;
       }
       case Step::NONE: break;
-      case Step::FLASH: {
-        const size_t es = dtype_size(c.act_dtype);
-        const int t = st.h * st.w;
-        rc = launch_flash_attention(ws + L.qkv, ws + L.qkv + (size_t)st.cin * es, (size_t)3 * st.cin, (size_t)t * 3 * st.cin,
-                                    ws + L.vt, dec->attn_tpad, ws + L.attn_o, ws + L.attn_scratch, c.act_dtype, batch, t, st.cin,
-                                    1.0f / sqrtf((float)st.cin), s);
+      case Step::FLASH:
+        rc = launch_flash_attention(ws + L.qkv, ws + L.attn_o, ws + L.attn_scratch, c.act_dtype, batch, st.h * st.w, 1.0f / sqrtf((float)st.cin), s);
         break;
-      }
     }
     return rc;
   }
@@ -1062,13 +1037,12 @@ int decoder_step_info(const wmdec_decoder* dec, int index, const char** kernel, 
   if (kernel) {
     switch (st.kind) {
       case Step::STATS: *kernel = st.from_producer ? "gn_finalize" : "gn_stats_vec"; break;
-      case Step::QKV_TRANSPOSE_V: *kernel = "transpose_kernel"; break;
       case Step::FLASH: *kernel = "flash_attn_kernel"; break;
       case Step::NONE: *kernel = ""; break;
       case Step::CONV: {
         ConvArgs a = step_shape_args(*dec, st, 1);   // only the fields the kernel choice looks at
         a.groups_norm = st.norm; a.silu = st.silu;
-        *kernel = conv_kernel_label(a);
+        *kernel = st.to_attn == 1 ? attention_qkv_label(a.op_dtype) : conv_kernel_label(a);
         break;
       }
     }

@@ -178,14 +178,13 @@ int adaln_max_d_cond(int w_dtype);  // longest conditioning vector (a lane keeps
 int launch_adaln_projection(const void* c, int c_dtype, const void* w, int w_dtype, const float* bias, float* out, int batch,
                             int d_cond, int rows, int apply_silu, hipStream_t s);
 
-// kernels_attn.hip
-// q,k: [n][t][ld] rows of d elements (16-bit type), vt: [n][t_pad / 32][d][40] (V transposed in blocks of 32 keys, rows padded to 40 elements, keys past t zero), o: [n][t][d]
-// scratch: flash_attention_scratch_bytes(n, t, d) bytes (partial outputs of the key splits), may be null if 0
-size_t flash_attention_scratch_bytes(int n, int t, int d);
-// elements of V^T per sample in the blocked, row-padded layout the kernel reads (see launch_transpose with dst_ld = 0)
-size_t flash_attention_vt_elems(int t, int d);
-int launch_flash_attention(const void* q, const void* k, size_t qk_ld, size_t qk_batch_stride,
-                           const void* vt, int t_pad, void* o, void* scratch, int dtype, int n, int t, int d,
-                           float scale, hipStream_t s);
+// kernels_attn.hip: attention over the t tokens of a sample, head dimension 512 (q, k, v in the fragment order described there)
+size_t attention_fragment_bytes(int n, int t);
+size_t flash_attention_scratch_bytes(int n, int t);   // partial outputs of the key ranges
+const char* attention_qkv_label(int dtype);
+// frag = [q|k|v] of act(x) as a describes it: a 1x1 convolution from 512 to 3 * 512 channels over a.h * a.w tokens
+int launch_attention_qkv(const ConvArgs& a, void* frag, hipStream_t s);
+// o: [n][t][512]
+int launch_flash_attention(const void* frag, void* o, void* scratch, int dtype, int n, int t, float scale, hipStream_t s);
 
 }  // namespace wmdec

@@ -1,5 +1,5 @@
 // Small data-movement kernels: nearest-2x upsample, weight packing, strided
-// transpose with type conversion (NCHW <-> NHWC, V -> V^T), fp32 copy.
+// transpose with type conversion (NCHW <-> NHWC), fp32 copy.
 #include "common.hpp"
 #include "pack_layout.hpp"
 
@@ -61,11 +61,8 @@ __global__ __launch_bounds__(256) void pack_conv_kernel(const S* __restrict__ sr
   dst[i] = from_float<D>(to_float(src[((size_t)co * cin + ci) * taps + tap]));
 }
 
-// dst[b][i][j] = src[b][j][i], 32x32 tiles through LDS.  BLOCKED (dst_ld = 0): the destination is cut into blocks of 32
-// source rows, dst[b][j / 32][i][40] with j % 32 in the first 32 of a row's 40 elements and zeros for source rows past
-// the end: the image of the attention kernel's V^T tile in LDS (32 keys, rows padded to 40 elements), which that
-// kernel copies as one contiguous run.
-template <typename S, typename D, bool BLOCKED = false>
+// dst[b][i][j] = src[b][j][i], 32x32 tiles through LDS.
+template <typename S, typename D>
 __global__ __launch_bounds__(256) void transpose_kernel(const S* __restrict__ src, D* __restrict__ dst, int rows, int cols,
                                                         size_t src_ld, size_t src_bs, size_t dst_ld, size_t dst_bs) {
   __shared__ float tile[32][33];
@@ -79,11 +76,7 @@ __global__ __launch_bounds__(256) void transpose_kernel(const S* __restrict__ sr
   __syncthreads();
   for (int k = ty; k < 32; k += 8) {
     const int c = c0 + k, r = r0 + tx;
-    if (BLOCKED) {
-      if (c < cols) dst[(size_t)b * dst_bs + ((size_t)blockIdx.y * cols + c) * 40 + tx] = from_float<D>(r < rows ? tile[tx][k] : 0.f);
-    } else if (r < rows && c < cols) {
-      dst[(size_t)b * dst_bs + (size_t)c * dst_ld + r] = from_float<D>(tile[tx][k]);
-    }
+    if (r < rows && c < cols) dst[(size_t)b * dst_bs + (size_t)c * dst_ld + r] = from_float<D>(tile[tx][k]);
   }
 }
 
@@ -130,8 +123,7 @@ int pack_t(const void* src, void* dst, int cout, int cin, int k, int row_off, in
 template <typename S, typename D>
 int transpose_t(const void* src, void* dst, int batch, int rows, int cols, size_t sld, size_t sbs, size_t dld, size_t dbs, hipStream_t s) {
   dim3 grid((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32), (unsigned)batch);
-  if (dld == 0) hipLaunchKernelGGL((transpose_kernel<S, D, true>), grid, dim3(256), 0, s, (const S*)src, (D*)dst, rows, cols, sld, sbs, dld, dbs);
-  else hipLaunchKernelGGL((transpose_kernel<S, D>), grid, dim3(256), 0, s, (const S*)src, (D*)dst, rows, cols, sld, sbs, dld, dbs);
+  hipLaunchKernelGGL((transpose_kernel<S, D>), grid, dim3(256), 0, s, (const S*)src, (D*)dst, rows, cols, sld, sbs, dld, dbs);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
 }

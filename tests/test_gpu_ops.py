@@ -485,6 +485,24 @@ def test_attention_bf16_sharp_softmax_with_the_same_storage_points():
     assert ref.rel_err(got - x, want - x) <= branch_tolerance(dtype, want, x)
 
 
+# 32-token tiles, 64-token projection workgroups and 128-query blocks: one token short of, at and past their edges
+@pytest.mark.parametrize("dtype,n,h,w", [("bf16", 1, 1, 31), ("f16", 2, 4, 8), ("f16", 1, 3, 11), ("bf16", 1, 8, 8), ("f16", 2, 5, 13),
+                                         ("bf16", 1, 1, 127), ("f16", 1, 8, 16), ("bf16", 2, 3, 43), ("f16", 1, 7, 37)])
+def test_attention_tile_edges(dtype, n, h, w):
+    got, want, x = run_attention(dtype, n, h, w, 23)
+    assert ref.rel_err(got, want) <= G.TOL[dtype]
+    assert ref.rel_err(got - x, want - x) <= branch_tolerance(dtype, want, x)
+
+
+def test_attention_reference_moves_inside_a_key_range():
+    """Logits of standard deviation 9 (13 in powers of two) over eight ranges of 256 keys: the maximum of a range lies about
+    0.8 standard deviations above that of its first 32 keys, so that most queries cross the slack of 2^8 behind the
+    first block and the output accumulators are rescaled."""
+    got, want, x = run_attention("f16", 1, 32, 64, 24, sharpen=3.0)
+    assert ref.rel_err(got, want) <= G.TOL["f16"]
+    assert ref.rel_err(got - x, want - x) <= branch_tolerance("f16", want, x)
+
+
 # ------------------------------------------------------------------ horizontally fused AdaLN projections (DiT)
 # d_model = d_cond = 1920 stands for the paper's 30-head transformer (64 per head; the paper gives no widths)
 @pytest.mark.parametrize("cdtype,wdtype,batch,d_cond,d_model,silu", [
