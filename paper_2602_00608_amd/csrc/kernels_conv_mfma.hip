@@ -26,135 +26,199 @@
 namespace wmdec {
 namespace {
 
-// Epilogue of one wavefront: its MI x NI accumulator tiles (32 pixels x 32 channels each, a lane
-// holding one channel column) go through a wavefront-private LDS patch, one 32-pixel M tile at a
-// time, and come back as rows of 8 consecutive channels per lane, so that bias, residual and the
-// output move as 16-byte vectors and every pixel's channel run is written contiguously.
-// lds: 32 x (NI*32 + 4) floats owned by this wavefront.  LDS operations of one wavefront execute
-// in order, so the patch needs no barrier between its write and read phases.
-// floats of the wavefront-private epilogue patch: 32 padded rows, and at least the 64 x 8 four-float entries
-// that the statistics reduction parks there
-constexpr int patch_floats(int ni, bool pairs = false) { return pairs ? 2 * 32 * (ni * 32 + 4) : 32 * (ni * 32 + 4) > 2048 ? 32 * (ni * 32 + 4) : 2048; }
+// MODE: kRows4 and kQuarters are forms between which and another kernel the batch decides, while a sample's bits must not
+// depend on that choice; so both keep the activation's roundings apart (PIN).
+//   kRows4     one of a pair of tiles, 4x16 and 8x16 (see four_row_slots): moments per four rows.
+//   kQuarters  the batched form of kernels_conv_ksplit.hip, with its order of summation: of every 64 input channels the
+//              k-th 16 belong to partial sum k, each of them is summed on its own, 16 channels and their nine taps at a
+//              time, and the four are added in order.  Here one after the other into a second set of accumulators, on M tiles of 4 x 8
+//              pixels, the blocks of that kernel's moments.
+enum ConvMode { kPlain = 0, kRows4 = 1, kQuarters = 2 };
 
-// PAIRS (NI = 1): two patches, and moments of the two M tiles of a pair from the values written back to them: a lane walks
-// one channel of either tile's 32 pixels.  One triple for both tiles (four rows of 16 pixels), or one for each (4 x 8 pixels).
-// A second emission of the other form (per-lane sums parked in LDS) cost 1.3 us of a launch of one round.
-template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, bool RES, bool PAIRS>
+// Sums over lanes in the vector ALU.  row_rotate: the value N lanes further round the row of 16; quad_xor: of lane ^ N (1, 2);
+// swap_sum: v of this lane plus that of lane ^ W (16, 32; the results of the swap are made opaque, as this compiler takes both
+// for the first one where the operands are the same).
+template <int N> __device__ __forceinline__ float row_rotate(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, true));
+}
+template <int N> __device__ __forceinline__ float quad_xor(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), N == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true));
+}
+template <int W> __device__ __forceinline__ float swap_sum(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  u32x2 r;
+  if constexpr (W == 16) r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  else r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  unsigned a = r.x, b = r.y;
+  asm volatile("" : "+v"(a), "+v"(b));
+  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
+
+// Moments of a wavefront's stored values in the making: per channel of the lane's octet sums shifted by the lane's first value,
+// over n pixels.
+struct LaneMoments { float n, shift[8], s[8], q[8]; };
+
+// ... merged per group and written.  A lane merges its channels of a group (PARTS groups per octet, or its part of a larger one),
+// then the lanes that hold the same octet, and those of the group's other octets, are summed in the vector ALU: the mean first,
+// then the squares about it.  (Through LDS, with a lane per channel that walked the others' sums and re-centred them one by
+// one, this was 13 of the 122 us of 128 -> 128 channels at 480x720, and 1.5 of 36 at 60x90.)  OCTETS: octets of channels of the wavefront.
+template <int OCTETS, int PARTS>
+__device__ __forceinline__ void emit_moments(const LaneMoments& st, int lane, int co_w, Moments* dst, int cpg, int stats_stride, bool handed_over) {
+  constexpr int PC = 8 / PARTS;
+  auto lanes = [&](float v) {
+    if constexpr (OCTETS <= 4) v += row_rotate<4>(v);
+    v += row_rotate<8>(v);
+    v = swap_sum<32>(swap_sum<16>(v));
+    if (cpg > 8) v += quad_xor<1>(v);
+    if (cpg > 16) v += quad_xor<2>(v);
+    return v;
+  };
+  const float inv = st.n > 0.f ? __builtin_amdgcn_rcpf(st.n) : 0.f;   // 1 ulp of a difference to the shift
+  const float n = lanes(st.n), ninv = n > 0.f ? __builtin_amdgcn_rcpf(n) : 0.f;
+#pragma unroll
+  for (int g = 0; g < PARTS; ++g) {
+    float mean[PC], m = 0.f, q = 0.f;
+#pragma unroll
+    for (int e = 0; e < PC; ++e) {
+      const int c = g * PC + e;
+      const float ds = st.s[c] * inv, m2 = st.q[c] - st.s[c] * ds;
+      mean[e] = st.shift[c] + ds;
+      m += mean[e];
+      q += m2 < 0.f ? 0.f : m2;     // (NaN stays NaN)
+    }
+    m = st.n > 0.f ? m * (1.f / PC) : 0.f;     // the shift of a lane without pixels has no meaning
+    float dev = 0.f;
+#pragma unroll
+    for (int e = 0; e < PC; ++e) { const float d = mean[e] - m; dev = fmaf(d, d, dev); }
+    const float mid = lanes(st.n * m) * ninv;
+    const float d = m - mid, nd = st.n * d;
+    const float rest = lanes(nd) * ninv;       // what the roundings of mid left
+    q = lanes(st.n > 0.f ? fmaf(st.n, dev, fmaf(nd * PC, d, q)) : 0.f) - n * PC * rest * rest;
+    const Moments out{n * PC, mid + rest, q < 0.f ? 0.f : q};
+    if (lane < OCTETS && ((lane * 8) & (cpg - 1)) == 0) {
+      Moments* at = dst + (size_t)((co_w + lane * 8 + g * PC) / cpg) * stats_stride;
+      if (handed_over) store_device(at, out);   // another workgroup of this launch may merge them, see the row hand-over in the kernel
+      else *at = out;
+    }
+  }
+}
+
+// floats of the wavefront-private epilogue patches: two of 32 padded rows
+constexpr int patch_floats(int ni) { return 2 * 32 * (ni * 32 + 4); }
+
+struct EpilogueParams {
+  const float* bias; const float* bias2;   // added here where the accumulators did not start with them (BIAS)
+  __amdgpu_buffer_rsrc_t res, y;           // the sample's residual and output, with its size: accesses outside are dropped
+  void* planar;                            // the sample's output where it is planar
+  int h, w, cout;
+  bool nchw;
+  Moments* stats; int cpg, stats_stride, pair_stride;
+  bool handed_over;
+};
+
+// Epilogue of one wavefront: its MI x NI accumulator tiles (32 pixels x 32 channels each, a lane holding one channel column)
+// go through wavefront-private LDS patches, one 32-pixel M tile at a time and the next one's values on their way to the other
+// patch, and come back as rows of 8 consecutive channels per lane, so that residual and output move as 16-byte vectors and every
+// pixel's channel run is written contiguously.  LDS operations of one wavefront execute in order: no barrier.
+// Residual and output are accessed through buffers with a lane offset that is the same for all vectors, or past the end for
+// pixels outside the image, and the vector's position in a scalar register: no address arithmetic, no masks.
+// Moments: one triple per group for all M tiles, or (kRows4) for every two of them, four rows of 16 pixels.  kQuarters (NI = 1):
+// one for each M tile of 4 x 8 pixels, from the values written back to the patches of a pair: a lane walks one channel
+// of either tile, as the kernel that it reproduces does.
+template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, bool RES, int MODE, bool BIAS>
 __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], float* wave_lds, int lane, int mt0, int ty0,
-                                               int tx0, int co_w, const float* bias, const float* bias2, const T* rin, TO* yout, int h,
-                                               int w_out, int cout, bool nchw, Moments* stats, int cpg, int stats_stride, int pair_stride) {
-  float* lds = wave_lds;
-  constexpr int RW = NI * 32 + 4;       // padded row of the patch, floats
-  if (nchw) {
+                                               int tx0, int co_w, const EpilogueParams& p) {
+  constexpr int RW = NI * 32 + 4;       // padded row of a patch, floats
+  constexpr bool PAIRS = MODE == kQuarters;
+  constexpr int EMIT = MODE == kRows4 ? 2 : MI;   // M tiles of a triple
+  const int lm = lane & 31, lk = lane >> 5;
+  auto put = [&](float* patch, int mi) {
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) patch[(8 * (r / 4) + 4 * lk + (r % 4)) * RW + ni * 32 + lm] = acc[mi][ni][r];
+  };
+  if (p.nchw) {
     // planar output with few channels (the frame): a lane owns one pixel of the M tile and walks the
     // channels, so that 32 lanes write 32 consecutive pixels of one plane
-    const int lm = lane & 31, lk = lane >> 5;
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
       const int mt = mt0 + mi;
       const int oy = ty0 + (mt / MT_PER_ROW) * MTH + lm / MTW, ox = tx0 + (mt % MT_PER_ROW) * MTW + lm % MTW;
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) lds[(8 * (r / 4) + 4 * lk + (r % 4)) * RW + ni * 32 + lm] = acc[mi][ni][r];
-      if (oy < h && ox < w_out) {
-        for (int c = lk; c < NI * 32 && co_w + c < cout; c += 2) {
-          const float v = lds[lm * RW + c] + (bias ? bias[co_w + c] : 0.f) + (bias2 ? bias2[co_w + c] : 0.f);
-          yout[((size_t)(co_w + c) * h + oy) * w_out + ox] = from_float<TO>(v);
-        }
+      put(wave_lds, mi);
+      if (oy < p.h && ox < p.w) {
+        for (int c = lk; c < NI * 32 && co_w + c < p.cout; c += 2)
+          reinterpret_cast<TO*>(p.planar)[((size_t)(co_w + c) * p.h + oy) * p.w + ox] = from_float<TO>(wave_lds[lm * RW + c]);
       }
     }
     return;
   }
   constexpr int VPL = 2 * NI;           // 8-channel vectors per lane per M tile (32 pixels x NI*4 vectors / 64 lanes)
-  const int lm = lane & 31, lk = lane >> 5;
+  constexpr int STEP = 64 / (NI * 4);   // pixels between two of them
+  static_assert(STEP % MTW == 0 || MTW % STEP == 0, "a vector's row and column are the lane's plus a constant");
   const int cvec = lane % (NI * 4);     // which 8-channel vector of the row this lane reads back
-  const int prow = lane / (NI * 4);     // first pixel row it reads; the others are prow + j * (64 / (NI*4))
+  const int prow = lane / (NI * 4);     // first pixel it reads; the others are prow + j * STEP
+  const int lane_row = prow / MTW, lane_col = prow % MTW;
   float bv[8];
+  if constexpr (BIAS) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) bv[e] = (bias ? bias[co_w + cvec * 8 + e] : 0.f) + (bias2 ? bias2[co_w + cvec * 8 + e] : 0.f);
-  // 32-bit element offset of this lane's vector in M tile mi, row j (or -1 outside the image)
-  auto vec_off = [&](int mi, int j) -> int {
-    const int mt = mt0 + mi;
-    const int pi = prow + j * (64 / (NI * 4));
-    const int oy = ty0 + (mt / MT_PER_ROW) * MTH + pi / MTW;
-    const int ox = tx0 + (mt % MT_PER_ROW) * MTW + pi % MTW;
-    return (oy < h && ox < w_out) ? (oy * w_out + ox) * cout + co_w + cvec * 8 : -1;   // < 2^30 elements (checked on the host)
-  };
-  // residual vectors are fetched two M tiles ahead (unconditional loads, clamped to element 0 outside the
-  // image) so that their latency hides behind the LDS round trips of the tiles before
-  constexpr int RD = 2;
+    for (int e = 0; e < 8; ++e) bv[e] = (p.bias ? p.bias[co_w + cvec * 8 + e] : 0.f) + (p.bias2 ? p.bias2[co_w + cvec * 8 + e] : 0.f);
+  }
+  // elements (< 2^29, checked on the host): the lane's part, and that of vector j of M tile mi
+  constexpr unsigned OUTSIDE = 1u << 29;
+  const unsigned lane_off = (unsigned)((lane_row * p.w + lane_col) * p.cout + cvec * 8);
+  auto row_of = [&](int mi, int j) { return ty0 + (mt0 + mi) / MT_PER_ROW * MTH + j * STEP / MTW; };
+  auto col_of = [&](int mi, int j) { return tx0 + (mt0 + mi) % MT_PER_ROW * MTW + j * STEP % MTW; };
+  auto inside = [&](int mi, int j) -> bool { return row_of(mi, j) + lane_row < p.h && col_of(mi, j) + lane_col < p.w; };
+  auto base_of = [&](int mi, int j) -> int { return (row_of(mi, j) * p.w + col_of(mi, j)) * p.cout + co_w; };
+  // residual vectors are requested ahead so that their latency hides behind the LDS round trips of the tiles before
+  constexpr int RD = NI == 1 && MI <= 4 ? MI : 2;
   u32x4 rv[RD][VPL];
+  auto request = [&](int mi) {
+#pragma unroll
+    for (int j = 0; j < VPL; ++j)
+      rv[mi % RD][j] = __builtin_amdgcn_raw_buffer_load_b128(p.res, (int)((inside(mi, j) ? lane_off : OUTSIDE) * sizeof(T)), base_of(mi, j) * (int)sizeof(T), 0);
+  };
   if constexpr (RES) {
 #pragma unroll
-    for (int mi = 0; mi < RD && mi < MI; ++mi)
-#pragma unroll
-      for (int j = 0; j < VPL; ++j) rv[mi][j] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(rin) + (unsigned)(max(vec_off(mi, j), 0) * (int)sizeof(T)));
+    for (int mi = 0; mi < RD && mi < MI; ++mi) request(mi);
   }
-  // moments of the values this lane stores, per channel of its octet (shifted sums: the shift is the first value)
-  float st_shift[8], st_s[8], st_q[8], st_n = 0.f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) { st_shift[e] = 0.f; st_s[e] = 0.f; st_q[e] = 0.f; }
-  auto emit_moments = [&](Moments* dst) {
-    // lane -> wavefront: every lane parks its 8 channels' (count, shift, sum, sum of squares) in the LDS patch;
-    // lane L then owns channel L of the wavefront's run, re-centres the entries of the lanes that held that
-    // channel (they differ in the pixel rows they read back) on one shift and adds them in a fixed order.
-    constexpr int CV = NI * 4;                 // octets per row of the patch
-    constexpr int ROWS = 64 / CV;              // lanes per octet
-    f32x4* park = reinterpret_cast<f32x4*>(lds);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) park[lane * 8 + e] = f32x4{st_n, st_shift[e], st_s[e], st_q[e]};
-    Moments m{0.f, 0.f, 0.f};
-    if (lane < CV * 8) {
-      float n0 = 0.f, a0 = 0.f, s0 = 0.f, q0 = 0.f;
-#pragma unroll
-      for (int r = 0; r < ROWS; ++r) {
-        const f32x4 en = park[r * (CV * 8) + lane];     // (row r, octet lane / 8, channel lane % 8)
-        if (en[0] > 0.f) {
-          if (n0 == 0.f) a0 = en[1];
-          const float d = en[1] - a0;
-          s0 += en[2] + en[0] * d;
-          q0 += en[3] + 2.f * d * en[2] + en[0] * d * d;
-          n0 += en[0];
-        }
-      }
-      if (n0 > 0.f) { const float ds = s0 / n0; m.n = n0; m.mean = a0 + ds; m.m2 = fmaxf(q0 - s0 * ds, 0.f); }
-    }
-    // channels of one group are cpg consecutive lanes
-    m = merge_to_first(m, lane, cpg);
-    // (device-scope stores: another workgroup of this launch may merge them, see the row hand-over in the kernel)
-    if (lane < CV * 8 && (lane & (cpg - 1)) == 0) store_device(dst + (size_t)((co_w + lane) / cpg) * stats_stride, m);
-  };
+  LaneMoments st = {};
+  put(wave_lds, 0);
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
-    if constexpr (PAIRS) lds = wave_lds + (mi & 1) * 32 * RW;
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) lds[(8 * (r / 4) + 4 * lk + (r % 4)) * RW + ni * 32 + lm] = acc[mi][ni][r];
+    float* lds = wave_lds + (mi & 1) * 32 * RW;
+    const bool ahead = mi + 1 < MI && !(PAIRS && mi % 2 == 1);   // (a pair's patches are read once more at its end)
+    if (ahead) put(wave_lds + ((mi + 1) & 1) * 32 * RW, mi + 1);
 #pragma unroll
     for (int j = 0; j < VPL; ++j) {
-      const int pi = prow + j * (64 / (NI * 4));
-      const int off = vec_off(mi, j);
+      const int pi = prow + j * STEP;
+      const bool ok = inside(mi, j);
       const f32x4 lo = *reinterpret_cast<const f32x4*>(lds + pi * RW + cvec * 8);
       const f32x4 hi = *reinterpret_cast<const f32x4*>(lds + pi * RW + cvec * 8 + 4);
-      float v[8] = {lo[0] + bv[0], lo[1] + bv[1], lo[2] + bv[2], lo[3] + bv[3],
-                    hi[0] + bv[4], hi[1] + bv[5], hi[2] + bv[6], hi[3] + bv[7]};
+      float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      if constexpr (BIAS) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += bv[e];
+      }
       if constexpr (RES) {
         float rf[8];
         unpack8<T>(rv[mi % RD][j], rf);
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] += rf[e];
-        if (mi + RD < MI)
-          rv[mi % RD][j] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(rin) + (unsigned)(max(vec_off(mi + RD, j), 0) * (int)sizeof(T)));
       }
       // the stored vector; the moments are those of the values as stored (after the rounding to the storage
       // type), which is what the consumer of the tensor normalises
       u32x4 packed;
-      if constexpr (sizeof(TO) == 2) {
-        packed = u32x4{pack2<T>(v[0], v[1]), pack2<T>(v[2], v[3]), pack2<T>(v[4], v[5]), pack2<T>(v[6], v[7])};
+      if constexpr (sizeof(TO) == 2) packed = u32x4{pack2<T>(v[0], v[1]), pack2<T>(v[2], v[3]), pack2<T>(v[4], v[5]), pack2<T>(v[6], v[7])};
+      const int at = (int)((ok ? lane_off : OUTSIDE) * sizeof(TO)), base = base_of(mi, j) * (int)sizeof(TO);
+      if constexpr (sizeof(TO) == 4) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), p.y, at, base, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[4], v[5], v[6], v[7]}), p.y, at + 16, base, 0);
+      } else {
+        __builtin_amdgcn_raw_buffer_store_b128(packed, p.y, at, base, 0);
       }
-      if (stats && off >= 0) {
+      if (p.stats) {
         float sv[8];
         if constexpr (sizeof(TO) == 2) {
           unpack8<T>(packed, sv);
@@ -163,43 +227,47 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
           for (int e = 0; e < 8; ++e) sv[e] = v[e];
         }
         if constexpr (PAIRS) {
-          *reinterpret_cast<f32x4*>(lds + pi * RW + cvec * 8) = f32x4{sv[0], sv[1], sv[2], sv[3]};
-          *reinterpret_cast<f32x4*>(lds + pi * RW + cvec * 8 + 4) = f32x4{sv[4], sv[5], sv[6], sv[7]};
-        } else {
-          if (st_n == 0.f) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) st_shift[e] = sv[e];
+          if (ok) {
+            *reinterpret_cast<f32x4*>(lds + pi * RW + cvec * 8) = f32x4{sv[0], sv[1], sv[2], sv[3]};
+            *reinterpret_cast<f32x4*>(lds + pi * RW + cvec * 8 + 4) = f32x4{sv[4], sv[5], sv[6], sv[7]};
           }
-#pragma unroll
-          for (int e = 0; e < 8; ++e) { const float dv = sv[e] - st_shift[e]; st_s[e] += dv; st_q[e] = fmaf(dv, dv, st_q[e]); }
-          st_n += 1.f;
-        }
-      }
-      if (off >= 0) {
-        TO* dst = reinterpret_cast<TO*>(reinterpret_cast<char*>(yout) + (unsigned)(off * (int)sizeof(TO)));
-        if constexpr (sizeof(TO) == 4) {
-          reinterpret_cast<f32x4*>(dst)[0] = f32x4{v[0], v[1], v[2], v[3]};
-          reinterpret_cast<f32x4*>(dst)[1] = f32x4{v[4], v[5], v[6], v[7]};
         } else {
-          *reinterpret_cast<u32x4*>(dst) = packed;
+          if (mi % EMIT == 0 && j == 0) {   // (outside the image only if all vectors of the lane are)
+            st.n = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { st.shift[e] = sv[e]; st.s[e] = 0.f; st.q[e] = 0.f; }
+          }
+          if (ok) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { const float dv = sv[e] - st.shift[e]; st.s[e] += dv; st.q[e] = fmaf(dv, dv, st.q[e]); }
+            st.n += 1.f;
+          }
         }
       }
+    }
+    if constexpr (RES) {
+      if (mi + RD < MI) request(mi + RD);
     }
     if constexpr (PAIRS) {
-      static_assert(NI == 1 && MI % 2 == 0 && ((MTW == 16 && MTH == 2) || (MTW == 8 && MTH == 4 && MT_PER_ROW == 2)), "a pair is four rows of 16 pixels");
-      if (mi % 2 == 1 && stats) {   // lanes 0-31: a channel of the pair's first tile, lanes 32-63: of the second
+      static_assert(NI == 1 && MI % 2 == 0 && MTW == 8 && MTH == 4 && MT_PER_ROW == 2, "a pair is four rows of 16 pixels");
+      if (mi % 2 == 1 && p.stats) {   // lanes 0-31: a channel of the pair's first tile, lanes 32-63: of the second
+        Moments* dst = p.stats + (mi / 2) * p.pair_stride;
         const int y0 = ty0 + (mt0 + mi - 1 + lk) / MT_PER_ROW * MTH, x0 = tx0 + (mt0 + mi - 1 + lk) % MT_PER_ROW * MTW;
-        Moments m = block_moments<MTH, MTW, MTW * RW, RW>(wave_lds + lk * 32 * RW + lm, min(MTH, h - y0), min(MTW, w_out - x0));
-        if constexpr (MT_PER_ROW == 1) m = butterfly(m, lane, 32);
-        m = merge_to_first(m, lane, cpg);
-        if ((MT_PER_ROW == 2 || lk == 0) && (lm & (cpg - 1)) == 0 && m.n > 0.f)
-          store_device(stats + (size_t)((co_w + lm) / cpg) * stats_stride + (MT_PER_ROW == 2 ? lk : 0), m);
-        stats += pair_stride;
+        Moments m = block_moments<MTH, MTW, MTW * RW, RW>(wave_lds + lk * 32 * RW + lm, min(MTH, p.h - y0), min(MTW, p.w - x0));
+        m = merge_to_first(m, lane, p.cpg);
+        if ((lm & (p.cpg - 1)) == 0 && m.n > 0.f) dst[(size_t)((co_w + lm) / p.cpg) * p.stats_stride + lk] = m;
+      }
+      if (mi + 1 < MI && !ahead) put(wave_lds + ((mi + 1) & 1) * 32 * RW, mi + 1);
+    } else if ((mi + 1) % EMIT == 0) {
+      // (kRows4: rows past the image have no slot)
+      if (p.stats && (MODE != kRows4 || row_of(mi + 1 - EMIT, 0) < p.h)) {
+        Moments* dst = p.stats + (mi / EMIT) * p.pair_stride;
+        if (p.cpg >= 8) emit_moments<NI * 4, 1>(st, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
+        else if (p.cpg == 4) emit_moments<NI * 4, 2>(st, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
+        else if (p.cpg == 2) emit_moments<NI * 4, 4>(st, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
+        else emit_moments<NI * 4, 8>(st, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
       }
     }
-  }
-  if constexpr (!PAIRS) {
-    if (stats) emit_moments(stats);
   }
 }
 
@@ -320,14 +388,6 @@ constexpr int tile_buf_elems(int th, int tw, int pad, int kc, int mtw) { return 
 // a chunk).  The whole-chunk ring is for launches that leave a compute unit at most two workgroups: there a wavefront
 // is alone on its SIMD, nothing else hides the latency of weights that come from beyond the L2 (every layer's weights
 // are new to the L2 inside a decoder run), and the registers of the third workgroup are free for it.
-// MODE: kRows4 and kQuarters are forms between which and another kernel the batch decides, while a sample's bits must not
-// depend on that choice; so both keep the activation's roundings apart (PIN).
-//   kRows4     one of a pair of tiles, 4x16 and 8x16 (see four_row_slots): moments per four rows.
-//   kQuarters  the batched form of kernels_conv_ksplit.hip, with its order of summation: of every 64 input channels the
-//              k-th 16 belong to partial sum k, each of them is summed on its own, 16 channels and their nine taps at a
-//              time, and the four are added in order.  Here one after the other into a second set of accumulators, on M tiles of 4 x 8
-//              pixels, the blocks of that kernel's moments.
-enum ConvMode { kPlain = 0, kRows4 = 1, kQuarters = 2 };
 constexpr int m_tile_width(int tw, int mode) { return mode == kQuarters ? 8 : tw < 32 ? tw : 32; }
 template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int ACT, int MODE = kPlain, int RING = 0>
 __global__ __launch_bounds__(64 * WM * WN, RING > 6 ? 2 : resident_workgroups(wave_m_tiles(TH, TW, WM) * NI, WM, WN))
@@ -373,13 +433,19 @@ void conv_mfma_kernel(MfmaParams p) {
   const int ty0 = (tile / p.tiles_x) * TH, tx0 = (tile % p.tiles_x) * TW;
   const int co0 = nt * TN;
 
-  f32x16 acc[MI][NI];
+  // The accumulators start with the bias of their channel column (requested first; QUARTERS has to add it last, as the kernel
+  // that it reproduces)
+  constexpr bool BIAS_LAST = QUARTERS;
+  float start[NI];
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  for (int ni = 0; ni < NI; ++ni) {
+    start[ni] = 0.f;
+    if constexpr (!BIAS_LAST) {
+      const int co = min(co0 + (wn * NI + ni) * 32 + lm, p.cout - 1);   // (the frame has fewer channels than the tile)
+      if (p.bias) start[ni] = p.bias[co];
+      if (p.bias2) start[ni] += p.bias2[co];
+    }
+  }
 
   // LDS element offset of this lane's pixel in each of its M tiles (tap (0,0), k offset of the lane half)
   int a_off[MI];
@@ -422,6 +488,7 @@ void conv_mfma_kernel(MfmaParams p) {
     else return wcol + (chunk * KK + kk) * kk_stride;
   };
   u32x4 bq[D][NI];
+  f32x16 acc[MI][NI];
 #pragma unroll
   for (int sp = 0; sp < D - 1; ++sp) {
     const int tap = QUARTERS ? sp % (KS * KS) : sp / KK, kk = QUARTERS ? sp / (KS * KS) : sp % KK;
@@ -505,6 +572,12 @@ void conv_mfma_kernel(MfmaParams p) {
   constexpr int SPREAD = (ACT == 0 || MI * NI > 4) ? -1 : (SPREAD_AVG > 1 ? SPREAD_AVG - 1 : 1);
   f32x4 abv[2];   // table entries of the part being activated and of the next one (sliced activation)
 
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = start[j];
   // ---- shortcut phase (3x3 kernels with a second input): acc = W2 * x2 over the tile's own pixels, a 1x1
   // contraction over cin2 channels taken as stored (no normalisation).  Chunks of KC channels go through the same
   // two LDS buffers with the tile's halo layout (only the centre tap is read), loads two chunks ahead; the main
@@ -670,22 +743,27 @@ void conv_mfma_kernel(MfmaParams p) {
     __syncthreads();          // other buffer staged; this one free for chunk c+2
   }
 
-  // ---- epilogue: bias, residual, one rounding, store (through a wavefront-private LDS patch over the tile buffers)
-  TO* yout = reinterpret_cast<TO*>(p.y) + (size_t)n * p.h * p.w_out * p.cout;
-  const T* rin = p.res ? reinterpret_cast<const T*>(p.res) + (size_t)n * p.h * p.w_out * p.cout : nullptr;
-  constexpr bool PAIRS = MODE != kPlain;
-  float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(NI, PAIRS);
+  // ---- epilogue: residual, one rounding, store (through wavefront-private LDS patches over the tile buffers)
+  constexpr bool BLOCKS = MODE != kPlain;
+  float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(NI);
   // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row], or by blocks of 4 rows x 16 or 8 pixels
   const int per_row = QUARTERS ? (p.w_out + 7) / 8 : p.tiles_x;   // slots of a row of blocks
-  const int slot = PAIRS ? ty0 / 4 * per_row + tx0 / (QUARTERS ? 8 : TW) : tile * WM + wm;
-  Moments* st = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + slot : nullptr;
+  const int slot = BLOCKS ? ty0 / 4 * per_row + tx0 / (QUARTERS ? 8 : TW) : tile * WM + wm;
+  EpilogueParams ep;
+  {
+    const int elems = p.h * p.w_out * p.cout;   // of a sample
+    char* y = reinterpret_cast<char*>(p.y) + (size_t)n * elems * sizeof(TO);
+    ep.y = __builtin_amdgcn_make_buffer_rsrc(y, 0, (int)(elems * sizeof(TO)), 0x00020000);
+    ep.planar = y;
+    const char* res = reinterpret_cast<const char*>(p.res) + (size_t)n * elems * sizeof(T);
+    ep.res = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(res), 0, (int)(elems * sizeof(T)), 0x00020000);
+  }
+  ep.bias = p.bias; ep.bias2 = p.bias2; ep.h = p.h; ep.w = p.w_out; ep.cout = p.cout; ep.nchw = p.y_nchw != 0 && !p.res;
+  ep.stats = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + slot : nullptr;
+  ep.cpg = p.stats_cpg; ep.stats_stride = p.stats_slots; ep.pair_stride = per_row; ep.handed_over = p.rows_out != nullptr;
   auto store = [&](const f32x16 (&sums)[MI][NI]) {
-    if (rin)
-      epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true, PAIRS>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
-                                                                p.bias2, rin, yout, p.h, p.w_out, p.cout, false, st, p.stats_cpg, p.stats_slots, per_row);
-    else
-      epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false, PAIRS>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, p.bias,
-                                                                 p.bias2, rin, yout, p.h, p.w_out, p.cout, p.y_nchw != 0, st, p.stats_cpg, p.stats_slots, per_row);
+    if (p.res) epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true, MODE, BIAS_LAST>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
+    else epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false, MODE, BIAS_LAST>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
   };
   if constexpr (QUARTERS) store(total);
   else store(acc);
@@ -713,7 +791,7 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
   }
   constexpr int NT = 64 * WM * WN;
   size_t smem = (((size_t)2 * tile_buf_elems(TH, TW, PAD, KC, m_tile_width(TW, MODE)) * 2 + 15) & ~(size_t)15) + (size_t)(a.cin + a.groups) * sizeof(float2);
-  const size_t patch = (size_t)(WM * WN) * patch_floats(NI, MODE != kPlain) * sizeof(float);   // epilogue patches of the wavefronts
+  const size_t patch = (size_t)(WM * WN) * patch_floats(NI) * sizeof(float);   // epilogue patches of the wavefronts
   if (smem < patch) smem = patch;
   WMDEC_REQUIRE(smem <= 80 * 1024, WMDEC_ERR_UNSUPPORTED, "conv_mfma: %zu bytes of LDS needed", smem);
   void (*kern)(MfmaParams) = !p.norm ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 0, MODE, RING>
@@ -750,8 +828,8 @@ constexpr TileShape kTiles[kNumTiles] = {
 
 // Layers whose 128 x 128 tiles leave half of the compute units empty at batch 1 and whose moments, per 4x16 block, are few
 // enough for the consumer to merge: 64 x 128 tiles where the launch still fits one round, 128 x 128 otherwise, with the same
-// order of summation and the same moments.  Measured, us, 64 x 128 against 128 x 128: 512 channels at 64x64 27.8 / 35.3, at
-// 45x80 26.2 / 34.1, 256 channels at 68x92 16.9 / 21.8; past one round 47.4 / 43.5 (64x64, two samples), 89 / 78 (four).
+// order of summation and the same moments.  Measured, us, 64 x 128 against 128 x 128: 512 channels at 64x64 24.8 / 30.0, at
+// 34x46 19.5 / 27.7; past one round 37.0 / 34.4 (60x90).
 // The larger tile of the pair runs as T128x128_1x4 does: ResBlocks of 2 / 4 / 8 samples take 93.0 / 156.6 / 284.6 us at 512
 // channels 45x80 against 93.2 / 157.5 / 286.0, at 256 channels 68x92 61.5 / 92.1 / 157.9 against 61.3 / 92.5 / 158.8.
 bool four_row_slots(const ConvArgs& a) {
@@ -770,7 +848,7 @@ TileId pick_tile(const ConvArgs& a) {
       return (long)((a.h + 3) / 4) * ((a.w + 15) / 16) * (a.cout / 128) * a.n <= 256 ? T64x128 : T128x128_ROWS4;
     // 128 pixels x 128 channels with every wavefront on all pixels x 32 channels (three workgroups per compute unit):
     // measured against the 256-pixel tile and the 2x2 wavefront layout on every layer shape of the decoder, it is
-    // equal or faster everywhere (128 -> 128 at 480x720: 110 against 120 us; 512 -> 512 at 60x90: 33.5 against 35.1)
+    // equal or faster everywhere (512 -> 512 at 60x90: 35 us against 48 to 57 for 192 or 256 pixels, at 120x180 101 against 110)
     // With 256 channels per workgroup the normalise + SiLU work and the input traffic per MFMA halve, at two workgroups
     // per compute unit instead of three: it pays (6 to 8 %) where that still leaves every compute unit two workgroups
     // (the 240x360 layers of the decoder), and loses on smaller layers.

@@ -294,6 +294,33 @@ def test_conv_epilogue_statistics(dtype, ydtype, n, cin, cout, h, w, residual):
     assert torch.equal(y, y2)
 
 
+# ... and one per width of a group (1 to 32 channels) on every form of the moments: one triple per 8x16 tile and wavefront
+# row (128x64, 128x128 and 128x256 tiles), one per four rows (the small and the large tile of the pair), ragged in both directions
+@pytest.mark.parametrize("dtype,ydtype,cout,h,w", [("f16", "f16", 64, 13, 37), ("bf16", "f32", 64, 9, 17), ("f16", "f16", 128, 101, 115),
+                                                   ("bf16", "bf16", 128, 27, 45), ("f16", "f32", 128, 5, 19), ("bf16", "bf16", 256, 253, 262)])
+@pytest.mark.parametrize("cpg", [1, 2, 4, 8, 16, 32])
+def test_conv_epilogue_statistics_group_widths(dtype, ydtype, cout, h, w, cpg):
+    """Means of 40 standard deviations, and outliers of 300 on single pixels: sums about the lane's first value and
+    merges about the mean lose at most (300 / 8)^2 half ulps of a variance to a shift that is an outlier, 1e-4."""
+    r = rng(16 + cpg)
+    n, cin, groups, eps = 2, 32, cout // cpg, 1e-6
+    xd = G.dev_nhwc(G.stored(r.standard_normal((n, cin, h, w)), dtype), dtype)
+    wt, b = synth.conv_params(r, cout, cin, 3, True)
+    b = (b + 40.0 * np.where(np.arange(cout) // cpg % 2 == 0, 1, -1)).astype(np.float32)
+    rf = r.standard_normal((n, cout, h, w))
+    rf[:, :, 0, 0] += 300.0
+    rf[:, :, h - 1, w - 1] -= 300.0
+    res = G.dev_nhwc(G.stored(rf, dtype), dtype)
+    y = torch.empty((n, h, w, cout), dtype=G.TORCH[ydtype], device="cuda")
+    ws = torch.full((wmdec.conv_stats_workspace_bytes(G.ENUM[dtype], G.ENUM[ydtype], n, h, w, cin, cout, groups),), 0xFF, dtype=torch.uint8, device="cuda")
+    mo, ro = torch.empty(n * groups, device="cuda"), torch.empty(n * groups, device="cuda")
+    wmdec.gn_silu_conv3x3_stats(xd, None, None, None, None, 32, False, G.pack(wt, dtype), G.dev_f32(b), res, y, groups, eps, mo, ro, ws)
+    v = y.double().view(n, h * w, groups, cpg).permute(0, 2, 1, 3).reshape(n * groups, -1)
+    wm, wr = v.mean(1), 1 / torch.sqrt(v.var(1, unbiased=False) + eps)
+    em, er = float(((mo - wm).abs() * wr).max()), float((ro / wr - 1).abs().max())
+    assert em < 2e-5 and er < 1e-4, (em, er)
+
+
 def test_conv_epilogue_statistics_unsupported_shapes_are_refused():
     x = torch.zeros((1, 8, 8, 32), dtype=torch.float32, device="cuda")
     assert wmdec.conv_stats_workspace_bytes(wmdec.F32, wmdec.F32, 1, 8, 8, 32, 64, 32) == 0
