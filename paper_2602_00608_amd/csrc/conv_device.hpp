@@ -117,24 +117,46 @@ __device__ __forceinline__ float2 merge_row(const Moments* row, int count, int s
   return make_float2(mean + d, 1.0f / sqrtf((q < 0.f ? 0.f : q) / n + eps));   // (NaN stays NaN)
 }
 
-// Moments of one channel over rows x cols pixels in row-major order, plain sums about the first value; `src` points at the
-// first pixel's value in LDS, pixels PX and image rows ROW floats apart, of a block of H x W.
-template <int H, int W, int ROW, int PX> __device__ __forceinline__ Moments block_moments(const float* src, int rows, int cols) {
-  if (rows <= 0 || cols <= 0) return Moments{0.f, 0.f, 0.f};
-  const float shift = src[0];
-  float s = 0.f, q = 0.f;
-  auto add = [&](int ty, int tx) {
-    const float d = src[ty * ROW + tx * PX] - shift;
-    s += d; q = fmaf(d, d, q);
-  };
-  if (rows == H && cols == W) {
+// Sums over lanes in the vector ALU.  row_rotate: the value N lanes further round the row of 16; quad_xor: of lane ^ N (1, 2);
+// swap_sum: v of this lane plus that of lane ^ W (16, 32; the results of the swap are made opaque, as this compiler takes both
+// for the first one where the operands are the same).
+template <int N> __device__ __forceinline__ float row_rotate(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, true));
+}
+template <int N> __device__ __forceinline__ float quad_xor(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), N == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true));
+}
+template <int W> __device__ __forceinline__ float swap_sum(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  u32x2 r;
+  if constexpr (W == 16) r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  else r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  unsigned a = r.x, b = r.y;
+  asm volatile("" : "+v"(a), "+v"(b));
+  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
+
+// Moments of one channel over a block of 4 x W pixels (rows x cols of them valid) in LDS, pixels PX and image rows ROW floats apart:
+// sums about the block's first value, the rows in chains of their own, which are added in pairs (so that two lanes may take
+// two rows each).
+struct Sums { float s, q; };
+__device__ __forceinline__ Sums operator+(Sums a, Sums b) { return Sums{a.s + b.s, a.q + b.q}; }
+template <int W, int PX, bool FULL> __device__ __forceinline__ Sums row_sums(const float* src, float shift, int count) {
+  Sums r{0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < H * W; ++i) add(i / W, i % W);
-  } else {
-    for (int ty = 0; ty < rows; ++ty)
-      for (int tx = 0; tx < cols; ++tx) add(ty, tx);
+  for (int x = 0; x < W; ++x) {
+    const float d = FULL || x < count ? src[x * PX] - shift : 0.f;
+    r.s += d; r.q = fmaf(d, d, r.q);
   }
-  const float cnt = (float)(rows * cols), ds = s / cnt, m2 = q - s * ds;
+  return r;
+}
+template <int W, int ROW, int PX> __device__ __forceinline__ Sums two_row_sums(const float* src, float shift, int rows, int cols) {
+  if (rows >= 2 && cols == W) return row_sums<W, PX, true>(src, shift, W) + row_sums<W, PX, true>(src + ROW, shift, W);
+  return row_sums<W, PX, false>(src, shift, rows > 0 ? cols : 0) + row_sums<W, PX, false>(src + ROW, shift, rows > 1 ? cols : 0);
+}
+__device__ __forceinline__ Moments block_moments(Sums t, float shift, int rows, int cols) {
+  if (rows <= 0 || cols <= 0) return Moments{0.f, 0.f, 0.f};
+  const float cnt = (float)(rows * cols), ds = t.s * __builtin_amdgcn_rcpf(cnt), m2 = t.q - t.s * ds;   // 1 ulp of a difference to the shift
   return Moments{cnt, shift + ds, m2 < 0.f ? 0.f : m2};
 }
 

@@ -110,12 +110,19 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
 #pragma unroll
     for (int k = 0; k < FV; ++k) f.v[k] = load_fragment(wrsrc, lo + 16 * k, off);
   };
+
+  // The first rounds' weights, behind the input and the moments, which are needed first: loads return in order.  (In front of
+  // them, 512 channels at 17x23 took 0.3 us more; with four rounds ahead instead of two 0.5 us more still.)
+  auto first_weights = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int r = 0; r < AHEAD; ++r)
+    for (int r = 0; r < AHEAD; ++r)
 #pragma unroll
-    for (int t = 0; t < STEPS; ++t)
+      for (int t = 0; t < STEPS; ++t)
 #pragma unroll
-      for (int ni = 0; ni < NI; ++ni) load_weights(bq[r][t][ni], r, t, ni);
+        for (int ni = 0; ni < NI; ++ni) load_weights(bq[r][t][ni], r, t, ni);
+    __builtin_amdgcn_sched_barrier(0);
+  };
 
   // ---- staging: a thread owns NV (pixel, channel vector) pairs of the halo patch; the channel vector is the same for all
   const int cvec = tid % VPP;
@@ -200,6 +207,7 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
   issue(raw[0], p.x, p.cin, 0);
   if (rounds > 1) issue(raw[1], p.x, p.cin, 1);
 
+  if constexpr (ACT == 0) first_weights();
   // ---- scale/shift table.  16-bit types: (a, b) = k * (gamma * rstd, beta - mean * gamma * rstd), k = -log2(e) with
   // SiLU (see silu_from_scaled).  fp32: (gamma * rstd, beta), the mean stays apart.
   const int cpg_in = ACT > 0 ? p.cin / p.groups : 1;
@@ -217,6 +225,7 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
     } else {
       for (int g = tid; g < p.groups; g += NT) s_stat[g] = make_float2(p.mean[n * p.groups + g], p.rstd[n * p.groups + g]);
     }
+    first_weights();
     __syncthreads();
     const float k = (ES == 2 && ACT == 2) ? -1.4426950408889634f : 1.0f;
     for (int c = tid; c < p.cin; c += NT) {
@@ -375,18 +384,22 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
     if (p.stats) *reinterpret_cast<f32x4*>(own) = v;
   }
   // ---- moments of the stored values, one triple per (group, 4x8 block of pixels) whatever the tile, in an order that
-  // depends on neither the tile nor the batch: a lane sums one channel over the block's pixels row by row (shifted by
-  // the block's first value), the channels of a group are consecutive lanes
+  // depends on neither the tile nor the batch: a lane takes one channel of two rows of the block, the lane 32 further the
+  // other two, and the channels of a group are consecutive lanes.  (One lane walking all 32 pixels held the launch up for
+  // 0.8 us more at 17x23.)
   if (p.stats) {
     __syncthreads();
     constexpr int BX = TW / 8;
-    static_assert(TH == 4 && TW % 8 == 0, "blocks of 4 x 8 pixels");
-    for (int i = tid; i < BX * TN; i += NT) {
-      const int b = i / TN, c = i % TN, x0 = tx0 + 8 * b;
+    static_assert(TH == 4 && TW % 8 == 0 && TN % 32 == 0, "blocks of 4 x 8 pixels");
+    const int half = lane >> 5;
+    for (int i = wave; i < BX * (TN / 32); i += NW) {   // (uniform: a wavefront takes 32 channels of a block)
+      const int b = i / (TN / 32), c = i % (TN / 32) * 32 + lm, x0 = tx0 + 8 * b;
       const int rows = min(4, p.h - ty0), cols = min(8, p.w_out - x0);
       if (cols <= 0) continue;
-      const Moments m = merge_to_first(block_moments<4, 8, TW * RR, RR>(red + (size_t)(8 * b) * RR + c, rows, cols), lane, p.stats_cpg);
-      if (c % p.stats_cpg == 0)
+      const float* src = red + (size_t)(8 * b) * RR + c;
+      const Sums own = two_row_sums<8, TW * RR, RR>(src + 2 * half * TW * RR, src[0], rows - 2 * half, cols);
+      const Moments m = merge_to_first(block_moments(Sums{swap_sum<32>(own.s), swap_sum<32>(own.q)}, src[0], rows, cols), lane, p.stats_cpg);
+      if (half == 0 && c % p.stats_cpg == 0)
         p.stats[((size_t)n * p.stats_groups + (co0 + c) / p.stats_cpg) * p.stats_slots + (ty0 / 4) * ((p.w_out + 7) / 8) + x0 / 8] = m;
     }
   }
@@ -433,7 +446,7 @@ int launch_tile(const ConvArgs& a, hipStream_t s) {
 // Tiles of the 16-bit launches (4 rows high, WK = 4 everywhere: the order in which an output's products are added, and
 // with it a frame's bits, depends neither on the tile nor on the batch, so the tile may follow the workgroups of the whole
 // launch).  The smallest tile whose workgroups fit one round of the compute units wins; measured on 512 -> 512 layers, us,
-// in the order K32x32, K32x64, K64x64, K64x128: 17x23 11.4 / 12.0 / 15.1 / 19.0; 32x32 16.8 / 15.3 / 16.0 / 19.5; 34x46
+// in the order K32x32, K32x64, K64x64, K64x128 (the first three since 0.2 to 1 us faster): 17x23 11.4 / 12.0 / 15.1 / 19.0; 32x32 16.8 / 15.3 / 16.0 / 19.5; 34x46
 // 26.9 / 20.9 / 17.3 / 20.4; 45x80 - / - / 35.5 / 24.9.
 enum KsplitTile { K32x32 = 0, K32x64, K64x64, K64x128 };
 KsplitTile pick_ksplit_tile(const ConvArgs& a) {

@@ -35,25 +35,6 @@ namespace {
 //              pixels, the blocks of that kernel's moments.
 enum ConvMode { kPlain = 0, kRows4 = 1, kQuarters = 2 };
 
-// Sums over lanes in the vector ALU.  row_rotate: the value N lanes further round the row of 16; quad_xor: of lane ^ N (1, 2);
-// swap_sum: v of this lane plus that of lane ^ W (16, 32; the results of the swap are made opaque, as this compiler takes both
-// for the first one where the operands are the same).
-template <int N> __device__ __forceinline__ float row_rotate(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, true));
-}
-template <int N> __device__ __forceinline__ float quad_xor(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), N == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true));
-}
-template <int W> __device__ __forceinline__ float swap_sum(float v) {
-  const unsigned u = __builtin_bit_cast(unsigned, v);
-  u32x2 r;
-  if constexpr (W == 16) r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  else r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  unsigned a = r.x, b = r.y;
-  asm volatile("" : "+v"(a), "+v"(b));
-  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
-}
-
 // Moments of a wavefront's stored values in the making: per channel of the lane's octet sums shifted by the lane's first value,
 // over n pixels.
 struct LaneMoments { float n, shift[8], s[8], q[8]; };
@@ -253,7 +234,10 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
       if (mi % 2 == 1 && p.stats) {   // lanes 0-31: a channel of the pair's first tile, lanes 32-63: of the second
         Moments* dst = p.stats + (mi / 2) * p.pair_stride;
         const int y0 = ty0 + (mt0 + mi - 1 + lk) / MT_PER_ROW * MTH, x0 = tx0 + (mt0 + mi - 1 + lk) % MT_PER_ROW * MTW;
-        Moments m = block_moments<MTH, MTW, MTW * RW, RW>(wave_lds + lk * 32 * RW + lm, min(MTH, p.h - y0), min(MTW, p.w - x0));
+        const float* src = wave_lds + lk * 32 * RW + lm;
+        const int rows = min(MTH, p.h - y0), cols = min(MTW, p.w - x0);
+        Moments m = block_moments(two_row_sums<MTW, MTW * RW, RW>(src, src[0], rows, cols) +
+                                  two_row_sums<MTW, MTW * RW, RW>(src + 2 * MTW * RW, src[0], rows - 2, cols), src[0], rows, cols);
         m = merge_to_first(m, lane, p.cpg);
         if ((lm & (p.cpg - 1)) == 0 && m.n > 0.f) dst[(size_t)((co_w + lm) / p.cpg) * p.stats_stride + lk] = m;
       }
