@@ -87,6 +87,9 @@ __device__ __forceinline__ void emit_moments(const LaneMoments& st, int lane, in
 // floats of the wavefront-private epilogue patches: two of 32 padded rows
 constexpr int patch_floats(int ni) { return 2 * 32 * (ni * 32 + 4); }
 
+// first row of M tile mi of a wavefront whose M tiles are rows r and r + APART (blocks of 2 APART rows)
+template <int APART> constexpr int apart_row(int mi) { return mi / APART * 2 * APART + mi % APART; }
+
 struct EpilogueParams {
   const float* bias; const float* bias2;   // added here where the accumulators did not start with them (BIAS)
   __amdgpu_buffer_rsrc_t res, y;           // the sample's residual and output, with its size: accesses outside are dropped
@@ -106,7 +109,8 @@ struct EpilogueParams {
 // Moments: one triple per group for all M tiles, or (kRows4) for every two of them, four rows of 16 pixels.  kQuarters (NI = 1):
 // one for each M tile of 4 x 8 pixels, from the values written back to the patches of a pair: a lane walks one channel
 // of either tile, as the kernel that it reproduces does.
-template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, bool RES, int MODE, bool BIAS>
+// APART: row distance of an M tile's two halves where they are not neighbours (see mfma_chunk_rows), otherwise 0.
+template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, int APART, bool RES, int MODE, bool BIAS>
 __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], float* wave_lds, int lane, int mt0, int ty0,
                                                int tx0, int co_w, const EpilogueParams& p) {
   constexpr int RW = NI * 32 + 4;       // padded row of a patch, floats
@@ -148,7 +152,11 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
   // elements (< 2^29, checked on the host): the lane's part, and that of vector j of M tile mi
   constexpr unsigned OUTSIDE = 1u << 29;
   const unsigned lane_off = (unsigned)((lane_row * p.w + lane_col) * p.cout + cvec * 8);
-  auto row_of = [&](int mi, int j) { return ty0 + (mt0 + mi) / MT_PER_ROW * MTH + j * STEP / MTW; };
+  static_assert(APART == 0 || (MTW == 16 && STEP <= 16 && MT_PER_ROW == 1), "the lanes of a vector are in one row");
+  auto row_of = [&](int mi, int j) {
+    if constexpr (APART > 0) return ty0 + apart_row<APART>(mi) + APART * (j * STEP / MTW);
+    else return ty0 + (mt0 + mi) / MT_PER_ROW * MTH + j * STEP / MTW;
+  };
   auto col_of = [&](int mi, int j) { return tx0 + (mt0 + mi) % MT_PER_ROW * MTW + j * STEP % MTW; };
   auto inside = [&](int mi, int j) -> bool { return row_of(mi, j) + lane_row < p.h && col_of(mi, j) + lane_col < p.w; };
   auto base_of = [&](int mi, int j) -> int { return (row_of(mi, j) * p.w + col_of(mi, j)) * p.cout + co_w; };
@@ -279,6 +287,10 @@ constexpr int prefetch_ring(int steps, int room) {
 // weights of the two lie at bcur / bcur1, and flush(0 / 1) runs behind each.
 // AD: how many k-steps ahead the A fragments are read (1 or 2).  One step is MI - 1 MFMAs of slack, about the LDS
 // latency: enough where other wavefronts of the SIMD fill the gaps, too little for a wavefront that is alone on it.
+// byte offset, from the chunk's first fragment, of the weights of k-step s in the order of mfma_chunk_rows
+template <int KK> __device__ __forceinline__ int rows_weight_offset(int s, int tap_stride, int kk_stride) {
+  return (s % 3 * 3 + s / 3 / KK) * tap_stride + s / 3 % KK * kk_stride;
+}
 struct NoFlush { __device__ void operator()(int) const {} };
 template <typename T, int MI, int NI, int KS, int KC, int ROW, int PS, int D, bool SLICED, int VALU_PER_MFMA, typename Slice, int AD = 1, bool KMAJOR = false, typename Flush = NoFlush>
 __device__ __forceinline__ void mfma_chunk(const T* buf, const int (&a_off)[MI], __amdgpu_buffer_rsrc_t wrsrc, int bcur, int bnext,
@@ -344,6 +356,59 @@ __device__ __forceinline__ void mfma_chunk(const T* buf, const int (&a_off)[MI],
   static_for<STEPS>(step);
 }
 
+// The same for 3x3 taps where a wavefront's M tiles are the pixel rows (r, r + APART), r = 0 .. APART - 1, of blocks of 2 APART
+// rows of 16: one tap row further down, M tile r reads what M tile r + 1 reads here.  So APART + 2 fragments serve the three
+// taps of a column, 3 APART MFMAs: at 4 rows apart half the LDS reads of a fragment per MFMA, which kept the LDS, at
+// 128 B/clk for four SIMDs, as busy as the matrix pipe.  K-steps run over the tap rows innermost, then the chunk's groups of 16 channels,
+// then the tap columns; a fragment is refreshed in place behind its last MFMA, at least APART + 1 MFMAs before the next use.
+// Measured against neighbouring rows with a read per tap, both sides' frames against one third build: 480x720 frame 1.025x
+// (f16) and 1.016x (bf16), four frames 1.022x, 256x256 1.017x, 136x184 1.005x, ResBlock 128 at 480x720 bf16 1.026x (229 -> 223
+// us).  Taller wavefronts of the same kind, at two workgroups per compute unit instead of three, are slower: 16 rows 0.96x,
+// 12 rows 0.93x on that ResBlock.
+template <typename T, int MI, int NI, int KC, int ROW, int PS, int D, int VALU_PER_MFMA, int APART, typename Slice>
+__device__ __forceinline__ void mfma_chunk_rows(const T* buf, int a_off, __amdgpu_buffer_rsrc_t wrsrc, int bcur, int bnext, int tap_stride, int kk_stride,
+                                                int lane16, u32x4 (&bq)[D][NI], f32x16 (&acc)[MI][NI], Slice&& slice) {
+  constexpr int KK = KC / 16, GROUPS = 3 * KK, STEPS = 3 * GROUPS, FRAGS = APART + 2;
+  static_assert(MI % APART == 0, "whole blocks");
+  u32x4 af[MI / APART][FRAGS];
+  auto read = [&](auto g_c, auto b_c, auto f_c) {
+    constexpr int g = decltype(g_c)::value, b = decltype(b_c)::value, f = decltype(f_c)::value;
+    af[b][f] = *reinterpret_cast<const u32x4*>(buf + a_off + (b * 2 * APART + f) * ROW + (g / KK) * PS + (g % KK) * 16);
+  };
+  static_for<FRAGS>([&](auto f_c) {
+    static_for<MI / APART>([&](auto b_c) { read(std::integral_constant<int, 0>{}, b_c, f_c); });
+  });
+  static_for<STEPS>([&](auto s_c) {
+    constexpr int s = decltype(s_c)::value, g = s / 3, ky = s % 3;
+    {
+      constexpr int sp = s + D - 1;
+      const int at = (sp < STEPS ? bcur : bnext) + rows_weight_offset<KK>(sp % STEPS, tap_stride, kk_stride);
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) bq[sp % D][ni] = load_fragment(wrsrc, lane16, at + ni * 1024);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // the fragment that M tile mi is the last to read at this tap row
+    constexpr auto last = [](int mi) constexpr { return g + 1 < GROUPS && (ky == 2 || mi % APART == 0); };
+    static_for<MI>([&](auto mi_c) {
+      constexpr int mi = decltype(mi_c)::value, b = mi / APART, f = mi % APART + ky;
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = Mma<T>::m32(af[b][f], bq[s % D][ni], acc[mi][ni]);
+      if constexpr (last(mi)) read(std::integral_constant<int, g + 1>{}, std::integral_constant<int, b>{}, std::integral_constant<int, f>{});
+      slice(std::integral_constant<int, s * MI + mi>{});
+      if constexpr (VALU_PER_MFMA < 0) __builtin_amdgcn_sched_barrier(0);
+    });
+    if constexpr (VALU_PER_MFMA >= 0) {   // issue order inside the k-step, as above
+      static_for<MI * NI>([&](auto j_c) {
+        constexpr int j = decltype(j_c)::value;
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                       // one MFMA
+        if constexpr (j % NI == NI - 1 && last(j / NI)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+        if constexpr (VALU_PER_MFMA > 0) __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER_MFMA, 0);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  });
+}
+
 // ACT: what happens to an input element on its way into LDS: 0 nothing, 1 scale/shift, 2 scale/shift + SiLU
 constexpr int wave_m_tiles(int th, int tw, int wm) { return th * tw / 32 / wm; }
 // Workgroups per compute unit the register budget is sized for: three for the small accumulator tiles, except the
@@ -373,6 +438,10 @@ constexpr int tile_buf_elems(int th, int tw, int pad, int kc, int mtw) { return 
 // is alone on its SIMD, nothing else hides the latency of weights that come from beyond the L2 (every layer's weights
 // are new to the L2 inside a decoder run), and the registers of the third workgroup are free for it.
 constexpr int m_tile_width(int tw, int mode) { return mode == kQuarters ? 8 : tw < 32 ? tw : 32; }
+// Wavefronts that hold all rows of a 16-pixel-wide patch take rows apart; kRows4: inside the four rows of a triple of moments.
+constexpr int rows_apart(int tw, int wm, int mi, int ks, int mode) {
+  return ks == 3 && tw == 16 && wm == 1 && mode != kQuarters ? (mode == kRows4 ? 2 : mi) : 0;
+}
 template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int ACT, int MODE = kPlain, int RING = 0>
 __global__ __launch_bounds__(64 * WM * WN, RING > 6 ? 2 : resident_workgroups(wave_m_tiles(TH, TW, WM) * NI, WM, WN))
 void conv_mfma_kernel(MfmaParams p) {
@@ -392,6 +461,7 @@ void conv_mfma_kernel(MfmaParams p) {
   constexpr int SPARE = HH_ * ROW;                       // element offset of the spare pixel slot
   constexpr int STEPS = KS * KS * (KC / 16), SLOTS = STEPS * MI;
   constexpr bool SLICED = KS == 3;               // activation of the next chunk is sliced into the MFMA sweep
+  constexpr int APART = rows_apart(TW, WM, MI, KS, MODE);   // see mfma_chunk_rows; 0: M tiles of neighbouring rows
   static_assert(NT % VPP == 0, "a thread keeps one channel octet");
 
   extern __shared__ __align__(16) unsigned char smem[];
@@ -436,7 +506,9 @@ void conv_mfma_kernel(MfmaParams p) {
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
     const int mt = wm * MI + mi;
-    const int ty = (mt / MT_PER_ROW) * MTH + lm / MTW, tx = (mt % MT_PER_ROW) * MTW + lm % MTW;
+    int ty = (mt / MT_PER_ROW) * MTH + lm / MTW;
+    if constexpr (APART > 0) ty = apart_row<APART>(mi) + APART * (lm / MTW);
+    const int tx = (mt % MT_PER_ROW) * MTW + lm % MTW;
     a_off[mi] = ty * ROW + tx * PS + 8 * lk;
   }
   constexpr int KK = KC / 16;
@@ -476,8 +548,9 @@ void conv_mfma_kernel(MfmaParams p) {
 #pragma unroll
   for (int sp = 0; sp < D - 1; ++sp) {
     const int tap = QUARTERS ? sp % (KS * KS) : sp / KK, kk = QUARTERS ? sp / (KS * KS) : sp % KK;
+    const int at = APART > 0 ? wcol + rows_weight_offset<KK>(sp, tap_stride, kk_stride) : weights_at(0, 0, kk) + tap * tap_stride;
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) bq[sp][ni] = load_fragment(wrsrc, lane16, weights_at(0, 0, kk) + tap * tap_stride + ni * 1024);
+    for (int ni = 0; ni < NI; ++ni) bq[sp][ni] = load_fragment(wrsrc, lane16, at + ni * 1024);
   }
 
   // ---- staging: a thread owns NV (pixel, channel-octet) vectors of the halo tile; the octet is the same for all
@@ -713,7 +786,8 @@ void conv_mfma_kernel(MfmaParams p) {
       };
       // the last chunk activates a harmless reload into the buffer nobody reads: one instruction stream, no
       // control flow inside the pinned schedule
-      mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, true, SPREAD, decltype(slice)&, (RING > 6 ? 2 : 1), QUARTERS>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, slice, bcur1, bnext1, flush);
+      if constexpr (APART > 0) mfma_chunk_rows<T, MI, NI, KC, ROW, PS, D, SPREAD, APART>(buf, a_off[0], wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, slice);
+      else mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, true, SPREAD, decltype(slice)&, (RING > 6 ? 2 : 1), QUARTERS>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, slice, bcur1, bnext1, flush);
     } else {
       auto none = [](auto) {};
       mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, false, -1, decltype(none)&, (RING > 6 ? 2 : 1)>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, none);
@@ -746,8 +820,8 @@ void conv_mfma_kernel(MfmaParams p) {
   ep.stats = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + slot : nullptr;
   ep.cpg = p.stats_cpg; ep.stats_stride = p.stats_slots; ep.pair_stride = per_row; ep.handed_over = p.rows_out != nullptr;
   auto store = [&](const f32x16 (&sums)[MI][NI]) {
-    if (p.res) epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true, MODE, BIAS_LAST>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
-    else epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false, MODE, BIAS_LAST>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
+    if (p.res) epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, APART, true, MODE, BIAS_LAST>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
+    else epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, APART, false, MODE, BIAS_LAST>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
   };
   if constexpr (QUARTERS) store(total);
   else store(acc);

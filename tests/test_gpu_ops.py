@@ -245,6 +245,26 @@ def test_gn_silu_conv3x3(dtype, ydtype, n, cin, cout, h, w, norm, silu, bias, re
         assert err <= tol / 2, err   # fp32 output of 16-bit operands: well inside the bar
 
 
+# every output channel one tap of one input channel: an exact copy of the input, displaced by the tap, whatever order the
+# products are summed in.  Ragged sizes of the tiles whose lanes hold rows apart: 8 rows of a wavefront, four of them, two
+# blocks of four in a larger batch, 64 channels a wavefront; one, two and three chunks of input channels.
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("n,cin,cout,h,w", [(1, 64, 128, 101, 115), (1, 32, 128, 97, 129), (1, 96, 128, 27, 45), (13, 96, 128, 27, 45),
+                                            (1, 32, 128, 1, 1), (1, 32, 128, 253, 262), (1, 96, 256, 253, 262)])
+def test_conv_of_single_taps_is_an_exact_displacement(dtype, n, cin, cout, h, w):
+    x = torch.from_numpy(rng(21).standard_normal((n, h, w, cin)).astype(np.float32)).to(G.TORCH[dtype])
+    wt = np.zeros((cout, cin, 3, 3), np.float32)
+    want = torch.zeros((n, h, w, cout), dtype=x.dtype)
+    padded = torch.nn.functional.pad(x, (0, 0, 1, 1, 1, 1))
+    for co in range(cout):
+        ci, ky, kx = 7 * co % cin, co % 9 // 3, co % 3
+        wt[co, ci, ky, kx] = 1.0
+        want[..., co] = padded[:, ky:ky + h, kx:kx + w, ci]
+    y = torch.empty(want.shape, dtype=x.dtype, device="cuda")
+    wmdec.gn_silu_conv3x3(x.cuda(), None, None, None, None, 32, False, G.pack(wt, dtype), None, None, y)
+    assert torch.equal(y.cpu(), want)
+
+
 # moments of a convolution's own output from its epilogue: one case per tile shape of the matrix-core kernel
 @pytest.mark.parametrize("dtype,ydtype,n,cin,cout,h,w,residual", [
     ("f16", "f16", 1, 128, 128, 40, 56, True),      # 128 x 128 tile, wavefronts 2x2
