@@ -52,17 +52,23 @@ __device__ __forceinline__ float half_sum(float v) {
   return v + __shfl_xor(v, 16);
 }
 
-// WM wavefront rows share the grid's four M tiles, WN wavefront columns of 32 channels.
+// Four wavefronts: WM rows share the grid's four M tiles, WN columns of 32 channels.  Where that leaves wavefronts over, KS
+// groups of them take a part of the input channels each, with patches of their own, and every wavefront finishes a KS-th of
+// its row's M tiles after the partial sums were exchanged through LDS.
 // FINE: moments of groups of one or two channels (sums per channel instead of per quad).
 template <typename T, int WM, int WN, bool FINE>
-__global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, int y_f32) {
-  constexpr int NT = 64 * WM * WN, MI = 4 / WM, TN = 32 * WN;
-  constexpr int VPP = KC / 8, NV = (PH_ * PW * VPP + NT - 1) / NT;
-  extern __shared__ __align__(16) unsigned char smem[];   // [2][BUFB]
+__global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32) {
+  constexpr int NT = 256, KS = 4 / (WM * WN), NTK = NT / KS, MI = 4 / WM, TN = 32 * WN;
+  constexpr int ME = MI / KS, WR = WM * KS;   // the epilogue's M tiles per wavefront, and its wavefront rows
+  constexpr int VPP = KC / 8, NV = (PH_ * PW * VPP + NTK - 1) / NTK;
+  static_assert(KS == 1 || (KS == 2 && MI == 2), "the exchange below hands over one of two M tiles");
+  extern __shared__ __align__(16) unsigned char smem_all[];   // [KS][2][BUFB]
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wn = wave % WN, wm = wave / WN;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wn = wave % WN, wm = wave / WN % WM, wk = wave / (WN * WM);
+  const int tid = threadIdx.x - wk * NTK;   // within the group
+  unsigned char* smem = smem_all + wk * 2 * BUFB;
   const int lm = lane & 31, lk = lane >> 5;
   int L;   // consecutive ids of one XCD (id % 8) are neighbours
   {
@@ -79,17 +85,18 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
   // weight fragments: tap t of k-step s is fragment (t, s); in place, one k-step (nine fragments) ahead
   const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w), 0, p.w_bytes, 0x00020000);
   const int kk_stride = p.cout_blocks * 1024, tap_stride = p.cin_blocks * kk_stride, wcol = (co_w >> 5) * 1024;
-  const int lane16 = lane * 16, ksteps = p.cin / 16;
+  const int chunks = p.cin / KC / KS, c0 = wk * chunks;   // chunks of the group, and its first
+  const int lane16 = lane * 16, ksteps = 2 * (c0 + chunks);
   u32x4 bq[9];
 #pragma unroll
-  for (int t = 0; t < 9; ++t) bq[t] = load_fragment(wrsrc, lane16, wcol + kTap[t] * tap_stride);
+  for (int t = 0; t < 9; ++t) bq[t] = load_fragment(wrsrc, lane16, wcol + 2 * c0 * kk_stride + kTap[t] * tap_stride);
 
   const int cvec = tid % VPP;
   const char* xin = reinterpret_cast<const char*>(p.x) + (size_t)n * h_in * w_in * p.cin * 2;
   int src_off[NV], dst_off[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const int hp = (tid + i * NT) / VPP, hy = hp / PW, hx = hp % PW;
+    const int hp = (tid + i * NTK) / VPP, hy = hp / PW, hx = hp % PW;
     const int gy = ty0 + hy - 1, gx = tx0 + hx - 1;
     const bool in_patch = hp < PH_ * PW, inside = in_patch && gy >= 0 && gy < h_in && gx >= 0 && gx < w_in;
     // outside the image: loaded from pixel 0, stored to the spare slot; the real slot is zeroed once
@@ -101,9 +108,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
     }
   }
   u32x4 raw[NV];
-  const int chunks = p.cin / KC;
   auto issue = [&](int c) {
-    const int cb = min(c, chunks - 1) * KC * 2;   // past the last chunk: a harmless reload
+    const int cb = (c0 + min(c, chunks - 1)) * KC * 2;   // past the last chunk: a harmless reload
 #pragma unroll
     for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(xin + (unsigned)(src_off[i] + cb));
   };
@@ -115,7 +121,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
   f32x16 acc[4][MI];   // A, B, C, D; every phase holds A once, so A starts from the bias
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const float bias = p.bias ? p.bias[co_w + 8 * (r / 4) + 4 * lk + r % 4] : 0.f;
+    const float bias = p.bias && wk == 0 ? p.bias[co_w + 8 * (r / 4) + 4 * lk + r % 4] : 0.f;
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -143,7 +149,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
     static_for<8>([&](auto g_c) {
       constexpr int g = decltype(g_c)::value, kk = g / 4, s = g % 4;   // shift s of k-step kk
       if constexpr (g + 2 < 8) read_shift(af[(g + 2) % 3], g + 2);
-      const int next = wcol + min(2 * c + kk + 1, ksteps - 1) * kk_stride;
+      const int next = wcol + min(2 * (c0 + c) + kk + 1, ksteps - 1) * kk_stride;
       static_for<kFirst[s + 1] - kFirst[s]>([&](auto t_c) {
         constexpr int t = kFirst[s] + decltype(t_c)::value;
 #pragma unroll
@@ -160,18 +166,44 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
     __syncthreads();
   }
 
+  // ---- the partial sums: a wavefront gives the M tile that the other group's wavefront of its row finishes
+  f32x16 sum[4][ME];
+  if constexpr (KS > 1) {
+    float* half = reinterpret_cast<float*>(smem_all);   // [4 wavefronts][2][16][64]: two accumulators at a time
+    const int other = wave ^ (WN * WM);
+#pragma unroll
+    for (int a0 = 0; a0 < 4; a0 += 2) {
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) half[((wave * 2 + a) * 16 + r) * 64 + lane] = wk ? acc[a0 + a][0][r] : acc[a0 + a][1][r];
+      __syncthreads();
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[a0 + a][0][r] = (wk ? acc[a0 + a][1][r] : acc[a0 + a][0][r]) + half[((other * 2 + a) * 16 + r) * 64 + lane];
+      __syncthreads();
+    }
+  } else {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int mi = 0; mi < ME; ++mi) sum[a][mi] = acc[a][mi];
+  }
+  const int wr = wm * KS + wk;   // wavefront row of the epilogue, M tiles wr * ME + (0 .. ME - 1)
+
   // ---- the four phases of every finished pixel, in registers.  Element r of a lane: channel co_w + 8 (r / 4) + 4 lk + r % 4
-  // of grid position (2 m + lm / 16, lm % 16).  Wavefront row wm needs the first grid row of the M tile below its last,
-  // which another wavefront holds when WM > 1: C and D of it travel through LDS.
-  float* ex = reinterpret_cast<float*>(smem);   // [WM][WN][2][16][64]
-  if constexpr (WM > 1) {
+  // of grid position (2 m + lm / 16, lm % 16).  Wavefront row wr needs the first grid row of the M tile below its last,
+  // which another wavefront holds when WR > 1: C and D of it travel through LDS.
+  float* ex = reinterpret_cast<float*>(smem_all);   // [WR][WN][2][16][64]
+  if constexpr (WR > 1) {
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ex[(((wm * WN + wn) * 2 + a) * 16 + r) * 64 + lane] = acc[2 + a][0][r];
+      for (int r = 0; r < 16; ++r) ex[(((wr * WN + wn) * 2 + a) * 16 + r) * 64 + lane] = sum[2 + a][0][r];
     __syncthreads();
   }
-  const int wb = (min(wm + 1, WM - 1) * WN + wn) * 2;   // the wavefront below; the last row's copy of itself reaches no output
+  const int wb = (min(wr + 1, WR - 1) * WN + wn) * 2;   // the wavefront below; the last row's copy of itself reaches no output
   const bool odd_row = (lm & 16) != 0;
   const size_t sample = (size_t)n * p.h * p.w_out * p.cout;
   const int cpg = p.stats_cpg;
@@ -179,12 +211,12 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
   // gets an offset of 2^31, behind any sample, where a store is dropped (a row further is still below 2^32)
   const int es = y_f32 ? 4 : 2;
   const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(p.y) + sample * es, 0, p.h * p.w_out * p.cout * es, 0x00020000);
-  unsigned y_off[MI];
+  unsigned y_off[ME];
   int live_px = 0, first_px = 0;   // pixels this wavefront finishes, and those of its first M tile (of which it has some if any)
-  bool live[MI];
+  bool live[ME];
 #pragma unroll
-  for (int mi = 0; mi < MI; ++mi) {
-    const int gy = 2 * (wm * MI + mi) + lm / GW, gx = lm % GW;
+  for (int mi = 0; mi < ME; ++mi) {
+    const int gy = 2 * (wr * ME + mi) + lm / GW, gx = lm % GW;
     const int iy = ty0 + gy, ix = tx0 + gx;
     live[mi] = gy < TH && gx < TW && iy < h_in && ix < w_in;
     y_off[mi] = live[mi] ? ((2 * iy * p.w_out + 2 * ix) * p.cout + co_w + (y_f32 ? 4 : 8) * lk) * es : 0x80000000u;
@@ -202,15 +234,15 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
 #pragma unroll
     for (int k = 0; k < NS; ++k) { sh[k] = 0.f; ss[k] = 0.f; sq[k] = 0.f; }
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
+    for (int mi = 0; mi < ME; ++mi) {
       float out[4][8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int r = 8 * qp + e;
-        const float a = acc[0][mi][r], b = acc[1][mi][r], c = acc[2][mi][r], d = acc[3][mi][r];
+        const float a = sum[0][mi][r], b = sum[1][mi][r], c = sum[2][mi][r], d = sum[3][mi][r];
         float cb = 0.f, db = 0.f;
-        if (mi + 1 < MI) { cb = acc[2][mi + 1 < MI ? mi + 1 : mi][r]; db = acc[3][mi + 1 < MI ? mi + 1 : mi][r]; }
-        else if constexpr (WM > 1) { cb = ex[((wb + 0) * 16 + r) * 64 + lane]; db = ex[((wb + 1) * 16 + r) * 64 + lane]; }
+        if (mi + 1 < ME) { cb = sum[2][mi + 1 < ME ? mi + 1 : mi][r]; db = sum[3][mi + 1 < ME ? mi + 1 : mi][r]; }
+        else if constexpr (WR > 1) { cb = ex[((wb + 0) * 16 + r) * 64 + lane]; db = ex[((wb + 1) * 16 + r) * 64 + lane]; }
         const float c1 = next_row(c, cb, odd_row), d1 = next_row(d, db, odd_row);
         out[0][e] = (a + b) + (c + d);
         out[1][e] = (a + c) + next_column(b + d);
@@ -278,7 +310,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
         if constexpr (FINE) mq[k % 4] = m;
         else mq[2 * qp + k] = m;
         if (FINE && k % 4 == 3 && lm == 0) {   // one quad's channels: four groups of one or two of two
-          Moments* dst = p.stats + ((size_t)n * p.stats_groups + (co_w + 8 * (2 * qp + k / 4) + 4 * lk) / cpg) * p.stats_slots + tile * WM + wm;
+          Moments* dst = p.stats + ((size_t)n * p.stats_groups + (co_w + 8 * (2 * qp + k / 4) + 4 * lk) / cpg) * p.stats_slots + tile * WR + wr;
           if (cpg == 2) { mq[0] = merge(mq[0], mq[1]); mq[1] = merge(mq[2], mq[3]); }
 #pragma unroll
           for (int g = 0; g < 4; ++g)
@@ -287,17 +319,17 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
       }
     }
   }
-  if (!FINE && p.stats) {   // quads of a group; WM wavefront rows leave a slot each
+  if (!FINE && p.stats) {   // quads of a group; WR wavefront rows leave a slot each
     if (cpg >= 16) { mq[0] = merge(mq[0], mq[1]); mq[2] = merge(mq[2], mq[3]); }
     if (cpg >= 32) mq[0] = merge(mq[0], mq[2]);
     if (lm == 0 && (lk == 0 || cpg == 4)) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if ((8 * q) % cpg == 0 || cpg == 4)
-          store_device(p.stats + ((size_t)n * p.stats_groups + (co_w + 8 * q + 4 * lk) / cpg) * p.stats_slots + tile * WM + wm, mq[q]);
+          store_device(p.stats + ((size_t)n * p.stats_groups + (co_w + 8 * q + 4 * lk) / cpg) * p.stats_slots + tile * WR + wr, mq[q]);
     }
   }
-  if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, nt * TN, TN, WM, tid, lane);
+  if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, nt * TN, TN, WR, threadIdx.x, lane);
 }
 
 // 64 channels a workgroup, two wavefronts on either half of the grid, two workgroups per compute unit: their epilogues
@@ -305,19 +337,35 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv_up_kernel(MfmaParams p, 
 // 170, one wavefront row 170, four 246); a wavefront row per M tile re-reads every weight fragment four times.
 constexpr int kWM = 2, kWN = 2, kTN = 32 * kWN;
 
+// ... or 32 channels, with the contraction split in two: one round of half as many channels then leaves compute units idle, and
+// a lone workgroup is bound by the weights that its wavefronts take through the vector L1 (64 B/clk), 1.2 MB at 512
+// channels, of which half the channels need half.  A function of the sample's shape: the sums do not depend on the batch.
+// 512 channels, us: 17x23 20.7 -> 17.4, 32x32 22.0 -> 19.3; frames of these sizes 1.008x and 1.006x.  Past 128 workgroups the halves
+// would share a compute unit again.
+bool split_channels(const ConvArgs& a) {
+  const long wgs = (long)((a.h / 2 + TH - 1) / TH) * ((a.w / 2 + TW - 1) / TW) * (a.cout / kTN);
+  return a.cin % (2 * KC) == 0 && wgs <= 128;
+}
+int tile_channels(const ConvArgs& a) { return split_channels(a) ? 32 : kTN; }
+int slots_per_tile(const ConvArgs& a) { return split_channels(a) ? 4 : kWM; }
+
 bool fine_moments(const ConvArgs& a) { return a.stats_groups > 0 && a.cout / a.stats_groups < 4; }
 
 template <typename T>
 int launch_up(const ConvArgs& a, hipStream_t s) {
-  MfmaParams p = conv_params(a, TH, TW, kTN, kWM, a.h / 2, a.w / 2);
+  const bool split = split_channels(a);
+  MfmaParams p = conv_params(a, TH, TW, tile_channels(a), slots_per_tile(a), a.h / 2, a.w / 2);
   const int rc = check_hand_over(p);
   if (rc != WMDEC_OK) return rc;
   p.w = a.wt;
   p.w_bytes = (int)(packed_elems(9, a.cout, a.cin) * sizeof(T));
   constexpr size_t kExchange = (size_t)kWM * kWN * 2 * 16 * 64 * sizeof(float);   // rows handed between wavefront rows
   constexpr size_t kSmem = 2 * BUFB > kExchange ? 2 * BUFB : kExchange;
-  hipLaunchKernelGGL(fine_moments(a) ? (conv_up_kernel<T, kWM, kWN, true>) : (conv_up_kernel<T, kWM, kWN, false>),
-                     dim3((unsigned)p.total), dim3(64 * kWM * kWN), kSmem, s, p, a.y_dtype == WMDEC_F32 ? 1 : 0);
+  constexpr size_t kSplitSmem = 4 * BUFB;   // patches of two groups
+  static_assert(kSplitSmem >= kExchange && kExchange == (size_t)4 * 2 * 16 * 64 * sizeof(float), "rows and partial sums fit the patches");
+  void (*kern)(MfmaParams, int) = split ? (fine_moments(a) ? conv_up_kernel<T, kWM, 1, true> : conv_up_kernel<T, kWM, 1, false>)
+                                        : (fine_moments(a) ? conv_up_kernel<T, kWM, kWN, true> : conv_up_kernel<T, kWM, kWN, false>);
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.total), dim3(256), split ? kSplitSmem : kSmem, s, p, a.y_dtype == WMDEC_F32 ? 1 : 0);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
 }
@@ -337,19 +385,20 @@ int conv_up_stats_slots(const ConvArgs& a) {
   if (a.stats_groups <= 0 || a.cout % a.stats_groups != 0) return 0;
   const int cpg = a.cout / a.stats_groups;
   if ((cpg & (cpg - 1)) != 0 || cpg > 32) return 0;   // a group must sit inside one wavefront's 32 channels
-  return ((a.h / 2 + TH - 1) / TH) * ((a.w / 2 + TW - 1) / TW) * kWM;
+  return ((a.h / 2 + TH - 1) / TH) * ((a.w / 2 + TW - 1) / TW) * slots_per_tile(a);
 }
 
 void conv_up_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row) {
   *tile_rows = (a.h / 2 + TH - 1) / TH;
-  *channel_tiles = a.cout / kTN;
+  *channel_tiles = a.cout / tile_channels(a);
   *tiles_per_row = (a.w / 2 + TW - 1) / TW;
 }
 
 const char* conv_up_label(const ConvArgs& a) {
-  static_assert(kWM == 2 && kWN == 2, "spelled out below");
-  if (fine_moments(a)) return a.op_dtype == WMDEC_BF16 ? "conv_up_kernel<wmdec::bf16_t, 2, 2, true>" : "conv_up_kernel<wmdec::f16_t, 2, 2, true>";
-  return a.op_dtype == WMDEC_BF16 ? "conv_up_kernel<wmdec::bf16_t, 2, 2, false>" : "conv_up_kernel<wmdec::f16_t, 2, 2, false>";
+  static thread_local char buf[64];
+  snprintf(buf, sizeof(buf), "conv_up_kernel<%s, %d, %d, %s>", a.op_dtype == WMDEC_BF16 ? "wmdec::bf16_t" : "wmdec::f16_t", kWM,
+           split_channels(a) ? 1 : kWN, fine_moments(a) ? "true" : "false");
+  return buf;
 }
 
 int launch_conv_up(const ConvArgs& a, hipStream_t s) { return a.op_dtype == WMDEC_BF16 ? launch_up<bf16_t>(a, s) : launch_up<f16_t>(a, s); }

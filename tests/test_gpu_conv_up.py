@@ -42,3 +42,10 @@ def test_upsampling_convolution_sample_bits_do_not_depend_on_the_batch():
     wmdec.upsample2x_conv3x3(x, wp, bd, y3)
     wmdec.upsample2x_conv3x3(x[1:2].contiguous(), wp, bd, y1)
     assert torch.equal(y3[1:2], y1)
+
+
+# 128 workgroups of 64 channels, the last count whose contraction is split in two, and the next size up; one chunk of 32 channels a half
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("w", [60, 61])
+def test_upsampling_convolution_either_side_of_the_split(dtype, w):
+    test_upsampling_convolution_tile_edges(dtype, 1, 64, 512, 28, w)
