@@ -888,6 +888,8 @@ constexpr TileShape kTiles[kNumTiles] = {
 // enough for the consumer to merge: 64 x 128 tiles where the launch still fits one round, 128 x 128 otherwise, with the same
 // order of summation and the same moments.  Measured, us, 64 x 128 against 128 x 128: 512 channels at 64x64 24.8 / 30.0, at
 // 34x46 19.5 / 27.7; past one round 37.0 / 34.4 (60x90).
+// The smaller tile always has a whole chunk of weight fragments in flight: two MFMAs a k-step cover little of the latency of
+// weights that are new to the L2 (256x256 frame 859 -> 853 us against half a chunk, 136x184 the same).
 // The larger tile of the pair runs as T128x128_1x4 does: ResBlocks of 2 / 4 / 8 samples take 93.0 / 156.6 / 284.6 us at 512
 // channels 45x80 against 93.2 / 157.5 / 286.0, at 256 channels 68x92 61.5 / 92.1 / 157.9 against 61.3 / 92.5 / 158.8.
 bool four_row_slots(const ConvArgs& a) {
@@ -935,7 +937,7 @@ int launch_3x3(const ConvArgs& a, hipStream_t s) {
     case T128x64: return launch_cfg<T, TO, 8, 16, 4, 1, 2, 3, 32>(a, s);
     case T128x128_1x4:
       return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32>(a, s);
-    case T64x128: return launch_cfg<T, TO, 4, 16, 1, 4, 1, 3, 32, 9, kRows4>(a, s);
+    case T64x128: return launch_cfg<T, TO, 4, 16, 1, 4, 1, 3, 32, 18, kRows4>(a, s);
     case T128x128_ROWS4:
       return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18, kRows4>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 0, kRows4>(a, s);
     case T128x256: return launch_cfg<T, TO, 8, 16, 1, 4, 2, 3, 32>(a, s);
@@ -1011,7 +1013,7 @@ const char* conv_mfma_label(const ConvArgs& a) {
   const int act = a.mean == nullptr && a.rows_in == nullptr && !a.groups_norm ? 0 : (a.silu ? 2 : 1);
   snprintf(buf, sizeof(buf), "conv_mfma_kernel<%s, %s, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d>", ty,
            a.y_dtype == WMDEC_F32 ? "float" : ty, ts.th, ts.tw, ts.wm, ts.wn, ts.ni, a.ksize, kc, act,
-           t == T64x128 || t == T128x128_ROWS4 ? kRows4 : kPlain, a.ksize == 3 && whole_chunk_ring(a) ? 18 : t == T64x128 ? 9 : 0);
+           t == T64x128 || t == T128x128_ROWS4 ? kRows4 : kPlain, a.ksize == 3 && whole_chunk_ring(a) ? 18 : t == T64x128 ? 18 : 0);
   return buf;
 }
 
