@@ -18,7 +18,7 @@ extern "C" {
 
 /* Per-step timing for measurement.  With profiling enabled decoder_run records
  * a HIP event on `stream` before the first and after every step of the graph
- * (a step = one GroupNorm statistics pass, one convolution, the V transpose or
+ * (a step = one GroupNorm statistics pass, one convolution, the attention projection or
  * the attention core).  decoder_step_info gives, for step `index`, the name of
  * the kernel that executes it (for convolutions the template instantiation as
  * a profiler prints it; the string is valid until the thread's next call) and
