@@ -7,6 +7,7 @@
 #include "mfma.hpp"
 #include "moments.hpp"
 #include "pack_layout.hpp"
+#include "sample_offsets.hpp"
 
 namespace wmdec {
 

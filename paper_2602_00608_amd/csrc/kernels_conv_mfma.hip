@@ -149,8 +149,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
 #pragma unroll
     for (int e = 0; e < 8; ++e) bv[e] = (p.bias ? p.bias[co_w + cvec * 8 + e] : 0.f) + (p.bias2 ? p.bias2[co_w + cvec * 8 + e] : 0.f);
   }
-  // elements (< 2^29, checked on the host): the lane's part, and that of vector j of M tile mi
-  constexpr unsigned OUTSIDE = 1u << 29;
+  // elements: the lane's part, and that of vector j of M tile mi
   const unsigned lane_off = (unsigned)((lane_row * p.w + lane_col) * p.cout + cvec * 8);
   static_assert(APART == 0 || (MTW == 16 && STEP <= 16 && MT_PER_ROW == 1), "the lanes of a vector are in one row");
   auto row_of = [&](int mi, int j) {
@@ -159,14 +158,14 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
   };
   auto col_of = [&](int mi, int j) { return tx0 + (mt0 + mi) % MT_PER_ROW * MTW + j * STEP % MTW; };
   auto inside = [&](int mi, int j) -> bool { return row_of(mi, j) + lane_row < p.h && col_of(mi, j) + lane_col < p.w; };
-  auto base_of = [&](int mi, int j) -> int { return (row_of(mi, j) * p.w + col_of(mi, j)) * p.cout + co_w; };
+  auto base_of = [&](int mi, int j) -> int { return vector_base(row_of(mi, j), col_of(mi, j), p.h, p.w, p.cout, co_w); };
   // residual vectors are requested ahead so that their latency hides behind the LDS round trips of the tiles before
   constexpr int RD = NI == 1 && MI <= 4 ? MI : 2;
   u32x4 rv[RD][VPL];
   auto request = [&](int mi) {
 #pragma unroll
     for (int j = 0; j < VPL; ++j)
-      rv[mi % RD][j] = __builtin_amdgcn_raw_buffer_load_b128(p.res, (int)((inside(mi, j) ? lane_off : OUTSIDE) * sizeof(T)), base_of(mi, j) * (int)sizeof(T), 0);
+      rv[mi % RD][j] = __builtin_amdgcn_raw_buffer_load_b128(p.res, (int)((inside(mi, j) ? lane_off : kOutside) * sizeof(T)), base_of(mi, j) * (int)sizeof(T), 0);
   };
   if constexpr (RES) {
 #pragma unroll
@@ -200,7 +199,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
       // type), which is what the consumer of the tensor normalises
       u32x4 packed;
       if constexpr (sizeof(TO) == 2) packed = u32x4{pack2<T>(v[0], v[1]), pack2<T>(v[2], v[3]), pack2<T>(v[4], v[5]), pack2<T>(v[6], v[7])};
-      const int at = (int)((ok ? lane_off : OUTSIDE) * sizeof(TO)), base = base_of(mi, j) * (int)sizeof(TO);
+      const int at = (int)((ok ? lane_off : kOutside) * sizeof(TO)), base = base_of(mi, j) * (int)sizeof(TO);
       if constexpr (sizeof(TO) == 4) {
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), p.y, at, base, 0);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[4], v[5], v[6], v[7]}), p.y, at + 16, base, 0);
@@ -979,7 +978,7 @@ bool conv_mfma_supported(const ConvArgs& a) {
   if (a.cin > 2048) return false;   // scale/shift table lives in LDS
   if (a.ksize != 1 && a.ksize != 3) return false;
   if (!packed_offsets_fit(a.ksize * a.ksize, a.cout, a.cin, a.op_dtype) || !packed_offsets_fit(1, a.cout, a.cin2, a.op_dtype)) return false;
-  if ((long)a.h * a.w * a.cin >= (1L << 29) || (long)a.h * a.w * a.cout >= (1L << 29)) return false;   // 32-bit byte offsets per sample
+  if ((long)a.h * a.w * a.cin >= (long)kOutside || (long)a.h * a.w * a.cout >= (long)kOutside) return false;   // 32-bit byte offsets per sample
   return true;
 }
 

@@ -4,8 +4,11 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <initializer_list>
+
 #include "wmdec.h"
 #include "wmdec_measure.h"
+#include "sample_offsets.hpp"
 
 static int fails = 0;
 #define CHECK(cond) do { if (!(cond)) { printf("host_sanitize_check: failed: %s (line %d): %s\n", #cond, __LINE__, wmdec_last_error()); ++fails; } } while (0)
@@ -55,7 +58,31 @@ static void exercise(const wmdec_decoder_config& cfg) {
   CHECK(decoder_destroy(dec) == WMDEC_OK);
 }
 
+// Offsets of an epilogue in the largest samples that the matrix-core kernels take (fewer than 2^29 elements): every position a
+// tile can ask for, overhang included, has an offset that fits 32 bits (the sanitizer watches the arithmetic itself).
+static void check_sample_offsets() {
+  const int shapes[][3] = {{1, 4194303, 128}, {1, 8388607, 64}, {2, 2097151, 128}, {3, 1398101, 128}, {2046, 2049, 128}, {2047, 2048, 128},
+                           {4194303, 1, 128}, {4194303, 2, 64}, {65535, 64, 128}, {9, 29127, 2048}, {1, 262143, 2048}, {1, 1, 64}};
+  for (const auto& s : shapes) {
+    const long h = s[0], w = s[1], c = s[2], elems = h * w * c;
+    CHECK(elems < (long)wmdec::kOutside);
+    const long rows[] = {0, h / 8 * 8, h - 1, h, h + 1, (h + 7) / 8 * 8 - 1}, cols[] = {0, w / 32 * 32, w - 1, w, w + 5, (w + 31) / 32 * 32 - 1};
+    for (long row : rows)
+      for (long col : cols)
+        for (long co : {0L, c - 32}) {
+          const int base = wmdec::vector_base((int)row, (int)col, (int)h, (int)w, (int)c, (int)co);
+          CHECK(base >= 0 && base < elems);
+          if (row < h && col < w) { CHECK(base == (row * w + col) * c + co); }
+          for (long bytes : {2L, 4L}) {
+            CHECK(base * bytes < (1L << 31) && base * bytes + (long)wmdec::kOutside * bytes + 16 < (1L << 32));
+            CHECK((long)wmdec::kOutside * bytes >= elems * bytes);   // dropped, with or without the base in the range check
+          }
+        }
+  }
+}
+
 int main() {
+  check_sample_offsets();
   wmdec_decoder_config cfg;
   decoder_default_config(&cfg);
   exercise(cfg);
