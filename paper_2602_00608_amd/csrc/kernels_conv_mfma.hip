@@ -91,7 +91,6 @@ constexpr int patch_floats(int ni) { return 2 * 32 * (ni * 32 + 4); }
 template <int APART> constexpr int apart_row(int mi) { return mi / APART * 2 * APART + mi % APART; }
 
 struct EpilogueParams {
-  const float* bias; const float* bias2;   // added here where the accumulators did not start with them (BIAS)
   __amdgpu_buffer_rsrc_t res, y;           // the sample's residual and output, with its size: accesses outside are dropped
   void* planar;                            // the sample's output where it is planar
   int h, w, cout;
@@ -104,15 +103,17 @@ struct EpilogueParams {
 // go through wavefront-private LDS patches, one 32-pixel M tile at a time and the next one's values on their way to the other
 // patch, and come back as rows of 8 consecutive channels per lane, so that residual and output move as 16-byte vectors and every
 // pixel's channel run is written contiguously.  LDS operations of one wavefront execute in order: no barrier.
+// The bias (of the lane's channel columns) is added to the finished sums, on their way to LDS: accumulators that start from it
+// round every partial sum at its exponent, an error of 4e-7 of the result against 3e-8 where the bias is many times the sum.
 // Residual and output are accessed through buffers with a lane offset that is the same for all vectors, or past the end for
 // pixels outside the image, and the vector's position in a scalar register: no address arithmetic, no masks.
 // Moments: one triple per group for all M tiles, or (kRows4) for every two of them, four rows of 16 pixels.  kQuarters (NI = 1):
 // one for each M tile of 4 x 8 pixels, from the values written back to the patches of a pair: a lane walks one channel
 // of either tile, as the kernel that it reproduces does.
 // APART: row distance of an M tile's two halves where they are not neighbours (see mfma_chunk_rows), otherwise 0.
-template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, int APART, bool RES, int MODE, bool BIAS>
-__device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], float* wave_lds, int lane, int mt0, int ty0,
-                                               int tx0, int co_w, const EpilogueParams& p) {
+template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, int APART, bool RES, int MODE>
+__device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], const float (&bias)[NI], float* wave_lds, int lane, int mt0,
+                                               int ty0, int tx0, int co_w, const EpilogueParams& p) {
   constexpr int RW = NI * 32 + 4;       // padded row of a patch, floats
   constexpr bool PAIRS = MODE == kQuarters;
   constexpr int EMIT = MODE == kRows4 ? 2 : MI;   // M tiles of a triple
@@ -121,7 +122,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) patch[(8 * (r / 4) + 4 * lk + (r % 4)) * RW + ni * 32 + lm] = acc[mi][ni][r];
+      for (int r = 0; r < 16; ++r) patch[(8 * (r / 4) + 4 * lk + (r % 4)) * RW + ni * 32 + lm] = acc[mi][ni][r] + bias[ni];
   };
   if (p.nchw) {
     // planar output with few channels (the frame): a lane owns one pixel of the M tile and walks the
@@ -144,11 +145,6 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
   const int cvec = lane % (NI * 4);     // which 8-channel vector of the row this lane reads back
   const int prow = lane / (NI * 4);     // first pixel it reads; the others are prow + j * STEP
   const int lane_row = prow / MTW, lane_col = prow % MTW;
-  float bv[8];
-  if constexpr (BIAS) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) bv[e] = (p.bias ? p.bias[co_w + cvec * 8 + e] : 0.f) + (p.bias2 ? p.bias2[co_w + cvec * 8 + e] : 0.f);
-  }
   // elements: the lane's part, and that of vector j of M tile mi
   const unsigned lane_off = (unsigned)((lane_row * p.w + lane_col) * p.cout + cvec * 8);
   static_assert(APART == 0 || (MTW == 16 && STEP <= 16 && MT_PER_ROW == 1), "the lanes of a vector are in one row");
@@ -185,10 +181,6 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], floa
       const f32x4 lo = *reinterpret_cast<const f32x4*>(lds + pi * RW + cvec * 8);
       const f32x4 hi = *reinterpret_cast<const f32x4*>(lds + pi * RW + cvec * 8 + 4);
       float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      if constexpr (BIAS) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] += bv[e];
-      }
       if constexpr (RES) {
         float rf[8];
         unpack8<T>(rv[mi % RD][j], rf);
@@ -486,19 +478,19 @@ void conv_mfma_kernel(MfmaParams p) {
   const int ty0 = (tile / p.tiles_x) * TH, tx0 = (tile % p.tiles_x) * TW;
   const int co0 = nt * TN;
 
-  // The accumulators start with the bias of their channel column (requested first; QUARTERS has to add it last, as the kernel
-  // that it reproduces)
-  constexpr bool BIAS_LAST = QUARTERS;
-  float start[NI];
+  // the bias of the lane's channel columns, for the epilogue: requested here, as a load there would be waited for, unless the
+  // main loop has no register left to hold it
+  constexpr bool BIAS_EARLY = !(QUARTERS || (MODE == kRows4 && RING == 0));
+  float bias[NI];
+  auto load_bias = [&]() {
 #pragma unroll
-  for (int ni = 0; ni < NI; ++ni) {
-    start[ni] = 0.f;
-    if constexpr (!BIAS_LAST) {
+    for (int ni = 0; ni < NI; ++ni) {
       const int co = min(co0 + (wn * NI + ni) * 32 + lm, p.cout - 1);   // (the frame has fewer channels than the tile)
-      if (p.bias) start[ni] = p.bias[co];
-      if (p.bias2) start[ni] += p.bias2[co];
+      bias[ni] = p.bias ? p.bias[co] : 0.f;
+      if (p.bias2) bias[ni] += p.bias2[co];
     }
-  }
+  };
+  if constexpr (BIAS_EARLY) load_bias();
 
   // LDS element offset of this lane's pixel in each of its M tiles (tap (0,0), k offset of the lane half)
   int a_off[MI];
@@ -628,12 +620,14 @@ void conv_mfma_kernel(MfmaParams p) {
   constexpr int SPREAD = (ACT == 0 || MI * NI > 4) ? -1 : (SPREAD_AVG > 1 ? SPREAD_AVG - 1 : 1);
   f32x4 abv[2];   // table entries of the part being activated and of the next one (sliced activation)
 
+  float zero = 0.f;
+  asm volatile("" : "+v"(zero));   // (seen as a constant, it costs the fullest of these kernels 190 spilled registers)
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = start[j];
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = zero;
   // ---- shortcut phase (3x3 kernels with a second input): acc = W2 * x2 over the tile's own pixels, a 1x1
   // contraction over cin2 channels taken as stored (no normalisation).  Chunks of KC channels go through the same
   // two LDS buffers with the tile's halo layout (only the centre tap is read), loads two chunks ahead; the main
@@ -800,7 +794,8 @@ void conv_mfma_kernel(MfmaParams p) {
     __syncthreads();          // other buffer staged; this one free for chunk c+2
   }
 
-  // ---- epilogue: residual, one rounding, store (through wavefront-private LDS patches over the tile buffers)
+  // ---- epilogue: bias, residual, one rounding, store (through wavefront-private LDS patches over the tile buffers)
+  if constexpr (!BIAS_EARLY) load_bias();
   constexpr bool BLOCKS = MODE != kPlain;
   float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(NI);
   // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row], or by blocks of 4 rows x 16 or 8 pixels
@@ -815,12 +810,12 @@ void conv_mfma_kernel(MfmaParams p) {
     const char* res = reinterpret_cast<const char*>(p.res) + (size_t)n * elems * sizeof(T);
     ep.res = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(res), 0, (int)(elems * sizeof(T)), 0x00020000);
   }
-  ep.bias = p.bias; ep.bias2 = p.bias2; ep.h = p.h; ep.w = p.w_out; ep.cout = p.cout; ep.nchw = p.y_nchw != 0 && !p.res;
+  ep.h = p.h; ep.w = p.w_out; ep.cout = p.cout; ep.nchw = p.y_nchw != 0 && !p.res;
   ep.stats = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + slot : nullptr;
   ep.cpg = p.stats_cpg; ep.stats_stride = p.stats_slots; ep.pair_stride = per_row; ep.handed_over = p.rows_out != nullptr;
   auto store = [&](const f32x16 (&sums)[MI][NI]) {
-    if (p.res) epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, APART, true, MODE, BIAS_LAST>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
-    else epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, APART, false, MODE, BIAS_LAST>(sums, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
+    if (p.res) epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, APART, true, MODE>(sums, bias, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
+    else epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, APART, false, MODE>(sums, bias, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
   };
   if constexpr (QUARTERS) store(total);
   else store(acc);

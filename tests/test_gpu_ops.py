@@ -265,6 +265,34 @@ def test_conv_of_single_taps_is_an_exact_displacement(dtype, n, cin, cout, h, w)
     assert torch.equal(y.cpu(), want)
 
 
+# A bias forty times the sums, fp32 output: the bias meets finished sums.  Bound on the rms error over half a million outputs or
+# more: that one addition rounds by ulp / sqrt(12) of the result in the mean, and the steps of the sums (16 products each) by at
+# most 2^-23, truncation included, of partial sums of rms 1, independently of each other.  Sums that start from the bias round
+# every step by ulp / sqrt(12) of the result: over five times as much at the least count of steps here with a tile of that kind (16).
+@pytest.mark.parametrize("k,n,cin,cout,h,w", [(3, 1, 64, 64, 130, 131), (3, 1, 64, 128, 97, 99), (3, 1, 32, 256, 256, 257), (3, 1, 64, 512, 64, 61),
+                                              (3, 2, 64, 512, 64, 61), (3, 1, 256, 512, 17, 23), (3, 16, 64, 128, 40, 41),
+                                              (1, 1, 512, 64, 90, 91), (1, 1, 512, 128, 64, 65), (1, 1, 256, 128, 363, 363), (1, 1, 288, 192, 64, 65)])
+def test_conv_adds_a_large_bias_to_finished_sums(k, n, cin, cout, h, w):
+    r = rng(22)
+    x = torch.from_numpy(r.standard_normal((n, h, w, cin)).astype(np.float32)).to(torch.float16)
+    wt = G.stored(r.standard_normal((cout, cin, k, k)) / np.sqrt(k * k * cin), "f16")
+    b = (r.choice([-1.0, 1.0], cout) * r.uniform(40, 60, cout)).astype(np.float32)
+    y = torch.empty((n, h, w, cout), dtype=torch.float32, device="cuda")
+    fn = wmdec.gn_silu_conv3x3 if k == 3 else wmdec.gn_conv1x1
+    fn(x.cuda(), None, None, None, None, 32, False, G.pack(wt, "f16"), G.dev_f32(b), None, y)
+    padded, taps = x.double(), torch.from_numpy(wt).double().permute(2, 3, 1, 0)
+    if k == 3:
+        padded = torch.nn.functional.pad(padded, (0, 0, 1, 1, 1, 1))
+    want = torch.zeros((n, h, w, cout), dtype=torch.float64) + torch.from_numpy(b).double()
+    for ky in range(k):
+        for kx in range(k):
+            want += padded[:, ky:ky + h, kx:kx + w].reshape(-1, cin).matmul(taps[ky, kx]).view(n, h, w, cout)
+    ulp = np.spacing(np.abs(want.numpy()).astype(np.float32)).astype(np.float64)
+    bound = float(np.sqrt(np.mean(ulp ** 2) / 12 + k * k * cin / 16 * 2.0 ** -46))
+    err = float((y.cpu().double() - want).square().mean().sqrt())
+    assert err <= bound, (err, bound)
+
+
 # moments of a convolution's own output from its epilogue: one case per tile shape of the matrix-core kernel
 @pytest.mark.parametrize("dtype,ydtype,n,cin,cout,h,w,residual", [
     ("f16", "f16", 1, 128, 128, 40, 56, True),      # 128 x 128 tile, wavefronts 2x2
