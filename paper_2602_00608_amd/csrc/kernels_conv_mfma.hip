@@ -84,8 +84,13 @@ __device__ __forceinline__ void emit_moments(const LaneMoments& st, int lane, in
   }
 }
 
-// floats of the wavefront-private epilogue patches: two of 32 padded rows
-constexpr int patch_floats(int ni) { return 2 * 32 * (ni * 32 + 4); }
+// Wavefront-private epilogue patches of 32 padded rows: a second one, for the next M tile's values, where there is a next M tile
+// and the workgroups that the registers allow still fit the LDS with it (four of 36.9 KB with one channel tile a wavefront, two of
+// 69.6 KB with two of them and eight accumulator tiles).  A third and fourth workgroup are worth more than the patch: one / two
+// patches, us, 3x3 64 -> 64 at 240x360 14.1 / 15.6, at 480x720 48.0 / 51.3; 1x1 512 -> 1536 at 60x90 21.6 / 23.7, 256 -> 64 at 240x360
+// 13.3 / 15.7.
+constexpr int epilogue_patches(int mi, int ni) { return mi > 1 && (ni == 1 || mi * ni > 4) ? 2 : 1; }
+constexpr int patch_floats(int mi, int ni) { return epilogue_patches(mi, ni) * 32 * (ni * 32 + 4); }
 
 // first row of M tile mi of a wavefront whose M tiles are rows r and r + APART (blocks of 2 APART rows)
 template <int APART> constexpr int apart_row(int mi) { return mi / APART * 2 * APART + mi % APART; }
@@ -100,8 +105,8 @@ struct EpilogueParams {
 };
 
 // Epilogue of one wavefront: its MI x NI accumulator tiles (32 pixels x 32 channels each, a lane holding one channel column)
-// go through wavefront-private LDS patches, one 32-pixel M tile at a time and the next one's values on their way to the other
-// patch, and come back as rows of 8 consecutive channels per lane, so that residual and output move as 16-byte vectors and every
+// go through wavefront-private LDS patches, one 32-pixel M tile at a time (the next one's values on their way to the other patch,
+// where there are two), and come back as rows of 8 consecutive channels per lane, so that residual and output move as 16-byte vectors and every
 // pixel's channel run is written contiguously.  LDS operations of one wavefront execute in order: no barrier.
 // The bias (of the lane's channel columns) is added to the finished sums, on their way to LDS: accumulators that start from it
 // round every partial sum at its exponent, an error of 4e-7 of the result against 3e-8 where the bias is many times the sum.
@@ -116,6 +121,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
                                                int ty0, int tx0, int co_w, const EpilogueParams& p) {
   constexpr int RW = NI * 32 + 4;       // padded row of a patch, floats
   constexpr bool PAIRS = MODE == kQuarters;
+  constexpr int PATCHES = epilogue_patches(MI, NI);
   constexpr int EMIT = MODE == kRows4 ? 2 : MI;   // M tiles of a triple
   const int lm = lane & 31, lk = lane >> 5;
   auto put = [&](float* patch, int mi) {
@@ -171,9 +177,9 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
   put(wave_lds, 0);
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
-    float* lds = wave_lds + (mi & 1) * 32 * RW;
-    const bool ahead = mi + 1 < MI && !(PAIRS && mi % 2 == 1);   // (a pair's patches are read once more at its end)
-    if (ahead) put(wave_lds + ((mi + 1) & 1) * 32 * RW, mi + 1);
+    float* lds = wave_lds + mi % PATCHES * 32 * RW;
+    const bool ahead = PATCHES == 2 && mi + 1 < MI && !(PAIRS && mi % 2 == 1);   // (a pair's patches are read once more at its end)
+    if (ahead) put(wave_lds + (mi + 1) % PATCHES * 32 * RW, mi + 1);
 #pragma unroll
     for (int j = 0; j < VPL; ++j) {
       const int pi = prow + j * STEP;
@@ -229,7 +235,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
       if (mi + RD < MI) request(mi + RD);
     }
     if constexpr (PAIRS) {
-      static_assert(NI == 1 && MI % 2 == 0 && MTW == 8 && MTH == 4 && MT_PER_ROW == 2, "a pair is four rows of 16 pixels");
+      static_assert(NI == 1 && PATCHES == 2 && MI % 2 == 0 && MTW == 8 && MTH == 4 && MT_PER_ROW == 2, "a pair is four rows of 16 pixels");
       if (mi % 2 == 1 && p.stats) {   // lanes 0-31: a channel of the pair's first tile, lanes 32-63: of the second
         Moments* dst = p.stats + (mi / 2) * p.pair_stride;
         const int y0 = ty0 + (mt0 + mi - 1 + lk) / MT_PER_ROW * MTH, x0 = tx0 + (mt0 + mi - 1 + lk) % MT_PER_ROW * MTW;
@@ -240,7 +246,6 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
         m = merge_to_first(m, lane, p.cpg);
         if ((lm & (p.cpg - 1)) == 0 && m.n > 0.f) dst[(size_t)((co_w + lm) / p.cpg) * p.stats_stride + lk] = m;
       }
-      if (mi + 1 < MI && !ahead) put(wave_lds + ((mi + 1) & 1) * 32 * RW, mi + 1);
     } else if ((mi + 1) % EMIT == 0) {
       // (kRows4: rows past the image have no slot)
       if (p.stats && (MODE != kRows4 || row_of(mi + 1 - EMIT, 0) < p.h)) {
@@ -251,6 +256,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
         else emit_moments<NI * 4, 8>(st, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
       }
     }
+    if (mi + 1 < MI && !ahead) put(wave_lds + (mi + 1) % PATCHES * 32 * RW, mi + 1);
   }
 }
 
@@ -454,6 +460,8 @@ void conv_mfma_kernel(MfmaParams p) {
   constexpr bool SLICED = KS == 3;               // activation of the next chunk is sliced into the MFMA sweep
   constexpr int APART = rows_apart(TW, WM, MI, KS, MODE);   // see mfma_chunk_rows; 0: M tiles of neighbouring rows
   static_assert(NT % VPP == 0, "a thread keeps one channel octet");
+  static_assert((RING > 6 ? 2 : resident_workgroups(MI * NI, WM, WN)) * WM * WN * patch_floats(MI, NI) * sizeof(float) <= 160 * 1024,
+                "the workgroups that the registers are budgeted for fit the LDS of a compute unit");
 
   extern __shared__ __align__(16) unsigned char smem[];
   T* s_a = reinterpret_cast<T*>(smem);                                          // [2][BUF]
@@ -797,7 +805,7 @@ void conv_mfma_kernel(MfmaParams p) {
   // ---- epilogue: bias, residual, one rounding, store (through wavefront-private LDS patches over the tile buffers)
   if constexpr (!BIAS_EARLY) load_bias();
   constexpr bool BLOCKS = MODE != kPlain;
-  float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(NI);
+  float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(MI, NI);
   // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row], or by blocks of 4 rows x 16 or 8 pixels
   const int per_row = QUARTERS ? (p.w_out + 7) / 8 : p.tiles_x;   // slots of a row of blocks
   const int slot = BLOCKS ? ty0 / 4 * per_row + tx0 / (QUARTERS ? 8 : TW) : tile * WM + wm;
@@ -843,7 +851,7 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
   }
   constexpr int NT = 64 * WM * WN;
   size_t smem = (((size_t)2 * tile_buf_elems(TH, TW, PAD, KC, m_tile_width(TW, MODE)) * 2 + 15) & ~(size_t)15) + (size_t)(a.cin + a.groups) * sizeof(float2);
-  const size_t patch = (size_t)(WM * WN) * patch_floats(NI) * sizeof(float);   // epilogue patches of the wavefronts
+  const size_t patch = (size_t)(WM * WN) * patch_floats(wave_m_tiles(TH, TW, WM), NI) * sizeof(float);   // epilogue patches of the wavefronts
   if (smem < patch) smem = patch;
   WMDEC_REQUIRE(smem <= 80 * 1024, WMDEC_ERR_UNSUPPORTED, "conv_mfma: %zu bytes of LDS needed", smem);
   void (*kern)(MfmaParams) = !p.norm ? conv_mfma_kernel<T, TO, TH, TW, WM, WN, NI, KS, KC, 0, MODE, RING>
