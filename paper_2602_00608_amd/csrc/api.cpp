@@ -351,7 +351,7 @@ static int build_plan(wmdec_decoder& d) {
     f.flops = 4.0 * (double)(h * w) * (double)(h * w) * c0;
     f.flops_dense = f.flops;
     f.bytes = 4.0 * h * w * c0 * dtype_size(c.act_dtype);
-    d.steps.push_back(f); d.launches += 2;
+    d.steps.push_back(f); d.launches += flash_attention_num_launches(h * w);
     d.flops += f.flops;
     d.flops_dense += f.flops_dense;
     Step p; p.kind = Step::CONV; p.to_attn = 2; p.dst = other(1); p.res = cur; p.h = h; p.w = w; p.cin = c0; p.cout = c0; p.ksize = 1;

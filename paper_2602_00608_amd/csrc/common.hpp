@@ -180,7 +180,8 @@ int launch_adaln_projection(const void* c, int c_dtype, const void* w, int w_dty
 
 // kernels_attn.hip: attention over the t tokens of a sample, head dimension 512 (q, k, v in the fragment order described there)
 size_t attention_fragment_bytes(int n, int t);
-size_t flash_attention_scratch_bytes(int n, int t);   // partial outputs of the key ranges
+size_t flash_attention_scratch_bytes(int n, int t);   // partial outputs of the key ranges (none where one range holds all keys)
+int flash_attention_num_launches(int t);
 const char* attention_qkv_label(int dtype);
 // frag = [q|k|v] of act(x) as a describes it: a 1x1 convolution from 512 to 3 * 512 channels over a.h * a.w tokens
 int launch_attention_qkv(const ConvArgs& a, void* frag, hipStream_t s);

@@ -3,7 +3,8 @@
 // Three launches hand over 32-token tiles in MFMA fragment order, so that every one of them loads and stores runs of 1 KiB:
 //   conv_mfma_kernel (here the q/k/v projection)  [q|k|v] = W norm(x) + b, straight from its accumulators into fragments
 //   flash_attn_kernel                             streams the keys, online softmax, unnormalised partial outputs
-//   attn_combine_kernel                           merges the partial outputs of the key ranges, normalises, rows of o
+//   attn_combine_kernel                           merges the partial outputs of the key ranges, normalises, rows of o (where one
+//                                                 range holds all keys, the core writes these rows itself)
 //
 // Fragments (16-bit type T, tile = 32 tokens x 512 = 32 KiB, 32 runs of 64 lanes x 16 bytes), lane = l32 + 32 * lk:
 //   q, k  [step 0..31][lane]     token l32, channels 16 * step + 8 * lk + 0..7: operand of the 32x32x16 MFMA as it is
@@ -248,9 +249,20 @@ template <int I> __device__ __forceinline__ void rescale_tile(f32x16& o, float f
 }
 #undef WMDEC_RESCALE
 
-template <typename T>
+// A lane's 16 channels (8 * (r / 4) + 4 * lk + r % 4) of 32 of its token's, divided by the sum of its probabilities: two runs of eight
+// channels, of which the second is 16 further.
+template <typename T> __device__ __forceinline__ void normalised_runs(const f32x4 (&num)[4], float inv, u32x4& first, u32x4& second) {
+  u32x2 w[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) w[g] = u32x2{pack2<T>(num[g][0] * inv, num[g][1] * inv), pack2<T>(num[g][2] * inv, num[g][3] * inv)};
+  first = join_halves(w[0], w[1]);
+  second = join_halves(w[2], w[3]);
+}
+
+// WHOLE: one range holds all keys, `out` is o; otherwise the partial outputs.
+template <typename T, bool WHOLE>
 __global__ __launch_bounds__(NT, 1) void flash_attn_kernel(const T* __restrict__ qf, const T* __restrict__ kf, const T* __restrict__ vf, size_t sample_stride,
-                                                           float* __restrict__ opart, float* __restrict__ ml, int t, int nqb, int splits, float scale_log2e) {
+                                                           void* __restrict__ out, float* __restrict__ ml, int t, int nqb, int splits, float scale_log2e) {
   extern __shared__ __align__(16) unsigned char smem[];
   T* s_k = reinterpret_cast<T*>(smem);   // [2] tiles of k
   T* s_v = s_k + 2 * TILE;               // [2] tiles of v
@@ -368,6 +380,9 @@ __global__ __launch_bounds__(NT, 1) void flash_attn_kernel(const T* __restrict__
     for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
   unsigned long long moved = 0;
   float factor = 1.f;
+  // (puts the loop where the other form has it, 36 bytes into a line of 64: a wavefront alone on its SIMD waits for its instructions;
+  // 16 770 tokens 965 -> 930 us)
+  if constexpr (WHOLE) asm volatile("s_nop 0\n\ts_nop 0\n\ts_nop 0");
 #pragma unroll 1
   for (int j = 0; j < nb; ++j) {
     // output of block j, with the softmax of block j + 1 and the requests of v of block j + 1 and k of block j + 3 in between
@@ -397,10 +412,29 @@ __global__ __launch_bounds__(NT, 1) void flash_attn_kernel(const T* __restrict__
   }
 
   l_run += __shfl_xor(l_run, 32);
-  if (qt < nkb) {
+  if (qt >= nkb) return;
+  int id = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));   // the lane once more: no register is left to hold it up to here
+  asm volatile("" : "+v"(id));
+  if constexpr (WHOLE) {
+    const float inv = 1.0f / l_run;
+    const int row = qt * KB + (id & 31);
+    T* dst = reinterpret_cast<T*>(out) + ((size_t)n * t + row) * D + (id >> 5) * 8;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const f32x4 num[4] = {{o[i][0], o[i][1], o[i][2], o[i][3]}, {o[i][4], o[i][5], o[i][6], o[i][7]},
+                            {o[i][8], o[i][9], o[i][10], o[i][11]}, {o[i][12], o[i][13], o[i][14], o[i][15]}};
+      u32x4 first, second;
+      normalised_runs<T>(num, inv, first, second);
+      if (row < t) {
+        *reinterpret_cast<u32x4*>(dst + i * 32) = first;
+        *reinterpret_cast<u32x4*>(dst + i * 32 + 16) = second;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
     const size_t row = ((size_t)n * splits + split) * nkb + qt;
-    if (lane < KB) reinterpret_cast<float2*>(ml)[row * KB + lane] = make_float2(m_run, l_run);
-    float* dst = opart + row * TILE + lane * 4;   // [dt][group of 8 channels][lane][4 channels]: what attn_combine_kernel reads
+    if (id < KB) reinterpret_cast<float2*>(ml)[row * KB + id] = make_float2(m_run, l_run);
+    float* dst = reinterpret_cast<float*>(out) + row * TILE + id * 4;   // [dt][group of 8 channels][lane][4 channels]: what attn_combine_kernel reads
 #pragma unroll
     for (int i = 0; i < 16; ++i)
 #pragma unroll
@@ -439,15 +473,13 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
     for (int g = 0; g < 4; ++g) num[g] += w * part[s][g];
   }
   const float inv = 1.0f / den;
-  u32x2 w[4];
-#pragma unroll
-  for (int g = 0; g < 4; ++g) w[g] = u32x2{pack2<T>(num[g][0] * inv, num[g][1] * inv), pack2<T>(num[g][2] * inv, num[g][3] * inv)};
-  const u32x4 v0 = join_halves(w[0], w[1]), v1 = join_halves(w[2], w[3]);
+  u32x4 first, second;
+  normalised_runs<T>(num, inv, first, second);
   const int row = tile * KB + l32;
   if (row >= t) return;
   T* dst = o + ((size_t)n * t + row) * D + dt * 32 + lk * 8;
-  *reinterpret_cast<u32x4*>(dst) = v0;
-  *reinterpret_cast<u32x4*>(dst + 16) = v1;
+  *reinterpret_cast<u32x4*>(dst) = first;
+  *reinterpret_cast<u32x4*>(dst + 16) = second;
 }
 
 constexpr int kMaxSplits = 8;
@@ -460,7 +492,7 @@ int splits_of(int t) {
   return max(1, min(min(256 / nqb, kMaxSplits), (nkb + 1) / 2));
 }
 
-template <typename T, int S>
+template <typename T, int S = 2>
 void combine(const float* opart, const float* ml, T* o, int n, int t, int splits, hipStream_t s) {
   if constexpr (S <= kMaxSplits) {
     if (splits == S) hipLaunchKernelGGL((attn_combine_kernel<T, S>), dim3((unsigned)tiles_of(t), D / 128, (unsigned)n), dim3(256), 0, s, opart, ml, o, t, tiles_of(t));
@@ -468,21 +500,21 @@ void combine(const float* opart, const float* ml, T* o, int n, int t, int splits
   }
 }
 
-template <typename T>
+template <typename T, bool WHOLE>
 int launch_flash(const void* frag, void* o, void* scratch, int n, int t, float scale, hipStream_t s) {
   const int splits = splits_of(t), nkb = tiles_of(t), nqb = (nkb + 3) / 4;
   const size_t per = (size_t)nkb * TILE;
   const T* q = (const T*)frag;
   float* opart = (float*)scratch;
-  float* ml = opart + (size_t)n * splits * per;
+  float* ml = WHOLE ? nullptr : opart + (size_t)n * splits * per;
   static std::once_flag attr_once;
   hipError_t attr_err = hipSuccess;
-  std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)flash_attn_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmemBytes); });
+  std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)flash_attn_kernel<T, WHOLE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmemBytes); });
   WMDEC_HIP(attr_err);
-  hipLaunchKernelGGL(flash_attn_kernel<T>, dim3((unsigned)(nqb * splits * n)), dim3(NT), kSmemBytes, s, q, q + n * per, q + 2 * n * per, per, opart, ml, t, nqb,
-                     splits, scale * 1.4426950408889634f);
+  hipLaunchKernelGGL((flash_attn_kernel<T, WHOLE>), dim3((unsigned)(nqb * splits * n)), dim3(NT), kSmemBytes, s, q, q + n * per, q + 2 * n * per, per,
+                     WHOLE ? o : scratch, ml, t, nqb, splits, scale * 1.4426950408889634f);
   WMDEC_HIP(hipGetLastError());
-  combine<T, 1>(opart, ml, (T*)o, n, t, splits, s);
+  if (!WHOLE) combine<T>(opart, ml, (T*)o, n, t, splits, s);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
 }
@@ -509,7 +541,9 @@ int launch_qkv_t(const ConvArgs& a, void* frag, hipStream_t s) {
 
 size_t attention_fragment_bytes(int n, int t) { return (size_t)n * 3 * tiles_of(t) * TILE * 2; }
 
-size_t flash_attention_scratch_bytes(int n, int t) { return (size_t)n * splits_of(t) * tiles_of(t) * KB * (D + 2) * sizeof(float); }
+size_t flash_attention_scratch_bytes(int n, int t) { return splits_of(t) == 1 ? 0 : (size_t)n * splits_of(t) * tiles_of(t) * KB * (D + 2) * sizeof(float); }
+
+int flash_attention_num_launches(int t) { return splits_of(t) == 1 ? 1 : 2; }
 
 const char* attention_qkv_label(int dtype) { return dtype == WMDEC_BF16 ? "conv_mfma_kernel<wmdec::bf16_t, 1>" : "conv_mfma_kernel<wmdec::f16_t, 1>"; }
 
@@ -522,8 +556,9 @@ int launch_attention_qkv(const ConvArgs& a, void* frag, hipStream_t s) {
 }
 
 int launch_flash_attention(const void* frag, void* o, void* scratch, int dtype, int n, int t, float scale, hipStream_t s) {
-  WMDEC_REQUIRE(is_16bit(dtype) && n > 0 && t > 0 && frag && o && scratch, WMDEC_ERR_INVALID_ARG, "attention: bad arguments");
-  return dtype == WMDEC_BF16 ? launch_flash<bf16_t>(frag, o, scratch, n, t, scale, s) : launch_flash<f16_t>(frag, o, scratch, n, t, scale, s);
+  WMDEC_REQUIRE(is_16bit(dtype) && n > 0 && t > 0 && frag && o && (scratch || splits_of(t) == 1), WMDEC_ERR_INVALID_ARG, "attention: bad arguments");
+  if (splits_of(t) == 1) return dtype == WMDEC_BF16 ? launch_flash<bf16_t, true>(frag, o, scratch, n, t, scale, s) : launch_flash<f16_t, true>(frag, o, scratch, n, t, scale, s);
+  return dtype == WMDEC_BF16 ? launch_flash<bf16_t, false>(frag, o, scratch, n, t, scale, s) : launch_flash<f16_t, false>(frag, o, scratch, n, t, scale, s);
 }
 
 }  // namespace wmdec

@@ -126,6 +126,19 @@ def test_step_accounting_adds_up():
     dec.close()
 
 
+def test_attention_scratch_holds_partial_outputs_only_where_keys_are_split():
+    """Fragments of q, k, v (tiles of 32 tokens) and o; from 16 385 tokens on, and up to 64, one range holds all keys and nothing else is needed."""
+    for n, h, w in ((1, 129, 130), (2, 1, 16385), (1, 200, 200), (1, 8, 8), (3, 1, 1)):
+        t, tiles = h * w, (h * w + 31) // 32
+        assert wmdec.attention_workspace_bytes(n, h, w, 512) == sum((b + 255) // 256 * 256 for b in (n * 3 * tiles * 32 * 512 * 2, n * t * 512 * 2)), (n, h, w)
+    for n, h, w in ((1, 1, 65), (1, 60, 90), (2, 128, 128)):
+        t, tiles = h * w, (h * w + 31) // 32
+        splits = max(1, min(256 // ((tiles + 3) // 4), 8, (tiles + 1) // 2))
+        assert splits > 1
+        want = sum((b + 255) // 256 * 256 for b in (n * 3 * tiles * 32 * 512 * 2, n * t * 512 * 2, n * splits * tiles * 32 * 514 * 4))
+        assert wmdec.attention_workspace_bytes(n, h, w, 512) == want, (n, h, w)
+
+
 def test_layers_whose_packed_weights_pass_32_bit_offsets_take_the_general_kernel():
     """9 * cin * cout * 2 bytes of weights from 2^31 on: no matrix-core kernel may take the layer (their fragment offsets and
     buffer sizes have 32 bits).  Only the dispatch is asked; nothing of that size is allocated."""

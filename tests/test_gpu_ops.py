@@ -569,6 +569,35 @@ def test_attention_tile_edges(dtype, n, h, w):
     assert ref.rel_err(got - x, want - x) <= branch_tolerance(dtype, want, x)
 
 
+@pytest.mark.parametrize("dtype,n,h,w", [("f16", 1, 113, 146), ("bf16", 2, 1, 16411)])
+def test_attention_long_sequence_in_one_range_of_keys(dtype, n, h, w):
+    """Sequences whose blocks of queries fill the chip by themselves: one range holds all keys and the core writes o itself.  64
+    tokens of the last sample, its first and last among them, against 64 bits."""
+    c, t, r = 512, h * w, rng(25)
+    x = torch.from_numpy(r.standard_normal((n, h, w, c)).astype(np.float32)).to(G.TORCH[dtype])
+    wts = {m: G.stored(r.standard_normal((c, c)) / np.sqrt(c), dtype) for m in "qkvo"}
+    b = {m: (0.05 * r.standard_normal(c)).astype(np.float32) for m in "qkvo"}
+    gamma, beta = (1 + 0.2 * r.standard_normal(c)).astype(np.float32), (0.2 * r.standard_normal(c)).astype(np.float32)
+    mean, rstd = (0.1 * r.standard_normal(n * 32)).astype(np.float32), (1 + 0.1 * r.standard_normal(n * 32)).astype(np.float32)
+    ws = torch.empty(wmdec.attention_workspace_bytes(n, h, w, c), dtype=torch.uint8, device="cuda")
+    y, check = G.canaried((n, h, w, c), G.TORCH[dtype])
+    four = lambda a: np.ascontiguousarray(a[:, :, None, None])
+    wmdec.attention(x.cuda(), G.dev_f32(mean), G.dev_f32(rstd), G.dev_f32(gamma), G.dev_f32(beta), 32,
+                    G.pack(four(np.concatenate([wts["q"], wts["k"], wts["v"]])), dtype), G.dev_f32(np.concatenate([b["q"], b["k"], b["v"]])),
+                    G.pack(four(wts["o"]), dtype), G.dev_f32(b["o"]), y, ws)
+    torch.cuda.synchronize()
+    check()
+    d = lambda a: torch.from_numpy(np.asarray(a)).double()
+    xs = x[-1].reshape(t, c).double()
+    hn = (xs - d(mean[-32:]).repeat_interleave(16)) * d(rstd[-32:]).repeat_interleave(16) * d(gamma) + d(beta)
+    at = torch.from_numpy(np.concatenate([[0, 31, 32, t - 2, t - 1], r.integers(0, t, 59)]))
+    proj = lambda m, v: v @ d(wts[m]).T + d(b[m])
+    o = torch.softmax(proj("q", hn[at]) @ proj("k", hn).T / math.sqrt(c), 1) @ proj("v", hn)
+    want, got = (xs[at] + proj("o", o)).numpy(), y[-1].reshape(t, c).cpu()[at].double().numpy()
+    assert ref.rel_err(got, want) <= G.TOL[dtype]
+    assert ref.rel_err(got - xs[at].numpy(), want - xs[at].numpy()) <= branch_tolerance(dtype, want, xs[at].numpy())
+
+
 def test_attention_reference_moves_inside_a_key_range():
     """Logits of standard deviation 9 (13 in powers of two) over eight ranges of 256 keys: the maximum of a range lies about
     0.8 standard deviations above that of its first 32 keys, so that most queries cross the slack of 2^8 behind the
