@@ -4,6 +4,11 @@ import os
 import subprocess
 import sys
 
+if __package__:
+    from . import asm_check
+else:
+    import asm_check
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
@@ -11,6 +16,9 @@ LIB = os.path.join(HERE, "libwmdec.so")
 
 SOURCES = ["api.cpp", "kernels_gn.hip", "kernels_conv_direct.hip", "kernels_conv_mfma.hip", "kernels_conv_ksplit.hip", "kernels_conv_up.hip",
            "kernels_conv_taps.hip", "kernels_misc.hip", "kernels_attn.hip", "kernels_adaln.hip"]
+
+# kernels with matrix instructions in inline assembly, whose code asm_check reads: source -> kernel
+CHECKED = {"kernels_attn.hip": "flash_attn_kernel"}
 
 FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -26,6 +34,14 @@ def _headers_mtime():
     return m
 
 
+def device_assembly(src):
+    """The device assembly that the flags of the build make of a source file."""
+    r = subprocess.run(["hipcc"] + FLAGS + ["-S", "--cuda-device-only", os.path.join(CSRC, src), "-o", "-"], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("hipcc failed for %s:\n%s" % (src, r.stderr))
+    return r.stdout
+
+
 def _compile(src, force):
     obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
     path = os.path.join(CSRC, src)
@@ -39,6 +55,11 @@ def _compile(src, force):
         raise RuntimeError("hipcc failed for %s:\n%s" % (src, out))
     if out.strip():
         sys.stderr.write(out + "\n")
+    if src in CHECKED:
+        faults = asm_check.check(device_assembly(src), CHECKED[src])
+        if faults:
+            os.remove(obj)
+            raise RuntimeError("%s: the compiled code breaks what its inline assembly relies on:\n%s" % (src, "\n".join(faults)))
     return obj
 
 

@@ -220,7 +220,8 @@ __device__ __forceinline__ float half_max(float v) {
 // register file; its query fragments are 128 of the other half.  The compiler gives every MFMA of a kernel its result in the
 // accumulation half, which the scores' 16 registers would overflow (336 registers spilled); so the scores' MFMAs are written
 // out, with the result in the other half.  The compiler does not see them as MFMAs: settle_scores() is the wait before
-// their result is read (11 wait states are due behind a 32x32x16 MFMA).  Nor does it keep the accumulators in place where a
+// their result is read (11 wait states are due behind a 32x32x16 MFMA), and the build fails where the compiler touches one earlier or
+// spills (asm_check.py).  Nor does it keep the accumulators in place where a
 // branch multiplies them (234 spilled): rescale_tile is one statement per tile that names the tile's registers and jumps to
 // the multiplications, out of line, only if a lane's reference has moved.
 template <typename T> __device__ __forceinline__ void score_first(f32x16& s, const u32x4& k, const u32x4& q) {
