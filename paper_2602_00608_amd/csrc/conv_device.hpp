@@ -7,6 +7,7 @@
 #include "mfma.hpp"
 #include "moments.hpp"
 #include "pack_layout.hpp"
+#include "quotient.hpp"
 #include "sample_offsets.hpp"
 
 namespace wmdec {
@@ -157,7 +158,7 @@ template <int W, int ROW, int PX> __device__ __forceinline__ Sums two_row_sums(c
 }
 __device__ __forceinline__ Moments block_moments(Sums t, float shift, int rows, int cols) {
   if (rows <= 0 || cols <= 0) return Moments{0.f, 0.f, 0.f};
-  const float cnt = (float)(rows * cols), ds = t.s * __builtin_amdgcn_rcpf(cnt), m2 = t.q - t.s * ds;   // 1 ulp of a difference to the shift
+  const float cnt = (float)(rows * cols), ds = quotient(t.s, cnt, __builtin_amdgcn_rcpf(cnt)), m2 = t.q - t.s * ds;
   return Moments{cnt, shift + ds, m2 < 0.f ? 0.f : m2};
 }
 

@@ -54,15 +54,15 @@ __device__ __forceinline__ void emit_moments(const LaneMoments& st, int lane, in
     if (cpg > 16) v += quad_xor<2>(v);
     return v;
   };
-  const float inv = st.n > 0.f ? __builtin_amdgcn_rcpf(st.n) : 0.f;   // 1 ulp of a difference to the shift
-  const float n = lanes(st.n), ninv = n > 0.f ? __builtin_amdgcn_rcpf(n) : 0.f;
+  const float inv = st.n > 0.f ? __builtin_amdgcn_rcpf(st.n) : 0.f;
+  const float n = lanes(st.n), ninv = n > 0.f ? __builtin_amdgcn_rcpf(n) : 0.f;   // 1 ulp: `rest` corrects the mean
 #pragma unroll
   for (int g = 0; g < PARTS; ++g) {
     float mean[PC], m = 0.f, q = 0.f;
 #pragma unroll
     for (int e = 0; e < PC; ++e) {
       const int c = g * PC + e;
-      const float ds = st.s[c] * inv, m2 = st.q[c] - st.s[c] * ds;
+      const float ds = quotient(st.s[c], st.n, inv), m2 = st.q[c] - st.s[c] * ds;
       mean[e] = st.shift[c] + ds;
       m += mean[e];
       q += m2 < 0.f ? 0.f : m2;     // (NaN stays NaN)

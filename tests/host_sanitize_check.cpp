@@ -1,6 +1,7 @@
 // Test infrastructure: drives the library's host-side logic (plan building, weight table, workspace layout, step
 // accounting, argument checks) with no GPU, in a build whose host code is compiled with -fsanitize=address,undefined
 // (tests/test_sanitizers.py).  Nothing here launches a kernel.
+#include <math.h>
 #include <stdio.h>
 #include <string.h>
 
@@ -8,6 +9,7 @@
 
 #include "wmdec.h"
 #include "wmdec_measure.h"
+#include "quotient.hpp"
 #include "sample_offsets.hpp"
 
 static int fails = 0;
@@ -81,8 +83,27 @@ static void check_sample_offsets() {
   }
 }
 
+// Division through a reciprocal that is off by an ulp either way: half an ulp of the quotient, for every count of pixels of a block.
+static void check_quotient() {
+  unsigned state = 1;
+  for (int n = 1; n <= 512; ++n) {
+    const float exact = 1.0f / (float)n, near[] = {nextafterf(exact, 0.f), exact, nextafterf(exact, 2.f)};
+    for (int i = 0; i < 200; ++i) {
+      state = state * 1664525u + 1013904223u;
+      const float a = (float)(int)state * 0x1p-28f;
+      for (float rcp : near) {
+        const double want = (double)a / n, got = wmdec::quotient(a, (float)n, rcp);
+        const float ulp = nextafterf(fabsf((float)want), INFINITY) - fabsf((float)want);
+        CHECK(fabs(got - want) <= 0.50001 * ulp);
+      }
+    }
+    CHECK(wmdec::quotient(0.f, (float)n, exact) == 0.f && isnan(wmdec::quotient(NAN, (float)n, exact)));
+  }
+}
+
 int main() {
   check_sample_offsets();
+  check_quotient();
   wmdec_decoder_config cfg;
   decoder_default_config(&cfg);
   exercise(cfg);
