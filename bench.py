@@ -129,7 +129,7 @@ def main():
         f["launches"] += 1
     dom = max(fam, key=lambda k: fam[k]["ms"])
     d = fam[dom]
-    bound = "mfma" if dom.startswith("conv_mfma") or dom.startswith("flash_attn") else "hbm"
+    bound = "mfma" if dom.startswith(("conv_mfma", "attn_qkv", "flash_attn")) else "hbm"
     if bound == "mfma":
         achieved = d["flops"] / (d["ms"] * 1e-3) / 1e12
         unit = "TFLOP/s"

@@ -1,7 +1,7 @@
 // Mid-block attention: one head of dimension 512, softmax(q k^T / sqrt(d)) v over the tokens of a sample.
 //
 // Three launches hand over 32-token tiles in MFMA fragment order, so that every one of them loads and stores runs of 1 KiB:
-//   conv_mfma_kernel (here the q/k/v projection)  [q|k|v] = W norm(x) + b, straight from its accumulators into fragments
+//   attn_qkv_kernel                               [q|k|v] = W norm(x) + b, straight from its accumulators into fragments
 //   flash_attn_kernel                             streams the keys, online softmax, unnormalised partial outputs
 //   attn_combine_kernel                           merges the partial outputs of the key ranges, normalises, rows of o (where one
 //                                                 range holds all keys, the core writes these rows itself)
@@ -49,8 +49,8 @@ struct QkvParams {
   int n, t, groups, tiles, w_bytes;   // tiles: workgroups along the tokens of a sample
 };
 
-template <typename T, int ACT>
-__global__ __launch_bounds__(QNT, 2) void conv_mfma_kernel(QkvParams p) {
+template <typename T>
+__global__ __launch_bounds__(QNT, 2) void attn_qkv_kernel(QkvParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
   T* s_x = reinterpret_cast<T*>(smem);                                   // [2][32 steps][64 lanes][8]
   float2* s_ab = reinterpret_cast<float2*>(smem + QT * D * sizeof(T));   // [D] (scale, shift)
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(QNT, 2) void conv_mfma_kernel(QkvParams p) {
     for (int ni = 0; ni < 2; ++ni) wq[s][ni] = load_fragment(wrsrc, lane16, wcol + s * STEP + ni * 1024);
 
   // ---- scale/shift table
-  if constexpr (ACT > 0) {
+  {
     const float ga = p.gamma[tid], be = p.beta[tid];      // one channel per thread
     static_assert(QNT == D, "one channel per thread");
     if (p.rows_in) {
@@ -106,11 +106,9 @@ __global__ __launch_bounds__(QNT, 2) void conv_mfma_kernel(QkvParams p) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int chunk = (wave * 2 + i / 4) * 4 + c4, tok = (i % 4) * 16 + tok16;
-    if constexpr (ACT > 0) {
-      const f32x4* tab = reinterpret_cast<const f32x4*>(s_ab + chunk * 8);
+    const f32x4* tab = reinterpret_cast<const f32x4*>(s_ab + chunk * 8);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) raw[i][k] = activate_word<T, ACT>(raw[i][k], tab[k]);
-    }
+    for (int k = 0; k < 4; ++k) raw[i][k] = activate_word<T, 1>(raw[i][k], tab[k]);   // (scale and shift)
     *reinterpret_cast<u32x4*>(s_x + (size_t)((tok / 32) * 32 + chunk / 2) * 512 + (tok % 32 + 32 * (chunk % 2)) * 8) = raw[i];
   }
   __syncthreads();
@@ -531,9 +529,9 @@ int launch_qkv_t(const ConvArgs& a, void* frag, hipStream_t s) {
   const size_t smem = (size_t)QT * D * sizeof(T) + (size_t)(D + a.groups) * sizeof(float2);
   static std::once_flag attr_once;
   hipError_t attr_err = hipSuccess;
-  std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)conv_mfma_kernel<T, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024); });
+  std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)attn_qkv_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024); });
   WMDEC_HIP(attr_err);
-  hipLaunchKernelGGL((conv_mfma_kernel<T, 1>), dim3((unsigned)(p.tiles * 3 * p.n)), dim3(QNT), smem, s, p);
+  hipLaunchKernelGGL(attn_qkv_kernel<T>, dim3((unsigned)(p.tiles * 3 * p.n)), dim3(QNT), smem, s, p);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
 }
@@ -546,7 +544,7 @@ size_t flash_attention_scratch_bytes(int n, int t) { return splits_of(t) == 1 ? 
 
 int flash_attention_num_launches(int t) { return splits_of(t) == 1 ? 1 : 2; }
 
-const char* attention_qkv_label(int dtype) { return dtype == WMDEC_BF16 ? "conv_mfma_kernel<wmdec::bf16_t, 1>" : "conv_mfma_kernel<wmdec::f16_t, 1>"; }
+const char* attention_qkv_label(int dtype) { return dtype == WMDEC_BF16 ? "attn_qkv_kernel<wmdec::bf16_t>" : "attn_qkv_kernel<wmdec::f16_t>"; }
 
 int launch_attention_qkv(const ConvArgs& a, void* frag, hipStream_t s) {
   WMDEC_REQUIRE(a.cin == D && a.cout == 3 * D && a.ksize == 1 && is_16bit(a.op_dtype) && a.x_dtype == a.op_dtype && a.bias && !a.res, WMDEC_ERR_UNSUPPORTED,

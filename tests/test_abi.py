@@ -96,10 +96,11 @@ def test_step_accounting_adds_up():
     assert abs(sum(f for _, f, _ in info) - dec.flops_per_frame()) / dec.flops_per_frame() < 1e-12
     assert all(k for k, _, _ in info)
     convs = [(k, f, b) for k, f, b in info if k.startswith("conv_mfma_kernel<")]
-    # 28 ResBlock convolutions (the two 1x1 shortcuts are folded into their second convolutions), qkv and output
-    # projection: 30 launches of the implicit-GEMM kernel; the three upsampling convolutions have a kernel of their own, and
-    # conv_out (three output channels) runs as a contraction onto (tap, channel) pairs
-    assert len(convs) == 30 and all(k.endswith(">") for k, _, _ in convs)
+    # 28 ResBlock convolutions (the two 1x1 shortcuts are folded into their second convolutions) and the output projection of the
+    # attention: 29 launches of the implicit-GEMM kernel; the q/k/v projection, which writes operand order, and the three upsampling
+    # convolutions have kernels of their own, and conv_out (three output channels) runs as a contraction onto (tap, channel) pairs
+    assert len(convs) == 29 and all(k.endswith(">") for k, _, _ in convs)
+    assert [(k, f) for k, f, _ in info if k.startswith("attn_qkv")] == [("attn_qkv_kernel<wmdec::f16_t>", 2.0 * 512 * 1536 * 5400)]
     assert [k for k, _, _ in info if k.startswith("conv_up_kernel<")] == ["conv_up_kernel<wmdec::f16_t, 2, 2, false>"] * 3
     assert info[-1][0] == "conv_taps_kernel<wmdec::f16_t, 8, 2>"
     # the ten 512 -> 512 layers at 60x90 leave compute units at most one workgroup: whole-chunk weight ring
