@@ -33,12 +33,21 @@ def test_upsampling_convolution_tile_edges(dtype, n, cin, cout, h, w):
         assert np.all(np.abs(got - want) <= tol), float(np.max(np.abs(got - want) - tol))
 
 
-def test_upsampling_convolution_sample_bits_do_not_depend_on_the_batch():
+# either side of the rule that splits the contraction of small images: 48 and 160 workgroups of 64 channels (the label of a
+# decoder's upsampling step, of the same shape, says which kernel a shape takes), and channels that cannot be split in two
+@pytest.mark.parametrize("cin,cout,h,w,split", [(64, 64, 20, 33, True), (96, 64, 20, 33, False), (512, 512, 17, 23, True), (512, 512, 28, 61, False)])
+def test_upsampling_convolution_sample_bits_do_not_depend_on_the_batch(cin, cout, h, w, split):
+    if cin == 512:
+        cfg = wmdec.decoder_default_config()
+        cfg.latent_h, cfg.latent_w = h, w
+        dec = wmdec.Decoder(cfg)
+        assert [k for k, _, _ in dec.step_info() if k.startswith("conv_up")][0] == "conv_up_kernel<wmdec::f16_t, 2, %d, false>" % (1 if split else 2)
+        dec.close()
     r = np.random.default_rng(synth.SEED_BASE + 51)
-    x = G.dev_nhwc(G.stored(r.standard_normal((3, 64, 20, 33)), "f16"), "f16")
-    wt, b = synth.conv_params(r, 64, 64, 3, True)
+    x = G.dev_nhwc(G.stored(r.standard_normal((3, cin, h, w)), "f16"), "f16")
+    wt, b = synth.conv_params(r, cout, cin, 3, True)
     wp, bd = G.pack_upconv(wt, "f16"), G.dev_f32(b)
-    y3, y1 = torch.empty((3, 40, 66, 64), dtype=torch.float16, device="cuda"), torch.empty((1, 40, 66, 64), dtype=torch.float16, device="cuda")
+    y3, y1 = (torch.empty((n, 2 * h, 2 * w, cout), dtype=torch.float16, device="cuda") for n in (3, 1))
     wmdec.upsample2x_conv3x3(x, wp, bd, y3)
     wmdec.upsample2x_conv3x3(x[1:2].contiguous(), wp, bd, y1)
     assert torch.equal(y3[1:2], y1)
