@@ -126,7 +126,7 @@ struct wmdec_decoder {
   std::vector<Step> steps;
   size_t weights_bytes = 0, packed_bytes = 0;
   size_t act_elems_per_frame = 0;   // largest activation tensor, elements per frame
-  int attn_t = 0, attn_tpad = 0, attn_c = 0;
+  int attn_t = 0, attn_c = 0;
   size_t qkv_w_off = 0, qkv_b_off = 0;   // fused [3c][c] projection and its [3c] bias in the packed blob
   double flops = 0.0;         // executed multiply-adds x 2 of one frame
   double flops_dense = 0.0;   // 2*k*k*cin*cout per output pixel everywhere (what an unfused graph would execute)
@@ -358,7 +358,7 @@ static int build_plan(wmdec_decoder& d) {
     B.conv_params("mid.attn.proj", c0, c0, 1, &p.w_off, &p.b_off);
     d.steps.push_back(p); B.count_conv(p);
     cur = other(1);
-    d.attn_t = h * w; d.attn_tpad = (h * w + 31) / 32 * 32; d.attn_c = c0;
+    d.attn_t = h * w; d.attn_c = c0;
   }
   B.resblock("mid.res2", cur, other(1), other(2), h, w, c0, c0);
   cur = other(2);

@@ -191,8 +191,8 @@ __global__ __launch_bounds__(QNT, 2) void attn_qkv_kernel(QkvParams p) {
 // has 32 MFMAs of scores and 32 of output, with one 1 KiB LDS read each; the wavefronts share nothing but the tiles.
 // Earlier 64 queries were the workgroup's, with the scores in other wavefronts than the output: twice the tile traffic per
 // query and the probabilities through LDS.  128 queries x 32 keys take 2300 cycles where the MFMAs take 2048; 5400 tokens
-// 91 -> 78 us, of which 60 us are the blocks (at 1 PFLOP/s the chip lowers its clock: three ranges of keys instead of
-// five run a block in 60 % of the time on 60 % of the compute units), 10 us the partial outputs (55 MB) and 9 us the
+// 91 -> 78 us, of which 60 us are the blocks (at 1 PFLOP/s the chip lowers its clock: with fewer compute units busy a block
+// takes less, but not by as much as there are more of them each, see splits_of), 10 us the partial outputs (55 MB) and 9 us the
 // first tiles.  Measured and not kept: tile requests dealt to one wavefront at a time with three buffers of k (86 us),
 // 4 or 16 fragments ahead (82, 125).
 constexpr int NT = 256;           // threads: four wavefronts of 32 queries
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(NT, 1) void flash_attn_kernel(const T* __restrict__
   const int kb0 = (int)((long)split * nkb / splits), nb = (int)((long)(split + 1) * nkb / splits) - kb0;   // key blocks of this range, at least one
   const int qt = qb * 4 + wave;          // this wavefront's query tile (past the last one: computed from the last, not stored)
 
-  // tile loads: straight into LDS, an eighth KiB run at a time; a block past the range reloads its last one, harmlessly
+  // tile loads: straight into LDS, a KiB at a time; a block past the range reloads its last one, harmlessly
   typedef const __attribute__((address_space(1))) void* gptr_t;
   typedef __attribute__((address_space(3))) void* lptr_t;
   constexpr int SHARE = TILE / 4;        // a wavefront's share of a tile
@@ -484,8 +484,11 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
 constexpr int kMaxSplits = 8;
 int tiles_of(int t) { return (t + KB - 1) / KB; }
 
-// ranges of keys per query block: about one workgroup per compute unit, two key blocks at least; independent of the batch, so
-// that a frame's bits do not depend on what it is batched with
+// ranges of keys per query block: as many workgroups as compute units, two key blocks at least; independent of the batch, so
+// that a frame's bits do not depend on what it is batched with.  A whole call in us, by ranges: 1024 tokens 4 46.8, 6 43.3, 7 42.6,
+// 8 42.8; 3600 tokens 5 76.2, 6 74.1, 7 73.4, 8 74.5; 5400 tokens 3 135.5, 4 120.8, 5 114.0, 6 (past one round) 151.7; 8372 tokens 2
+// 270, 3 217, 4 287; 12 000 tokens 1 647, 2 404, 3 500.  A range costs t * 2 KiB of workspace: 5400 tokens take 78 MB with five,
+// 56 with three.
 int splits_of(int t) {
   const int nkb = tiles_of(t), nqb = (nkb + 3) / 4;
   return max(1, min(min(256 / nqb, kMaxSplits), (nkb + 1) / 2));

@@ -446,8 +446,7 @@ int launch_tile(const ConvArgs& a, hipStream_t s) {
 // Tiles of the 16-bit launches (4 rows high, WK = 4 everywhere: the order in which an output's products are added, and
 // with it a frame's bits, depends neither on the tile nor on the batch, so the tile may follow the workgroups of the whole
 // launch).  The smallest tile whose workgroups fit one round of the compute units wins; measured on 512 -> 512 layers, us,
-// in the order K32x32, K32x64, K64x64, K64x128 (the first three since 0.2 to 1 us faster): 17x23 11.4 / 12.0 / 15.1 / 19.0; 32x32 16.8 / 15.3 / 16.0 / 19.5; 34x46
-// 26.9 / 20.9 / 17.3 / 20.4; 45x80 - / - / 35.5 / 24.9.
+// in the order K32x32, K32x64, K64x64, K64x128: 17x23 8.6 / 8.5 / 12.2 / 16.3; 32x32 12.9 / 11.5 / 12.3 / 16.4; 34x46 21.0 / 16.8 / 14.5 / 16.5; two samples of it 34.1 / 32.8 / 28.2 / 21.3.
 enum KsplitTile { K32x32 = 0, K32x64, K64x64, K64x128 };
 KsplitTile pick_ksplit_tile(const ConvArgs& a) {
   const long b8 = (long)((a.h + 3) / 4) * ((a.w + 7) / 8) * a.n, b16 = (long)((a.h + 3) / 4) * ((a.w + 15) / 16) * a.n;
@@ -482,8 +481,9 @@ bool batched_form(const ConvArgs& a) {
 }  // namespace
 
 // 16-bit types: images of at most 2^20 output elements a sample (2048 pixels of 512 channels), where the 128 x 128 tiles
-// leave at least three quarters of the compute units empty.  Measured against them, us at one sample: 17x23 of 512
-// channels 11.4 against 29.8; 32x32 15.3 / 30.2; 34x46 17.3 / 30.2; 68x92 of 256 channels, past the line, 16.2 / 21.7.  The
+// leave at least three quarters of the compute units empty.  Measured against what takes larger layers (64 x 128 tiles), us at
+// one sample: 17x23 of 512 channels 8.3 against 17.3; 32x32 11.5 / 17.4; 34x46 13.6 / 17.5; past the line 68x92 of 256 channels
+// 12.0 / 11.3, 64x64 of 512 22.0 / 22.3.  The
 // line may not depend on the batch: the order of summation does.  What the batch decides is the tile, see batched_form
 // and pick_ksplit_tile.
 // fp32: every size; 64 -> 64 channels at 32x32 take 10 us where the vector-ALU kernel takes 97.

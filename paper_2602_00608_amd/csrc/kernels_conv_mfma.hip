@@ -271,6 +271,8 @@ constexpr int prefetch_ring(int steps, int room) {
   return steps % 3 == 0 ? 3 : (steps % 4 == 0 ? 4 : 2);
 }
 
+struct NoFlush { __device__ void operator()(int) const {} };
+
 // MFMA work of one staged chunk: STEPS = taps * KC/16 k-steps, each MI x NI 32x32x16 MFMAs.
 // Weight fragments are fetched D-1 steps ahead (bq is a ring that persists across chunks: on
 // entry it holds steps 0..D-2 of this chunk, on exit steps 0..D-2 of the chunk at `bnext`).
@@ -284,11 +286,6 @@ constexpr int prefetch_ring(int steps, int room) {
 // weights of the two lie at bcur / bcur1, and flush(0 / 1) runs behind each.
 // AD: how many k-steps ahead the A fragments are read (1 or 2).  One step is MI - 1 MFMAs of slack, about the LDS
 // latency: enough where other wavefronts of the SIMD fill the gaps, too little for a wavefront that is alone on it.
-// byte offset, from the chunk's first fragment, of the weights of k-step s in the order of mfma_chunk_rows
-template <int KK> __device__ __forceinline__ int rows_weight_offset(int s, int tap_stride, int kk_stride) {
-  return (s % 3 * 3 + s / 3 / KK) * tap_stride + s / 3 % KK * kk_stride;
-}
-struct NoFlush { __device__ void operator()(int) const {} };
 template <typename T, int MI, int NI, int KS, int KC, int ROW, int PS, int D, bool SLICED, int VALU_PER_MFMA, typename Slice, int AD = 1, bool KMAJOR = false, typename Flush = NoFlush>
 __device__ __forceinline__ void mfma_chunk(const T* buf, const int (&a_off)[MI], __amdgpu_buffer_rsrc_t wrsrc, int bcur, int bnext,
                                            int tap_stride, int kk_stride, int lane16, u32x4 (&bq)[D][NI],
@@ -351,6 +348,11 @@ __device__ __forceinline__ void mfma_chunk(const T* buf, const int (&a_off)[MI],
     }
   };
   static_for<STEPS>(step);
+}
+
+// byte offset, from the chunk's first fragment, of the weights of k-step s in the order of mfma_chunk_rows
+template <int KK> __device__ __forceinline__ int rows_weight_offset(int s, int tap_stride, int kk_stride) {
+  return (s % 3 * 3 + s / 3 / KK) * tap_stride + s / 3 % KK * kk_stride;
 }
 
 // The same for 3x3 taps where a wavefront's M tiles are the pixel rows (r, r + APART), r = 0 .. APART - 1, of blocks of 2 APART
@@ -888,8 +890,8 @@ constexpr TileShape kTiles[kNumTiles] = {
 
 // Layers whose 128 x 128 tiles leave half of the compute units empty at batch 1 and whose moments, per 4x16 block, are few
 // enough for the consumer to merge: 64 x 128 tiles where the launch still fits one round, 128 x 128 otherwise, with the same
-// order of summation and the same moments.  Measured, us, 64 x 128 against 128 x 128: 512 channels at 64x64 24.8 / 30.0, at
-// 34x46 19.5 / 27.7; past one round 37.0 / 34.4 (60x90).
+// order of summation and the same moments.  Measured, us, 64 x 128 against 128 x 128: 512 channels at 64x64 23.1 / 26.2, at
+// 48x72 21.0 / 25.6, 256 channels at 68x92 11.6 / 15.5; past one round 33.3 / 28.5 (512 channels at 60x90).
 // The smaller tile always has a whole chunk of weight fragments in flight: two MFMAs a k-step cover little of the latency of
 // weights that are new to the L2 (256x256 frame 859 -> 853 us against half a chunk, 136x184 the same).
 // The larger tile of the pair runs as T128x128_1x4 does: ResBlocks of 2 / 4 / 8 samples take 93.0 / 156.6 / 284.6 us at 512
@@ -925,7 +927,8 @@ TileId pick_tile(const ConvArgs& a) {
 }
 
 // The 128x128 tiles with a whole chunk of weight fragments in flight (see RING): launches of at most two workgroups per
-// compute unit (two frames of 360x640: 4.13 -> 4.08 ms with the ring and the pair's moments from the written-back values).  Unlike the tile shape this may depend on the batch: the ring changes no summation order.
+// compute unit (against the shorter ring: 480x720 frame 2.92 -> 2.89 ms, two of 360x640 3.79 -> 3.76; layers on their own, whose
+// weights stay in the L2, are the same).  Unlike the tile shape this may depend on the batch: the ring changes no summation order.
 bool whole_chunk_ring(const ConvArgs& a) {
   const TileId t = pick_tile(a);
   if (t != T128x128_1x4 && t != T128x128_ROWS4) return false;
