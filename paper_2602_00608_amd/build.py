@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libwmdec.so")
 
-SOURCES = ["api.cpp", "kernels_gn.hip", "kernels_conv_direct.hip", "kernels_conv_mfma.hip", "kernels_conv_ksplit.hip", "kernels_conv_up.hip",
+SOURCES = ["api.cpp", "kernels_gn.hip", "kernels_conv_direct.hip", "kernels_conv_mfma.hip", "kernels_conv_rows.hip", "kernels_conv_ksplit.hip", "kernels_conv_up.hip",
            "kernels_conv_taps.hip", "kernels_misc.hip", "kernels_attn.hip", "kernels_adaln.hip"]
 
 # kernels with matrix instructions in inline assembly, whose code asm_check reads: source -> kernel

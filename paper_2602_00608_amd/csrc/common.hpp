@@ -114,6 +114,9 @@ bool conv_mfma_supported(const ConvArgs& a);
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s);
 // the layers of conv_ksplit_supported (16 bit, cout % 128 == 0, no shortcut) in large batches: that kernel's bits and moments
 int launch_conv_quarters(const ConvArgs& a, hipStream_t s);
+// kernels_conv_rows.hip: its 3x3 layers on tiles of th rows x 16 pixels x 128 ni output channels; rows4: moments per four rows;
+// whole_ring: a whole chunk of weights in flight
+int launch_conv_rows(const ConvArgs& a, int th, int ni, bool rows4, bool whole_ring, hipStream_t s);
 // moment slots per (sample, group) the MFMA kernel would write for this launch; 0: it cannot emit statistics
 int conv_mfma_stats_slots(const ConvArgs& a);
 void conv_mfma_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row);

@@ -58,6 +58,21 @@ __device__ __forceinline__ u32x4 load_fragment(__amdgpu_buffer_rsrc_t rsrc, int 
   return __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane16, off, 0);
 }
 
+// 16 bytes of every lane to a buffer, at a lane offset plus a wave-uniform one in a scalar register.  The store reads its data late: where
+// the next instruction overwrites them it may store what that one wrote (seen on this chip, the last lanes of a row first).
+// The compiler leaves a wait state between the two only where the scalar offset is a constant; here two stand in between, and
+// uses of `v` that follow come after them.
+__device__ __forceinline__ void store_vector(__amdgpu_buffer_rsrc_t rsrc, u32x4& v, int lane_offset, int base) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, lane_offset, base, 0);
+  asm volatile("s_nop 1" : "+v"(v));
+}
+
+// pack2 by one instruction
+template <typename T> __device__ __forceinline__ uint32_t pack_word(float f0, float f1) {
+  if constexpr (std::is_same<T, f16_t>::value) return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{f0, f1}, f16x2_t));
+  else return pack2<T>(f0, f1);
+}
+
 // Word (two channels) of a staged vector with the table entries ab = (a0, b0, a1, b1); ACT: 0 as it is, 1 scale/shift,
 // 2 scale/shift + SiLU.  PIN: the last fp32 operation and the conversion stay apart.  The compiler otherwise folds them into
 // one (v_fma_mixlo_f16, one rounding instead of two) at some places and not at others, and the bits of a value would
@@ -68,7 +83,7 @@ template <typename T, int ACT, bool PIN = false> __device__ __forceinline__ uint
     if constexpr (ACT == 2) { f0 = silu_from_scaled(f0); f1 = silu_from_scaled(f1); }
     if constexpr (PIN) {
       asm("" : "+v"(f0), "+v"(f1));
-      if constexpr (std::is_same<T, f16_t>::value) return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{f0, f1}, f16x2_t));   // one instruction
+      return pack_word<T>(f0, f1);
     }
     wv = pack2<T>(f0, f1);
   }

@@ -21,68 +21,10 @@
 
 #include <mutex>
 
-#include "conv_device.hpp"
+#include "conv_moments.hpp"
 
 namespace wmdec {
 namespace {
-
-// MODE: kRows4 and kQuarters are forms between which and another kernel the batch decides, while a sample's bits must not
-// depend on that choice; so both keep the activation's roundings apart (PIN).
-//   kRows4     one of a pair of tiles, 4x16 and 8x16 (see four_row_slots): moments per four rows.
-//   kQuarters  the batched form of kernels_conv_ksplit.hip, with its order of summation: of every 64 input channels the
-//              k-th 16 belong to partial sum k, each of them is summed on its own, 16 channels and their nine taps at a
-//              time, and the four are added in order.  Here one after the other into a second set of accumulators, on M tiles of 4 x 8
-//              pixels, the blocks of that kernel's moments.
-enum ConvMode { kPlain = 0, kRows4 = 1, kQuarters = 2 };
-
-// Moments of a wavefront's stored values in the making: per channel of the lane's octet sums shifted by the lane's first value,
-// over n pixels.
-struct LaneMoments { float n, shift[8], s[8], q[8]; };
-
-// ... merged per group and written.  A lane merges its channels of a group (PARTS groups per octet, or its part of a larger one),
-// then the lanes that hold the same octet, and those of the group's other octets, are summed in the vector ALU: the mean first,
-// then the squares about it.  (Through LDS, with a lane per channel that walked the others' sums and re-centred them one by
-// one, this was 13 of the 122 us of 128 -> 128 channels at 480x720, and 1.5 of 36 at 60x90.)  OCTETS: octets of channels of the wavefront.
-template <int OCTETS, int PARTS>
-__device__ __forceinline__ void emit_moments(const LaneMoments& st, int lane, int co_w, Moments* dst, int cpg, int stats_stride, bool handed_over) {
-  constexpr int PC = 8 / PARTS;
-  auto lanes = [&](float v) {
-    if constexpr (OCTETS <= 4) v += row_rotate<4>(v);
-    v += row_rotate<8>(v);
-    v = swap_sum<32>(swap_sum<16>(v));
-    if (cpg > 8) v += quad_xor<1>(v);
-    if (cpg > 16) v += quad_xor<2>(v);
-    return v;
-  };
-  const float inv = st.n > 0.f ? __builtin_amdgcn_rcpf(st.n) : 0.f;
-  const float n = lanes(st.n), ninv = n > 0.f ? __builtin_amdgcn_rcpf(n) : 0.f;   // 1 ulp: `rest` corrects the mean
-#pragma unroll
-  for (int g = 0; g < PARTS; ++g) {
-    float mean[PC], m = 0.f, q = 0.f;
-#pragma unroll
-    for (int e = 0; e < PC; ++e) {
-      const int c = g * PC + e;
-      const float ds = quotient(st.s[c], st.n, inv), m2 = st.q[c] - st.s[c] * ds;
-      mean[e] = st.shift[c] + ds;
-      m += mean[e];
-      q += m2 < 0.f ? 0.f : m2;     // (NaN stays NaN)
-    }
-    m = st.n > 0.f ? m * (1.f / PC) : 0.f;     // the shift of a lane without pixels has no meaning
-    float dev = 0.f;
-#pragma unroll
-    for (int e = 0; e < PC; ++e) { const float d = mean[e] - m; dev = fmaf(d, d, dev); }
-    const float mid = lanes(st.n * m) * ninv;
-    const float d = m - mid, nd = st.n * d;
-    const float rest = lanes(nd) * ninv;       // what the roundings of mid left
-    q = lanes(st.n > 0.f ? fmaf(st.n, dev, fmaf(nd * PC, d, q)) : 0.f) - n * PC * rest * rest;
-    const Moments out{n * PC, mid + rest, q < 0.f ? 0.f : q};
-    if (lane < OCTETS && ((lane * 8) & (cpg - 1)) == 0) {
-      Moments* at = dst + (size_t)((co_w + lane * 8 + g * PC) / cpg) * stats_stride;
-      if (handed_over) store_device(at, out);   // another workgroup of this launch may merge them, see the row hand-over in the kernel
-      else *at = out;
-    }
-  }
-}
 
 // Wavefront-private epilogue patches of 32 padded rows: a second one, for the next M tile's values, where there is a next M tile
 // and the workgroups that the registers allow still fit the LDS with it (four of 36.9 KB with one channel tile a wavefront, two of
@@ -91,9 +33,6 @@ __device__ __forceinline__ void emit_moments(const LaneMoments& st, int lane, in
 // 13.3 / 15.7.
 constexpr int epilogue_patches(int mi, int ni) { return mi > 1 && (ni == 1 || mi * ni > 4) ? 2 : 1; }
 constexpr int patch_floats(int mi, int ni) { return epilogue_patches(mi, ni) * 32 * (ni * 32 + 4); }
-
-// first row of M tile mi of a wavefront whose M tiles are rows r and r + APART (blocks of 2 APART rows)
-template <int APART> constexpr int apart_row(int mi) { return mi / APART * 2 * APART + mi % APART; }
 
 struct EpilogueParams {
   __amdgpu_buffer_rsrc_t res, y;           // the sample's residual and output, with its size: accesses outside are dropped
@@ -112,17 +51,15 @@ struct EpilogueParams {
 // round every partial sum at its exponent, an error of 4e-7 of the result against 3e-8 where the bias is many times the sum.
 // Residual and output are accessed through buffers with a lane offset that is the same for all vectors, or past the end for
 // pixels outside the image, and the vector's position in a scalar register: no address arithmetic, no masks.
-// Moments: one triple per group for all M tiles, or (kRows4) for every two of them, four rows of 16 pixels.  kQuarters (NI = 1):
+// Moments: one triple per group for all M tiles.  kQuarters (NI = 1):
 // one for each M tile of 4 x 8 pixels, from the values written back to the patches of a pair: a lane walks one channel
 // of either tile, as the kernel that it reproduces does.
-// APART: row distance of an M tile's two halves where they are not neighbours (see mfma_chunk_rows), otherwise 0.
-template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, int APART, bool RES, int MODE>
+template <typename T, typename TO, int MI, int NI, int MTW, int MTH, int MT_PER_ROW, bool RES, int MODE>
 __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], const float (&bias)[NI], float* wave_lds, int lane, int mt0,
                                                int ty0, int tx0, int co_w, const EpilogueParams& p) {
   constexpr int RW = NI * 32 + 4;       // padded row of a patch, floats
   constexpr bool PAIRS = MODE == kQuarters;
   constexpr int PATCHES = epilogue_patches(MI, NI);
-  constexpr int EMIT = MODE == kRows4 ? 2 : MI;   // M tiles of a triple
   const int lm = lane & 31, lk = lane >> 5;
   auto put = [&](float* patch, int mi) {
 #pragma unroll
@@ -153,11 +90,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
   const int lane_row = prow / MTW, lane_col = prow % MTW;
   // elements: the lane's part, and that of vector j of M tile mi
   const unsigned lane_off = (unsigned)((lane_row * p.w + lane_col) * p.cout + cvec * 8);
-  static_assert(APART == 0 || (MTW == 16 && STEP <= 16 && MT_PER_ROW == 1), "the lanes of a vector are in one row");
-  auto row_of = [&](int mi, int j) {
-    if constexpr (APART > 0) return ty0 + apart_row<APART>(mi) + APART * (j * STEP / MTW);
-    else return ty0 + (mt0 + mi) / MT_PER_ROW * MTH + j * STEP / MTW;
-  };
+  auto row_of = [&](int mi, int j) { return ty0 + (mt0 + mi) / MT_PER_ROW * MTH + j * STEP / MTW; };
   auto col_of = [&](int mi, int j) { return tx0 + (mt0 + mi) % MT_PER_ROW * MTW + j * STEP % MTW; };
   auto inside = [&](int mi, int j) -> bool { return row_of(mi, j) + lane_row < p.h && col_of(mi, j) + lane_col < p.w; };
   auto base_of = [&](int mi, int j) -> int { return vector_base(row_of(mi, j), col_of(mi, j), p.h, p.w, p.cout, co_w); };
@@ -199,10 +132,11 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
       if constexpr (sizeof(TO) == 2) packed = u32x4{pack2<T>(v[0], v[1]), pack2<T>(v[2], v[3]), pack2<T>(v[4], v[5]), pack2<T>(v[6], v[7])};
       const int at = (int)((ok ? lane_off : kOutside) * sizeof(TO)), base = base_of(mi, j) * (int)sizeof(TO);
       if constexpr (sizeof(TO) == 4) {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), p.y, at, base, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[4], v[5], v[6], v[7]}), p.y, at + 16, base, 0);
+        u32x4 a = __builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), b = __builtin_bit_cast(u32x4, f32x4{v[4], v[5], v[6], v[7]});
+        store_vector(p.y, a, at, base);
+        store_vector(p.y, b, at + 16, base);
       } else {
-        __builtin_amdgcn_raw_buffer_store_b128(packed, p.y, at, base, 0);
+        store_vector(p.y, packed, at, base);
       }
       if (p.stats) {
         float sv[8];
@@ -218,7 +152,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
             *reinterpret_cast<f32x4*>(lds + pi * RW + cvec * 8 + 4) = f32x4{sv[4], sv[5], sv[6], sv[7]};
           }
         } else {
-          if (mi % EMIT == 0 && j == 0) {   // (outside the image only if all vectors of the lane are)
+          if (mi == 0 && j == 0) {   // (outside the image only if all vectors of the lane are)
             st.n = 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) { st.shift[e] = sv[e]; st.s[e] = 0.f; st.q[e] = 0.f; }
@@ -246,15 +180,8 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
         m = merge_to_first(m, lane, p.cpg);
         if ((lm & (p.cpg - 1)) == 0 && m.n > 0.f) dst[(size_t)((co_w + lm) / p.cpg) * p.stats_stride + lk] = m;
       }
-    } else if ((mi + 1) % EMIT == 0) {
-      // (kRows4: rows past the image have no slot)
-      if (p.stats && (MODE != kRows4 || row_of(mi + 1 - EMIT, 0) < p.h)) {
-        Moments* dst = p.stats + (mi / EMIT) * p.pair_stride;
-        if (p.cpg >= 8) emit_moments<NI * 4, 1>(st, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
-        else if (p.cpg == 4) emit_moments<NI * 4, 2>(st, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
-        else if (p.cpg == 2) emit_moments<NI * 4, 4>(st, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
-        else emit_moments<NI * 4, 8>(st, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
-      }
+    } else if (mi + 1 == MI) {
+      if (p.stats) emit_groups<NI * 4, false>(st, lane, co_w, p.stats, p.cpg, p.stats_stride, p.handed_over);
     }
     if (mi + 1 < MI && !ahead) put(wave_lds + (mi + 1) % PATCHES * 32 * RW, mi + 1);
   }
@@ -350,64 +277,6 @@ __device__ __forceinline__ void mfma_chunk(const T* buf, const int (&a_off)[MI],
   static_for<STEPS>(step);
 }
 
-// byte offset, from the chunk's first fragment, of the weights of k-step s in the order of mfma_chunk_rows
-template <int KK> __device__ __forceinline__ int rows_weight_offset(int s, int tap_stride, int kk_stride) {
-  return (s % 3 * 3 + s / 3 / KK) * tap_stride + s / 3 % KK * kk_stride;
-}
-
-// The same for 3x3 taps where a wavefront's M tiles are the pixel rows (r, r + APART), r = 0 .. APART - 1, of blocks of 2 APART
-// rows of 16: one tap row further down, M tile r reads what M tile r + 1 reads here.  So APART + 2 fragments serve the three
-// taps of a column, 3 APART MFMAs: at 4 rows apart half the LDS reads of a fragment per MFMA, which kept the LDS, at
-// 128 B/clk for four SIMDs, as busy as the matrix pipe.  K-steps run over the tap rows innermost, then the chunk's groups of 16 channels,
-// then the tap columns; a fragment is refreshed in place behind its last MFMA, at least APART + 1 MFMAs before the next use.
-// Measured against neighbouring rows with a read per tap, both sides' frames against one third build: 480x720 frame 1.025x
-// (f16) and 1.016x (bf16), four frames 1.022x, 256x256 1.017x, 136x184 1.005x, ResBlock 128 at 480x720 bf16 1.026x (229 -> 223
-// us).  Taller wavefronts of the same kind, at two workgroups per compute unit instead of three, are slower: 16 rows 0.96x,
-// 12 rows 0.93x on that ResBlock.
-template <typename T, int MI, int NI, int KC, int ROW, int PS, int D, int VALU_PER_MFMA, int APART, typename Slice>
-__device__ __forceinline__ void mfma_chunk_rows(const T* buf, int a_off, __amdgpu_buffer_rsrc_t wrsrc, int bcur, int bnext, int tap_stride, int kk_stride,
-                                                int lane16, u32x4 (&bq)[D][NI], f32x16 (&acc)[MI][NI], Slice&& slice) {
-  constexpr int KK = KC / 16, GROUPS = 3 * KK, STEPS = 3 * GROUPS, FRAGS = APART + 2;
-  static_assert(MI % APART == 0, "whole blocks");
-  u32x4 af[MI / APART][FRAGS];
-  auto read = [&](auto g_c, auto b_c, auto f_c) {
-    constexpr int g = decltype(g_c)::value, b = decltype(b_c)::value, f = decltype(f_c)::value;
-    af[b][f] = *reinterpret_cast<const u32x4*>(buf + a_off + (b * 2 * APART + f) * ROW + (g / KK) * PS + (g % KK) * 16);
-  };
-  static_for<FRAGS>([&](auto f_c) {
-    static_for<MI / APART>([&](auto b_c) { read(std::integral_constant<int, 0>{}, b_c, f_c); });
-  });
-  static_for<STEPS>([&](auto s_c) {
-    constexpr int s = decltype(s_c)::value, g = s / 3, ky = s % 3;
-    {
-      constexpr int sp = s + D - 1;
-      const int at = (sp < STEPS ? bcur : bnext) + rows_weight_offset<KK>(sp % STEPS, tap_stride, kk_stride);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) bq[sp % D][ni] = load_fragment(wrsrc, lane16, at + ni * 1024);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    // the fragment that M tile mi is the last to read at this tap row
-    constexpr auto last = [](int mi) constexpr { return g + 1 < GROUPS && (ky == 2 || mi % APART == 0); };
-    static_for<MI>([&](auto mi_c) {
-      constexpr int mi = decltype(mi_c)::value, b = mi / APART, f = mi % APART + ky;
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = Mma<T>::m32(af[b][f], bq[s % D][ni], acc[mi][ni]);
-      if constexpr (last(mi)) read(std::integral_constant<int, g + 1>{}, std::integral_constant<int, b>{}, std::integral_constant<int, f>{});
-      slice(std::integral_constant<int, s * MI + mi>{});
-      if constexpr (VALU_PER_MFMA < 0) __builtin_amdgcn_sched_barrier(0);
-    });
-    if constexpr (VALU_PER_MFMA >= 0) {   // issue order inside the k-step, as above
-      static_for<MI * NI>([&](auto j_c) {
-        constexpr int j = decltype(j_c)::value;
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                       // one MFMA
-        if constexpr (j % NI == NI - 1 && last(j / NI)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-        if constexpr (VALU_PER_MFMA > 0) __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER_MFMA, 0);
-      });
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  });
-}
-
 // ACT: what happens to an input element on its way into LDS: 0 nothing, 1 scale/shift, 2 scale/shift + SiLU
 constexpr int wave_m_tiles(int th, int tw, int wm) { return th * tw / 32 / wm; }
 // Workgroups per compute unit the register budget is sized for: three for the small accumulator tiles, except the
@@ -433,14 +302,8 @@ constexpr int tile_row_elems(int tw, int pad, int kc, int mtw) {
 constexpr int tile_buf_elems(int th, int tw, int pad, int kc, int mtw) { return (th + 2 * pad) * tile_row_elems(tw, pad, kc, mtw) + (kc + 8); }
 
 // RING: 0 = weight-fragment ring sized by prefetch_ring; otherwise its length in k-steps (a divisor of the k-steps of
-// a chunk).  The whole-chunk ring is for launches that leave a compute unit at most two workgroups: there a wavefront
-// is alone on its SIMD, nothing else hides the latency of weights that come from beyond the L2 (every layer's weights
-// are new to the L2 inside a decoder run), and the registers of the third workgroup are free for it.
+// a chunk).
 constexpr int m_tile_width(int tw, int mode) { return mode == kQuarters ? 8 : tw < 32 ? tw : 32; }
-// Wavefronts that hold all rows of a 16-pixel-wide patch take rows apart; kRows4: inside the four rows of a triple of moments.
-constexpr int rows_apart(int tw, int wm, int mi, int ks, int mode) {
-  return ks == 3 && tw == 16 && wm == 1 && mode != kQuarters ? (mode == kRows4 ? 2 : mi) : 0;
-}
 template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int ACT, int MODE = kPlain, int RING = 0>
 __global__ __launch_bounds__(64 * WM * WN, RING > 6 ? 2 : resident_workgroups(wave_m_tiles(TH, TW, WM) * NI, WM, WN))
 void conv_mfma_kernel(MfmaParams p) {
@@ -460,7 +323,6 @@ void conv_mfma_kernel(MfmaParams p) {
   constexpr int SPARE = HH_ * ROW;                       // element offset of the spare pixel slot
   constexpr int STEPS = KS * KS * (KC / 16), SLOTS = STEPS * MI;
   constexpr bool SLICED = KS == 3;               // activation of the next chunk is sliced into the MFMA sweep
-  constexpr int APART = rows_apart(TW, WM, MI, KS, MODE);   // see mfma_chunk_rows; 0: M tiles of neighbouring rows
   static_assert(NT % VPP == 0, "a thread keeps one channel octet");
   static_assert((RING > 6 ? 2 : resident_workgroups(MI * NI, WM, WN)) * WM * WN * patch_floats(MI, NI) * sizeof(float) <= 160 * 1024,
                 "the workgroups that the registers are budgeted for fit the LDS of a compute unit");
@@ -490,7 +352,7 @@ void conv_mfma_kernel(MfmaParams p) {
 
   // the bias of the lane's channel columns, for the epilogue: requested here, as a load there would be waited for, unless the
   // main loop has no register left to hold it
-  constexpr bool BIAS_EARLY = !(QUARTERS || (MODE == kRows4 && RING == 0));
+  constexpr bool BIAS_EARLY = !QUARTERS;
   float bias[NI];
   auto load_bias = [&]() {
 #pragma unroll
@@ -507,8 +369,7 @@ void conv_mfma_kernel(MfmaParams p) {
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
     const int mt = wm * MI + mi;
-    int ty = (mt / MT_PER_ROW) * MTH + lm / MTW;
-    if constexpr (APART > 0) ty = apart_row<APART>(mi) + APART * (lm / MTW);
+    const int ty = (mt / MT_PER_ROW) * MTH + lm / MTW;
     const int tx = (mt % MT_PER_ROW) * MTW + lm % MTW;
     a_off[mi] = ty * ROW + tx * PS + 8 * lk;
   }
@@ -549,7 +410,7 @@ void conv_mfma_kernel(MfmaParams p) {
 #pragma unroll
   for (int sp = 0; sp < D - 1; ++sp) {
     const int tap = QUARTERS ? sp % (KS * KS) : sp / KK, kk = QUARTERS ? sp / (KS * KS) : sp % KK;
-    const int at = APART > 0 ? wcol + rows_weight_offset<KK>(sp, tap_stride, kk_stride) : weights_at(0, 0, kk) + tap * tap_stride;
+    const int at = weights_at(0, 0, kk) + tap * tap_stride;
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) bq[sp][ni] = load_fragment(wrsrc, lane16, at + ni * 1024);
   }
@@ -694,7 +555,7 @@ void conv_mfma_kernel(MfmaParams p) {
       // mean / rstd of every group from the row triples its producer left: eight lanes per group take the rows
       // round-robin (16 in the form that has to reproduce a kernel with 16); (mean, rstd) parked behind the table
       float2* s_stat = s_ab + p.cin;
-      // Launches that leave a wavefront alone on its SIMD (RING): gamma / beta of this thread's first two table
+      // kQuarters: gamma / beta of this thread's first two table
       // entries are requested together with the triples, one memory round trip less in front of the first chunk
       // (elsewhere other workgroups cover that latency and the registers are better left to the main loop).
       constexpr int PRE = RING > 6 ? 2 : 0;
@@ -789,8 +650,7 @@ void conv_mfma_kernel(MfmaParams p) {
       };
       // the last chunk activates a harmless reload into the buffer nobody reads: one instruction stream, no
       // control flow inside the pinned schedule
-      if constexpr (APART > 0) mfma_chunk_rows<T, MI, NI, KC, ROW, PS, D, SPREAD, APART>(buf, a_off[0], wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, slice);
-      else mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, true, SPREAD, decltype(slice)&, (RING > 6 ? 2 : 1), QUARTERS>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, slice, bcur1, bnext1, flush);
+      mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, true, SPREAD, decltype(slice)&, (RING > 6 ? 2 : 1), QUARTERS>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, slice, bcur1, bnext1, flush);
     } else {
       auto none = [](auto) {};
       mfma_chunk<T, MI, NI, KS, KC, ROW, PS, D, false, -1, decltype(none)&, (RING > 6 ? 2 : 1)>(buf, a_off, wrsrc, bcur, bnext, tap_stride, kk_stride, lane16, bq, acc, none);
@@ -806,11 +666,10 @@ void conv_mfma_kernel(MfmaParams p) {
 
   // ---- epilogue: bias, residual, one rounding, store (through wavefront-private LDS patches over the tile buffers)
   if constexpr (!BIAS_EARLY) load_bias();
-  constexpr bool BLOCKS = MODE != kPlain;
   float* patch = reinterpret_cast<float*>(smem) + wave * patch_floats(MI, NI);
-  // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row], or by blocks of 4 rows x 16 or 8 pixels
+  // statistics slot of this wavefront: [sample][group][spatial tile * WM + wave row], or by blocks of 4 rows x 8 pixels
   const int per_row = QUARTERS ? (p.w_out + 7) / 8 : p.tiles_x;   // slots of a row of blocks
-  const int slot = BLOCKS ? ty0 / 4 * per_row + tx0 / (QUARTERS ? 8 : TW) : tile * WM + wm;
+  const int slot = QUARTERS ? ty0 / 4 * per_row + tx0 / 8 : tile * WM + wm;
   EpilogueParams ep;
   {
     const int elems = p.h * p.w_out * p.cout;   // of a sample
@@ -824,8 +683,8 @@ void conv_mfma_kernel(MfmaParams p) {
   ep.stats = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + slot : nullptr;
   ep.cpg = p.stats_cpg; ep.stats_stride = p.stats_slots; ep.pair_stride = per_row; ep.handed_over = p.rows_out != nullptr;
   auto store = [&](const f32x16 (&sums)[MI][NI]) {
-    if (p.res) epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, APART, true, MODE>(sums, bias, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
-    else epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, APART, false, MODE>(sums, bias, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
+    if (p.res) epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, true, MODE>(sums, bias, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
+    else epilogue_store<T, TO, MI, NI, MTW, MTH, MT_PER_ROW, false, MODE>(sums, bias, patch, lane, wm * MI, ty0, tx0, co0 + wn * NI * 32, ep);
   };
   if constexpr (QUARTERS) store(total);
   else store(acc);
@@ -838,7 +697,7 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
   constexpr int PAD = KS / 2;
   constexpr int TN = WN * NI * 32;
   MfmaParams p = conv_params(a, TH, TW, TN, WM, a.h, a.w);
-  if (MODE != kPlain) p.stats_slots = ((a.h + 3) / 4) * (MODE == kQuarters ? (a.w + 7) / 8 : p.tiles_x);
+  if (MODE == kQuarters) p.stats_slots = ((a.h + 3) / 4) * ((a.w + 7) / 8);
   WMDEC_REQUIRE(MODE != kQuarters || (!a.x2 && a.cin % 64 == 0), WMDEC_ERR_UNSUPPORTED, "conv_mfma: this form takes no shortcut");
   WMDEC_REQUIRE(MODE == kPlain || !a.rows_out, WMDEC_ERR_UNSUPPORTED, "conv_mfma: this tile hands over no rows");
   const int rc = check_hand_over(p);
@@ -938,16 +797,10 @@ bool whole_chunk_ring(const ConvArgs& a) {
 
 template <typename T, typename TO>
 int launch_3x3(const ConvArgs& a, hipStream_t s) {
-  switch (pick_tile(a)) {
-    case T128x64: return launch_cfg<T, TO, 8, 16, 4, 1, 2, 3, 32>(a, s);
-    case T128x128_1x4:
-      return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32>(a, s);
-    case T64x128: return launch_cfg<T, TO, 4, 16, 1, 4, 1, 3, 32, 18, kRows4>(a, s);
-    case T128x128_ROWS4:
-      return whole_chunk_ring(a) ? launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 18, kRows4>(a, s) : launch_cfg<T, TO, 8, 16, 1, 4, 1, 3, 32, 0, kRows4>(a, s);
-    case T128x256: return launch_cfg<T, TO, 8, 16, 1, 4, 2, 3, 32>(a, s);
-    default: return launch_cfg<T, TO, 8, 32, 4, 1, 1, 3, 32>(a, s);
-  }
+  const TileId t = pick_tile(a);
+  if (t == T128x64) return launch_cfg<T, TO, 8, 16, 4, 1, 2, 3, 32>(a, s);
+  if (t == T256x32) return launch_cfg<T, TO, 8, 32, 4, 1, 1, 3, 32>(a, s);
+  return launch_conv_rows(a, kTiles[t].th, kTiles[t].ni, t == T64x128 || t == T128x128_ROWS4, t == T64x128 || whole_chunk_ring(a), s);
 }
 
 // chunk of input channels a 1x1 launch stages at a time: 64 halves the barriers

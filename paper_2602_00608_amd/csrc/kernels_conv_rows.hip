@@ -1,0 +1,531 @@
+// 3x3 convolution on 16x16x32 MFMAs: a wavefront holds all rows of a 16-pixel-wide patch.
+//
+// The form that the large layers take (128 output channels and more a workgroup).  GEMM view, staging, statistics and epilogue semantics
+// are those of kernels_conv_mfma.hip: a workgroup of four wavefronts owns TH rows x 16 pixels and 128 * NI output channels, 32 * NI a
+// wavefront; per chunk of 32 input channels the patch plus halo goes through one of two LDS buffers, normalised and
+// activated once per element, and the nine taps are swept over it.
+//
+// Why this MFMA: the power limit decides the clock of these kernels, and 16x16x32 does a sixth more under it than 32x32x16
+// (operands in registers, values as in a layer: 1.95 against 1.68 PFLOP/s, at 1.95 and 1.70 GHz).  One MFMA takes 32 channels of a row of
+// 16 pixels and 16 output channels.
+// A = weights, B = pixels: a lane then holds four consecutive output channels of a pixel; the two tiles of a 32-channel fragment pair take its rows
+// dealt so that a lane holds eight (tile h, row m: channel 8 (m / 4) + 4 h + m % 4), and residual and output move as
+// 16-byte vectors straight from the accumulators.
+#include <stdio.h>
+
+#include <mutex>
+
+#include "conv_moments.hpp"
+
+namespace wmdec {
+namespace {
+
+// LDS layout of a staged patch: 96 bytes from pixel to pixel.  A fragment is 16 pixels x 32 channels, lanes i and i + 16 a channel octet
+// apart; 96 bytes serve that in one pass (4 cycles a KiB, measured), 64, 80 and 144 bytes in two.  One pixel slot behind the patch is spare:
+// vectors outside the image are stored there.
+constexpr int kChunk = 32;                 // input channels of a chunk
+constexpr int PS = kChunk + 16;            // elements from pixel to pixel
+constexpr int PW = 18, ROW = PW * PS;      // pixels, elements of a row of the patch
+constexpr int buf_elems(int th) { return (th + 2) * ROW + PS; }
+
+// Three workgroups per compute unit leave 168 registers: the offsets of the vectors that a thread stages then wait in LDS for their
+// place in a sweep (the compiler would spill them, and wait for every load in flight where it takes them back).
+constexpr int resident_workgroups(int th, int ni, int ring) { return th * ni <= 8 && ring == 0 ? 3 : 2; }
+constexpr bool park_offsets(int th, int ni, int ring) { return resident_workgroups(th, ni, ring) == 3; }
+constexpr size_t fixed_lds(int th, int ni, int ring) {   // patches, bias, parked offsets; the table of the activation lies behind them
+  return (size_t)2 * buf_elems(th) * 2 + (size_t)128 * ni * sizeof(float) + (park_offsets(th, ni, ring) ? 2 * 256 * 16 : 0);
+}
+
+// byte offset, from the chunk's first fragment, of the weights of step s = (tap column, tap row, ni)
+template <int NI> __device__ __forceinline__ int weight_offset(int s, int tap_stride) {
+  return (s / NI % 3 * 3 + s / (3 * NI)) * tap_stride + s % NI * 1024;
+}
+
+// MFMA work of one staged chunk: 9 NI steps, each 2 R MFMAs with the weights of a tap and 32 output channels.
+// One tap row further down, row r reads what row r + 1 reads here: R + 2 fragments serve the three taps of a column.  Steps
+// run over ni innermost, then the tap rows, then the tap columns.  The fragments of the chunk's three columns are
+// numbered on and kept in a ring: number q takes the place of q - SLOTS behind the last MFMA of that one (which is in the last of the NI
+// steps of a tap: with two of them, all R fragments of a tap must have a place).  With eight rows
+// seven places leave at least 12 MFMAs between a read and its use, eight 14, with four rows six leave 10.
+// Weights are requested D - 1 steps ahead, into a ring that persists across chunks: on entry it holds steps 0 .. D - 2 of this chunk, on
+// exit those of the chunk at `bnext` (LAST: there is none).
+// The order is pinned as written, slice(m) behind MFMA m.
+template <typename T, int R, int NI, int D, bool LAST, typename Slice>
+__device__ __forceinline__ void sweep_chunk(const T* buf, __amdgpu_buffer_rsrc_t wrsrc, int bcur, int bnext, int tap_stride, int lane_w,
+                                            u32x4 (&bq)[D][2], f32x4 (&acc)[R][2 * NI], Slice&& slice) {
+  constexpr int STEPS = 9 * NI, FRAGS = R + 2, SLOTS = R < 8 ? FRAGS : NI == 1 ? R - 1 : R;
+  static_assert(STEPS % D == 0, "the ring position must be the same at every chunk start");
+  u32x4 af[SLOTS];
+  auto read = [&](auto q_c) {
+    constexpr int q = decltype(q_c)::value;
+    af[q % SLOTS] = *reinterpret_cast<const u32x4*>(buf + q % FRAGS * ROW + q / FRAGS * PS);
+  };
+  static_for<SLOTS>(read);
+  static_for<STEPS>([&](auto s_c) {
+    constexpr int s = decltype(s_c)::value, g = s / (3 * NI), ky = s / NI % 3, ni = s % NI, sp = s + D - 1;
+    if constexpr (!LAST || sp < STEPS) {
+      const int at = (sp < STEPS ? bcur : bnext) + weight_offset<NI>(sp % STEPS, tap_stride);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) bq[sp % D][h] = load_fragment(wrsrc, lane_w, at + 64 * h);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // row r is the last to read its fragment, and there is one to take its place
+    constexpr auto last = [](int r) constexpr { return ni == NI - 1 && (ky == 2 || r == 0) && g * FRAGS + r + ky + SLOTS < 3 * FRAGS; };
+    static_for<R>([&](auto r_c) {
+      constexpr int r = decltype(r_c)::value;
+      static_for<2>([&](auto h_c) {
+        constexpr int h = decltype(h_c)::value;
+        acc[r][2 * ni + h] = Mma<T>::m16(bq[s % D][h], af[(g * FRAGS + r + ky) % SLOTS], acc[r][2 * ni + h]);
+        if constexpr (h == 1 && last(r)) read(std::integral_constant<int, g * FRAGS + r + ky + SLOTS>{});
+        slice(std::integral_constant<int, (s * R + r) * 2 + h>{});
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+  });
+}
+
+struct EpilogueParams {
+  __amdgpu_buffer_rsrc_t res, y;           // the sample's residual and output, with its size: accesses outside are dropped
+  int h, w, cout;
+  Moments* stats; int cpg, stats_stride, row_stride;
+  bool handed_over;
+};
+
+// the residual vector of row r and channels co .. co + 31 (lane: pixel lane % 16, channel octet lane / 16)
+template <typename T> __device__ __forceinline__ u32x4 load_residual(const EpilogueParams& p, int lane, int row, int tx0, int co) {
+  const int px = lane & 15, oct = lane >> 4;
+  const unsigned at = row < p.h && tx0 + px < p.w ? (unsigned)(px * p.cout + oct * 8) : kOutside;
+  return __builtin_amdgcn_raw_buffer_load_b128(p.res, (int)(at * sizeof(T)), vector_base(row, tx0, p.h, p.w, p.cout, co) * (int)sizeof(T), 0);
+}
+
+// Epilogue of one wavefront: bias, residual, one rounding, store: a pixel's 32 channels are 64 contiguous bytes.  (Through LDS
+// patches, as in kernels_conv_mfma.hip, the same lanes write 64 values one by one and wait for them.)  The bias is added to
+// the finished sums: accumulators that start from it round every partial sum at its exponent.
+// rv: the residual of the first 32 channels, requested by the last sweep.
+// Moments, of the values as stored: one triple per group for all R rows, or (kRows4) for every four of them.
+template <typename T, typename TO, int R, int NI, bool RES, bool STATS, int MODE>
+__device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], u32x4 (&rv)[NI][R], const float* s_bias, int lane, int ty0, int tx0, int co_w,
+                                         const EpilogueParams& p) {
+  constexpr int EMIT = MODE == kRows4 ? 4 : R;   // rows of a triple
+  static_assert(R % EMIT == 0, "whole triples");
+  const int px = lane & 15, oct = lane >> 4;
+  const bool col_ok = tx0 + px < p.w;
+  const unsigned lane_off = (unsigned)(px * p.cout + oct * 8);
+  if constexpr (RES) {
+#pragma unroll
+    for (int ni = 1; ni < NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < R; ++r) rv[ni][r] = load_residual<T>(p, lane, ty0 + r, tx0, co_w + 32 * ni);
+  }
+#pragma unroll
+  for (int ni = 0; ni < NI; ++ni) {
+    const f32x4 b0 = *reinterpret_cast<const f32x4*>(s_bias + 32 * ni + 8 * oct), b1 = *reinterpret_cast<const f32x4*>(s_bias + 32 * ni + 8 * oct + 4);
+    LaneMoments moments[R / EMIT] = {};   // (written behind the last row: in between, the compiler would spill the accumulators)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const f32x4 lo = acc[r][2 * ni] + b0, hi = acc[r][2 * ni + 1] + b1;
+      float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      if constexpr (RES) {
+        float rf[8];
+        unpack8<T>(rv[ni][r], rf);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += rf[e];
+      }
+      const bool ok = ty0 + r < p.h && col_ok;
+      const int at = (int)((ok ? lane_off : kOutside) * sizeof(TO)), base = vector_base(ty0 + r, tx0, p.h, p.w, p.cout, co_w + 32 * ni) * (int)sizeof(TO);
+      float sv[8];   // as stored
+      if constexpr (sizeof(TO) == 4) {
+        u32x4 a = __builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), b = __builtin_bit_cast(u32x4, f32x4{v[4], v[5], v[6], v[7]});
+        store_vector(p.y, a, at, base);
+        store_vector(p.y, b, at + 16, base);
+        const f32x4 sa = __builtin_bit_cast(f32x4, a), sb = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { sv[e] = sa[e]; sv[4 + e] = sb[e]; }
+      } else {
+        u32x4 packed = u32x4{pack2<T>(v[0], v[1]), pack2<T>(v[2], v[3]), pack2<T>(v[4], v[5]), pack2<T>(v[6], v[7])};
+        store_vector(p.y, packed, at, base);
+        unpack8<T>(packed, sv);
+      }
+      if constexpr (STATS) {
+        LaneMoments& st = moments[r / EMIT];
+        if (r % EMIT == 0) {   // (outside the image only if all vectors of the lane's triple are)
+          st.n = 0.f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) { st.shift[e] = sv[e]; st.s[e] = 0.f; st.q[e] = 0.f; }
+        }
+        if (ok) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) { const float dv = sv[e] - st.shift[e]; st.s[e] += dv; st.q[e] = fmaf(dv, dv, st.q[e]); }
+          st.n += 1.f;
+        }
+      }
+    }
+    if constexpr (STATS) {
+#pragma unroll
+      for (int t = 0; t < R / EMIT; ++t)   // (kRows4: rows past the image have no slot)
+        if (MODE != kRows4 || ty0 + t * EMIT < p.h)
+          emit_groups<4, true>(moments[t], lane, co_w + 32 * ni, p.stats + t * p.row_stride, p.cpg, p.stats_stride, p.handed_over);
+    }
+  }
+}
+
+// ACT: what happens to an input element on its way into LDS: 0 nothing, 1 scale/shift, 2 scale/shift + SiLU
+// RING: 0 = weights two steps ahead; otherwise the length of the weight ring in k-steps of 16 channels (18: a whole chunk).  The
+// whole-chunk ring is for launches that leave a compute unit at most two workgroups: there a wavefront
+// is alone on its SIMD, nothing else hides the latency of weights that come from beyond the L2 (every layer's weights
+// are new to the L2 inside a decoder run), and the registers of the third workgroup are free for it.
+// (TW, WM, WN, KS, KC: always 16, 1, 4, 3, 32; the name of an instantiation reads as those of kernels_conv_mfma.hip do.)
+template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int ACT, int MODE, int RING>
+__global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_mfma_kernel(MfmaParams p) {
+  static_assert(TW == 16 && WM == 1 && WN == 4 && KS == 3 && KC == kChunk, "one layout");
+  constexpr int NT = 256, HP = PW * (TH + 2), TN = 128 * NI;
+  constexpr int VPP = KC / 8;                        // 16-byte vectors per pixel per chunk
+  constexpr int NV = (HP * VPP + NT - 1) / NT;       // vectors a thread stages per chunk
+  constexpr int BUF = buf_elems(TH), SPARE = (TH + 2) * ROW;
+  constexpr int D = RING > 0 ? RING / 2 * NI : 3;    // weight ring, steps
+  constexpr bool PARK = park_offsets(TH, NI, RING);
+  static_assert(!PARK || NV == 3, "three offsets of either kind");
+
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* s_a = reinterpret_cast<T*>(smem);                                          // [2][BUF]
+  float* s_bias = reinterpret_cast<float*>(smem + 2 * BUF * 2);                 // [TN]
+  u32x4* s_off = reinterpret_cast<u32x4*>(s_bias + TN);                         // [2][NT] offsets (PARK)
+  float2* s_ab = reinterpret_cast<float2*>(smem + fixed_lds(TH, NI, RING));     // [cin] (scale, shift)
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wn = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform: keeps the per-wave addresses scalar
+
+  // workgroup id -> (channel tile, sample, spatial tile); consecutive ids of one XCD (id % 8) are neighbours
+  int L;
+  {
+    const int i = blockIdx.x, per = p.total / 8, rem = p.total % 8;
+    const int x = i % 8, j = i / 8;
+    L = x * per + (x < rem ? x : rem) + j;
+  }
+  const int tiles = p.tiles_x * p.tiles_y;
+  const int nt = L / (tiles * p.n);
+  const int n = (L / tiles) % p.n;
+  const int tile = L % tiles;
+  const int ty0 = (tile / p.tiles_x) * TH, tx0 = (tile % p.tiles_x) * TW;
+  const int co0 = nt * TN, co_w = co0 + wn * NI * 32;
+
+  if (tid < TN) s_bias[tid] = (p.bias ? p.bias[co0 + tid] : 0.f) + (p.bias2 ? p.bias2[co0 + tid] : 0.f);
+
+  // ---- weights: the wavefront's fragment column (wave-uniform), and the lane's 16 bytes in tile 0 of a pair of fragments
+  const int kk_stride = p.cout_blocks * 1024, tap_stride = p.cin_blocks * kk_stride;   // bytes
+  const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w), 0, p.w_bytes, 0x00020000);
+  const int wcol = (co_w >> 5) * 1024;
+  const int lane_w = (lane >> 5) * kk_stride + ((lane & 12) * 2 + (lane & 3) + (lane & 16) * 2) * 16;
+  u32x4 bq[D][2];
+  f32x4 acc[TH][2 * NI];
+#pragma unroll
+  for (int sp = 0; sp < D - 1; ++sp)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) bq[sp][h] = load_fragment(wrsrc, lane_w, wcol + weight_offset<NI>(sp, tap_stride) + 64 * h);
+
+  // ---- staging: a thread owns NV (pixel, channel-octet) vectors of the halo patch; the octet is the same for all.
+  // Zero padding without per-element work: a vector outside the image is loaded from pixel 0 (a load under a lane
+  // mask would make the compiler wait for it at the end of the branch), activated like any other, and stored to
+  // the spare pixel slot behind the patch; its real slot is zeroed once, here, in both buffers.
+  const int cvec = tid % VPP;
+  const char* xin = reinterpret_cast<const char*>(p.x) + (size_t)n * p.h * p.w_out * p.cin * sizeof(T);   // uniform base
+  auto pixel_of = [&](int i, int& at) -> int {   // index of vector i's source pixel in the sample, or -1; at: its slot in a patch
+    const int hp = (tid + i * NT) / VPP;
+    const int hy = hp / PW, hx = hp % PW;
+    const int gy = ty0 + hy - 1, gx = tx0 + hx - 1;
+    at = hp < HP ? hy * ROW + hx * PS : SPARE;
+    return hp < HP && gy >= 0 && gy < p.h && gx >= 0 && gx < p.w_out ? gy * p.w_out + gx : -1;
+  };
+  int src_off[NV];          // byte offset of the vector in the first chunk of x
+  int dst_off[NV];          // element offset of its slot in a patch
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    int at;
+    const int pix = pixel_of(i, at);
+    src_off[i] = max(pix, 0) * p.cin * (int)sizeof(T) + cvec * 16;
+    dst_off[i] = (pix >= 0 ? at : SPARE) + cvec * 8;
+    if (pix < 0 && at != SPARE) {
+      *reinterpret_cast<u32x4*>(s_a + at + cvec * 8) = u32x4{0u, 0u, 0u, 0u};
+      *reinterpret_cast<u32x4*>(s_a + BUF + at + cvec * 8) = u32x4{0u, 0u, 0u, 0u};
+    }
+  }
+  // One register set of raw vectors: the loads of chunk c + 2 are issued behind the sweep of chunk c, and the vectors of chunk c + 1 are
+  // activated and stored into the other LDS buffer in the last two thirds of that sweep.
+  const int nchunks = p.cin / KC;
+  u32x4 raw[NV];
+
+  float zero = 0.f;
+  asm volatile("" : "+v"(zero));   // (seen as a constant, it costs the fullest of these kernels spilled registers)
+#pragma unroll
+  for (int i = 0; i < TH; ++i)
+#pragma unroll
+    for (int j = 0; j < 2 * NI; ++j) acc[i][j] = f32x4{zero, zero, zero, zero};
+  const int row_off = (lane & 15) * PS + (lane >> 4) * 8;   // the lane's pixel and octet in a row of the patch
+
+  // ---- shortcut phase (a second input): acc = W2 * x2 over the tile's own pixels, a 1x1
+  // contraction over cin2 channels taken as stored (no normalisation).  Chunks go through the same
+  // two LDS buffers with the halo layout (only the centre tap is read), loads two chunks ahead; the main
+  // loop below then adds the 3x3 contraction to the same accumulators, so the shortcut tensor never exists in
+  // memory and the epilogue adds both biases.
+  if (p.x2) {
+    const char* xin2 = reinterpret_cast<const char*>(p.x2) + (size_t)n * p.h * p.w_out * p.cin2 * sizeof(T);
+    const int nch2 = p.cin2 / KC;
+    int src2[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      int at;
+      src2[i] = max(pixel_of(i, at), 0) * p.cin2 * (int)sizeof(T) + cvec * 16;
+    }
+    auto issue2 = [&](int chunk) {
+      const int cb = min(chunk, nch2 - 1) * KC * (int)sizeof(T);
+#pragma unroll
+      for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(xin2 + (unsigned)(src2[i] + cb));
+    };
+    auto store_all = [&](T* buf) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) *reinterpret_cast<u32x4*>(buf + dst_off[i]) = raw[i];
+    };
+    const __amdgpu_buffer_rsrc_t wrsrc2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w2), 0, p.w2_bytes, 0x00020000);
+    u32x4 wa[2 * NI], wb[2 * NI];   // both tiles of every 32 channels, of this chunk and the next
+    auto load2 = [&](u32x4 (&f)[2 * NI], int chunk) {
+#pragma unroll
+      for (int j = 0; j < 2 * NI; ++j) f[j] = load_fragment(wrsrc2, lane_w, wcol + min(chunk, nch2 - 1) * 2 * kk_stride + j / 2 * 1024 + 64 * (j % 2));
+    };
+    load2(wa, 0);
+    issue2(0);
+    store_all(s_a);
+    issue2(1);
+    __syncthreads();
+    for (int c = 0; c < nch2; ++c) {
+      load2(wb, c + 1);
+      const T* ctr = s_a + (c & 1) * BUF + row_off + ROW + PS;
+#pragma unroll
+      for (int r = 0; r < TH; ++r) {
+        const u32x4 px = *reinterpret_cast<const u32x4*>(ctr + r * ROW);
+#pragma unroll
+        for (int j = 0; j < 2 * NI; ++j) acc[r][j] = Mma<T>::m16(wa[j], px, acc[r][j]);
+      }
+#pragma unroll
+      for (int j = 0; j < 2 * NI; ++j) wa[j] = wb[j];
+      if (c + 1 < nch2) store_all(s_a + ((c + 1) & 1) * BUF);
+      issue2(c + 2);
+      __syncthreads();
+    }
+  }
+
+#pragma unroll
+  for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(xin + (unsigned)src_off[i]);
+  // ---- per-channel scale/shift table: a = gamma*rstd, b = beta - mean*a (built behind the first chunk's loads, so that its own
+  // global loads overlap them).  With SiLU the table holds -log2(e) * (a, b):
+  // the staged value is u = -log2(e) * t, from which silu(t) = t / (1 + 2^u) = u / (-log2(e) - log2(e) * 2^u) takes
+  // one exp2, one fma, one reciprocal and one multiply
+  if constexpr (ACT > 0) {
+    const int cpg = p.cin / p.groups;
+    const float k = ACT == 2 ? -1.4426950408889634f : 1.0f;
+    if (p.rows_in) {
+      // mean / rstd of every group from the row triples its producer left: eight lanes per group take the rows
+      // round-robin; (mean, rstd) parked behind the table
+      float2* s_stat = s_ab + p.cin;
+      // Launches that leave a wavefront alone on its SIMD (RING): gamma / beta of this thread's first two table
+      // entries are requested together with the triples, one memory round trip less in front of the first chunk
+      // (elsewhere other workgroups cover that latency and the registers are better left to the main loop).
+      constexpr int PRE = RING > 0 ? 2 : 0;
+      float gpre[2] = {0.f, 0.f}, bpre[2] = {0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < PRE; ++j) {
+        const int c = min(tid + j * NT, p.cin - 1);
+        gpre[j] = p.gamma[c]; bpre[j] = p.beta[c];
+      }
+      constexpr int LANES = 8;
+      const int sub = tid % LANES;
+      for (int g = tid / LANES; g < p.groups; g += NT / LANES) {
+        const float2 m = merge_row<LANES>(p.rows_in + (size_t)(n * p.groups + g) * p.rows_in_count, p.rows_in_count, sub, p.eps);
+        if (sub == 0) s_stat[g] = m;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < PRE; ++j) {
+        const int c = tid + j * NT;
+        if (c < p.cin) {
+          const float2 st = s_stat[c / cpg];
+          const float a = gpre[j] * st.y;
+          s_ab[c] = make_float2(k * a, k * (bpre[j] - st.x * a));
+        }
+      }
+      for (int c = tid + PRE * NT; c < p.cin; c += NT) {
+        const float2 st = s_stat[c / cpg];
+        const float a = p.gamma[c] * st.y;
+        s_ab[c] = make_float2(k * a, k * (p.beta[c] - st.x * a));
+      }
+    } else {
+      for (int c = tid; c < p.cin; c += NT) {
+        const int g = c / cpg;
+        const float a = p.gamma[c] * p.rstd[n * p.groups + g];
+        s_ab[c] = make_float2(k * a, k * (p.beta[c] - p.mean[n * p.groups + g] * a));
+      }
+    }
+  }
+  __syncthreads();            // scale/shift table complete
+  auto table = [&](const float2* tab, int part) -> f32x4 {   // entries of word `part` of the thread's octet
+    if constexpr (ACT > 0) return *reinterpret_cast<const f32x4*>(tab + 2 * part);
+    else return f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+#pragma unroll
+  for (int part = 0; part < 4; ++part) {
+    const f32x4 ab = table(s_ab + cvec * 8, part);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) raw[i][part] = activate_word<T, ACT, true>(raw[i][part], ab);
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) *reinterpret_cast<u32x4*>(s_a + dst_off[i]) = raw[i];
+  if (nchunks > 1) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(xin + (unsigned)(src_off[i] + KC * (int)sizeof(T)));
+  }
+  if constexpr (PARK) {
+    s_off[tid] = u32x4{(unsigned)dst_off[0], (unsigned)dst_off[1], (unsigned)dst_off[NV - 1], 0u};
+    s_off[NT + tid] = u32x4{(unsigned)src_off[0], (unsigned)src_off[1], (unsigned)src_off[NV - 1], 0u};
+  }
+  __syncthreads();
+
+  EpilogueParams ep;
+  {
+    const int elems = p.h * p.w_out * p.cout;   // of a sample
+    char* y = reinterpret_cast<char*>(p.y) + (size_t)n * elems * sizeof(TO);
+    ep.y = __builtin_amdgcn_make_buffer_rsrc(y, 0, (int)(elems * sizeof(TO)), 0x00020000);
+    const char* res = reinterpret_cast<const char*>(p.res) + (size_t)n * elems * sizeof(T);
+    ep.res = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(res), 0, p.res ? (int)(elems * sizeof(T)) : 0, 0x00020000);   // (none: reads zeros)
+  }
+  ep.h = p.h; ep.w = p.w_out; ep.cout = p.cout;
+  // statistics slot of this tile: [sample][group][spatial tile], or by blocks of 4 rows x 16 pixels
+  ep.stats = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + (MODE == kRows4 ? ty0 / 4 * p.tiles_x + tx0 / TW : tile) : nullptr;
+  ep.cpg = p.stats_cpg; ep.stats_stride = p.stats_slots; ep.row_stride = p.tiles_x; ep.handed_over = p.rows_out != nullptr;
+
+  // ---- the chunks.  In the last two thirds of a sweep the words (two channels) of the next chunk's vectors are activated: all vectors of a
+  // thread hold the same channel octet, so they are taken part by part (word `part` of every vector, then the next part), with the
+  // table entries of a part read from LDS once, ahead of their first use.  A word's operations are dealt to the MFMAs from
+  // its start on, so that none waits for the one before it.
+  const T* rows_at = s_a + row_off;          // what a sweep reads, advanced from chunk to chunk
+  const float2* tab = s_ab + cvec * 8;       // the table entries of the chunk that a sweep activates
+  float k;
+  asm("s_mov_b32 %0, 0xbfb8aa3b" : "=s"(k));   // -log2(e), see silu_from_scaled: the compiler would keep it in a vector register
+  for (int c = 0; c + 1 < nchunks; ++c) {
+    T* nbuf = s_a + ((c + 1) & 1) * BUF;
+    tab += KC;
+    u32x4 off;                                 // (PARK) the offsets at hand: dst_off towards the end of the sweep, src_off behind it
+    f32x4 ab;
+    float t0, t1, e0, e1;                      // a word's values on their way
+    auto slice = [&](auto m_c) {
+      constexpr int m = decltype(m_c)::value, ALL = 18 * NI * TH, FIRST = ALL / 3, SPAN = ALL - FIRST, NW = NV * 4;
+      constexpr bool FINE = SPAN / NW >= 8;    // eight MFMAs a word, otherwise six
+      static_assert(SPAN / NW >= 6, "a word takes six MFMAs");
+      if constexpr (m == FIRST - 8) ab = table(tab, 0);
+      if constexpr (PARK && m == FIRST + NV * 3 * SPAN / NW - 8) off = s_off[tid];
+      if constexpr (m >= FIRST) {
+        constexpr int wi = ((m - FIRST + 1) * NW - 1) / SPAN;        // the last word that starts at this MFMA or before it:
+        constexpr int at = m - FIRST - wi * SPAN / NW;               // word wi starts at FIRST + wi * SPAN / NW
+        constexpr int stage = FINE ? at : at == 0 ? 0 : at == 1 ? 12 : at == 2 ? 3 : at == 3 ? 45 : at + 2;
+        constexpr int part = wi / NV, i = wi % NV;
+        if constexpr (ACT > 0 && stage == 0) {
+          t0 = fmaf(unpack_lo<T>(raw[i][part]), ab[0], ab[1]);
+          t1 = fmaf(unpack_hi<T>(raw[i][part]), ab[2], ab[3]);
+        }
+        if constexpr (stage == 0 && i == NV - 1 && part < 3) ab = table(tab, part + 1);
+        if constexpr (ACT == 2) {
+          if constexpr (stage == 1 || stage == 12) e0 = __builtin_amdgcn_exp2f(t0);
+          if constexpr (stage == 2 || stage == 12) e1 = __builtin_amdgcn_exp2f(t1);
+          if constexpr (stage == 3) { e0 = fmaf(e0, k, k); e1 = fmaf(e1, k, k); }
+          if constexpr (stage == 4 || stage == 45) e0 = __builtin_amdgcn_rcpf(e0);
+          if constexpr (stage == 5 || stage == 45) e1 = __builtin_amdgcn_rcpf(e1);
+          if constexpr (stage == 6) { t0 *= e0; t1 *= e1; }
+        }
+        if constexpr (stage == 7) {
+          if constexpr (ACT > 0) {
+            asm("" : "+v"(t0), "+v"(t1));   // the roundings stay apart, see activate_word
+            raw[i][part] = pack_word<T>(t0, t1);
+          }
+          if constexpr (part == 3) *reinterpret_cast<u32x4*>(nbuf + (PARK ? (int)off[i] : dst_off[i])) = raw[i];
+        }
+      }
+    };
+    const int bcur = wcol + c * 2 * kk_stride;
+    sweep_chunk<T, TH, NI, D, false>(rows_at, wrsrc, bcur, bcur + 2 * kk_stride, tap_stride, lane_w, bq, acc, slice);
+    if (c + 2 < nchunks) {
+      if constexpr (PARK) off = s_off[NT + tid];
+#pragma unroll
+      for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(xin + (unsigned)((PARK ? (int)off[i] : src_off[i]) + (c + 2) * KC * (int)sizeof(T)));
+    }
+    rows_at += c & 1 ? -BUF : BUF;
+    __syncthreads();          // other buffer staged; this one free for chunk c + 2
+  }
+  // the last one: nothing to activate, and behind its last weights the residual is requested, so that the epilogue does not wait for it
+  u32x4 rv[NI][TH];
+  auto ask = [&](auto m_c) {
+    constexpr int m = decltype(m_c)::value, FROM = (9 * NI - (D - 1)) * TH * 2;
+    if constexpr (m >= FROM && m < FROM + TH) rv[0][m - FROM] = load_residual<T>(ep, lane, ty0 + m - FROM, tx0, co_w);
+  };
+  sweep_chunk<T, TH, NI, D, true>(rows_at, wrsrc, wcol + (nchunks - 1) * 2 * kk_stride, 0, tap_stride, lane_w, bq, acc, ask);
+
+  const float* bias_w = s_bias + wn * NI * 32;
+  if (p.stats) {
+    if (p.res) epilogue<T, TO, TH, NI, true, true, MODE>(acc, rv, bias_w, lane, ty0, tx0, co_w, ep);
+    else epilogue<T, TO, TH, NI, false, true, MODE>(acc, rv, bias_w, lane, ty0, tx0, co_w, ep);
+  } else {
+    if (p.res) epilogue<T, TO, TH, NI, true, false, MODE>(acc, rv, bias_w, lane, ty0, tx0, co_w, ep);
+    else epilogue<T, TO, TH, NI, false, false, MODE>(acc, rv, bias_w, lane, ty0, tx0, co_w, ep);
+  }
+
+  if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, co0, TN, WM, tid, lane);
+}
+
+template <typename T, typename TO, int TH, int NI, int MODE, int RING>
+int launch_cfg(const ConvArgs& a, hipStream_t s) {
+  MfmaParams p = conv_params(a, TH, 16, 128 * NI, 1, a.h, a.w);
+  if (MODE == kRows4) p.stats_slots = ((a.h + 3) / 4) * p.tiles_x;
+  WMDEC_REQUIRE(a.cin % kChunk == 0 && a.cout % (128 * NI) == 0 && !a.y_nchw, WMDEC_ERR_UNSUPPORTED, "conv_rows: channels do not fit the tile");
+  WMDEC_REQUIRE(MODE == kPlain || !a.rows_out, WMDEC_ERR_UNSUPPORTED, "conv_rows: this tile hands over no rows");
+  const int rc = check_hand_over(p);
+  if (rc != WMDEC_OK) return rc;
+  p.w = a.wt;
+  p.w_bytes = (int)(packed_elems(9, a.cout, a.cin) * sizeof(T));
+  if (a.x2) {
+    WMDEC_REQUIRE(a.w2 && a.cin2 > 0 && a.cin2 % kChunk == 0 && (long)a.h * a.w * a.cin2 < (1L << 29), WMDEC_ERR_UNSUPPORTED,
+                  "conv_rows: a folded shortcut needs cin2 %% %d == 0", kChunk);
+    p.x2 = a.x2; p.w2 = a.w2; p.bias2 = a.bias2; p.cin2 = a.cin2;
+    p.w2_bytes = (int)(packed_elems(1, a.cout, a.cin2) * sizeof(T));
+  }
+  const size_t smem = fixed_lds(TH, NI, RING) + (size_t)(a.cin + a.groups) * sizeof(float2);
+  WMDEC_REQUIRE(smem <= 80 * 1024, WMDEC_ERR_UNSUPPORTED, "conv_rows: %zu bytes of LDS needed", smem);
+  void (*kern)(MfmaParams) = !p.norm ? conv_mfma_kernel<T, TO, TH, 16, 1, 4, NI, 3, kChunk, 0, MODE, RING>
+                             : (a.silu ? conv_mfma_kernel<T, TO, TH, 16, 1, 4, NI, 3, kChunk, 2, MODE, RING>
+                                       : conv_mfma_kernel<T, TO, TH, 16, 1, 4, NI, 3, kChunk, 1, MODE, RING>);
+  // once per instantiation and activation mode (80 KiB: two workgroups per compute unit)
+  static std::once_flag attr_once[3];
+  hipError_t attr_err = hipSuccess;
+  std::call_once(attr_once[!p.norm ? 0 : (a.silu ? 2 : 1)],
+                 [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024); });
+  WMDEC_HIP(attr_err);
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.total), dim3(256), smem, s, p);
+  WMDEC_HIP(hipGetLastError());
+  return WMDEC_OK;
+}
+
+template <typename T, typename TO>
+int launch_form(const ConvArgs& a, int th, int ni, bool rows4, bool whole_ring, hipStream_t s) {
+  if (th == 4) return launch_cfg<T, TO, 4, 1, kRows4, 18>(a, s);
+  if (ni == 2) return launch_cfg<T, TO, 8, 2, kPlain, 0>(a, s);
+  if (rows4) return whole_ring ? launch_cfg<T, TO, 8, 1, kRows4, 18>(a, s) : launch_cfg<T, TO, 8, 1, kRows4, 0>(a, s);
+  return whole_ring ? launch_cfg<T, TO, 8, 1, kPlain, 18>(a, s) : launch_cfg<T, TO, 8, 1, kPlain, 0>(a, s);
+}
+
+template <typename T> int launch_type(const ConvArgs& a, int th, int ni, bool rows4, bool whole_ring, hipStream_t s) {
+  return a.y_dtype == WMDEC_F32 ? launch_form<T, float>(a, th, ni, rows4, whole_ring, s) : launch_form<T, T>(a, th, ni, rows4, whole_ring, s);
+}
+
+}  // namespace
+
+int launch_conv_rows(const ConvArgs& a, int th, int ni, bool rows4, bool whole_ring, hipStream_t s) {
+  return a.op_dtype == WMDEC_BF16 ? launch_type<bf16_t>(a, th, ni, rows4, whole_ring, s) : launch_type<f16_t>(a, th, ni, rows4, whole_ring, s);
+}
+
+}  // namespace wmdec
