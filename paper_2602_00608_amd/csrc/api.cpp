@@ -37,6 +37,21 @@ int launch_conv(const ConvArgs& a, hipStream_t s) {
   return launch_conv_direct(a, s);
 }
 
+// What a launch with these arguments reads of its packed weights, for the launch before it; no weights: it is not worth the trouble.
+static NextWeights next_weights(const ConvArgs& a, bool to_attn) {
+  NextWeights nw;
+  if (to_attn) attention_qkv_grid(a, &nw);
+  else if (conv_taps_supported(a)) return nw;
+  else if (conv_up_supported(a)) conv_up_grid(a, &nw);
+  else if (conv_ksplit_supported(a)) conv_ksplit_grid(a, &nw);
+  else if (conv_mfma_supported(a)) conv_mfma_grid(a, &nw);
+  else return nw;
+  nw.rows = a.ksize * a.ksize * packed_cin_blocks(a.cin);
+  nw.cout_blocks = packed_cout_blocks(a.cout);
+  nw.w = a.wt;
+  return nw;
+}
+
 // Triples per (sample, group) that the kernel launch_conv picks for this shape emits with stats_ws set; 0: it emits none.
 static int conv_stats_slots(const ConvArgs& a) {
   if (conv_taps_supported(a)) return 0;
@@ -917,6 +932,15 @@ static int launch_step(wmdec_decoder* dec, const WsLayout& L, const Step& st, co
           (*emitted_slots) = conv_stats_slots(a);
           if ((*emitted_slots) > 0) a.stats_ws = st.emit_direct ? ws + L.rows[st.emit_rows] : ws + L.stats_ws;
           if (st.emit_rows >= 0 && !st.emit_direct) { a.rows_out = ws + L.rows[st.emit_rows]; a.tickets = ws + L.conv_tickets; }
+        }
+        const Step* after = &st + 1;
+        while (after < dec->steps.data() + dec->steps.size() && after->kind != Step::CONV) ++after;
+        if (after < dec->steps.data() + dec->steps.size()) {
+          ConvArgs b = step_shape_args(*dec, *after, batch);
+          b.wt = pk + after->w_off;
+          b.groups_norm = after->norm;
+          if (after->sc_src != BUF_NONE) b.x2 = b.wt;   // (that there is one decides the tile)
+          a.next = next_weights(b, after->to_attn == 1);
         }
         rc = st.to_attn == 1 ? launch_attention_qkv(a, ws + L.qkv, s) : launch_conv(a, s);
         break;

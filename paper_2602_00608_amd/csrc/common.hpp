@@ -61,6 +61,14 @@ inline bool is_16bit(int dt) { return dt == WMDEC_BF16 || dt == WMDEC_F16; }
 inline bool valid_dtype(int dt) { return dt == WMDEC_F32 || is_16bit(dt); }
 inline size_t dtype_size(int dt) { return dt == WMDEC_F32 ? 4 : 2; }
 
+// The packed weights of a launch that follows, and which workgroup of it reads which (see warm_weights): its workgroups are `total`,
+// the ones of a channel tile of `tile_blocks` * 32 output channels are `per_tile` consecutive ones.
+struct NextWeights {
+  const void* w = nullptr;
+  int rows = 0, cout_blocks = 0;   // taps * input blocks, output blocks of the packed layout
+  int total = 0, per_tile = 1, tile_blocks = 1;
+};
+
 // Arguments of every convolution launch (3x3 / 1x1, optional fused pieces).
 struct ConvArgs {
   const void* x = nullptr;       // input activations
@@ -100,6 +108,7 @@ struct ConvArgs {
   const void* rows_in = nullptr; // non-null instead of mean / rstd: row triples of x, [n][groups][rows_in_count]
   int rows_in_count = 0;
   float eps = 0.f;               // with rows_in: rstd = 1/sqrt(var + eps)
+  NextWeights next;              // next.w non-null: weights that the launch brings into the L2s for a launch that follows it
 };
 
 // kernels_conv_direct.hip: general VALU convolution (any shape, all dtypes).
@@ -137,6 +146,10 @@ const char* conv_ksplit_label(const ConvArgs& a);
 bool conv_taps_supported(const ConvArgs& a);
 int launch_conv_taps(const ConvArgs& a, hipStream_t s);
 const char* conv_taps_label(const ConvArgs& a);
+// Workgroups of the launch that these arguments make: next->total, per_tile, tile_blocks.
+void conv_mfma_grid(const ConvArgs& a, NextWeights* next);
+void conv_up_grid(const ConvArgs& a, NextWeights* next);
+void conv_ksplit_grid(const ConvArgs& a, NextWeights* next);
 // picks the kernel
 int launch_conv(const ConvArgs& a, hipStream_t s);
 const char* conv_kernel_label(const ConvArgs& a);
@@ -186,6 +199,7 @@ size_t attention_fragment_bytes(int n, int t);
 size_t flash_attention_scratch_bytes(int n, int t);   // partial outputs of the key ranges (none where one range holds all keys)
 int flash_attention_num_launches(int t);
 const char* attention_qkv_label(int dtype);
+void attention_qkv_grid(const ConvArgs& a, NextWeights* next);   // as conv_mfma_grid
 // frag = [q|k|v] of act(x) as a describes it: a 1x1 convolution from 512 to 3 * 512 channels over a.h * a.w tokens
 int launch_attention_qkv(const ConvArgs& a, void* frag, hipStream_t s);
 // o: [n][t][512]

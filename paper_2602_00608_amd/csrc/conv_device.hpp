@@ -1,6 +1,7 @@
 // Pieces shared by the matrix-core convolution kernels: launch parameters, operand loads, the activation on the load
 // path and the row hand-over of the output statistics.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -32,6 +33,7 @@ struct MfmaParams {
   // 1x1 shortcut folded into the contraction (3x3 only): y += W2 * x2 + bias2, x2 [n,h,w,cin2] taken as stored
   const void* x2; const void* w2; const float* bias2;
   int cin2, w2_bytes;
+  NextWeights next;              // next.w non-null: workgroups from `total` on only bring these weights into the L2s
 };
 
 template <typename T> __device__ __forceinline__ void unpack8(const u32x4& v, float* f) {
@@ -56,6 +58,37 @@ __device__ __forceinline__ float silu_from_scaled(float u) {
 // (a global load would add the 64-bit base per fragment), and offsets past the blob read zeros instead of faulting.
 __device__ __forceinline__ u32x4 load_fragment(__amdgpu_buffer_rsrc_t rsrc, int lane16, int off) {
   return __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane16, off, 0);
+}
+
+// Inside a decoder run every layer's weights are new to the L2s, and a launch of one round has nothing to hide their latency under.
+// So the launch before it carries a few workgroups more, which read them: each XCD (workgroup id % 8) those that its workgroups
+// of the coming launch will ask for, by the mapping that all these kernels share (consecutive L on one XCD, channel tiles outermost).  They are dispatched
+// last and run beside the others.
+constexpr int kWarmAhead = 8;   // loads in flight per wavefront, a KiB each
+__device__ __forceinline__ void warm_weights(const NextWeights& nw, int first_id, int waves, int wave, int lane) {
+  const int x = blockIdx.x % 8, groups = (gridDim.x - first_id) / 8;
+  const int per = nw.total / 8, rem = nw.total % 8;
+  const int l0 = x * per + min(x, rem), count = per + (x < rem ? 1 : 0);
+  if (count == 0) return;
+  const int b0 = l0 / nw.per_tile * nw.tile_blocks, b1 = min(((l0 + count - 1) / nw.per_tile + 1) * nw.tile_blocks, nw.cout_blocks);
+  const int blocks = b1 - b0, items = nw.rows * blocks, step = groups * waves;
+  const char* w = reinterpret_cast<const char*>(nw.w) + lane * 16;
+  for (int i0 = (blockIdx.x - first_id) / 8 * waves + wave; i0 < items; i0 += kWarmAhead * step) {
+    u32x4 v[kWarmAhead];
+#pragma unroll
+    for (int k = 0; k < kWarmAhead; ++k) {
+      const int i = min(i0 + k * step, items - 1);
+      v[k] = *reinterpret_cast<const u32x4*>(w + ((size_t)(i / blocks) * nw.cout_blocks + b0 + i % blocks) * 1024);
+    }
+#pragma unroll
+    for (int k = 0; k < kWarmAhead; ++k) asm volatile("" :: "v"(v[k]));
+  }
+}
+// workgroups of `waves` wavefronts that a launch carries for it: two trips through the loads in flight, at most eight on an XCD
+inline int warm_groups(const NextWeights& nw, int waves) {
+  if (!nw.w) return 0;
+  const long items = (long)nw.rows * nw.cout_blocks / std::max(1, std::min(8, (nw.cout_blocks + nw.tile_blocks - 1) / nw.tile_blocks));
+  return 8 * (int)std::min(8L, (items + 2 * kWarmAhead * waves - 1) / (2 * kWarmAhead * waves));
 }
 
 // 16 bytes of every lane to a buffer, at a lane offset plus a wave-uniform one in a scalar register.  The store reads its data late: where
@@ -234,6 +267,7 @@ inline MfmaParams conv_params(const ConvArgs& a, int th, int tw, int tn, int slo
   p.rows_out = (Moments*)a.rows_out; p.tickets = (unsigned*)a.tickets;
   p.rows_in = (const Moments*)a.rows_in; p.rows_in_count = a.rows_in_count; p.eps = a.eps;
   p.x2 = nullptr; p.w2 = nullptr; p.bias2 = nullptr; p.cin2 = 0; p.w2_bytes = 0;
+  p.next = a.next;
   return p;
 }
 // the statistics hand-over a launch is asked for is one its kernel can serve

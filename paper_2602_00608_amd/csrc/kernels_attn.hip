@@ -549,6 +549,12 @@ int flash_attention_num_launches(int t) { return splits_of(t) == 1 ? 1 : 2; }
 
 const char* attention_qkv_label(int dtype) { return dtype == WMDEC_BF16 ? "attn_qkv_kernel<wmdec::bf16_t>" : "attn_qkv_kernel<wmdec::f16_t>"; }
 
+void attention_qkv_grid(const ConvArgs& a, NextWeights* next) {
+  next->per_tile = (a.h * a.w + QT - 1) / QT * a.n;
+  next->tile_blocks = D / 32;
+  next->total = next->per_tile * 3;
+}
+
 int launch_attention_qkv(const ConvArgs& a, void* frag, hipStream_t s) {
   WMDEC_REQUIRE(a.cin == D && a.cout == 3 * D && a.ksize == 1 && is_16bit(a.op_dtype) && a.x_dtype == a.op_dtype && a.bias && !a.res, WMDEC_ERR_UNSUPPORTED,
                 "attention: the projection takes %d channels in a 16-bit type", D);

@@ -81,6 +81,8 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
   const int wn = wave % WN, wk = wave / WN;
   const int lm = lane & 31, lk = lane >> 5;
 
+  if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, NW, wave, lane); return; }
+
   // workgroup id -> (channel tile, sample, spatial tile): the ids of one XCD (id % 8) cover neighbouring tiles of one
   // channel range, so its L2 fetches an eighth of the weights
   int L;
@@ -432,7 +434,7 @@ int launch_act(const ConvArgs& a, hipStream_t s) {
   hipError_t attr_err = hipSuccess;
   std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds); });
   WMDEC_HIP(attr_err);
-  hipLaunchKernelGGL(kern, dim3((unsigned)p.total), dim3(NT), smem, s, p, a.y_dtype == WMDEC_F32 ? 1 : 0);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.total + warm_groups(p.next, WN * WK))), dim3(NT), smem, s, p, a.y_dtype == WMDEC_F32 ? 1 : 0);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
 }
@@ -496,6 +498,14 @@ bool conv_ksplit_supported(const ConvArgs& a) {
   if ((long)a.h * a.w * a.cin >= (1L << 29) || (long)a.h * a.w * a.cout >= (1L << 29) || (long)a.h * a.w * a.cin2 >= (1L << 29)) return false;
   if (a.op_dtype == WMDEC_F32) return a.cin % 32 == 0 && a.cin2 % (a.cin % 64 == 0 ? 64 : 32) == 0 && a.cout % 32 == 0 && !a.stats_ws;
   return is_16bit(a.op_dtype) && a.cin % 64 == 0 && a.cin2 % 64 == 0 && a.cout % 64 == 0 && (long)a.h * a.w * a.cout <= (1L << 20);
+}
+
+void conv_ksplit_grid(const ConvArgs& a, NextWeights* next) {
+  static const struct { int th, tw, blocks; } shapes[] = {{4, 8, 1}, {4, 8, 2}, {4, 16, 2}, {4, 16, 4}, {8, 16, 4}};   // as KsplitTile, and the batched form
+  const auto& t = shapes[batched_form(a) ? 4 : a.op_dtype == WMDEC_F32 ? 0 : (int)pick_ksplit_tile(a)];
+  next->per_tile = ((a.h + t.th - 1) / t.th) * ((a.w + t.tw - 1) / t.tw) * a.n;
+  next->tile_blocks = t.blocks;
+  next->total = next->per_tile * (a.cout / (32 * t.blocks));
 }
 
 int conv_ksplit_stats_slots(const ConvArgs& a) {

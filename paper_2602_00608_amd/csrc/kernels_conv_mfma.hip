@@ -336,6 +336,8 @@ void conv_mfma_kernel(MfmaParams p) {
   const int wm = wave / WN, wn = wave % WN;
   const int lm = lane & 31, lk = lane >> 5;
 
+  if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, WM * WN, wave, lane); return; }
+
   // workgroup id -> (channel tile, sample, spatial tile); consecutive ids of one XCD (id % 8) are neighbours
   int L;
   {
@@ -724,7 +726,7 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
   std::call_once(attr_once[!p.norm ? 0 : (a.silu ? 2 : 1)],
                  [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024); });
   WMDEC_HIP(attr_err);
-  hipLaunchKernelGGL(kern, dim3((unsigned)p.total), dim3(NT), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.total + warm_groups(p.next, WM * WN))), dim3(NT), smem, s, p);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
 }
@@ -859,6 +861,13 @@ void conv_mfma_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles
   *tile_rows = (a.h + ts.th - 1) / ts.th;
   *channel_tiles = (a.cout + tn - 1) / tn;
   *tiles_per_row = (a.w + ts.tw - 1) / ts.tw;
+}
+
+void conv_mfma_grid(const ConvArgs& a, NextWeights* next) {
+  const TileShape& ts = kTiles[pick_tile(a)];
+  next->per_tile = ((a.h + ts.th - 1) / ts.th) * ((a.w + ts.tw - 1) / ts.tw) * a.n;
+  next->tile_blocks = ts.wn * ts.ni;
+  next->total = next->per_tile * ((a.cout + 32 * next->tile_blocks - 1) / (32 * next->tile_blocks));
 }
 
 // the instantiation a launch would use, spelled like a profiler prints it

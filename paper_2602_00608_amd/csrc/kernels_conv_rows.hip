@@ -195,6 +195,8 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
   const int tid = threadIdx.x, lane = tid & 63;
   const int wn = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform: keeps the per-wave addresses scalar
 
+  if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, WN, wn, lane); return; }
+
   // workgroup id -> (channel tile, sample, spatial tile); consecutive ids of one XCD (id % 8) are neighbours
   int L;
   {
@@ -505,7 +507,7 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
   std::call_once(attr_once[!p.norm ? 0 : (a.silu ? 2 : 1)],
                  [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024); });
   WMDEC_HIP(attr_err);
-  hipLaunchKernelGGL(kern, dim3((unsigned)p.total), dim3(256), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.total + warm_groups(p.next, 4))), dim3(256), smem, s, p);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
 }

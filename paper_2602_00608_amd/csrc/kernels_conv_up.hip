@@ -59,6 +59,7 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
   const int tid = threadIdx.x - wk * NTK;   // within the group
   unsigned char* smem = smem_all + wk * 2 * BUFB;
   const int px = lane & 15, oct = lane >> 4;
+  if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, 4, wave, lane); return; }
   int L;   // consecutive ids of one XCD (id % 8) are neighbours
   {
     const int i = blockIdx.x, per = p.total / 8, rem = p.total % 8;
@@ -324,7 +325,7 @@ int launch_up(const ConvArgs& a, hipStream_t s) {
   constexpr size_t kSmem = 2 * BUFB, kSplitSmem = 4 * BUFB;   // patches of one group, of two
   void (*kern)(MfmaParams, int) = split ? (fine_moments(a) ? conv_up_kernel<T, kH, 1, true> : conv_up_kernel<T, kH, 1, false>)
                                         : (fine_moments(a) ? conv_up_kernel<T, kH, kWN, true> : conv_up_kernel<T, kH, kWN, false>);
-  hipLaunchKernelGGL(kern, dim3((unsigned)p.total), dim3(256), split ? kSplitSmem : kSmem, s, p, a.y_dtype == WMDEC_F32 ? 1 : 0);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.total + warm_groups(p.next, 4))), dim3(256), split ? kSplitSmem : kSmem, s, p, a.y_dtype == WMDEC_F32 ? 1 : 0);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
 }
@@ -351,6 +352,12 @@ void conv_up_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, 
   *tile_rows = (a.h / 2 + TH - 1) / TH;
   *channel_tiles = a.cout / tile_channels(a);
   *tiles_per_row = (a.w / 2 + TW - 1) / TW;
+}
+
+void conv_up_grid(const ConvArgs& a, NextWeights* next) {
+  next->per_tile = ((a.h / 2 + TH - 1) / TH) * ((a.w / 2 + TW - 1) / TW) * a.n;
+  next->tile_blocks = tile_channels(a) / 32;
+  next->total = next->per_tile * (a.cout / tile_channels(a));
 }
 
 const char* conv_up_label(const ConvArgs& a) {
