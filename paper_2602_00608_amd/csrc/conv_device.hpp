@@ -34,7 +34,31 @@ struct MfmaParams {
   const void* x2; const void* w2; const float* bias2;
   int cin2, w2_bytes;
   NextWeights next;              // next.w non-null: workgroups from `total` on only bring these weights into the L2s
+  unsigned inv_tiles_n, inv_tiles, inv_tiles_x;   // see div_rem: of tiles_x * tiles_y * n, tiles_x * tiles_y, tiles_x
 };
+
+// a / d and its remainder, inv = reciprocal(d): the product's high half is the quotient or one less.  (The compiler's division is some
+// thirty dependent instructions, and a workgroup starts with a chain of them.)
+inline unsigned reciprocal(unsigned d) { return d == 1 ? 0xffffffffu : (unsigned)((1ull << 32) / d); }
+__device__ __forceinline__ int div_rem(unsigned a, unsigned d, unsigned inv, int& rem) {
+  unsigned q = __umulhi(a, inv), r = a - q * d;
+  if (r >= d) { ++q; r -= d; }
+  rem = (int)r;
+  return (int)q;
+}
+// workgroup id -> (channel tile, sample, spatial tile, its row and column); the ids of one XCD (id % 8) cover neighbouring tiles of
+// one channel range, so that its L2 fetches an eighth of the weights
+struct WorkTile { int nt, n, tile, y, x; };
+__device__ __forceinline__ WorkTile workgroup_tile(const MfmaParams& p) {
+  const int i = blockIdx.x, per = p.total / 8, rem = p.total % 8;
+  const int x = i % 8, j = i / 8, tiles = p.tiles_x * p.tiles_y;
+  WorkTile t;
+  int in_nt;
+  t.nt = div_rem(x * per + (x < rem ? x : rem) + j, tiles * p.n, p.inv_tiles_n, in_nt);
+  t.n = div_rem(in_nt, tiles, p.inv_tiles, t.tile);
+  t.y = div_rem(t.tile, p.tiles_x, p.inv_tiles_x, t.x);
+  return t;
+}
 
 template <typename T> __device__ __forceinline__ void unpack8(const u32x4& v, float* f) {
   f[0] = unpack_lo<T>(v.x); f[1] = unpack_hi<T>(v.x); f[2] = unpack_lo<T>(v.y); f[3] = unpack_hi<T>(v.y);
@@ -123,48 +147,85 @@ template <typename T, int ACT, bool PIN = false> __device__ __forceinline__ uint
   return wv;
 }
 
-// (mean, rstd) of a group from the `count` triples of its row, merged by LANES consecutive lanes (all of them active), eight
-// loads in flight per lane: the mean first, then the differences to it and their squares, from the same registers.  (A chain
+// (mean, rstd) of G groups from the `count` triples of their rows, each merged by LANES consecutive lanes (all of them active), K
+// loads in flight per lane and group: the mean first, then the differences to it and their squares, from the same registers.  (A chain
 // of pairwise merges has a reciprocal each and stood in front of every layer's first chunk; one pass of sums about the
 // first triple's mean cancels where that triple is an outlier: 1e-5 of the variance at 100 standard deviations.)  Triples
-// past 8 * LANES are summed about the mean of those, at least half of the row, which costs a factor of two at most.
-template <int LANES>
-__device__ __forceinline__ float2 merge_row(const Moments* row, int count, int sub, float eps) {
-  const float first = row[0].mean;
-  Moments t[8];
-  auto load = [&](int r0) {
+// past K * LANES are summed about the mean of those, at least half of the row, which costs a factor of two at most.
+template <int LANES, int K, int G>
+__device__ __forceinline__ void merge_rows(const Moments* const (&row)[G], int count, int sub, float eps, float2 (&out)[G]) {
+  float first[G];
+  Moments t[G][K];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int r = r0 + LANES * k;
-      t[k] = row[min(r, count - 1)];
-      if (r >= count) { t[k].n = 0.f; t[k].m2 = 0.f; }
-    }
-  };
-  float n = 0.f, s = 0.f, q = 0.f;
-  auto add = [&](float shift) {
+  for (int g = 0; g < G; ++g) {
+    first[g] = row[g][0].mean;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float d = t[k].n > 0.f ? t[k].mean - shift : 0.f, nd = t[k].n * d;   // an empty triple's mean has no meaning
-      n += t[k].n; s += nd; q += fmaf(nd, d, t[k].m2);
-    }
-  };
-  load(sub);
-  add(first);
-  const float head = lanes_sum<LANES>(n);
-  const float mean = first + lanes_sum<LANES>(s) * __builtin_amdgcn_rcpf(head);
-  n = 0.f; s = 0.f; q = 0.f;
-  add(mean);
-  if (count > 8 * LANES) {
-    n = 0.f;
-    for (int r0 = sub + 8 * LANES; r0 < count + sub; r0 += 8 * LANES) { load(r0); add(mean); }
-    n = head + lanes_sum<LANES>(n);
-  } else {
-    n = head;
+    for (int k = 0; k < K; ++k) t[g][k] = row[g][min(sub + LANES * k, count - 1)];
   }
-  s = lanes_sum<LANES>(s); q = lanes_sum<LANES>(q);
-  const float d = s * __builtin_amdgcn_rcpf(n);     // (also what the roundings of `mean` left)
-  q -= s * d;
-  return make_float2(mean + d, 1.0f / sqrtf((q < 0.f ? 0.f : q) / n + eps));   // (NaN stays NaN)
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    auto past = [&](int r0) {
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (r0 + LANES * k >= count) { t[g][k].n = 0.f; t[g][k].m2 = 0.f; }
+    };
+    float n = 0.f, s = 0.f, q = 0.f;
+    auto add = [&](float shift) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const float d = t[g][k].n > 0.f ? t[g][k].mean - shift : 0.f, nd = t[g][k].n * d;   // an empty triple's mean has no meaning
+        n += t[g][k].n; s += nd; q += fmaf(nd, d, t[g][k].m2);
+      }
+    };
+    past(sub);
+    add(first[g]);
+    const float head = lanes_sum<LANES>(n);
+    const float mean = first[g] + lanes_sum<LANES>(s) * __builtin_amdgcn_rcpf(head);
+    n = 0.f; s = 0.f; q = 0.f;
+    add(mean);
+    if (K == 8 && count > K * LANES) {
+      n = 0.f;
+      for (int r0 = sub + K * LANES; r0 < count + sub; r0 += K * LANES) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) t[g][k] = row[g][min(r0 + LANES * k, count - 1)];
+        past(r0);
+        add(mean);
+      }
+      n = head + lanes_sum<LANES>(n);
+    } else {
+      n = head;
+    }
+    s = lanes_sum<LANES>(s); q = lanes_sum<LANES>(q);
+    const float d = s * __builtin_amdgcn_rcpf(n);     // (also what the roundings of `mean` left)
+    q -= s * d;
+    out[g] = make_float2(mean + d, 1.0f / sqrtf((q < 0.f ? 0.f : q) / n + eps));   // (NaN stays NaN)
+  }
+}
+// ... of all groups of a sample into s_stat, by NT threads: as many loads as the row needs (a triple that does not exist adds zeros,
+// so the number changes no bits), and of two groups at a time where the threads do not reach round.
+template <int LANES, int NT>
+__device__ __forceinline__ void merge_sample(const Moments* rows, int groups, int count, int tid, float eps, float2* s_stat) {
+  constexpr int STEP = NT / LANES;
+  const int sub = tid % LANES;
+  auto all = [&](auto k_c, auto g_c) __attribute__((always_inline)) {
+    constexpr int K = decltype(k_c)::value, G = decltype(g_c)::value;
+    for (int g0 = tid / LANES; g0 < groups; g0 += G * STEP) {
+      const Moments* row[G];
+      float2 st[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) row[g] = rows + (size_t)min(g0 + g * STEP, groups - 1) * count;
+      merge_rows<LANES, K, G>(row, count, sub, eps, st);
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+        if (sub == 0 && g0 + g * STEP < groups) s_stat[g0 + g * STEP] = st[g];
+    }
+  };
+  const std::integral_constant<int, 1> one{};
+  const std::integral_constant<int, (STEP < 32 ? 2 : 1)> pair{};
+  if (count <= LANES) all(one, pair);
+  else if (count <= 2 * LANES) all(std::integral_constant<int, 2>{}, pair);
+  else if (count <= 4 * LANES) all(std::integral_constant<int, 4>{}, pair);
+  else all(std::integral_constant<int, 8>{}, one);
 }
 
 // Sums over lanes in the vector ALU.  row_rotate: the value N lanes further round the row of 16; quad_xor: of lane ^ N (1, 2);
@@ -184,6 +245,25 @@ template <int W> __device__ __forceinline__ float swap_sum(float v) {
   unsigned a = r.x, b = r.y;
   asm volatile("" : "+v"(a), "+v"(b));
   return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
+
+// Moments of a group's channels (cpg consecutive lanes, a power of two up to 32) over the same pixels, in all of these lanes: the mean
+// first, then the squares about it.
+__device__ __forceinline__ Moments merge_channels(Moments m, int cpg) {
+  auto sum = [&](float v) {
+    auto dpp = [](float x, auto c) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(c)::value, 0xf, 0xf, true)); };
+    if (cpg > 1) v += quad_xor<1>(v);
+    if (cpg > 2) v += quad_xor<2>(v);
+    if (cpg > 4) v += dpp(v, std::integral_constant<int, 0x141>{});   // mirrored in eight lanes
+    if (cpg > 8) v += dpp(v, std::integral_constant<int, 0x140>{});   // ... in sixteen
+    if (cpg > 16) v = swap_sum<16>(v);
+    return v;
+  };
+  const float inv = __builtin_amdgcn_rcpf((float)cpg);   // (a power of two: exact)
+  const float mean = sum(m.mean) * inv, d = m.mean - mean;
+  const float rest = sum(d) * inv;                       // what the roundings of the mean left
+  const float m2 = sum(fmaf(m.n * d, d, m.m2)) - m.n * (float)cpg * rest * rest;
+  return Moments{m.n * (float)cpg, mean + rest, m2 < 0.f ? 0.f : m2};   // (NaN stays NaN)
 }
 
 // Moments of one channel over a block of 4 x W pixels (rows x cols of them valid) in LDS, pixels PX and image rows ROW floats apart:
@@ -261,6 +341,7 @@ inline MfmaParams conv_params(const ConvArgs& a, int th, int tw, int tn, int slo
   p.n = a.n; p.h = a.h; p.w_out = a.w; p.cin = a.cin; p.cout = a.cout;
   p.tiles_x = (w_t + tw - 1) / tw; p.tiles_y = (h_t + th - 1) / th; p.ntiles = (a.cout + tn - 1) / tn;
   p.total = p.tiles_x * p.tiles_y * p.ntiles * a.n;
+  p.inv_tiles_n = reciprocal(p.tiles_x * p.tiles_y * a.n); p.inv_tiles = reciprocal(p.tiles_x * p.tiles_y); p.inv_tiles_x = reciprocal(p.tiles_x);
   p.cin_blocks = packed_cin_blocks(a.cin); p.cout_blocks = packed_cout_blocks(a.cout); p.y_nchw = a.y_nchw;
   p.stats = (Moments*)a.stats_ws; p.stats_groups = a.stats_groups; p.stats_cpg = a.stats_groups > 0 ? a.cout / a.stats_groups : 1;
   p.stats_slots = p.tiles_x * p.tiles_y * slots_per_tile;

@@ -89,11 +89,7 @@ __global__ __launch_bounds__(QNT, 2) void attn_qkv_kernel(QkvParams p) {
     const float ga = p.gamma[tid], be = p.beta[tid];      // one channel per thread
     static_assert(QNT == D, "one channel per thread");
     if (p.rows_in) {
-      constexpr int LANES = 8;
-      for (int g = tid / LANES; g < p.groups; g += QNT / LANES) {
-        const float2 m = merge_row<LANES>(p.rows_in + (size_t)(n * p.groups + g) * p.rows_in_count, p.rows_in_count, tid % LANES, p.eps);
-        if (tid % LANES == 0) s_stat[g] = m;
-      }
+      merge_sample<8, QNT>(p.rows_in + (size_t)n * p.groups * p.rows_in_count, p.groups, p.rows_in_count, tid, p.eps, s_stat);
     } else {
       for (int g = tid; g < p.groups; g += QNT) s_stat[g] = make_float2(p.mean[n * p.groups + g], p.rstd[n * p.groups + g]);
     }

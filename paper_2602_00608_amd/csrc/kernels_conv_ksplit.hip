@@ -83,19 +83,9 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
 
   if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, NW, wave, lane); return; }
 
-  // workgroup id -> (channel tile, sample, spatial tile): the ids of one XCD (id % 8) cover neighbouring tiles of one
-  // channel range, so its L2 fetches an eighth of the weights
-  int L;
-  {
-    const int i = blockIdx.x, per = p.total / 8, rem = p.total % 8;
-    const int x = i % 8, j = i / 8;
-    L = x * per + (x < rem ? x : rem) + j;
-  }
-  const int tiles = p.tiles_x * p.tiles_y;
-  const int nt = L / (tiles * p.n);
-  const int n = (L / tiles) % p.n;
-  const int tile = L % tiles;
-  const int ty0 = (tile / p.tiles_x) * TH, tx0 = (tile % p.tiles_x) * TW;
+  const WorkTile wt = workgroup_tile(p);
+  const int nt = wt.nt, n = wt.n;
+  const int ty0 = wt.y * TH, tx0 = wt.x * TW;
   const int co0 = nt * TN;
   const int rounds = p.cin / KC;
 
@@ -218,12 +208,7 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
     float gpre = 0.f, bpre = 0.f;                    // requested together with the triples: one round trip less
     if (tid < p.cin) { gpre = p.gamma[tid]; bpre = p.beta[tid]; }
     if (p.rows_in) {
-      const int sub = tid % TPG;
-      for (int g = tid / TPG; g < p.groups; g += NT / TPG) {
-        const Moments* row = p.rows_in + (size_t)(n * p.groups + g) * p.rows_in_count;
-        const float2 st = merge_row<TPG>(row, p.rows_in_count, sub, p.eps);
-        if (sub == 0) s_stat[g] = st;   // (at most 128 triples per group)
-      }
+      merge_sample<TPG, NT>(p.rows_in + (size_t)n * p.groups * p.rows_in_count, p.groups, p.rows_in_count, tid, p.eps, s_stat);   // (at most 128 triples per group)
     } else {
       for (int g = tid; g < p.groups; g += NT) s_stat[g] = make_float2(p.mean[n * p.groups + g], p.rstd[n * p.groups + g]);
     }
@@ -400,7 +385,7 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
       if (cols <= 0) continue;
       const float* src = red + (size_t)(8 * b) * RR + c;
       const Sums own = two_row_sums<8, TW * RR, RR>(src + 2 * half * TW * RR, src[0], rows - 2 * half, cols);
-      const Moments m = merge_to_first(block_moments(Sums{swap_sum<32>(own.s), swap_sum<32>(own.q)}, src[0], rows, cols), lane, p.stats_cpg);
+      const Moments m = merge_channels(block_moments(Sums{swap_sum<32>(own.s), swap_sum<32>(own.q)}, src[0], rows, cols), p.stats_cpg);
       if (half == 0 && c % p.stats_cpg == 0)
         p.stats[((size_t)n * p.stats_groups + (co0 + c) / p.stats_cpg) * p.stats_slots + (ty0 / 4) * ((p.w_out + 7) / 8) + x0 / 8] = m;
     }

@@ -177,7 +177,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
         const int rows = min(MTH, p.h - y0), cols = min(MTW, p.w - x0);
         Moments m = block_moments(two_row_sums<MTW, MTW * RW, RW>(src, src[0], rows, cols) +
                                   two_row_sums<MTW, MTW * RW, RW>(src + 2 * MTW * RW, src[0], rows - 2, cols), src[0], rows, cols);
-        m = merge_to_first(m, lane, p.cpg);
+        m = merge_channels(m, p.cpg);
         if ((lm & (p.cpg - 1)) == 0 && m.n > 0.f) dst[(size_t)((co_w + lm) / p.cpg) * p.stats_stride + lk] = m;
       }
     } else if (mi + 1 == MI) {
@@ -338,18 +338,9 @@ void conv_mfma_kernel(MfmaParams p) {
 
   if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, WM * WN, wave, lane); return; }
 
-  // workgroup id -> (channel tile, sample, spatial tile); consecutive ids of one XCD (id % 8) are neighbours
-  int L;
-  {
-    const int i = blockIdx.x, per = p.total / 8, rem = p.total % 8;
-    const int x = i % 8, j = i / 8;
-    L = x * per + (x < rem ? x : rem) + j;
-  }
-  const int tiles = p.tiles_x * p.tiles_y;
-  const int nt = L / (tiles * p.n);
-  const int n = (L / tiles) % p.n;
-  const int tile = L % tiles;
-  const int ty0 = (tile / p.tiles_x) * TH, tx0 = (tile % p.tiles_x) * TW;
+  const WorkTile wt = workgroup_tile(p);
+  const int nt = wt.nt, n = wt.n, tile = wt.tile;
+  const int ty0 = wt.y * TH, tx0 = wt.x * TW;
   const int co0 = nt * TN;
 
   // the bias of the lane's channel columns, for the epilogue: requested here, as a load there would be waited for, unless the
@@ -568,12 +559,7 @@ void conv_mfma_kernel(MfmaParams p) {
         gpre[j] = p.gamma[c]; bpre[j] = p.beta[c];
       }
       constexpr int LANES = QUARTERS ? 16 : 8;
-      const int sub = tid % LANES;
-      for (int g = tid / LANES; g < p.groups; g += NT / LANES) {
-        const Moments* row = p.rows_in + (size_t)(n * p.groups + g) * p.rows_in_count;
-        const float2 m = merge_row<LANES>(row, p.rows_in_count, sub, p.eps);
-        if (sub == 0) s_stat[g] = m;
-      }
+      merge_sample<LANES, NT>(p.rows_in + (size_t)n * p.groups * p.rows_in_count, p.groups, p.rows_in_count, tid, p.eps, s_stat);
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < PRE; ++j) {
@@ -691,7 +677,7 @@ void conv_mfma_kernel(MfmaParams p) {
   if constexpr (QUARTERS) store(total);
   else store(acc);
 
-  if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, co0, TN, WM, tid, lane);
+  if (p.rows_out) hand_over_row<NT>(p, n, wt.y, nt, co0, TN, WM, tid, lane);
 }
 
 template <typename T, typename TO, int TH, int TW, int WM, int WN, int NI, int KS, int KC, int RING = 0, int MODE = kPlain>

@@ -197,18 +197,9 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
 
   if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, WN, wn, lane); return; }
 
-  // workgroup id -> (channel tile, sample, spatial tile); consecutive ids of one XCD (id % 8) are neighbours
-  int L;
-  {
-    const int i = blockIdx.x, per = p.total / 8, rem = p.total % 8;
-    const int x = i % 8, j = i / 8;
-    L = x * per + (x < rem ? x : rem) + j;
-  }
-  const int tiles = p.tiles_x * p.tiles_y;
-  const int nt = L / (tiles * p.n);
-  const int n = (L / tiles) % p.n;
-  const int tile = L % tiles;
-  const int ty0 = (tile / p.tiles_x) * TH, tx0 = (tile % p.tiles_x) * TW;
+  const WorkTile wt = workgroup_tile(p);
+  const int nt = wt.nt, n = wt.n, tile = wt.tile;
+  const int ty0 = wt.y * TH, tx0 = wt.x * TW;
   const int co0 = nt * TN, co_w = co0 + wn * NI * 32;
 
   if (tid < TN) s_bias[tid] = (p.bias ? p.bias[co0 + tid] : 0.f) + (p.bias2 ? p.bias2[co0 + tid] : 0.f);
@@ -339,11 +330,7 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
         gpre[j] = p.gamma[c]; bpre[j] = p.beta[c];
       }
       constexpr int LANES = 8;
-      const int sub = tid % LANES;
-      for (int g = tid / LANES; g < p.groups; g += NT / LANES) {
-        const float2 m = merge_row<LANES>(p.rows_in + (size_t)(n * p.groups + g) * p.rows_in_count, p.rows_in_count, sub, p.eps);
-        if (sub == 0) s_stat[g] = m;
-      }
+      merge_sample<LANES, NT>(p.rows_in + (size_t)n * p.groups * p.rows_in_count, p.groups, p.rows_in_count, tid, p.eps, s_stat);
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < PRE; ++j) {
@@ -477,7 +464,7 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
     else epilogue<T, TO, TH, NI, false, false, MODE>(acc, rv, bias_w, lane, ty0, tx0, co_w, ep);
   }
 
-  if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, co0, TN, WM, tid, lane);
+  if (p.rows_out) hand_over_row<NT>(p, n, wt.y, nt, co0, TN, WM, tid, lane);
 }
 
 template <typename T, typename TO, int TH, int NI, int MODE, int RING>

@@ -60,15 +60,9 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
   unsigned char* smem = smem_all + wk * 2 * BUFB;
   const int px = lane & 15, oct = lane >> 4;
   if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, 4, wave, lane); return; }
-  int L;   // consecutive ids of one XCD (id % 8) are neighbours
-  {
-    const int i = blockIdx.x, per = p.total / 8, rem = p.total % 8;
-    const int x = i % 8, j = i / 8;
-    L = x * per + (x < rem ? x : rem) + j;
-  }
-  const int tiles = p.tiles_x * p.tiles_y;
-  const int nt = L / (tiles * p.n), n = (L / tiles) % p.n, tile = L % tiles;
-  const int ty0 = (tile / p.tiles_x) * TH, tx0 = (tile % p.tiles_x) * TW;
+  const WorkTile wt = workgroup_tile(p);
+  const int nt = wt.nt, n = wt.n, tile = wt.tile;
+  const int ty0 = wt.y * TH, tx0 = wt.x * TW;
   const int h_in = p.h >> 1, w_in = p.w_out >> 1;
   const int co_w = nt * TN + wn * 16;
 
@@ -292,7 +286,7 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
       store_device(dst + (size_t)((co_w + 4 * oct) / cpg) * p.stats_slots, mq[0]);
     }
   }
-  if (p.rows_out) hand_over_row<NT>(p, n, tile / p.tiles_x, nt, nt * TN, TN, KS * (cpg > 16 ? 2 : 1), threadIdx.x, lane);
+  if (p.rows_out) hand_over_row<NT>(p, n, wt.y, nt, nt * TN, TN, KS * (cpg > 16 ? 2 : 1), threadIdx.x, lane);
 }
 
 // 64 channels a workgroup, 16 a wavefront, two workgroups per compute unit: their epilogues
