@@ -222,19 +222,15 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
   // the spare pixel slot behind the patch; its real slot is zeroed once, here, in both buffers.
   const int cvec = tid % VPP;
   const char* xin = reinterpret_cast<const char*>(p.x) + (size_t)n * p.h * p.w_out * p.cin * sizeof(T);   // uniform base
-  auto pixel_of = [&](int i, int& at) -> int {   // index of vector i's source pixel in the sample, or -1; at: its slot in a patch
-    const int hp = (tid + i * NT) / VPP;
-    const int hy = hp / PW, hx = hp % PW;
-    const int gy = ty0 + hy - 1, gx = tx0 + hx - 1;
-    at = hp < HP ? hy * ROW + hx * PS : SPARE;
-    return hp < HP && gy >= 0 && gy < p.h && gx >= 0 && gx < p.w_out ? gy * p.w_out + gx : -1;
-  };
   int src_off[NV];          // byte offset of the vector in the first chunk of x
   int dst_off[NV];          // element offset of its slot in a patch
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    int at;
-    const int pix = pixel_of(i, at);
+    const int hp = (tid + i * NT) / VPP;
+    const int hy = hp / PW, hx = hp % PW;
+    const int gy = ty0 + hy - 1, gx = tx0 + hx - 1;
+    const int at = hp < HP ? hy * ROW + hx * PS : SPARE;
+    const int pix = hp < HP && gy >= 0 && gy < p.h && gx >= 0 && gx < p.w_out ? gy * p.w_out + gx : -1;   // its source in the sample
     src_off[i] = max(pix, 0) * p.cin * (int)sizeof(T) + cvec * 16;
     dst_off[i] = (pix >= 0 ? at : SPARE) + cvec * 8;
     if (pix < 0 && at != SPARE) {
@@ -257,52 +253,55 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
 
   // ---- shortcut phase (a second input): acc = W2 * x2 over the tile's own pixels, a 1x1
   // contraction over cin2 channels taken as stored (no normalisation).  Chunks go through the same
-  // two LDS buffers with the halo layout (only the centre tap is read), loads two chunks ahead; the main
+  // two LDS buffers, to their pixels' slots in the patch; the main
   // loop below then adds the 3x3 contraction to the same accumulators, so the shortcut tensor never exists in
-  // memory and the epilogue adds both biases.
+  // memory and the epilogue adds both biases.  A chunk is little work (16 MFMAs a wavefront and 32 channels), so input and weights travel three
+  // chunks ahead.
   if (p.x2) {
+    constexpr int NC = TH * 16 * VPP / NT, AHEAD = 3;   // vectors of a thread: the pixels without the halo
+    static_assert(NC * NT == TH * 16 * VPP, "whole vectors");
     const char* xin2 = reinterpret_cast<const char*>(p.x2) + (size_t)n * p.h * p.w_out * p.cin2 * sizeof(T);
     const int nch2 = p.cin2 / KC;
-    int src2[NV];
+    int src2[NC], dst2[NC];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      int at;
-      src2[i] = max(pixel_of(i, at), 0) * p.cin2 * (int)sizeof(T) + cvec * 16;
+    for (int i = 0; i < NC; ++i) {
+      const int v = (tid + i * NT) / VPP, y = v / 16, x = v % 16;
+      const bool inside = ty0 + y < p.h && tx0 + x < p.w_out;   // (the others' slots stay zero: the 3x3 taps read them)
+      src2[i] = (inside ? (ty0 + y) * p.w_out + tx0 + x : 0) * p.cin2 * (int)sizeof(T) + cvec * 16;
+      dst2[i] = (inside ? (y + 1) * ROW + (x + 1) * PS : SPARE) + cvec * 8;
     }
-    auto issue2 = [&](int chunk) {
-      const int cb = min(chunk, nch2 - 1) * KC * (int)sizeof(T);
-#pragma unroll
-      for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(xin2 + (unsigned)(src2[i] + cb));
-    };
-    auto store_all = [&](T* buf) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) *reinterpret_cast<u32x4*>(buf + dst_off[i]) = raw[i];
-    };
     const __amdgpu_buffer_rsrc_t wrsrc2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w2), 0, p.w2_bytes, 0x00020000);
-    u32x4 wa[2 * NI], wb[2 * NI];   // both tiles of every 32 channels, of this chunk and the next
+    u32x4 x2[AHEAD][NC], w2[AHEAD][2 * NI];   // of chunk c in place c % AHEAD; past the last chunk: a harmless reload
+    auto issue2 = [&](u32x4 (&v)[NC], int chunk) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) v[i] = *reinterpret_cast<const u32x4*>(xin2 + (unsigned)(src2[i] + min(chunk, nch2 - 1) * KC * (int)sizeof(T)));
+    };
     auto load2 = [&](u32x4 (&f)[2 * NI], int chunk) {
 #pragma unroll
       for (int j = 0; j < 2 * NI; ++j) f[j] = load_fragment(wrsrc2, lane_w, wcol + min(chunk, nch2 - 1) * 2 * kk_stride + j / 2 * 1024 + 64 * (j % 2));
     };
-    load2(wa, 0);
-    issue2(0);
-    store_all(s_a);
-    issue2(1);
-    __syncthreads();
-    for (int c = 0; c < nch2; ++c) {
-      load2(wb, c + 1);
-      const T* ctr = s_a + (c & 1) * BUF + row_off + ROW + PS;
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) { issue2(x2[k], k); load2(w2[k], k); }
+    auto chunk2 = [&](auto k_c, int c) {
+      constexpr int k = decltype(k_c)::value;
+      T* buf = s_a + (c & 1) * BUF;
+#pragma unroll
+      for (int i = 0; i < NC; ++i) *reinterpret_cast<u32x4*>(buf + dst2[i]) = x2[k][i];
+      issue2(x2[k], c + AHEAD);
+      __syncthreads();   // (the other buffer is rewritten only behind the next barrier)
+      const T* ctr = buf + row_off + ROW + PS;
 #pragma unroll
       for (int r = 0; r < TH; ++r) {
         const u32x4 px = *reinterpret_cast<const u32x4*>(ctr + r * ROW);
 #pragma unroll
-        for (int j = 0; j < 2 * NI; ++j) acc[r][j] = Mma<T>::m16(wa[j], px, acc[r][j]);
+        for (int j = 0; j < 2 * NI; ++j) acc[r][j] = Mma<T>::m16(w2[k][j], px, acc[r][j]);
       }
-#pragma unroll
-      for (int j = 0; j < 2 * NI; ++j) wa[j] = wb[j];
-      if (c + 1 < nch2) store_all(s_a + ((c + 1) & 1) * BUF);
-      issue2(c + 2);
-      __syncthreads();
+      load2(w2[k], c + AHEAD);
+    };
+    for (int c = 0; c < nch2; c += AHEAD) {
+      chunk2(std::integral_constant<int, 0>{}, c);
+      if (c + 1 < nch2) chunk2(std::integral_constant<int, 1>{}, c + 1);
+      if (c + 2 < nch2) chunk2(std::integral_constant<int, 2>{}, c + 2);
     }
   }
 
