@@ -1,8 +1,9 @@
-"""Build libwmdec.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Build libwmdec.so (HIP, gfx950 only) in-tree with hipcc, and the native Python binding with g++."""
 import concurrent.futures
 import os
 import subprocess
 import sys
+import sysconfig
 
 if __package__:
     from . import asm_check
@@ -13,6 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libwmdec.so")
+BINDING = os.path.join(HERE, "_binding.so")
 
 SOURCES = ["api.cpp", "kernels_gn.hip", "kernels_conv_direct.hip", "kernels_conv_mfma.hip", "kernels_conv_rows.hip", "kernels_conv_ksplit.hip", "kernels_conv_up.hip",
            "kernels_conv_taps.hip", "kernels_misc.hip", "kernels_attn.hip", "kernels_adaln.hip"]
@@ -63,10 +65,28 @@ def _compile(src, force):
     return obj
 
 
+def build_binding(force=True):
+    """The native Python module (csrc/binding.cpp) against the installed torch."""
+    src = os.path.join(CSRC, "binding.cpp")
+    if not force and os.path.exists(BINDING) and os.path.getmtime(BINDING) >= max(os.path.getmtime(src), _headers_mtime()):
+        return BINDING
+    import torch
+    from torch.utils import cpp_extension
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), src, "-o", BINDING]
+    cmd += ["-I" + d for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
+    cmd += ["-L" + d for d in cpp_extension.library_paths()] + ["-lc10", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for binding.cpp:\n%s" % r.stderr)
+    return BINDING
+
+
 def build(force=True, jobs=8):
     os.makedirs(OBJ, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
+        binding = ex.submit(build_binding, force)
         objs = list(ex.map(lambda s: _compile(s, force), SOURCES))
+        binding.result()
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.check_call(cmd)
     return LIB

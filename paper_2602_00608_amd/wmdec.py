@@ -1,7 +1,9 @@
-"""ctypes binding of libwmdec.so: same names as include/wmdec.h, argument
-marshalling only (torch tensors -> device pointers, current stream -> void*).
+"""Binding of libwmdec.so: same names as include/wmdec.h, argument
+marshalling only (torch tensors -> device pointers, current stream -> void*):
+ctypes, and for the operators that a layer is made of a native module
+(csrc/binding.cpp), whose calls cost a tenth.
 Every computation happens in the library's HIP kernels; there is no fallback:
-if the shared library is missing, loading raises."""
+if the shared library or the native module is missing, loading raises."""
 import ctypes
 import os
 
@@ -89,11 +91,16 @@ SIGNATURES = {
 }
 
 _lib = None
+_native = None   # the native module, bound to the loaded library
+
+# entry points that the native module calls, in the order of its bind()
+_BOUND = ("wmdec_gn_stats", "wmdec_gn_silu_conv3x3", "wmdec_gn_conv1x1", "wmdec_gn_silu_conv3x3_shortcut",
+          "wmdec_gn_silu_conv3x3_stats", "wmdec_upsample2x_conv3x3", "wmdec_attention", "wmdec_adaln_fused_projection")
 
 
 def lib():
     """The loaded shared library; raises if it has not been built."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("libwmdec.so is missing (%s): build it with "
@@ -103,8 +110,20 @@ def lib():
             fn = getattr(l, name)
             fn.restype = res
             fn.argtypes = args
-        _lib = l
+        try:
+            from paper_2602_00608_amd import _binding
+        except ImportError as e:
+            raise RuntimeError("the native binding is missing (%s): build it with "
+                               "`python -m paper_2602_00608_amd.build`; there is no fallback path" % e) from e
+        _binding.bind(*(ctypes.cast(getattr(l, name), _vp).value for name in _BOUND))
+        _lib, _native = l, _binding
     return _lib
+
+
+def _ops():
+    if _native is None:
+        lib()
+    return _native
 
 
 def last_error():
@@ -147,9 +166,7 @@ def gn_stats_workspace_bytes(n, h, w, c, groups):
 
 def gn_stats(x, groups, eps, mean, rstd, workspace):
     """x: [n,h,w,c] NHWC tensor; mean, rstd: fp32 [n*groups]; workspace: uint8 tensor."""
-    n, h, w, c = x.shape
-    _check(lib().wmdec_gn_stats(_ptr(x), dtype_enum(x), n, h, w, c, groups, eps, _ptr(mean), _ptr(rstd),
-                                _ptr(workspace), workspace.numel() * workspace.element_size(), _stream()))
+    _check(_ops().gn_stats(x, groups, eps, mean, rstd, workspace, _stream()))
 
 
 def gn_stats_noalloc(x, groups, eps, mean, rstd):
@@ -168,24 +185,13 @@ def pack_conv_weights(src, packed, op_dtype):
     _check(lib().wmdec_pack_conv_weights(_ptr(src), dtype_enum(src), cout, cin, k, _ptr(packed), op_dtype, _stream()))
 
 
-def _conv(fn, x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, residual, y, cin, cout):
-    n, h, w, _ = y.shape
-    _check(fn(_ptr(x), dtype_enum(x), _ptr(mean), _ptr(rstd), _ptr(gamma), _ptr(beta), groups, int(apply_silu),
-              _ptr(w_packed), _ptr(bias), _ptr(residual), _ptr(y), dtype_enum(y), n, h, w, cin, cout, _stream()))
-
-
 def gn_silu_conv3x3(x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, residual, y):
-    _conv(lib().wmdec_gn_silu_conv3x3, x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, residual, y,
-          x.shape[3], y.shape[3])
+    _check(_ops().conv(3, x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, residual, y, _stream()))
 
 
 def gn_silu_conv3x3_shortcut(x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, x2, w2_packed, bias2, y):
     """y = conv3x3(act(x)) + bias + W2 * x2 + bias2 (the 1x1 shortcut of a channel-changing ResBlock folded in)."""
-    n, h, w, _ = y.shape
-    _check(lib().wmdec_gn_silu_conv3x3_shortcut(
-        _ptr(x), dtype_enum(x), _ptr(mean), _ptr(rstd), _ptr(gamma), _ptr(beta), groups, int(apply_silu), _ptr(w_packed),
-        _ptr(bias), _ptr(x2), x2.shape[3], _ptr(w2_packed), _ptr(bias2), _ptr(y), dtype_enum(y), n, h, w, x.shape[3],
-        y.shape[3], _stream()))
+    _check(_ops().conv_shortcut(x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, x2, w2_packed, bias2, y, _stream()))
 
 
 def conv_stats_workspace_bytes(act_dtype, y_dtype, n, h, w, cin, cout, out_groups):
@@ -195,12 +201,8 @@ def conv_stats_workspace_bytes(act_dtype, y_dtype, n, h, w, cin, cout, out_group
 def gn_silu_conv3x3_stats(x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, residual, y,
                           out_groups, out_eps, mean_out, rstd_out, workspace):
     """gn_silu_conv3x3 that also returns mean / rstd of its own output y per (sample, output group)."""
-    n, h, w, _ = y.shape
-    _check(lib().wmdec_gn_silu_conv3x3_stats(
-        _ptr(x), dtype_enum(x), _ptr(mean), _ptr(rstd), _ptr(gamma), _ptr(beta), groups, int(apply_silu),
-        _ptr(w_packed), _ptr(bias), _ptr(residual), _ptr(y), dtype_enum(y), n, h, w, x.shape[3], y.shape[3],
-        out_groups, out_eps, _ptr(mean_out), _ptr(rstd_out), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream()))
+    _check(_ops().conv_stats(x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, residual, y, out_groups, out_eps, mean_out,
+                             rstd_out, workspace, _stream()))
 
 
 def measure_copy(src, dst):
@@ -209,8 +211,7 @@ def measure_copy(src, dst):
 
 
 def gn_conv1x1(x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, residual, y):
-    _conv(lib().wmdec_gn_conv1x1, x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, residual, y,
-          x.shape[3], y.shape[3])
+    _check(_ops().conv(1, x, mean, rstd, gamma, beta, groups, apply_silu, w_packed, bias, residual, y, _stream()))
 
 
 def upconv_packed_bytes(cout, cin, op_dtype):
@@ -224,9 +225,7 @@ def pack_upconv_weights(src, packed, op_dtype):
 
 
 def upsample2x_conv3x3(x, w_packed, bias, y):
-    n, h, w, cin = x.shape
-    _check(lib().wmdec_upsample2x_conv3x3(_ptr(x), dtype_enum(x), _ptr(w_packed), _ptr(bias), _ptr(y), dtype_enum(y),
-                                          n, h, w, cin, y.shape[3], _stream()))
+    _check(_ops().upconv(x, w_packed, bias, y, _stream()))
 
 
 def upsample2x_nearest(x, y):
@@ -249,10 +248,7 @@ def attention_workspace_bytes(n, h, w, c):
 
 
 def attention(x, mean, rstd, gamma, beta, groups, wqkv_packed, bqkv, wo_packed, bo, y, workspace):
-    n, h, w, c = x.shape
-    _check(lib().wmdec_attention(_ptr(x), dtype_enum(x), _ptr(mean), _ptr(rstd), _ptr(gamma), _ptr(beta), groups,
-                                 _ptr(wqkv_packed), _ptr(bqkv), _ptr(wo_packed), _ptr(bo), _ptr(y), n, h, w, c,
-                                 _ptr(workspace), workspace.numel() * workspace.element_size(), _stream()))
+    _check(_ops().attention(x, mean, rstd, gamma, beta, groups, wqkv_packed, bqkv, wo_packed, bo, y, workspace, _stream()))
 
 
 def latent_extrapolate(z_prev, v_prev, lam, steps, z_out):
@@ -267,10 +263,7 @@ def adaln_max_batch(d_cond):
 
 def adaln_fused_projection(c, w_fused, bias, out, apply_silu=True):
     """out[b, :] = bias + w_fused @ act(c[b]); c [batch, d_cond], w_fused [rows, d_cond], out fp32 [batch, rows]."""
-    batch, d_cond = c.shape
-    rows = w_fused.shape[0]
-    _check(lib().wmdec_adaln_fused_projection(_ptr(c), dtype_enum(c), _ptr(w_fused), dtype_enum(w_fused), _ptr(bias), _ptr(out),
-                                              batch, d_cond, rows, int(apply_silu), _stream()))
+    _check(_ops().adaln(c, w_fused, bias, out, apply_silu, _stream()))
 
 
 # ------------------------------------------------------------------ decoder
