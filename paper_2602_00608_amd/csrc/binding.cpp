@@ -2,9 +2,12 @@
 //
 // What bounds a small layer is the host: through ctypes a convolution's nineteen arguments cost 5 us of marshalling (1.9 us of conversions,
 // 0.28 us for each of nine tensors) beside 2 to 3 us of the launch itself; here 0.6 us.  The entry points are bound by address, so that the
-// library is loaded in one place (wmdec.py).  Every function returns the library's status.
+// library is loaded in one place (wmdec.py).  Every function returns the library's status; what torch throws (a tensor without storage has no
+// address) becomes a Python error at the entry.
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
+
+#include <exception>
 
 #include "../../include/wmdec.h"
 
@@ -19,12 +22,15 @@ decltype(&wmdec_upsample2x_conv3x3) g_upconv;
 decltype(&wmdec_attention) g_attention;
 decltype(&wmdec_adaln_fused_projection) g_adaln;
 
+constexpr Py_ssize_t kBind = 8;   // arguments of bind(): as many as no other function has
+
 // Reads the arguments; the first one that is not what it should be leaves a Python error and `ok` false.
 struct Reader {
   PyObject* const* args;
   bool ok;
   Reader(const char* who, PyObject* const* a, Py_ssize_t given, Py_ssize_t wanted) : args(a), ok(given == wanted) {
     if (!ok) PyErr_Format(PyExc_TypeError, "%s: %zd arguments expected, got %zd", who, wanted, given);
+    else if (wanted != kBind && !g_adaln) { ok = false; PyErr_SetString(PyExc_RuntimeError, "the entry points have not been bound"); }
   }
   const at::Tensor* tensor(int i) {
     if (!ok) return nullptr;
@@ -205,9 +211,9 @@ PyObject* adaln(PyObject*, PyObject* const* a, Py_ssize_t na) {
 
 // the addresses of the entry points, in the order of wmdec.py
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t na) {
-  Reader r("bind", a, na, 8);
-  void* f[8];
-  for (int i = 0; i < 8; ++i) f[i] = r.address(i);
+  Reader r("bind", a, na, kBind);
+  void* f[kBind];
+  for (int i = 0; i < kBind; ++i) f[i] = r.address(i);
   if (!r.ok) return nullptr;
   g_gn_stats = (decltype(g_gn_stats))f[0]; g_conv3x3 = (decltype(g_conv3x3))f[1]; g_conv1x1 = (decltype(g_conv1x1))f[2];
   g_shortcut = (decltype(g_shortcut))f[3]; g_conv_stats = (decltype(g_conv_stats))f[4]; g_upconv = (decltype(g_upconv))f[5];
@@ -215,7 +221,15 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t na) {
   Py_RETURN_NONE;
 }
 
-#define WMDEC_METHOD(name_) {#name_, (PyCFunction)(void (*)())name_, METH_FASTCALL, nullptr}
+template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)> PyObject* entry(PyObject* self, PyObject* const* a, Py_ssize_t na) {
+  try {
+    return F(self, a, na);
+  } catch (const std::exception& e) {
+    PyErr_SetString(PyExc_RuntimeError, e.what());
+    return nullptr;
+  }
+}
+#define WMDEC_METHOD(name_) {#name_, (PyCFunction)(void (*)())entry<name_>, METH_FASTCALL, nullptr}
 PyMethodDef g_methods[] = {WMDEC_METHOD(gn_stats), WMDEC_METHOD(conv), WMDEC_METHOD(conv_shortcut), WMDEC_METHOD(conv_stats), WMDEC_METHOD(upconv),
                            WMDEC_METHOD(attention), WMDEC_METHOD(adaln), WMDEC_METHOD(bind), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};

@@ -116,7 +116,8 @@ def lib():
             raise RuntimeError("the native binding is missing (%s): build it with "
                                "`python -m paper_2602_00608_amd.build`; there is no fallback path" % e) from e
         _binding.bind(*(ctypes.cast(getattr(l, name), _vp).value for name in _BOUND))
-        _lib, _native = l, _binding
+        _native = _binding   # (before _lib: another thread takes a set _lib for both)
+        _lib = l
     return _lib
 
 
