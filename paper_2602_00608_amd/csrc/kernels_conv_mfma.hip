@@ -1,4 +1,5 @@
-// Implicit-GEMM convolution on the gfx950 matrix cores.
+// Implicit-GEMM convolution on the gfx950 matrix cores: 1x1 layers, 3x3 layers with 64 output channels or few, the batched form of
+// kernels_conv_ksplit.hip; and the choice of tile for all, also for the 3x3 layers of kernels_conv_rows.hip.
 //
 // GEMM view: M = output pixels, N = output channels, K = taps * C_in.
 // One workgroup (4 wavefronts) owns a TH x TW patch of output pixels and TN
@@ -726,30 +727,45 @@ constexpr TileShape kTiles[kNumTiles] = {
     {4, 32, 4, 1, 2},    // T128x64_ROW: 128 x 64 on a 4x32 patch (1x1 convolutions)
     {8, 16, 4, 1, 2},    // T128x64: 128 x 64 on an 8x16 patch
     {8, 32, 4, 1, 1},    // T256x32: 256 x 32 (few output channels: the frame)
-    {8, 16, 1, 4, 1},    // T128x128_1x4: 128 x 128, every wavefront all pixels x 32 channels: a weight fragment feeds four
-                         //     MFMAs, which keeps the fragment loads off the limit of the vector L1 (64 B/clk per compute unit)
-    {8, 16, 1, 4, 2},    // T128x256: 128 x 256, every wavefront all pixels x 64 channels: a staged (normalised, activated) patch
-                         //     feeds twice the channels, i.e. half the staging work and input traffic per MFMA; two
-                         //     workgroups per compute unit
+                         // the tiles of kernels_conv_rows.hip:
+    {8, 16, 1, 4, 1},    // T128x128_1x4: 128 x 128, every wavefront all pixels x 32 channels: a weight fragment feeds all
+                         //     rows, which keeps the fragment loads off the limit of the vector L1 (64 B/clk per compute unit)
+    {8, 16, 1, 4, 2},    // T128x256: 128 x 256, every wavefront all pixels x 64 channels (see wide_channels); two workgroups per
+                         //     compute unit
     {4, 16, 1, 4, 1},    // T64x128: 64 x 128, T128x128_1x4 at half the height, for launches of at most one workgroup per compute unit
     {8, 16, 1, 4, 1},    // T128x128_ROWS4: the same layers in larger batches
 };
 
 // Layers whose 128 x 128 tiles leave half of the compute units empty at batch 1 and whose moments, per 4x16 block, are few
 // enough for the consumer to merge: 64 x 128 tiles where the launch still fits one round, 128 x 128 otherwise, with the same
-// order of summation and the same moments.  Measured, us, 64 x 128 against 128 x 128: 512 channels at 64x64 23.1 / 26.2, at
-// 48x72 21.0 / 25.6, 256 channels at 68x92 11.6 / 15.5; past one round 33.3 / 28.5 (512 channels at 60x90).
+// order of summation and the same moments.  Measured, us, 64 x 128 against 128 x 128: 512 channels at 64x64 24.0 / 29.2, at
+// 48x72 21.1 / 27.1, 256 channels at 68x92 11.7 / 16.0; past one round 31.3 / 29.1 (512 channels at 60x90).
 // The smaller tile always has a whole chunk of weight fragments in flight: two MFMAs a k-step cover little of the latency of
 // weights that are new to the L2 (256x256 frame 859 -> 853 us against half a chunk, 136x184 the same).
-// The larger tile of the pair runs as T128x128_1x4 does: ResBlocks of 2 / 4 / 8 samples take 93.0 / 156.6 / 284.6 us at 512
-// channels 45x80 against 93.2 / 157.5 / 286.0, at 256 channels 68x92 61.5 / 92.1 / 157.9 against 61.3 / 92.5 / 158.8.
+// The larger tile of the pair runs as T128x128_1x4 does (its moments take four rows each; ResBlocks of 2 to 8 samples within 0.6 % of each other).
 bool four_row_slots(const ConvArgs& a) {
   const long blocks = (long)((a.h + 3) / 4) * ((a.w + 15) / 16);
   return a.ksize == 3 && !a.y_nchw && a.cout % 128 == 0 && !a.rows_out && !a.wide_tiles && blocks <= 128 && blocks * (a.cout / 128) <= 256;
 }
 
-// which tile shape a launch uses; a function of the per-sample shape only (but for the pair above), so that every
-// summation order does not depend on the batch
+// 128 or 256 channels a workgroup where the layer has both: whichever walks its rounds sooner.  With 256 a staged patch feeds twice the
+// channels, half the normalise + SiLU work and input traffic per MFMA, so that a compute unit takes 1.8 times the time of a 128-channel tile per
+// 256-channel tile instead of twice; but tiles are dealt to 256 compute units in larger pieces.  us, 128 / 256 channels,
+// 256 -> 256 channels, by the number of 256-channel tiles: 180 29.1 / 26.7, 250 32.9 / 31.7, 260 42.3 / 48.2, 380 48.2 / 50.7, 420 57.9 / 52.6,
+// 510 62.9 / 57.7, 520 70.8 / 75.8, 640 76.0 / 77.3, 700 86.4 / 80.5, 800 99.1 / 99.7, 900 111.8 / 102.6, 1100 129.2 / 126.5; 512 -> 512: 120
+// 32.9 / 48.6, 220 56.6 / 52.9, 300 79.8 / 88.5, 480 113 / 102, 1440 320 / 290.  Both add a sum's products in the same order and leave the same
+// moments per 8x16 block, so the batch may decide.  Where the rows' moments are merged by the launch itself, its ticket counters are sized for one
+// sample's choice by its pixels alone (fits_wide): never more channel tiles than that.
+bool fits_wide(const ConvArgs& a) { return a.cout % 256 == 0 && (((long)a.h * a.w + 127) / 128) * (a.cout / 256) >= 2 * 256; }
+bool wide_channels(const ConvArgs& a) {
+  if (a.cout % 256 != 0) return false;
+  if (a.rows_out && fits_wide(a)) return true;
+  const long tiles = (long)((a.h + 7) / 8) * ((a.w + 15) / 16) * (a.cout / 256) * a.n;
+  return 9 * ((tiles + 255) / 256) <= 5 * ((2 * tiles + 255) / 256);
+}
+
+// which tile shape a launch uses: a function of the per-sample shape only, so that the order of a summation does not depend on the
+// batch, but for the two pairs above
 TileId pick_tile(const ConvArgs& a) {
   const long px = (long)a.h * a.w;
   const bool n128 = a.cout % 128 == 0;
@@ -757,25 +773,17 @@ TileId pick_tile(const ConvArgs& a) {
     if (a.cout <= 32) return T256x32;
     if (four_row_slots(a))
       return (long)((a.h + 3) / 4) * ((a.w + 15) / 16) * (a.cout / 128) * a.n <= 256 ? T64x128 : T128x128_ROWS4;
-    // 128 pixels x 128 channels with every wavefront on all pixels x 32 channels (three workgroups per compute unit):
-    // measured against the 256-pixel tile and the 2x2 wavefront layout on every layer shape of the decoder, it is
-    // equal or faster everywhere (512 -> 512 at 60x90: 35 us against 48 to 57 for 192 or 256 pixels, at 120x180 101 against 110)
-    // With 256 channels per workgroup the normalise + SiLU work and the input traffic per MFMA halve, at two workgroups
-    // per compute unit instead of three: it pays (6 to 8 %) where that still leaves every compute unit two workgroups
-    // (the 240x360 layers of the decoder), and loses on smaller layers.
-    if (a.cout % 256 == 0 && ((px + 127) / 128) * (a.cout / 256) >= 2 * 256) return T128x256;
-    // (a 96-pixel tile on 6x16 patches, which puts the 512 -> 512 layers at 60x90 on 240 instead of 192 compute units,
-    // measured 3 % on those layers: a lone workgroup's time is set by its weight stream, 1.2 MB through the vector
-    // L1 whatever its pixel count; not kept)
+    if (wide_channels(a)) return T128x256;
     return n128 ? T128x128_1x4 : T128x64;
   }
   if (n128 && a.cin % 64 == 0 && px * (a.cout / 128) >= 256L * 256 * 2) return T256x128;
   return n128 ? T128x128_ROW : T128x64_ROW;
 }
 
-// The 128x128 tiles with a whole chunk of weight fragments in flight (see RING): launches of at most two workgroups per
-// compute unit (against the shorter ring: 480x720 frame 2.92 -> 2.89 ms, two of 360x640 3.79 -> 3.76; layers on their own, whose
-// weights stay in the L2, are the same).  Unlike the tile shape this may depend on the batch: the ring changes no summation order.
+// The 128x128 tiles with a whole chunk of weight fragments in flight (see RING in kernels_conv_rows.hip): launches of at most two workgroups
+// per compute unit, in their order of summation the same as the others, so that the batch may decide.  us, whole chunk / two steps ahead, with the
+// weights in the L2: 512 channels at 60x90 32.4 / 34.1, two samples 53.4 / 54.5, 256 channels at 120x180 28.3 / 29.3; in a decoder run,
+// where they are not, the difference is larger (the ten such layers of a 480x720 frame: 30 us when both rings were longer).
 bool whole_chunk_ring(const ConvArgs& a) {
   const TileId t = pick_tile(a);
   if (t != T128x128_1x4 && t != T128x128_ROWS4) return false;
@@ -841,7 +849,8 @@ int conv_mfma_stats_slots(const ConvArgs& a) {
 
 // tile rows / channel tiles of a launch: the extents of the row moments it can leave and of its ticket counters
 void conv_mfma_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row) {
-  const TileId t = pick_tile(a);
+  TileId t = pick_tile(a);
+  if (t == T128x256 || t == T128x128_1x4) t = fits_wide(a) ? T128x256 : T128x128_1x4;
   const TileShape& ts = kTiles[t];
   const int tn = ts.wn * ts.ni * 32;
   *tile_rows = (a.h + ts.th - 1) / ts.th;

@@ -9,10 +9,11 @@ from tests import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 
-# 64 x 128 tiles; 128 x 128 with moments per four rows, short and whole ring of weights; 128 x 128, both rings; 128 x 256, one and two chunks
+# 64 x 128 tiles; 128 x 128 with moments per four rows, short and whole ring of weights; 128 x 128, both rings, and of 256 channels; 128 x 256, one and two chunks
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("n,cin,cout,h,w", [(1, 32, 128, 5, 17), (5, 32, 256, 37, 50), (16, 32, 256, 37, 50), (1, 96, 128, 121, 67),
-                                            (1, 32, 128, 127, 530), (1, 32, 256, 257, 259), (1, 64, 256, 182, 367)])
+                                            (1, 32, 128, 127, 530), (1, 32, 256, 257, 259), (1, 64, 256, 182, 367),
+                                            (1, 32, 256, 100, 203), (2, 64, 256, 91, 130)])
 def test_tile_edges(dtype, n, cin, cout, h, w):
     g = torch.Generator(device="cuda")
     g.manual_seed(synth.SEED_BASE + 60)
@@ -48,3 +49,37 @@ def test_tile_edges(dtype, n, cin, cout, h, w):
             v = y.double().view(n, h * w, groups, cout // groups)
             m, r = v.mean((1, 3)).flatten(), (v.var((1, 3), unbiased=False) + 1e-6).rsqrt().flatten()
             assert float((mean.double() - m).abs().max()) <= 2e-5 and float((rstd.double() / r - 1).abs().max()) <= 2e-5
+
+
+# 91 tiles of 8 x 16 pixels a sample and 256 channels: 128-channel tiles for one or three samples, 256-channel tiles for two or five
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("cin2", [0, 96])
+def test_a_sample_keeps_its_bits_where_the_batch_chooses_the_width(dtype, cin2):
+    n, h, w, cin, cout, groups = 5, 100, 100, 64, 256, 32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(synth.SEED_BASE + 61)
+
+    def draw(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+    x, res, bias = draw(n, h, w, cin).to(G.TORCH[dtype]), draw(n, h, w, cout).to(G.TORCH[dtype]), draw(cout)
+    mean, rstd, gamma, beta = draw(n, groups), draw(n, groups).abs() + 0.5, draw(cin), draw(cin)
+    packed = G.pack((draw(cout, cin, 3, 3) / (9 * cin) ** 0.5).bfloat16().float().cpu().numpy(), dtype)
+    if cin2:
+        x2, bias2 = draw(n, h, w, cin2).to(G.TORCH[dtype]), draw(cout)
+        packed2 = G.pack((draw(cout, cin2, 1, 1) / cin2 ** 0.5).bfloat16().float().cpu().numpy(), dtype)
+
+    def run(k):
+        y = torch.empty((k, h, w, cout), dtype=G.TORCH[dtype], device="cuda")
+        head = (x[:k], mean[:k].reshape(-1), rstd[:k].reshape(-1), gamma, beta, groups, True, packed, bias)
+        if cin2:
+            wmdec.gn_silu_conv3x3_shortcut(*head, x2[:k], packed2, bias2, y)
+            return (y,)
+        ws = torch.zeros(wmdec.conv_stats_workspace_bytes(G.ENUM[dtype], G.ENUM[dtype], k, h, w, cin, cout, groups), dtype=torch.uint8, device="cuda")
+        m, r = torch.empty((k, groups), device="cuda"), torch.empty((k, groups), device="cuda")
+        wmdec.gn_silu_conv3x3_stats(*head, res[:k], y, groups, 1e-6, m, r, ws)
+        return y, m, r
+    alone = run(1)
+    for k in (2, 3, 5):
+        batch = run(k)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a[:1], b[:1]) for a, b in zip(alone, batch)), k
