@@ -296,7 +296,7 @@ constexpr int kH = 2, kWN = 2, kTN = 32 * kWN;
 // ... or 32 channels, with the contraction split in two: one round of half as many channels then leaves compute units idle, and
 // a lone workgroup is bound by the weights that its wavefronts take through the vector L1 (64 B/clk), 1.2 MB at 512
 // channels, of which half the channels need half.  A function of the sample's shape: the sums do not depend on the batch.
-// 512 channels, us: 17x23 20.7 -> 17.4, 32x32 22.0 -> 19.3; frames of these sizes 1.008x and 1.006x.  Past 128 workgroups the halves
+// 512 channels, us, measured in this kernel's earlier form on 32x32x16 MFMAs: 17x23 20.7 -> 17.4, 32x32 22.0 -> 19.3.  Past 128 workgroups the halves
 // would share a compute unit again.
 bool split_channels(const ConvArgs& a) {
   const long wgs = (long)((a.h / 2 + TH - 1) / TH) * ((a.w / 2 + TW - 1) / TW) * (a.cout / kTN);
