@@ -300,8 +300,13 @@ static void fuse_stats_into_producers(wmdec_decoder& d) {
     if (cons.kind != Step::CONV || !cons.norm || cons.src != st.src || !conv_mfma_supported(step_shape_args(d, cons, 1))) continue;
     if (conv_taps_supported(step_shape_args(d, cons, 1))) continue;   // that kernel takes mean / rstd only
     // A producer with few spatial tiles needs no merge of its own at all: the consumer reads its triples as they are.
-    const int slots = conv_stats_slots(step_shape_args(d, d.steps[j], 1));
-    if (slots <= 128) {
+    // (An upsampling convolution counts two triples a tile, whichever it leaves: up to 64 tiles the row buffers hold them anyway, above that they
+    // would grow the workspace that a caller has to pass.)
+    const ConvArgs prod = step_shape_args(d, d.steps[j], 1);
+    const int slots = conv_stats_slots(prod);
+    int rows = 0, ctiles = 0, per_row = 0;
+    const bool merges_rows = conv_row_extents(prod, &rows, &ctiles, &per_row);
+    if (slots <= 128 && !(conv_up_supported(prod) && rows * per_row > 64)) {
       d.steps[j].emit_rows = parity;
       d.steps[j].emit_direct = 1;
       cons.rows_from = parity;
@@ -311,9 +316,7 @@ static void fuse_stats_into_producers(wmdec_decoder& d) {
       d.launches -= 1;
       continue;
     }
-    int rows = 0, ctiles = 0, per_row = 0;
-    if (!conv_row_extents(step_shape_args(d, d.steps[j], 1), &rows, &ctiles, &per_row)) continue;
-    if (rows > 64) continue;   // keeps the consumer's merge short
+    if (!merges_rows || rows > 64) continue;   // keeps the consumer's merge short
     // The hand-over keeps every workgroup of the producer resident for two more memory round trips (its stores, its
     // ticket).  Measured, that costs a launch of several rounds of workgroups as much as the merge launch it saves;
     // it wins where the producer is a single round (at most three workgroups per compute unit, per sample).
