@@ -168,6 +168,7 @@ static ConvArgs step_shape_args(const wmdec_decoder& d, const Step& st, int batc
   a.n = batch; a.h = st.h; a.w = st.w; a.cin = st.cin; a.cout = st.cout; a.ksize = st.ksize; a.upsample = st.upsample;
   a.stats_groups = d.cfg.groups;
   a.cin2 = st.sc_cin;
+  if (st.norm) { a.groups_norm = 1; a.groups = d.cfg.groups; a.silu = st.silu; }
   return a;
 }
 
@@ -941,7 +942,6 @@ static int launch_step(wmdec_decoder* dec, const WsLayout& L, const Step& st, co
         if (after < dec->steps.data() + dec->steps.size()) {
           ConvArgs b = step_shape_args(*dec, *after, batch);
           b.wt = pk + after->w_off;
-          b.groups_norm = after->norm;
           if (after->sc_src != BUF_NONE) b.x2 = b.wt;   // (that there is one decides the tile)
           a.next = next_weights(b, after->to_attn == 1);
         }
@@ -1068,7 +1068,6 @@ int decoder_step_info(const wmdec_decoder* dec, int index, const char** kernel, 
       case Step::NONE: *kernel = ""; break;
       case Step::CONV: {
         ConvArgs a = step_shape_args(*dec, st, 1);   // only the fields the kernel choice looks at
-        a.groups_norm = st.norm; a.silu = st.silu;
         *kernel = st.to_attn == 1 ? attention_qkv_label(a.op_dtype) : conv_kernel_label(a);
         break;
       }

@@ -81,7 +81,7 @@ struct ConvArgs {
   const float* gamma = nullptr;  // [cin]
   const float* beta = nullptr;
   int groups = 1;
-  int groups_norm = 0;           // label queries only: the launch will normalise although mean is not known yet
+  int groups_norm = 0;           // queries of a shape only: the launch will normalise although mean is not known yet
   int silu = 0;
   const void* wt = nullptr;      // packed [k*k][cout][cin] in op dtype
   int op_dtype = WMDEC_F32;      // arithmetic: F32 (FMA) or BF16 / F16 (operands rounded to it)

@@ -127,6 +127,19 @@ def test_step_accounting_adds_up():
     dec.close()
 
 
+def test_convolution_of_few_normalised_channels_leaves_no_moments():
+    """The kernel for few input channels does not normalise, so a ResBlock's 8 -> 64 convolution runs on the general one, which emits no moments:
+    the second convolution needs a statistics pass over what it wrote."""
+    cfg = wmdec.decoder_default_config()
+    cfg.latent_h = cfg.latent_w = 8
+    cfg.num_levels, cfg.resblocks_per_level, cfg.groups = 3, 1, 8
+    cfg.level_channels[0], cfg.level_channels[1], cfg.level_channels[2] = 512, 8, 64
+    dec = wmdec.Decoder(cfg)
+    kernels = [k for k, _, _ in dec.step_info()]
+    assert kernels[-7:-2] == ["gn_stats_vec", "conv_direct_kernel", "conv_direct_kernel", "gn_stats_vec", "conv_ksplit_kernel<wmdec::f16_t, 4, 8, 1, 1, 4, 2, 2, 2>"], kernels
+    dec.close()
+
+
 def test_attention_scratch_holds_partial_outputs_only_where_keys_are_split():
     """Fragments of q, k, v (tiles of 32 tokens) and o; from 16 385 tokens on, and up to 64, one range holds all keys and nothing else is needed."""
     for n, h, w in ((1, 129, 130), (2, 1, 16385), (1, 200, 200), (1, 8, 8), (3, 1, 1)):

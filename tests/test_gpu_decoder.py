@@ -276,6 +276,18 @@ def test_upsampling_convolutions_with_groups_of_one_and_two_channels():
     assert err <= G.TOL["f16"], err
 
 
+def test_level_of_eight_channels():
+    """Normalised convolutions of eight input channels leave no moments (the kernel for few channels does not normalise)."""
+    chans = (512, 8, 64)
+    cfg = small_cfg(wmdec.F16)
+    cfg.latent_h, cfg.latent_w, cfg.num_levels, cfg.groups = 6, 7, 3, 8
+    cfg.level_channels[1], cfg.level_channels[2] = 8, 64
+    weights = synth.draw_params(synth.decoder_weight_spec(level_channels=chans, resblocks_per_level=2), synth.weight_seed(16), random_affine=True)
+    z = synth.latent_sequence(workload=16, frames=2, h=6, w=7)
+    err = ref.rel_err(run_decoder(cfg, weights, z), ref.decoder(z, weights, level_channels=chans, resblocks_per_level=2, groups=8, eps=1e-6))
+    assert err <= G.TOL["f16"], err
+
+
 @pytest.mark.parametrize("dtype,last", [("f16", 128), ("bf16", 128), ("f16", 64)])
 def test_last_convolution_as_taps_contraction(dtype, last):
     """The decoder's last layer (few output channels, planar fp32 frame) runs as a 1x1 contraction onto (tap, channel)
