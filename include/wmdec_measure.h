@@ -20,8 +20,9 @@ extern "C" {
  * a HIP event on `stream` before the first and after every step of the graph
  * (a step = one GroupNorm statistics pass, one convolution, the attention projection or
  * the attention core).  decoder_step_info gives, for step `index`, the name of
- * the kernel that executes it (for convolutions the template instantiation as
- * a profiler prints it; the string is valid until the thread's next call) and
+ * the kernel that executes it in a run of one frame (for convolutions the template
+ * instantiation as a profiler prints it; batches may take another tile of the same
+ * sums; the string is valid until the thread's next call) and
  * its algorithmic FLOPs and HBM bytes per frame (every input, residual, output
  * and weight tensor counted once: the Eq. 9 accounting).  decoder_step_times
  * waits for the last profiled decoder_run and returns the elapsed milliseconds

@@ -159,15 +159,19 @@ struct wmdec_decoder {
 
 namespace wmdec {
 
-// the launch-shape part of a CONV step's arguments (pointers left null)
+// The launch-shape part of a CONV step's arguments: what the choice of a kernel and its tile looks at, for the launch and every question about
+// it alike.  Optional tensors are there or not; those that are there point to a placeholder until the launch sets them.
 static ConvArgs step_shape_args(const wmdec_decoder& d, const Step& st, int batch) {
+  static char there;
   ConvArgs a;
   a.op_dtype = d.cfg.act_dtype; a.res_dtype = a.op_dtype;
   a.x_dtype = st.src == BUF_LATENT ? d.cfg.latent_dtype : a.op_dtype; a.x_nchw = st.x_nchw;
   a.y_dtype = st.dst == BUF_OUT ? (int)WMDEC_F32 : a.op_dtype; a.y_nchw = st.y_nchw;
   a.n = batch; a.h = st.h; a.w = st.w; a.cin = st.cin; a.cout = st.cout; a.ksize = st.ksize; a.upsample = st.upsample;
   a.stats_groups = d.cfg.groups;
-  a.cin2 = st.sc_cin;
+  if (st.res != BUF_NONE) a.res = &there;
+  if (st.sc_src != BUF_NONE) { a.x2 = &there; a.cin2 = st.sc_cin; }
+  if (st.emit_rows >= 0 && !st.emit_direct) a.rows_out = &there;
   if (st.norm) { a.groups_norm = 1; a.groups = d.cfg.groups; a.silu = st.silu; }
   return a;
 }
@@ -914,25 +918,21 @@ static int launch_step(wmdec_decoder* dec, const WsLayout& L, const Step& st, co
                                (unsigned*)(ws + L.tickets), ws + L.stats_ws, L.stats_ws_bytes, s);
         break;
       case Step::CONV: {
-        ConvArgs a;
-        a.op_dtype = c.act_dtype; a.res_dtype = c.act_dtype;
-        if (st.src == BUF_LATENT) { a.x = latent.z; a.x_dtype = c.latent_dtype; a.x_nchw = 1; a.x_step = latent.step; a.step_scale = latent.scale; }
-        else if (st.to_attn == 2) { a.x = ws + L.attn_o; a.x_dtype = c.act_dtype; }
-        else { a.x = buf(st.src); a.x_dtype = c.act_dtype; }
+        ConvArgs a = step_shape_args(*dec, st, batch);
+        if (st.src == BUF_LATENT) { a.x = latent.z; a.x_step = latent.step; a.step_scale = latent.scale; }
+        else if (st.to_attn == 2) a.x = ws + L.attn_o;
+        else a.x = buf(st.src);
         if (st.norm) {
-          a.gamma = (const float*)(pk + st.gamma_off); a.beta = (const float*)(pk + st.beta_off); a.groups = c.groups; a.silu = st.silu;
+          a.gamma = (const float*)(pk + st.gamma_off); a.beta = (const float*)(pk + st.beta_off);
           if (st.rows_from >= 0) { a.rows_in = ws + L.rows[st.rows_from]; a.rows_in_count = st.rows_count; a.eps = c.eps; }
           else { a.mean = mean; a.rstd = rstd; }
         }
         a.wt = pk + st.w_off; a.bias = (const float*)(pk + st.b_off);
         a.res = buf(st.res);
-        if (st.sc_src != BUF_NONE) { a.x2 = buf(st.sc_src); a.cin2 = st.sc_cin; a.w2 = pk + st.sc_w_off; a.bias2 = (const float*)(pk + st.sc_b_off); }
-        if (st.dst == BUF_OUT) { a.y = out; a.y_dtype = WMDEC_F32; a.y_nchw = 1; }
-        else if (st.to_attn == 1) { a.y_dtype = c.act_dtype; }   // (in fragment order, see kernels_attn.hip)
-        else { a.y = buf(st.dst); a.y_dtype = c.act_dtype; }
-        a.n = batch; a.h = st.h; a.w = st.w; a.cin = st.cin; a.cout = st.cout; a.ksize = st.ksize; a.upsample = st.upsample;
+        if (st.sc_src != BUF_NONE) { a.x2 = buf(st.sc_src); a.w2 = pk + st.sc_w_off; a.bias2 = (const float*)(pk + st.sc_b_off); }
+        if (st.dst == BUF_OUT) a.y = out;
+        else if (st.to_attn != 1) a.y = buf(st.dst);   // (1: in fragment order, see kernels_attn.hip)
         if (st.emit_stats) {
-          a.stats_groups = c.groups;
           (*emitted_slots) = conv_stats_slots(a);
           if ((*emitted_slots) > 0) a.stats_ws = st.emit_direct ? ws + L.rows[st.emit_rows] : ws + L.stats_ws;
           if (st.emit_rows >= 0 && !st.emit_direct) { a.rows_out = ws + L.rows[st.emit_rows]; a.tickets = ws + L.conv_tickets; }
@@ -942,7 +942,6 @@ static int launch_step(wmdec_decoder* dec, const WsLayout& L, const Step& st, co
         if (after < dec->steps.data() + dec->steps.size()) {
           ConvArgs b = step_shape_args(*dec, *after, batch);
           b.wt = pk + after->w_off;
-          if (after->sc_src != BUF_NONE) b.x2 = b.wt;   // (that there is one decides the tile)
           a.next = next_weights(b, after->to_attn == 1);
         }
         rc = st.to_attn == 1 ? launch_attention_qkv(a, ws + L.qkv, s) : launch_conv(a, s);
@@ -1067,7 +1066,7 @@ int decoder_step_info(const wmdec_decoder* dec, int index, const char** kernel, 
       case Step::FLASH: *kernel = "flash_attn_kernel"; break;
       case Step::NONE: *kernel = ""; break;
       case Step::CONV: {
-        ConvArgs a = step_shape_args(*dec, st, 1);   // only the fields the kernel choice looks at
+        const ConvArgs a = step_shape_args(*dec, st, 1);
         *kernel = st.to_attn == 1 ? attention_qkv_label(a.op_dtype) : conv_kernel_label(a);
         break;
       }

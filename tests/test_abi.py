@@ -140,6 +140,25 @@ def test_convolution_of_few_normalised_channels_leaves_no_moments():
     dec.close()
 
 
+def test_layers_that_hand_rows_over_are_named_by_the_tile_they_launch():
+    """60x80 latent: the 256-channel layers at 240x320 whose launch merges its own rows have ticket counters for 256-channel tiles and run on
+    them, the last one of the level, which hands over to nobody, on 128-channel tiles."""
+    cfg = wmdec.decoder_default_config()
+    cfg.latent_h, cfg.latent_w = 60, 80
+    dec = wmdec.Decoder(cfg)
+    info = dec.step_info()
+    at = [i for i, (k, f, _) in enumerate(info) if f in (2.0 * 9 * 512 * 256 * 240 * 320, 2.0 * (9 * 256 + 512) * 256 * 240 * 320)]
+    assert len(at) == 4 and at[:2] == [23, 24]
+    name = "conv_mfma_kernel<wmdec::f16_t, wmdec::f16_t, 8, 16, 1, 4, %d, 3, 32, 2, 0, 0>"
+    assert [info[i][0] for i in range(23, 29)] == [name % 2] * 5 + [name % 1]
+    dec.close()
+    cfg.separate_merge_launch = 1   # no rows are handed over: all as the last one
+    dec = wmdec.Decoder(cfg)
+    convs = [k for k, f, _ in dec.step_info() if f in (2.0 * 9 * 256 * 256 * 240 * 320, info[23][1], info[24][1]) and k.startswith("conv_mfma")]
+    assert name % 2 not in convs and name % 1 in convs, convs
+    dec.close()
+
+
 def test_attention_scratch_holds_partial_outputs_only_where_keys_are_split():
     """Fragments of q, k, v (tiles of 32 tokens) and o; from 16 385 tokens on, and up to 64, one range holds all keys and nothing else is needed."""
     for n, h, w in ((1, 129, 130), (2, 1, 16385), (1, 200, 200), (1, 8, 8), (3, 1, 1)):

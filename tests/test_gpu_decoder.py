@@ -276,6 +276,22 @@ def test_upsampling_convolutions_with_groups_of_one_and_two_channels():
     assert err <= G.TOL["f16"], err
 
 
+def test_rows_handed_over_by_256_channel_tiles():
+    """600 tiles of 256 channels: the 32 -> 256 layer at 240x320 merges its own rows on them; without the hand-over it runs on 128-channel tiles."""
+    chans = (512, 32, 256)
+    cfg = small_cfg(wmdec.F16)
+    cfg.latent_h, cfg.latent_w, cfg.num_levels, cfg.max_batch = 60, 80, 3, 1
+    cfg.level_channels[1], cfg.level_channels[2] = 32, 256
+    dec = wmdec.Decoder(cfg)
+    assert "conv_mfma_kernel<wmdec::f16_t, wmdec::f16_t, 8, 16, 1, 4, 2, 3, 32, 2, 0, 0>" in [k for k, _, _ in dec.step_info()]
+    dec.close()
+    weights = synth.draw_params(synth.decoder_weight_spec(level_channels=chans, resblocks_per_level=2), synth.weight_seed(17), random_affine=True)
+    z = synth.latent_sequence(workload=17, frames=1, h=60, w=80)
+    got = run_decoder(cfg, weights, z)
+    cfg.separate_merge_launch = 1
+    assert ref.rel_err(got, run_decoder(cfg, weights, z)) <= G.TOL["f16"]
+
+
 def test_level_of_eight_channels():
     """Normalised convolutions of eight input channels leave no moments (the kernel for few channels does not normalise)."""
     chans = (512, 8, 64)
