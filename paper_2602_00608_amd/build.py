@@ -1,9 +1,11 @@
 """Build libwmdec.so (HIP, gfx950 only) in-tree with hipcc, and the native Python binding with g++."""
 import concurrent.futures
+import glob
 import os
 import subprocess
 import sys
 import sysconfig
+import tempfile
 
 if __package__:
     from . import asm_check
@@ -19,8 +21,8 @@ BINDING = os.path.join(HERE, "_binding.so")
 SOURCES = ["api.cpp", "kernels_gn.hip", "kernels_conv_direct.hip", "kernels_conv_mfma.hip", "kernels_conv_rows.hip", "kernels_conv_ksplit.hip", "kernels_conv_up.hip",
            "kernels_conv_taps.hip", "kernels_misc.hip", "kernels_attn.hip", "kernels_adaln.hip"]
 
-# kernels with matrix instructions in inline assembly, whose code asm_check reads: source -> kernel
-CHECKED = {"kernels_attn.hip": "flash_attn_kernel"}
+# what asm_check looks for beside the stores of every source: kernels with matrix instructions in inline assembly, kernels that must not spill
+CHECKED = {"kernels_attn.hip": {"scores": "flash_attn_kernel"}}
 
 FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -49,19 +51,24 @@ def _compile(src, force):
     path = os.path.join(CSRC, src)
     if not force and os.path.exists(obj) and os.path.getmtime(obj) >= max(os.path.getmtime(path), _headers_mtime()):
         return obj
-    cmd = ["hipcc"] + FLAGS + ["-c", path, "-o", obj]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    out = "\n".join(l for l in (r.stdout + r.stderr).splitlines()
-                    if "packed-fp32-ops" not in l and "is not a recognized feature" not in l)
-    if r.returncode != 0:
-        raise RuntimeError("hipcc failed for %s:\n%s" % (src, out))
-    if out.strip():
-        sys.stderr.write(out + "\n")
-    if src in CHECKED:
-        faults = asm_check.check(device_assembly(src), CHECKED[src])
-        if faults:
+    with tempfile.TemporaryDirectory() as temps:   # the device assembly on its way into the object
+        cmd = ["hipcc"] + FLAGS + ["-save-temps", "-c", path, "-o", obj]
+        r = subprocess.run(cmd, capture_output=True, text=True, cwd=temps)
+        out = "\n".join(l for l in (r.stdout + r.stderr).splitlines()
+                        if "packed-fp32-ops" not in l and "is not a recognized feature" not in l)
+        if r.returncode != 0:
+            raise RuntimeError("hipcc failed for %s:\n%s" % (src, out))
+        if out.strip():
+            sys.stderr.write(out + "\n")
+        assembly = glob.glob(os.path.join(temps, "*amdgcn*.s"))
+        if len(assembly) != 1:
             os.remove(obj)
-            raise RuntimeError("%s: the compiled code breaks what its inline assembly relies on:\n%s" % (src, "\n".join(faults)))
+            raise RuntimeError("%s: %d device assembly files" % (src, len(assembly)))
+        with open(assembly[0]) as f:
+            faults = asm_check.check_source(f.read(), **CHECKED.get(src, {}))
+    if faults:
+        os.remove(obj)
+        raise RuntimeError("%s: the compiled code breaks what its source relies on:\n%s" % (src, "\n".join(faults)))
     return obj
 
 
