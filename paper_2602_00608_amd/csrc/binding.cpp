@@ -54,24 +54,26 @@ struct Reader {
       default: ok = false; PyErr_SetString(PyExc_KeyError, "tensor type is none of float32, bfloat16, float16"); return 0;
     }
   }
-  int size(int i, int dim, int dims) {   // of a tensor of `dims` dimensions
+  int size(int i, int dim, int dims, bool more = false) {   // of a tensor of `dims` dimensions, or of more
     const at::Tensor* t = tensor(i);
     if (!t) return 0;
-    if (t->dim() != dims) { ok = false; PyErr_Format(PyExc_ValueError, "argument %d: %d dimensions expected, got %d", i, dims, (int)t->dim()); return 0; }
+    if (t->dim() < dims || (t->dim() > dims && !more)) { ok = false; PyErr_Format(PyExc_ValueError, "argument %d: %d dimensions expected, got %d", i, dims, (int)t->dim()); return 0; }
     return (int)t->size(dim);
   }
   size_t bytes(int i) { const at::Tensor* t = tensor(i); return t ? (size_t)t->nbytes() : 0; }
-  int integer(int i) {
+  int integer(int i) {   // the low bits of what can stand for an index, as ctypes passes it
     if (!ok) return 0;
-    const long v = PyLong_AsLong(args[i]);
-    if (v == -1 && PyErr_Occurred()) ok = false;
+    const unsigned long v = PyLong_AsUnsignedLongMask(args[i]);
+    if (v == (unsigned long)-1 && PyErr_Occurred()) ok = false;
     return (int)v;
   }
-  int truth(int i) {
+  int flag(int i) {   // int() of the argument: None and texts that are no number are refused, 0.5 is 0
     if (!ok) return 0;
-    const int v = PyObject_IsTrue(args[i]);
-    if (v < 0) ok = false;
-    return v;
+    PyObject* whole = PyNumber_Long(args[i]);
+    const unsigned long v = whole ? PyLong_AsUnsignedLongMask(whole) : 0;
+    Py_XDECREF(whole);
+    if (PyErr_Occurred()) ok = false;
+    return (int)v;
   }
   float real(int i) {
     if (!ok) return 0.f;
@@ -115,9 +117,9 @@ struct ConvHead {
   const float *mean, *rstd, *gamma, *beta, *bias;
   int dt, groups, silu, cin;
   ConvHead(Reader& r, int at)
-      : x(r.ptr(at)), w(nullptr), dt(r.dtype(at)), cin(r.size(at, 3, 4)) {
+      : x(r.ptr(at)), w(nullptr), dt(r.dtype(at)), cin(r.size(at, 3, 4, true)) {
     mean = (const float*)r.ptr(at + 1); rstd = (const float*)r.ptr(at + 2); gamma = (const float*)r.ptr(at + 3); beta = (const float*)r.ptr(at + 4);
-    groups = r.integer(at + 5); silu = r.truth(at + 6);
+    groups = r.integer(at + 5); silu = r.flag(at + 6);
     w = r.ptr(at + 7); bias = (const float*)r.ptr(at + 8);
   }
 };
@@ -141,7 +143,7 @@ PyObject* conv_shortcut(PyObject*, PyObject* const* a, Py_ssize_t na) {
   if (!r.ok) return nullptr;
   const ConvHead c(r, 0);
   const void *x2 = r.ptr(9), *w2 = r.ptr(10);
-  const int cin2 = r.size(9, 3, 4);
+  const int cin2 = r.size(9, 3, 4, true);
   const float* bias2 = (const float*)r.ptr(11);
   const Output y(r, 12);
   void* stream = r.address(13);
@@ -204,7 +206,7 @@ PyObject* adaln(PyObject*, PyObject* const* a, Py_ssize_t na) {
   const int rows = wt && wt->dim() > 0 ? (int)wt->size(0) : 0;
   const float* bias = (const float*)r.ptr(2);
   float* out = (float*)r.ptr(3);
-  const int silu = r.truth(4);
+  const int silu = r.flag(4);
   void* stream = r.address(5);
   WMDEC_RETURN(g_adaln(c, cdt, w, wdt, bias, out, batch, d, rows, silu, stream));
 }
