@@ -88,13 +88,19 @@ struct Reader {
     return v;
   }
 };
+// Other threads run Python until its end, also where that is an exception: the handler in entry() sets a Python error.
+struct ThreadsAllowed {
+  PyThreadState* state = PyEval_SaveThread();
+  ~ThreadsAllowed() { PyEval_RestoreThread(state); }
+};
 #define WMDEC_RETURN(call_)                    \
   do {                                         \
     if (!r.ok) return nullptr;                 \
     int status;                                \
-    Py_BEGIN_ALLOW_THREADS                     \
-    status = call_;                            \
-    Py_END_ALLOW_THREADS                       \
+    {                                          \
+      ThreadsAllowed threads;                  \
+      status = call_;                          \
+    }                                          \
     return PyLong_FromLong(status);            \
   } while (0)
 

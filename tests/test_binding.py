@@ -85,3 +85,23 @@ for f in (adaln, lambda silu: conv(2, silu)):
 for groups in (None, 2.0, "2"): refused(TypeError, conv, groups, 1)
 refused(ValueError, conv, 2, 1, Device(2, 2, 3))
 """)
+
+
+def test_an_exception_from_an_entry_point_becomes_a_python_error(tmp_path):
+    _with_stand_in(tmp_path, r"""
+import threading
+def call():
+    for _ in range(200): refused(RuntimeError, adaln, True)
+others = [threading.Thread(target=call) for _ in range(4)]
+for t in others: t.start()
+call()
+for t in others: t.join()
+try: adaln(True)
+except RuntimeError as e: assert str(e) == "no memory for it", e
+""", """
+#include <stdexcept>
+extern "C" {
+int conv() { return 0; }
+int adaln() { throw std::runtime_error("no memory for it"); }
+}
+""")
