@@ -22,7 +22,7 @@ SOURCES = ["api.cpp", "kernels_gn.hip", "kernels_conv_direct.hip", "kernels_conv
            "kernels_conv_taps.hip", "kernels_misc.hip", "kernels_attn.hip", "kernels_adaln.hip"]
 
 # what asm_check looks for beside the stores of every source: kernels with matrix instructions in inline assembly, kernels that must not spill
-CHECKED = {"kernels_attn.hip": {"scores": "flash_attn_kernel"}}
+CHECKED = {"kernels_attn.hip": {"scores": "flash_attn_kernel"}, "kernels_conv_rows.hip": {"spills": "conv_mfma_kernel"}}
 
 FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -247,15 +247,26 @@ template <int W> __device__ __forceinline__ float swap_sum(float v) {
   return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
 }
 
+// value of the mirrored lane in eight, in sixteen lanes
+__device__ __forceinline__ float mirror8(float v) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xf, 0xf, true)); }
+__device__ __forceinline__ float mirror16(float v) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xf, 0xf, true)); }
+// sum over WIDTH consecutive lanes (a power of two up to 16), in all of them
+template <int WIDTH> __device__ __forceinline__ float lane_group_sum(float v) {
+  if constexpr (WIDTH > 1) v += quad_xor<1>(v);
+  if constexpr (WIDTH > 2) v += quad_xor<2>(v);
+  if constexpr (WIDTH > 4) v += mirror8(v);
+  if constexpr (WIDTH > 8) v += mirror16(v);
+  return v;
+}
+
 // Moments of a group's channels (cpg consecutive lanes, a power of two up to 32) over the same pixels, in all of these lanes: the mean
 // first, then the squares about it.
 __device__ __forceinline__ Moments merge_channels(Moments m, int cpg) {
   auto sum = [&](float v) {
-    auto dpp = [](float x, auto c) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(c)::value, 0xf, 0xf, true)); };
     if (cpg > 1) v += quad_xor<1>(v);
     if (cpg > 2) v += quad_xor<2>(v);
-    if (cpg > 4) v += dpp(v, std::integral_constant<int, 0x141>{});   // mirrored in eight lanes
-    if (cpg > 8) v += dpp(v, std::integral_constant<int, 0x140>{});   // ... in sixteen
+    if (cpg > 4) v += mirror8(v);
+    if (cpg > 8) v += mirror16(v);
     if (cpg > 16) v = swap_sum<16>(v);
     return v;
   };

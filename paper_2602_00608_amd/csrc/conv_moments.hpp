@@ -13,73 +13,104 @@ namespace wmdec {
 //              pixels, the blocks of that kernel's moments.
 enum ConvMode { kPlain = 0, kRows4 = 1, kQuarters = 2 };
 
-// Moments of a wavefront's stored values in the making: per channel of the lane's octet sums shifted by the lane's first value,
-// over n pixels.
-struct LaneMoments { float n, shift[8], s[8], q[8]; };
+// Moments of a wavefront's stored values in the making: per channel of the lane (CH neighbouring ones) shifted sums over n pixels.
+template <int CH> struct LaneMoments { float n, shift[CH], s[CH], q[CH]; };
 
-// ... merged per group and written.  A lane merges its channels of a group (PARTS groups per octet, or its part of a larger one),
-// then the lanes that hold the same octet, and those of the group's other octets, are summed in the vector ALU: the mean first,
+// ... merged per group and written, N of them side by side (each is a chain of dependent lane moves).  A lane merges its channels of a
+// group (PARTS groups, or its part of a larger one), then the lanes that hold the same channels, and those of the group's other
+// channels, are summed in the vector ALU (lanes): the mean first,
 // then the squares about it.  (Through LDS, with a lane per channel that walked the others' sums and re-centred them one by
-// one, this was 13 of the 122 us of 128 -> 128 channels at 480x720, and 1.5 of 36 at 60x90.)  OCTETS: octets of channels of the wavefront;
-// LANE_ROWS: a row of 16 lanes holds one of four octets, otherwise lane l holds octet l % OCTETS.
-template <int OCTETS, int PARTS, bool LANE_ROWS>
-__device__ __forceinline__ void emit_moments(const LaneMoments& st, int lane, int co_w, Moments* dst, int cpg, int stats_stride, bool handed_over) {
-  static_assert(!LANE_ROWS || OCTETS == 4, "a row of lanes per octet");
-  constexpr int PC = 8 / PARTS;
-  auto lanes = [&](float v) {
-    if constexpr (LANE_ROWS) {
-      v += row_rotate<1>(v);
-      v += row_rotate<2>(v);
-      v += row_rotate<4>(v);
-      v += row_rotate<8>(v);
-      if (cpg > 8) v = swap_sum<16>(v);
-      if (cpg > 16) v = swap_sum<32>(v);
-    } else {
-      if constexpr (OCTETS <= 4) v += row_rotate<4>(v);
-      v += row_rotate<8>(v);
-      v = swap_sum<32>(swap_sum<16>(v));
-      if (cpg > 8) v += quad_xor<1>(v);
-      if (cpg > 16) v += quad_xor<2>(v);
-    }
-    return v;
-  };
-  const float inv = st.n > 0.f ? __builtin_amdgcn_rcpf(st.n) : 0.f;
-  const float n = lanes(st.n), ninv = n > 0.f ? __builtin_amdgcn_rcpf(n) : 0.f;   // 1 ulp: `rest` corrects the mean
+// one, this was 13 of the 122 us of 128 -> 128 channels at 480x720, and 1.5 of 36 at 60x90.)  co: the lane's first channel; writes: whether
+// it is the lane that writes its groups; SOME: dst is null where there are none; all_n: pixels times lanes of a group where that is known, otherwise 0.
+template <int CH, int PARTS, bool SOME, int N, typename Lanes>
+__device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Moments* const (&dst)[N], int co, bool writes, int cpg, int stats_stride, bool handed_over,
+                                             float all_n, Lanes&& lanes) {
+  constexpr int PC = CH / PARTS;
+  float inv[N], n[N], ninv[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    inv[k] = st[k].n > 0.f ? __builtin_amdgcn_rcpf(st[k].n) : 0.f;
+    n[k] = all_n > 0.f ? all_n : lanes(st[k].n);
+    ninv[k] = n[k] > 0.f ? __builtin_amdgcn_rcpf(n[k]) : 0.f;   // 1 ulp: `rest` corrects the mean
+  }
 #pragma unroll
   for (int g = 0; g < PARTS; ++g) {
-    float mean[PC], m = 0.f, q = 0.f;
+    float m[N], q[N], dev[N], mid[N], rest[N];
 #pragma unroll
-    for (int e = 0; e < PC; ++e) {
-      const int c = g * PC + e;
-      const float ds = quotient(st.s[c], st.n, inv), m2 = st.q[c] - st.s[c] * ds;
-      mean[e] = st.shift[c] + ds;
-      m += mean[e];
-      q += m2 < 0.f ? 0.f : m2;     // (NaN stays NaN)
+    for (int k = 0; k < N; ++k) {
+      float mean[PC];
+      m[k] = 0.f; q[k] = 0.f; dev[k] = 0.f;
+#pragma unroll
+      for (int e = 0; e < PC; ++e) {
+        const int c = g * PC + e;
+        const float ds = quotient(st[k].s[c], st[k].n, inv[k]), m2 = st[k].q[c] - st[k].s[c] * ds;
+        mean[e] = st[k].shift[c] + ds;
+        m[k] += mean[e];
+        q[k] += m2 < 0.f ? 0.f : m2;     // (NaN stays NaN)
+      }
+      m[k] = st[k].n > 0.f ? m[k] * (1.f / PC) : 0.f;     // the shift of a lane without pixels has no meaning
+#pragma unroll
+      for (int e = 0; e < PC; ++e) { const float d = mean[e] - m[k]; dev[k] = fmaf(d, d, dev[k]); }
     }
-    m = st.n > 0.f ? m * (1.f / PC) : 0.f;     // the shift of a lane without pixels has no meaning
-    float dev = 0.f;
 #pragma unroll
-    for (int e = 0; e < PC; ++e) { const float d = mean[e] - m; dev = fmaf(d, d, dev); }
-    const float mid = lanes(st.n * m) * ninv;
-    const float d = m - mid, nd = st.n * d;
-    const float rest = lanes(nd) * ninv;       // what the roundings of mid left
-    q = lanes(st.n > 0.f ? fmaf(st.n, dev, fmaf(nd * PC, d, q)) : 0.f) - n * PC * rest * rest;
-    const Moments out{n * PC, mid + rest, q < 0.f ? 0.f : q};
-    const int octet = LANE_ROWS ? lane >> 4 : lane;
-    if ((LANE_ROWS ? (lane & 15) == 0 : lane < OCTETS) && ((octet * 8) & (cpg - 1)) == 0) {
-      Moments* at = dst + (size_t)((co_w + octet * 8 + g * PC) / cpg) * stats_stride;
-      if (handed_over) store_device(at, out);   // another workgroup of this launch may merge them, see the row hand-over of the kernels
-      else *at = out;
+    for (int k = 0; k < N; ++k) mid[k] = lanes(st[k].n * m[k]) * ninv[k];
+#pragma unroll
+    for (int k = 0; k < N; ++k) rest[k] = lanes(st[k].n * (m[k] - mid[k])) * ninv[k];       // what the roundings of mid left
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const float d = m[k] - mid[k], nd = st[k].n * d;
+      q[k] = lanes(st[k].n > 0.f ? fmaf(st[k].n, dev[k], fmaf(nd * PC, d, q[k])) : 0.f) - n[k] * PC * rest[k] * rest[k];
+    }
+    if (writes) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        if (SOME && !dst[k]) continue;
+        const Moments out{n[k] * PC, mid[k] + rest[k], q[k] < 0.f ? 0.f : q[k]};
+        Moments* at = dst[k] + (size_t)((co + g * PC) / cpg) * stats_stride;
+        if (handed_over) store_device(at, out);   // another workgroup of this launch may merge them, see the row hand-over of the kernels
+        else *at = out;
+      }
     }
   }
 }
 
-template <int OCTETS, bool LANE_ROWS>
-__device__ __forceinline__ void emit_groups(const LaneMoments& st, int lane, int co_w, Moments* dst, int cpg, int stats_stride, bool handed_over) {
-  if (cpg >= 8) emit_moments<OCTETS, 1, LANE_ROWS>(st, lane, co_w, dst, cpg, stats_stride, handed_over);
-  else if (cpg == 4) emit_moments<OCTETS, 2, LANE_ROWS>(st, lane, co_w, dst, cpg, stats_stride, handed_over);
-  else if (cpg == 2) emit_moments<OCTETS, 4, LANE_ROWS>(st, lane, co_w, dst, cpg, stats_stride, handed_over);
-  else emit_moments<OCTETS, 8, LANE_ROWS>(st, lane, co_w, dst, cpg, stats_stride, handed_over);
+// Lane l holds octet l % OCTETS of the wavefront's channels.
+template <int OCTETS>
+__device__ __forceinline__ void emit_octets(const LaneMoments<8> (&st)[1], int lane, int co_w, Moments* const (&dst)[1], int cpg, int stats_stride, bool handed_over) {
+  auto lanes = [&](float v) {
+    if constexpr (OCTETS <= 4) v += row_rotate<4>(v);
+    v += row_rotate<8>(v);
+    v = swap_sum<32>(swap_sum<16>(v));
+    if (cpg > 8) v += quad_xor<1>(v);
+    if (cpg > 16) v += quad_xor<2>(v);
+    return v;
+  };
+  const int co = co_w + lane * 8;
+  const bool writes = lane < OCTETS && ((lane * 8) & (cpg - 1)) == 0;
+  if (cpg >= 8) emit_moments<8, 1, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
+  else if (cpg == 4) emit_moments<8, 2, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
+  else if (cpg == 2) emit_moments<8, 4, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
+  else emit_moments<8, 8, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
+}
+
+// Lane l holds channels 2 (l % 16) and the next of 32, of the pixels of quarter l / 16; full: all lanes hold the same number of them.
+// A form for every size of a group: with the size looked at between the lane moves, the branches took longer than they do.
+template <int N>
+__device__ __forceinline__ void emit_pairs(const LaneMoments<2> (&st)[N], bool full, int lane, int co_w, Moments* const (&dst)[N], int cpg, int stats_stride, bool handed_over) {
+  auto emit = [&](auto cpg_c) __attribute__((always_inline)) {
+    constexpr int CPG = decltype(cpg_c)::value, PARTS = CPG == 1 ? 2 : 1, WIDTH = CPG == 1 ? 1 : CPG / 2;   // lanes of a group
+    auto lanes = [&](float v) {
+      v = swap_sum<32>(swap_sum<16>(v));
+      return lane_group_sum<WIDTH>(v);
+    };
+    emit_moments<2, PARTS, (N > 1)>(st, dst, co_w + 2 * (lane & 15), lane < 16 && lane % WIDTH == 0, CPG, stats_stride, handed_over, full ? st[0].n * (4.f * WIDTH) : 0.f, lanes);
+  };
+  if (cpg == 16) emit(std::integral_constant<int, 16>{});
+  else if (cpg == 8) emit(std::integral_constant<int, 8>{});
+  else if (cpg == 4) emit(std::integral_constant<int, 4>{});
+  else if (cpg == 2) emit(std::integral_constant<int, 2>{});
+  else if (cpg == 1) emit(std::integral_constant<int, 1>{});
+  else emit(std::integral_constant<int, 32>{});
 }
 
 }  // namespace wmdec

@@ -107,7 +107,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
 #pragma unroll
     for (int mi = 0; mi < RD && mi < MI; ++mi) request(mi);
   }
-  LaneMoments st = {};
+  LaneMoments<8> st = {};
   put(wave_lds, 0);
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
@@ -182,7 +182,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
         if ((lm & (p.cpg - 1)) == 0 && m.n > 0.f) dst[(size_t)((co_w + lm) / p.cpg) * p.stats_stride + lk] = m;
       }
     } else if (mi + 1 == MI) {
-      if (p.stats) emit_groups<NI * 4, false>(st, lane, co_w, p.stats, p.cpg, p.stats_stride, p.handed_over);
+      if (p.stats) emit_octets<NI * 4>({st}, lane, co_w, {p.stats}, p.cpg, p.stats_stride, p.handed_over);
     }
     if (mi + 1 < MI && !ahead) put(wave_lds + (mi + 1) % PATCHES * 32 * RW, mi + 1);
   }

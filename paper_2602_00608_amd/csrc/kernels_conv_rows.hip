@@ -8,9 +8,13 @@
 // Why this MFMA: the power limit decides the clock of these kernels, and 16x16x32 does a sixth more under it than 32x32x16
 // (operands in registers, values as in a layer: 1.95 against 1.68 PFLOP/s, at 1.95 and 1.70 GHz).  One MFMA takes 32 channels of a row of
 // 16 pixels and 16 output channels.
-// A = weights, B = pixels: a lane then holds four consecutive output channels of a pixel; the two tiles of a 32-channel fragment pair take its rows
-// dealt so that a lane holds eight (tile h, row m: channel 8 (m / 4) + 4 h + m % 4), and residual and output move as
-// 16-byte vectors straight from the accumulators.
+// A = pixels, B = weights: lane l then holds four consecutive pixels, 4 (l / 16) .. + 3, of one output channel of a tile; the two tiles of 32
+// channels take the even and the odd ones, so that it is channels 2 (l % 16) and the next.  Residual and output move as pairs
+// straight from the accumulators, 16 consecutive lanes on the 64 contiguous bytes of a pixel.  (With the operands the other way round a
+// lane holds eight channels of one pixel, a 16-byte vector, but the four lanes on a pixel's 64 bytes are 16 lanes apart: every vector is
+// a request of its own, and the moments of eight channels a lane spilled registers of the fullest forms.  us, that / this: plain input, 32 -> 128
+// channels at 480x720 34.4 / 29.4, with residual 40.4 / 35.8; 32 -> 256 eight samples of 68x92 19.7 / 12.7, with moments 28.1 / 19.2; with
+// SiLU, 256 -> 256 at the same size 58.3 / 56.9, 65.0 / 63.5.)
 #include <stdio.h>
 
 #include <mutex>
@@ -66,7 +70,7 @@ __device__ __forceinline__ void sweep_chunk(const T* buf, __amdgpu_buffer_rsrc_t
     if constexpr (!LAST || sp < STEPS) {
       const int at = (sp < STEPS ? bcur : bnext) + weight_offset<NI>(sp % STEPS, tap_stride);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) bq[sp % D][h] = load_fragment(wrsrc, lane_w, at + 64 * h);
+      for (int h = 0; h < 2; ++h) bq[sp % D][h] = load_fragment(wrsrc, lane_w, at + 16 * h);
     }
     __builtin_amdgcn_sched_barrier(0);
     // row r is the last to read its fragment, and there is one to take its place
@@ -75,7 +79,7 @@ __device__ __forceinline__ void sweep_chunk(const T* buf, __amdgpu_buffer_rsrc_t
       constexpr int r = decltype(r_c)::value;
       static_for<2>([&](auto h_c) {
         constexpr int h = decltype(h_c)::value;
-        acc[r][2 * ni + h] = Mma<T>::m16(bq[s % D][h], af[(g * FRAGS + r + ky) % SLOTS], acc[r][2 * ni + h]);
+        acc[r][2 * ni + h] = Mma<T>::m16(af[(g * FRAGS + r + ky) % SLOTS], bq[s % D][h], acc[r][2 * ni + h]);
         if constexpr (h == 1 && last(r)) read(std::integral_constant<int, g * FRAGS + r + ky + SLOTS>{});
         slice(std::integral_constant<int, (s * R + r) * 2 + h>{});
         __builtin_amdgcn_sched_barrier(0);
@@ -84,6 +88,11 @@ __device__ __forceinline__ void sweep_chunk(const T* buf, __amdgpu_buffer_rsrc_t
   });
 }
 
+// Rows of the residual that are on their way at a time.  The last sweep requests the first ones, a pixel of the lane behind each of
+// its last MFMAs, the epilogue the one that takes a row's place when that is used up.  All rows of a patch would be spilled where the accumulators
+// are 128 registers, or the values to store as many as the accumulators.
+constexpr int held_rows(int th, int ni, size_t out_size) { return ni == 1 && out_size == 2 ? th : 4; }
+
 struct EpilogueParams {
   __amdgpu_buffer_rsrc_t res, y;           // the sample's residual and output, with its size: accesses outside are dropped
   int h, w, cout;
@@ -91,82 +100,106 @@ struct EpilogueParams {
   bool handed_over;
 };
 
-// the residual vector of row r and channels co .. co + 31 (lane: pixel lane % 16, channel octet lane / 16)
-template <typename T> __device__ __forceinline__ u32x4 load_residual(const EpilogueParams& p, int lane, int row, int tx0, int co) {
-  const int px = lane & 15, oct = lane >> 4;
-  const unsigned at = row < p.h && tx0 + px < p.w ? (unsigned)(px * p.cout + oct * 8) : kOutside;
-  return __builtin_amdgcn_raw_buffer_load_b128(p.res, (int)(at * sizeof(T)), vector_base(row, tx0, p.h, p.w, p.cout, co) * (int)sizeof(T), 0);
+// element offset of a lane's channels at pixel i of its four, from channel 0 of the tile's first pixel; outside the image: kOutside
+__device__ __forceinline__ unsigned lane_offset(const EpilogueParams& p, int lane, int tx0, int i) {
+  const int px = 4 * (lane >> 4) + i;
+  return tx0 + px < p.w ? (unsigned)(px * p.cout + 2 * (lane & 15)) : kOutside;
+}
+// the residual of channels co .. co + 31 of a row's pixels i (rows past the image take the last one's: no output is made of it)
+template <typename T> __device__ __forceinline__ uint32_t load_residual(const EpilogueParams& p, unsigned at, int row, int tx0, int co) {
+  return __builtin_amdgcn_raw_buffer_load_b32(p.res, (int)(at * sizeof(T)), vector_base(row, tx0, p.h, p.w, p.cout, co) * (int)sizeof(T), 0);
 }
 
-// Epilogue of one wavefront: bias, residual, one rounding, store: a pixel's 32 channels are 64 contiguous bytes.  (Through LDS
+// Epilogue of one wavefront: bias, residual, one rounding, store.  (Through LDS
 // patches, as in kernels_conv_mfma.hip, the same lanes write 64 values one by one and wait for them.)  The bias is added to
 // the finished sums: accumulators that start from it round every partial sum at its exponent.
-// rv: the residual of the first 32 channels, requested by the last sweep.
-// Moments, of the values as stored: one triple per group for all R rows, or (kRows4) for every four of them.
-template <typename T, typename TO, int R, int NI, bool RES, bool STATS, int MODE>
-__device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], u32x4 (&rv)[NI][R], const float* s_bias, int lane, int ty0, int tx0, int co_w,
+// rv: the residual of the first rows, on their way.
+// Moments, of the values as stored: one triple per group for all R rows, or (kRows4) for every four of them.  FULL: no pixel of the patch lies
+// outside the image (the moments need no masks, and the rows are scheduled as one).
+template <typename T, typename TO, int R, int NI, bool RES, bool STATS, bool FULL, int MODE>
+__device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], uint32_t (&rv)[held_rows(R, NI, sizeof(TO))][4], const float* s_bias, int lane, int ty0, int tx0, int co_w,
                                          const EpilogueParams& p) {
-  constexpr int EMIT = MODE == kRows4 ? 4 : R;   // rows of a triple
+  constexpr int EMIT = MODE == kRows4 ? 4 : R, HELD = held_rows(R, NI, sizeof(TO));   // rows of a triple
   static_assert(R % EMIT == 0, "whole triples");
-  const int px = lane & 15, oct = lane >> 4;
-  const bool col_ok = tx0 + px < p.w;
-  const unsigned lane_off = (unsigned)(px * p.cout + oct * 8);
-  if constexpr (RES) {
+  const bool columns = tx0 + 16 <= p.w;                           // all columns lie inside the image,
+  const int cols = min(max(p.w - tx0 - 4 * (lane >> 4), 0), 4);   // and of the lane's four so many
+  unsigned at[4];
 #pragma unroll
-    for (int ni = 1; ni < NI; ++ni)
-#pragma unroll
-      for (int r = 0; r < R; ++r) rv[ni][r] = load_residual<T>(p, lane, ty0 + r, tx0, co_w + 32 * ni);
-  }
+  for (int i = 0; i < 4; ++i) at[i] = lane_offset(p, lane, tx0, i);
+  LaneMoments<2> st[NI * (R / EMIT)];
+  Moments* dst[NI * (R / EMIT)];
 #pragma unroll
   for (int ni = 0; ni < NI; ++ni) {
-    const f32x4 b0 = *reinterpret_cast<const f32x4*>(s_bias + 32 * ni + 8 * oct), b1 = *reinterpret_cast<const f32x4*>(s_bias + 32 * ni + 8 * oct + 4);
-    LaneMoments moments[R / EMIT] = {};   // (written behind the last row: in between, the compiler would spill the accumulators)
+    const float2 bias = *reinterpret_cast<const float2*>(s_bias + 32 * ni + 2 * (lane & 15));
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const f32x4 lo = acc[r][2 * ni] + b0, hi = acc[r][2 * ni + 1] + b1;
-      float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      if constexpr (RES) {
-        float rf[8];
-        unpack8<T>(rv[ni][r], rf);
+    for (int t = 0; t < R / EMIT; ++t) {
+      float n = 0.f, shift[2] = {0.f, 0.f}, s[2][4] = {}, q[2][4] = {};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] += rf[e];
-      }
-      const bool ok = ty0 + r < p.h && col_ok;
-      const int at = (int)((ok ? lane_off : kOutside) * sizeof(TO)), base = vector_base(ty0 + r, tx0, p.h, p.w, p.cout, co_w + 32 * ni) * (int)sizeof(TO);
-      float sv[8];   // as stored
-      if constexpr (sizeof(TO) == 4) {
-        u32x4 a = __builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), b = __builtin_bit_cast(u32x4, f32x4{v[4], v[5], v[6], v[7]});
-        store_vector(p.y, a, at, base);
-        store_vector(p.y, b, at + 16, base);
-        const f32x4 sa = __builtin_bit_cast(f32x4, a), sb = __builtin_bit_cast(f32x4, b);
+      for (int r = t * EMIT; r < (t + 1) * EMIT; ++r) {
+        const int held = (ni * R + r) % HELD, ahead = ni * R + r + HELD;   // place of this row's residual, and the row that takes it next
+        auto request = [&]() {
+          if constexpr (RES) {
+            if (ahead < NI * R) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { sv[e] = sa[e]; sv[4 + e] = sb[e]; }
-      } else {
-        u32x4 packed = u32x4{pack2<T>(v[0], v[1]), pack2<T>(v[2], v[3]), pack2<T>(v[4], v[5]), pack2<T>(v[6], v[7])};
-        store_vector(p.y, packed, at, base);
-        unpack8<T>(packed, sv);
-      }
-      if constexpr (STATS) {
-        LaneMoments& st = moments[r / EMIT];
-        if (r % EMIT == 0) {   // (outside the image only if all vectors of the lane's triple are)
-          st.n = 0.f;
+              for (int i = 0; i < 4; ++i) rv[held][i] = load_residual<T>(p, at[i], ty0 + ahead % R, tx0, co_w + 32 * (ahead / R));
+            }
+          }
+        };
+        if (!FULL && ty0 + r >= p.h) { request(); continue; }
+        const int base = vector_base(ty0 + r, tx0, p.h, p.w, p.cout, co_w + 32 * ni) * (int)sizeof(TO);
+        float v[4][2];   // as stored
 #pragma unroll
-          for (int e = 0; e < 8; ++e) { st.shift[e] = sv[e]; st.s[e] = 0.f; st.q[e] = 0.f; }
+        for (int i = 0; i < 4; ++i) {
+          v[i][0] = acc[r][2 * ni][i] + bias.x;
+          v[i][1] = acc[r][2 * ni + 1][i] + bias.y;
+          if constexpr (RES) { v[i][0] += unpack_lo<T>(rv[held][i]); v[i][1] += unpack_hi<T>(rv[held][i]); }
+          if constexpr (sizeof(TO) == 4) {
+            f32x2 pair{v[i][0], v[i][1]};
+            asm volatile("" : "+v"(pair));   // (in this order: the compiler would form all pairs first)
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, pair), p.y, (int)(at[i] * sizeof(TO)), base, 0);
+            v[i][0] = pair[0]; v[i][1] = pair[1];
+          } else {
+            uint32_t word = pack2<T>(v[i][0], v[i][1]);
+            asm("" : "+v"(word));   // (the stored values are taken from it: the compiler would convert each once more)
+            __builtin_amdgcn_raw_buffer_store_b32(word, p.y, (int)(at[i] * sizeof(TO)), base, 0);
+            v[i][0] = unpack_lo<T>(word); v[i][1] = unpack_hi<T>(word);
+          }
         }
-        if (ok) {
+        request();
+        if constexpr (STATS) {
+          n += FULL ? 4.f : (float)cols;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) { const float dv = sv[e] - st.shift[e]; st.s[e] += dv; st.q[e] = fmaf(dv, dv, st.q[e]); }
-          st.n += 1.f;
+          for (int e = 0; e < 2; ++e) {
+            // Shifted by the mean of the lane's first four pixels, a fourth of whichever is far off; in a ragged patch by the first (outside the image only if
+            // all pixels of the lane are).
+            if (r == t * EMIT) shift[e] = FULL || columns ? 0.25f * ((v[0][e] + v[1][e]) + (v[2][e] + v[3][e])) : v[0][e];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float d = v[i][e] - shift[e];
+              s[e][i] += d; q[e][i] = fmaf(d, d, q[e][i]);
+            }
+          }
         }
       }
-    }
-    if constexpr (STATS) {
+      if (STATS && !FULL) {   // a column outside the image has a sum of its own
 #pragma unroll
-      for (int t = 0; t < R / EMIT; ++t)   // (kRows4: rows past the image have no slot)
-        if (MODE != kRows4 || ty0 + t * EMIT < p.h)
-          emit_groups<4, true>(moments[t], lane, co_w + 32 * ni, p.stats + t * p.row_stride, p.cpg, p.stats_stride, p.handed_over);
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) { s[e][i] = i < cols ? s[e][i] : 0.f; q[e][i] = i < cols ? q[e][i] : 0.f; }
+      }
+      LaneMoments<2>& own = st[ni * (R / EMIT) + t];
+      own.n = n;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        own.shift[e] = shift[e];
+        own.s[e] = (s[e][0] + s[e][1]) + (s[e][2] + s[e][3]);
+        own.q[e] = (q[e][0] + q[e][1]) + (q[e][2] + q[e][3]);
+      }
+      dst[ni * (R / EMIT) + t] = FULL || MODE != kRows4 || ty0 + t * EMIT < p.h   // (kRows4: rows past the image have no slot)
+                                     ? p.stats + t * p.row_stride + (size_t)(32 * ni / p.cpg) * p.stats_stride : nullptr;
     }
   }
+  if constexpr (STATS) emit_pairs(st, FULL, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
 }
 
 // ACT: what happens to an input element on its way into LDS: 0 nothing, 1 scale/shift, 2 scale/shift + SiLU
@@ -204,17 +237,17 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
 
   if (tid < TN) s_bias[tid] = (p.bias ? p.bias[co0 + tid] : 0.f) + (p.bias2 ? p.bias2[co0 + tid] : 0.f);
 
-  // ---- weights: the wavefront's fragment column (wave-uniform), and the lane's 16 bytes in tile 0 of a pair of fragments
+  // ---- weights: the wavefront's fragment column (wave-uniform), and the lane's 16 bytes in tile 0 (the even channels) of a pair of fragments
   const int kk_stride = p.cout_blocks * 1024, tap_stride = p.cin_blocks * kk_stride;   // bytes
   const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w), 0, p.w_bytes, 0x00020000);
   const int wcol = (co_w >> 5) * 1024;
-  const int lane_w = (lane >> 5) * kk_stride + ((lane & 12) * 2 + (lane & 3) + (lane & 16) * 2) * 16;
+  const int lane_w = (lane >> 5) * kk_stride + (2 * (lane & 15) + 2 * (lane & 16)) * 16;
   u32x4 bq[D][2];
   f32x4 acc[TH][2 * NI];
 #pragma unroll
   for (int sp = 0; sp < D - 1; ++sp)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) bq[sp][h] = load_fragment(wrsrc, lane_w, wcol + weight_offset<NI>(sp, tap_stride) + 64 * h);
+    for (int h = 0; h < 2; ++h) bq[sp][h] = load_fragment(wrsrc, lane_w, wcol + weight_offset<NI>(sp, tap_stride) + 16 * h);
 
   // ---- staging: a thread owns NV (pixel, channel-octet) vectors of the halo patch; the octet is the same for all.
   // Zero padding without per-element work: a vector outside the image is loaded from pixel 0 (a load under a lane
@@ -278,7 +311,7 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
     };
     auto load2 = [&](u32x4 (&f)[2 * NI], int chunk) {
 #pragma unroll
-      for (int j = 0; j < 2 * NI; ++j) f[j] = load_fragment(wrsrc2, lane_w, wcol + min(chunk, nch2 - 1) * 2 * kk_stride + j / 2 * 1024 + 64 * (j % 2));
+      for (int j = 0; j < 2 * NI; ++j) f[j] = load_fragment(wrsrc2, lane_w, wcol + min(chunk, nch2 - 1) * 2 * kk_stride + j / 2 * 1024 + 16 * (j % 2));
     };
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k) { issue2(x2[k], k); load2(w2[k], k); }
@@ -294,7 +327,7 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
       for (int r = 0; r < TH; ++r) {
         const u32x4 px = *reinterpret_cast<const u32x4*>(ctr + r * ROW);
 #pragma unroll
-        for (int j = 0; j < 2 * NI; ++j) acc[r][j] = Mma<T>::m16(w2[k][j], px, acc[r][j]);
+        for (int j = 0; j < 2 * NI; ++j) acc[r][j] = Mma<T>::m16(px, w2[k][j], acc[r][j]);
       }
       load2(w2[k], c + AHEAD);
     };
@@ -447,20 +480,37 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
     __syncthreads();          // other buffer staged; this one free for chunk c + 2
   }
   // the last one: nothing to activate, and behind its last weights the residual is requested, so that the epilogue does not wait for it
-  u32x4 rv[NI][TH];
+  constexpr int HELD = held_rows(TH, NI, sizeof(TO));
+  uint32_t rv[HELD][4];
+  unsigned at[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) at[i] = lane_offset(ep, lane, tx0, i);
   auto ask = [&](auto m_c) {
-    constexpr int m = decltype(m_c)::value, FROM = (9 * NI - (D - 1)) * TH * 2;
-    if constexpr (m >= FROM && m < FROM + TH) rv[0][m - FROM] = load_residual<T>(ep, lane, ty0 + m - FROM, tx0, co_w);
+    constexpr int m = decltype(m_c)::value, AFTER = (9 * NI - (D - 1)) * TH * 2, FROM = NI == 1 ? AFTER : 18 * NI * TH - 4 * HELD, j = m - FROM;
+    static_assert(FROM >= AFTER && FROM + 4 * HELD <= 18 * NI * TH, "behind the last weights, and all of them");
+    if constexpr (j >= 0 && j < 4 * HELD) rv[j / 4][j % 4] = load_residual<T>(ep, at[j % 4], ty0 + j / 4, tx0, co_w);
   };
   sweep_chunk<T, TH, NI, D, true>(rows_at, wrsrc, wcol + (nchunks - 1) * 2 * kk_stride, 0, tap_stride, lane_w, bq, acc, ask);
 
+  int last = lane;
+  asm volatile("" : "+v"(last));   // (what the epilogue derives from it is not held through the sweeps)
   const float* bias_w = s_bias + wn * NI * 32;
-  if (p.stats) {
-    if (p.res) epilogue<T, TO, TH, NI, true, true, MODE>(acc, rv, bias_w, lane, ty0, tx0, co_w, ep);
-    else epilogue<T, TO, TH, NI, false, true, MODE>(acc, rv, bias_w, lane, ty0, tx0, co_w, ep);
+  auto finish = [&](auto res_c, auto stats_c, auto full_c) __attribute__((always_inline)) {
+    epilogue<T, TO, TH, NI, decltype(res_c)::value, decltype(stats_c)::value, decltype(full_c)::value, MODE>(acc, rv, bias_w, last, ty0, tx0, co_w, ep);
+  };
+  const std::true_type yes{};
+  const std::false_type no{};
+  if (!p.stats) {
+    if (p.res) finish(yes, no, no);
+    else finish(no, no, no);
+  } else if (sizeof(TO) == 2 && ty0 + TH <= p.h && tx0 + 16 <= p.w_out) {   // (fp32 values of all rows at once would be spilled)
+    if constexpr (sizeof(TO) == 2) {
+      if (p.res) finish(yes, yes, yes);
+      else finish(no, yes, yes);
+    }
   } else {
-    if (p.res) epilogue<T, TO, TH, NI, true, false, MODE>(acc, rv, bias_w, lane, ty0, tx0, co_w, ep);
-    else epilogue<T, TO, TH, NI, false, false, MODE>(acc, rv, bias_w, lane, ty0, tx0, co_w, ep);
+    if (p.res) finish(yes, yes, no);
+    else finish(no, yes, no);
   }
 
   if (p.rows_out) hand_over_row<NT>(p, n, wt.y, nt, co0, TN, WM, tid, lane);

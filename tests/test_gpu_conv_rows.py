@@ -1,4 +1,4 @@
-"""3x3 convolution on 16x16x32 MFMAs (tiles of 4 or 8 rows x 16 pixels): every instantiation at ragged tile edges against nine shifted
+"""3x3 convolution on 16x16x32 MFMAs (tiles of 4 or 8 rows x 16 pixels): every tile and activation at ragged edges against nine shifted
 products in 64 bits, without and with residual and moments, at one type's rounding of the result."""
 import pytest
 import torch
@@ -9,46 +9,77 @@ from tests import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 
-# 64 x 128 tiles; 128 x 128 with moments per four rows, short and whole ring of weights; 128 x 128, both rings, and of 256 channels; 128 x 256, one and two chunks
+# 64 x 128 tiles; 128 x 128 with moments per four rows, whole and short ring of weights (also with one chunk of channels); 128 x 128, both rings; of
+# 256 channels, one to three chunks.  Without normalisation, with scale and shift, with SiLU.
+@pytest.mark.parametrize("act", [None, "affine", "silu"])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("n,cin,cout,h,w", [(1, 32, 128, 5, 17), (5, 32, 256, 37, 50), (16, 32, 256, 37, 50), (1, 96, 128, 121, 67),
                                             (1, 32, 128, 127, 530), (1, 32, 256, 257, 259), (1, 64, 256, 182, 367),
-                                            (1, 32, 256, 100, 203), (2, 64, 256, 91, 130)])
-def test_tile_edges(dtype, n, cin, cout, h, w):
+                                            (1, 32, 256, 100, 203), (2, 64, 256, 91, 130), (1, 288, 256, 202, 263)])
+def test_tile_edges(dtype, n, cin, cout, h, w, act):
     g = torch.Generator(device="cuda")
     g.manual_seed(synth.SEED_BASE + 60)
 
     def draw(*shape):
         return torch.randn(shape, generator=g, device="cuda")
-    x, res, bias = draw(n, h, w, cin).to(G.TORCH[dtype]), draw(n, h, w, cout).to(G.TORCH[dtype]), draw(cout)
+    x, res, bias = (draw(n, h, w, cin) * 8).round().clamp(-24, 24).div(8).to(G.TORCH[dtype]), draw(n, h, w, cout).to(G.TORCH[dtype]), draw(cout)
     wt = (draw(cout, cin, 3, 3) / (9 * cin) ** 0.5).bfloat16()
     packed = G.pack(wt.float().cpu().numpy(), dtype)
-    pad = torch.zeros((n, h + 2, w + 2, cin), dtype=torch.float64, device="cuda")
-    pad[:, 1:-1, 1:-1] = x.double()
-    conv = bias.double().expand(n * h * w, cout).clone()
-    for ky in range(3):
-        for kx in range(3):
-            conv += pad[:, ky:ky + h, kx:kx + w].reshape(-1, cin) @ wt[:, :, ky, kx].double().t().contiguous()
-    conv = conv.view(n, h, w, cout)
     groups, ulp = 32, 2.0 ** -8 if dtype == "bf16" else 2.0 ** -11
-    ws = torch.zeros(wmdec.conv_stats_workspace_bytes(G.ENUM[dtype], G.ENUM[dtype], n, h, w, cin, cout, groups), dtype=torch.uint8, device="cuda")
-    mean, rstd = torch.empty(n * groups, device="cuda"), torch.empty(n * groups, device="cuda")
-    for residual, ydtype, stats in ((None, "f32", False), (None, dtype, False), (None, dtype, True), (res, dtype, False), (res, dtype, True)):
+    head, operand = (x, None, None, None, None, 1, False, packed, bias), x.double()
+    if act:   # eighths, means in eighths, scales that are powers of two: the scaled value is exact in either type
+        mean, rstd = (draw(n, groups) * 4).round().clamp(-8, 8) / 8, 2.0 ** draw(n, groups).round().clamp(-2, 2)
+        gamma, beta = 2.0 ** draw(cin).round().clamp(-1, 1), torch.zeros(cin, device="cuda")
+        head = (x, mean.flatten(), rstd.flatten(), gamma, beta, groups, act == "silu", packed, bias)
+        t = (x - mean.repeat_interleave(cin // groups, 1)[:, None, None]).double() * (gamma * rstd.repeat_interleave(cin // groups, 1))[:, None, None].double()
+        operand = (t * torch.sigmoid(t) if act == "silu" else t).to(G.TORCH[dtype]).double()
+
+    def contract(v, weights):
+        pad = torch.zeros((n, h + 2, w + 2, cin), dtype=torch.float64, device="cuda")
+        pad[:, 1:-1, 1:-1] = v
+        out = torch.zeros((n * h * w, cout), dtype=torch.float64, device="cuda")
+        for ky in range(3):
+            for kx in range(3):
+                out += pad[:, ky:ky + h, kx:kx + w].reshape(-1, cin) @ weights[:, :, ky, kx].double().t().contiguous()
+        return out.view(n, h, w, cout)
+    conv = contract(operand, wt) + bias.double()
+    slack = 2 * ulp * contract(operand.abs(), wt.abs()) if act == "silu" else 0.0   # an activated value near a rounding boundary may be the next one
+    mean_out, rstd_out = torch.empty(n * groups, device="cuda"), torch.empty(n * groups, device="cuda")
+    for residual, ydtype, stats in ((None, "f32", False), (res, "f32", True), (None, "f32", True), (None, dtype, False), (None, dtype, True), (res, dtype, False), (res, dtype, True)):
         y, check = G.canaried((n, h, w, cout), G.TORCH[ydtype])
         if stats:
-            wmdec.gn_silu_conv3x3_stats(x, None, None, None, None, 1, False, packed, bias, residual, y, groups, 1e-6, mean, rstd, ws)
+            ws = torch.zeros(wmdec.conv_stats_workspace_bytes(G.ENUM[dtype], G.ENUM[ydtype], n, h, w, cin, cout, groups), dtype=torch.uint8, device="cuda")
+            wmdec.gn_silu_conv3x3_stats(*head, residual, y, groups, 1e-6, mean_out, rstd_out, ws)
         else:
-            wmdec.gn_silu_conv3x3(x, None, None, None, None, 1, False, packed, bias, residual, y)
+            wmdec.gn_silu_conv3x3(*head, residual, y)
         torch.cuda.synchronize()
         check()
         want = conv if residual is None else conv + res.double()
         # operands are exact: fp32 sums of 9 * cin products, and half an ulp of a 16-bit output's own size
-        tol = 2e-5 * want.pow(2).mean().sqrt() + (0.0 if ydtype == "f32" else ulp) * want.abs()
+        tol = 2e-5 * want.pow(2).mean().sqrt() + slack + (0.0 if ydtype == "f32" else ulp) * (want.abs() + slack)
         assert bool(((y.double() - want).abs() <= tol).all()), (residual is not None, ydtype, stats, float(((y.double() - want).abs() - tol).max()))
         if stats:   # of the stored values
             v = y.double().view(n, h * w, groups, cout // groups)
             m, r = v.mean((1, 3)).flatten(), (v.var((1, 3), unbiased=False) + 1e-6).rsqrt().flatten()
-            assert float((mean.double() - m).abs().max()) <= 2e-5 and float((rstd.double() / r - 1).abs().max()) <= 2e-5
+            assert float((mean_out.double() - m).abs().max()) <= 2e-5 and float((rstd_out.double() / r - 1).abs().max()) <= 2e-5
+
+
+# groups of 1 to 32 channels: a lane holds two of them, the others of a group are up to 16 lanes of it
+@pytest.mark.parametrize("groups", [8, 16, 64, 128, 256])
+@pytest.mark.parametrize("n,cin,cout,h,w", [(1, 32, 256, 37, 50), (16, 32, 256, 37, 50), (1, 96, 256, 121, 131), (1, 288, 256, 202, 263)])
+def test_moments_of_groups_of_any_size(groups, n, cin, cout, h, w):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(synth.SEED_BASE + 62)
+    x, bias = torch.randn((n, h, w, cin), generator=g, device="cuda").half(), torch.randn(cout, generator=g, device="cuda") * 3
+    packed = G.pack((torch.randn((cout, cin, 3, 3), generator=g, device="cuda") / (9 * cin) ** 0.5).bfloat16().float().cpu().numpy(), "f16")
+    y = torch.empty((n, h, w, cout), dtype=torch.float16, device="cuda")
+    ws = torch.full((wmdec.conv_stats_workspace_bytes(wmdec.F16, wmdec.F16, n, h, w, cin, cout, groups),), 0xA5, dtype=torch.uint8, device="cuda")
+    mean, rstd = torch.empty(n * groups, device="cuda"), torch.empty(n * groups, device="cuda")
+    wmdec.gn_silu_conv3x3_stats(x, None, None, None, None, 1, False, packed, bias, None, y, groups, 1e-6, mean, rstd, ws)
+    v = y.double().view(n, h * w, groups, cout // groups)
+    m, sd = v.mean((1, 3)).flatten(), v.var((1, 3), unbiased=False).flatten().sqrt()
+    # fp32 sums shifted by a value of the block: a few 2^-24 of the values, which are up to some 5 standard deviations
+    assert float(((mean.double() - m) / sd).abs().max()) <= 4e-6 and float((rstd.double() * (sd ** 2 + 1e-6).sqrt() - 1).abs().max()) <= 4e-6
 
 
 # 91 tiles of 8 x 16 pixels a sample and 256 channels: 128-channel tiles for one or three samples, 256-channel tiles for two or five
