@@ -9,8 +9,8 @@ from tests import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 
-# 64 x 128 tiles; 128 x 128 with moments per four rows, whole and short ring of weights (also with one chunk of channels); 128 x 128, both rings; of
-# 256 channels, one to three chunks.  Without normalisation, with scale and shift, with SiLU.
+# 64 x 128 tiles; 128 x 128 with moments per four rows, whole and short ring of weights (also with one chunk of channels); 128 x 128, whole ring and short;
+# 128 x 256, one to nine chunks.  Without normalisation, with scale and shift, with SiLU.
 @pytest.mark.parametrize("act", [None, "affine", "silu"])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("n,cin,cout,h,w", [(1, 32, 128, 5, 17), (5, 32, 256, 37, 50), (16, 32, 256, 37, 50), (1, 96, 128, 121, 67),

@@ -250,7 +250,7 @@ def test_gn_silu_conv3x3(dtype, ydtype, n, cin, cout, h, w, norm, silu, bias, re
 # blocks of four in a larger batch, 64 channels a wavefront; one, two and three chunks of input channels.
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("n,cin,cout,h,w", [(1, 64, 128, 101, 115), (1, 32, 128, 97, 129), (1, 96, 128, 27, 45), (13, 96, 128, 27, 45),
-                                            (1, 32, 128, 1, 1), (1, 32, 128, 253, 262), (1, 96, 256, 253, 262)])
+                                            (1, 32, 128, 1, 1), (1, 32, 128, 253, 262), (1, 96, 256, 253, 262), (1, 96, 256, 100, 203)])
 def test_conv_of_single_taps_is_an_exact_displacement(dtype, n, cin, cout, h, w):
     x = torch.from_numpy(rng(21).standard_normal((n, h, w, cin)).astype(np.float32)).to(G.TORCH[dtype])
     wt = np.zeros((cout, cin, 3, 3), np.float32)
@@ -270,7 +270,7 @@ def test_conv_of_single_taps_is_an_exact_displacement(dtype, n, cin, cout, h, w)
 # most 2^-23, truncation included, of partial sums of rms 1, independently of each other.  Sums that start from the bias round
 # every step by ulp / sqrt(12) of the result: over five times as much at the least count of steps here with a tile of that kind (16).
 @pytest.mark.parametrize("k,n,cin,cout,h,w", [(3, 1, 64, 64, 130, 131), (3, 1, 64, 128, 97, 99), (3, 1, 32, 256, 256, 257), (3, 1, 64, 512, 64, 61),
-                                              (3, 2, 64, 512, 64, 61), (3, 1, 256, 512, 17, 23), (3, 16, 64, 128, 40, 41),
+                                              (3, 2, 64, 512, 64, 61), (3, 1, 256, 512, 17, 23), (3, 16, 64, 128, 40, 41), (3, 1, 32, 256, 100, 203),
                                               (1, 1, 512, 64, 90, 91), (1, 1, 512, 128, 64, 65), (1, 1, 256, 128, 363, 363), (1, 1, 288, 192, 64, 65)])
 def test_conv_adds_a_large_bias_to_finished_sums(k, n, cin, cout, h, w):
     r = rng(22)
