@@ -276,6 +276,22 @@ def test_upsampling_convolutions_with_groups_of_one_and_two_channels():
     assert err <= G.TOL["f16"], err
 
 
+def test_upsampling_convolutions_with_groups_of_32_channels():
+    """16 groups: a group of the upsampling convolutions at 512 channels spans both wavefronts of a pair, which leave a triple each: two a tile, four
+    where the contraction is split (the first of the two, 48 workgroups of 64 channels; the second has 192)."""
+    chans = (512, 512, 32)
+    cfg = small_cfg(wmdec.F16)
+    cfg.latent_h, cfg.latent_w, cfg.num_levels, cfg.groups = 14, 40, 3, 16
+    cfg.level_channels[1], cfg.level_channels[2] = 512, 32
+    dec = wmdec.Decoder(cfg)
+    assert [k for k, _, _ in dec.step_info() if k.startswith("conv_up_kernel<")] == ["conv_up_kernel<wmdec::f16_t, 2, %d, false>" % n for n in (1, 2)]
+    dec.close()
+    weights = synth.draw_params(synth.decoder_weight_spec(level_channels=chans, resblocks_per_level=2), synth.weight_seed(18), random_affine=True)
+    z = synth.latent_sequence(workload=18, frames=2, h=14, w=40)
+    err = ref.rel_err(run_decoder(cfg, weights, z), ref.decoder(z, weights, level_channels=chans, resblocks_per_level=2, groups=16, eps=1e-6))
+    assert err <= G.TOL["f16"], err
+
+
 def test_rows_handed_over_by_256_channel_tiles():
     """600 tiles of 256 channels: the 32 -> 256 layer at 240x320 merges its own rows on them; without the hand-over it runs on 128-channel tiles."""
     chans = (512, 32, 256)
