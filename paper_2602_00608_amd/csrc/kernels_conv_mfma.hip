@@ -189,15 +189,9 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
 }
 
 // Ring length of the weight-fragment prefetch: it must divide the k-steps of a chunk so that the ring
-// position is the same at every chunk start.
-// It is as long as the register budget of the tile allows (`room`: accumulator tiles per wavefront): the fragments
-// come from the L2, whose latency is several k-steps.  The 256-pixel tiles, at the 256-register limit, take the
-// short ring and spend the registers on the activation-table prefetch instead (measured: +1.5 to 2 %).
-constexpr int prefetch_ring(int steps, int room) {
-  if (room > 4 && steps % 3 == 0) return 3;
-  if (steps % 6 == 0) return 6;
-  return steps % 3 == 0 ? 3 : (steps % 4 == 0 ? 4 : 2);
-}
+// position is the same at every chunk start (18 with 3x3 taps; 4 or 2 with one).  The fragments come from the L2, whose latency is
+// several k-steps.
+constexpr int prefetch_ring(int steps) { return steps % 6 == 0 ? 6 : steps % 4 == 0 ? 4 : 2; }
 
 struct NoFlush { __device__ void operator()(int) const {} };
 
@@ -284,7 +278,7 @@ constexpr int wave_m_tiles(int th, int tw, int wm) { return th * tw / 32 / wm; }
 // 2x2-wavefront 128x128 shape, which is only picked for layers with at most two workgroups per compute unit and
 // uses the registers for a longer prefetch instead.
 constexpr int resident_workgroups(int acc_tiles, int wm, int wn) {
-  return wm * wn == 8 ? 1 : (acc_tiles <= 4 && !(wm == 2 && wn == 2) ? 3 : 2);
+  return acc_tiles <= 4 && !(wm == 2 && wn == 2) ? 3 : 2;
 }
 
 // LDS layout of a staged tile (elements of the 16-bit type): pixel (hy, hx) of the halo patch sits at hy * ROW + hx * PS.
@@ -368,7 +362,7 @@ void conv_mfma_kernel(MfmaParams p) {
     a_off[mi] = ty * ROW + tx * PS + 8 * lk;
   }
   constexpr int KK = KC / 16;
-  constexpr int D = RING > 0 ? RING : prefetch_ring(KS * KS * KK, MI * NI);   // weight fragments are fetched D-1 k-steps ahead
+  constexpr int D = RING > 0 ? RING : prefetch_ring(KS * KS * KK);   // weight fragments are fetched D-1 k-steps ahead
   static_assert((KS * KS * KK) % D == 0, "the ring position must be the same at every chunk start");
   const int tap_stride = p.cin_blocks * p.cout_blocks * 1024, kk_stride = p.cout_blocks * 1024;   // bytes
   // byte offset of this wavefront's fragment column (wave-uniform; the lane's 16 bytes are added by the load)
@@ -479,10 +473,9 @@ void conv_mfma_kernel(MfmaParams p) {
   };
   const int nchunks = p.cin / KC;
   // vector-ALU instructions of the activation per MFMA of an active k-step (8 per element with SiLU, 3 without),
-  // one less than the average so that the tail of a word does not delay the next k-step; the 256-pixel tiles keep
-  // the order as written (spreading measured 0 to -4 % there, +1 to +2 % on the small tiles)
+  // one less than the average so that the tail of a word does not delay the next k-step (against the order as written: 1 to 2 %)
   constexpr int SPREAD_AVG = (NV * 8 * (ACT == 2 ? 8 : 3) + (SLOTS - SLOTS / 3) * NI - 1) / ((SLOTS - SLOTS / 3) * NI);
-  constexpr int SPREAD = (ACT == 0 || MI * NI > 4) ? -1 : (SPREAD_AVG > 1 ? SPREAD_AVG - 1 : 1);
+  constexpr int SPREAD = ACT == 0 ? -1 : (SPREAD_AVG > 1 ? SPREAD_AVG - 1 : 1);
   f32x4 abv[2];   // table entries of the part being activated and of the next one (sliced activation)
 
   float zero = 0.f;
