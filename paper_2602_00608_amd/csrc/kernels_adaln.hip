@@ -4,9 +4,9 @@
 //
 // With a handful of conditioning vectors per call (one per frame) the product is a matrix-vector product: every weight
 // is used `batch` times, far below the ridge point, so the bound is the single read of the weights from HBM and the
-// matrix cores have nothing to add.  A wavefront owns eight weight rows at a time: a lane reads 16 contiguous bytes of
+// matrix cores have nothing to add.  A wavefront owns four weight rows: a lane reads 16 contiguous bytes of
 // each row per step (a wavefront's load is 1 KiB of one row), the activated conditioning vectors sit in LDS as fp32
-// and are read once per step for all eight rows, partial sums stay in registers and are reduced over the 64 lanes at
+// and are read once per step for all four rows, partial sums stay in registers and are reduced over the 64 lanes at
 // the end with a fixed butterfly.
 #include "common.hpp"
 

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
     out[3] = (a + next_column(b)) + (c1 + next_column(d1));
   };
   // Moments of the stored values: plain sums of a quad (FINE: of a channel), shifted by the mean of the first phase over every other row
-  // (over a whole group where one spans quads of this wavefront): a seventh of the values or more, so that no single
+  // (over a whole group where one spans quads of this wavefront): an eighth of the values or more, so that no single
   // one of them, however far off, can cancel the sums
   constexpr int NS = FINE ? 4 : 1, CH = 4 / NS;
   float sh[NS], ss[NS], sq[NS];
@@ -296,8 +296,8 @@ constexpr int kH = 2, kWN = 2, kTN = 32 * kWN;
 // ... or 32 channels, with the contraction split in two: one round of half as many channels then leaves compute units idle, and
 // a lone workgroup is bound by the weights that its wavefronts take through the vector L1 (64 B/clk), 1.2 MB at 512
 // channels, of which half the channels need half.  A function of the sample's shape: the sums do not depend on the batch.
-// 512 channels, us, measured in this kernel's earlier form on 32x32x16 MFMAs: 17x23 20.7 -> 17.4, 32x32 22.0 -> 19.3.  Past 128 workgroups the halves
-// would share a compute unit again.
+// us, whole / split, by the number of whole workgroups: 512 channels 48 16.2 / 11.9, 120 16.4 / 12.6, 128 16.9 / 13.6, 160 17.3 / 19.1, 240 20.7 / 22.9;
+// 256 channels 60 10.7 / 9.0, 120 11.1 / 9.8, 144 11.4 / 12.9; 128 channels 96 8.3 / 7.8.  Past 128 workgroups the halves share a compute unit again.
 bool split_channels(const ConvArgs& a) {
   const long wgs = (long)((a.h / 2 + TH - 1) / TH) * ((a.w / 2 + TW - 1) / TW) * (a.cout / kTN);
   return a.cin % (2 * KC) == 0 && wgs <= 128;
