@@ -88,10 +88,12 @@ __device__ __forceinline__ void sweep_chunk(const T* buf, __amdgpu_buffer_rsrc_t
   });
 }
 
-// Rows of the residual that are on their way at a time.  The last sweep requests the first ones, a pixel of the lane behind each of
-// its last MFMAs, the epilogue the one that takes a row's place when that is used up.  All rows of a patch would be spilled where the accumulators
-// are 128 registers, or the values to store as many as the accumulators.
-constexpr int held_rows(int th, int ni, size_t out_size) { return ni == 1 && out_size == 2 ? th : 4; }
+// Rows of the residual that the last sweep requests, a pixel of the lane behind each of its last MFMAs; the epilogue requests the others in
+// front of its first store.  (More of them in the sweep would be spilled where the accumulators are 128 registers, or the values to store as many as the
+// accumulators.  Requested between the stores, each as the one four rows before it is used up, a row waits for the stores in front of it:
+// what the residual costs 256-channel tiles, us, that way / this way: 256 -> 256 channels 150x150 4.9 / 2.1 beside 26 to 29, 480x480 34 / 14 beside 202 to 233, 32 -> 256 at
+// 400x400 16 / 11 beside 31, 512 -> 512 at 106x82 3.4 / 1.6 beside 48 to 50.)
+constexpr int asked_rows(int th, int ni, size_t out_size) { return ni == 1 && out_size == 2 ? th : 4; }
 
 struct EpilogueParams {
   __amdgpu_buffer_rsrc_t res, y;           // the sample's residual and output, with its size: accesses outside are dropped
@@ -113,19 +115,26 @@ template <typename T> __device__ __forceinline__ uint32_t load_residual(const Ep
 // Epilogue of one wavefront: bias, residual, one rounding, store.  (Through LDS
 // patches, as in kernels_conv_mfma.hip, the same lanes write 64 values one by one and wait for them.)  The bias is added to
 // the finished sums: accumulators that start from it round every partial sum at its exponent.
-// rv: the residual of the first rows, on their way.
+// rv: the residual; that of the first rows is on its way.
 // Moments, of the values as stored: one triple per group for all R rows, or (kRows4) for every four of them.  FULL: no pixel of the patch lies
 // outside the image (the moments need no masks, and the rows are scheduled as one).
 template <typename T, typename TO, int R, int NI, bool RES, bool STATS, bool FULL, int MODE>
-__device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], uint32_t (&rv)[held_rows(R, NI, sizeof(TO))][4], const float* s_bias, int lane, int ty0, int tx0, int co_w,
+__device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], uint32_t (&rv)[NI * R][4], const float* s_bias, int lane, int ty0, int tx0, int co_w,
                                          const EpilogueParams& p) {
-  constexpr int EMIT = MODE == kRows4 ? 4 : R, HELD = held_rows(R, NI, sizeof(TO));   // rows of a triple
+  constexpr int EMIT = MODE == kRows4 ? 4 : R;   // rows of a triple
   static_assert(R % EMIT == 0, "whole triples");
   const bool columns = tx0 + 16 <= p.w;                           // all columns lie inside the image,
   const int cols = min(max(p.w - tx0 - 4 * (lane >> 4), 0), 4);   // and of the lane's four so many
   unsigned at[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) at[i] = lane_offset(p, lane, tx0, i);
+  if constexpr (RES) {
+#pragma unroll
+    for (int k = asked_rows(R, NI, sizeof(TO)); k < NI * R; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rv[k][i] = load_residual<T>(p, at[i], ty0 + k % R, tx0, co_w + 32 * (k / R));
+    __builtin_amdgcn_sched_barrier(0);
+  }
   LaneMoments<2> st[NI * (R / EMIT)];
   Moments* dst[NI * (R / EMIT)];
 #pragma unroll
@@ -136,23 +145,14 @@ __device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], uint32_t
       float n = 0.f, shift[2] = {0.f, 0.f}, s[2][4] = {}, q[2][4] = {};
 #pragma unroll
       for (int r = t * EMIT; r < (t + 1) * EMIT; ++r) {
-        const int held = (ni * R + r) % HELD, ahead = ni * R + r + HELD;   // place of this row's residual, and the row that takes it next
-        auto request = [&]() {
-          if constexpr (RES) {
-            if (ahead < NI * R) {
-#pragma unroll
-              for (int i = 0; i < 4; ++i) rv[held][i] = load_residual<T>(p, at[i], ty0 + ahead % R, tx0, co_w + 32 * (ahead / R));
-            }
-          }
-        };
-        if (!FULL && ty0 + r >= p.h) { request(); continue; }
+        if (!FULL && ty0 + r >= p.h) continue;
         const int base = vector_base(ty0 + r, tx0, p.h, p.w, p.cout, co_w + 32 * ni) * (int)sizeof(TO);
         float v[4][2];   // as stored
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           v[i][0] = acc[r][2 * ni][i] + bias.x;
           v[i][1] = acc[r][2 * ni + 1][i] + bias.y;
-          if constexpr (RES) { v[i][0] += unpack_lo<T>(rv[held][i]); v[i][1] += unpack_hi<T>(rv[held][i]); }
+          if constexpr (RES) { v[i][0] += unpack_lo<T>(rv[ni * R + r][i]); v[i][1] += unpack_hi<T>(rv[ni * R + r][i]); }
           if constexpr (sizeof(TO) == 4) {
             f32x2 pair{v[i][0], v[i][1]};
             asm volatile("" : "+v"(pair));   // (in this order: the compiler would form all pairs first)
@@ -165,7 +165,6 @@ __device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], uint32_t
             v[i][0] = unpack_lo<T>(word); v[i][1] = unpack_hi<T>(word);
           }
         }
-        request();
         if constexpr (STATS) {
           n += FULL ? 4.f : (float)cols;
 #pragma unroll
@@ -228,7 +227,7 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
   const int tid = threadIdx.x, lane = tid & 63;
   const int wn = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform: keeps the per-wave addresses scalar
 
-  if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, WN, wn, lane); return; }
+  if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, WN, wn, lane); return; }   // (carries_weights: spilled registers of the fullest form)
 
   const WorkTile wt = workgroup_tile(p);
   const int nt = wt.nt, n = wt.n, tile = wt.tile;
@@ -480,15 +479,15 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
     __syncthreads();          // other buffer staged; this one free for chunk c + 2
   }
   // the last one: nothing to activate, and behind its last weights the residual is requested, so that the epilogue does not wait for it
-  constexpr int HELD = held_rows(TH, NI, sizeof(TO));
-  uint32_t rv[HELD][4];
+  constexpr int ASKED = asked_rows(TH, NI, sizeof(TO));
+  uint32_t rv[NI * TH][4];
   unsigned at[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) at[i] = lane_offset(ep, lane, tx0, i);
   auto ask = [&](auto m_c) {
-    constexpr int m = decltype(m_c)::value, AFTER = (9 * NI - (D - 1)) * TH * 2, FROM = NI == 1 ? AFTER : 18 * NI * TH - 4 * HELD, j = m - FROM;
-    static_assert(FROM >= AFTER && FROM + 4 * HELD <= 18 * NI * TH, "behind the last weights, and all of them");
-    if constexpr (j >= 0 && j < 4 * HELD) rv[j / 4][j % 4] = load_residual<T>(ep, at[j % 4], ty0 + j / 4, tx0, co_w);
+    constexpr int m = decltype(m_c)::value, AFTER = (9 * NI - (D - 1)) * TH * 2, FROM = NI == 1 ? AFTER : 18 * NI * TH - 4 * ASKED, j = m - FROM;
+    static_assert(FROM >= AFTER && FROM + 4 * ASKED <= 18 * NI * TH, "behind the last weights, and all of them");
+    if constexpr (j >= 0 && j < 4 * ASKED) rv[j / 4][j % 4] = load_residual<T>(ep, at[j % 4], ty0 + j / 4, tx0, co_w);
   };
   sweep_chunk<T, TH, NI, D, true>(rows_at, wrsrc, wcol + (nchunks - 1) * 2 * kk_stride, 0, tap_stride, lane_w, bq, acc, ask);
 

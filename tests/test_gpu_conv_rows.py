@@ -82,11 +82,12 @@ def test_moments_of_groups_of_any_size(groups, n, cin, cout, h, w):
     assert float(((mean.double() - m) / sd).abs().max()) <= 4e-6 and float((rstd.double() * (sd ** 2 + 1e-6).sqrt() - 1).abs().max()) <= 4e-6
 
 
-# 91 tiles of 8 x 16 pixels a sample and 256 channels: 128-channel tiles for one or three samples, 256-channel tiles for two or five
+# 91 tiles of 8 x 16 pixels a sample and 256 channels: 128-channel tiles for one or three samples, 256-channel tiles for two or five (beside a residual
+# from 128 input channels on)
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("cin2", [0, 96])
-def test_a_sample_keeps_its_bits_where_the_batch_chooses_the_width(dtype, cin2):
-    n, h, w, cin, cout, groups = 5, 100, 100, 64, 256, 32
+@pytest.mark.parametrize("cin,cin2", [(64, 0), (64, 96), (128, 0)])
+def test_a_sample_keeps_its_bits_where_the_batch_chooses_the_width(dtype, cin, cin2):
+    n, h, w, cout, groups = 5, 100, 100, 256, 32
     g = torch.Generator(device="cuda")
     g.manual_seed(synth.SEED_BASE + 61)
 

@@ -23,8 +23,8 @@ def tiles(tmp_path_factory):
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-std=c++17", "-I" + os.path.join(pkg, "csrc"), "-I" + os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "tile_names.cpp"),
                     "-L" + pkg, "-lwmdec", "-Wl,-rpath," + pkg, "-o", exe], check=True)
 
-    def ask(shapes):   # (ksize, n, cin, cout, h, w, fp32 output) -> tile, or the kernel's name where it is another one
-        out = subprocess.run([exe] + [",".join(str(int(v)) for v in s) for s in shapes], check=True, capture_output=True, text=True).stdout.split("\n")[:-1]
+    def ask(shapes, residual=False):   # (ksize, n, cin, cout, h, w, fp32 output) -> tile, or the kernel's name where it is another one
+        out = subprocess.run([exe] + [",".join(str(int(v)) for v in s + (residual,)) for s in shapes], check=True, capture_output=True, text=True).stdout.split("\n")[:-1]
         names = []
         for label in out:
             p = label[label.find("<") + 1:-1].split(", ")
@@ -44,10 +44,12 @@ def test_edges_of_every_tile(tiles):
     want = [NARROW4, ROWS4_RING, ROWS4, RING, NARROW, NARROW, NARROW, WIDE, WIDE, WIDE]
     for f32 in (False, True):
         assert tiles([(3,) + c + (f32,) for c in cases]) == want
+        assert tiles([(3,) + c + (f32,) for c in cases], residual=True) == want[:7] + [RING, RING, WIDE]   # (few channels: 128 beside a residual)
 
 
 def test_widths_that_the_batch_chooses(tiles):
     assert tiles([(3, n, 64, 256, 100, 100, False) for n in (1, 2, 3, 5)]) == [RING, WIDE, NARROW, WIDE]
+    assert tiles([(3, n, 128, 256, 100, 100, False) for n in (1, 2, 3, 5)], residual=True) == [RING, WIDE, NARROW, WIDE]
 
 
 def test_exact_displacements(tiles):
