@@ -60,6 +60,14 @@ __device__ __forceinline__ WorkTile workgroup_tile(const MfmaParams& p) {
   return t;
 }
 
+// Whether the workgroup is one of those behind the launch's own that only bring weights (see warm_weights).  Its tile is worked out in front of the
+// question, so that the parameters of both are loaded in one round trip, and the answer's code belongs at the end of the kernel (__builtin_expect):
+// between a kernel's first instructions and the rest it was 0.2 of 9.3 us of a 1x1 layer, 512 -> 512 channels two samples of 26x55.
+__device__ __forceinline__ bool carries_weights(const MfmaParams& p, const WorkTile& t) {
+  asm volatile("" :: "s"(t.nt), "s"(t.n), "s"(t.y), "s"(t.x));
+  return p.next.w && (int)blockIdx.x >= p.total;
+}
+
 template <typename T> __device__ __forceinline__ void unpack8(const u32x4& v, float* f) {
   f[0] = unpack_lo<T>(v.x); f[1] = unpack_hi<T>(v.x); f[2] = unpack_lo<T>(v.y); f[3] = unpack_hi<T>(v.y);
   f[4] = unpack_lo<T>(v.z); f[5] = unpack_hi<T>(v.z); f[6] = unpack_lo<T>(v.w); f[7] = unpack_hi<T>(v.w);

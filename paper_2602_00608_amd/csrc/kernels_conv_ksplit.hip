@@ -81,9 +81,8 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
   const int wn = wave % WN, wk = wave / WN;
   const int lm = lane & 31, lk = lane >> 5;
 
-  if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, NW, wave, lane); return; }
-
   const WorkTile wt = workgroup_tile(p);
+  if (__builtin_expect(carries_weights(p, wt), 0)) { warm_weights(p.next, p.total, NW, wave, lane); return; }
   const int nt = wt.nt, n = wt.n;
   const int ty0 = wt.y * TH, tx0 = wt.x * TW;
   const int co0 = nt * TN;

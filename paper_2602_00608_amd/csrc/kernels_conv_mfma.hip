@@ -331,9 +331,8 @@ void conv_mfma_kernel(MfmaParams p) {
   const int wm = wave / WN, wn = wave % WN;
   const int lm = lane & 31, lk = lane >> 5;
 
-  if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, WM * WN, wave, lane); return; }
-
   const WorkTile wt = workgroup_tile(p);
+  if (__builtin_expect(carries_weights(p, wt), 0)) { warm_weights(p.next, p.total, WM * WN, wave, lane); return; }
   const int nt = wt.nt, n = wt.n, tile = wt.tile;
   const int ty0 = wt.y * TH, tx0 = wt.x * TW;
   const int co0 = nt * TN;

@@ -59,8 +59,8 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
   const int tid = threadIdx.x - wk * NTK;   // within the group
   unsigned char* smem = smem_all + wk * 2 * BUFB;
   const int px = lane & 15, oct = lane >> 4;
-  if (p.next.w && (int)blockIdx.x >= p.total) { warm_weights(p.next, p.total, 4, wave, lane); return; }
   const WorkTile wt = workgroup_tile(p);
+  if (__builtin_expect(carries_weights(p, wt), 0)) { warm_weights(p.next, p.total, 4, wave, lane); return; }
   const int nt = wt.nt, n = wt.n, tile = wt.tile;
   const int ty0 = wt.y * TH, tx0 = wt.x * TW;
   const int h_in = p.h >> 1, w_in = p.w_out >> 1;
