@@ -747,9 +747,9 @@ bool four_row_slots(const ConvArgs& a) {
 // 510 62.9 / 57.7, 520 70.8 / 75.8, 640 76.0 / 77.3, 700 86.4 / 80.5, 800 99.1 / 99.7, 900 111.8 / 102.6, 1100 129.2 / 126.5; 512 -> 512: 120
 // 32.9 / 48.6, 220 56.6 / 52.9, 300 79.8 / 88.5, 480 113 / 102, 1440 320 / 290.  Both add a sum's products in the same order and leave the same
 // moments per 8x16 block, so the batch may decide.  With a residual the epilogue of 256 channels waits for more of it: 256 channels lose where
-// there are few products beside it (400x400, 128 / 256 channels: 32 -> 256 36.5 / 42.7, 128 -> 256 88.3 / 86.5; 256x256 16.8 / 18.5, 39.6 / 38.9).  Where the rows' moments are merged by the launch itself, its ticket counters are sized for one
-// sample's choice by its pixels alone (fits_wide) and the launch keeps to it: never more channel tiles than that.  (Between 513 and 640 tiles that is the
-// slower of the two, by 4 to 9 %.)
+// there are few products beside it (400x400, 128 / 256 channels: 32 -> 256 36.5 / 42.7, 128 -> 256 88.3 / 86.5; 256x256 16.8 / 18.5, 39.6 / 38.9).
+// Where the rows' moments are merged by the launch itself, its ticket counters are sized for one sample's choice by its pixels alone (fits_wide)
+// and the launch keeps to it: never more channel tiles than that.  (Between 513 and 640 tiles that is the slower of the two, by 4 to 9 %.)
 bool fits_wide(const ConvArgs& a) { return a.cout % 256 == 0 && (((long)a.h * a.w + 127) / 128) * (a.cout / 256) >= 2 * 256; }
 bool wide_channels(const ConvArgs& a) {
   if (a.cout % 256 != 0) return false;
