@@ -60,11 +60,12 @@ __device__ __forceinline__ WorkTile workgroup_tile(const MfmaParams& p) {
   return t;
 }
 
-// Whether the workgroup is one of those behind the launch's own that only bring weights (see warm_weights).  Its tile is worked out in front of the
-// question, so that the parameters of both are loaded in one round trip, and the answer's code belongs at the end of the kernel (__builtin_expect):
-// between a kernel's first instructions and the rest it was 0.2 of 9.3 us of a 1x1 layer, 512 -> 512 channels two samples of 26x55.
+// Whether the workgroup is one of those behind the launch's own that only bring weights (see warm_weights).  Its tile and the parameters of the first
+// loads are asked for in front of the question, so that all of them arrive in one round trip, and the answer's code belongs at the end of the
+// kernel (__builtin_expect).  1x1 layers, us, without such workgroups / with the question first / this:
+// 512 -> 512 at 60x90 9.37 / 9.44 / 8.86, 512 -> 64 at 58x35 10.98 / 11.20 / 10.97, 32 -> 512 at 10x16 4.45 / 4.67 / 4.50.
 __device__ __forceinline__ bool carries_weights(const MfmaParams& p, const WorkTile& t) {
-  asm volatile("" :: "s"(t.nt), "s"(t.n), "s"(t.y), "s"(t.x));
+  asm volatile("" :: "s"(t.nt), "s"(t.n), "s"(t.y), "s"(t.x), "s"(p.x), "s"(p.w), "s"(p.bias), "s"(p.w_bytes), "s"(p.cin_blocks), "s"(p.cout_blocks), "s"(p.cin));
   return p.next.w && (int)blockIdx.x >= p.total;
 }
 
