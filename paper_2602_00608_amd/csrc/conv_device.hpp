@@ -35,6 +35,7 @@ struct MfmaParams {
   int cin2, w2_bytes;
   NextWeights next;              // next.w non-null: workgroups from `total` on only bring these weights into the L2s
   unsigned inv_tiles_n, inv_tiles, inv_tiles_x;   // see div_rem: of tiles_x * tiles_y * n, tiles_x * tiles_y, tiles_x
+  unsigned cpg_in, inv_cpg_in;                    // channels of a group of x, their reciprocal
 };
 
 // a / d and its remainder, inv = reciprocal(d): the product's high half is the quotient or one less.  (The compiler's division is some
@@ -46,12 +47,21 @@ __device__ __forceinline__ int div_rem(unsigned a, unsigned d, unsigned inv, int
   rem = (int)r;
   return (int)q;
 }
+__device__ __forceinline__ int quotient_of(unsigned a, unsigned d, unsigned inv) { int rem; return div_rem(a, d, inv, rem); }
+// Brings the arguments of the kernel (BYTES of them) into the scalar cache in one round trip.  The compiler loads them where they are first
+// needed, and every 64 bytes that were not asked for before are a trip of their own to memory, 500 cycles each in front of everything else: a workgroup
+// of 512 channels at 60x90 had its tile after 2530 cycles, now 1100.
+template <int BYTES> __device__ __forceinline__ void fetch_arguments() {
+  static_assert(BYTES > 4 * 64 && BYTES <= 5 * 64, "five lines, wherever the first begins");
+  const auto* at = (const uint32_t __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" :: "s"(at[0]), "s"(at[16]), "s"(at[32]), "s"(at[48]), "s"(at[64]), "s"(at[BYTES / 4 - 1]));
+}
 // workgroup id -> (channel tile, sample, spatial tile, its row and column); the ids of one XCD (id % 8) cover neighbouring tiles of
 // one channel range, so that its L2 fetches an eighth of the weights
 struct WorkTile { int nt, n, tile, y, x; };
 __device__ __forceinline__ WorkTile workgroup_tile(const MfmaParams& p) {
-  const int i = blockIdx.x, per = p.total / 8, rem = p.total % 8;
-  const int x = i % 8, j = i / 8, tiles = p.tiles_x * p.tiles_y;
+  const unsigned i = blockIdx.x, per = (unsigned)p.total / 8, rem = (unsigned)p.total % 8;
+  const unsigned x = i % 8, j = i / 8, tiles = p.tiles_x * p.tiles_y;
   WorkTile t;
   int in_nt;
   t.nt = div_rem(x * per + (x < rem ? x : rem) + j, tiles * p.n, p.inv_tiles_n, in_nt);
@@ -60,14 +70,9 @@ __device__ __forceinline__ WorkTile workgroup_tile(const MfmaParams& p) {
   return t;
 }
 
-// Whether the workgroup is one of those behind the launch's own that only bring weights (see warm_weights).  Its tile and the parameters of the first
-// loads are asked for in front of the question, so that all of them arrive in one round trip, and the answer's code belongs at the end of the
-// kernel (__builtin_expect).  1x1 layers, us, without such workgroups / with the question first / this:
-// 512 -> 512 at 60x90 9.37 / 9.44 / 8.86, 512 -> 64 at 58x35 10.98 / 11.20 / 10.97, 32 -> 512 at 10x16 4.45 / 4.67 / 4.50.
-__device__ __forceinline__ bool carries_weights(const MfmaParams& p, const WorkTile& t) {
-  asm volatile("" :: "s"(t.nt), "s"(t.n), "s"(t.y), "s"(t.x), "s"(p.x), "s"(p.w), "s"(p.bias), "s"(p.w_bytes), "s"(p.cin_blocks), "s"(p.cout_blocks), "s"(p.cin));
-  return p.next.w && (int)blockIdx.x >= p.total;
-}
+// Whether the workgroup is one of those behind the launch's own that only bring weights (see warm_weights).  The answer's code belongs at the end of the
+// kernel (__builtin_expect): 1x1 layers of few tiles lost 0.1 to 0.2 us of 4.5 to 11 otherwise.
+__device__ __forceinline__ bool carries_weights(const MfmaParams& p) { return p.next.w && (int)blockIdx.x >= p.total; }
 
 template <typename T> __device__ __forceinline__ void unpack8(const u32x4& v, float* f) {
   f[0] = unpack_lo<T>(v.x); f[1] = unpack_hi<T>(v.x); f[2] = unpack_lo<T>(v.y); f[3] = unpack_hi<T>(v.y);
@@ -159,11 +164,22 @@ template <typename T, int ACT, bool PIN = false> __device__ __forceinline__ uint
   return wv;
 }
 
+// 1 / sqrt(m2 / n + eps) to three quarters of an ulp, without the compiler's division and square root (which round twice, and are some
+// fifty dependent instructions a launch waits for) unless the variance leaves the range where the steps below are exact enough.
+__device__ __forceinline__ float inverse_deviation(float m2, float n, float eps) {
+  const float v = quotient(m2, n, __builtin_amdgcn_rcpf(n)) + eps;
+  float r = __builtin_amdgcn_rsqf(v);
+  r = fmaf(0.5f * r, fmaf(-(v * r), r, 1.0f), r);
+  if (!(v > 1e-30f && v < 1e30f)) r = 1.0f / sqrtf(m2 / n + eps);   // (zero, infinite, NaN)
+  return r;
+}
+
 // (mean, rstd) of G groups from the `count` triples of their rows, each merged by LANES consecutive lanes (all of them active), K
 // loads in flight per lane and group: the mean first, then the differences to it and their squares, from the same registers.  (A chain
 // of pairwise merges has a reciprocal each and stood in front of every layer's first chunk; one pass of sums about the
 // first triple's mean cancels where that triple is an outlier: 1e-5 of the variance at 100 standard deviations.)  Triples
 // past K * LANES are summed about the mean of those, at least half of the row, which costs a factor of two at most.
+constexpr int kMaxTriples = 128;   // of a group that a prologue merges
 template <int LANES, int K, int G>
 __device__ __forceinline__ void merge_rows(const Moments* const (&row)[G], int count, int sub, float eps, float2 (&out)[G]) {
   float first[G];
@@ -195,7 +211,7 @@ __device__ __forceinline__ void merge_rows(const Moments* const (&row)[G], int c
     const float mean = first[g] + lanes_sum<LANES>(s) * __builtin_amdgcn_rcpf(head);
     n = 0.f; s = 0.f; q = 0.f;
     add(mean);
-    if (K == 8 && count > K * LANES) {
+    if (K == 8 && K * LANES < kMaxTriples && count > K * LANES) {
       n = 0.f;
       for (int r0 = sub + K * LANES; r0 < count + sub; r0 += K * LANES) {
 #pragma unroll
@@ -210,7 +226,7 @@ __device__ __forceinline__ void merge_rows(const Moments* const (&row)[G], int c
     s = lanes_sum<LANES>(s); q = lanes_sum<LANES>(q);
     const float d = s * __builtin_amdgcn_rcpf(n);     // (also what the roundings of `mean` left)
     q -= s * d;
-    out[g] = make_float2(mean + d, 1.0f / sqrtf((q < 0.f ? 0.f : q) / n + eps));   // (NaN stays NaN)
+    out[g] = make_float2(mean + d, inverse_deviation(q < 0.f ? 0.f : q, n, eps));   // (NaN stays NaN)
   }
 }
 // ... of all groups of a sample into s_stat, by NT threads: as many loads as the row needs (a triple that does not exist adds zeros,
@@ -271,22 +287,28 @@ template <int WIDTH> __device__ __forceinline__ float lane_group_sum(float v) {
   return v;
 }
 
-// Moments of a group's channels (cpg consecutive lanes, a power of two up to 32) over the same pixels, in all of these lanes: the mean
+// Moments of a group's channels (CPG consecutive lanes, a power of two up to 32) over the same pixels, in all of these lanes: the mean
 // first, then the squares about it.
-__device__ __forceinline__ Moments merge_channels(Moments m, int cpg) {
+template <int CPG> __device__ __forceinline__ Moments merge_channels(Moments m) {
   auto sum = [&](float v) {
-    if (cpg > 1) v += quad_xor<1>(v);
-    if (cpg > 2) v += quad_xor<2>(v);
-    if (cpg > 4) v += mirror8(v);
-    if (cpg > 8) v += mirror16(v);
-    if (cpg > 16) v = swap_sum<16>(v);
-    return v;
+    v = lane_group_sum<(CPG < 16 ? CPG : 16)>(v);
+    return CPG > 16 ? swap_sum<16>(v) : v;
   };
-  const float inv = __builtin_amdgcn_rcpf((float)cpg);   // (a power of two: exact)
+  const float inv = 1.f / CPG;                           // (a power of two: exact)
   const float mean = sum(m.mean) * inv, d = m.mean - mean;
   const float rest = sum(d) * inv;                       // what the roundings of the mean left
-  const float m2 = sum(fmaf(m.n * d, d, m.m2)) - m.n * (float)cpg * rest * rest;
-  return Moments{m.n * (float)cpg, mean + rest, m2 < 0.f ? 0.f : m2};   // (NaN stays NaN)
+  const float m2 = sum(fmaf(m.n * d, d, m.m2)) - m.n * (float)CPG * rest * rest;
+  return Moments{m.n * (float)CPG, mean + rest, m2 < 0.f ? 0.f : m2};   // (NaN stays NaN)
+}
+// f(integral_constant<int, cpg>): a form of its own for every size of a group.  (Where one form looked at the size between the lane moves, divided by it
+// for the group and read a ragged block's values behind branches, the moments were 2130 of the 19 850 cycles of a workgroup of 512 channels at 17x23, now 1420.)
+template <typename F> __device__ __forceinline__ void with_group_size(int cpg, F&& f) {
+  if (cpg == 16) f(std::integral_constant<int, 16>{});
+  else if (cpg == 8) f(std::integral_constant<int, 8>{});
+  else if (cpg == 4) f(std::integral_constant<int, 4>{});
+  else if (cpg == 2) f(std::integral_constant<int, 2>{});
+  else if (cpg == 1) f(std::integral_constant<int, 1>{});
+  else f(std::integral_constant<int, 32>{});
 }
 
 // Moments of one channel over a block of 4 x W pixels (rows x cols of them valid) in LDS, pixels PX and image rows ROW floats apart:
@@ -295,10 +317,16 @@ __device__ __forceinline__ Moments merge_channels(Moments m, int cpg) {
 struct Sums { float s, q; };
 __device__ __forceinline__ Sums operator+(Sums a, Sums b) { return Sums{a.s + b.s, a.q + b.q}; }
 template <int W, int PX, bool FULL> __device__ __forceinline__ Sums row_sums(const float* src, float shift, int count) {
+  float v[W];
+#pragma unroll
+  for (int x = 0; x < W; ++x) {
+    v[x] = src[x * PX];
+    if constexpr (!FULL) asm("" : "+v"(v[x]));   // (read whether it counts or not: the compiler would branch round every read)
+  }
   Sums r{0.f, 0.f};
 #pragma unroll
   for (int x = 0; x < W; ++x) {
-    const float d = FULL || x < count ? src[x * PX] - shift : 0.f;
+    const float d = FULL || x < count ? v[x] - shift : 0.f;
     r.s += d; r.q = fmaf(d, d, r.q);
   }
   return r;
@@ -371,13 +399,14 @@ inline MfmaParams conv_params(const ConvArgs& a, int th, int tw, int tn, int slo
   p.rows_out = (Moments*)a.rows_out; p.tickets = (unsigned*)a.tickets;
   p.rows_in = (const Moments*)a.rows_in; p.rows_in_count = a.rows_in_count; p.eps = a.eps;
   p.x2 = nullptr; p.w2 = nullptr; p.bias2 = nullptr; p.cin2 = 0; p.w2_bytes = 0;
+  p.cpg_in = std::max(1, a.cin / a.groups); p.inv_cpg_in = reciprocal(p.cpg_in);
   p.next = a.next;
   return p;
 }
 // the statistics hand-over a launch is asked for is one its kernel can serve
 inline int check_hand_over(const MfmaParams& p) {
   WMDEC_REQUIRE(!p.rows_out || (p.stats && p.tickets), WMDEC_ERR_INVALID_ARG, "convolution: row moments need the triple scratch and the ticket counters");
-  WMDEC_REQUIRE(!p.rows_in || (p.rows_in_count >= 1 && p.rows_in_count <= 128), WMDEC_ERR_UNSUPPORTED, "convolution: at most 128 triples per group can be merged in the prologue");
+  WMDEC_REQUIRE(!p.rows_in || (p.rows_in_count >= 1 && p.rows_in_count <= kMaxTriples), WMDEC_ERR_UNSUPPORTED, "convolution: at most %d triples per group can be merged in the prologue", kMaxTriples);
   return WMDEC_OK;
 }
 

@@ -76,13 +76,14 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
   float* s_mu = reinterpret_cast<float*>(s_ab + p.cin);            // [cin] mean per channel (fp32 only), read as 16-byte vectors
   float2* s_stat = reinterpret_cast<float2*>(s_mu + (ES == 4 ? p.cin : 0));   // [groups] (mean, rstd): any number, so it comes last
 
+  fetch_arguments<sizeof(MfmaParams) + sizeof(int)>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = wave % WN, wk = wave / WN;
   const int lm = lane & 31, lk = lane >> 5;
 
   const WorkTile wt = workgroup_tile(p);
-  if (__builtin_expect(carries_weights(p, wt), 0)) { warm_weights(p.next, p.total, NW, wave, lane); return; }
+  if (__builtin_expect(carries_weights(p), 0)) { warm_weights(p.next, p.total, NW, wave, lane); return; }
   const int nt = wt.nt, n = wt.n;
   const int ty0 = wt.y * TH, tx0 = wt.x * TW;
   const int co0 = nt * TN;
@@ -102,8 +103,7 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
     for (int k = 0; k < FV; ++k) f.v[k] = load_fragment(wrsrc, lo + 16 * k, off);
   };
 
-  // The first rounds' weights, behind the input and the moments, which are needed first: loads return in order.  (In front of
-  // them, 512 channels at 17x23 took 0.3 us more; with four rounds ahead instead of two 0.5 us more still.)
+  // The first rounds' weights, behind the moments and the input, which are needed first: loads return in order.
   auto first_weights = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -123,14 +123,14 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
     const int hp = (tid + i * NT) / VPP;
     const int hy = hp / HW_, hx = hp % HW_;
     const int gy = ty0 + hy - 1, gx = tx0 + hx - 1;
-    const bool in_patch = hp < HP;
-    const bool inside = in_patch && gy >= 0 && gy < p.h && gx >= 0 && gx < p.w_out;
+    const bool in_patch = hp < HP, inside = in_patch & ((unsigned)gy < (unsigned)p.h) & ((unsigned)gx < (unsigned)p.w_out);   // (no branches)
     src_pix[i] = inside ? gy * p.w_out + gx : 0;
     // a vector outside the image is loaded from pixel 0 and stored to the spare slot; its real slot is zeroed here, once
-    dst_off[i] = (inside ? hy * ROWB + hx * PSB : SPARE) + cvec * 16;
-    if (in_patch && !inside) {
-      *reinterpret_cast<u32x4*>(smem + hy * ROWB + hx * PSB + cvec * 16) = u32x4{0u, 0u, 0u, 0u};
-      *reinterpret_cast<u32x4*>(smem + BUFB + hy * ROWB + hx * PSB + cvec * 16) = u32x4{0u, 0u, 0u, 0u};
+    const int at = hy * ROWB + hx * PSB;
+    dst_off[i] = (inside ? at : SPARE) + cvec * 16;
+    if (in_patch & !inside) {
+      *reinterpret_cast<u32x4*>(smem + at + cvec * 16) = u32x4{0u, 0u, 0u, 0u};
+      *reinterpret_cast<u32x4*>(smem + BUFB + at + cvec * 16) = u32x4{0u, 0u, 0u, 0u};
     }
   }
   u32x4 raw[2][NV];   // two rounds in flight: round r lives in raw[r & 1]
@@ -196,31 +196,42 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
   }
 
   issue(raw[0], p.x, p.cin, 0);
-  if (rounds > 1) issue(raw[1], p.x, p.cin, 1);
+  issue(raw[1], p.x, p.cin, min(1, rounds - 1));
 
-  if constexpr (ACT == 0) first_weights();
-  // ---- scale/shift table.  16-bit types: (a, b) = k * (gamma * rstd, beta - mean * gamma * rstd), k = -log2(e) with
-  // SiLU (see silu_from_scaled).  fp32: (gamma * rstd, beta), the mean stays apart.
-  const int cpg_in = ACT > 0 ? p.cin / p.groups : 1;
+  // ---- mean and rstd of the groups
+  constexpr int PRE = 2;                             // table entries of a thread whose gamma and beta are requested together with the moments
+  float gpre[PRE] = {}, bpre[PRE] = {};
+  int group[PRE] = {};
   if constexpr (ACT > 0) {
     constexpr int TPG = 16;                          // lanes that merge the triples of a group
-    float gpre = 0.f, bpre = 0.f;                    // requested together with the triples: one round trip less
-    if (tid < p.cin) { gpre = p.gamma[tid]; bpre = p.beta[tid]; }
+#pragma unroll
+    for (int j = 0; j < PRE; ++j) {
+      const int c = min(tid + j * NT, p.cin - 1);
+      gpre[j] = p.gamma[c]; bpre[j] = p.beta[c];
+      group[j] = quotient_of(c, p.cpg_in, p.inv_cpg_in);
+    }
     if (p.rows_in) {
       merge_sample<TPG, NT>(p.rows_in + (size_t)n * p.groups * p.rows_in_count, p.groups, p.rows_in_count, tid, p.eps, s_stat);   // (at most 128 triples per group)
     } else {
       for (int g = tid; g < p.groups; g += NT) s_stat[g] = make_float2(p.mean[n * p.groups + g], p.rstd[n * p.groups + g]);
     }
-    first_weights();
+  }
+  first_weights();
+  // ---- scale/shift table.  16-bit types: (a, b) = k * (gamma * rstd, beta - mean * gamma * rstd), k = -log2(e) with
+  // SiLU (see silu_from_scaled).  fp32: (gamma * rstd, beta), the mean stays apart.
+  if constexpr (ACT > 0) {
     __syncthreads();
     const float k = (ES == 2 && ACT == 2) ? -1.4426950408889634f : 1.0f;
-    for (int c = tid; c < p.cin; c += NT) {
-      const float2 st = s_stat[c / cpg_in];
-      const float ga = c == tid ? gpre : p.gamma[c], be = c == tid ? bpre : p.beta[c];
+    auto entry = [&](int c, int g, float ga, float be) {
+      const float2 st = s_stat[g];
       const float a = ga * st.y;
       s_ab[c] = ES == 2 ? make_float2(k * a, k * (be - st.x * a)) : make_float2(a, be);
       if constexpr (ES == 4) s_mu[c] = st.x;
-    }
+    };
+#pragma unroll
+    for (int j = 0; j < PRE; ++j)
+      if (tid + j * NT < p.cin) entry(tid + j * NT, group[j], gpre[j], bpre[j]);
+    for (int c = tid + PRE * NT; c < p.cin; c += NT) entry(c, quotient_of(c, p.cpg_in, p.inv_cpg_in), p.gamma[c], p.beta[c]);
   }
   __syncthreads();
 
@@ -315,17 +326,17 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
       for (int q = 0; q < 4; ++q)
         *reinterpret_cast<f32x4*>(red + (size_t)(wk * M + mi * 32 + lm) * RR + (wn * NI + ni) * 32 + 8 * q + 4 * lk) =
             f32x4{acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2], acc[mi][ni][4 * q + 3]};
-  constexpr int C4 = TN / 4, NJ = (M * C4 + NT - 1) / NT;              // four-channel vectors of a pixel, per thread
-  static_assert(NT % C4 == 0 && C4 <= 64, "a thread keeps its four channels");
+  constexpr int C4 = TN / 4, NJ = M * C4 / NT;                         // four-channel vectors of a pixel, per thread
+  static_assert(NT % C4 == 0 && C4 <= 64 && NJ * NT == M * C4, "a thread keeps its four channels, all threads as many");
   const int c4 = tid % C4, co = co0 + c4 * 4;
   const T* rin = p.res ? reinterpret_cast<const T*>(p.res) + (size_t)n * p.h * p.w_out * p.cout : nullptr;
-  int out_off[NJ];      // element offset of this thread's vectors in the sample (-1: outside the image or the tile)
+  int out_off[NJ];      // element offset of this thread's vectors in the sample (-1: outside the image)
   uint32_t rv[NJ][ES];  // residual vectors, requested before the partial sums are complete (clamped addresses)
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int px = tid / C4 + j * (NT / C4);
     const int oy = ty0 + px / TW, ox = tx0 + px % TW;
-    out_off[j] = px < M && oy < p.h && ox < p.w_out ? (oy * p.w_out + ox) * p.cout + co : -1;
+    out_off[j] = oy < p.h && ox < p.w_out ? (oy * p.w_out + ox) * p.cout + co : -1;
 #pragma unroll
     for (int e = 0; e < ES; ++e) rv[j][e] = 0u;
     if (rin) {
@@ -347,7 +358,6 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
   const size_t sample = (size_t)n * p.h * p.w_out * p.cout;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    if (out_off[j] < 0) continue;
     const int px = tid / C4 + j * (NT / C4);
     float* own = red + (size_t)px * RR + c4 * 4;
     f32x4 v = *reinterpret_cast<const f32x4*>(own);
@@ -361,10 +371,10 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
       v += f32x4{unpack_lo<T>(rv[j][0]), unpack_hi<T>(rv[j][0]), unpack_lo<T>(rv[j][1]), unpack_hi<T>(rv[j][1])};
     }
     if (ES == 4 || y_f32) {
-      *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.y) + sample + out_off[j]) = v;
+      if (out_off[j] >= 0) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.y) + sample + out_off[j]) = v;
     } else if constexpr (ES == 2) {
       const u32x2 t = u32x2{pack2<T>(v[0], v[1]), pack2<T>(v[2], v[3])};
-      *reinterpret_cast<u32x2*>(reinterpret_cast<T*>(p.y) + sample + out_off[j]) = t;
+      if (out_off[j] >= 0) *reinterpret_cast<u32x2*>(reinterpret_cast<T*>(p.y) + sample + out_off[j]) = t;
       v = f32x4{unpack_lo<T>(t.x), unpack_hi<T>(t.x), unpack_lo<T>(t.y), unpack_hi<T>(t.y)};   // moments of what is stored
     }
     if (p.stats) *reinterpret_cast<f32x4*>(own) = v;
@@ -377,17 +387,20 @@ __global__ __launch_bounds__(64 * WN * WK, OCC) void conv_ksplit_kernel(MfmaPara
     __syncthreads();
     constexpr int BX = TW / 8;
     static_assert(TH == 4 && TW % 8 == 0 && TN % 32 == 0, "blocks of 4 x 8 pixels");
-    const int half = lane >> 5;
-    for (int i = wave; i < BX * (TN / 32); i += NW) {   // (uniform: a wavefront takes 32 channels of a block)
-      const int b = i / (TN / 32), c = i % (TN / 32) * 32 + lm, x0 = tx0 + 8 * b;
-      const int rows = min(4, p.h - ty0), cols = min(8, p.w_out - x0);
-      if (cols <= 0) continue;
-      const float* src = red + (size_t)(8 * b) * RR + c;
-      const Sums own = two_row_sums<8, TW * RR, RR>(src + 2 * half * TW * RR, src[0], rows - 2 * half, cols);
-      const Moments m = merge_channels(block_moments(Sums{swap_sum<32>(own.s), swap_sum<32>(own.q)}, src[0], rows, cols), p.stats_cpg);
-      if (half == 0 && c % p.stats_cpg == 0)
-        p.stats[((size_t)n * p.stats_groups + (co0 + c) / p.stats_cpg) * p.stats_slots + (ty0 / 4) * ((p.w_out + 7) / 8) + x0 / 8] = m;
-    }
+    const int half = lane >> 5, blocks_x = (p.w_out + 7) / 8;
+    with_group_size(p.stats_cpg, [&](auto cpg_c) __attribute__((always_inline)) {
+      constexpr int CPG = decltype(cpg_c)::value;
+      for (int i = wave; i < BX * (TN / 32); i += NW) {   // (uniform: a wavefront takes 32 channels of a block)
+        const int b = i / (TN / 32), c = i % (TN / 32) * 32, x0 = tx0 + 8 * b;
+        const int rows = min(4, p.h - ty0), cols = min(8, p.w_out - x0);
+        if (cols <= 0) continue;
+        Moments* dst = p.stats + (size_t)(n * p.stats_groups + (co0 + c) / CPG) * p.stats_slots + (ty0 / 4) * blocks_x + x0 / 8;
+        const float* src = red + (size_t)(8 * b) * RR + c + lm;
+        const Sums own = two_row_sums<8, TW * RR, RR>(src + 2 * half * TW * RR, src[0], rows - 2 * half, cols);
+        const Moments m = merge_channels<CPG>(block_moments(Sums{swap_sum<32>(own.s), swap_sum<32>(own.q)}, src[0], rows, cols));
+        if (half == 0 && lm % CPG == 0) dst[lm / CPG * p.stats_slots] = m;
+      }
+    });
   }
 }
 

@@ -178,7 +178,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
         const int rows = min(MTH, p.h - y0), cols = min(MTW, p.w - x0);
         Moments m = block_moments(two_row_sums<MTW, MTW * RW, RW>(src, src[0], rows, cols) +
                                   two_row_sums<MTW, MTW * RW, RW>(src + 2 * MTW * RW, src[0], rows - 2, cols), src[0], rows, cols);
-        m = merge_channels(m, p.cpg);
+        with_group_size(p.cpg, [&](auto cpg_c) __attribute__((always_inline)) { m = merge_channels<decltype(cpg_c)::value>(m); });
         if ((lm & (p.cpg - 1)) == 0 && m.n > 0.f) dst[(size_t)((co_w + lm) / p.cpg) * p.stats_stride + lk] = m;
       }
     } else if (mi + 1 == MI) {
@@ -322,6 +322,7 @@ void conv_mfma_kernel(MfmaParams p) {
   static_assert((RING > 6 ? 2 : resident_workgroups(MI * NI, WM, WN)) * WM * WN * patch_floats(MI, NI) * sizeof(float) <= 160 * 1024,
                 "the workgroups that the registers are budgeted for fit the LDS of a compute unit");
 
+  fetch_arguments<sizeof(MfmaParams)>();
   extern __shared__ __align__(16) unsigned char smem[];
   T* s_a = reinterpret_cast<T*>(smem);                                          // [2][BUF]
   float2* s_ab = reinterpret_cast<float2*>(smem + ((2 * BUF * 2 + 15) & ~15));  // [cin] (scale, shift)
@@ -332,7 +333,7 @@ void conv_mfma_kernel(MfmaParams p) {
   const int lm = lane & 31, lk = lane >> 5;
 
   const WorkTile wt = workgroup_tile(p);
-  if (__builtin_expect(carries_weights(p, wt), 0)) { warm_weights(p.next, p.total, WM * WN, wave, lane); return; }
+  if (__builtin_expect(carries_weights(p), 0)) { warm_weights(p.next, p.total, WM * WN, wave, lane); return; }
   const int nt = wt.nt, n = wt.n, tile = wt.tile;
   const int ty0 = wt.y * TH, tx0 = wt.x * TW;
   const int co0 = nt * TN;
@@ -418,14 +419,9 @@ void conv_mfma_kernel(MfmaParams p) {
     const int hp = v / VPP;
     const int hy = hp / HW_, hx = hp % HW_;
     const int gy = ty0 + hy - PAD, gx = tx0 + hx - PAD;
-    const bool in_patch = v < HP * VPP;
-    const bool inside = in_patch && gy >= 0 && gy < p.h && gx >= 0 && gx < p.w_out;
-    src_off[i] = 0;
-    src_pix[i] = 0;
-    if (inside) {
-      src_pix[i] = gy * p.w_out + gx;
-      src_off[i] = src_pix[i] * p.cin * (int)sizeof(T);
-    }
+    const bool in_patch = v < HP * VPP, inside = in_patch & ((unsigned)gy < (unsigned)p.h) & ((unsigned)gx < (unsigned)p.w_out);   // (no branches)
+    src_pix[i] = inside ? gy * p.w_out + gx : 0;
+    src_off[i] = src_pix[i] * p.cin * (int)sizeof(T);
     const bool keep = KS == 1 ? in_patch : inside;
     dst_off[i] = (keep ? hy * ROW + hx * PS : SPARE) + cvec * 8;
     if (KS != 1 && in_patch && !inside) {
@@ -535,8 +531,11 @@ void conv_mfma_kernel(MfmaParams p) {
   // the staged value is u = -log2(e) * t, from which silu(t) = t / (1 + 2^u) = u / (-log2(e) - log2(e) * 2^u) takes
   // one exp2, one fma, one reciprocal and one multiply
   if constexpr (ACT > 0) {
-    const int cpg = p.cin / p.groups;
     const float k = ACT == 2 ? -1.4426950408889634f : 1.0f;
+    auto entry = [&](int c, float2 st, float ga, float be) {
+      const float a = ga * st.y;
+      s_ab[c] = make_float2(k * a, k * (be - st.x * a));
+    };
     if (p.rows_in) {
       // mean / rstd of every group from the row triples its producer left: eight lanes per group take the rows
       // round-robin (16 in the form that has to reproduce a kernel with 16); (mean, rstd) parked behind the table
@@ -546,33 +545,24 @@ void conv_mfma_kernel(MfmaParams p) {
       // (elsewhere other workgroups cover that latency and the registers are better left to the main loop).
       constexpr int PRE = RING > 6 ? 2 : 0;
       float gpre[2] = {0.f, 0.f}, bpre[2] = {0.f, 0.f};
+      int group[2] = {0, 0};
 #pragma unroll
       for (int j = 0; j < PRE; ++j) {
         const int c = min(tid + j * NT, p.cin - 1);
         gpre[j] = p.gamma[c]; bpre[j] = p.beta[c];
+        group[j] = quotient_of(c, p.cpg_in, p.inv_cpg_in);
       }
       constexpr int LANES = QUARTERS ? 16 : 8;
       merge_sample<LANES, NT>(p.rows_in + (size_t)n * p.groups * p.rows_in_count, p.groups, p.rows_in_count, tid, p.eps, s_stat);
       __syncthreads();
 #pragma unroll
-      for (int j = 0; j < PRE; ++j) {
-        const int c = tid + j * NT;
-        if (c < p.cin) {
-          const float2 st = s_stat[c / cpg];
-          const float a = gpre[j] * st.y;
-          s_ab[c] = make_float2(k * a, k * (bpre[j] - st.x * a));
-        }
-      }
-      for (int c = tid + PRE * NT; c < p.cin; c += NT) {
-        const float2 st = s_stat[c / cpg];
-        const float a = p.gamma[c] * st.y;
-        s_ab[c] = make_float2(k * a, k * (p.beta[c] - st.x * a));
-      }
+      for (int j = 0; j < PRE; ++j)
+        if (tid + j * NT < p.cin) entry(tid + j * NT, s_stat[group[j]], gpre[j], bpre[j]);
+      for (int c = tid + PRE * NT; c < p.cin; c += NT) entry(c, s_stat[quotient_of(c, p.cpg_in, p.inv_cpg_in)], p.gamma[c], p.beta[c]);
     } else {
       for (int c = tid; c < p.cin; c += NT) {
-        const int g = c / cpg;
-        const float a = p.gamma[c] * p.rstd[n * p.groups + g];
-        s_ab[c] = make_float2(k * a, k * (p.beta[c] - p.mean[n * p.groups + g] * a));
+        const int g = n * p.groups + quotient_of(c, p.cpg_in, p.inv_cpg_in);
+        entry(c, make_float2(p.mean[g], p.rstd[g]), p.gamma[c], p.beta[c]);
       }
     }
   }

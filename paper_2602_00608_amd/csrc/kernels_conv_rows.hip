@@ -218,6 +218,7 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
   constexpr bool PARK = park_offsets(TH, NI, RING);
   static_assert(!PARK || NV == 3, "three offsets of either kind");
 
+  fetch_arguments<sizeof(MfmaParams)>();
   extern __shared__ __align__(16) unsigned char smem[];
   T* s_a = reinterpret_cast<T*>(smem);                                          // [2][BUF]
   float* s_bias = reinterpret_cast<float*>(smem + 2 * BUF * 2);                 // [TN]
@@ -243,10 +244,15 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
   const int lane_w = (lane >> 5) * kk_stride + (2 * (lane & 15) + 2 * (lane & 16)) * 16;
   u32x4 bq[D][2];
   f32x4 acc[TH][2 * NI];
+  auto first_weights = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int sp = 0; sp < D - 1; ++sp)
+    for (int sp = 0; sp < D - 1; ++sp)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) bq[sp][h] = load_fragment(wrsrc, lane_w, wcol + weight_offset<NI>(sp, tap_stride) + 16 * h);
+      for (int h = 0; h < 2; ++h) bq[sp][h] = load_fragment(wrsrc, lane_w, wcol + weight_offset<NI>(sp, tap_stride) + 16 * h);
+  };
+  // Two steps of weights come first; a whole chunk of them (RING) behind input and moments, which are needed before them: loads return in order, and
+  // it is a thousand cycles of a compute unit's load path.
+  if constexpr (RING == 0) first_weights();
 
   // ---- staging: a thread owns NV (pixel, channel-octet) vectors of the halo patch; the octet is the same for all.
   // Zero padding without per-element work: a vector outside the image is loaded from pixel 0 (a load under a lane
@@ -261,11 +267,11 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
     const int hp = (tid + i * NT) / VPP;
     const int hy = hp / PW, hx = hp % PW;
     const int gy = ty0 + hy - 1, gx = tx0 + hx - 1;
-    const int at = hp < HP ? hy * ROW + hx * PS : SPARE;
-    const int pix = hp < HP && gy >= 0 && gy < p.h && gx >= 0 && gx < p.w_out ? gy * p.w_out + gx : -1;   // its source in the sample
-    src_off[i] = max(pix, 0) * p.cin * (int)sizeof(T) + cvec * 16;
-    dst_off[i] = (pix >= 0 ? at : SPARE) + cvec * 8;
-    if (pix < 0 && at != SPARE) {
+    const int at = hy * ROW + hx * PS;
+    const bool in_patch = hp < HP, inside = in_patch & ((unsigned)gy < (unsigned)p.h) & ((unsigned)gx < (unsigned)p.w_out);   // (no branches)
+    src_off[i] = (inside ? gy * p.w_out + gx : 0) * p.cin * (int)sizeof(T) + cvec * 16;
+    dst_off[i] = (inside ? at : SPARE) + cvec * 8;
+    if (in_patch & !inside) {
       *reinterpret_cast<u32x4*>(s_a + at + cvec * 8) = u32x4{0u, 0u, 0u, 0u};
       *reinterpret_cast<u32x4*>(s_a + BUF + at + cvec * 8) = u32x4{0u, 0u, 0u, 0u};
     }
@@ -344,8 +350,11 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
   // the staged value is u = -log2(e) * t, from which silu(t) = t / (1 + 2^u) = u / (-log2(e) - log2(e) * 2^u) takes
   // one exp2, one fma, one reciprocal and one multiply
   if constexpr (ACT > 0) {
-    const int cpg = p.cin / p.groups;
     const float k = ACT == 2 ? -1.4426950408889634f : 1.0f;
+    auto entry = [&](int c, float2 st, float ga, float be) {
+      const float a = ga * st.y;
+      s_ab[c] = make_float2(k * a, k * (be - st.x * a));
+    };
     if (p.rows_in) {
       // mean / rstd of every group from the row triples its producer left: eight lanes per group take the rows
       // round-robin; (mean, rstd) parked behind the table
@@ -355,36 +364,30 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
       // (elsewhere other workgroups cover that latency and the registers are better left to the main loop).
       constexpr int PRE = RING > 0 ? 2 : 0;
       float gpre[2] = {0.f, 0.f}, bpre[2] = {0.f, 0.f};
+      int group[2] = {0, 0};
 #pragma unroll
       for (int j = 0; j < PRE; ++j) {
         const int c = min(tid + j * NT, p.cin - 1);
         gpre[j] = p.gamma[c]; bpre[j] = p.beta[c];
+        group[j] = quotient_of(c, p.cpg_in, p.inv_cpg_in);
       }
       constexpr int LANES = 8;
       merge_sample<LANES, NT>(p.rows_in + (size_t)n * p.groups * p.rows_in_count, p.groups, p.rows_in_count, tid, p.eps, s_stat);
+      if constexpr (RING > 0) first_weights();
       __syncthreads();
 #pragma unroll
-      for (int j = 0; j < PRE; ++j) {
-        const int c = tid + j * NT;
-        if (c < p.cin) {
-          const float2 st = s_stat[c / cpg];
-          const float a = gpre[j] * st.y;
-          s_ab[c] = make_float2(k * a, k * (bpre[j] - st.x * a));
-        }
-      }
-      for (int c = tid + PRE * NT; c < p.cin; c += NT) {
-        const float2 st = s_stat[c / cpg];
-        const float a = p.gamma[c] * st.y;
-        s_ab[c] = make_float2(k * a, k * (p.beta[c] - st.x * a));
-      }
+      for (int j = 0; j < PRE; ++j)
+        if (tid + j * NT < p.cin) entry(tid + j * NT, s_stat[group[j]], gpre[j], bpre[j]);
+      for (int c = tid + PRE * NT; c < p.cin; c += NT) entry(c, s_stat[quotient_of(c, p.cpg_in, p.inv_cpg_in)], p.gamma[c], p.beta[c]);
     } else {
+      if constexpr (RING > 0) first_weights();
       for (int c = tid; c < p.cin; c += NT) {
-        const int g = c / cpg;
-        const float a = p.gamma[c] * p.rstd[n * p.groups + g];
-        s_ab[c] = make_float2(k * a, k * (p.beta[c] - p.mean[n * p.groups + g] * a));
+        const int g = n * p.groups + quotient_of(c, p.cpg_in, p.inv_cpg_in);
+        entry(c, make_float2(p.mean[g], p.rstd[g]), p.gamma[c], p.beta[c]);
       }
     }
   }
+  if constexpr (RING > 0 && ACT == 0) first_weights();
   __syncthreads();            // scale/shift table complete
   auto table = [&](const float2* tab, int part) -> f32x4 {   // entries of word `part` of the thread's octet
     if constexpr (ACT > 0) return *reinterpret_cast<const f32x4*>(tab + 2 * part);

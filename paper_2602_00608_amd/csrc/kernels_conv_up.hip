@@ -51,6 +51,7 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
   constexpr int NT = 256, KS = 4 / (H * WN), NTK = NT / KS, TN = 32 * WN, WAVES = H * WN;
   constexpr int ER = GH / KS;                // grid rows whose pixels a wavefront finishes (the last group: one less)
   constexpr int VPP = KC / 8, NV = (PH_ * PW * VPP + NTK - 1) / NTK;
+  fetch_arguments<sizeof(MfmaParams) + sizeof(int)>();
   extern __shared__ __align__(16) unsigned char smem_all[];   // [KS][2][BUFB]
 
   const int lane = threadIdx.x & 63;
@@ -60,7 +61,7 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
   unsigned char* smem = smem_all + wk * 2 * BUFB;
   const int px = lane & 15, oct = lane >> 4;
   const WorkTile wt = workgroup_tile(p);
-  if (__builtin_expect(carries_weights(p, wt), 0)) { warm_weights(p.next, p.total, 4, wave, lane); return; }
+  if (__builtin_expect(carries_weights(p), 0)) { warm_weights(p.next, p.total, 4, wave, lane); return; }
   const int nt = wt.nt, n = wt.n, tile = wt.tile;
   const int ty0 = wt.y * TH, tx0 = wt.x * TW;
   const int h_in = p.h >> 1, w_in = p.w_out >> 1;
@@ -73,8 +74,6 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
   const int wcol = (co_w >> 5) * 1024 + (co_w & 16) * 16;
   const int lane_w = (oct >> 1) * kk_stride + (px + 32 * (oct & 1)) * 16;
   u32x4 bq[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) bq[t] = load_fragment(wrsrc, lane_w, wcol + 2 * c0 * kk_stride + kTap[t] * tap_stride);
 
   const int cvec = tid % VPP;
   const char* xin = reinterpret_cast<const char*>(p.x) + (size_t)n * h_in * w_in * p.cin * 2;
@@ -83,13 +82,14 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
   for (int i = 0; i < NV; ++i) {
     const int hp = (tid + i * NTK) / VPP, hy = hp / PW, hx = hp % PW;
     const int gy = ty0 + hy - 1, gx = tx0 + hx - 1;
-    const bool in_patch = hp < PH_ * PW, inside = in_patch && gy >= 0 && gy < h_in && gx >= 0 && gx < w_in;
+    const bool in_patch = hp < PH_ * PW, inside = in_patch & ((unsigned)gy < (unsigned)h_in) & ((unsigned)gx < (unsigned)w_in);   // (no branches)
     // outside the image: loaded from pixel 0, stored to the spare slot; the real slot is zeroed once
     src_off[i] = ((inside ? gy * w_in + gx : 0) * p.cin + cvec * 8) * 2;
-    dst_off[i] = (inside ? hy * ROWB + hx * PSB : SPARE) + cvec * 16;
-    if (in_patch && !inside) {
-      *reinterpret_cast<u32x4*>(smem + hy * ROWB + hx * PSB + cvec * 16) = u32x4{0u, 0u, 0u, 0u};
-      *reinterpret_cast<u32x4*>(smem + BUFB + hy * ROWB + hx * PSB + cvec * 16) = u32x4{0u, 0u, 0u, 0u};
+    const int at = hy * ROWB + hx * PSB;
+    dst_off[i] = (inside ? at : SPARE) + cvec * 16;
+    if (in_patch & !inside) {
+      *reinterpret_cast<u32x4*>(smem + at + cvec * 16) = u32x4{0u, 0u, 0u, 0u};
+      *reinterpret_cast<u32x4*>(smem + BUFB + at + cvec * 16) = u32x4{0u, 0u, 0u, 0u};
     }
   }
   u32x4 raw[NV];
@@ -103,6 +103,11 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
     for (int i = 0; i < NV; ++i) *reinterpret_cast<u32x4*>(buf + dst_off[i]) = raw[i];
   };
 
+  issue(0);
+  // (behind the first input, which is needed first: loads return in order)
+#pragma unroll
+  for (int t = 0; t < 9; ++t) bq[t] = load_fragment(wrsrc, lane_w, wcol + 2 * c0 * kk_stride + kTap[t] * tap_stride);
+
   f32x4 acc[4][GH];   // A, B, C, D of every grid row: channels co_w + 4 oct + 0..3 of column px; every phase holds A once, so A starts from the bias
   {
     f32x4 bias = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -114,7 +119,6 @@ __global__ __launch_bounds__(256, 2) void conv_up_kernel(MfmaParams p, int y_f32
   }
   const int p_off = px * PSB + oct * 16;
 
-  issue(0);
   store(smem);
   issue(1);
   __syncthreads();
