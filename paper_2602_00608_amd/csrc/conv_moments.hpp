@@ -74,23 +74,24 @@ __device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Mom
   }
 }
 
-// Lane l holds octet l % OCTETS of the wavefront's channels.
-template <int OCTETS>
-__device__ __forceinline__ void emit_octets(const LaneMoments<8> (&st)[1], int lane, int co_w, Moments* const (&dst)[1], int cpg, int stats_stride, bool handed_over) {
+// Lane l holds vector l % VECTORS of the wavefront's channels, CH of them each.
+template <int VECTORS, int CH>
+__device__ __forceinline__ void emit_vectors(const LaneMoments<CH> (&st)[1], int lane, int co_w, Moments* const (&dst)[1], int cpg, int stats_stride, bool handed_over) {
+  static_assert(CH == 4 || CH == 8, "16 bytes");
   auto lanes = [&](float v) {
-    if constexpr (OCTETS <= 4) v += row_rotate<4>(v);
+    if constexpr (VECTORS <= 4) v += row_rotate<4>(v);
     v += row_rotate<8>(v);
     v = swap_sum<32>(swap_sum<16>(v));
-    if (cpg > 8) v += quad_xor<1>(v);
-    if (cpg > 16) v += quad_xor<2>(v);
+    if (cpg > CH) v += quad_xor<1>(v);
+    if (cpg > 2 * CH) v += quad_xor<2>(v);
     return v;
   };
-  const int co = co_w + lane * 8;
-  const bool writes = lane < OCTETS && ((lane * 8) & (cpg - 1)) == 0;
-  if (cpg >= 8) emit_moments<8, 1, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
-  else if (cpg == 4) emit_moments<8, 2, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
-  else if (cpg == 2) emit_moments<8, 4, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
-  else emit_moments<8, 8, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
+  const int co = co_w + lane * CH;
+  const bool writes = lane < VECTORS && ((lane * CH) & (cpg - 1)) == 0;
+  if (cpg >= CH) emit_moments<CH, 1, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
+  else if (cpg == CH / 2) emit_moments<CH, 2, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
+  else if (cpg == CH / 4) emit_moments<CH, 4, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
+  else if constexpr (CH == 8) emit_moments<8, 8, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
 }
 
 // Lane l holds channels 2 (l % 16) and the next of 32, of the pixels of quarter l / 16; full: all lanes hold the same number of them.

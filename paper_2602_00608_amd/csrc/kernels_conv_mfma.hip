@@ -182,7 +182,7 @@ __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[MI][NI], cons
         if ((lm & (p.cpg - 1)) == 0 && m.n > 0.f) dst[(size_t)((co_w + lm) / p.cpg) * p.stats_stride + lk] = m;
       }
     } else if (mi + 1 == MI) {
-      if (p.stats) emit_octets<NI * 4>({st}, lane, co_w, {p.stats}, p.cpg, p.stats_stride, p.handed_over);
+      if (p.stats) emit_vectors<NI * 4, 8>({st}, lane, co_w, {p.stats}, p.cpg, p.stats_stride, p.handed_over);
     }
     if (mi + 1 < MI && !ahead) put(wave_lds + (mi + 1) % PATCHES * 32 * RW, mi + 1);
   }

@@ -21,7 +21,7 @@
 #include <mutex>
 #include <type_traits>
 
-#include "moments.hpp"
+#include "conv_moments.hpp"
 
 #if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
 #error "kernels_gn.hip relies on gfx950 memory behaviour (see the note on the single-launch kernel)"
@@ -48,10 +48,12 @@ constexpr int kVecThreads = 1024;
 constexpr int kVecMaxChunks = 256;
 constexpr int kVecMaxGroups = 256;
 
-template <typename T, int V, bool MASKED>
+// MIX: of f16, conversion and shift are one instruction (v_fma_mix_f32; the compiler makes it if it does not see that the factor is 1).
+template <typename T, int V, bool MASKED, int U = 8, bool MIX = false>
 __device__ __forceinline__ void gn_accumulate(const char* slab, unsigned off, unsigned end, unsigned sweep, const float* shift,
                                               float* s, float* q) {
-  constexpr int U = 8;
+  float one = 1.f;
+  if constexpr (MIX && std::is_same<T, f16_t>::value) asm("" : "+v"(one));
   Vec16<T> v[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -63,7 +65,7 @@ __device__ __forceinline__ void gn_accumulate(const char* slab, unsigned off, un
     const bool live = !MASKED || off + u * sweep < end;
 #pragma unroll
     for (int j = 0; j < V; ++j) {
-      const float d = live ? to_float(v[u].v[j]) - shift[j] : 0.f;
+      const float d = live ? fmaf(to_float(v[u].v[j]), one, -shift[j]) : 0.f;
       s[j] += d;
       q[j] = fmaf(d, d, q[j]);
     }
@@ -202,6 +204,49 @@ __global__ __launch_bounds__(kVecThreads, vec_waves<T>()) void gn_stats_vec(cons
   }
 }
 
+// Columns: a workgroup takes 64 bytes of every pixel of a sample, whole groups, and needs nothing from the others.  A thread sums the channels of
+// its vector shifted by its first pixel, the lanes of a wavefront are merged as in the convolutions' epilogues, the 16 wavefronts' triples of a
+// group by 16 lanes.  Few compute units stream it, each bound by latency and conversions (four vectors in flight a thread: eight or sixteen are slower, as are 32 bytes
+// a pixel), so it is for images of few pixels, where gn_stats_vec waits longer for its hand-over: publish, ticket and read are three memory round trips one
+// after the other.
+constexpr int kColThreads = 1024, kColVecs = 4;
+template <typename T>
+__global__ __launch_bounds__(kColThreads) void gn_stats_columns(const T* __restrict__ x, int pixels, int c, int groups, float eps, float* __restrict__ mean, float* __restrict__ rstd) {
+  constexpr int V = Vec16<T>::N, VECS = kColVecs, U = 4, CH = VECS * V, WAVES = kColThreads / 64, ROWS = kColThreads / VECS;
+  __shared__ Moments s_w[CH][WAVES];   // triples per (group, wavefront)
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // workgroup id -> (sample, column); the ids of one XCD (id % 8) are neighbours: the columns of a 128-byte line come out of one L2
+  const unsigned cols = c / CH, total = gridDim.x, per = total / 8, rem = total % 8, xcd = blockIdx.x % 8;
+  const unsigned at = xcd * per + min(xcd, rem) + blockIdx.x / 8, n = at / cols, col = at % cols;
+  const unsigned pitch = (unsigned)c * sizeof(T), sweep = ROWS * pitch, end = (unsigned)pixels * pitch;   // (a sample is below 2^31 bytes)
+  const char* slab = reinterpret_cast<const char*>(x + (size_t)n * pixels * c) + col * (VECS * 16);
+  const int row = tid / VECS, own = row < pixels ? (pixels - row + ROWS - 1) / ROWS : 0;
+  unsigned off = (unsigned)row * pitch + (tid % VECS) * 16;
+  LaneMoments<V> st[1];
+  st[0].n = (float)own;
+  {
+    const Vec16<T> v = *reinterpret_cast<const Vec16<T>*>(slab + (off < end ? off : (tid % VECS) * 16));
+#pragma unroll
+    for (int j = 0; j < V; ++j) { st[0].shift[j] = to_float(v.v[j]); st[0].s[j] = 0.f; st[0].q[j] = 0.f; }
+  }
+  for (; off + (U - 1) * sweep < end; off += U * sweep) gn_accumulate<T, V, false, U, true>(slab, off, end, sweep, st[0].shift, st[0].s, st[0].q);
+  if (off < end) gn_accumulate<T, V, true, U, true>(slab, off, end, sweep, st[0].shift, st[0].s, st[0].q);
+  const int cpg = c / groups;
+  Moments* const dst[1] = {&s_w[0][wave]};
+  emit_vectors<VECS, V>(st, lane, 0, dst, cpg, WAVES, false);
+  __syncthreads();
+  const int own_groups = CH / cpg;
+  if (tid < own_groups * WAVES) {   // (whole rows of 16 lanes)
+    const Moments* const rows[1] = {&s_w[tid / WAVES][0]};
+    float2 out[1];
+    merge_rows<WAVES, 1, 1>(rows, WAVES, tid % WAVES, eps, out);
+    if (tid % WAVES == 0) {
+      const int g = n * groups + col * own_groups + tid / WAVES;
+      mean[g] = out[0].x; rstd[g] = out[0].y;
+    }
+  }
+}
+
 // General path (any c, groups): grid = (chunks, groups, n); one workgroup walks
 // the (pixel, channel-in-group) pairs of its slab.
 template <typename T>
@@ -283,7 +328,13 @@ int pick_chunks(int pixels, int c, int V, bool vec) {
   return chunks;
 }
 
-struct Plan { bool vec; int chunks; int chunk_pixels; };
+// Images of up to so many pixels take gn_stats_columns.  us, gn_stats_vec / columns, inputs from beyond the L2s: f16 512 channels 17x23 9.7 / 4.9, 32x32 10.2 / 5.0,
+// four of them 10.5 / 5.6, 45x60 10.8 / 8.7; 256 channels two 61x47 10.8 / 8.0; 128 channels 64x64 10.1 / 8.6; f32 64 channels 32x32 (one slab) 6.1 / 4.3, 64x64
+// 8.9 / 7.3; past the line 60x90 of 512 11.5 / 12.7, of 128 10.3 / 11.4, 80x100 10.4 / 14.3.  (Not a function of the batch: a sample's result must not depend on its
+// neighbours.)
+constexpr int kColPixels = 4096;
+
+struct Plan { bool vec; int chunks; int chunk_pixels; bool columns; };
 
 Plan make_plan(int x_dtype, int n, int h, int w, int c, int groups) {
   (void)n;
@@ -300,6 +351,7 @@ Plan make_plan(int x_dtype, int n, int h, int w, int c, int groups) {
     p.chunk_pixels = ((p.chunk_pixels + ppi - 1) / ppi) * ppi;
   }
   p.chunks = (pixels + p.chunk_pixels - 1) / p.chunk_pixels;
+  p.columns = p.vec && pixels <= kColPixels && c % (kColVecs * V) == 0 && cpg <= kColVecs * V;
   return p;
 }
 
@@ -323,6 +375,11 @@ int gn_stats_num_launches(int x_dtype, int h, int w, int c, int groups) {
   return make_plan(x_dtype, 1, h, w, c, groups).vec ? 1 : 2;
 }
 
+const char* gn_stats_label(int x_dtype, int h, int w, int c, int groups) {
+  const Plan p = make_plan(x_dtype, 1, h, w, c, groups);
+  return p.columns ? "gn_stats_columns" : p.vec ? "gn_stats_vec" : "gn_partial_any";
+}
+
 static int launch_general(const void* x, int x_dtype, int n, int pixels, int c, int groups, int slabs, int slab_pixels, float eps,
                           float* mean, float* rstd, Moments* wsm, hipStream_t s) {
   dim3 grid((unsigned)slabs, (unsigned)groups, (unsigned)n);
@@ -342,6 +399,17 @@ int launch_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int 
                 "gn_stats: workspace of %zu bytes is too small", moments_bytes);
   Moments* wsm = (Moments*)moments;
   const int pixels = h * w;
+  if (p.columns) {
+    auto launch = [&](auto t) {
+      using T = decltype(t);
+      hipLaunchKernelGGL(gn_stats_columns<T>, dim3((unsigned)(c / (kColVecs * Vec16<T>::N) * n)), dim3(kColThreads), 0, s, (const T*)x, pixels, c, groups, eps, mean, rstd);
+    };
+    if (x_dtype == WMDEC_F32) launch(float{});
+    else if (x_dtype == WMDEC_BF16) launch(bf16_t{});
+    else launch(f16_t{});
+    WMDEC_HIP(hipGetLastError());
+    return WMDEC_OK;
+  }
   if (p.vec) {
     dim3 grid((unsigned)p.chunks, (unsigned)n);
     switch (x_dtype) {
