@@ -4,16 +4,17 @@
 //
 // With a handful of conditioning vectors per call (one per frame) the product is a matrix-vector product: every weight
 // is used `batch` times, far below the ridge point, so the bound is the single read of the weights from HBM and the
-// matrix cores have nothing to add.  A wavefront owns four weight rows: a lane reads 16 contiguous bytes of
+// matrix cores have nothing to add.  A wavefront owns two or four weight rows: a lane reads 16 contiguous bytes of
 // each row per step (a wavefront's load is 1 KiB of one row), the activated conditioning vectors sit in LDS as fp32
-// and are read once per step for all four rows, partial sums stay in registers and are reduced over the 64 lanes at
-// the end with a fixed butterfly.
-#include "common.hpp"
+// and are read once per step for all of them, partial sums stay in registers and are reduced over the 64 lanes at
+// the end in a fixed order.  What a call takes beside the weights (22 MB at 1920, 4.3 us) is the launch, the trip to memory and the vectors' activation:
+// asked for behind the weights, stored word by word and read two ways into the same banks they were most of it.  us at 1920 bf16, before / now, by the
+// vectors: one 8.2 / 5.6, two 10.8 / 6.3, four 16.8 / 8.6, eight 28.6 / 14.0; 384: 3.5 / 2.3 to 12.0 / 3.9.
+#include "conv_device.hpp"
 
 namespace wmdec {
 namespace {
 
-constexpr int kRowsPerWave = 4;
 constexpr int kWaves = 4;
 constexpr int kMaxBatch = 16;
 constexpr int kMaxLdsFloats = 16384;   // batch * d_cond fp32 values of the conditioning vectors (64 KiB)
@@ -23,58 +24,71 @@ template <typename T> struct Vec8 { static constexpr int N = 16 / sizeof(T); T v
 
 // B: conditioning vectors the accumulators are sized for (batch rounded up); STEPS: 16-byte steps per lane and row.
 // All RW x STEPS weight vectors of a wavefront are requested before the first is used: the kernel lives on loads in
-// flight, and a loop that waits for one step before it asks for the next would pay the HBM latency STEPS times.
-template <typename TW, int B, int STEPS>
+// flight, and a loop that waits for one step before it asks for the next would pay the HBM latency STEPS times.  Loads return in order, so what is
+// needed before the weights (the first conditioning vectors) and what would be a trip of its own behind them (the bias) are asked for in front of them.
+template <typename TW, int B, int STEPS, int RW>
 __global__ __launch_bounds__(64 * kWaves) void adaln_projection_kernel(const void* __restrict__ c, int c_dtype, const TW* __restrict__ w,
                                                                        const float* __restrict__ bias, float* __restrict__ out,
                                                                        int batch, int d_cond, int rows, int apply_silu) {
-  constexpr int V = 16 / sizeof(TW);   // weights per 16-byte load
-  extern __shared__ __align__(16) float s_a[];   // [B][d_cond]; vectors past `batch` are zero
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row0 = (blockIdx.x * kWaves + wave) * kRowsPerWave;
-  Vec8<TW> wv[kRowsPerWave][STEPS];
+  constexpr int V = 16 / sizeof(TW), NT = 64 * kWaves;   // weights per 16-byte load
+  // [B][d_cond], vectors past `batch` are zero; four values a place.  A lane takes V of them at a time: where that is eight, all first fours come
+  // first and the others behind them, so that the lanes' reads are next to each other.
+  extern __shared__ __align__(16) float s_a[];
+  const int fours = B * d_cond / 4;
+  auto place = [&](int f) -> float4& { return reinterpret_cast<float4*>(s_a)[V == 8 ? (f & 1) * (fours / 2) + f / 2 : f]; };
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int row0 = (blockIdx.x * kWaves + wave) * RW;
+  const int per = c_dtype == WMDEC_F32 ? 4 : 8;            // elements per 16-byte load of the conditioning vectors, four loads in flight per thread
+  const int nvec = batch * d_cond / per, total = B * d_cond / per;
+  uint4 q[4];
+  auto ask = [&](int i0) {
 #pragma unroll
-  for (int r = 0; r < kRowsPerWave; ++r)   // rows and columns past the end re-read valid elements; they are masked below
+    for (int u = 0; u < 4; ++u) q[u] = reinterpret_cast<const uint4*>(c)[min(i0 + u * NT, nvec - 1)];
+  };
+  ask(tid);
+  float bv[RW];
+#pragma unroll
+  for (int r = 0; r < RW; ++r) bv[r] = bias ? bias[min(row0 + r, rows - 1)] : 0.f;
+  __builtin_amdgcn_sched_barrier(0);
+  Vec8<TW> wv[RW][STEPS];
+#pragma unroll
+  for (int r = 0; r < RW; ++r)   // rows and columns past the end re-read valid elements; they are masked below
 #pragma unroll
     for (int st = 0; st < STEPS; ++st)
       wv[r][st] = *reinterpret_cast<const Vec8<TW>*>(w + (size_t)min(row0 + r, rows - 1) * d_cond + min((st * 64 + lane) * V, d_cond - V));
-  // conditioning vectors -> LDS as fp32, activated; 16-byte loads, four in flight per thread (a loop that waits for
-  // each load would cost more than the pass over the weights)
-  {
-    const int per = c_dtype == WMDEC_F32 ? 4 : 8;            // elements per 16-byte load
-    const int nvec = batch * d_cond / per, total = B * d_cond / per;
-    for (int i0 = tid; i0 < total; i0 += 4 * 64 * kWaves) {
-      uint4 q[4];
+  __builtin_amdgcn_sched_barrier(0);
+  // conditioning vectors -> LDS as fp32, activated
+  for (int i0 = tid; i0 < total; i0 += 4 * NT) {
+    if (i0 != tid) ask(i0);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) q[u] = reinterpret_cast<const uint4*>(c)[min(i0 + u * 64 * kWaves, nvec - 1)];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + u * 64 * kWaves;
-        if (i >= total) continue;
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + u * NT;
+      if (i >= total) continue;
+      auto act = [&](float v) -> float {
+        if (i >= nvec) return 0.f;
+        return apply_silu ? silu_f(v) : v;
+      };
+      if (c_dtype == WMDEC_F32) {
+        place(i) = make_float4(act(__uint_as_float(q[u].x)), act(__uint_as_float(q[u].y)), act(__uint_as_float(q[u].z)), act(__uint_as_float(q[u].w)));
+      } else {
+        const uint32_t wd[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
         float t[8];
-        if (c_dtype == WMDEC_F32) {
-          t[0] = __uint_as_float(q[u].x); t[1] = __uint_as_float(q[u].y); t[2] = __uint_as_float(q[u].z); t[3] = __uint_as_float(q[u].w);
-        } else {
-          const uint32_t wd[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (c_dtype == WMDEC_BF16) { t[2 * e] = to_float(bf16_t{(uint16_t)(wd[e] & 0xffffu)}); t[2 * e + 1] = to_float(bf16_t{(uint16_t)(wd[e] >> 16)}); }
-            else { t[2 * e] = to_float(f16_t{(uint16_t)(wd[e] & 0xffffu)}); t[2 * e + 1] = to_float(f16_t{(uint16_t)(wd[e] >> 16)}); }
-          }
+        for (int e = 0; e < 4; ++e) {
+          if (c_dtype == WMDEC_BF16) { t[2 * e] = to_float(bf16_t{(uint16_t)(wd[e] & 0xffffu)}); t[2 * e + 1] = to_float(bf16_t{(uint16_t)(wd[e] >> 16)}); }
+          else { t[2 * e] = to_float(f16_t{(uint16_t)(wd[e] & 0xffffu)}); t[2 * e + 1] = to_float(f16_t{(uint16_t)(wd[e] >> 16)}); }
         }
-        for (int e = 0; e < per; ++e) {
-          float v = i < nvec ? t[e] : 0.f;
-          if (apply_silu) v = silu_f(v);
-          s_a[i * per + e] = v;
-        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          place(2 * i + h) = make_float4(act(t[4 * h]), act(t[4 * h + 1]), act(t[4 * h + 2]), act(t[4 * h + 3]));
       }
     }
   }
   __syncthreads();
   if (row0 >= rows) return;
-  float acc[kRowsPerWave][B];
+  float acc[RW][B];
 #pragma unroll
-  for (int r = 0; r < kRowsPerWave; ++r)
+  for (int r = 0; r < RW; ++r)
 #pragma unroll
     for (int b = 0; b < B; ++b) acc[r][b] = 0.f;
 #pragma unroll
@@ -86,35 +100,43 @@ __global__ __launch_bounds__(64 * kWaves) void adaln_projection_kernel(const voi
         float a[V];
 #pragma unroll
         for (int j = 0; j < V; j += 4) {
-          const float4 q = *reinterpret_cast<const float4*>(s_a + b * d_cond + k0 + j);
-          a[j] = q.x; a[j + 1] = q.y; a[j + 2] = q.z; a[j + 3] = q.w;
+          const float4 t = place((b * d_cond + k0 + j) / 4);
+          a[j] = t.x; a[j + 1] = t.y; a[j + 2] = t.z; a[j + 3] = t.w;
         }
 #pragma unroll
-        for (int r = 0; r < kRowsPerWave; ++r)
+        for (int r = 0; r < RW; ++r)
 #pragma unroll
           for (int j = 0; j < V; ++j) acc[r][b] = fmaf(to_float(wv[r][st].v[j]), a[j], acc[r][b]);
       }
     }
   }
 #pragma unroll
-  for (int r = 0; r < kRowsPerWave; ++r)
+  for (int r = 0; r < RW; ++r)
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-      float v = acc[r][b];
-      for (int mask = 32; mask > 0; mask >>= 1) v += __shfl_xor(v, mask);
-      if (lane == 0 && row0 + r < rows && b < batch) out[(size_t)b * rows + row0 + r] = v + (bias ? bias[row0 + r] : 0.f);
+      const float v = swap_sum<32>(swap_sum<16>(lane_group_sum<16>(acc[r][b])));
+      if (lane == 0 && row0 + r < rows && b < batch) out[(size_t)b * rows + row0 + r] = v + bv[r];
     }
 }
 
-template <typename TW, int B, int STEPS>
-int launch_k(const void* c, int c_dtype, const void* w, const float* bias, float* out, int batch, int d_cond, int rows, int silu, hipStream_t s) {
-  const dim3 grid((unsigned)((rows + kWaves * kRowsPerWave - 1) / (kWaves * kRowsPerWave)));
+template <typename TW, int B, int STEPS, int RW>
+int launch_rows(const void* c, int c_dtype, const void* w, const float* bias, float* out, int batch, int d_cond, int rows, int silu, hipStream_t s) {
+  const dim3 grid((unsigned)((rows + kWaves * RW - 1) / (kWaves * RW)));
   const size_t smem = (size_t)B * d_cond * sizeof(float);
-  auto kern = adaln_projection_kernel<TW, B, STEPS>;
+  auto kern = adaln_projection_kernel<TW, B, STEPS, RW>;
   if (smem > 48 * 1024) WMDEC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
   hipLaunchKernelGGL(kern, grid, dim3(64 * kWaves), smem, s, c, c_dtype, (const TW*)w, bias, out, batch, d_cond, rows, silu);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
+}
+
+template <typename TW, int B, int STEPS>
+int launch_k(const void* c, int c_dtype, const void* w, const float* bias, float* out, int batch, int d_cond, int rows, int silu, hipStream_t s) {
+  // Rows of a wavefront: two, so that the rows of most layers are dealt to the compute units more evenly, as long as three workgroups' vectors fit a compute
+  // unit's LDS; beyond that four, which activate the vectors half as often.  us, four / two rows: bf16 1920 one vector 6.39 / 5.61, four 9.70 / 8.55, eight
+  // 13.95 / 16.5; 1472 eight 11.3 / 10.4; 384 one 2.47 / 2.28; f32 1920 one 10.75 / 9.28, eight 18.4 / 19.4.
+  if ((long)B * d_cond <= 12288) return launch_rows<TW, B, STEPS, 2>(c, c_dtype, w, bias, out, batch, d_cond, rows, silu, s);
+  return launch_rows<TW, B, STEPS, 4>(c, c_dtype, w, bias, out, batch, d_cond, rows, silu, s);
 }
 
 template <typename TW, int B>
