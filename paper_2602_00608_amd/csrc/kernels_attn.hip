@@ -79,10 +79,15 @@ __global__ __launch_bounds__(QNT, 2) void attn_qkv_kernel(QkvParams p) {
   constexpr int STEP = 3 * D / 32 * 1024;                 // bytes of the weights of a contraction step
   const int wcol = (part * (D / 32) + wave * 2) * 1024, lane16 = lane * 16;
   u32x4 wq[QRING][2];
+  // The first weights, 112 KiB of a workgroup, behind the input and the moments, which are needed before them: loads return in order.
+  auto first_weights = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int s = 0; s < QRING - 1; ++s)
+    for (int s = 0; s < QRING - 1; ++s)
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) wq[s][ni] = load_fragment(wrsrc, lane16, wcol + s * STEP + ni * 1024);
+      for (int ni = 0; ni < 2; ++ni) wq[s][ni] = load_fragment(wrsrc, lane16, wcol + s * STEP + ni * 1024);
+    __builtin_amdgcn_sched_barrier(0);
+  };
 
   // ---- scale/shift table
   {
@@ -93,6 +98,7 @@ __global__ __launch_bounds__(QNT, 2) void attn_qkv_kernel(QkvParams p) {
     } else {
       for (int g = tid; g < p.groups; g += QNT) s_stat[g] = make_float2(p.mean[n * p.groups + g], p.rstd[n * p.groups + g]);
     }
+    first_weights();
     __syncthreads();
     const float2 st = s_stat[tid / (D / p.groups)];
     const float a = ga * st.y;
@@ -143,12 +149,15 @@ __global__ __launch_bounds__(QNT, 2) void attn_qkv_kernel(QkvParams p) {
   T* dst = reinterpret_cast<T*>(p.frag) + ((size_t)(part * p.n + n) * nkb + tile * 2) * TILE + lane * 8;
   const float* bias = p.bias + part * D + wave * 64;
   if (part < 2) {
+    f32x4 bq[2][4];   // (requested in front of the contraction: behind it they would be a trip of their own)
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) bq[ni][g] = f32x4{bias[ni * 32 + 8 * g + 4 * lk], bias[ni * 32 + 8 * g + 4 * lk + 1], bias[ni * 32 + 8 * g + 4 * lk + 2], bias[ni * 32 + 8 * g + 4 * lk + 3]};
     contract(std::false_type{});
 #pragma unroll
     for (int ni = 0; ni < 2; ++ni) {
-      f32x4 b[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) b[g] = f32x4{bias[ni * 32 + 8 * g + 4 * lk], bias[ni * 32 + 8 * g + 4 * lk + 1], bias[ni * 32 + 8 * g + 4 * lk + 2], bias[ni * 32 + 8 * g + 4 * lk + 3]};
+      const f32x4 (&b)[4] = bq[ni];
 #pragma unroll
       for (int mi = 0; mi < 2; ++mi) {
         if (tile * 2 + mi >= nkb) continue;
@@ -161,10 +170,11 @@ __global__ __launch_bounds__(QNT, 2) void attn_qkv_kernel(QkvParams p) {
       }
     }
   } else {
+    const float bv[2] = {bias[l32], bias[32 + l32]};
     contract(std::true_type{});
 #pragma unroll
     for (int ni = 0; ni < 2; ++ni) {
-      const float b = bias[ni * 32 + l32];
+      const float b = bv[ni];
 #pragma unroll
       for (int mi = 0; mi < 2; ++mi) {
         if (tile * 2 + mi >= nkb) continue;
