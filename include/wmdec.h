@@ -59,10 +59,10 @@ const char* wmdec_status_string(int status);
  *   pixels;  mean[n*groups+g] = average,  rstd[...] = 1/sqrt(biased variance + eps).
  * x: [n,h,w,c] NHWC of x_dtype.  mean, rstd: fp32 [n*groups] outputs.
  * workspace: at least wmdec_gn_stats_workspace_bytes(...) bytes of device
- * memory, ZERO-FILLED once before the first call that uses it: its head holds
- * one ticket counter per sample, which every call leaves at zero again, so
- * the buffer can be reused (also with other shapes of the same n) without
- * clearing.  The rest is scratch (contents undefined afterwards).
+ * memory: a head of four bytes a sample that no call touches (earlier versions
+ * kept counters there, which is why callers clear it), and scratch (contents
+ * undefined afterwards), so the buffer can be reused without clearing.
+ * One or two kernels are enqueued.
  * Calls sharing a workspace must be ordered on one stream.
  * Errors: c % groups != 0 -> WMDEC_ERR_SHAPE. */
 size_t wmdec_gn_stats_workspace_bytes(int n, int h, int w, int c, int groups);
@@ -71,14 +71,13 @@ int wmdec_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int g
 
 /* The same statistics for callers that cannot allocate device memory or hand
  * over a workspace (code under HIP-graph capture, tight serving loops,
- * harnesses that forbid hipMalloc): the partial moments and the ticket
- * counters live in a file-scope device array of the library, 1 MiB + 256
+ * harnesses that forbid hipMalloc): the partial moments
+ * live in a file-scope device array of the library, 1 MiB + 256
  * bytes per GPU, held until the process ends.  The call allocates nothing and
- * enqueues kernels only (a small fill kernel puts the counters back to zero,
- * then the statistics kernels of wmdec_gn_stats run on that array), so mean
+ * enqueues kernels only (those of wmdec_gn_stats, on that array), so mean
  * and rstd equal wmdec_gn_stats's bit for bit.
  * Limits: n <= 64 and n * groups * slabs * 12 bytes <= 1 MiB, where slabs <=
- * 256 for shapes of the single-launch layout (16-bit: c % 8 == 0, c/8 divides
+ * 256 for shapes of the vector layout (16-bit: c % 8 == 0, c/8 divides
  * 1024, channels per group a power of two <= 64) and <= 2048 otherwise; e.g.
  * every activation of the 720x480 decoder up to batch 10.  Beyond the limit:
  * WMDEC_ERR_WORKSPACE and nothing is launched.

@@ -503,7 +503,7 @@ int wmdec_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int g
   WMDEC_REQUIRE(aligned16(x) && aligned16(workspace), WMDEC_ERR_INVALID_ARG, "gn_stats: pointers must be 16-byte aligned");
   const size_t head = gn_stats_ticket_bytes(n);
   WMDEC_REQUIRE(workspace && workspace_bytes > head, WMDEC_ERR_WORKSPACE, "gn_stats: workspace of %zu bytes is too small", workspace_bytes);
-  return launch_gn_stats(x, x_dtype, n, h, w, c, groups, eps, mean, rstd, (unsigned*)workspace, (char*)workspace + head,
+  return launch_gn_stats(x, x_dtype, n, h, w, c, groups, eps, mean, rstd, (char*)workspace + head,
                          workspace_bytes - head, (hipStream_t)stream);
 }
 
@@ -915,7 +915,7 @@ static int launch_step(wmdec_decoder* dec, const WsLayout& L, const Step& st, co
           rc = launch_gn_finalize(ws + L.stats_ws, batch * c.groups, (*emitted_slots), c.eps, mean, rstd, s);
         else
           rc = launch_gn_stats(buf(st.src), c.act_dtype, batch, st.h, st.w, st.cin, c.groups, c.eps, mean, rstd,
-                               (unsigned*)(ws + L.tickets), ws + L.stats_ws, L.stats_ws_bytes, s);
+                               ws + L.stats_ws, L.stats_ws_bytes, s);
         break;
       case Step::CONV: {
         ConvArgs a = step_shape_args(*dec, st, batch);

@@ -155,13 +155,13 @@ int launch_conv(const ConvArgs& a, hipStream_t s);
 const char* conv_kernel_label(const ConvArgs& a);
 
 // kernels_gn.hip
-// ticket: one zero-initialised counter per sample (gn_stats_ticket_bytes(n) bytes), left zero by every launch;
+// gn_stats_ticket_bytes: the head of a caller's workspace, which no kernel uses any more;
 // moments: scratch of at least gn_stats_moments_bytes(n, groups) bytes
 size_t gn_stats_ticket_bytes(int n);
 size_t gn_stats_moments_bytes(int n, int groups);
-int gn_stats_num_launches(int x_dtype, int h, int w, int c, int groups);   // 1: single-launch kernel, 2: partial + merge
+int gn_stats_num_launches(int x_dtype, int h, int w, int c, int groups);   // 2: partial + merge
 int launch_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int groups, float eps,
-                    float* mean, float* rstd, unsigned* ticket, void* moments, size_t moments_bytes, hipStream_t s);
+                    float* mean, float* rstd, void* moments, size_t moments_bytes, hipStream_t s);
 
 // same statistics with the library's built-in scratch (a file-scope device array) instead of a caller workspace
 int launch_gn_stats_static(const void* x, int x_dtype, int n, int h, int w, int c, int groups, float eps,

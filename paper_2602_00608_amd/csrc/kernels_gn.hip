@@ -6,26 +6,13 @@
 // shifted sums in fp32 (so that E[d^2]-E[d]^2 never cancels) and produces one
 // (count, mean, M2) triple per group.  Triples are merged with the pairwise
 // update of Chan et al., or many at a time about their common mean, in a fixed
-// order, so the result does not depend on scheduling.  Channel counts that fit the vector layout take the single-launch
-// kernel gn_stats_vec, whose last workgroup per sample does the merge; everything
-// else takes gn_partial_any followed by gn_finalize, which also merges the
-// moments a convolution emitted from its epilogue.
-//
-// Hardware assumption of the single-launch kernel (gfx950 only, checked below): its cross-workgroup hand-over uses
-// no release / acquire fence, because an agent-scope fence on this chip writes back or invalidates the whole L2
-// of the XCD (microseconds per wavefront).  Instead every shared word is itself accessed with agent-scope atomic
-// stores and loads, which gfx950 executes as write-through stores / L2-bypassing loads of memory that is coherent
-// across the XCDs; the publishing wavefront waits until the memory system has acknowledged its stores (vmcnt = 0)
-// before it takes the ticket, and only the workgroup that draws the last ticket reads.  Under the language memory
-// model the relaxed accesses alone would not order the stores before the ticket; the wait does, on this hardware.
+// order, so the result does not depend on scheduling.  Channel counts that fit the vector layout take gn_stats_columns (small
+// images) or gn_stats_vec; everything else takes gn_partial_any.  Where several workgroups share a sample, gn_finalize merges their triples, as
+// it does the moments a convolution emitted from its epilogue.
 #include <mutex>
 #include <type_traits>
 
 #include "conv_moments.hpp"
-
-#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
-#error "kernels_gn.hip relies on gfx950 memory behaviour (see the note on the single-launch kernel)"
-#endif
 
 namespace wmdec {
 namespace {
@@ -38,12 +25,14 @@ template <> struct alignas(16) Vec16<bf16_t> { static constexpr int N = 8; bf16_
 template <> struct alignas(16) Vec16<f16_t> { static constexpr int N = 8; f16_t v[8]; };
 
 // Fast path: c % V == 0, vp = c / V divides 1024, channels per group a power of two <= 64.
-// grid = (chunks, n), 1024 threads.  ws: [n][groups][chunks] Moments.  One launch does everything: a workgroup
+// grid = (chunks, n), 1024 threads.  ws: [n][groups][chunks] Moments.  A workgroup
 // streams its slab (8 loads of 16 bytes in flight per thread, the ragged end as one masked batch), sums
 // x - shift and its square per thread (shift = the thread's first pixel, so that an outlier costs only the sums of
 // the thread that starts with it), merges the (mean, M2) of a channel's threads in a fixed order through LDS, the
-// channels of a group in its lanes, and writes one triple per group.  The workgroup of a sample that finishes last (one wrapping ticket counter per
-// sample, which returns to zero by itself) merges the sample's triples in a fixed order into mean / rstd.
+// channels of a group in its lanes, and writes one triple per group, which gn_finalize merges (mean / rstd at once where a slab is the sample).  A launch of its own
+// for that takes 2.3 us; with the merge in the sample's last workgroup (triples written through to memory, a ticket, triples read back: three
+// memory round trips behind each other) all shapes took longer.  us, that way / this way: f16 512 channels 60x90 11.1 / 9.0, 120x180 15.5 / 11.0, 256 channels 240x360 18.6 / 14.0,
+// 128 channels 480x720 23.1 / 19.9, four of them 71.5 / 65.6; f32 512 channels 60x90 11.6 / 8.1, 120x180 17.3 / 12.5, 128 channels 480x720 39.8 / 37.6.
 constexpr int kVecThreads = 1024;
 constexpr int kVecMaxChunks = 256;
 constexpr int kVecMaxGroups = 256;
@@ -99,14 +88,12 @@ template <typename T> constexpr int vec_waves() { return std::is_same<T, bf16_t>
 
 template <typename T>
 __global__ __launch_bounds__(kVecThreads, vec_waves<T>()) void gn_stats_vec(const T* __restrict__ x, int pixels, int c, int groups,
-                                                            int chunk_pixels, Moments* ws, unsigned* ticket, float eps,
+                                                            int chunk_pixels, Moments* ws, float eps,
                                                             float* __restrict__ mean, float* __restrict__ rstd) {
   constexpr int V = Vec16<T>::N;
   constexpr int U = 8;
   __shared__ float2 s_e[kVecThreads * V];   // (mean, M2) per (pixel lane, channel)
   __shared__ Moments s_p[kVecThreads];      // triples per (part of the pixel lanes, channel)
-  __shared__ Moments s_g[kVecMaxGroups];    // the slab's moments per group
-  __shared__ unsigned s_last;
   const int tid = threadIdx.x;
   const int vp = c / V;           // vectors per pixel
   const int cv = tid % vp;        // this thread's channel vector
@@ -157,49 +144,7 @@ __global__ __launch_bounds__(kVecThreads, vec_waves<T>()) void gn_stats_vec(cons
       if (chunks == 1) {   // a slab is the sample: nothing to hand over
         mean[n * groups + ch / cpg] = m.mean;
         rstd[n * groups + ch / cpg] = 1.0f / sqrtf(m.m2 / m.n + eps);
-      } else s_g[ch / cpg] = m;
-    }
-  }
-  if (chunks == 1) return;
-  __syncthreads();
-
-  // One wavefront publishes the slab's triples and takes the sample's ticket.  No fences (a fence walks the whole
-  // L2 and costs microseconds per workgroup): the triples are written with device-scope stores, which go through
-  // to memory, the wavefront waits for them to complete before it takes the ticket, and the sample's last
-  // workgroup reads all triples with device-scope loads, which do not hit stale lines of its own L2.
-  if (tid < 64) {
-    for (int g = tid; g < groups; g += 64) store_device(ws + ((size_t)n * groups + g) * chunks + chunk, s_g[g]);
-    wait_stores();
-    if (tid == 0) s_last = atomicInc(ticket + n, chunks - 1) == (unsigned)(chunks - 1);
-  }
-  __syncthreads();
-  if (!s_last) return;
-  // half a wavefront per group, 8 slots per lane: the mean, then the differences to it and their squares, in a fixed order
-  const int sub = tid & 31, half = tid >> 5;
-  for (int g = half; g < groups; g += kVecThreads / 32) {
-    const Moments* row = ws + ((size_t)n * groups + g) * chunks;
-    Moments t[kVecMaxChunks / 32];
-    const float first = load_device(row).mean;
-#pragma unroll
-    for (int k = 0; k < kVecMaxChunks / 32; ++k) {
-      const int i = sub + 32 * k;
-      t[k] = load_device(row + min(i, chunks - 1));
-      if (i >= chunks) { t[k].n = 0.f; t[k].m2 = 0.f; }
-    }
-    float cn = 0.f, sd = 0.f, sq = 0.f;
-#pragma unroll
-    for (int k = 0; k < kVecMaxChunks / 32; ++k) { cn += t[k].n; sd = fmaf(t[k].n, t[k].mean - first, sd); }
-    cn = lanes_sum<16>(cn); sd = lanes_sum<16>(sd);
-    cn += __shfl_xor(cn, 16); sd += __shfl_xor(sd, 16);
-    const float inv = __builtin_amdgcn_rcpf(cn), m = fmaf(sd, inv, first);
-    sd = 0.f;
-#pragma unroll
-    for (int k = 0; k < kVecMaxChunks / 32; ++k) { const float d = t[k].mean - m, nd = t[k].n * d; sd += nd; sq += fmaf(nd, d, t[k].m2); }
-    sd = lanes_sum<16>(sd); sq = lanes_sum<16>(sq);
-    sd += __shfl_xor(sd, 16); sq += __shfl_xor(sq, 16);
-    if (sub == 0) {
-      mean[n * groups + g] = fmaf(sd, inv, m);    // (what the roundings of m left)
-      rstd[n * groups + g] = 1.0f / sqrtf(sq / cn + eps);
+      } else ws[((size_t)n * groups + ch / cpg) * chunks + chunk] = m;
     }
   }
 }
@@ -207,8 +152,7 @@ __global__ __launch_bounds__(kVecThreads, vec_waves<T>()) void gn_stats_vec(cons
 // Columns: a workgroup takes 64 bytes of every pixel of a sample, whole groups, and needs nothing from the others.  A thread sums the channels of
 // its vector shifted by its first pixel, the lanes of a wavefront are merged as in the convolutions' epilogues, the 16 wavefronts' triples of a
 // group by 16 lanes.  Few compute units stream it, each bound by latency and conversions (four vectors in flight a thread: eight or sixteen are slower, as are 32 bytes
-// a pixel), so it is for images of few pixels, where gn_stats_vec waits longer for its hand-over: publish, ticket and read are three memory round trips one
-// after the other.
+// a pixel), so it is for images of few pixels, where the launch that merges the triples of gn_stats_vec takes longer.
 constexpr int kColThreads = 1024, kColVecs = 4;
 template <typename T>
 __global__ __launch_bounds__(kColThreads) void gn_stats_columns(const T* __restrict__ x, int pixels, int c, int groups, float eps, float* __restrict__ mean, float* __restrict__ rstd) {
@@ -277,39 +221,76 @@ __global__ __launch_bounds__(256) void gn_partial_any(const T* __restrict__ x, i
   if (tid == 0) ws[((size_t)n * groups + g) * chunks + chunk] = s_m[0];
 }
 
-// grid = n*groups workgroups of 1024 threads: thread t merges slots t, t+1024, ... in order (loaded four at a
-// time: a row of up to 4096 slots costs one memory round trip), then a fixed merge tree over each wavefront, then
-// over the 16 wavefronts.
-constexpr int kFinThreads = 1024;
+// grid = n*groups workgroups of as many wavefronts as hold the row's triples, kFinLoads in a lane (up to 16; longer rows go round).  A wavefront
+// takes the mean of its triples first, then the differences to it and their squares from the same registers; up to 256 triples that is the
+// result, otherwise 16 lanes merge the wavefronts' triples the same way.  Bound by the launch, one trip to memory and the chain behind it: with
+// pairwise merges, a reciprocal in each, and always 16 wavefronts, us of calls with one merge, before / now: ResBlock 256 -> 256 channels at 120x180 76.4 / 74.7,
+// 128 -> 128 at 480x720 209.8 / 207.3, 256 -> 128 at 61x47 (two) 28.9 / 28.1.
+constexpr int kFinThreads = 1024, kFinLoads = 4;
+__device__ __forceinline__ float wave_sum(float v) { return swap_sum<32>(swap_sum<16>(lane_group_sum<16>(v))); }
 __global__ __launch_bounds__(kFinThreads) void gn_finalize(const Moments* __restrict__ ws, int chunks, float eps,
                                                            float* __restrict__ mean, float* __restrict__ rstd) {
-  __shared__ Moments s_w[kFinThreads / 64];
-  const int ng = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  constexpr int WAVES = kFinThreads / 64;
+  constexpr float kUnit = 0x1p-20f;   // pixels are counted in it where they weigh a mean: the weighted sum of large means stays in range
+  __shared__ Moments s_w[WAVES];
+  const int ng = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   const Moments* row = ws + (size_t)ng * chunks;
-  Moments m{0.f, 0.f, 0.f};
-  for (int i0 = tid; i0 < chunks; i0 += kFinThreads * 4) {
-    Moments t[4];
+  // (an infinite mean stays one: what would be subtracted from it is left out)
+  auto finite = [](float v) { return fabsf(v) < __builtin_inff() ? v : 0.f; };
+  auto step = [&](const Moments& t, float about, float& weight, float& sum, float& squares) {   // an empty triple's mean has no meaning
+    const float w = t.n * kUnit, d = t.n > 0.f ? t.mean - about : 0.f;
+    weight += w; sum = fmaf(w, d, sum); squares += fmaf(t.n * d, d, t.n > 0.f ? t.m2 : 0.f);
+  };
+  Moments t[kFinLoads];
+  auto fetch = [&](int i0) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + kFinThreads * k;
-      t[k] = row[min(i, chunks - 1)];
-      if (i >= chunks) t[k].n = 0.f;
-    }
+    for (int k = 0; k < kFinLoads; ++k) t[k] = row[min(i0 + k * nt, chunks - 1)];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) m = merge(m, t[k]);
+    for (int k = 0; k < kFinLoads; ++k)
+      if (i0 + k * nt >= chunks) t[k].n = 0.f;
+  };
+  float first = row[0].mean, w = 0.f, s = 0.f, q = 0.f;
+  fetch(tid);
+  first = finite(first);
+#pragma unroll
+  for (int k = 0; k < kFinLoads; ++k) step(t[k], first, w, s, q);
+  w = wave_sum(w);
+  const float mid = first + wave_sum(s) * (w > 0.f ? __builtin_amdgcn_rcpf(w) : 0.f), about = finite(mid);   // 1 ulp: what the roundings leave follows
+  w = 0.f; s = 0.f; q = 0.f;
+#pragma unroll
+  for (int k = 0; k < kFinLoads; ++k) step(t[k], about, w, s, q);
+  for (int i0 = tid + kFinLoads * nt; i0 - tid < chunks; i0 += kFinLoads * nt) {
+    fetch(i0);
+#pragma unroll
+    for (int k = 0; k < kFinLoads; ++k) step(t[k], about, w, s, q);
   }
-  m = merge_to_first(m, lane, 64);   // fixed order
-  if (lane == 0) s_w[tid >> 6] = m;
+  auto close = [&](float all_w, float all_s, float all_q) -> Moments {
+    const float ds = all_s * (all_w > 0.f ? __builtin_amdgcn_rcpf(all_w) : 0.f), m2 = all_q - all_s * (1.f / kUnit) * ds;
+    return Moments{all_w * (1.f / kUnit), about + ds, m2 < 0.f ? 0.f : m2};   // (NaN stays NaN)
+  };
+  auto write = [&](const Moments& m) { mean[ng] = m.mean; rstd[ng] = inverse_deviation(m.m2, m.n, eps); };
+  const Moments own = close(wave_sum(w), wave_sum(s), wave_sum(q));
+  if (nt == 64) {
+    if (tid == 0) write(own);
+    return;
+  }
+  if ((tid & 63) == 0) s_w[tid >> 6] = own;
   __syncthreads();
-  if (tid < 64) {   // the 16 wavefront results: four merge levels inside one row of lanes instead of a chain of 15
-    static_assert(kFinThreads / 64 == 16, "one row of 16 lanes");
-    m = tid < kFinThreads / 64 ? s_w[tid] : Moments{0.f, 0.f, 0.f};
-    m = merge_to_first(m, lane, 16);
-    if (tid == 0) {
-      mean[ng] = m.mean;
-      rstd[ng] = 1.0f / sqrtf(m.m2 / m.n + eps);
-    }
-  }
+  if (tid >= WAVES) return;
+  static_assert(WAVES == 16, "one row of 16 lanes");
+  Moments m = s_w[min(tid, nt / 64 - 1)];
+  if (tid >= nt / 64) m.n = 0.f;
+  const float head = finite(s_w[0].mean);
+  w = 0.f; s = 0.f; q = 0.f;
+  step(m, head, w, s, q);
+  w = lane_group_sum<16>(w);
+  const float at = head + lane_group_sum<16>(s) * __builtin_amdgcn_rcpf(w);
+  s = 0.f; q = 0.f;
+  float again = 0.f;
+  step(m, finite(at), again, s, q);
+  s = lane_group_sum<16>(s); q = lane_group_sum<16>(q);
+  const float ds = s * __builtin_amdgcn_rcpf(w), m2 = q - s * (1.f / kUnit) * ds;
+  if (tid == 0) write(Moments{w * (1.f / kUnit), finite(at) + ds, m2 < 0.f ? 0.f : m2});
 }
 
 int pick_chunks(int pixels, int c, int V, bool vec) {
@@ -318,8 +299,7 @@ int pick_chunks(int pixels, int c, int V, bool vec) {
   // Never a function of the batch size: a sample's result must not depend on its neighbours.
   const int ppi = vec ? kVecThreads / (c / V) : 1;
   const int min_chunk = vec ? 4 * ppi : 1024;
-  // A tensor of at most 16 sweeps (256 KiB a sample) stays with one workgroup: streaming it alone takes less than the
-  // hand-over's three memory round trips.
+  // A tensor of at most 16 sweeps (256 KiB a sample) stays with one workgroup: streaming it alone takes less than a launch that merges.
   if (vec && pixels <= 16 * ppi) return 1;
   int chunks = (pixels + min_chunk - 1) / min_chunk;
   const int cap = vec ? kVecMaxChunks : 2048;
@@ -328,9 +308,9 @@ int pick_chunks(int pixels, int c, int V, bool vec) {
   return chunks;
 }
 
-// Images of up to so many pixels take gn_stats_columns.  us, gn_stats_vec / columns, inputs from beyond the L2s: f16 512 channels 17x23 9.7 / 4.9, 32x32 10.2 / 5.0,
-// four of them 10.5 / 5.6, 45x60 10.8 / 8.7; 256 channels two 61x47 10.8 / 8.0; 128 channels 64x64 10.1 / 8.6; f32 64 channels 32x32 (one slab) 6.1 / 4.3, 64x64
-// 8.9 / 7.3; past the line 60x90 of 512 11.5 / 12.7, of 128 10.3 / 11.4, 80x100 10.4 / 14.3.  (Not a function of the batch: a sample's result must not depend on its
+// Images of up to so many pixels take gn_stats_columns.  us, gn_stats_vec with its merge / columns, inputs from beyond the L2s: f16 256 channels two 61x47 8.7 / 8.0, 128 channels 68x68
+// 8.7 / 8.6; past the line 60x90 of 512 9.0 / 12.7, 80x100 9.4 / 14.3; far below it 512 channels 17x23 take 4.9 in columns, 32x32 5.0, 45x60 8.7, f32 64 channels 32x32 4.3,
+// where a merging launch alone is 2.3.  (Not a function of the batch: a sample's result must not depend on its
 // neighbours.)
 constexpr int kColPixels = 4096;
 
@@ -358,12 +338,13 @@ Plan make_plan(int x_dtype, int n, int h, int w, int c, int groups) {
 }  // namespace
 
 int launch_gn_finalize(const void* ws, int n_groups, int slots, float eps, float* mean, float* rstd, hipStream_t s) {
-  hipLaunchKernelGGL(gn_finalize, dim3((unsigned)n_groups), dim3(kFinThreads), 0, s, (const Moments*)ws, slots, eps, mean, rstd);
+  const int waves = min(kFinThreads / 64, (slots + 64 * kFinLoads - 1) / (64 * kFinLoads));
+  hipLaunchKernelGGL(gn_finalize, dim3((unsigned)n_groups), dim3((unsigned)(64 * waves)), 0, s, (const Moments*)ws, slots, eps, mean, rstd);
   WMDEC_HIP(hipGetLastError());
   return WMDEC_OK;
 }
 
-// one ticket counter per sample for the single-launch path
+// head of a caller's workspace, four bytes a sample: nothing is kept there any more, its size is what callers have passed
 size_t gn_stats_ticket_bytes(int n) { return ((size_t)n * sizeof(unsigned) + 255) / 256 * 256; }
 
 size_t gn_stats_moments_bytes(int n, int groups) {
@@ -372,7 +353,8 @@ size_t gn_stats_moments_bytes(int n, int groups) {
 }
 
 int gn_stats_num_launches(int x_dtype, int h, int w, int c, int groups) {
-  return make_plan(x_dtype, 1, h, w, c, groups).vec ? 1 : 2;
+  const Plan p = make_plan(x_dtype, 1, h, w, c, groups);
+  return p.columns || (p.vec && p.chunks == 1) ? 1 : 2;
 }
 
 static int launch_general(const void* x, int x_dtype, int n, int pixels, int c, int groups, int slabs, int slab_pixels, float eps,
@@ -388,9 +370,9 @@ static int launch_general(const void* x, int x_dtype, int n, int pixels, int c, 
 }
 
 int launch_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int groups, float eps,
-                    float* mean, float* rstd, unsigned* ticket, void* moments, size_t moments_bytes, hipStream_t s) {
+                    float* mean, float* rstd, void* moments, size_t moments_bytes, hipStream_t s) {
   const Plan p = make_plan(x_dtype, n, h, w, c, groups);
-  WMDEC_REQUIRE(ticket && moments && moments_bytes >= (size_t)n * groups * p.chunks * sizeof(Moments), WMDEC_ERR_WORKSPACE,
+  WMDEC_REQUIRE(moments && moments_bytes >= (size_t)n * groups * p.chunks * sizeof(Moments), WMDEC_ERR_WORKSPACE,
                 "gn_stats: workspace of %zu bytes is too small", moments_bytes);
   Moments* wsm = (Moments*)moments;
   const int pixels = h * w;
@@ -408,11 +390,12 @@ int launch_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int 
   if (p.vec) {
     dim3 grid((unsigned)p.chunks, (unsigned)n);
     switch (x_dtype) {
-      case WMDEC_F32: hipLaunchKernelGGL(gn_stats_vec<float>, grid, dim3(kVecThreads), 0, s, (const float*)x, pixels, c, groups, p.chunk_pixels, wsm, ticket, eps, mean, rstd); break;
-      case WMDEC_BF16: hipLaunchKernelGGL(gn_stats_vec<bf16_t>, grid, dim3(kVecThreads), 0, s, (const bf16_t*)x, pixels, c, groups, p.chunk_pixels, wsm, ticket, eps, mean, rstd); break;
-      default: hipLaunchKernelGGL(gn_stats_vec<f16_t>, grid, dim3(kVecThreads), 0, s, (const f16_t*)x, pixels, c, groups, p.chunk_pixels, wsm, ticket, eps, mean, rstd); break;
+      case WMDEC_F32: hipLaunchKernelGGL(gn_stats_vec<float>, grid, dim3(kVecThreads), 0, s, (const float*)x, pixels, c, groups, p.chunk_pixels, wsm, eps, mean, rstd); break;
+      case WMDEC_BF16: hipLaunchKernelGGL(gn_stats_vec<bf16_t>, grid, dim3(kVecThreads), 0, s, (const bf16_t*)x, pixels, c, groups, p.chunk_pixels, wsm, eps, mean, rstd); break;
+      default: hipLaunchKernelGGL(gn_stats_vec<f16_t>, grid, dim3(kVecThreads), 0, s, (const f16_t*)x, pixels, c, groups, p.chunk_pixels, wsm, eps, mean, rstd); break;
     }
     WMDEC_HIP(hipGetLastError());
+    if (p.chunks > 1) return launch_gn_finalize(wsm, n * groups, p.chunks, eps, mean, rstd, s);
     return WMDEC_OK;
   }
   return launch_general(x, x_dtype, n, pixels, c, groups, p.chunks, p.chunk_pixels, eps, mean, rstd, wsm, s);
@@ -429,7 +412,7 @@ int launch_gn_stats_small_ws(const void* x, int x_dtype, int n, int h, int w, in
 }
 
 // ---- the variant for callers that cannot allocate: the workspace is a file-scope device array
-constexpr size_t kStaticTicketBytes = 256;                 // 64 ticket counters
+constexpr size_t kStaticTicketBytes = 256;                 // a head of four bytes a sample, as in a caller's workspace: at most 64 of them
 constexpr size_t kStaticMomentsBytes = (size_t)1 << 20;    // 87381 moment triples
 static __device__ __align__(256) unsigned char scratch[kStaticTicketBytes + kStaticMomentsBytes];
 
@@ -459,12 +442,8 @@ int launch_gn_stats_static(const void* x, int x_dtype, int n, int h, int w, int 
     }
     ptr = dev_scratch[dev];
   }
-  // the array keeps what the last call left: the counters are put back to zero by a fill kernel (not a memset
-  // node: the call may be captured in a graph); the moment slots are all written before they are read
-  const int rc = launch_zero_u32(ptr, (int)(kStaticTicketBytes / sizeof(unsigned)), s);
-  if (rc != WMDEC_OK) return rc;
-  return launch_gn_stats(x, x_dtype, n, h, w, c, groups, eps, mean, rstd, (unsigned*)ptr, ptr + kStaticTicketBytes,
-                         kStaticMomentsBytes, s);
+  // (the array keeps what the last call left; the moment slots are all written before they are read)
+  return launch_gn_stats(x, x_dtype, n, h, w, c, groups, eps, mean, rstd, ptr + kStaticTicketBytes, kStaticMomentsBytes, s);
 }
 
 }  // namespace wmdec
