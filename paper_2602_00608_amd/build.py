@@ -18,11 +18,15 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libwmdec.so")
 BINDING = os.path.join(HERE, "_binding.so")
 
-SOURCES = ["api.cpp", "kernels_gn.hip", "kernels_conv_direct.hip", "kernels_conv_mfma.hip", "kernels_conv_rows.hip", "kernels_conv_ksplit.hip", "kernels_conv_up.hip",
+SOURCES = ["api.cpp", "kernels_gn.hip", "kernels_conv_direct.hip", "kernels_conv_mfma.hip", "kernels_conv_rows.hip", "kernels_conv_rows_bf16.hip", "kernels_conv_ksplit.hip", "kernels_conv_up.hip",
            "kernels_conv_taps.hip", "kernels_misc.hip", "kernels_attn.hip", "kernels_adaln.hip"]
 
 # what asm_check looks for beside the stores of every source: kernels with matrix instructions in inline assembly, kernels that must not spill
-CHECKED = {"kernels_attn.hip": {"scores": "flash_attn_kernel"}, "kernels_conv_rows.hip": {"spills": "conv_mfma_kernel"}}
+CHECKED = {"kernels_attn.hip": {"scores": "flash_attn_kernel"}, "kernels_conv_rows.hip": {"spills": "conv_mfma_kernel"},
+           "kernels_conv_rows_bf16.hip": {"spills": "conv_mfma_kernel"}}
+
+# sources that include another one
+INCLUDES = {"kernels_conv_rows_bf16.hip": "kernels_conv_rows.hip"}
 
 FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -49,7 +53,7 @@ def device_assembly(src):
 def _compile(src, force):
     obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
     path = os.path.join(CSRC, src)
-    if not force and os.path.exists(obj) and os.path.getmtime(obj) >= max(os.path.getmtime(path), _headers_mtime()):
+    if not force and os.path.exists(obj) and os.path.getmtime(obj) >= max(os.path.getmtime(path), os.path.getmtime(os.path.join(CSRC, INCLUDES.get(src, src))), _headers_mtime()):
         return obj
     with tempfile.TemporaryDirectory() as temps:   # the device assembly on its way into the object
         cmd = ["hipcc"] + FLAGS + ["-save-temps", "-c", path, "-o", obj]

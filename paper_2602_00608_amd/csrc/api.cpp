@@ -129,6 +129,7 @@ struct Step {
   size_t sc_w_off = 0, sc_b_off = 0;
   double flops = 0.0, bytes = 0.0;   // algorithmic work / HBM traffic of this step for one frame
   double flops_dense = 0.0;          // the same with an upsampling convolution priced as nine taps per output
+  int eight_rows = 0;                // CONV: see ConvArgs
 };
 
 }  // namespace wmdec
@@ -168,7 +169,7 @@ static ConvArgs step_shape_args(const wmdec_decoder& d, const Step& st, int batc
   a.x_dtype = st.src == BUF_LATENT ? d.cfg.latent_dtype : a.op_dtype; a.x_nchw = st.x_nchw;
   a.y_dtype = st.dst == BUF_OUT ? (int)WMDEC_F32 : a.op_dtype; a.y_nchw = st.y_nchw;
   a.n = batch; a.h = st.h; a.w = st.w; a.cin = st.cin; a.cout = st.cout; a.ksize = st.ksize; a.upsample = st.upsample;
-  a.stats_groups = d.cfg.groups;
+  a.stats_groups = d.cfg.groups; a.eight_rows = st.eight_rows;
   if (st.res != BUF_NONE) a.res = &there;
   if (st.sc_src != BUF_NONE) { a.x2 = &there; a.cin2 = st.sc_cin; }
   if (st.emit_rows >= 0 && !st.emit_direct) a.rows_out = &there;
@@ -307,7 +308,12 @@ static void fuse_stats_into_producers(wmdec_decoder& d) {
     // A producer with few spatial tiles needs no merge of its own at all: the consumer reads its triples as they are.
     // (An upsampling convolution counts two triples a tile, whichever it leaves: up to 64 tiles the row buffers hold them anyway, above that they
     // would grow the workspace that a caller has to pass.)
-    const ConvArgs prod = step_shape_args(d, d.steps[j], 1);
+    // (Tiles that leave more than that while others do not are not worth a merge.)
+    ConvArgs prod = step_shape_args(d, d.steps[j], 1);
+    if (conv_stats_slots(prod) > 128) {
+      prod.eight_rows = 1;
+      d.steps[j].eight_rows = prod.eight_rows = conv_stats_slots(prod) <= 128;
+    }
     const int slots = conv_stats_slots(prod);
     int rows = 0, ctiles = 0, per_row = 0;
     const bool merges_rows = conv_row_extents(prod, &rows, &ctiles, &per_row);

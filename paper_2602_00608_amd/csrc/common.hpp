@@ -100,6 +100,7 @@ struct ConvArgs {
   const float* bias2 = nullptr;
   int cin2 = 0;
   int wide_tiles = 0;            // size queries only: 1: the widest tiles, i.e. the fewest moment triples a launch of this shape can leave
+  int eight_rows = 0;            // 1: no tile of the pair of six and eight rows, which leaves more triples (six_eight_pair)
   void* stats_ws = nullptr;      // non-null: also emit GroupNorm moments of y, [n][stats_groups][slots] triples
   int stats_groups = 0;
   // matrix-core kernel only: statistics handed from producer to consumer without a merge launch
@@ -123,9 +124,9 @@ bool conv_mfma_supported(const ConvArgs& a);
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s);
 // the layers of conv_ksplit_supported (16 bit, cout % 128 == 0, no shortcut) in large batches: that kernel's bits and moments
 int launch_conv_quarters(const ConvArgs& a, hipStream_t s);
-// kernels_conv_rows.hip: its 3x3 layers on tiles of th rows x 16 pixels x 128 ni output channels; rows4: moments per four rows;
+// kernels_conv_rows.hip: its 3x3 layers on tiles of th rows x 16 pixels x 128 ni output channels; mode: a ConvMode, the rows of a triple of moments;
 // whole_ring: a whole chunk of weights in flight
-int launch_conv_rows(const ConvArgs& a, int th, int ni, bool rows4, bool whole_ring, hipStream_t s);
+int launch_conv_rows(const ConvArgs& a, int th, int ni, int mode, bool whole_ring, hipStream_t s);
 // moment slots per (sample, group) the MFMA kernel would write for this launch; 0: it cannot emit statistics
 int conv_mfma_stats_slots(const ConvArgs& a);
 void conv_mfma_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row);

@@ -4,14 +4,26 @@
 
 namespace wmdec {
 
-// MODE of a matrix-core kernel: kRows4 and kQuarters are forms between which and another kernel the batch decides, while a sample's
-// bits must not depend on that choice; so both keep the activation's roundings apart (PIN).
+// MODE of a matrix-core kernel: kRows4, kQuarters and kSixEight are forms between which and another kernel the batch decides, while a sample's
+// bits must not depend on that choice; so they keep the activation's roundings apart (PIN).
 //   kRows4     one of a pair of tiles, 4x16 and 8x16 (see four_row_slots): moments per four rows.
 //   kQuarters  the batched form of kernels_conv_ksplit.hip, with its order of summation: of every 64 input channels the
 //              k-th 16 belong to partial sum k, each of them is summed on its own, 16 channels and their nine taps at a
 //              time, and the four are added in order.  Here one after the other into a second set of accumulators, on M tiles of 4 x 8
 //              pixels, the blocks of that kernel's moments.
-enum ConvMode { kPlain = 0, kRows4 = 1, kQuarters = 2 };
+//   kSixEight  one of a pair of tiles, 6x16 and 8x16 (see six_eight_pair): moments per run of rows between multiples of six and of eight, one or two
+//              runs a tile of either kind.
+enum ConvMode { kPlain = 0, kRows4 = 1, kQuarters = 2, kSixEight = 3 };
+
+// kSixEight: of every 24 rows the runs begin at 0, 6, 8, 12, 16 and 18.  The run that a row belongs to, and the rows from it to the next run.
+__host__ __device__ constexpr int six_eight_run(int row) {
+  const int r = row % 24;
+  return row / 24 * 6 + (r >= 6) + (r >= 8) + (r >= 12) + (r >= 16) + (r >= 18);
+}
+__host__ __device__ constexpr int six_eight_rows_left(int row) {
+  const int six = 6 - row % 6, eight = 8 - row % 8;
+  return six < eight ? six : eight;
+}
 
 // Moments of a wavefront's stored values in the making: per channel of the lane (CH neighbouring ones) shifted sums over n pixels.
 template <int CH> struct LaneMoments { float n, shift[CH], s[CH], q[CH]; };

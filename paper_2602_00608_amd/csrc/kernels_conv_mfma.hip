@@ -702,7 +702,7 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
 
 // Tile shapes: patch height x width, wavefront rows x columns, 32-channel tiles per wavefront.
 struct TileShape { int th, tw, wm, wn, ni; };
-enum TileId { T256x128 = 0, T128x128_ROW, T128x64_ROW, T128x64, T256x32, T128x128_1x4, T128x256, T64x128, T128x128_ROWS4, kNumTiles };
+enum TileId { T256x128 = 0, T128x128_ROW, T128x64_ROW, T128x64, T256x32, T128x128_1x4, T128x256, T64x128, T128x128_ROWS4, T96x128, T96x256, T128x128_PAIR, T128x256_PAIR, kNumTiles };
 constexpr TileShape kTiles[kNumTiles] = {
     {8, 32, 2, 2, 2},    // T256x128: 256 pixels x 128 channels (large 1x1 convolutions)
     {4, 32, 2, 2, 2},    // T128x128_ROW: 128 x 128 on a 4x32 patch (1x1 convolutions)
@@ -716,6 +716,10 @@ constexpr TileShape kTiles[kNumTiles] = {
                          //     compute unit
     {4, 16, 1, 4, 1},    // T64x128: 64 x 128, T128x128_1x4 at half the height, for launches of at most one workgroup per compute unit
     {8, 16, 1, 4, 1},    // T128x128_ROWS4: the same layers in larger batches
+    {6, 16, 1, 4, 1},    // T96x128 and
+    {6, 16, 1, 4, 2},    // T96x256: the two above at three quarters of the height, where a launch's last round is fuller with them (see six_eight_pair), and
+    {8, 16, 1, 4, 1},    // T128x128_PAIR,
+    {8, 16, 1, 4, 2},    // T128x256_PAIR: the same layers in other batches
 };
 
 // Layers whose 128 x 128 tiles leave half of the compute units empty at batch 1 and whose moments, per 4x16 block, are few
@@ -749,8 +753,34 @@ bool wide_channels(const ConvArgs& a) {
   return 9 * ((tiles + 255) / 256) <= 5 * ((2 * tiles + 255) / 256);
 }
 
+// Tiles of six rows for launches of few rounds: a tile takes four fifths of the time of eight rows (the fixed parts and the weights are the same), and a launch takes
+// as long as its fullest compute unit, so six rows are ahead where their tiles need no more rounds.  The estimate, which the batch may follow (y is the same with every
+// tile, and both heights leave the same moments, see kSixEight), counts rounds of 256 tiles; tiles of 256 channels take 9 / 5 of 128.
+// us, eight / six rows, SiLU, residual, without moments: 512 channels 60x90 29.0 / 27.2, two samples 47.9 / 43.0, three 75.6 / 67.4, four 85.2 / 81.1; 54x80 26.9 / 23.5, 50x90 27.0 / 23.6,
+// 90x120 48.1 / 43.1, 80x100 47.3 / 43.8; 256 channels 100x100 15.7 / 13.9, 120x180 28.1 / 25.8; 512 -> 256 at 120x180 51.8 / 49.1; 128 channels 160x200 15.4 / 13.4;
+// where the estimate says eight: 512 channels 62x90 27.6 / 37.9, 90x160 54.8 / 63.1, eight samples of 60x90 152.6 / 158.3; 128 channels 136x184 10.5 / 13.0, 240x360 24.7 / 26.6.
+// Which layers may change their height is a function of the sample alone (its moments depend on it): those that gain at one sample, of at most two rounds (120x180 of
+// 512 channels: 83.1 / 80.8, which larger batches would lose again), from 128 input channels on and not widening, where the products outweigh the fixed parts.
+// Layers with fp32 output or rows merged by the launch itself stay with eight rows, and so do a decoder's whose consumer can read the fewer triples of eight rows only.
+// What the second triple of a tile costs the eight-row forms: ResBlocks of 512 channels at 60x90, eight samples, 329.5 -> 332, 128 channels at 160x200, three, 81.2 -> 82.8;
+// with six rows, one sample, 512 channels at 60x90 67.5 -> 65.9, 54x80 70.0 -> 61.3, 90x120 113.5 -> 107.1, 512 -> 256 at 100x100 62.3 -> 60.0, 128 at 160x200 46.8 -> 43.7.
+struct TileCost { int cost; bool wide; };
+TileCost tile_cost(const ConvArgs& a, int th, int n) {   // in fifths of the time of a 128 x 128 tile
+  const long tiles = (long)((a.h + th - 1) / th) * ((a.w + 15) / 16) * n, narrow = tiles * (a.cout / 128), wide = tiles * (a.cout / 256);
+  const long c1 = (narrow + 255) / 256 * (th == 6 ? 4 : 5), c2 = (wide + 255) / 256 * (th == 6 ? 7 : 9);
+  const bool only_wide = th == 6 && narrow > 2 * 256;    // (six rows of 128 channels come with the whole-chunk ring alone)
+  if (a.cout % 256 != 0) return {only_wide ? 1 << 30 : (int)c1, false};
+  return only_wide || c2 < c1 ? TileCost{(int)c2, true} : TileCost{(int)c1, false};
+}
+bool six_eight_pair(const ConvArgs& a) {
+  if (a.ksize != 3 || a.cout % 128 != 0 || a.y_nchw || a.y_dtype == WMDEC_F32 || a.rows_out || a.wide_tiles || a.eight_rows) return false;
+  if (a.cin < 128 || a.cin < a.cout) return false;
+  if ((long)((a.h + 7) / 8) * ((a.w + 15) / 16) * (a.cout / 128) > 2 * 256) return false;
+  return tile_cost(a, 6, 1).cost < tile_cost(a, 8, 1).cost;
+}
+
 // which tile shape a launch uses: a function of the per-sample shape only, so that the order of a summation does not depend on the
-// batch, but for the two pairs above
+// batch, but for the pairs above
 TileId pick_tile(const ConvArgs& a) {
   const long px = (long)a.h * a.w;
   const bool n128 = a.cout % 128 == 0;
@@ -758,6 +788,11 @@ TileId pick_tile(const ConvArgs& a) {
     if (a.cout <= 32) return T256x32;
     if (four_row_slots(a))
       return (long)((a.h + 3) / 4) * ((a.w + 15) / 16) * (a.cout / 128) * a.n <= 256 ? T64x128 : T128x128_ROWS4;
+    if (six_eight_pair(a)) {
+      const TileCost six = tile_cost(a, 6, a.n);
+      if (six.cost < tile_cost(a, 8, a.n).cost) return six.wide ? T96x256 : T96x128;
+      return wide_channels(a) ? T128x256_PAIR : T128x128_PAIR;
+    }
     if (wide_channels(a)) return T128x256;
     return n128 ? T128x128_1x4 : T128x64;
   }
@@ -765,12 +800,15 @@ TileId pick_tile(const ConvArgs& a) {
   return n128 ? T128x128_ROW : T128x64_ROW;
 }
 
+ConvMode mode_of(TileId t) { return t == T64x128 || t == T128x128_ROWS4 ? kRows4 : t >= T96x128 && t <= T128x256_PAIR ? kSixEight : kPlain; }
+
 // The 128x128 tiles with a whole chunk of weight fragments in flight (see RING in kernels_conv_rows.hip): launches of at most two workgroups
 // per compute unit, in their order of summation the same as the others, so that the batch may decide.  us, whole chunk / two steps ahead, with the
 // weights in the L2: 512 channels at 60x90 32.4 / 34.1, two samples 53.4 / 54.5, 256 channels at 120x180 28.3 / 29.3; in a decoder run,
 // where they are not, the difference is larger (the ten such layers of a 480x720 frame: 30 us when both rings were longer).
 bool whole_chunk_ring(const ConvArgs& a) {
   const TileId t = pick_tile(a);
+  if (t == T96x128) return true;
   if (t != T128x128_1x4 && t != T128x128_ROWS4) return false;
   const long wgs = (long)((a.h + 7) / 8) * ((a.w + 15) / 16) * (a.cout / 128) * a.n;
   return wgs <= 2 * 256;
@@ -781,7 +819,7 @@ int launch_3x3(const ConvArgs& a, hipStream_t s) {
   const TileId t = pick_tile(a);
   if (t == T128x64) return launch_cfg<T, TO, 8, 16, 4, 1, 2, 3, 32>(a, s);
   if (t == T256x32) return launch_cfg<T, TO, 8, 32, 4, 1, 1, 3, 32>(a, s);
-  return launch_conv_rows(a, kTiles[t].th, kTiles[t].ni, t == T64x128 || t == T128x128_ROWS4, t == T64x128 || whole_chunk_ring(a), s);
+  return launch_conv_rows(a, kTiles[t].th, kTiles[t].ni, mode_of(t), t == T64x128 || whole_chunk_ring(a), s);
 }
 
 // chunk of input channels a 1x1 launch stages at a time: 64 halves the barriers
@@ -828,14 +866,15 @@ int conv_mfma_stats_slots(const ConvArgs& a) {
   if ((cpg & (cpg - 1)) != 0 || cpg > 32) return 0;   // a group must sit inside one wavefront's 64-channel run
   const TileId t = pick_tile(a);
   const TileShape& ts = kTiles[t];
-  if (t == T64x128 || t == T128x128_ROWS4) return ((a.h + 3) / 4) * ((a.w + 15) / 16);
+  if (mode_of(t) == kRows4) return ((a.h + 3) / 4) * ((a.w + 15) / 16);
+  if (mode_of(t) == kSixEight) return (six_eight_run(a.h - 1) + 1) * ((a.w + 15) / 16);
   return ((a.w + ts.tw - 1) / ts.tw) * ((a.h + ts.th - 1) / ts.th) * ts.wm;
 }
 
 // tile rows / channel tiles of a launch: the extents of the row moments it can leave and of its ticket counters
 void conv_mfma_row_extents(const ConvArgs& a, int* tile_rows, int* channel_tiles, int* tiles_per_row) {
   TileId t = pick_tile(a);
-  if (t == T128x256 || t == T128x128_1x4) t = fits_wide(a) ? T128x256 : T128x128_1x4;
+  if (t == T128x256 || t == T128x128_1x4 || mode_of(t) == kSixEight) t = fits_wide(a) ? T128x256 : T128x128_1x4;   // (launches that merge rows take no tile of that pair)
   const TileShape& ts = kTiles[t];
   const int tn = ts.wn * ts.ni * 32;
   *tile_rows = (a.h + ts.th - 1) / ts.th;
@@ -860,7 +899,7 @@ const char* conv_mfma_label(const ConvArgs& a) {
   const int act = a.mean == nullptr && a.rows_in == nullptr && !a.groups_norm ? 0 : (a.silu ? 2 : 1);
   snprintf(buf, sizeof(buf), "conv_mfma_kernel<%s, %s, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d>", ty,
            a.y_dtype == WMDEC_F32 ? "float" : ty, ts.th, ts.tw, ts.wm, ts.wn, ts.ni, a.ksize, kc, act,
-           t == T64x128 || t == T128x128_ROWS4 ? kRows4 : kPlain, a.ksize == 3 && whole_chunk_ring(a) ? 18 : t == T64x128 ? 18 : 0);
+           mode_of(t), a.ksize == 3 && whole_chunk_ring(a) ? 18 : t == T64x128 ? 18 : 0);
   return buf;
 }
 

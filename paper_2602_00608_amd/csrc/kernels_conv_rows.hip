@@ -1,6 +1,6 @@
 // 3x3 convolution on 16x16x32 MFMAs: a wavefront holds all rows of a 16-pixel-wide patch.
 //
-// The form that the large layers take (128 output channels and more a workgroup).  GEMM view, staging, statistics and epilogue semantics
+// The form that the large layers take (128 output channels and more a workgroup; tiles of 8, 6 or 4 rows).  GEMM view, staging, statistics and epilogue semantics
 // are those of kernels_conv_mfma.hip: a workgroup of four wavefronts owns TH rows x 16 pixels and 128 * NI output channels, 32 * NI a
 // wavefront; per chunk of 32 input channels the patch plus halo goes through one of two LDS buffers, normalised and
 // activated once per element, and the nine taps are swept over it.
@@ -99,6 +99,7 @@ struct EpilogueParams {
   __amdgpu_buffer_rsrc_t res, y;           // the sample's residual and output, with its size: accesses outside are dropped
   int h, w, cout;
   Moments* stats; int cpg, stats_stride, row_stride;
+  int cut;                                 // (kSixEight) row of the tile with which its second triple begins; R or more: there is none
   bool handed_over;
 };
 
@@ -116,7 +117,8 @@ template <typename T> __device__ __forceinline__ uint32_t load_residual(const Ep
 // patches, as in kernels_conv_mfma.hip, the same lanes write 64 values one by one and wait for them.)  The bias is added to
 // the finished sums: accumulators that start from it round every partial sum at its exponent.
 // rv: the residual; that of the first rows is on its way.
-// Moments, of the values as stored: one triple per group for all R rows, or (kRows4) for every four of them.  FULL: no pixel of the patch lies
+// Moments, of the values as stored: one triple per group for all R rows, or (kRows4) for every four of them, or (kSixEight) for the rows in front of
+// `cut` and those from it on.  FULL: no pixel of the patch lies
 // outside the image (the moments need no masks, and the rows are scheduled as one).
 template <typename T, typename TO, int R, int NI, bool RES, bool STATS, bool FULL, int MODE>
 __device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], uint32_t (&rv)[NI * R][4], const float* s_bias, int lane, int ty0, int tx0, int co_w,
@@ -135,14 +137,32 @@ __device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], uint32_t
       for (int i = 0; i < 4; ++i) rv[k][i] = load_residual<T>(p, at[i], ty0 + k % R, tx0, co_w + 32 * (k / R));
     __builtin_amdgcn_sched_barrier(0);
   }
-  LaneMoments<2> st[NI * (R / EMIT)];
-  Moments* dst[NI * (R / EMIT)];
+  constexpr int TRIPLES = MODE == kSixEight ? 2 : R / EMIT;
+  constexpr bool EACH = MODE == kSixEight && NI * R > 12;   // the triples are written 32 channels at a time: beside the accumulators those of all would be spilled
+  LaneMoments<2> st[(EACH ? 1 : NI) * TRIPLES];
+  Moments* dst[(EACH ? 1 : NI) * TRIPLES];
 #pragma unroll
   for (int ni = 0; ni < NI; ++ni) {
     const float2 bias = *reinterpret_cast<const float2*>(s_bias + 32 * ni + 2 * (lane & 15));
 #pragma unroll
     for (int t = 0; t < R / EMIT; ++t) {
       float n = 0.f, shift[2] = {0.f, 0.f}, s[2][4] = {}, q[2][4] = {};
+      auto close = [&](LaneMoments<2>& own) __attribute__((always_inline)) {
+        if (STATS && !FULL) {   // a column outside the image has a sum of its own
+#pragma unroll
+          for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { s[e][i] = i < cols ? s[e][i] : 0.f; q[e][i] = i < cols ? q[e][i] : 0.f; }
+        }
+        own.n = n;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          own.shift[e] = shift[e];
+          own.s[e] = (s[e][0] + s[e][1]) + (s[e][2] + s[e][3]);
+          own.q[e] = (q[e][0] + q[e][1]) + (q[e][2] + q[e][3]);
+        }
+      };
+      LaneMoments<2> front{};   // (kSixEight) the rows in front of the cut, once it is behind
 #pragma unroll
       for (int r = t * EMIT; r < (t + 1) * EMIT; ++r) {
         if (!FULL && ty0 + r >= p.h) continue;
@@ -166,12 +186,22 @@ __device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], uint32_t
           }
         }
         if constexpr (STATS) {
+          if constexpr (MODE == kSixEight) {
+            if (r > 0 && r % 2 == 0 && r == p.cut) {   // (uniform)
+              close(front);
+              n = 0.f;
+#pragma unroll
+              for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { s[e][i] = 0.f; q[e][i] = 0.f; }
+            }
+          }
           n += FULL ? 4.f : (float)cols;
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
             // Shifted by the mean of the lane's first four pixels, a fourth of whichever is far off; in a ragged patch by the first (outside the image only if
             // all pixels of the lane are).
-            if (r == t * EMIT) shift[e] = FULL || columns ? 0.25f * ((v[0][e] + v[1][e]) + (v[2][e] + v[3][e])) : v[0][e];
+            if (r == t * EMIT || (MODE == kSixEight && r % 2 == 0 && r == p.cut)) shift[e] = FULL || columns ? 0.25f * ((v[0][e] + v[1][e]) + (v[2][e] + v[3][e])) : v[0][e];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const float d = v[i][e] - shift[e];
@@ -180,25 +210,32 @@ __device__ __forceinline__ void epilogue(const f32x4 (&acc)[R][2 * NI], uint32_t
           }
         }
       }
-      if (STATS && !FULL) {   // a column outside the image has a sum of its own
+      if constexpr (MODE == kSixEight) {
+        const bool two = p.cut < R && (FULL || ty0 + p.cut < p.h);
+        constexpr int STEP = EACH ? 0 : 2;
+        LaneMoments<2> rear;
+        close(rear);
+        LaneMoments<2>& lead = st[STEP * ni];   // (value by value: of the two as a whole the compiler would select an address)
+        lead.n = two ? front.n : rear.n;
 #pragma unroll
-        for (int e = 0; e < 2; ++e)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) { s[e][i] = i < cols ? s[e][i] : 0.f; q[e][i] = i < cols ? q[e][i] : 0.f; }
+        for (int e = 0; e < 2; ++e) {
+          lead.shift[e] = two ? front.shift[e] : rear.shift[e];
+          lead.s[e] = two ? front.s[e] : rear.s[e];
+          lead.q[e] = two ? front.q[e] : rear.q[e];
+        }
+        rear.n = two ? rear.n : 0.f;
+        st[STEP * ni + 1] = rear;
+        dst[STEP * ni] = p.stats + (size_t)(32 * ni / p.cpg) * p.stats_stride;
+        dst[STEP * ni + 1] = two ? dst[STEP * ni] + p.row_stride : nullptr;
+        if constexpr (STATS && EACH) emit_pairs(st, false, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
+      } else {
+        close(st[ni * TRIPLES + t]);
+        dst[ni * TRIPLES + t] = FULL || MODE != kRows4 || ty0 + t * EMIT < p.h   // (kRows4: rows past the image have no slot)
+                                    ? p.stats + t * p.row_stride + (size_t)(32 * ni / p.cpg) * p.stats_stride : nullptr;
       }
-      LaneMoments<2>& own = st[ni * (R / EMIT) + t];
-      own.n = n;
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        own.shift[e] = shift[e];
-        own.s[e] = (s[e][0] + s[e][1]) + (s[e][2] + s[e][3]);
-        own.q[e] = (q[e][0] + q[e][1]) + (q[e][2] + q[e][3]);
-      }
-      dst[ni * (R / EMIT) + t] = FULL || MODE != kRows4 || ty0 + t * EMIT < p.h   // (kRows4: rows past the image have no slot)
-                                     ? p.stats + t * p.row_stride + (size_t)(32 * ni / p.cpg) * p.stats_stride : nullptr;
     }
   }
-  if constexpr (STATS) emit_pairs(st, FULL, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
+  if constexpr (STATS && !EACH) emit_pairs(st, FULL && MODE != kSixEight, lane, co_w, dst, p.cpg, p.stats_stride, p.handed_over);
 }
 
 // ACT: what happens to an input element on its way into LDS: 0 nothing, 1 scale/shift, 2 scale/shift + SiLU
@@ -296,15 +333,14 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
   // memory and the epilogue adds both biases.  A chunk is little work (16 MFMAs a wavefront and 32 channels), so input and weights travel three
   // chunks ahead.
   if (p.x2) {
-    constexpr int NC = TH * 16 * VPP / NT, AHEAD = 3;   // vectors of a thread: the pixels without the halo
-    static_assert(NC * NT == TH * 16 * VPP, "whole vectors");
+    constexpr int ALL = TH * 16 * VPP, NC = (ALL + NT - 1) / NT, AHEAD = 3;   // vectors of a thread: the pixels without the halo
     const char* xin2 = reinterpret_cast<const char*>(p.x2) + (size_t)n * p.h * p.w_out * p.cin2 * sizeof(T);
     const int nch2 = p.cin2 / KC;
     int src2[NC], dst2[NC];
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
       const int v = (tid + i * NT) / VPP, y = v / 16, x = v % 16;
-      const bool inside = ty0 + y < p.h && tx0 + x < p.w_out;   // (the others' slots stay zero: the 3x3 taps read them)
+      const bool inside = (NC * NT == ALL || v < TH * 16) && ty0 + y < p.h && tx0 + x < p.w_out;   // (the others' slots stay zero: the 3x3 taps read them)
       src2[i] = (inside ? (ty0 + y) * p.w_out + tx0 + x : 0) * p.cin2 * (int)sizeof(T) + cvec * 16;
       dst2[i] = (inside ? (y + 1) * ROW + (x + 1) * PS : SPARE) + cvec * 8;
     }
@@ -421,7 +457,8 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
   }
   ep.h = p.h; ep.w = p.w_out; ep.cout = p.cout;
   // statistics slot of this tile: [sample][group][spatial tile], or by blocks of 4 rows x 16 pixels
-  ep.stats = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + (MODE == kRows4 ? ty0 / 4 * p.tiles_x + tx0 / TW : tile) : nullptr;
+  ep.stats = p.stats ? p.stats + (size_t)n * p.stats_groups * p.stats_slots + (MODE == kRows4 ? ty0 / 4 * p.tiles_x + tx0 / TW : MODE == kSixEight ? six_eight_run(ty0) * p.tiles_x + tx0 / TW : tile) : nullptr;
+  ep.cut = MODE == kSixEight ? six_eight_rows_left(ty0) : TH;
   ep.cpg = p.stats_cpg; ep.stats_stride = p.stats_slots; ep.row_stride = p.tiles_x; ep.handed_over = p.rows_out != nullptr;
 
   // ---- the chunks.  In the last two thirds of a sweep the words (two channels) of the next chunk's vectors are activated: all vectors of a
@@ -522,6 +559,7 @@ template <typename T, typename TO, int TH, int NI, int MODE, int RING>
 int launch_cfg(const ConvArgs& a, hipStream_t s) {
   MfmaParams p = conv_params(a, TH, 16, 128 * NI, 1, a.h, a.w);
   if (MODE == kRows4) p.stats_slots = ((a.h + 3) / 4) * p.tiles_x;
+  if (MODE == kSixEight) p.stats_slots = (six_eight_run(a.h - 1) + 1) * p.tiles_x;
   WMDEC_REQUIRE(a.cin % kChunk == 0 && a.cout % (128 * NI) == 0 && !a.y_nchw, WMDEC_ERR_UNSUPPORTED, "conv_rows: channels do not fit the tile");
   WMDEC_REQUIRE(MODE == kPlain || !a.rows_out, WMDEC_ERR_UNSUPPORTED, "conv_rows: this tile hands over no rows");
   const int rc = check_hand_over(p);
@@ -551,21 +589,32 @@ int launch_cfg(const ConvArgs& a, hipStream_t s) {
 }
 
 template <typename T, typename TO>
-int launch_form(const ConvArgs& a, int th, int ni, bool rows4, bool whole_ring, hipStream_t s) {
+int launch_form(const ConvArgs& a, int th, int ni, ConvMode mode, bool whole_ring, hipStream_t s) {
+  if constexpr (sizeof(TO) == 2) {
+    if (th == 6) return ni == 2 ? launch_cfg<T, TO, 6, 2, kSixEight, 0>(a, s) : launch_cfg<T, TO, 6, 1, kSixEight, 18>(a, s);
+    if (mode == kSixEight) return ni == 2 ? launch_cfg<T, TO, 8, 2, kSixEight, 0>(a, s) : launch_cfg<T, TO, 8, 1, kSixEight, 0>(a, s);
+  }
   if (th == 4) return launch_cfg<T, TO, 4, 1, kRows4, 18>(a, s);
   if (ni == 2) return launch_cfg<T, TO, 8, 2, kPlain, 0>(a, s);
-  if (rows4) return whole_ring ? launch_cfg<T, TO, 8, 1, kRows4, 18>(a, s) : launch_cfg<T, TO, 8, 1, kRows4, 0>(a, s);
+  if (mode == kRows4) return whole_ring ? launch_cfg<T, TO, 8, 1, kRows4, 18>(a, s) : launch_cfg<T, TO, 8, 1, kRows4, 0>(a, s);
   return whole_ring ? launch_cfg<T, TO, 8, 1, kPlain, 18>(a, s) : launch_cfg<T, TO, 8, 1, kPlain, 0>(a, s);
 }
 
-template <typename T> int launch_type(const ConvArgs& a, int th, int ni, bool rows4, bool whole_ring, hipStream_t s) {
-  return a.y_dtype == WMDEC_F32 ? launch_form<T, float>(a, th, ni, rows4, whole_ring, s) : launch_form<T, T>(a, th, ni, rows4, whole_ring, s);
+template <typename T> int launch_type(const ConvArgs& a, int th, int ni, ConvMode mode, bool whole_ring, hipStream_t s) {
+  return a.y_dtype == WMDEC_F32 ? launch_form<T, float>(a, th, ni, mode, whole_ring, s) : launch_form<T, T>(a, th, ni, mode, whole_ring, s);
 }
 
 }  // namespace
 
-int launch_conv_rows(const ConvArgs& a, int th, int ni, bool rows4, bool whole_ring, hipStream_t s) {
-  return a.op_dtype == WMDEC_BF16 ? launch_type<bf16_t>(a, th, ni, rows4, whole_ring, s) : launch_type<f16_t>(a, th, ni, rows4, whole_ring, s);
+// bf16 is compiled by kernels_conv_rows_bf16.hip, which includes this file: the two types beside each other take half of the time.
+#ifdef WMDEC_CONV_ROWS_BF16
+int launch_conv_rows_bf16(const ConvArgs& a, int th, int ni, int mode, bool whole_ring, hipStream_t s) { return launch_type<bf16_t>(a, th, ni, (ConvMode)mode, whole_ring, s); }
+#else
+int launch_conv_rows_bf16(const ConvArgs& a, int th, int ni, int mode, bool whole_ring, hipStream_t s);
+int launch_conv_rows(const ConvArgs& a, int th, int ni, int mode, bool whole_ring, hipStream_t s) {
+  WMDEC_REQUIRE(mode != kSixEight || a.y_dtype != WMDEC_F32, WMDEC_ERR_UNSUPPORTED, "conv_rows: this tile stores 16 bits");
+  return a.op_dtype == WMDEC_BF16 ? launch_conv_rows_bf16(a, th, ni, mode, whole_ring, s) : launch_type<f16_t>(a, th, ni, (ConvMode)mode, whole_ring, s);
 }
+#endif
 
 }  // namespace wmdec

@@ -115,3 +115,63 @@ def test_a_sample_keeps_its_bits_where_the_batch_chooses_the_width(dtype, cin, c
         batch = run(k)
         torch.cuda.synchronize()
         assert all(torch.equal(a[:1], b[:1]) for a, b in zip(alone, batch)), k
+
+
+# tiles of six rows and the eight-row tiles that share their moments: 96 x 128 (one or two samples of 128 channels, one of 256), 96 x 256 (two of 256
+# channels), 128 x 128 (three of 128, seven of 256) and 128 x 256 (five)
+PAIR = [(1, 128, 128, 131, 145), (3, 128, 128, 131, 145), (1, 256, 256, 101, 99), (2, 256, 256, 101, 99), (5, 256, 256, 101, 99), (7, 256, 256, 101, 99)]
+
+
+@pytest.mark.parametrize("act", [None, "affine", "silu"])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("n,cin,cout,h,w", PAIR)
+def test_tile_edges_where_the_height_is_chosen(dtype, n, cin, cout, h, w, act):
+    test_tile_edges(dtype, n, cin, cout, h, w, act)
+
+
+def _same_bits_in_batches(dtype, sizes, cin, cin2, cout, h, w, groups):
+    n, g = max(sizes), torch.Generator(device="cuda")
+    g.manual_seed(synth.SEED_BASE + 63)
+
+    def draw(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+    x, res, bias = draw(n, h, w, cin).to(G.TORCH[dtype]), draw(n, h, w, cout).to(G.TORCH[dtype]), draw(cout)
+    mean, rstd, gamma, beta = draw(n, 32), draw(n, 32).abs() + 0.5, draw(cin), draw(cin)
+    packed = G.pack((draw(cout, cin, 3, 3) / (9 * cin) ** 0.5).bfloat16().float().cpu().numpy(), dtype)
+    if cin2:
+        x2, bias2 = draw(n, h, w, cin2).to(G.TORCH[dtype]), draw(cout)
+        packed2 = G.pack((draw(cout, cin2, 1, 1) / cin2 ** 0.5).bfloat16().float().cpu().numpy(), dtype)
+
+    def run(k):
+        y = torch.empty((k, h, w, cout), dtype=G.TORCH[dtype], device="cuda")
+        head = (x[:k], mean[:k].reshape(-1), rstd[:k].reshape(-1), gamma, beta, 32, True, packed, bias)
+        if cin2:
+            wmdec.gn_silu_conv3x3_shortcut(*head, x2[:k], packed2, bias2, y)
+            return (y,)
+        ws = torch.full((wmdec.conv_stats_workspace_bytes(G.ENUM[dtype], G.ENUM[dtype], k, h, w, cin, cout, groups),), 0xA5, dtype=torch.uint8, device="cuda")
+        m, r = torch.empty((k, groups), device="cuda"), torch.empty((k, groups), device="cuda")
+        wmdec.gn_silu_conv3x3_stats(*head, res[:k], y, groups, 1e-6, m, r, ws)
+        return y, m, r
+    first, *others = [run(k) for k in sizes]
+    for k, batch in zip(sizes[1:], others):
+        assert all(torch.equal(a, b[:sizes[0]]) for a, b in zip(first, batch)), k
+    if not cin2:
+        y, m, r = first
+        v = y.double().view(sizes[0], h * w, groups, cout // groups)
+        mu, sd = v.mean((1, 3)), v.var((1, 3), unbiased=False).sqrt()
+        # fp32 sums shifted by a value of the block: a few 2^-24 of the values, which are up to some 5 standard deviations
+        assert float(((m.double() - mu) / sd).abs().max()) <= 4e-6 and float((r.double() * (sd ** 2 + 1e-6).sqrt() - 1).abs().max()) <= 4e-6
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("cin2", [0, 96])
+@pytest.mark.parametrize("sizes,c,h,w", [((1, 2, 3), 128, 131, 145), ((1, 2, 5, 7), 256, 101, 99)])
+def test_a_sample_keeps_its_bits_where_the_batch_chooses_the_height(dtype, sizes, c, cin2, h, w):
+    _same_bits_in_batches(dtype, sizes, c, cin2, c, h, w, 32)
+
+
+# every way in which the last runs of rows end, and groups of every size
+@pytest.mark.parametrize("groups", [4, 8, 16, 32, 64, 128])
+def test_moments_where_the_batch_chooses_the_height(groups):
+    for h in range(128 + groups.bit_length() % 3, 152, 3):
+        _same_bits_in_batches("f16", (1, 3), 128, 0, 128, h, 129, groups)

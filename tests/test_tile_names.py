@@ -60,3 +60,11 @@ def test_exact_displacements(tiles):
 def test_large_biases(tiles):
     got = tiles([c + (True,) for c in _cases(test_gpu_ops.test_conv_adds_a_large_bias_to_finished_sums, "k,n,cin,cout,h,w")])
     assert {NARROW4, RING, NARROW, WIDE} <= set(got), got
+
+
+def test_heights_that_the_batch_chooses(tiles):
+    six, six_wide, eight, eight_wide = "6, 1, 3, 18", "6, 2, 3, 0", "8, 1, 3, 0", "8, 2, 3, 0"
+    got = tiles([(3,) + c + (False,) for c in test_gpu_conv_rows.PAIR])
+    assert got == [six, eight, six, six_wide, eight_wide, eight], got
+    assert tiles([(3, n, 128, 128, h, 129, False) for n in (1, 3) for h in (128, 151)]) == [six, six, eight, eight]
+    assert tiles([(3, 1, 256, 256, 101, 99, True), (3, 1, 128, 256, 101, 99, False)]) == [RING, RING]   # (fp32 output, a layer that widens)
