@@ -341,8 +341,8 @@ __device__ __forceinline__ Moments block_moments(Sums t, float shift, int rows, 
   return Moments{cnt, shift + ds, m2 < 0.f ? 0.f : m2};
 }
 
-// Row hand-over: the workgroup that finishes a (sample, tile row, channel tile) last merges that row's triples.  Same
-// protocol as the single-launch statistics kernel: the triples were written with device-scope stores, every wavefront
+// Row hand-over: the workgroup that finishes a (sample, tile row, channel tile) last merges that row's triples.  The
+// triples were written with device-scope stores, every wavefront
 // waits for its stores, the workgroup takes a ticket (a wrapping counter that returns to zero by itself), and only the
 // last one reads, with device-scope loads, in a fixed order.  per_tile: triples of one group a workgroup leaves.
 template <int NT>

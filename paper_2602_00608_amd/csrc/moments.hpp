@@ -64,8 +64,16 @@ template <int LANES> __device__ __forceinline__ float lanes_sum(float v) {
 }
 
 // Device-scope (write-through / L2-bypassing) accesses of a triple and the wait that orders a wavefront's stores before
-// a ticket it takes afterwards: the hand-over between workgroups of one launch that both the single-launch statistics
-// kernel and the convolution epilogue use (gfx950; see the note at the top of kernels_gn.hip).
+// a ticket it takes afterwards: the hand-over between workgroups of one launch that the convolution epilogue uses.
+// Hardware assumption (gfx950 only, checked here): no release / acquire fence is used, because an agent-scope fence on this chip writes back or
+// invalidates the whole L2 of the XCD (microseconds per wavefront).  Instead every shared word is itself accessed with agent-scope atomic
+// stores and loads, which gfx950 executes as write-through stores / L2-bypassing loads of memory that is coherent
+// across the XCDs; the publishing wavefront waits until the memory system has acknowledged its stores (vmcnt = 0)
+// before it takes the ticket, and only the workgroup that draws the last ticket reads.  Under the language memory
+// model the relaxed accesses alone would not order the stores before the ticket; the wait does, on this hardware.
+#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
+#error "the hand-over of moments relies on gfx950 memory behaviour"
+#endif
 __device__ __forceinline__ void store_device(Moments* p, Moments m) {
   __hip_atomic_store(&p->n, m.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(&p->mean, m.mean, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
