@@ -806,10 +806,13 @@ ConvMode mode_of(TileId t) { return t == T64x128 || t == T128x128_ROWS4 ? kRows4
 // per compute unit, in their order of summation the same as the others, so that the batch may decide.  us, whole chunk / two steps ahead, with the
 // weights in the L2: 512 channels at 60x90 32.4 / 34.1, two samples 53.4 / 54.5, 256 channels at 120x180 28.3 / 29.3; in a decoder run,
 // where they are not, the difference is larger (the ten such layers of a 480x720 frame: 30 us when both rings were longer).
+// The eight-row tiles that share their moments with six rows from 256 input channels on: below that a launch has too few chunks for it to pay.  us, whole
+// chunk / two steps, three samples of 128 output channels at 131x145, with residual: f16 512 -> 128 59.0 / 60.4, bf16 58.6 / 59.0; four at 49x286, f16 256 -> 128 32.1 / 32.6, bf16 as
+// fast; 128 -> 128 19.1 / 19.0 and 18.9 / 18.7, with moments 22.7 / 22.7 and 22.9 / 22.6.
 bool whole_chunk_ring(const ConvArgs& a) {
   const TileId t = pick_tile(a);
   if (t == T96x128) return true;
-  if (t != T128x128_1x4 && t != T128x128_ROWS4) return false;
+  if (t != T128x128_1x4 && t != T128x128_ROWS4 && !(t == T128x128_PAIR && a.cin >= 256)) return false;
   const long wgs = (long)((a.h + 7) / 8) * ((a.w + 15) / 16) * (a.cout / 128) * a.n;
   return wgs <= 2 * 256;
 }

@@ -592,7 +592,8 @@ template <typename T, typename TO>
 int launch_form(const ConvArgs& a, int th, int ni, ConvMode mode, bool whole_ring, hipStream_t s) {
   if constexpr (sizeof(TO) == 2) {
     if (th == 6) return ni == 2 ? launch_cfg<T, TO, 6, 2, kSixEight, 0>(a, s) : launch_cfg<T, TO, 6, 1, kSixEight, 18>(a, s);
-    if (mode == kSixEight) return ni == 2 ? launch_cfg<T, TO, 8, 2, kSixEight, 0>(a, s) : launch_cfg<T, TO, 8, 1, kSixEight, 0>(a, s);
+    if (mode == kSixEight && ni == 2) return launch_cfg<T, TO, 8, 2, kSixEight, 0>(a, s);
+    if (mode == kSixEight) return whole_ring ? launch_cfg<T, TO, 8, 1, kSixEight, 18>(a, s) : launch_cfg<T, TO, 8, 1, kSixEight, 0>(a, s);
   }
   if (th == 4) return launch_cfg<T, TO, 4, 1, kRows4, 18>(a, s);
   if (ni == 2) return launch_cfg<T, TO, 8, 2, kPlain, 0>(a, s);

@@ -118,8 +118,8 @@ def test_a_sample_keeps_its_bits_where_the_batch_chooses_the_width(dtype, cin, c
 
 
 # tiles of six rows and the eight-row tiles that share their moments: 96 x 128 (one or two samples of 128 channels, one of 256), 96 x 256 (two of 256
-# channels), 128 x 128 (three of 128, seven of 256) and 128 x 256 (five)
-PAIR = [(1, 128, 128, 131, 145), (3, 128, 128, 131, 145), (1, 256, 256, 101, 99), (2, 256, 256, 101, 99), (5, 256, 256, 101, 99), (7, 256, 256, 101, 99)]
+# channels), 128 x 128 (three of 128, with a short ring of weights and a whole one; seven of 256) and 128 x 256 (five)
+PAIR = [(1, 128, 128, 131, 145), (3, 128, 128, 131, 145), (3, 256, 128, 131, 145), (1, 256, 256, 101, 99), (2, 256, 256, 101, 99), (5, 256, 256, 101, 99), (7, 256, 256, 101, 99)]
 
 
 @pytest.mark.parametrize("act", [None, "affine", "silu"])
@@ -168,6 +168,12 @@ def _same_bits_in_batches(dtype, sizes, cin, cin2, cout, h, w, groups):
 @pytest.mark.parametrize("sizes,c,h,w", [((1, 2, 3), 128, 131, 145), ((1, 2, 5, 7), 256, 101, 99)])
 def test_a_sample_keeps_its_bits_where_the_batch_chooses_the_height(dtype, sizes, c, cin2, h, w):
     _same_bits_in_batches(dtype, sizes, c, cin2, c, h, w, 32)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("cin2", [0, 96])
+def test_a_sample_keeps_its_bits_where_the_batch_chooses_the_height_and_the_ring_is_whole(dtype, cin2):
+    _same_bits_in_batches(dtype, (1, 3, 4), 256, cin2, 128, 131, 145, 32)
 
 
 # every way in which the last runs of rows end, and groups of every size

@@ -63,8 +63,10 @@ def test_large_biases(tiles):
 
 
 def test_heights_that_the_batch_chooses(tiles):
-    six, six_wide, eight, eight_wide = "6, 1, 3, 18", "6, 2, 3, 0", "8, 1, 3, 0", "8, 2, 3, 0"
+    six, six_wide, eight, eight_ring, eight_wide = "6, 1, 3, 18", "6, 2, 3, 0", "8, 1, 3, 0", "8, 1, 3, 18", "8, 2, 3, 0"
     got = tiles([(3,) + c + (False,) for c in test_gpu_conv_rows.PAIR])
-    assert got == [six, eight, six, six_wide, eight_wide, eight], got
+    assert got == [six, eight, eight_ring, six, six_wide, eight_wide, eight], got
+    # a whole ring up to 512 workgroups, from 256 input channels on
+    assert tiles([(3, n, cin, 128, 131, 145, False) for n in (3, 4) for cin in (224, 256, 512)]) == [eight, eight_ring, eight_ring] + [eight] * 3
     assert tiles([(3, n, 128, 128, h, 129, False) for n in (1, 3) for h in (128, 151)]) == [six, six, eight, eight]
     assert tiles([(3, 1, 256, 256, 101, 99, True), (3, 1, 128, 256, 101, 99, False)]) == [RING, RING]   # (fp32 output, a layer that widens)
