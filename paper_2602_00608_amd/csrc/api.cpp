@@ -310,7 +310,7 @@ static void fuse_stats_into_producers(wmdec_decoder& d) {
     // would grow the workspace that a caller has to pass.)
     // (Tiles that leave more than that while others do not are not worth a merge.)
     ConvArgs prod = step_shape_args(d, d.steps[j], 1);
-    if (conv_stats_slots(prod) > 128) {
+    if (!prod.eight_rows && conv_stats_slots(prod) > 128) {
       prod.eight_rows = 1;
       d.steps[j].eight_rows = prod.eight_rows = conv_stats_slots(prod) <= 128;
     }
@@ -343,6 +343,34 @@ static void fuse_stats_into_producers(wmdec_decoder& d) {
   for (const Step& st : d.steps)
     if (st.kind != Step::NONE) kept.push_back(st);
   d.steps.swap(kept);
+}
+
+// layout of the workspace for `batch` frames
+struct WsLayout {
+  size_t tickets, conv_tickets, conv_ticket_bytes, rows[2], act[3], qkv, attn_o, attn_scratch, mean, rstd, stats_ws, stats_ws_bytes, total;
+};
+static WsLayout ws_layout(const wmdec_decoder* d, int batch, size_t least_scratch = 0);
+
+// fuse_stats_into_producers with the tiles of six rows, if the workspace stays within what it has been without them: a caller may keep the figure.  It was
+// the row buffers with the triples of eight rows and scratch for any statistics pass (2048 triples); a plan without such a pass has less scratch, which
+// nearly always holds what six rows add to the row buffers (all latents from 5x5 to 66x99 of four level lists).  Otherwise every layer that leaves moments stays with
+// eight rows (the outputs are the same).
+static void fuse_stats(wmdec_decoder& d) {
+  const std::vector<Step> steps = d.steps;
+  const int launches = d.launches;
+  auto fuse = [&](int eight_rows) {
+    d.steps = steps; d.launches = launches;
+    for (Step& st : d.steps) st.eight_rows = eight_rows;
+    fuse_stats_into_producers(d);
+    for (Step& st : d.steps)
+      if (!st.emit_stats) st.eight_rows = 0;
+  };
+  fuse(1);
+  std::vector<size_t> held;
+  for (int b = 1; b <= d.cfg.max_batch; ++b) held.push_back(ws_layout(&d, b, gn_stats_moments_bytes(b, d.cfg.groups)).total);
+  fuse(0);
+  for (int b = 1; b <= d.cfg.max_batch; ++b)
+    if (ws_layout(&d, b).total > held[b - 1]) { fuse(1); break; }
 }
 
 static int build_plan(wmdec_decoder& d) {
@@ -422,7 +450,7 @@ static int build_plan(wmdec_decoder& d) {
   }
   d.weights_bytes = B.off;
   d.packed_bytes = B.poff;
-  if (!c.separate_stats_pass) fuse_stats_into_producers(d);
+  if (!c.separate_stats_pass) fuse_stats(d);
   return WMDEC_OK;
 }
 
@@ -432,19 +460,14 @@ static const Param* find_param(const wmdec_decoder* d, const char* name) {
   return nullptr;
 }
 
-// layout of the workspace for `batch` frames
-struct WsLayout {
-  size_t tickets, conv_tickets, conv_ticket_bytes, rows[2], act[3], qkv, attn_o, attn_scratch, mean, rstd, stats_ws, stats_ws_bytes, total;
-};
-
-static WsLayout ws_layout(const wmdec_decoder* d, int batch) {
+static WsLayout ws_layout(const wmdec_decoder* d, int batch, size_t least_scratch) {
   WsLayout L;
   const size_t es = dtype_size(d->cfg.act_dtype);
   const size_t act = align_up(d->act_elems_per_frame * es * batch, 256);
   size_t o = 0;
   L.tickets = o; o += gn_stats_ticket_bytes(d->cfg.max_batch);   // same place and size for every batch: zeroed once
-  // ticket counters and row moments of the convolutions that hand their statistics over without a merge launch (sized
-  // for max_batch, like the counters above: they are zeroed once per workspace and return to zero by themselves)
+  // ticket counters (sized for max_batch, like the counters above: they are zeroed once per workspace and return to zero by themselves) and row
+  // moments of the convolutions that hand their statistics over without a merge launch
   size_t max_tickets = 0, max_rows = 0;
   for (const Step& st : d->steps) {
     if (st.kind != Step::CONV || st.emit_rows < 0) continue;
@@ -456,14 +479,16 @@ static WsLayout ws_layout(const wmdec_decoder* d, int batch) {
   }
   L.conv_ticket_bytes = align_up(max_tickets * d->cfg.max_batch * sizeof(unsigned), 256);
   L.conv_tickets = o; o += L.conv_ticket_bytes;
-  for (int i = 0; i < 2; ++i) { L.rows[i] = o; o += align_up(max_rows * d->cfg.max_batch * d->cfg.groups * 3 * sizeof(float), 256); }
+  for (int i = 0; i < 2; ++i) { L.rows[i] = o; o += align_up(max_rows * batch * d->cfg.groups * 3 * sizeof(float), 256); }
   for (int i = 0; i < 3; ++i) { L.act[i] = o; o += act; }
   L.qkv = o; o += align_up(attention_fragment_bytes(batch, d->attn_t), 256);
   L.attn_o = o; o += align_up((size_t)batch * d->attn_t * d->attn_c * es, 256);
   L.attn_scratch = o; o += align_up(flash_attention_scratch_bytes(batch, d->attn_t), 256);
   L.mean = o; o += align_up((size_t)batch * d->cfg.groups * sizeof(float), 256);
   L.rstd = o; o += align_up((size_t)batch * d->cfg.groups * sizeof(float), 256);
-  L.stats_ws_bytes = gn_stats_moments_bytes(batch, d->cfg.groups);
+  L.stats_ws_bytes = least_scratch;
+  for (const Step& st : d->steps)
+    if (st.kind == Step::STATS && !st.from_producer) L.stats_ws_bytes = gn_stats_moments_bytes(batch, d->cfg.groups);
   for (const Step& st : d->steps) {
     if (st.kind != Step::CONV || !st.emit_stats) continue;
     const size_t need = (size_t)batch * d->cfg.groups * conv_stats_slots(step_shape_args(*d, st, batch)) * 3 * sizeof(float);

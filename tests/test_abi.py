@@ -127,6 +127,35 @@ def test_step_accounting_adds_up():
     dec.close()
 
 
+def test_workspaces_sized_by_earlier_versions_are_enough():
+    """Bytes that a decoder of up to four frames asked for before there were tiles of six rows (one frame, four): a caller may keep them.  At 25x40, 30x45 and
+    11x88 the triples of six rows are more than the row buffers of eight rows held; at 67x61 nothing else gives room for them, and layers that leave
+    moments keep eight rows."""
+    def six_rows(h, w):
+        cfg = wmdec.decoder_default_config()
+        cfg.latent_h, cfg.latent_w = h, w
+        dec = wmdec.Decoder(cfg)
+        need, names = (dec.workspace_bytes(1), dec.workspace_bytes(4)), [k for k, _, _ in dec.step_info()]
+        dec.close()
+        return need, sum(1 for k in names if k.startswith("conv_mfma_kernel<wmdec::f16_t, wmdec::f16_t, 6, "))
+    for h, w, one, four, six in ((25, 40, 120252160, 480561408, True), (30, 45, 161905920, 647122688, True), (11, 88, 116448512, 465348352, True),
+                                 (60, 90, 609986048, 2438833408, True), (67, 61, 486916096, 1947031552, False)):
+        need, tiles = six_rows(h, w)
+        assert need[0] <= one and need[1] <= four and (tiles > 1) == six, (h, w, need, tiles)
+
+
+def test_layers_keep_eight_rows_where_six_would_need_a_merge():
+    """The consumer of a layer's moments merges up to 128 triples itself.  45x60: at 90x120 six rows leave 184 triples, eight 96: the layers that leave moments
+    keep eight rows and no merge follows, the last one, which leaves none, takes six.  60x90: 90 triples, all take six rows."""
+    for h, w, first, rows in ((45, 60, 15, ["8"] * 5 + ["6"]), (60, 90, 6, ["6"] * 8)):
+        cfg = wmdec.decoder_default_config()
+        cfg.latent_h, cfg.latent_w = h, w
+        dec = wmdec.Decoder(cfg)
+        kernels = [k for k, _, _ in dec.step_info()][first:first + len(rows) + 1]
+        assert kernels[-1].startswith("conv_up_kernel<") and [k.split(", ")[2] for k in kernels[:-1]] == rows, kernels
+        dec.close()
+
+
 def test_convolution_of_few_normalised_channels_leaves_no_moments():
     """The kernel for few input channels does not normalise, so a ResBlock's 8 -> 64 convolution runs on the general one, which emits no moments:
     the second convolution needs a statistics pass over what it wrote."""

@@ -569,6 +569,39 @@ def test_statistics_hand_over_without_a_merge_launch():
     assert np.array_equal(run_decoder(cfg, weights, z[2:3])[0], outs[0][2])
 
 
+def test_frames_are_the_same_whichever_tiles_the_batch_takes():
+    """One level of 512 channels at 85x33: its layers run on tiles of six rows and 128 channels for one frame, six rows and 256 channels for two, eight rows
+    and 256 channels for three, and the next layer's prologue merges the moments they leave.  A frame has the same bits in each, and nothing is written behind the
+    workspace that the batch asks for."""
+    cfg = wmdec.decoder_default_config()
+    cfg.latent_h, cfg.latent_w, cfg.num_levels, cfg.resblocks_per_level, cfg.max_batch = 85, 33, 1, 1, 3
+    spec = synth.decoder_weight_spec(level_channels=(512,), resblocks_per_level=1)
+    weights = synth.draw_params(spec, synth.weight_seed(13), random_affine=True)
+    z = synth.latent_sequence(workload=13, frames=3, h=85, w=33)
+    dec = wmdec.Decoder(cfg)
+    packed = torch.empty(dec.packed_bytes(), dtype=torch.uint8, device="cuda")
+    dec.pack_weights(make_blob(dec, weights), packed)
+    zd = dev_latent(z, cfg)
+
+    def run(frames):
+        n = len(frames)
+        need = dec.workspace_bytes(n)
+        ws = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        dec.set_workspace(ws[:need])
+        out = torch.empty((n, 3, 85, 33), dtype=torch.float32, device="cuda")
+        dec.run(zd[frames].contiguous(), packed, out)
+        torch.cuda.synchronize()
+        assert bool((ws[need:] == 0xA5).all())
+        return out
+    three = run([0, 1, 2])
+    for frames in ([0], [1], [2], [1, 2], [2, 0]):
+        assert torch.equal(run(frames), three[frames]), frames
+    want = ref.decoder(z[:1], weights, level_channels=(512,), resblocks_per_level=1)
+    err = ref.rel_err(three[:1].cpu().numpy().astype(np.float64), want)
+    assert err <= G.TOL["f16"], err
+    dec.close()
+
+
 def test_folded_shortcut_against_separate_shortcut_and_the_oracle():
     """The 1x1 shortcut of the channel-changing ResBlocks as extra contraction steps of the second convolution
     (default) and as a launch of its own: both graphs against the oracle; fewer launches with the fold."""
