@@ -128,8 +128,9 @@ int wmdec_gn_silu_conv3x3(const void* x, int act_dtype, const float* mean, const
  * (wmdec_conv_stats_workspace_bytes(...) bytes, no initialisation needed); a
  * second small launch merges them in a fixed order.  A smaller workspace that
  * still holds a triple per (sample, group) and tile of 8x16 pixels (four per
- * tile if cout % 128 != 0) is accepted: y has the same bits, its statistics are
- * then taken by a pass over y.
+ * tile if cout % 128 != 0) is accepted: y has the same bits.  Where the layer
+ * would run on tiles of 6x16 pixels its statistics then come from tiles of 8x16,
+ * otherwise from a pass over y.
  * Moments are emitted for 16-bit act_dtype by the matrix-core kernels
  * (cin % 32 == 0, cout % 64 == 0, cout/out_groups a power of two <= 32)
  * and the kernel for cin <= 8 (the decoder's conv_in: no normalisation of x,

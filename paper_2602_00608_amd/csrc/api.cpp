@@ -663,7 +663,7 @@ int wmdec_gn_silu_conv3x3_stats(const void* x, int act_dtype, const float* mean,
   a.x = x; a.mean = mean; a.rstd = mean ? rstd : nullptr; a.gamma = gamma; a.beta = beta;
   a.groups = mean ? groups : 1; a.silu = (mean && apply_silu) ? 1 : 0;
   a.wt = w_packed; a.bias = bias; a.res = residual; a.y = y;
-  const int slots = conv_stats_slots(a);
+  int slots = conv_stats_slots(a);
   WMDEC_REQUIRE(slots > 0, WMDEC_ERR_UNSUPPORTED,
                 "%s: this shape / type takes no kernel that emits moments (16-bit types and either cin %% 32 == 0, cout %% 64 == 0, "
                 "channels per output group a power of two <= 32, or cin <= 8 without normalisation and residual, channels per "
@@ -675,7 +675,11 @@ int wmdec_gn_silu_conv3x3_stats(const void* x, int act_dtype, const float* mean,
   const size_t triple = (size_t)n * out_groups * 3 * sizeof(float), need = triple * slots, least = triple * conv_stats_slots(wide);
   WMDEC_REQUIRE(workspace && aligned16(workspace) && workspace_bytes >= (least > 0 && least < need ? least : need), WMDEC_ERR_WORKSPACE,
                 "%s: workspace needs %zu bytes, got %zu", who, need, workspace_bytes);
-  if (workspace_bytes >= need) a.stats_ws = workspace;
+  // (Tiles of eight rows store the same bits as those of six and leave fewer triples: where those fit, the workspace may choose them.)
+  ConvArgs eight = a;
+  eight.eight_rows = 1;
+  if (workspace_bytes < need && workspace_bytes >= triple * conv_stats_slots(eight)) { a.eight_rows = 1; slots = conv_stats_slots(a); }
+  if (workspace_bytes >= triple * slots) a.stats_ws = workspace;
   const int rl = launch_conv(a, (hipStream_t)stream);
   if (rl != WMDEC_OK) return rl;
   if (!a.stats_ws)

@@ -176,6 +176,43 @@ def test_a_sample_keeps_its_bits_where_the_batch_chooses_the_height_and_the_ring
     _same_bits_in_batches(dtype, (1, 3, 4), 256, cin2, 128, 131, 145, 32)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("n,cin,cout,h,w", PAIR)
+def test_a_workspace_for_the_triples_of_eight_rows(dtype, n, cin, cout, h, w):
+    """What such a layer asked for before it could take six rows still gets its moments from the convolution, one triple per group and 8 x 16 tile, and the same y."""
+    g, groups = torch.Generator(device="cuda"), 32
+    g.manual_seed(synth.SEED_BASE + 64)
+
+    def draw(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+    x, res, bias = draw(n, h, w, cin).to(G.TORCH[dtype]), draw(n, h, w, cout).to(G.TORCH[dtype]), draw(cout)
+    mean, rstd, gamma, beta = draw(n * 32), draw(n * 32).abs() + 0.5, draw(cin), draw(cin)
+    packed = G.pack((draw(cout, cin, 3, 3) / (9 * cin) ** 0.5).bfloat16().float().cpu().numpy(), dtype)
+    tiles_y, tiles_x = -(-h // 8), -(-w // 16)
+    full, few = wmdec.conv_stats_workspace_bytes(G.ENUM[dtype], G.ENUM[dtype], n, h, w, cin, cout, groups), 12 * groups * n * tiles_y * tiles_x
+    assert few < full
+
+    def run(size):
+        y, ws = torch.empty((n, h, w, cout), dtype=G.TORCH[dtype], device="cuda"), torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        m, r = torch.empty(n * groups, device="cuda"), torch.empty(n * groups, device="cuda")
+        wmdec.gn_silu_conv3x3_stats(x, mean, rstd, gamma, beta, 32, True, packed, bias, res, y, groups, 1e-6, m, r, ws[:size])
+        assert bool((ws[size:] == 0xA5).all())
+        return y, m, r, ws[:size]
+    y, m, r, _ = run(full)
+    for size in (few, full - 12):
+        y2, m2, r2, ws = run(size)
+        v = y2.double().view(n, h * w, groups, cout // groups)
+        mu, sd = v.mean((1, 3)).flatten(), v.var((1, 3), unbiased=False).sqrt().flatten()
+        # fp32 sums shifted by a value of the block: a few 2^-24 of the values, which are up to some 5 standard deviations
+        assert torch.equal(y, y2) and float(((m2.double() - mu) / sd).abs().max()) <= 4e-6 and float((r2.double() * (sd ** 2 + 1e-6).sqrt() - 1).abs().max()) <= 4e-6
+        count = ws[:few].view(torch.float32).view(n, groups, tiles_y, tiles_x, 3)[..., 0]
+        rows, cols = ([min(t, e - t * i) for i in range(k)] for t, e, k in ((8, h, tiles_y), (16, w, tiles_x)))
+        assert torch.equal(count, torch.outer(torch.tensor(rows), torch.tensor(cols)).mul(cout // groups).float().cuda().expand_as(count))
+    with pytest.raises(wmdec.WmdecError) as e:
+        run(few - 12)
+    assert e.value.status == wmdec.ERR_WORKSPACE
+
+
 # every way in which the last runs of rows end, and groups of every size
 @pytest.mark.parametrize("groups", [4, 8, 16, 32, 64, 128])
 def test_moments_where_the_batch_chooses_the_height(groups):
