@@ -221,7 +221,8 @@ __global__ __launch_bounds__(256) void gn_partial_any(const T* __restrict__ x, i
   if (tid == 0) ws[((size_t)n * groups + g) * chunks + chunk] = s_m[0];
 }
 
-// grid = n*groups workgroups of as many wavefronts as hold the row's triples, kFinLoads in a lane (up to 16; longer rows go round).  A wavefront
+// grid = n*groups workgroups of as many wavefronts as hold the row's triples, kFinLoads in a lane (up to 16; of rows of more than 4096 every lane takes
+// more, reading them twice: sums about the mean of the first 4096 alone would cancel as many times over as the row is longer).  A wavefront
 // takes the mean of its triples first, then the differences to it and their squares from the same registers; up to 256 triples that is the
 // result, otherwise 16 lanes merge the wavefronts' triples the same way.  Bound by the launch, one trip to memory and the chain behind it: with
 // pairwise merges, a reciprocal in each, and always 16 wavefronts, us of calls with one merge, before / now: ResBlock 256 -> 256 channels at 120x180 76.4 / 74.7,
@@ -250,20 +251,27 @@ __global__ __launch_bounds__(kFinThreads) void gn_finalize(const Moments* __rest
       if (i0 + k * nt >= chunks) t[k].n = 0.f;
   };
   float first = row[0].mean, w = 0.f, s = 0.f, q = 0.f;
+  auto rest = [&](float about) {   // of a longer row, behind the triples at hand
+    for (int i0 = tid + kFinLoads * nt; i0 - tid < chunks; i0 += kFinLoads * nt) {
+      fetch(i0);
+#pragma unroll
+      for (int k = 0; k < kFinLoads; ++k) step(t[k], about, w, s, q);
+    }
+  };
   fetch(tid);
   first = finite(first);
 #pragma unroll
   for (int k = 0; k < kFinLoads; ++k) step(t[k], first, w, s, q);
+  if (chunks > kFinLoads * nt) {
+    rest(first);
+    fetch(tid);
+  }
   w = wave_sum(w);
   const float mid = first + wave_sum(s) * (w > 0.f ? __builtin_amdgcn_rcpf(w) : 0.f), about = finite(mid);   // 1 ulp: what the roundings leave follows
   w = 0.f; s = 0.f; q = 0.f;
 #pragma unroll
   for (int k = 0; k < kFinLoads; ++k) step(t[k], about, w, s, q);
-  for (int i0 = tid + kFinLoads * nt; i0 - tid < chunks; i0 += kFinLoads * nt) {
-    fetch(i0);
-#pragma unroll
-    for (int k = 0; k < kFinLoads; ++k) step(t[k], about, w, s, q);
-  }
+  rest(about);
   auto close = [&](float all_w, float all_s, float all_q) -> Moments {
     const float ds = all_s * (all_w > 0.f ? __builtin_amdgcn_rcpf(all_w) : 0.f), m2 = all_q - all_s * (1.f / kUnit) * ds;
     return Moments{all_w * (1.f / kUnit), about + ds, m2 < 0.f ? 0.f : m2};   // (NaN stays NaN)

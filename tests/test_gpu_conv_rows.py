@@ -218,3 +218,30 @@ def test_a_workspace_for_the_triples_of_eight_rows(dtype, n, cin, cout, h, w):
 def test_moments_where_the_batch_chooses_the_height(groups):
     for h in range(128 + groups.bit_length() % 3, 152, 3):
         _same_bits_in_batches("f16", (1, 3), 128, 0, 128, h, 129, groups)
+
+
+# rows of more than 4096 triples, which a lane of the merge takes in several rounds (a tile of 8 x 16 pixels and 64 channels leaves four, here of few
+# pixels each): one full round, 4100, remainders, and a row 100 rounds long.  The first triples lie 100 standard deviations of the others from them.
+@pytest.mark.parametrize("h,w", [(8192, 3), (8193, 3), (10800, 2), (21600, 1), (819200, 1)])
+@pytest.mark.parametrize("band", [0, 2, 4096])
+def test_moments_of_long_rows_of_triples(h, w, band):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(synth.SEED_BASE + 65)
+    c, groups = 64, 32
+    x = torch.randn((1, h, w, c), generator=g, device="cuda")
+    x[:, :band] += 100
+    x = x.half()
+    wt = torch.zeros((c, c, 3, 3))
+    wt[torch.arange(c), torch.arange(c), 1, 1] = 1
+    packed, y = G.pack(wt.numpy(), "f16"), torch.empty_like(x)
+    mean, rstd = torch.empty(groups, device="cuda"), torch.empty(groups, device="cuda")
+    size = wmdec.conv_stats_workspace_bytes(wmdec.F16, wmdec.F16, 1, h, w, c, c, groups)
+    assert size == 12 * groups * 4 * -(-h // 8)
+    ws = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    wmdec.gn_silu_conv3x3_stats(x, None, None, None, None, 1, False, packed, None, None, y, groups, 1e-6, mean, rstd, ws[:size])
+    assert torch.equal(x, y) and bool((ws[size:] == 0xA5).all())
+    v = y.double().view(h * w, groups, c // groups)
+    m, sd = v.mean((0, 2)), v.var((0, 2), unbiased=False).sqrt()
+    # fp32 sums shifted by a value of the block, merged about their mean: a few 2^-24 of the values
+    err = float(((mean.double() - m) / sd).abs().max()), float((rstd.double() * (sd ** 2 + 1e-6).sqrt() - 1).abs().max())
+    assert err[0] <= 4e-6 and err[1] <= 4e-6, err
