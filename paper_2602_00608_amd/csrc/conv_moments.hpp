@@ -33,11 +33,14 @@ template <int CH> struct LaneMoments { float n, shift[CH], s[CH], q[CH]; };
 // channels, are summed in the vector ALU (lanes): the mean first,
 // then the squares about it.  (Through LDS, with a lane per channel that walked the others' sums and re-centred them one by
 // one, this was 13 of the 122 us of 128 -> 128 channels at 480x720, and 1.5 of 36 at 60x90.)  co: the lane's first channel; writes: whether
-// it is the lane that writes its groups; SOME: dst is null where there are none; all_n: pixels times lanes of a group where that is known, otherwise 0.
-template <int CH, int PARTS, bool SOME, int N, typename Lanes>
+// it is the lane that writes its groups; SOME: dst is null where there are none; all_n: pixels times lanes of a group where that is known, otherwise 0; WIDE: values up to
+// the end of fp32's range (lane `head` holds the group's first channels, of pixels if there are any): means are summed as differences to that lane's and in 1024ths of a pixel, up to 1024
+// pixels times lanes, so that sums of them stay in range and nothing deviates from the mean of equal values.
+template <int CH, int PARTS, bool SOME, bool WIDE = false, int N, typename Lanes>
 __device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Moments* const (&dst)[N], int co, bool writes, int cpg, int stats_stride, bool handed_over,
-                                             float all_n, Lanes&& lanes) {
+                                             float all_n, Lanes&& lanes, int head = 0) {
   constexpr int PC = CH / PARTS;
+  constexpr float kUnit = WIDE ? 0x1p-10f : 1.f;
   float inv[N], n[N], ninv[N];
 #pragma unroll
   for (int k = 0; k < N; ++k) {
@@ -57,17 +60,22 @@ __device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Mom
         const int c = g * PC + e;
         const float ds = quotient(st[k].s[c], st[k].n, inv[k]), m2 = st[k].q[c] - st[k].s[c] * ds;
         mean[e] = st[k].shift[c] + ds;
-        m[k] += mean[e];
+        m[k] += WIDE ? mean[e] * (1.f / PC) : mean[e];
         q[k] += m2 < 0.f ? 0.f : m2;     // (NaN stays NaN)
       }
-      m[k] = st[k].n > 0.f ? m[k] * (1.f / PC) : 0.f;     // the shift of a lane without pixels has no meaning
+      m[k] = st[k].n > 0.f ? (WIDE ? m[k] : m[k] * (1.f / PC)) : 0.f;     // the shift of a lane without pixels has no meaning
 #pragma unroll
       for (int e = 0; e < PC; ++e) { const float d = mean[e] - m[k]; dev[k] = fmaf(d, d, dev[k]); }
     }
 #pragma unroll
-    for (int k = 0; k < N; ++k) mid[k] = lanes(st[k].n * m[k]) * ninv[k];
+    for (int k = 0; k < N; ++k) {
+      if constexpr (WIDE) {
+        const float first = __shfl(m[k], head);
+        mid[k] = first + lanes(st[k].n * kUnit * (m[k] - first)) * (ninv[k] * (1.f / kUnit));
+      } else mid[k] = lanes(st[k].n * m[k]) * ninv[k];
+    }
 #pragma unroll
-    for (int k = 0; k < N; ++k) rest[k] = lanes(st[k].n * (m[k] - mid[k])) * ninv[k];       // what the roundings of mid left
+    for (int k = 0; k < N; ++k) rest[k] = lanes(st[k].n * kUnit * (m[k] - mid[k])) * (ninv[k] * (1.f / kUnit));       // what the roundings of mid left
 #pragma unroll
     for (int k = 0; k < N; ++k) {
       const float d = m[k] - mid[k], nd = st[k].n * d;
@@ -87,7 +95,7 @@ __device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Mom
 }
 
 // Lane l holds vector l % VECTORS of the wavefront's channels, CH of them each.
-template <int VECTORS, int CH>
+template <int VECTORS, int CH, bool WIDE = false>
 __device__ __forceinline__ void emit_vectors(const LaneMoments<CH> (&st)[1], int lane, int co_w, Moments* const (&dst)[1], int cpg, int stats_stride, bool handed_over) {
   static_assert(CH == 4 || CH == 8, "16 bytes");
   auto lanes = [&](float v) {
@@ -99,11 +107,12 @@ __device__ __forceinline__ void emit_vectors(const LaneMoments<CH> (&st)[1], int
     return v;
   };
   const int co = co_w + lane * CH;
+  const int head = lane % VECTORS & ~(max(cpg / CH, 1) - 1);
   const bool writes = lane < VECTORS && ((lane * CH) & (cpg - 1)) == 0;
-  if (cpg >= CH) emit_moments<CH, 1, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
-  else if (cpg == CH / 2) emit_moments<CH, 2, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
-  else if (cpg == CH / 4) emit_moments<CH, 4, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
-  else if constexpr (CH == 8) emit_moments<8, 8, false>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes);
+  if (cpg >= CH) emit_moments<CH, 1, false, WIDE>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, head);
+  else if (cpg == CH / 2) emit_moments<CH, 2, false, WIDE>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, head);
+  else if (cpg == CH / 4) emit_moments<CH, 4, false, WIDE>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, head);
+  else if constexpr (CH == 8) emit_moments<8, 8, false, WIDE>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, head);
 }
 
 // Lane l holds channels 2 (l % 16) and the next of 32, of the pixels of quarter l / 16; full: all lanes hold the same number of them.

@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kColThreads) void gn_stats_columns(const T* __restr
   if (off < end) gn_accumulate<T, V, true, U, true>(slab, off, end, sweep, st[0].shift, st[0].s, st[0].q);
   const int cpg = c / groups;
   Moments* const dst[1] = {&s_w[0][wave]};
-  emit_vectors<VECS, V>(st, lane, 0, dst, cpg, WAVES, false);
+  emit_vectors<VECS, V, !std::is_same<T, f16_t>::value>(st, lane, 0, dst, cpg, WAVES, false);   // (a wavefront's pixels are 256 at most)
   __syncthreads();
   const int own_groups = CH / cpg;
   if (tid < own_groups * WAVES) {   // (whole rows of 16 lanes)

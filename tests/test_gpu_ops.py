@@ -96,6 +96,19 @@ def test_gn_stats_with_an_outlier_first_pixel(c, h, w):
     assert np.max(np.abs(mean.cpu().numpy() - wm.ravel()) * wr.ravel()) < 5e-7
 
 
+# Small images (one workgroup's columns), one workgroup, and several with a merge; groups of one to 64 bytes of a pixel.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("c,groups,h,w", [(64, 32, 32, 32), (64, 64, 64, 64), (128, 8, 1, 1), (64, 4, 5, 7), (8, 4, 3, 5), (64, 8, 120, 180)])
+def test_gn_stats_of_values_near_the_end_of_the_range(dtype, c, groups, h, w):
+    """Constant 3e38 in every second group: a sum of a few such values is infinite, their mean is not, and nothing deviates from it."""
+    x = np.full((2, c, h, w), 3e38, np.float32)
+    x[:, (np.arange(c) * groups // c) % 2 == 1] = -2.0
+    x = G.stored(x, dtype)
+    mean, rstd = G.gn_stats(G.dev_nhwc(x, dtype), groups, 1e-6)
+    want = x[:, ::c // groups, 0, 0].ravel()
+    assert np.max(np.abs(mean.cpu().numpy() / want - 1.0)) < 1e-6 and np.max(np.abs(rstd.cpu().numpy() - 1e3)) < 1e-2
+
+
 @pytest.mark.parametrize("h,w", [(120, 180), (16, 16)])
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
 @pytest.mark.parametrize("last", [False, True])
