@@ -602,6 +602,40 @@ def test_frames_are_the_same_whichever_tiles_the_batch_takes():
     dec.close()
 
 
+def test_rows_are_handed_over_the_same_in_every_round():
+    """The last workgroup of a tile row merges the triples of the others, which no fence orders (device-scope stores, a wait, a ticket).  A triple read too early would show as
+    a frame that differs between repetitions: two latents in turn, one and two frames, 40 rounds on one workspace, each equal to the first round's bit for bit."""
+    cfg = wmdec.decoder_default_config()
+    cfg.latent_h, cfg.latent_w, cfg.num_levels, cfg.resblocks_per_level, cfg.max_batch = 33, 37, 3, 3, 2
+    cfg.level_channels[0], cfg.level_channels[1], cfg.level_channels[2] = 512, 128, 128
+    spec = synth.decoder_weight_spec(level_channels=(512, 128, 128), resblocks_per_level=3)
+    weights = synth.draw_params(spec, synth.weight_seed(14), random_affine=True)
+    dec = wmdec.Decoder(cfg)
+    cfg.separate_merge_launch = 1
+    merged = wmdec.Decoder(cfg)
+    kernels = [[k for k, _, _ in d.step_info()] for d in (dec, merged)]
+    ends = [k[max(i for i, name in enumerate(k) if name.startswith("conv_up_kernel<")):] for k in kernels]
+    # the upsampling convolution and the layers of 128 channels at 132x148 (170 triples each, more than a consumer merges) merge their rows; a merge in front of conv_out remains
+    assert ends[0].count("gn_finalize") == 1 and ends[1].count("gn_finalize") == 7 and len(ends[0]) == 9
+    merged.close()
+    packed = torch.empty(dec.packed_bytes(), dtype=torch.uint8, device="cuda")
+    dec.pack_weights(make_blob(dec, weights), packed)
+    dec.set_workspace(torch.full((dec.workspace_bytes(2),), 0xA5, dtype=torch.uint8, device="cuda"))
+    zd = dev_latent(synth.latent_sequence(workload=14, frames=2, h=33, w=37), cfg)
+    first = {}
+    for r in range(40):
+        outs = {}
+        for frames in ([0], [1], [0, 1]):
+            out = torch.empty((len(frames), 3, 132, 148), dtype=torch.float32, device="cuda")
+            dec.run(zd[frames].contiguous(), packed, out)
+            outs[tuple(frames)] = out
+        torch.cuda.synchronize()
+        first = first or outs
+        assert all(torch.equal(outs[k], first[k]) for k in outs), r
+    assert torch.equal(first[0, 1], torch.cat([first[0,], first[1,]]))
+    dec.close()
+
+
 def test_folded_shortcut_against_separate_shortcut_and_the_oracle():
     """The 1x1 shortcut of the channel-changing ResBlocks as extra contraction steps of the second convolution
     (default) and as a launch of its own: both graphs against the oracle; fewer launches with the fold."""
