@@ -54,7 +54,7 @@ def pack_upconv(w_oihw, dtype):
 
 def gn_stats(x_dev, groups, eps):
     n, h, w, c = x_dev.shape
-    ws = torch.zeros(max(wmdec.gn_stats_workspace_bytes(n, h, w, c, groups), 256), dtype=torch.uint8, device="cuda")   # ticket counter starts at zero
+    ws = torch.full((max(wmdec.gn_stats_workspace_bytes(n, h, w, c, groups), 256),), 0xA5, dtype=torch.uint8, device="cuda")   # (no initial contents needed)
     mean = torch.empty(n * groups, dtype=torch.float32, device="cuda")
     rstd = torch.empty(n * groups, dtype=torch.float32, device="cuda")
     wmdec.gn_stats(x_dev, groups, eps, mean, rstd, ws)

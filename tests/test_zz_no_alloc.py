@@ -1,5 +1,5 @@
-"""The statistics entry point that allocates nothing: wmdec_gn_stats_noalloc keeps its partial moments and ticket
-counters in a device array built into the library.  Checked through the C ABI against wmdec_gn_stats (same kernels,
+"""The statistics entry point that allocates nothing: wmdec_gn_stats_noalloc keeps its partial moments in a device
+array built into the library.  Checked through the C ABI against wmdec_gn_stats (same kernels,
 hence the same bits) and the oracle, on two calls in a row, the second with a smaller input."""
 import numpy as np
 import pytest
@@ -26,7 +26,7 @@ def test_noalloc_matches_workspace_entry_point_on_two_calls_in_a_row():
     groups, eps = 32, 1e-6
     r = np.random.default_rng(synth.SEED_BASE + 500)
     # a large input first (many slabs, all 256 slots per group in use), then a smaller one of another layout, then
-    # a shape of the general (two-launch) path, then the large one again: the array keeps the last call's contents
+    # a shape of the general path, then the large one again: the array keeps the last call's contents
     shapes = [("f16", 2, 128, 240, 360), ("f16", 1, 256, 17, 23), ("bf16", 3, 24, 9, 11), ("f32", 1, 64, 32, 32),
               ("f16", 2, 128, 240, 360)]
     for dtype, n, c, h, w in shapes:
@@ -49,7 +49,7 @@ def test_noalloc_rejects_sizes_beyond_the_built_in_scratch():
     with pytest.raises(wmdec.WmdecError) as e:
         wmdec.gn_stats_noalloc(x, 96, 1e-6, mean, rstd)
     assert e.value.status == wmdec.ERR_WORKSPACE and "limit" in str(e.value)
-    # more samples than the 64 built-in ticket counters
+    # more than 64 samples
     x = torch.zeros((65, 2, 2, 32), dtype=torch.float16, device="cuda")
     with pytest.raises(wmdec.WmdecError) as e:
         wmdec.gn_stats_noalloc(x, 32, 1e-6, torch.zeros(65 * 32, device="cuda"), torch.zeros(65 * 32, device="cuda"))
