@@ -149,7 +149,7 @@ struct wmdec_decoder {
   int launches = 0;
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  bool ws_fresh = true;    // the statistics ticket counter of a newly set workspace has not been zeroed yet
+  bool ws_fresh = true;    // the ticket counters of a newly set workspace have not been zeroed yet
   bool profiling = false;
   int profiled_batch = 0;
   std::vector<hipEvent_t> events;   // steps.size() + 1 when profiling was ever enabled
@@ -347,7 +347,7 @@ static void fuse_stats_into_producers(wmdec_decoder& d) {
 
 // layout of the workspace for `batch` frames
 struct WsLayout {
-  size_t tickets, conv_tickets, conv_ticket_bytes, rows[2], act[3], qkv, attn_o, attn_scratch, mean, rstd, stats_ws, stats_ws_bytes, total;
+  size_t tickets, ticket_bytes, rows[2], act[3], qkv, attn_o, attn_scratch, mean, rstd, stats_ws, stats_ws_bytes, total;
 };
 static WsLayout ws_layout(const wmdec_decoder* d, int batch, size_t least_scratch = 0);
 
@@ -465,8 +465,7 @@ static WsLayout ws_layout(const wmdec_decoder* d, int batch, size_t least_scratc
   const size_t es = dtype_size(d->cfg.act_dtype);
   const size_t act = align_up(d->act_elems_per_frame * es * batch, 256);
   size_t o = 0;
-  L.tickets = o; o += gn_stats_ticket_bytes(d->cfg.max_batch);   // same place and size for every batch: zeroed once
-  // ticket counters (sized for max_batch, like the counters above: they are zeroed once per workspace and return to zero by themselves) and row
+  // ticket counters (same place and size for every batch: they are zeroed once per workspace and return to zero by themselves) and row
   // moments of the convolutions that hand their statistics over without a merge launch
   size_t max_tickets = 0, max_rows = 0;
   for (const Step& st : d->steps) {
@@ -477,8 +476,8 @@ static WsLayout ws_layout(const wmdec_decoder* d, int batch, size_t least_scratc
     if ((size_t)rows * ctiles > max_tickets) max_tickets = (size_t)rows * ctiles;
     if ((size_t)rows > max_rows) max_rows = rows;
   }
-  L.conv_ticket_bytes = align_up(max_tickets * d->cfg.max_batch * sizeof(unsigned), 256);
-  L.conv_tickets = o; o += L.conv_ticket_bytes;
+  L.ticket_bytes = align_up(max_tickets * d->cfg.max_batch * sizeof(unsigned), 256);
+  L.tickets = o; o += L.ticket_bytes;
   for (int i = 0; i < 2; ++i) { L.rows[i] = o; o += align_up(max_rows * batch * d->cfg.groups * 3 * sizeof(float), 256); }
   for (int i = 0; i < 3; ++i) { L.act[i] = o; o += act; }
   L.qkv = o; o += align_up(attention_fragment_bytes(batch, d->attn_t), 256);
@@ -970,7 +969,7 @@ static int launch_step(wmdec_decoder* dec, const WsLayout& L, const Step& st, co
         if (st.emit_stats) {
           (*emitted_slots) = conv_stats_slots(a);
           if ((*emitted_slots) > 0) a.stats_ws = st.emit_direct ? ws + L.rows[st.emit_rows] : ws + L.stats_ws;
-          if (st.emit_rows >= 0 && !st.emit_direct) { a.rows_out = ws + L.rows[st.emit_rows]; a.tickets = ws + L.conv_tickets; }
+          if (st.emit_rows >= 0 && !st.emit_direct) { a.rows_out = ws + L.rows[st.emit_rows]; a.tickets = ws + L.tickets; }
         }
         const Step* after = &st + 1;
         while (after < dec->steps.data() + dec->steps.size() && after->kind != Step::CONV) ++after;
@@ -1001,8 +1000,8 @@ static int run_graph(const char* who, wmdec_decoder* dec, const LatentSource& la
   WMDEC_REQUIRE(dec->ws && dec->ws_bytes >= L.total, WMDEC_ERR_WORKSPACE, "%s: workspace needs %zu bytes, has %zu", who, L.total, dec->ws_bytes);
   hipStream_t s = (hipStream_t)stream;
   char* ws = (char*)dec->ws;
-  if (dec->ws_fresh) {   // once per workspace: the ticket counter of the statistics kernel starts at zero
-    const int rc0 = launch_zero_u32(ws + L.tickets, (int)((gn_stats_ticket_bytes(dec->cfg.max_batch) + L.conv_ticket_bytes) / 4), s);
+  if (dec->ws_fresh) {   // once per workspace: the ticket counters start at zero
+    const int rc0 = L.ticket_bytes ? launch_zero_u32(ws + L.tickets, (int)(L.ticket_bytes / 4), s) : WMDEC_OK;
     if (rc0 != WMDEC_OK) return rc0;
     dec->ws_fresh = false;
   }

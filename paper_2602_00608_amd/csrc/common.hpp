@@ -156,7 +156,7 @@ int launch_conv(const ConvArgs& a, hipStream_t s);
 const char* conv_kernel_label(const ConvArgs& a);
 
 // kernels_gn.hip
-// gn_stats_ticket_bytes: the head of a caller's workspace, which no kernel uses any more;
+// gn_stats_ticket_bytes: the head of a caller's workspace, which no kernel touches;
 // moments: scratch of at least gn_stats_moments_bytes(n, groups) bytes
 size_t gn_stats_ticket_bytes(int n);
 size_t gn_stats_moments_bytes(int n, int groups);

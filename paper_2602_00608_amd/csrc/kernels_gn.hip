@@ -35,7 +35,7 @@ template <> struct alignas(16) Vec16<f16_t> { static constexpr int N = 8; f16_t 
 // 128 channels 480x720 23.1 / 19.9, four of them 71.5 / 65.6; f32 512 channels 60x90 11.6 / 8.1, 120x180 17.3 / 12.5, 128 channels 480x720 39.8 / 37.6.
 constexpr int kVecThreads = 1024;
 constexpr int kVecMaxChunks = 256;
-constexpr int kVecMaxGroups = 256;
+constexpr int kVecMaxGroups = 256;    // (more take the general pass; no level of a decoder has them)
 
 // MIX: of f16, conversion and shift are one instruction (v_fma_mix_f32; the compiler makes it if it does not see that the factor is 1).
 template <typename T, int V, bool MASKED, int U = 8, bool MIX = false>
@@ -409,8 +409,7 @@ int launch_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int 
   return launch_general(x, x_dtype, n, pixels, c, groups, p.chunks, p.chunk_pixels, eps, mean, rstd, wsm, s);
 }
 
-// The general path in at most max_slabs slabs, for callers whose workspace holds that many triples per (sample, group) and
-// no ticket counters.
+// The general path in at most max_slabs slabs, for callers whose workspace holds that many triples per (sample, group).
 int launch_gn_stats_small_ws(const void* x, int x_dtype, int n, int h, int w, int c, int groups, float eps, float* mean,
                              float* rstd, void* moments, int max_slabs, hipStream_t s) {
   const int pixels = h * w;
@@ -420,7 +419,7 @@ int launch_gn_stats_small_ws(const void* x, int x_dtype, int n, int h, int w, in
 }
 
 // ---- the variant for callers that cannot allocate: the workspace is a file-scope device array
-constexpr size_t kStaticTicketBytes = 256;                 // a head of four bytes a sample, as in a caller's workspace: at most 64 of them
+constexpr size_t kStaticTicketBytes = 256;                 // a head of four bytes a sample, as in a caller's workspace: the interface takes at most 64
 constexpr size_t kStaticMomentsBytes = (size_t)1 << 20;    // 87381 moment triples
 static __device__ __align__(256) unsigned char scratch[kStaticTicketBytes + kStaticMomentsBytes];
 
