@@ -22,7 +22,9 @@ extern "C" {
  * the attention core).  decoder_step_info gives, for step `index`, the name of
  * the kernel that executes it in a run of one frame (for convolutions the template
  * instantiation as a profiler prints it; batches may take another tile of the same
- * sums; the string is valid until the thread's next call) and
+ * sums; for a statistics pass the kernel that reads the tensor, behind which
+ * gn_finalize may merge what its workgroups left; the string is valid until the
+ * thread's next call) and
  * its algorithmic FLOPs and HBM bytes per frame (every input, residual, output
  * and weight tensor counted once: the Eq. 9 accounting).  decoder_step_times
  * waits for the last profiled decoder_run and returns the elapsed milliseconds

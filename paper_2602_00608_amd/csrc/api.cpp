@@ -1096,7 +1096,7 @@ int decoder_step_info(const wmdec_decoder* dec, int index, const char** kernel, 
   if (bytes) *bytes = st.bytes;
   if (kernel) {
     switch (st.kind) {
-      case Step::STATS: *kernel = st.from_producer ? "gn_finalize" : "gn_stats_vec"; break;   // (the pass over a tensor, in either form)
+      case Step::STATS: *kernel = st.from_producer ? "gn_finalize" : gn_stats_label(dec->cfg.act_dtype, st.h, st.w, st.cin, dec->cfg.groups); break;
       case Step::FLASH: *kernel = "flash_attn_kernel"; break;
       case Step::NONE: *kernel = ""; break;
       case Step::CONV: {

@@ -161,6 +161,7 @@ const char* conv_kernel_label(const ConvArgs& a);
 size_t gn_stats_ticket_bytes(int n);
 size_t gn_stats_moments_bytes(int n, int groups);
 int gn_stats_num_launches(int x_dtype, int h, int w, int c, int groups);   // 2: partial + merge
+const char* gn_stats_label(int x_dtype, int h, int w, int c, int groups);  // the kernel that reads the tensor
 int launch_gn_stats(const void* x, int x_dtype, int n, int h, int w, int c, int groups, float eps,
                     float* mean, float* rstd, void* moments, size_t moments_bytes, hipStream_t s);
 

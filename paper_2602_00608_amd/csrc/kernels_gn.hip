@@ -365,6 +365,11 @@ int gn_stats_num_launches(int x_dtype, int h, int w, int c, int groups) {
   return p.columns || (p.vec && p.chunks == 1) ? 1 : 2;
 }
 
+const char* gn_stats_label(int x_dtype, int h, int w, int c, int groups) {
+  const Plan p = make_plan(x_dtype, 1, h, w, c, groups);
+  return p.columns ? "gn_stats_columns" : p.vec ? "gn_stats_vec" : "gn_partial_any";
+}
+
 static int launch_general(const void* x, int x_dtype, int n, int pixels, int c, int groups, int slabs, int slab_pixels, float eps,
                           float* mean, float* rstd, Moments* wsm, hipStream_t s) {
   dim3 grid((unsigned)slabs, (unsigned)groups, (unsigned)n);

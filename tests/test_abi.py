@@ -118,7 +118,7 @@ def test_step_accounting_adds_up():
     # (conv_in, the 60x90 and 120x180 layers: 22 normalisations) the consumer's prologue merges either the producer's triples
     # themselves (few tiles) or what its last workgroup per tile row merged; the 8 producers of several rounds (240x360,
     # 480x720) keep a small merge launch.
-    assert sum(1 for k, _, _ in info if k == "gn_stats_vec") == 0 and sum(1 for k, _, _ in info if k == "gn_finalize") == 8
+    assert sum(1 for k, _, _ in info if k.startswith(("gn_stats", "gn_partial"))) == 0 and sum(1 for k, _, _ in info if k == "gn_finalize") == 8
     cfg = wmdec.decoder_default_config()
     cfg.separate_merge_launch = 1
     d2 = wmdec.Decoder(cfg)
@@ -165,7 +165,27 @@ def test_convolution_of_few_normalised_channels_leaves_no_moments():
     cfg.level_channels[0], cfg.level_channels[1], cfg.level_channels[2] = 512, 8, 64
     dec = wmdec.Decoder(cfg)
     kernels = [k for k, _, _ in dec.step_info()]
-    assert kernels[-7:-2] == ["gn_stats_vec", "conv_direct_kernel", "conv_direct_kernel", "gn_stats_vec", "conv_ksplit_kernel<wmdec::f16_t, 4, 8, 1, 1, 4, 2, 2, 2>"], kernels
+    assert kernels[-7:-2] == ["gn_stats_vec", "conv_direct_kernel", "conv_direct_kernel", "gn_stats_columns", "conv_ksplit_kernel<wmdec::f16_t, 4, 8, 1, 1, 4, 2, 2, 2>"], kernels
+    dec.close()
+
+
+def test_statistics_passes_are_named_by_the_kernel_that_reads_the_tensor():
+    """Every normalisation with a pass of its own: up to 4096 pixels whole groups of 64 bytes by one workgroup, larger images and other channel counts in
+    slabs of whole pixels (and a merge where there are several), channel counts that do not divide 1024 vectors by the general kernel."""
+    cfg = wmdec.decoder_default_config()
+    cfg.latent_h = cfg.latent_w = 32
+    cfg.num_levels, cfg.resblocks_per_level, cfg.separate_stats_pass, cfg.groups = 3, 1, 1, 8
+    cfg.level_channels[0], cfg.level_channels[1], cfg.level_channels[2] = 512, 96, 16
+    dec = wmdec.Decoder(cfg)
+    kernels = [k for k, _, _ in dec.step_info() if k.startswith("gn_")]
+    # 512 channels (64 a group: more than 64 bytes) at 32x32 seven times and at 64x64, 96 at 64x64 and at 128x128, 16 at 128x128 twice
+    assert kernels == ["gn_stats_vec"] * 8 + ["gn_partial_any"] * 2 + ["gn_stats_vec"] * 2, kernels
+    dec.close()
+    cfg.groups = 32
+    cfg.level_channels[1], cfg.level_channels[2] = 128, 64
+    dec = wmdec.Decoder(cfg)
+    kernels = [k for k, _, _ in dec.step_info() if k.startswith("gn_")]
+    assert kernels == ["gn_stats_columns"] * 9 + ["gn_stats_vec"] * 3, kernels
     dec.close()
 
 
