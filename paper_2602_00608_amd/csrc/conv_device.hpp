@@ -164,8 +164,9 @@ template <typename T, int ACT, bool PIN = false> __device__ __forceinline__ uint
   return wv;
 }
 
-// 1 / sqrt(m2 / n + eps) to three quarters of an ulp, without the compiler's division and square root (which round twice, and are some
-// fifty dependent instructions a launch waits for) unless the variance leaves the range where the steps below are exact enough.
+// 1 / sqrt(m2 / n + eps) without the compiler's division and square root (some fifty dependent instructions a launch waits for) unless the variance
+// leaves the range where the steps below are exact enough.  One ulp given v, two in all; by division and square root, which round twice, it is 1.5 and 2.3
+// (four million draws each, eps 0, 1e-6 and 0.3, starting values an ulp off).
 __device__ __forceinline__ float inverse_deviation(float m2, float n, float eps) {
   const float v = quotient(m2, n, __builtin_amdgcn_rcpf(n)) + eps;
   float r = __builtin_amdgcn_rsqf(v);
