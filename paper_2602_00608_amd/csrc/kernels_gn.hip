@@ -318,7 +318,8 @@ int pick_chunks(int pixels, int c, int V, bool vec) {
 
 // Images of up to so many pixels take gn_stats_columns.  us, gn_stats_vec with its merge / columns, inputs from beyond the L2s: f16 256 channels two 61x47 8.7 / 8.0, 128 channels 68x68
 // 8.7 / 8.6; past the line 60x90 of 512 9.0 / 12.7, 80x100 9.4 / 14.3; far below it 512 channels 17x23 take 4.9 in columns, 32x32 5.0, 45x60 8.7, f32 64 channels 32x32 4.3,
-// where a merging launch alone is 2.3.  (Not a function of the batch: a sample's result must not depend on its
+// where a merging launch alone is 2.3.  Groups of one 16-bit channel, eight chains of lane moves a lane, stay with gn_stats_vec where one workgroup streams the sample and no merge follows:
+// 64 channels at 6x6 4.9 / 6.2, 32x32 5.8 / 6.9, 32 channels at 64x64 8.2 / 8.9; beyond, 64 at 48x48 10.6 / 8.3.  (Not a function of the batch: a sample's result must not depend on its
 // neighbours.)
 constexpr int kColPixels = 4096;
 
@@ -339,7 +340,7 @@ Plan make_plan(int x_dtype, int n, int h, int w, int c, int groups) {
     p.chunk_pixels = ((p.chunk_pixels + ppi - 1) / ppi) * ppi;
   }
   p.chunks = (pixels + p.chunk_pixels - 1) / p.chunk_pixels;
-  p.columns = p.vec && pixels <= kColPixels && c % (kColVecs * V) == 0 && cpg <= kColVecs * V;
+  p.columns = p.vec && pixels <= kColPixels && c % (kColVecs * V) == 0 && cpg <= kColVecs * V && !(V == 8 && cpg == 1 && p.chunks == 1);
   return p;
 }
 

@@ -187,6 +187,13 @@ def test_statistics_passes_are_named_by_the_kernel_that_reads_the_tensor():
     kernels = [k for k, _, _ in dec.step_info() if k.startswith("gn_")]
     assert kernels == ["gn_stats_columns"] * 9 + ["gn_stats_vec"] * 3, kernels
     dec.close()
+    # groups of one 16-bit channel: one workgroup for the sample while its channels come to 131072 values, columns beyond
+    cfg.groups, cfg.num_levels, cfg.level_channels[1] = 64, 2, 64
+    for w, name in ((16, "gn_stats_vec"), (17, "gn_stats_columns")):
+        cfg.latent_h, cfg.latent_w = 32, w
+        dec = wmdec.Decoder(cfg)
+        assert [k for k, _, _ in dec.step_info() if k.startswith("gn_")][-2:] == [name] * 2
+        dec.close()
 
 
 def test_layers_that_hand_rows_over_are_named_by_the_tile_they_launch():

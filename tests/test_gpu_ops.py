@@ -44,9 +44,10 @@ def test_gn_stats(dtype, n, c, h, w, groups):
 
 
 # images of up to 4096 pixels with whole groups in 64 bytes of a pixel: one pixel, fewer than the 16 wavefronts' 256 rows, a remainder behind four sweeps of
-# them, both sides of the line, group sizes from one channel to 64 bytes; and a group of 128 bytes, which the other kernel takes
+# them, both sides of the line, group sizes from one channel to 64 bytes; and a group of 128 bytes and groups of one 16-bit channel in one slab, which the other kernel takes
 @pytest.mark.parametrize("dtype,n,c,h,w,groups", [("f32", 1, 16, 1, 1, 16), ("bf16", 3, 32, 15, 17, 1), ("f16", 2, 64, 16, 16, 32), ("f16", 1, 64, 1, 257, 64), ("f32", 2, 32, 41, 25, 8),
-                                                  ("bf16", 1, 256, 25, 41, 64), ("f32", 1, 1024, 3, 7, 64), ("f16", 2, 128, 64, 64, 32), ("f16", 2, 128, 1, 4097, 32), ("bf16", 1, 512, 23, 17, 8)])
+                                                  ("bf16", 1, 256, 25, 41, 64), ("f32", 1, 1024, 3, 7, 64), ("f16", 2, 128, 64, 64, 32), ("f16", 2, 128, 1, 4097, 32), ("bf16", 1, 512, 23, 17, 8),
+                                                  ("f16", 2, 64, 32, 64, 64), ("bf16", 2, 64, 1, 2049, 64), ("f16", 1, 256, 27, 31, 256)])
 def test_gn_stats_of_small_images(dtype, n, c, h, w, groups):
     """A sample's result is its own bit for bit; errors: a thread sums at most 16 pixels, then some ten levels of merges, each rounded once: 26 * 2^-24 = 1.6e-6."""
     x = G.stored(rng(8).standard_normal((n, c, h, w)) * 1.7 + 0.6, dtype)
