@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
   };
   // Two steps of weights come first; a whole chunk of them (RING) behind input and moments, which are needed before them: loads return in order, and
   // it is a thousand cycles of a compute unit's load path.
-  if constexpr (RING == 0) first_weights();
+  if constexpr (RING == 0 || ACT == 0) first_weights();
 
   // ---- staging: a thread owns NV (pixel, channel-octet) vectors of the halo patch; the octet is the same for all.
   // Zero padding without per-element work: a vector outside the image is loaded from pixel 0 (a load under a lane
@@ -423,7 +423,6 @@ __global__ __launch_bounds__(256, resident_workgroups(TH, NI, RING)) void conv_m
       }
     }
   }
-  if constexpr (RING > 0 && ACT == 0) first_weights();
   __syncthreads();            // scale/shift table complete
   auto table = [&](const float2* tab, int part) -> f32x4 {   // entries of word `part` of the thread's octet
     if constexpr (ACT > 0) return *reinterpret_cast<const f32x4*>(tab + 2 * part);
