@@ -353,8 +353,8 @@ static WsLayout ws_layout(const wmdec_decoder* d, int batch, size_t least_scratc
 
 // fuse_stats_into_producers with the tiles of six rows, if the workspace stays within what it has been without them: a caller may keep the figure.  It was
 // the row buffers with the triples of eight rows and scratch for any statistics pass (2048 triples); a plan without such a pass has less scratch, which
-// nearly always holds what six rows add to the row buffers (all latents from 5x5 to 66x99 of four level lists).  Otherwise every layer that leaves moments stays with
-// eight rows (the outputs are the same).
+// nearly always holds what six rows add to the row buffers (of the 6365 latents from 5x5 to 71x99 all but 16 with the default levels).  Otherwise every layer that leaves
+// moments stays with eight rows.
 static void fuse_stats(wmdec_decoder& d) {
   const std::vector<Step> steps = d.steps;
   const int launches = d.launches;

@@ -761,7 +761,8 @@ bool wide_channels(const ConvArgs& a) {
 // where the estimate says eight: 512 channels 62x90 27.6 / 37.9, 90x160 54.8 / 63.1, eight samples of 60x90 152.6 / 158.3; 128 channels 136x184 10.5 / 13.0, 240x360 24.7 / 26.6.
 // Which layers may change their height is a function of the sample alone (its moments depend on it): those that gain at one sample, of at most two rounds (120x180 of
 // 512 channels: 83.1 / 80.8, which larger batches would lose again), from 128 input channels on and not widening, where the products outweigh the fixed parts.
-// Layers with fp32 output or rows merged by the launch itself stay with eight rows, and so do a decoder's whose consumer can read the fewer triples of eight rows only.
+// Layers with fp32 output stay with eight rows, and so do a decoder's that leave moments where the launch merges its rows itself (256 channels at 120x180), where their consumer can read
+// the fewer triples of eight rows only (512 channels at 72x128, 80x100, 90x120) or where the workspace would grow (see fuse_stats), and a caller's whose workspace holds those of eight.
 // What the second triple of a tile costs the eight-row forms: ResBlocks of 512 channels at 60x90, eight samples, 329.5 -> 332, 128 channels at 160x200, three, 81.2 -> 82.8;
 // with six rows, one sample, 512 channels at 60x90 67.5 -> 65.9, 54x80 70.0 -> 61.3, 90x120 113.5 -> 107.1, 512 -> 256 at 100x100 62.3 -> 60.0, 128 at 160x200 46.8 -> 43.7.
 struct TileCost { int cost; bool wide; };
