@@ -27,20 +27,20 @@ __host__ __device__ constexpr int six_eight_rows_left(int row) {
 
 // Moments of a wavefront's stored values in the making: per channel of the lane (CH neighbouring ones) shifted sums over n pixels.
 template <int CH> struct LaneMoments { float n, shift[CH], s[CH], q[CH]; };
+struct RelMoments { float n, mean, m2, about; };   // (the mean lacks `about`)
 
 // ... merged per group and written, N of them side by side (each is a chain of dependent lane moves).  A lane merges its channels of a
 // group (PARTS groups, or its part of a larger one), then the lanes that hold the same channels, and those of the group's other
 // channels, are summed in the vector ALU (lanes): the mean first,
 // then the squares about it.  (Through LDS, with a lane per channel that walked the others' sums and re-centred them one by
 // one, this was 13 of the 122 us of 128 -> 128 channels at 480x720, and 1.5 of 36 at 60x90.)  co: the lane's first channel; writes: whether
-// it is the lane that writes its groups; SOME: dst is null where there are none; all_n: pixels times lanes of a group where that is known, otherwise 0; WIDE: values up to
-// the end of fp32's range (lane `head` holds the group's first channels, of pixels if there are any): means are summed as differences to that lane's and in 1024ths of a pixel, up to 1024
-// pixels times lanes, so that sums of them stay in range and nothing deviates from the mean of equal values.
-template <int CH, int PARTS, bool SOME, bool WIDE = false, int N, typename Lanes>
-__device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Moments* const (&dst)[N], int co, bool writes, int cpg, int stats_stride, bool handed_over,
-                                             float all_n, Lanes&& lanes, int head = 0) {
+// it is the lane that writes its groups; SOME: dst is null where there are none; all_n: pixels times lanes of a group where that is known, otherwise 0; REL: for lanes of few
+// pixels.  Means, and the one written, are differences to that of one lane where the values lie far from zero (from_lane chooses, the same for all lanes that are summed): a few pixels' own mean is
+// rounded at its exponent, which the squares about the group's mean would count.
+template <int CH, int PARTS, bool SOME, bool REL = false, int N, typename Out, typename Lanes, typename Lane>
+__device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Out* const (&dst)[N], int co, bool writes, int cpg, int stats_stride, bool handed_over,
+                                             float all_n, Lanes&& lanes, Lane&& from_lane) {
   constexpr int PC = CH / PARTS;
-  constexpr float kUnit = WIDE ? 0x1p-10f : 1.f;
   float inv[N], n[N], ninv[N];
 #pragma unroll
   for (int k = 0; k < N; ++k) {
@@ -50,32 +50,28 @@ __device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Mom
   }
 #pragma unroll
   for (int g = 0; g < PARTS; ++g) {
-    float m[N], q[N], dev[N], mid[N], rest[N];
+    float m[N], q[N], dev[N], mid[N], rest[N], about[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) {
       float mean[PC];
-      m[k] = 0.f; q[k] = 0.f; dev[k] = 0.f;
+      m[k] = 0.f; q[k] = 0.f; dev[k] = 0.f; about[k] = 0.f;
+      if constexpr (REL) about[k] = from_lane(st[k].n > 0.f ? fmaf(st[k].s[g * PC], inv[k], st[k].shift[g * PC]) : __builtin_inff());
 #pragma unroll
       for (int e = 0; e < PC; ++e) {
         const int c = g * PC + e;
         const float ds = quotient(st[k].s[c], st[k].n, inv[k]), m2 = st[k].q[c] - st[k].s[c] * ds;
-        mean[e] = st[k].shift[c] + ds;
-        m[k] += WIDE ? mean[e] * (1.f / PC) : mean[e];
+        mean[e] = REL ? (st[k].shift[c] - about[k]) + ds : st[k].shift[c] + ds;
+        m[k] += mean[e];
         q[k] += m2 < 0.f ? 0.f : m2;     // (NaN stays NaN)
       }
-      m[k] = st[k].n > 0.f ? (WIDE ? m[k] : m[k] * (1.f / PC)) : 0.f;     // the shift of a lane without pixels has no meaning
+      m[k] = st[k].n > 0.f ? m[k] * (1.f / PC) : 0.f;     // the shift of a lane without pixels has no meaning
 #pragma unroll
       for (int e = 0; e < PC; ++e) { const float d = mean[e] - m[k]; dev[k] = fmaf(d, d, dev[k]); }
     }
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-      if constexpr (WIDE) {
-        const float first = __shfl(m[k], head);
-        mid[k] = first + lanes(st[k].n * kUnit * (m[k] - first)) * (ninv[k] * (1.f / kUnit));
-      } else mid[k] = lanes(st[k].n * m[k]) * ninv[k];
-    }
+    for (int k = 0; k < N; ++k) mid[k] = lanes(st[k].n * m[k]) * ninv[k];
 #pragma unroll
-    for (int k = 0; k < N; ++k) rest[k] = lanes(st[k].n * kUnit * (m[k] - mid[k])) * (ninv[k] * (1.f / kUnit));       // what the roundings of mid left
+    for (int k = 0; k < N; ++k) rest[k] = REL ? 0.f : lanes(st[k].n * (m[k] - mid[k])) * ninv[k];       // what the roundings of mid left (nothing of a difference)
 #pragma unroll
     for (int k = 0; k < N; ++k) {
       const float d = m[k] - mid[k], nd = st[k].n * d;
@@ -85,18 +81,21 @@ __device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Mom
 #pragma unroll
       for (int k = 0; k < N; ++k) {
         if (SOME && !dst[k]) continue;
-        const Moments out{n[k] * PC, mid[k] + rest[k], q[k] < 0.f ? 0.f : q[k]};
-        Moments* at = dst[k] + (size_t)((co + g * PC) / cpg) * stats_stride;
-        if (handed_over) store_device(at, out);   // another workgroup of this launch may merge them, see the row hand-over of the kernels
-        else *at = out;
+        Out* at = dst[k] + (size_t)((co + g * PC) / cpg) * stats_stride;
+        if constexpr (REL) *at = RelMoments{n[k] * PC, mid[k] + rest[k], q[k] < 0.f ? 0.f : q[k], about[k]};
+        else {
+          const Moments out{n[k] * PC, mid[k] + rest[k], q[k] < 0.f ? 0.f : q[k]};
+          if (handed_over) store_device(at, out);   // another workgroup of this launch may merge them, see the row hand-over of the kernels
+          else *at = out;
+        }
       }
     }
   }
 }
 
 // Lane l holds vector l % VECTORS of the wavefront's channels, CH of them each.
-template <int VECTORS, int CH, bool WIDE = false>
-__device__ __forceinline__ void emit_vectors(const LaneMoments<CH> (&st)[1], int lane, int co_w, Moments* const (&dst)[1], int cpg, int stats_stride, bool handed_over) {
+template <int VECTORS, int CH, bool REL = false, typename Out>
+__device__ __forceinline__ void emit_vectors(const LaneMoments<CH> (&st)[1], int lane, int co_w, Out* const (&dst)[1], int cpg, int stats_stride, bool handed_over) {
   static_assert(CH == 4 || CH == 8, "16 bytes");
   auto lanes = [&](float v) {
     if constexpr (VECTORS <= 4) v += row_rotate<4>(v);
@@ -107,12 +106,18 @@ __device__ __forceinline__ void emit_vectors(const LaneMoments<CH> (&st)[1], int
     return v;
   };
   const int co = co_w + lane * CH;
-  const int head = lane % VECTORS & ~(max(cpg / CH, 1) - 1);
+  // of a channel's mean in two lanes that are half a wavefront apart the one nearer to zero, if it is far from zero for how far they are from each other; otherwise there is nothing to take off, or
+  // one of them has an outlier among its pixels
+  auto from_lane = [&](float v) {
+    const int head = lane % VECTORS & ~(max(cpg / CH, 1) - 1);   // the lanes of the group's first channels
+    const float low = __shfl(v, head), high = __shfl(v, head + 32), near = fabsf(low) <= fabsf(high) ? low : high;
+    return fabsf(near) > 8.f * fabsf(low - high) || fabsf(high) == __builtin_inff() ? near : 0.f;   // (infinite: a lane without pixels)
+  };
   const bool writes = lane < VECTORS && ((lane * CH) & (cpg - 1)) == 0;
-  if (cpg >= CH) emit_moments<CH, 1, false, WIDE>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, head);
-  else if (cpg == CH / 2) emit_moments<CH, 2, false, WIDE>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, head);
-  else if (cpg == CH / 4) emit_moments<CH, 4, false, WIDE>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, head);
-  else if constexpr (CH == 8) emit_moments<8, 8, false, WIDE>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, head);
+  if (cpg >= CH) emit_moments<CH, 1, false, REL>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, from_lane);
+  else if (cpg == CH / 2) emit_moments<CH, 2, false, REL>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, from_lane);
+  else if (cpg == CH / 4) emit_moments<CH, 4, false, REL>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, from_lane);
+  else if constexpr (CH == 8) emit_moments<8, 8, false, REL>(st, dst, co, writes, cpg, stats_stride, handed_over, 0.f, lanes, from_lane);
 }
 
 // Lane l holds channels 2 (l % 16) and the next of 32, of the pixels of quarter l / 16; full: all lanes hold the same number of them.
@@ -125,7 +130,7 @@ __device__ __forceinline__ void emit_pairs(const LaneMoments<2> (&st)[N], bool f
       v = swap_sum<32>(swap_sum<16>(v));
       return lane_group_sum<WIDTH>(v);
     };
-    emit_moments<2, PARTS, (N > 1)>(st, dst, co_w + 2 * (lane & 15), lane < 16 && lane % WIDTH == 0, CPG, stats_stride, handed_over, full ? st[0].n * (4.f * WIDTH) : 0.f, lanes);
+    emit_moments<2, PARTS, (N > 1)>(st, dst, co_w + 2 * (lane & 15), lane < 16 && lane % WIDTH == 0, CPG, stats_stride, handed_over, full ? st[0].n * (4.f * WIDTH) : 0.f, lanes, [](float v) { return v; });
   };
   if (cpg == 16) emit(std::integral_constant<int, 16>{});
   else if (cpg == 8) emit(std::integral_constant<int, 8>{});

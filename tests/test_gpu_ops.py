@@ -97,6 +97,19 @@ def test_gn_stats_with_an_outlier_first_pixel(c, h, w):
     assert np.max(np.abs(mean.cpu().numpy() - wm.ravel()) * wr.ravel()) < 5e-7
 
 
+@pytest.mark.parametrize("dtype,c,h,w,mean,std", [("f16", 512, 54, 24, 37.0, 0.01), ("f16", 256, 61, 47, 100.0, 0.01), ("f16", 64, 33, 9, 1000.0, 1.0), ("bf16", 512, 54, 24, 1000.0, 1.0),
+                                                  ("bf16", 128, 47, 24, 100.0, 0.1), ("f32", 512, 17, 23, 100.0, 0.01), ("f32", 64, 32, 32, -1000.0, 0.3)])
+def test_gn_stats_of_few_pixels_a_lane_far_from_zero(dtype, c, h, w, mean, std):
+    """Means of five or six pixels, rounded at the values' exponent, would stand in the squares about the group's mean (the quantised values of 16 bits make the same error again and
+    again): what counts are differences, as exact as where the mean is zero (1.6e-6 there, see test_gn_stats_of_small_images), and the mean is rounded once."""
+    x = G.stored(rng(9).standard_normal((1, c, h, w)) * std + mean, dtype)
+    m, r = G.gn_stats(G.dev_nhwc(x, dtype), 32, 0.0)
+    v = x.astype(np.float64).reshape(32, -1)
+    wm, wr = v.mean(1), 1.0 / v.std(1)
+    assert np.max(np.abs(r.cpu().numpy() / wr - 1.0)) < 1.6e-6
+    assert np.max(np.abs(m.cpu().numpy() - wm) - np.abs(wm) * 2.0 ** -23) * np.max(wr) < 1.6e-6
+
+
 # Small images (one workgroup's columns), one workgroup, and several with a merge; groups of one to 64 bytes of a pixel.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("c,groups,h,w", [(64, 32, 32, 32), (64, 64, 64, 64), (128, 8, 1, 1), (64, 4, 5, 7), (8, 4, 3, 5), (64, 8, 120, 180)])
