@@ -48,19 +48,25 @@ __device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Out
     n[k] = all_n > 0.f ? all_n : lanes(st[k].n);
     ninv[k] = n[k] > 0.f ? __builtin_amdgcn_rcpf(n[k]) : 0.f;   // 1 ulp: `rest` corrects the mean
   }
+  float about[PARTS][N];
+  if constexpr (REL) {
+#pragma unroll
+    for (int g = 0; g < PARTS; ++g)   // (of all groups at once: what the lanes are asked for is under way together)
+#pragma unroll
+      for (int k = 0; k < N; ++k) about[g][k] = from_lane(st[k].n > 0.f ? fmaf(st[k].s[g * PC], inv[k], st[k].shift[g * PC]) : __builtin_inff());
+  }
 #pragma unroll
   for (int g = 0; g < PARTS; ++g) {
-    float m[N], q[N], dev[N], mid[N], rest[N], about[N];
+    float m[N], q[N], dev[N], mid[N], rest[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) {
       float mean[PC];
-      m[k] = 0.f; q[k] = 0.f; dev[k] = 0.f; about[k] = 0.f;
-      if constexpr (REL) about[k] = from_lane(st[k].n > 0.f ? fmaf(st[k].s[g * PC], inv[k], st[k].shift[g * PC]) : __builtin_inff());
+      m[k] = 0.f; q[k] = 0.f; dev[k] = 0.f;
 #pragma unroll
       for (int e = 0; e < PC; ++e) {
         const int c = g * PC + e;
         const float ds = quotient(st[k].s[c], st[k].n, inv[k]), m2 = st[k].q[c] - st[k].s[c] * ds;
-        mean[e] = REL ? (st[k].shift[c] - about[k]) + ds : st[k].shift[c] + ds;
+        mean[e] = REL ? (st[k].shift[c] - about[g][k]) + ds : st[k].shift[c] + ds;
         m[k] += mean[e];
         q[k] += m2 < 0.f ? 0.f : m2;     // (NaN stays NaN)
       }
@@ -82,7 +88,7 @@ __device__ __forceinline__ void emit_moments(const LaneMoments<CH> (&st)[N], Out
       for (int k = 0; k < N; ++k) {
         if (SOME && !dst[k]) continue;
         Out* at = dst[k] + (size_t)((co + g * PC) / cpg) * stats_stride;
-        if constexpr (REL) *at = RelMoments{n[k] * PC, mid[k] + rest[k], q[k] < 0.f ? 0.f : q[k], about[k]};
+        if constexpr (REL) *at = RelMoments{n[k] * PC, mid[k] + rest[k], q[k] < 0.f ? 0.f : q[k], about[g][k]};
         else {
           const Moments out{n[k] * PC, mid[k] + rest[k], q[k] < 0.f ? 0.f : q[k]};
           if (handed_over) store_device(at, out);   // another workgroup of this launch may merge them, see the row hand-over of the kernels

@@ -161,7 +161,7 @@ template <int LANES> __device__ __forceinline__ float2 merge_lanes(const Moments
 
 // Columns: a workgroup takes 64 bytes of every pixel of a sample, whole groups, and needs nothing from the others.  A thread sums the channels of
 // its vector shifted by its first pixel, the lanes of a wavefront are merged as in the convolutions' epilogues, where they lie far from zero by their means' differences to one lane's (a lane has a few
-// pixels: at 54x24, f16 of 37 +- 0.01, rstd was wrong by 2e-5, now 8e-8; us, before / now, f32 64 channels at 32x32 3.28 / 3.31, f16 512 at 17x23 4.47 / 4.49), the 16 wavefronts' triples of a
+// pixels: at 54x24, f16 of 37 +- 0.01, rstd was wrong by 2e-5, now 8e-8; us, before / now, f32 64 channels at 32x32 3.25 / 3.27, f16 512 at 17x23 4.50 / 4.53), the 16 wavefronts' triples of a
 // group by 16 lanes.  Few compute units stream it, each bound by latency and conversions (four vectors in flight a thread: eight or sixteen are slower, as are 32 bytes
 // a pixel), so it is for images of few pixels, where the launch that merges the triples of gn_stats_vec takes longer.
 constexpr int kColThreads = 1024, kColVecs = 4;
